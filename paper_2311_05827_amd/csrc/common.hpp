@@ -277,14 +277,24 @@ __device__ __forceinline__ double load_device_scope(const double* p) {
   return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-// u in [0,1) on a 2^-24 grid: top 24 bits of splitmix64's output function at
-// seed + (idx+1) * 0x9E3779B97F4A7C15.
-__device__ __forceinline__ float counter_uniform(uint64_t seed, uint64_t idx) {
-  uint64_t z = seed + (idx + 1ull) * 0x9E3779B97F4A7C15ull;
+// Counter-based uniform numbers: element idx gets u = (top 24 bits of h) * 2^-24, h = splitmix64's
+// output function at the state z = seed + (idx+1) * kRandStep.  States of neighbouring elements
+// differ by a constant, so a kernel forms one state per thread and adds from there.
+constexpr uint64_t kRandStep = 0x9E3779B97F4A7C15ull;
+__device__ __forceinline__ uint64_t rand_state(uint64_t seed, uint64_t idx) { return seed + (idx + 1ull) * kRandStep; }
+
+// u * 2^32 as a float32 (exact: 24 significant bits).  Written on 32-bit halves: the output
+// function's last step z ^ (z >> 31) leaves the top 31 bits as they are, so only the high word of
+// the second product is formed, and a 64-bit source would be converted to float by a sequence of
+// seven instructions where one does.
+__device__ __forceinline__ float rand_u32(uint64_t z) {
   z = (z ^ (z >> 30)) * 0xBF58476D1CE4E5B9ull;
-  z = (z ^ (z >> 27)) * 0x94D049BB133111EBull;
-  z = z ^ (z >> 31);
-  return float(uint32_t(z >> 40)) * 0x1p-24f;
+  z ^= z >> 27;
+  constexpr uint64_t C2 = 0x94D049BB133111EBull;
+  const uint32_t lo = uint32_t(z), hi = uint32_t(z >> 32);
+  uint32_t h = __umulhi(lo, uint32_t(C2)) + lo * uint32_t(C2 >> 32) + hi * uint32_t(C2);
+  h &= 0xFFFFFF00u;
+  return float(h);
 }
 
 #endif  // __HIPCC__

@@ -363,34 +363,49 @@ __global__ __launch_bounds__(kWave) void range_finalize_kernel(const float* __re
 }
 
 // =========================================================================== quantize (U2)
-// One element: v = x * r (one float32 multiply), round, clamp, offset to a k-bit code.
-template <int K, bool STOCH>
-__device__ __forceinline__ uint32_t quantize1(float f, float r, uint64_t seed, int64_t idx) {
+// One element, round half to even: v = x * r (one float32 multiply), round, clamp, offset to a
+// k-bit code.
+template <int K>
+__device__ __forceinline__ uint32_t quantize_rne(float f, float r) {
   constexpr int HALF = 1 << (K - 1);
   constexpr uint32_t MASK = (1u << K) - 1u;
   const float v = __fmul_rn(f, r);
-  if (!STOCH) {
-    // Round half to even through the magic-number add.  |v| <= L(1 + 2^-23), so the rounded
-    // value lies in [-L, L] and the clamp of the definition never binds; the mask only keeps
-    // codes of non-finite inputs inside their k bits.  The sum's low mantissa bits are
-    // q + HALF (k < 8) or q mod 256 (k = 8).
-    const float t = __fadd_rn(v, kRoundMagic + float(K == 8 ? 0 : HALF));
-    return f32_as_u32(t) & MASK;
-  }
-  const float fl = floorf(v);
-  const float pr = __fsub_rn(v, fl);  // exact
-  const float u = counter_uniform(seed, uint64_t(idx));
-  int q = int(fl) + (u < pr ? 1 : 0);
-  q = min(max(q, -HALF), HALF - 1);
-  return (K == 8) ? (uint32_t(q) & 0xFFu) : uint32_t(q + HALF);
+  // Round half to even through the magic-number add.  |v| <= L(1 + 2^-23), so the rounded
+  // value lies in [-L, L] and the clamp of the definition never binds; the mask only keeps
+  // codes of non-finite inputs inside their k bits.  The sum's low mantissa bits are
+  // q + HALF (k < 8) or q mod 256 (k = 8).
+  const float t = __fadd_rn(v, kRoundMagic + float(K == 8 ? 0 : HALF));
+  return f32_as_u32(t) & MASK;
 }
 
-// Four consecutive elements -> one 4k-bit piece, first element most significant.
+// One element, stochastic: floor(v) + (u < v - floor(v)), clamped; the signed value.  z is the
+// element's random state.
+__device__ __forceinline__ int quantize_stochastic(float f, float r, int half, uint64_t z) {
+  const float v = __fmul_rn(f, r);
+  const float fl = floorf(v);
+  const float pr = __fsub_rn(v, fl);
+  const int q = int(fl) + (rand_u32(z) < pr * 0x1p32f ? 1 : 0);
+  return min(max(q, -half), half - 1);
+}
+
+// Four consecutive elements -> one 4k-bit piece, first element most significant.  z0: random
+// state of the first (stochastic rounding only).
 template <int K, bool STOCH>
-__device__ __forceinline__ uint32_t quantize4(const float* f, const float* r, uint64_t seed, int64_t idx0) {
+__device__ __forceinline__ uint32_t quantize4(const float* f, const float* r, uint64_t z0) {
   uint32_t piece = 0;
+  if constexpr (STOCH) {
+    // The clamped values are added up with their signs; adding the offset of all four codes at
+    // once then makes every field non-negative (k = 8: and the xor takes the offset out again).
+    constexpr uint32_t OFFSETS = uint32_t((1ull << (K - 1)) * (1ull + (1ull << K) + (1ull << (2 * K)) + (1ull << (3 * K))));
 #pragma unroll
-  for (int e = 0; e < 4; ++e) piece = (piece << K) | quantize1<K, STOCH>(f[e], r[e], seed, idx0 + e);
+    for (int e = 0; e < 4; ++e)
+      piece = (piece << K) + uint32_t(quantize_stochastic(f[e], r[e], 1 << (K - 1), z0 + uint64_t(e) * kRandStep));
+    piece += OFFSETS;
+    if (K == 8) piece ^= OFFSETS;
+  } else {
+#pragma unroll
+    for (int e = 0; e < 4; ++e) piece = (piece << K) | quantize_rne<K>(f[e], r[e]);
+  }
   return piece;
 }
 
@@ -412,6 +427,11 @@ __device__ __forceinline__ void pack8(const uint32_t (&P)[8], uint32_t (&out)[K]
   }
 }
 
+// k-bit code of a signed value.
+__device__ __forceinline__ uint32_t code_of_q(int q, int k) {
+  return k == 8 ? (uint32_t(q) & 0xFFu) : uint32_t(q + (1 << (k - 1)));
+}
+
 // Slow path for one group of 8 elements -> k bytes (tails and odd channel geometries):
 // scalar loads, per-byte stores guarded by the payload size.  Elements at or beyond N
 // contribute zero bits.
@@ -423,7 +443,11 @@ __device__ __forceinline__ void quantize_group8(const T* __restrict__ x, uint8_t
   for (int e = 0; e < 8; ++e) {
     const int64_t i = grp * 8 + e;
     uint64_t code = 0;
-    if (i < N) code = quantize1<K, STOCH>(load_one(x + i), r_of(i), seed, i);
+    if (i < N) {
+      const float f = load_one(x + i), r = r_of(i);
+      code = STOCH ? code_of_q(quantize_stochastic(f, r, 1 << (K - 1), rand_state(seed, uint64_t(i))), K)
+                   : quantize_rne<K>(f, r);
+    }
     acc = (acc << K) | code;
   }
 #pragma unroll
@@ -564,6 +588,12 @@ __global__ __launch_bounds__(kBlock) void quantize_pack_kernel(
     __syncthreads();
   }
 
+  // Stochastic rounding is bound by its vector instructions (26 per element, 17 of them the random
+  // number; every 64-bit or multiply instruction costs about 4.3 cycles like any other on this
+  // chip, so the count is what matters): states step by constants from one per thread, and the
+  // number is formed on 32-bit halves.  51.4 M float32 values at k = 4: call 80.5 -> 73.2 us
+  // against a state multiplied out per element and a 64-bit integer converted to float.
+  const uint64_t z_thread = STOCH ? rand_state(seed, uint64_t(tid * VEC)) : 0;  // of the thread's first element of tile 0
   int buf = 0;
   for (int64_t tile_f = blockIdx.x; tile_f < full_tiles; tile_f += gridDim.x, buf ^= 1) {
     const int64_t tile = tile_of(tile_f);
@@ -579,6 +609,7 @@ __global__ __launch_bounds__(kBlock) void quantize_pack_kernel(
     ChanPos pos = first_pos;
     if (MODE != kOneRange) chan_advance(geom, pos, mine);
     const int32_t ch0 = first_pos.ch;
+    uint64_t z = STOCH ? z_thread + uint64_t(tile) * (uint64_t(kTileElems) * kRandStep) : 0;
 #pragma unroll
     for (int u = 0; u < LOADS; ++u) {
       float r[VEC];
@@ -590,12 +621,12 @@ __global__ __launch_bounds__(kBlock) void quantize_pack_kernel(
         ranges_of_vector<MODE, VEC>(rtab, r_tensor, pos.ch, r);
       }
       if (MODE != kOneRange) chan_advance(geom, pos, geom.s256);
-      const int64_t e0 = tile * kTileElems + int64_t(u * kBlock + tid) * VEC;
       float f[VEC];
       widen(raw[u], f);
 #pragma unroll
       for (int h = 0; h < QPV; ++h)
-        pieces[buf][(u * kBlock + tid) * QPV + h] = quantize4<K, STOCH>(&f[4 * h], &r[4 * h], seed, e0 + 4 * h);
+        pieces[buf][(u * kBlock + tid) * QPV + h] = quantize4<K, STOCH>(&f[4 * h], &r[4 * h], z + uint64_t(4 * h) * kRandStep);
+      z += uint64_t(kBlock * VEC) * kRandStep;
     }
     if (next_f < full_tiles) ask_for_tile(tile_of(next_f));
     if (MODE == kRangePerVectorLocal && next_f < full_tiles)
@@ -815,21 +846,16 @@ hipError_t launch_quant(const accept_desc& d, const UPlan& p, const T* x, float*
 // the integers into bytes.  The bit width is a run-time argument here; the reciprocal of every
 // range group comes from the table that range_finalize_kernel writes.
 
-// k-bit code of one element, as quantize1 computes it (same arithmetic, run-time k).
+// k-bit code of one element, as the packed path computes it (same arithmetic, run-time k).
 __device__ __forceinline__ uint32_t quantize_any(float f, float r, int k, bool stoch, uint64_t seed, int64_t idx) {
   const int half = 1 << (k - 1);
   const uint32_t mask = (1u << k) - 1u;
-  const float v = __fmul_rn(f, r);
   if (!stoch) {
+    const float v = __fmul_rn(f, r);
     const float t = __fadd_rn(v, kRoundMagic + float(k == 8 ? 0 : half));
     return f32_as_u32(t) & mask;
   }
-  const float fl = floorf(v);
-  const float pr = __fsub_rn(v, fl);
-  const float u = counter_uniform(seed, uint64_t(idx));
-  int q = int(fl) + (u < pr ? 1 : 0);
-  q = min(max(q, -half), half - 1);
-  return (k == 8) ? (uint32_t(q) & 0xFFu) : uint32_t(q + half);
+  return code_of_q(quantize_stochastic(f, r, half, rand_state(seed, uint64_t(idx))), k);
 }
 // Signed value of a code.
 __device__ __forceinline__ int code_to_q(uint32_t code, int k) {

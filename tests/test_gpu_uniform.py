@@ -243,6 +243,14 @@ def test_stochastic_rounding_bit_exact(A, k):
     run_case(A, x, k, 4, 4146, channels=2, rounding=1, seed=9, in_bf16=True, tag="stoch-ch")
 
 
+@pytest.mark.parametrize("k,bf16,seed", [(4, False, (1 << 64) - 3), (8, True, 11)])
+def test_stochastic_rounding_over_many_tiles(A, k, bf16, seed):
+    """More 8192-element tiles than workgroups, tiles in reversed order plus leftovers: the random
+    state a workgroup carries from tile to tile is the one of the element's index."""
+    N = 2061 * 8192 + 41
+    run_case(A, si.make_shape("grad", (1, N), 64), k, 1, N, rounding=1, seed=seed, in_bf16=bf16, tag="stoch-tiles")
+
+
 def test_decoder_on_oracle_stream(A):
     """Feed the oracle's own header and payload to the GPU decoder."""
     torch = torch_mod()
