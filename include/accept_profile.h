@@ -28,6 +28,16 @@ accept_status accept_compress_timed(const accept_desc* desc, const void* x_dev, 
 accept_status accept_decompress_timed(const accept_desc* desc, const void* header_dev, const void* payload_dev,
                                       void* xhat_dev, void* hip_stream, float* stage_ms, int* n_stages);
 
+/*
+ * accept_compress with a smaller bound on the wait inside one of its kernels: the workgroups of the
+ * UNIFORM compressor for mid-sized tensors look at most `polls` times (0 .. 64, 64 being what
+ * accept_compress does) for each other's results before they leave the rest to the kernel that
+ * follows.  The outputs are the same for every value; tests use it to take the second way on purpose.
+ */
+accept_status accept_compress_polls(const accept_desc* desc, const void* x_dev, const float* alpha_prev_dev,
+                                    void* header_dev, void* payload_dev, void* workspace_dev, void* hip_stream,
+                                    int polls);
+
 /* Name of stage i of the call accept_*_timed would make for this descriptor
  * (is_decompress = 0/1); null when i is out of range.  Host-only. */
 const char* accept_stage_name(const accept_desc* desc, int is_decompress, int i);

@@ -62,6 +62,7 @@ def _load():
     lib.accept_mbq_compress_first.argtypes = [P(Desc), V, V, V, V, V]
     lib.accept_compress_timed.argtypes = [P(Desc), V, V, V, V, V, V, P(ctypes.c_float), P(I)]
     lib.accept_decompress_timed.argtypes = [P(Desc), V, V, V, V, P(ctypes.c_float), P(I)]
+    lib.accept_compress_polls.argtypes = [P(Desc), V, V, V, V, V, V, I]
     lib.accept_stage_name.argtypes = [P(Desc), I, I]
     lib.accept_stage_name.restype = ctypes.c_char_p
     lib.accept_bits_schedule.argtypes = [I, I]
@@ -71,7 +72,8 @@ def _load():
     lib.accept_version.argtypes = []
     lib.accept_version.restype = ctypes.c_char_p
     for name in ("accept_packed_size", "accept_workspace_size", "accept_compress", "accept_decompress",
-                 "accept_compress_noalloc", "accept_mbq_init", "accept_mbq_compress_first", "accept_compress_timed", "accept_decompress_timed"):
+                 "accept_compress_noalloc", "accept_mbq_init", "accept_mbq_compress_first", "accept_compress_timed", "accept_decompress_timed",
+                 "accept_compress_polls"):
         getattr(lib, name).restype = I
     return lib
 
@@ -271,6 +273,15 @@ def accept_compress_timed(desc, x, alpha_prev, header, payload, workspace):
                                    _ptr(workspace), _stream_handle(), ms, ctypes.byref(ns))
     _check(st, "accept_compress_timed")
     return [(accept_stage_name(desc, 0, i), float(ms[i])) for i in range(ns.value)]
+
+
+def accept_compress_polls(desc, x, header, payload, workspace, polls):
+    """accept_compress with a bounded number of looks inside the uniform compressor (see accept_profile.h)."""
+    _check_compress_args("accept_compress_polls", desc, x, None, header, payload, workspace, False)
+    st = lib.accept_compress_polls(ctypes.byref(desc), _ptr(x), _ptr(None), _ptr(header), _ptr(payload),
+                                   _ptr(workspace), _stream_handle(), int(polls))
+    _check(st, "accept_compress_polls")
+    return header, payload
 
 
 def accept_decompress_timed(desc, header, payload, out):

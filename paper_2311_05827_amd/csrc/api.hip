@@ -80,7 +80,8 @@ accept_status finish_timer(StageTimer& tm, hipError_t launch_err, float* stage_m
 }
 
 accept_status do_compress(const accept_desc* d, const void* x, const float* alpha_prev, void* header, void* payload,
-                          void* ws, void* stream, StageTimer* tm, hipError_t* launch_err) {
+                          void* ws, void* stream, StageTimer* tm, hipError_t* launch_err,
+                          int held_polls = kHeldPolls) {
   *launch_err = hipSuccess;
   const accept_status st = check_desc(d);
   if (st != ACCEPT_OK) return st;
@@ -90,7 +91,7 @@ accept_status do_compress(const accept_desc* d, const void* x, const float* alph
   hipStream_t s = static_cast<hipStream_t>(stream);
   if (d->scheme == ACCEPT_UNIFORM) {
     const UPlan p = make_uplan(*d);
-    *launch_err = launch_uniform_compress(*d, p, x, header, payload, ws, s, tm);
+    *launch_err = launch_uniform_compress(*d, p, x, header, payload, ws, s, tm, held_polls);
   } else {
     if (!alpha_prev || !aligned(alpha_prev, 4)) return ACCEPT_ERR_INVALID_ARG;
     const MPlan p = make_mplan(*d);
@@ -215,6 +216,15 @@ accept_status accept_compress_timed(const accept_desc* desc, const void* x_dev, 
       do_compress(desc, x_dev, alpha_prev_dev, header_dev, payload_dev, workspace_dev, hip_stream, &tm, &e);
   if (st != ACCEPT_OK && st != ACCEPT_ERR_HIP) return st;
   return finish_timer(tm, e, stage_ms, n_stages);
+}
+
+accept_status accept_compress_polls(const accept_desc* desc, const void* x_dev, const float* alpha_prev_dev,
+                                    void* header_dev, void* payload_dev, void* workspace_dev, void* hip_stream,
+                                    int polls) {
+  if (polls < 0 || polls > kHeldPolls) return ACCEPT_ERR_INVALID_ARG;
+  hipError_t e;
+  return do_compress(desc, x_dev, alpha_prev_dev, header_dev, payload_dev, workspace_dev, hip_stream, nullptr, &e,
+                     polls);
 }
 
 accept_status accept_decompress_timed(const accept_desc* desc, const void* header_dev, const void* payload_dev,

@@ -47,9 +47,11 @@ inline void mark(StageTimer* t, hipStream_t s) {
 
 // Every workspace starts with a control block that the library keeps between calls: words that
 // must be zero when a call starts and are put back to zero before it ends (the work counters of
-// the multi-bit encoder).  The caller zero-fills the workspace once; no kernel of either scheme
-// writes anything else there.
+// the multi-bit encoder in its first half, the mailboxes of the uniform scheme's held pass in its
+// second).  The caller zero-fills the workspace once; no kernel of either scheme writes anything
+// else there.
 constexpr size_t kCtrlBytes = 16384;
+constexpr size_t kMailOffset = 8192;
 
 // ---- scheme U (uniform) -----------------------------------------------------------------
 enum UMode { U_TENSOR = 0, U_SEGMENTED = 1, U_GENERIC = 2 };
@@ -68,14 +70,22 @@ struct UPlan {
   bool fast;           // vector path usable (every 16-byte vector lies inside one range group, or per_element)
   bool local_ranges;   // U_SEGMENTED: the quantize pass finishes the per-channel ranges itself, tile by tile
   bool per_element;    // U_GENERIC: one element per segment and rows of whole vectors (channels-last)
+  bool held;           // U_TENSOR: the range pass keeps the end of the tensor on the chip and quantizes it itself
+  int64_t held_units;  // held: whole units (see kUnitElems) of the tensor
+  int held_lds;        // held: units per workgroup that stay in local memory (the others in registers)
+  int64_t held_first;  // held: units [held_first, held_units) are kept, the others are read again
   size_t off_rtab;     // byte offset of the per-channel reciprocal table in the workspace
   size_t bytes;        // workspace bytes
 };
 
 UPlan make_uplan(const accept_desc& d);
 
+// held_polls: how often a workgroup of the held pass looks for the others' maxima before it gives up
+// (kHeldPolls; fewer only where a test wants the case that it gives up).
+constexpr int kHeldPolls = 64;
 hipError_t launch_uniform_compress(const accept_desc& d, const UPlan& p, const void* x, void* header,
-                                   void* payload, void* ws, hipStream_t s, StageTimer* tm);
+                                   void* payload, void* ws, hipStream_t s, StageTimer* tm,
+                                   int held_polls = kHeldPolls);
 hipError_t launch_uniform_decompress(const accept_desc& d, const void* header, const void* payload,
                                      void* xhat, hipStream_t s, StageTimer* tm);
 

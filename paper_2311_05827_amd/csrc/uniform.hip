@@ -32,6 +32,26 @@ constexpr float kRoundMagic = 12582912.0f;  // 1.5 * 2^23: adding it rounds to i
 constexpr int kRangeGridMax = 512;     // partial maxima of the per-tensor range pass
 constexpr int kQuantGridMax = 2048;    // workgroups of the quantize+pack kernel
 constexpr int kDequantGridMax = 8192;
+// The held pass (quantize_held_kernel): one workgroup per compute unit, two wavefronts per SIMD.
+constexpr int kHeldGrid = 256;
+constexpr int kHeldBlock = 512;
+constexpr int kUnitElems = 2 * kTileElems;  // elements a workgroup takes at a time
+template <typename T>
+constexpr int kHeldVecs = sizeof(T) == 4 ? 56 : 48;  // 16-byte vectors a thread keeps in registers (bfloat16: 56 would spill)
+constexpr int kHeldLdsVecs = 16;                     // and in local memory
+template <typename T>
+constexpr int kHeldUnits = kHeldVecs<T> * kHeldBlock * Elem<T>::VEC / kUnitElems;  // 7 (float32), 12 (bfloat16)
+template <typename T>
+constexpr int kHeldLdsUnits = kHeldLdsVecs * kHeldBlock * Elem<T>::VEC / kUnitElems;  // 2, 4
+// Tensors that take the held pass.  Below, its second kernel (4 us that do nearly nothing) costs
+// more than the saved read: 35 MB 18.4 us against 17.8 with two reads, 51 MB 20.9 against 22.1
+// (float32, k = 8), 50 MB 23.9 against 23.7 (bfloat16).  Above, the part that is kept gets small
+// and the workgroups drift apart by more than they wait for each other: 205 MB 59.1 against 69.5,
+// 300 MB 97 against 110, 400 MB 150 against 149.
+constexpr int64_t kHeldMinBytes = int64_t(48) << 20;
+constexpr int64_t kHeldMaxBytes = int64_t(256) << 20;
+static_assert(kHeldMinBytes / 4 >= int64_t(kHeldGrid) * kUnitElems, "every workgroup has a unit");
+static_assert(kMailOffset + kHeldGrid * sizeof(uint64_t) <= kCtrlBytes, "the control block holds the mailboxes");
 static_assert(kQuantGridMax % 8 == 0 && kRangeGridMax % 8 == 0, "grids at their caps keep tile and workgroup index equal modulo 8");
 static_assert(kRangeGridMax <= 4096, "the workspace holds at most 4096 partial maxima");
 
@@ -105,6 +125,9 @@ constexpr int kRangePerElement = 2;  // one element per segment (channels-last) 
 constexpr int kRangePerVectorLocal = 3;  // as kRangePerVector, quantizer only: no table in memory yet, the workgroup
                                          // finishes the ranges of each tile's channels itself; ChanPos.ch then indexes
                                          // its own small table (channel minus the tile's first channel, modulo C)
+constexpr int kOneRangeHeld = 4;  // as kOneRange, quantizer only: after quantize_held_kernel, of whose part only what
+                                  // it did not finish is left to do
+constexpr bool one_range(int mode) { return mode == kOneRange || mode == kOneRangeHeld; }
 // The per-group values (reciprocals for the quantizer, scales for the decoder) of a vector's elements.
 template <int MODE, int VEC>
 __device__ __forceinline__ void ranges_of_vector(const float* __restrict__ tab, float one, int32_t ch,
@@ -116,7 +139,7 @@ __device__ __forceinline__ void ranges_of_vector(const float* __restrict__ tab, 
       out[4 * h] = t.x; out[4 * h + 1] = t.y; out[4 * h + 2] = t.z; out[4 * h + 3] = t.w;
     }
   } else {
-    const float v = MODE == kOneRange ? one : tab[ch];
+    const float v = one_range(MODE) ? one : tab[ch];
 #pragma unroll
     for (int e = 0; e < VEC; ++e) out[e] = v;
   }
@@ -364,18 +387,20 @@ __global__ __launch_bounds__(kWave) void range_finalize_kernel(const float* __re
 
 // =========================================================================== quantize (U2)
 // One element, round half to even: v = x * r (one float32 multiply), round, clamp, offset to a
-// k-bit code.
+// k-bit code.  The _raw form leaves other bits above the low k.
 template <int K>
-__device__ __forceinline__ uint32_t quantize_rne(float f, float r) {
+__device__ __forceinline__ uint32_t quantize_rne_raw(float f, float r) {
   constexpr int HALF = 1 << (K - 1);
-  constexpr uint32_t MASK = (1u << K) - 1u;
   const float v = __fmul_rn(f, r);
   // Round half to even through the magic-number add.  |v| <= L(1 + 2^-23), so the rounded
-  // value lies in [-L, L] and the clamp of the definition never binds; the mask only keeps
-  // codes of non-finite inputs inside their k bits.  The sum's low mantissa bits are
-  // q + HALF (k < 8) or q mod 256 (k = 8).
-  const float t = __fadd_rn(v, kRoundMagic + float(K == 8 ? 0 : HALF));
-  return f32_as_u32(t) & MASK;
+  // value lies in [-L, L] and the clamp of the definition never binds; taking k bits only keeps
+  // codes of non-finite inputs inside them.  The sum's low mantissa bits are q + HALF (k < 8) or
+  // q mod 256 (k = 8).
+  return f32_as_u32(__fadd_rn(v, kRoundMagic + float(K == 8 ? 0 : HALF)));
+}
+template <int K>
+__device__ __forceinline__ uint32_t quantize_rne(float f, float r) {
+  return quantize_rne_raw<K>(f, r) & ((1u << K) - 1u);
 }
 
 // One element, stochastic: floor(v) + (u < v - floor(v)), clamped; the signed value.  z is the
@@ -388,42 +413,45 @@ __device__ __forceinline__ int quantize_stochastic(float f, float r, int half, u
   return min(max(q, -half), half - 1);
 }
 
-// Four consecutive elements -> one 4k-bit piece, first element most significant.  z0: random
-// state of the first (stochastic rounding only).
+// Four consecutive elements -> one 4k-bit piece in the top bits of a dword (zeros below), first
+// element most significant.  z0: random state of the first (stochastic rounding only).
+// The codes enter from the top, last element first: one funnel shift per element takes the low k
+// bits of the sum (whatever stands above them) and moves the earlier ones down.
 template <int K, bool STOCH>
 __device__ __forceinline__ uint32_t quantize4(const float* f, const float* r, uint64_t z0) {
+  constexpr int HALF = 1 << (K - 1);
   uint32_t piece = 0;
-  if constexpr (STOCH) {
-    // The clamped values are added up with their signs; adding the offset of all four codes at
-    // once then makes every field non-negative (k = 8: and the xor takes the offset out again).
-    constexpr uint32_t OFFSETS = uint32_t((1ull << (K - 1)) * (1ull + (1ull << K) + (1ull << (2 * K)) + (1ull << (3 * K))));
 #pragma unroll
-    for (int e = 0; e < 4; ++e)
-      piece = (piece << K) + uint32_t(quantize_stochastic(f[e], r[e], 1 << (K - 1), z0 + uint64_t(e) * kRandStep));
-    piece += OFFSETS;
-    if (K == 8) piece ^= OFFSETS;
-  } else {
-#pragma unroll
-    for (int e = 0; e < 4; ++e) piece = (piece << K) | quantize_rne<K>(f[e], r[e]);
+  for (int e = 3; e >= 0; --e) {
+    uint32_t code;
+    if constexpr (STOCH)
+      code = uint32_t(quantize_stochastic(f[e], r[e], HALF, z0 + uint64_t(e) * kRandStep));
+    else
+      code = quantize_rne_raw<K>(f[e], r[e]);
+    piece = __builtin_amdgcn_alignbit(code, piece, K);
+  }
+  if constexpr (STOCH && K < 8) {  // two's complement -> offset binary: flip the top bit of each field
+    constexpr uint64_t TOP = uint64_t(HALF) * (1ull + (1ull << K) + (1ull << (2 * K)) + (1ull << (3 * K)));
+    piece ^= uint32_t(TOP << (32 - 4 * K));
   }
   return piece;
 }
 
-// U3 for 32 consecutive codes: eight 4k-bit pieces -> k dwords of the big-endian bit
-// stream, each dword byte-swapped into memory order.
+// U3 for 32 consecutive codes: eight 4k-bit pieces (in the top bits of a dword each) -> k dwords
+// of the big-endian bit stream, each dword byte-swapped into memory order.
 template <int K>
 __device__ __forceinline__ void pack8(const uint32_t (&P)[8], uint32_t (&out)[K]) {
   constexpr int W = 4 * K;
-  uint64_t acc = 0;
-  int nb = 0, o = 0;
 #pragma unroll
-  for (int i = 0; i < 8; ++i) {
-    acc = (W == 32) ? ((acc << 32) | P[i]) : ((acc << W) | P[i]);
-    nb += W;
-    if (nb >= 32) {
-      out[o++] = __builtin_bswap32(uint32_t(acc >> (nb - 32)));
-      nb -= 32;
+  for (int o = 0; o < K; ++o) {
+    uint32_t w = 0;
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+      const int at = W * i - 32 * o;  // first bit of the piece, counted from the dword's first bit
+      if (at >= 0 && at < 32) w |= P[i] >> at;
+      if (at < 0 && at > -W) w |= P[i] << -at;
     }
+    out[o] = __builtin_bswap32(w);
   }
 }
 
@@ -464,15 +492,15 @@ __device__ __forceinline__ void quantize_group8(const T* __restrict__ x, uint8_t
 // barrier per tile is enough.  MODE says where an element's range comes from (kOneRange ..
 // kRangePerVectorLocal above).  kOneRange folds U1b into the prologue: every workgroup reduces
 // the range pass's partial maxima itself and workgroup 0 writes s to the header;
-// kRangePerVectorLocal folds it into the tile loop (see local_r below); the other two modes read
-// the table that a U1b kernel has written.  Elements after the last whole tile take the slow
+// kRangePerVectorLocal folds it into the tile loop (see local_r below); kOneRangeHeld is kOneRange
+// after quantize_held_kernel; the other two modes read the table that a U1b kernel has written.  Elements after the last whole tile take the slow
 // path at the end.
 template <typename T, int K, int MODE, bool STOCH>
 __global__ __launch_bounds__(kBlock) void quantize_pack_kernel(
     const T* __restrict__ x, uint32_t* __restrict__ payload32, float* __restrict__ header,
     const float* __restrict__ partials, int npart, const float* __restrict__ rtab, int64_t N, int64_t full_tiles,
     int64_t rev_tiles, int64_t slow_first_group, int64_t payload_bytes, ChanGeom geom, LocalRanges local, int64_t m,
-    int64_t seg_len, uint64_t seed) {
+    int64_t seg_len, uint64_t seed, int64_t held_tiles, uint64_t* __restrict__ mail) {
   constexpr int VEC = Elem<T>::VEC;
   constexpr int64_t TILE_VECS = kTileElems / VEC;
   constexpr int QPV = VEC / 4;                       // pieces per vector
@@ -480,6 +508,7 @@ __global__ __launch_bounds__(kBlock) void quantize_pack_kernel(
   constexpr int PIECES = kTileElems / 4;
   __shared__ __attribute__((aligned(16))) uint32_t pieces[2][PIECES];
   __shared__ float red[kBlock / kWave];
+  __shared__ int red_up[kBlock / kWave];
 
   const int tid = threadIdx.x;
   // Tile order.  The range pass has just read the tensor front to back, so its end is what the
@@ -488,7 +517,12 @@ __global__ __launch_bounds__(kBlock) void quantize_pack_kernel(
   // of the plain order.  A workgroup's tiles then step backwards by one grid stride, and tile and
   // workgroup index stay equal modulo 8: the die that read a tile in the range pass reads it
   // again here.  The up to seven tiles after rev_tiles keep their plain places.
+  // kOneRangeHeld: only the tiles behind the last whole unit, or all if a workgroup of the held
+  // pass gave up; in plain order.
+  int64_t tiles = MODE == kOneRangeHeld ? 0 : full_tiles;  // places to go through
+  int64_t skip = 0;
   auto tile_of = [&](int64_t tile_f) {
+    if (MODE == kOneRangeHeld) return tile_f + skip;
     return tile_f < rev_tiles ? rev_tiles - 8 - (tile_f & ~int64_t(7)) + (tile_f & 7) : tile_f;
   };
   // A tile's vectors are asked for one tile ahead: those of the first tile here, before anything
@@ -499,14 +533,24 @@ __global__ __launch_bounds__(kBlock) void quantize_pack_kernel(
 #pragma unroll
     for (int u = 0; u < LOADS; ++u) raw[u] = load16_stream(xt + (u * kBlock + tid) * VEC);
   };
-  if (int64_t(blockIdx.x) < full_tiles) ask_for_tile(tile_of(blockIdx.x));
+  if (int64_t(blockIdx.x) < tiles) ask_for_tile(tile_of(blockIdx.x));
 
   float r_tensor = 0.0f;
-  if (MODE == kOneRange) {
+  if (one_range(MODE)) {
     float c = 0.0f;
-    for (int i = tid; i < npart; i += kBlock) c = fmaxf(c, partials[i]);
+    bool done = true;
+    if (MODE == kOneRangeHeld) {  // one record per workgroup of the held pass
+      for (int i = tid; i < npart; i += kBlock) {
+        const float2 rec = reinterpret_cast<const float2*>(partials)[i];
+        c = fmaxf(c, rec.x);
+        done = done && rec.y != 0.0f;
+      }
+    } else {
+      for (int i = tid; i < npart; i += kBlock) c = fmaxf(c, partials[i]);
+    }
     c = wave_max(c);
-    if ((tid & (kWave - 1)) == 0) red[tid / kWave] = c;
+    const bool gave_up = __ballot(!done) != 0;
+    if ((tid & (kWave - 1)) == 0) { red[tid / kWave] = c; red_up[tid / kWave] = gave_up ? 1 : 0; }
     __syncthreads();
     c = red[0];
 #pragma unroll
@@ -514,13 +558,25 @@ __global__ __launch_bounds__(kBlock) void quantize_pack_kernel(
     float s;
     scale_from_range(c, K, s, r_tensor);
     if (blockIdx.x == 0 && tid == 0) header[0] = s;
+    if (MODE == kOneRangeHeld) {
+      // the mailboxes have been read by everyone: empty again for the next call
+      if (blockIdx.x == 0)
+        for (int i = tid; i < kHeldGrid; i += kBlock) mail[i] = 0;
+      int up = 0;
+#pragma unroll
+      for (int w = 0; w < kBlock / kWave; ++w) up |= red_up[w];
+      // rare: one gave up, all tiles once more (the same bytes where they were done)
+      skip = __builtin_amdgcn_readfirstlane(up) != 0 ? 0 : held_tiles;
+      tiles = full_tiles - skip;
+      if (int64_t(blockIdx.x) < tiles) ask_for_tile(tile_of(blockIdx.x));
+    }
   }
 
   // Channel position of a tile's first vector (the same in all threads), stepped from tile to
   // tile; a thread's own position is that plus its index.
   ChanPos first_pos{0, 0};
   ChanStep mine{0, 0};
-  if (MODE != kOneRange && int64_t(blockIdx.x) < full_tiles) {
+  if (!one_range(MODE) && int64_t(blockIdx.x) < full_tiles) {
     first_pos = chan_init(geom, tile_of(blockIdx.x) * TILE_VECS);
     mine.dr = int64_t(tid) % geom.seg_vecs;
     mine.dch = int32_t((int64_t(tid) / geom.seg_vecs) % geom.C);
@@ -595,19 +651,19 @@ __global__ __launch_bounds__(kBlock) void quantize_pack_kernel(
   // against a state multiplied out per element and a 64-bit integer converted to float.
   const uint64_t z_thread = STOCH ? rand_state(seed, uint64_t(tid * VEC)) : 0;  // of the thread's first element of tile 0
   int buf = 0;
-  for (int64_t tile_f = blockIdx.x; tile_f < full_tiles; tile_f += gridDim.x, buf ^= 1) {
+  for (int64_t tile_f = blockIdx.x; tile_f < tiles; tile_f += gridDim.x, buf ^= 1) {
     const int64_t tile = tile_of(tile_f);
     // the next tile of this workgroup: one grid stride back inside the reversed part
     const int64_t next_f = tile_f + gridDim.x;
     ChanPos next_pos = first_pos;
     LocalFetch next_lf;
-    if (MODE != kOneRange && next_f < full_tiles) {
+    if (!one_range(MODE) && next_f < tiles) {
       if (next_f < rev_tiles) chan_retreat(geom, next_pos, geom.sgrid);
       else next_pos = chan_init(geom, tile_of(next_f) * TILE_VECS);
       if (MODE == kRangePerVectorLocal) local_fetch(next_pos, next_lf);
     }
     ChanPos pos = first_pos;
-    if (MODE != kOneRange) chan_advance(geom, pos, mine);
+    if (!one_range(MODE)) chan_advance(geom, pos, mine);
     const int32_t ch0 = first_pos.ch;
     uint64_t z = STOCH ? z_thread + uint64_t(tile) * (uint64_t(kTileElems) * kRandStep) : 0;
 #pragma unroll
@@ -620,7 +676,7 @@ __global__ __launch_bounds__(kBlock) void quantize_pack_kernel(
       } else {
         ranges_of_vector<MODE, VEC>(rtab, r_tensor, pos.ch, r);
       }
-      if (MODE != kOneRange) chan_advance(geom, pos, geom.s256);
+      if (!one_range(MODE)) chan_advance(geom, pos, geom.s256);
       float f[VEC];
       widen(raw[u], f);
 #pragma unroll
@@ -628,8 +684,8 @@ __global__ __launch_bounds__(kBlock) void quantize_pack_kernel(
         pieces[buf][(u * kBlock + tid) * QPV + h] = quantize4<K, STOCH>(&f[4 * h], &r[4 * h], z + uint64_t(4 * h) * kRandStep);
       z += uint64_t(kBlock * VEC) * kRandStep;
     }
-    if (next_f < full_tiles) ask_for_tile(tile_of(next_f));
-    if (MODE == kRangePerVectorLocal && next_f < full_tiles)
+    if (next_f < tiles) ask_for_tile(tile_of(next_f));
+    if (MODE == kRangePerVectorLocal && next_f < tiles)
       local_finish(tile_of(next_f), next_pos, next_lf, local_r[buf ^ 1]);
     first_pos = next_pos;
     __syncthreads();
@@ -646,11 +702,207 @@ __global__ __launch_bounds__(kBlock) void quantize_pack_kernel(
   uint8_t* payload8 = reinterpret_cast<uint8_t*>(payload32);
   for (int64_t g = slow_first_group + int64_t(blockIdx.x) * kBlock + tid; g < groups;
        g += int64_t(gridDim.x) * kBlock) {
-    if (MODE != kOneRange) {
+    if (!one_range(MODE)) {
       quantize_group8<T, K, STOCH>(x, payload8, g, N, payload_bytes, seed,
                                    [&](int64_t i) { return rtab[(i % m) / seg_len]; });
     } else {
       quantize_group8<T, K, STOCH>(x, payload8, g, N, payload_bytes, seed, [&](int64_t) { return r_tensor; });
+    }
+  }
+}
+
+// U1, and U2 + U3 for the end of the tensor, in one kernel (one range for the tensor, rounding to
+// nearest).  The range has to be known before the first element can be quantized, so the plain way
+// reads the tensor twice, and the memory-side cache does not help: it delivers 7.4 TB/s, memory
+// itself 7.2.  The registers and local memories of the chip hold 168 MiB, though.  Here one workgroup per compute unit
+// reads units (16384 elements) b, b + 256, ..., keeps the last of them (151 MB over the chip, two
+// thirds in registers, one in local memory), hands its maximum to the other workgroups through a mailbox, waits for
+// theirs, quantizes what it kept and reads the units before held_first once more.
+// quantize_pack_kernel does the elements behind the last whole unit.
+//
+// The wait is bounded: nothing says that all 256 workgroups run at the same time (another kernel may
+// hold some compute units).  A workgroup that has not seen all mailboxes after `polls` looks gives
+// up, says so in its record and ends; quantize_pack_kernel then takes the held units too.  So every
+// workgroup ends whatever else runs, and the result does not depend on it.
+//
+// A mailbox is one 64-bit word, value and a "full" mark together, written and read with device-scope
+// accesses (they bypass the dies' second-level caches): no ordering between two words is needed.
+// quantize_pack_kernel empties the mailboxes.
+//
+// 51.4 M float32 values (205 MB), k = 8: 59.4 us a call against 69.5 with two reads (range 32.8,
+// quantize 38.0); here 32.7 us to the mailboxes, 15 us of quantizing, 4 us of kernel end, 4.5 us for
+// the other kernel.  100 MB: 30.7 against 38.0; bfloat16 103 MB: 35.1 against 44.8.
+// Stochastic rounding keeps the two reads: it is bound by its instructions, which the second read
+// hides behind.
+template <typename T, int K>
+__global__ __launch_bounds__(kHeldBlock, 2) void quantize_held_kernel(const T* __restrict__ x,
+                                                                      uint32_t* __restrict__ payload32,
+                                                                      float2* __restrict__ records,
+                                                                      uint64_t* __restrict__ mail, int64_t units,
+                                                                      int64_t held_first, int lds_units, int polls) {
+  constexpr int VEC = Elem<T>::VEC;
+  constexpr int LOADS = kUnitElems / (kHeldBlock * VEC);  // vectors per thread and unit
+  constexpr int SLOTS = kHeldUnits<T>;
+  constexpr int RING = 32 / (4 * LOADS) * 2;  // units in flight while nothing is kept yet: 128 KiB per workgroup
+  constexpr int WAVES = kHeldBlock / kWave;
+  constexpr int LDS_UNITS = kHeldLdsUnits<T>;
+  static_assert(SLOTS * LOADS == kHeldVecs<T> && RING >= 2 && RING < SLOTS, "registers");
+  static_assert(LDS_UNITS % RING == 0 && LDS_UNITS < SLOTS, "units kept in local memory pass through the ring in whole turns");
+  constexpr int PIECES = kUnitElems / 4;
+  constexpr int QPV = VEC / 4;
+  // local memory, all 160 KiB of it: what is kept, and two buffers of pieces (the first of which the
+  // reductions use before)
+  struct Local {
+    uint4 kept[LDS_UNITS][LOADS][kHeldBlock];
+    uint32_t pieces[2][PIECES];
+  };
+  static_assert(sizeof(Local) <= 160 * 1024, "local memory of a compute unit");
+  __shared__ __attribute__((aligned(16))) Local local;
+  float* const red = reinterpret_cast<float*>(local.pieces[0]);
+  int* const red_up = reinterpret_cast<int*>(local.pieces[0]) + WAVES;
+  const int tid = threadIdx.x;
+  const int lane = tid & (kWave - 1), wave = tid / kWave;
+
+  // units of this workgroup: ordinals 0 .. count-1, unit = ordinal * 256 + b; those before `first`
+  // (held_first is a multiple of 256) are only looked at
+  const int count = int((units - blockIdx.x + kHeldGrid - 1) / kHeldGrid);  // at least 1 (host)
+  const int first = int(held_first / kHeldGrid);
+  uint4 kept[SLOTS][LOADS];
+  auto ask = [&](int slot_ordinal, uint4 (&raw)[LOADS]) {
+    const T* xu = x + (int64_t(slot_ordinal) * kHeldGrid + blockIdx.x) * kUnitElems;
+#pragma unroll
+    for (int u = 0; u < LOADS; ++u) raw[u] = load16_stream(xu + (u * kHeldBlock + tid) * VEC);
+  };
+  float c = 0.0f;
+  auto look = [&](const uint4 (&raw)[LOADS]) {
+#pragma unroll
+    for (int u = 0; u < LOADS; ++u) {
+      float f[VEC];
+      widen(raw[u], f);
+#pragma unroll
+      for (int e = 0; e < VEC; ++e) c = fmaxf(c, fabsf(f[e]));
+    }
+  };
+  // Slots 0 .. RING-1 are a ring while the units before `first` go by: a unit looked at makes room
+  // for the one RING ordinals later (it exists: the held part is longer than the ring), and when
+  // the loop ends slot j holds ordinal first + j, like the other slots.  The loop runs whole turns;
+  // what is left over by a division goes through the slots behind the ring beforehand.  (Loads and
+  // looks of the loop are unconditional, so that the compiler knows how many loads are in flight
+  // and waits for no more than it needs.)
+  const int extra = first % RING;
+#pragma unroll
+  for (int j = 0; j < RING - 1; ++j)
+    if (j < extra) ask(j, kept[RING + j]);
+#pragma unroll
+  for (int j = 0; j < RING; ++j) ask(extra + j < count ? extra + j : count - 1, kept[j]);
+#pragma unroll
+  for (int j = 0; j < RING - 1; ++j)
+    if (j < extra) look(kept[RING + j]);
+  for (int o = extra; o < first; o += RING) {
+#pragma unroll
+    for (int j = 0; j < RING; ++j) {
+      look(kept[j]);
+      __builtin_amdgcn_sched_barrier(0);  // the next unit's loads are issued here, before the other slots are waited for
+      ask(o + RING + j, kept[j]);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+  }
+  if (lds_units != 0) {  // 0 or LDS_UNITS: ordinals first .. first + LDS_UNITS - 1 go on to local memory
+#pragma unroll
+    for (int q = 0; q < LDS_UNITS; ++q) {
+      look(kept[q % RING]);
+#pragma unroll
+      for (int u = 0; u < LOADS; ++u) local.kept[q][u][tid] = kept[q % RING][u];
+      __builtin_amdgcn_sched_barrier(0);
+      ask(first + q + RING, kept[q % RING]);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+  }
+  const int base = first + lds_units;  // slot j: ordinal base + j
+#pragma unroll
+  for (int j = RING; j < SLOTS; ++j)
+    if (base + j < count) ask(base + j, kept[j]);
+#pragma unroll
+  for (int j = 0; j < RING; ++j) look(kept[j]);  // (a clamped copy of the last unit does no harm)
+#pragma unroll
+  for (int j = RING; j < SLOTS; ++j)
+    if (base + j < count) look(kept[j]);
+  __builtin_amdgcn_s_waitcnt(0x0F70);  // nothing is in flight from here on, whichever slots are in use
+
+  c = wave_max(c);
+  if (lane == 0) red[wave] = c;
+  __syncthreads();
+  c = red[0];
+#pragma unroll
+  for (int w = 1; w < WAVES; ++w) c = fmaxf(c, red[w]);
+  const float mine = c;
+  if (tid == 0)
+    __hip_atomic_store(mail + blockIdx.x, (uint64_t(1) << 32) | f32_as_u32(mine), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  __syncthreads();  // red is free again
+  if (tid < kHeldGrid) {  // wavefront w watches mailboxes 64w .. 64w+63
+    uint64_t v = 0;
+    bool all = false;
+    for (int i = 0; i < polls; ++i) {
+      v = __hip_atomic_load(mail + tid, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      all = __ballot((v >> 32) == 0) == 0;
+      if (all) break;
+      __builtin_amdgcn_s_sleep(4);
+    }
+    const float cw = wave_max(u32_as_f32(uint32_t(v)));
+    if (lane == 0) { red[wave] = cw; red_up[wave] = all ? 0 : 1; }
+  }
+  __syncthreads();
+  int up = 0;
+  c = 0.0f;
+#pragma unroll
+  for (int w = 0; w < kHeldGrid / kWave; ++w) { c = fmaxf(c, red[w]); up |= red_up[w]; }
+  up = __builtin_amdgcn_readfirstlane(up);
+  if (tid == 0) records[blockIdx.x] = make_float2(mine, up ? 0.0f : 1.0f);
+  if (up) return;
+
+  float s, r;
+  scale_from_range(c, K, s, r);
+  float rv[VEC];
+#pragma unroll
+  for (int e = 0; e < VEC; ++e) rv[e] = r;
+  int buf_i = 0;
+  auto quantize_unit = [&](int ordinal, auto vec_of) {
+    uint32_t* buf = local.pieces[buf_i];
+    buf_i ^= 1;
+#pragma unroll
+    for (int u = 0; u < LOADS; ++u) {
+      float f[VEC];
+      widen(vec_of(u), f);
+#pragma unroll
+      for (int h = 0; h < QPV; ++h) buf[(u * kHeldBlock + tid) * QPV + h] = quantize4<K, false>(&f[4 * h], &rv[4 * h], 0);
+    }
+    __syncthreads();  // double buffered: one barrier per unit
+    const uint4 a = *reinterpret_cast<const uint4*>(&buf[8 * tid]);
+    const uint4 b = *reinterpret_cast<const uint4*>(&buf[8 * tid + 4]);
+    const uint32_t P[8] = {a.x, a.y, a.z, a.w, b.x, b.y, b.z, b.w};
+    uint32_t out[K];
+    pack8<K>(P, out);
+    store_dwords<K>(payload32 + ((int64_t(ordinal) * kHeldGrid + blockIdx.x) * kHeldBlock + tid) * K, out);
+  };
+  __syncthreads();  // the reductions' words are free: pieces from here on
+  // A slot that has been quantized takes a unit that was only looked at, the last of them first;
+  // those loads are under way while the other kept units are quantized.  (Conditions are the same
+  // in all threads.)
+#pragma unroll
+  for (int j = 0; j < SLOTS; ++j) {
+    if (base + j < count) quantize_unit(base + j, [&](int u) { return kept[j][u]; });
+    if (j < first) ask(first - 1 - j, kept[j]);
+  }
+  if (lds_units != 0) {
+    for (int q = 0; q < LDS_UNITS; ++q) quantize_unit(first + q, [&](int u) { return local.kept[q][u][tid]; });
+  }
+  for (int o = first - 1; o >= 0; o -= SLOTS) {
+#pragma unroll
+    for (int j = 0; j < SLOTS; ++j) {
+      if (o - j >= 0) {
+        quantize_unit(o - j, [&](int u) { return kept[j][u]; });
+        if (o - j - SLOTS >= 0) ask(o - j - SLOTS, kept[j]);
+      }
     }
   }
 }
@@ -813,21 +1065,23 @@ ChanStep make_step(int64_t step_vecs, int64_t seg_vecs, int64_t C) {
 
 template <typename T, int K, int MODE, bool STOCH>
 hipError_t launch_quant(const accept_desc& d, const UPlan& p, const T* x, float* header, uint32_t* payload,
-                        const float* partials, const float* rtab, hipStream_t s) {
+                        const float* partials, const float* rtab, uint64_t* mail, hipStream_t s) {
   const int64_t N = p.N;
   const int64_t full_tiles = p.fast ? N / kTileElems : 0;
   const int64_t groups = (N + 7) / 8;
   const int64_t slow_first = full_tiles * (kTileElems / 8);
+  const int64_t held_tiles = MODE == kOneRangeHeld ? p.held_units * (kUnitElems / kTileElems) : 0;
   const int64_t slow_groups = groups - slow_first;
   int64_t want = full_tiles > (slow_groups + kBlock - 1) / kBlock ? full_tiles : (slow_groups + kBlock - 1) / kBlock;
   if (want < 1) want = 1;
+  if (MODE == kOneRangeHeld) want = kHeldGrid;  // nearly nothing to do, but for the case that it is everything
   const int grid = int(want < kQuantGridMax ? want : kQuantGridMax);
   // the reversed tile order needs tile and workgroup index to agree modulo 8
   const int64_t rev_tiles = (grid % 8 == 0) ? (full_tiles & ~int64_t(7)) : 0;
   ChanGeom g{};
   g.seg_vecs = 1;
   g.C = 1;
-  if (MODE != kOneRange && p.fast) {
+  if (!one_range(MODE) && p.fast) {
     // per element: the "segments" are single vectors and the "channels" the m / vec vectors of a row
     g.seg_vecs = MODE == kRangePerElement ? 1 : p.seg_len / p.vec;
     g.C = int32_t(MODE == kRangePerElement ? p.m / p.vec : p.C);
@@ -836,8 +1090,9 @@ hipError_t launch_quant(const accept_desc& d, const UPlan& p, const T* x, float*
   }
   const int64_t payload_bytes = (N * K + 7) / 8;
   hipLaunchKernelGGL((quantize_pack_kernel<T, K, MODE, STOCH>), dim3(grid), dim3(kBlock), 0, s, x, payload, header,
-                     partials, p.range_grid, rtab, N, full_tiles, rev_tiles, slow_first, payload_bytes, g,
-                     LocalRanges{int32_t(d.n * p.cps)}, p.m, p.seg_len, d.seed);
+                     partials, MODE == kOneRangeHeld ? kHeldGrid : p.range_grid, rtab, N, full_tiles, rev_tiles,
+                     slow_first, payload_bytes, g, LocalRanges{int32_t(d.n * p.cps)}, p.m, p.seg_len, d.seed, held_tiles,
+                     mail);
   return hipGetLastError();
 }
 
@@ -1015,31 +1270,62 @@ int plain_grid(int64_t units) {
 
 template <typename T, int K>
 hipError_t launch_quant_k(const accept_desc& d, const UPlan& p, const T* x, float* header, uint32_t* payload,
-                          const float* partials, const float* rtab, hipStream_t s) {
+                          const float* partials, const float* rtab, uint64_t* mail, hipStream_t s) {
   const bool stoch = d.rounding == ACCEPT_ROUND_STOCHASTIC;
+  if (p.held) return launch_quant<T, K, kOneRangeHeld, false>(d, p, x, header, payload, partials, rtab, mail, s);
   if (p.mode == U_TENSOR) {
-    return stoch ? launch_quant<T, K, kOneRange, true>(d, p, x, header, payload, partials, rtab, s)
-                 : launch_quant<T, K, kOneRange, false>(d, p, x, header, payload, partials, rtab, s);
+    return stoch ? launch_quant<T, K, kOneRange, true>(d, p, x, header, payload, partials, rtab, mail, s)
+                 : launch_quant<T, K, kOneRange, false>(d, p, x, header, payload, partials, rtab, mail, s);
   }
   if (p.per_element) {
-    return stoch ? launch_quant<T, K, kRangePerElement, true>(d, p, x, header, payload, partials, rtab, s)
-                 : launch_quant<T, K, kRangePerElement, false>(d, p, x, header, payload, partials, rtab, s);
+    return stoch ? launch_quant<T, K, kRangePerElement, true>(d, p, x, header, payload, partials, rtab, mail, s)
+                 : launch_quant<T, K, kRangePerElement, false>(d, p, x, header, payload, partials, rtab, mail, s);
   }
   if (p.local_ranges) {
-    return stoch ? launch_quant<T, K, kRangePerVectorLocal, true>(d, p, x, header, payload, partials, rtab, s)
-                 : launch_quant<T, K, kRangePerVectorLocal, false>(d, p, x, header, payload, partials, rtab, s);
+    return stoch ? launch_quant<T, K, kRangePerVectorLocal, true>(d, p, x, header, payload, partials, rtab, mail, s)
+                 : launch_quant<T, K, kRangePerVectorLocal, false>(d, p, x, header, payload, partials, rtab, mail, s);
   }
-  return stoch ? launch_quant<T, K, kRangePerVector, true>(d, p, x, header, payload, partials, rtab, s)
-               : launch_quant<T, K, kRangePerVector, false>(d, p, x, header, payload, partials, rtab, s);
+  return stoch ? launch_quant<T, K, kRangePerVector, true>(d, p, x, header, payload, partials, rtab, mail, s)
+               : launch_quant<T, K, kRangePerVector, false>(d, p, x, header, payload, partials, rtab, mail, s);
+}
+
+// Compute units of the current device (0 if the question fails).
+int compute_units() {
+  int dev = -1, cus = 0;
+  if (hipGetDevice(&dev) != hipSuccess) return 0;
+  if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) return 0;
+  return cus;
 }
 
 template <typename T>
-hipError_t compress_typed(const accept_desc& d, const UPlan& p, const T* x, float* header, uint32_t* payload,
-                          void* ws, hipStream_t s, StageTimer* tm) {
+hipError_t launch_held(const accept_desc& d, const UPlan& p, const T* x, uint32_t* payload, float* partials,
+                       uint64_t* mail, int polls, hipStream_t s) {
+  float2* records = reinterpret_cast<float2*>(partials);
+#define ACCEPT_HELD(KK)                                                                                          \
+  case KK:                                                                                                       \
+    hipLaunchKernelGGL((quantize_held_kernel<T, KK>), dim3(kHeldGrid), dim3(kHeldBlock), 0, s, x, payload, records, \
+                       mail, p.held_units, p.held_first, p.held_lds, polls);                                     \
+    break;
+  switch (d.bits) {
+    ACCEPT_HELD(2) ACCEPT_HELD(3) ACCEPT_HELD(4) ACCEPT_HELD(5) ACCEPT_HELD(6) ACCEPT_HELD(7) ACCEPT_HELD(8)
+    default: return hipErrorInvalidValue;
+  }
+#undef ACCEPT_HELD
+  return hipGetLastError();
+}
+
+template <typename T>
+hipError_t compress_typed(const accept_desc& d, UPlan p, const T* x, float* header, uint32_t* payload,
+                          void* ws, hipStream_t s, StageTimer* tm, int held_polls) {
+  uint64_t* mail = reinterpret_cast<uint64_t*>(reinterpret_cast<char*>(ws) + kMailOffset);
+  if (p.held && compute_units() < kHeldGrid) p.held = false;  // its workgroups could never run together
   float* partials = reinterpret_cast<float*>(reinterpret_cast<char*>(ws) + kCtrlBytes);
   float* rtab = reinterpret_cast<float*>(reinterpret_cast<char*>(ws) + p.off_rtab);
   mark(tm, s);
-  if (p.mode == U_TENSOR) {
+  if (p.held) {
+    const hipError_t e = launch_held<T>(d, p, x, payload, partials, mail, held_polls, s);
+    if (e != hipSuccess) return e;
+  } else if (p.mode == U_TENSOR) {
     hipLaunchKernelGGL((range_tensor_kernel<T>), dim3(p.range_grid), dim3(kBlock), 0, s, x, p.N, partials);
   } else if (p.mode == U_SEGMENTED) {
     const int64_t tiles = (p.N + kTileElems - 1) / kTileElems;  // below 2^31: N is at most 2^40
@@ -1091,13 +1377,13 @@ hipError_t compress_typed(const accept_desc& d, const UPlan& p, const T* x, floa
     return hipSuccess;
   }
   switch (d.bits) {
-    case 2: e = launch_quant_k<T, 2>(d, p, x, header, payload, partials, rtab, s); break;
-    case 3: e = launch_quant_k<T, 3>(d, p, x, header, payload, partials, rtab, s); break;
-    case 4: e = launch_quant_k<T, 4>(d, p, x, header, payload, partials, rtab, s); break;
-    case 5: e = launch_quant_k<T, 5>(d, p, x, header, payload, partials, rtab, s); break;
-    case 6: e = launch_quant_k<T, 6>(d, p, x, header, payload, partials, rtab, s); break;
-    case 7: e = launch_quant_k<T, 7>(d, p, x, header, payload, partials, rtab, s); break;
-    case 8: e = launch_quant_k<T, 8>(d, p, x, header, payload, partials, rtab, s); break;
+    case 2: e = launch_quant_k<T, 2>(d, p, x, header, payload, partials, rtab, mail, s); break;
+    case 3: e = launch_quant_k<T, 3>(d, p, x, header, payload, partials, rtab, mail, s); break;
+    case 4: e = launch_quant_k<T, 4>(d, p, x, header, payload, partials, rtab, mail, s); break;
+    case 5: e = launch_quant_k<T, 5>(d, p, x, header, payload, partials, rtab, mail, s); break;
+    case 6: e = launch_quant_k<T, 6>(d, p, x, header, payload, partials, rtab, mail, s); break;
+    case 7: e = launch_quant_k<T, 7>(d, p, x, header, payload, partials, rtab, mail, s); break;
+    case 8: e = launch_quant_k<T, 8>(d, p, x, header, payload, partials, rtab, mail, s); break;
     default: return hipErrorInvalidValue;
   }
   if (e != hipSuccess) return e;
@@ -1206,6 +1492,17 @@ UPlan make_uplan(const accept_desc& d) {
     if (blocks < 1) blocks = 1;
     p.range_grid = int(blocks < kRangeGridMax ? blocks : kRangeGridMax);
     partial_bytes = size_t(4096) * sizeof(float);
+    const int64_t bytes = p.N * (p.vec == 8 ? 2 : 4);
+    p.held = d.layout == ACCEPT_LAYOUT_PACKED && d.rounding == ACCEPT_ROUND_NEAREST_EVEN && bytes >= kHeldMinBytes &&
+             bytes <= kHeldMaxBytes;
+    if (p.held) {
+      const int64_t keep = p.vec == 8 ? kHeldUnits<bf16_t> : kHeldUnits<float>;
+      const int64_t keep_lds = p.vec == 8 ? kHeldLdsUnits<bf16_t> : kHeldLdsUnits<float>;
+      p.held_units = p.N / kUnitElems;
+      const int64_t rounds = (p.held_units + kHeldGrid - 1) / kHeldGrid;
+      p.held_lds = rounds > keep ? int(keep_lds) : 0;
+      p.held_first = rounds > keep + keep_lds ? (rounds - keep - keep_lds) * kHeldGrid : 0;
+    }
   } else if (p.seg_len % p.vec == 0 && p.seg_len >= 512) {
     p.mode = U_SEGMENTED;
     p.fast = true;
@@ -1249,12 +1546,12 @@ UPlan make_uplan(const accept_desc& d) {
 }
 
 hipError_t launch_uniform_compress(const accept_desc& d, const UPlan& p, const void* x, void* header, void* payload,
-                                   void* ws, hipStream_t s, StageTimer* tm) {
+                                   void* ws, hipStream_t s, StageTimer* tm, int held_polls) {
   if (d.in_dtype == ACCEPT_BF16)
     return compress_typed<bf16_t>(d, p, static_cast<const bf16_t*>(x), static_cast<float*>(header),
-                                  static_cast<uint32_t*>(payload), ws, s, tm);
+                                  static_cast<uint32_t*>(payload), ws, s, tm, held_polls);
   return compress_typed<float>(d, p, static_cast<const float*>(x), static_cast<float*>(header),
-                               static_cast<uint32_t*>(payload), ws, s, tm);
+                               static_cast<uint32_t*>(payload), ws, s, tm, held_polls);
 }
 
 hipError_t launch_uniform_decompress(const accept_desc& d, const void* header, const void* payload, void* xhat,

@@ -251,6 +251,46 @@ def test_stochastic_rounding_over_many_tiles(A, k, bf16, seed):
     run_case(A, si.make_shape("grad", (1, N), 64), k, 1, N, rounding=1, seed=seed, in_bf16=bf16, tag="stoch-tiles")
 
 
+# One range, nearest rounding, 48 to 256 MiB: the end of the tensor is kept on the chip between the
+# range and the quantizer.  256 workgroups, units of 16384 elements; per workgroup 7 (bfloat16: 12)
+# units in registers, 2 (4) in local memory, the rest read twice.
+HELD_ROUND = 256 * 16384
+
+
+@pytest.mark.parametrize("k,N,bf16", [
+    (8, 3 * HELD_ROUND, False),                      # the smallest, no tail
+    (3, 3 * HELD_ROUND + 5 * 16384 + 8193, False),   # a few workgroups with one unit more, a tile and one element behind
+    (5, 7 * HELD_ROUND + 16384, False),              # local memory comes into use
+    (4, 10 * HELD_ROUND - 16384 * 7 + 33, False),    # one unit per workgroup is read twice, some have none
+    (7, 6 * HELD_ROUND + 31, True),
+    (6, 17 * HELD_ROUND + 16384 * 255, True),        # two read twice
+    (2, 30 * HELD_ROUND + 8192, True),               # more are read twice than there are slots
+])
+def test_held_pass(A, k, N, bf16):
+    x = si.make_shape("grad", (1, N), 200 + k)
+    x[0, N - 1 - N // 7] = 0.5  # the largest value, far from either end
+    run_case(A, x, k, 1, N, in_bf16=bf16, out_bf16=bf16, tag="held")
+
+
+def test_held_pass_that_gives_up(A):
+    """A workgroup that does not see the others' maxima in time leaves its part to the second
+    kernel; whatever share of them does (0, some, none), the bytes are the same, and the
+    workspace is ready for the next call."""
+    torch = torch_mod()
+    k, N = 5, 3 * HELD_ROUND + 16384 * 9 + 100
+    xs = [torch.from_numpy(si.make_shape("grad", (N,), 220 + i) * np.float32(1 + i)).cuda() for i in range(2)]
+    d = A.make_desc(A.UNIFORM, k, 1, N)
+    want = [orc.uniform_compress(x.cpu().numpy(), k, 1, N) for x in xs]
+    header, payload, ws = A.alloc_outputs(d, "cuda")
+    for polls in (0, 1, 2, 64, 0, 3, 64):
+        for x, (oh, op) in zip(xs, want):
+            payload.zero_()
+            A.accept_compress_polls(d, x, header, payload, ws, polls)
+            torch.cuda.synchronize()
+            assert dev_bytes(header) == oh, polls
+            assert first_mismatch(dev_bytes(payload), op.tobytes()) is None, polls
+
+
 def test_decoder_on_oracle_stream(A):
     """Feed the oracle's own header and payload to the GPU decoder."""
     torch = torch_mod()
