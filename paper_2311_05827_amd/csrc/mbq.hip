@@ -9,6 +9,8 @@
 // no LDS exchange and its k*VEC output bytes per lane are contiguous across lanes.  The
 // least-squares sums ride along in the same pass: bit counts come from popcounts of the
 // finished plane bytes, B^T x from multiply-adds with the 0/1 plane bits.
+#include <type_traits>
+
 #include "common.hpp"
 
 namespace accept {
@@ -187,6 +189,31 @@ __device__ __forceinline__ int build_bucket_table(uint8_t* lut, F count_below) {
   return mymax;
 }
 
+// M1 for k <= 4 by one wavefront, in registers: lane p holds pattern p's level (float32 sum in the
+// order j = 0..k-1 from 0).  Its rank is the number of levels below its own (ties by pattern); a
+// lane-to-lane push hands every level to the lane of its rank.  Afterwards lane i < 2^k has the
+// i-th level and its pattern, and tau_i (+inf from lane 2^k - 1 on).
+template <int K>
+__device__ __forceinline__ void sort_levels(const float (&alpha)[K], float& lv_s, uint32_t& pat_s, float& tau) {
+  constexpr int P = 1 << K;
+  const int pat = threadIdx.x & (kWave - 1);
+  float lv = 0.0f;
+#pragma unroll
+  for (int j = 0; j < K; ++j) lv = __fadd_rn(lv, ((pat >> j) & 1) ? alpha[j] : -alpha[j]);
+  int rank = 0;
+#pragma unroll
+  for (int q = 0; q < P; ++q) {
+    const float o = u32_as_f32(uint32_t(__builtin_amdgcn_readlane(int(f32_as_u32(lv)), q)));
+    rank += (o < lv || (o == lv && q < pat)) ? 1 : 0;
+  }
+  if (pat >= P) rank = pat;  // idle lanes push to themselves
+  lv_s = u32_as_f32(uint32_t(__builtin_amdgcn_ds_permute(rank * 4, int(f32_as_u32(lv)))));
+  pat_s = uint32_t(__builtin_amdgcn_ds_permute(rank * 4, pat));
+  const float lv_next = u32_as_f32(uint32_t(__builtin_amdgcn_ds_bpermute(((pat + 1) & (kWave - 1)) * 4,
+                                                                        int(f32_as_u32(lv_s)))));
+  tau = pat < P - 1 ? __fmul_rn(0.5f, __fadd_rn(lv_s, lv_next)) : __builtin_inff();
+}
+
 // M1 and the search tables.  alpha[0..K) = the previous coefficients, already in registers (the
 // caller loads them first thing, so that their trip to memory overlaps its other set-up work).
 template <int K>
@@ -198,27 +225,12 @@ __device__ __forceinline__ void build_encode_tables(const float (&alpha)[K], Enc
   int mymax = 0;
   if (tid == 0) tb.maxcnt = 1;
   if constexpr (K <= 4) {
-    // Few levels: the first wavefront sorts them in registers, lane p holding pattern p.  Its rank
-    // is the number of levels below its own (ties by pattern); a lane-to-lane push then hands
-    // every level to the lane of its rank, and thresholds, spread patterns and the pair table
-    // follow without a barrier.
+    // Few levels: the first wavefront sorts them in registers; thresholds, spread patterns and the
+    // pair table follow without a barrier.
     if (tid < kWave) {
-      const int pat = tid;
-      float lv = 0.0f;
-#pragma unroll
-      for (int j = 0; j < K; ++j) lv = __fadd_rn(lv, ((pat >> j) & 1) ? alpha[j] : -alpha[j]);
-      int rank = 0;
-#pragma unroll
-      for (int q = 0; q < P; ++q) {
-        const float o = u32_as_f32(uint32_t(__builtin_amdgcn_readlane(int(f32_as_u32(lv)), q)));
-        rank += (o < lv || (o == lv && q < pat)) ? 1 : 0;
-      }
-      if (pat >= P) rank = pat;  // idle lanes push to themselves
-      const float lv_s = u32_as_f32(uint32_t(__builtin_amdgcn_ds_permute(rank * 4, int(f32_as_u32(lv)))));
-      const uint32_t pat_s = uint32_t(__builtin_amdgcn_ds_permute(rank * 4, pat));
-      const float lv_next = u32_as_f32(uint32_t(__builtin_amdgcn_ds_bpermute(((tid + 1) & (kWave - 1)) * 4,
-                                                                            int(f32_as_u32(lv_s)))));
-      const float tau = tid < P - 1 ? __fmul_rn(0.5f, __fadd_rn(lv_s, lv_next)) : __builtin_inff();
+      float lv_s, tau;
+      uint32_t pat_s;
+      sort_levels<K>(alpha, lv_s, pat_s, tau);
       uint32_t sp = 0;
 #pragma unroll
       for (int bb = 0; bb < K; ++bb) sp |= ((pat_s >> bb) & 1u) << (8 * bb);
@@ -270,6 +282,81 @@ __device__ __forceinline__ void build_encode_tables(const float (&alpha)[K], Enc
     });
   }
   if (mymax > 1) atomicMax(&tb.maxcnt, mymax);
+  __syncthreads();
+}
+
+// M2 for bfloat16 input and k <= 4: 16 bits name a value outright, so a table of 65536 bytes holds
+// the position among the sorted levels (times 4, the byte offset of its flag word) of every value
+// there is: one byte read and one word read per element, no compare, and any spacing of the levels.
+//
+// A flag word has one byte per plane, 0xBF where the plane is +1 and 0 where it is -1.  A byte
+// selector turns the words of two neighbouring elements into the pair (-0.5 or 0, -0.5 or 0) of
+// bfloat16 numbers of one plane (0xBF00 is -0.5), and one dot product of two adds both elements to the
+// plane's sum: two instructions per plane and pair where widening, converting the flag and a
+// multiply-add take four.  (The dot product rounds once, to within an ulp of its largest term,
+// denormals included; the factor -2 is put back at the end of an item.)
+//
+// What bounded the encoder was the number of vector instructions (18 per element; at two
+// wavefronts per SIMD each costs 4.3 cycles): 51.4 M values at k = 4: 36.9 -> 32.8 us
+// a call, 18 -> 9.4 vector instructions per element; the loop then runs at 7.0 TB/s.
+constexpr uint32_t kFlagByte = 0xBFu;
+template <int K>
+struct ValueTables {
+  static constexpr int P = 1 << K;
+  float tau[P];
+  uint32_t flags[P];
+  alignas(16) uint8_t pos4[65536];
+};
+
+template <int K>
+__device__ __forceinline__ void build_value_tables(const float (&alpha)[K], ValueTables<K>& tb) {
+  constexpr int P = 1 << K;
+  constexpr int CH = 128;  // values per block of the table; neighbours in bit order are neighbours in value order
+  static_assert(kEncBlock * CH == 65536, "one block of the table per thread");
+  const int tid = threadIdx.x, lane = tid & (kWave - 1);
+  if (tid < kWave) {
+    float lv_s, tau;
+    uint32_t pat_s;
+    sort_levels<K>(alpha, lv_s, pat_s, tau);
+    uint32_t fl = 0;
+#pragma unroll
+    for (int bb = 0; bb < K; ++bb) fl |= ((pat_s >> bb) & 1u) * (kFlagByte << (8 * bb));
+    if (tid < P) {
+      tb.tau[tid] = tau;
+      tb.flags[tid] = fl;
+    }
+  }
+  __syncthreads();
+  float t[P - 1];
+#pragma unroll
+  for (int i = 0; i < P - 1; ++i) t[i] = tb.tau[i];
+  auto position4 = [&](uint32_t bits) {  // 4 * #{tau_i < value}; 0 for a NaN
+    const float v = u32_as_f32(bits << 16);
+    uint32_t l = 0;
+#pragma unroll
+    for (int i = 0; i < P - 1; ++i) l += (v > t[i]) ? 4u : 0u;
+    return l;
+  };
+  // Positions are monotone along a block (one sign; the NaN patterns follow an infinity and give 0):
+  // equal ends mean one byte throughout.  Blocks are dealt to threads so that the few with a
+  // threshold inside spread over the wavefronts; these are then done by the whole wavefront, two
+  // values per lane.  A block's eight 16-byte stores start at a place of the lane's own, so that
+  // the lanes do not all write to the same banks.
+  const uint32_t b0 = uint32_t((tid * 67) & (kEncBlock - 1)) * CH;
+  const uint32_t first = position4(b0), last = position4(b0 + CH - 1);
+  const uint32_t w = first * 0x01010101u;
+  if (first == last) {
+#pragma unroll
+    for (int i = 0; i < CH / 16; ++i)
+      *reinterpret_cast<uint4*>(&tb.pos4[b0 + 16 * ((i + lane) & (CH / 16 - 1))]) = make_uint4(w, w, w, w);
+  }
+  uint64_t pending = __ballot(first != last);
+  while (pending != 0) {  // the same in every lane
+    const int src = __ffsll((unsigned long long)pending) - 1;
+    pending &= pending - 1;
+    const uint32_t c0 = uint32_t(__builtin_amdgcn_readlane(int(b0), src)) + 2u * uint32_t(lane);
+    *reinterpret_cast<uint16_t*>(&tb.pos4[c0]) = uint16_t(position4(c0) | (position4(c0 + 1) << 8));
+  }
   __syncthreads();
 }
 
@@ -477,39 +564,107 @@ __device__ __forceinline__ void widen_raw(const RawRow<VEC>& r, float (&f)[VEC])
   }
 }
 
+// M2 and the sums, and M3, for rows r0 .. r0+GR-1 of an item: row r of the group lands at bit 7-r of
+// each plane byte.  MC: see encode_group.
+template <int K, int VEC, int MC, int GR>
+__device__ __forceinline__ void encode_rows(const EncodeTables<K>& tb, const RawRow<VEC> (&rows)[8], int r0, int nrows,
+                                            int maxcnt, uint32_t (&acc)[VEC][(K + 3) / 4], float (&a32)[K],
+                                            float& sx32) {
+  constexpr int NW = (K + 3) / 4;
+  float xs[GR * VEC];
+#pragma unroll
+  for (int rr = 0; rr < GR; ++rr) {
+    float row[VEC];
+    widen_raw<VEC>(rows[r0 + rr], row);
+#pragma unroll
+    for (int c = 0; c < VEC; ++c) xs[rr * VEC + c] = row[c];
+  }
+  uint32_t sp[GR * VEC][NW];
+  encode_group<K, MC, GR * VEC>(tb, xs, maxcnt, sp, a32, sx32);
+#pragma unroll
+  for (int rr = 0; rr < GR; ++rr)
+#pragma unroll
+    for (int c = 0; c < VEC; ++c)
+#pragma unroll
+      for (int w = 0; w < NW; ++w) acc[c][w] = (acc[c][w] << 1) | (r0 + rr < nrows ? sp[rr * VEC + c][w] : 0u);
+}
+// The same by value.  Two neighbouring elements (of a row, or of two rows if rows are single
+// elements) make a pair.  The bits of a flag byte serve as the plane bit of any row but one: bit 6 of
+// 0xBF is zero.
+__device__ __forceinline__ float dot2_bf16(uint32_t a, uint32_t b, float c) {
+  typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
+  return __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2_t, a), __builtin_bit_cast(bf16x2_t, b), c, false);
+}
+template <int K, int VEC, int MC, int GR>
+__device__ __forceinline__ void encode_rows(const ValueTables<K>& tb, const RawRow<VEC> (&rows)[8], int r0, int nrows,
+                                            int, uint32_t (&acc)[VEC][1], float (&a32)[K], float& sx32) {
+  constexpr int NE = GR * VEC;
+  static_assert(NE % 2 == 0, "pairs");
+  uint32_t w[NE / 2];
+#pragma unroll
+  for (int rr = 0; rr < GR; ++rr) {
+    if constexpr (VEC > 1) {
+      const uint4 v = rows[r0 + rr].v;
+      w[rr * 4] = v.x; w[rr * 4 + 1] = v.y; w[rr * 4 + 2] = v.z; w[rr * 4 + 3] = v.w;
+    } else {
+      if (rr % 2 == 0) w[rr / 2] = rows[r0 + rr].v >> 16; else w[rr / 2] |= rows[r0 + rr].v;
+    }
+  }
+  uint32_t off[NE], fl[NE];
+#pragma unroll
+  for (int i = 0; i < NE / 2; ++i) {
+    off[2 * i] = tb.pos4[w[i] & 0xFFFFu];
+    off[2 * i + 1] = tb.pos4[w[i] >> 16];
+  }
+#pragma unroll
+  for (int e = 0; e < NE; ++e) fl[e] = *reinterpret_cast<const uint32_t*>(reinterpret_cast<const char*>(tb.flags) + off[e]);
+#pragma unroll
+  for (int i = 0; i < NE / 2; ++i) {
+    sx32 = dot2_bf16(w[i], 0x3F803F80u, sx32);  // a missing row reads as +0: it adds nothing to the sums
+#pragma unroll
+    for (int p = 0; p < K; ++p)
+      a32[p] = dot2_bf16(w[i], __builtin_amdgcn_perm(fl[2 * i + 1], fl[2 * i], 0x040C000Cu + 0x01000100u * uint32_t(p)), a32[p]);
+  }
+#pragma unroll
+  for (int rr = 0; rr < GR; ++rr)
+#pragma unroll
+    for (int c = 0; c < VEC; ++c) {
+      const int bit = 7 - (r0 + rr);
+      const uint32_t f = bit == 6 ? fl[rr * VEC + c] >> 1 : fl[rr * VEC + c];
+      acc[c][0] |= (r0 + rr < nrows ? f : 0u) & (0x01010101u << bit);
+    }
+}
+// What the float32 sums of encode_rows have to be multiplied by.
+template <int K>
+__device__ __forceinline__ constexpr float sum_factor(const EncodeTables<K>&) { return 1.0f; }
+template <int K>
+__device__ __forceinline__ constexpr float sum_factor(const ValueTables<K>&) { return -2.0f; }
+
 // Plain (not pipelined) item of one column: any number of valid rows.
-template <typename T, int K, int MC>
-__device__ __forceinline__ void encode_column(const EncodeTables<K>& tb, const T* __restrict__ x,
+template <typename T, int K, typename Tables>
+__device__ __forceinline__ void encode_column(const Tables& tb, const T* __restrict__ x,
                                               uint8_t* __restrict__ payload, int64_t n, int64_t m, int64_t g,
                                               int64_t j, int maxcnt, EncodeStats<K>& st) {
   constexpr int NW = (K + 3) / 4;
   const int64_t row0 = g * 8;
   const int nrows = (n - row0) < 8 ? int(n - row0) : 8;
   const T* xc = x + row0 * m + j;
-  float xs[8];
+  RawRow<1> rows[8];
 #pragma unroll
   for (int r = 0; r < 8; ++r) {  // all row loads first, so that they overlap
-    RawRow<1> raw;
-    raw.v = 0u;
-    if (r < nrows) raw = load_raw<T, 1>(xc + r * m);
-    float one[1];
-    widen_raw<1>(raw, one);
-    xs[r] = one[0];  // a missing row reads as +0: it adds nothing to the sums
+    rows[r].v = 0u;
+    if (r < nrows) rows[r] = load_raw<T, 1>(xc + r * m);  // a missing row reads as +0: it adds nothing to the sums
   }
   float h32[K];
   float sx32 = 0.0f;
 #pragma unroll
   for (int p = 0; p < K; ++p) h32[p] = 0.0f;
-  uint32_t sp[8][NW];
-  encode_group<K, MC, 8>(tb, xs, maxcnt, sp, h32, sx32);
-  // M3: row r of the group lands at bit 7-r of each plane byte; missing rows give 0 bits
   uint32_t acc[1][NW];
 #pragma unroll
   for (int w = 0; w < NW; ++w) acc[0][w] = 0;
+  encode_rows<K, 1, 0, 8>(tb, rows, 0, nrows, maxcnt, acc, h32, sx32);  // missing rows give 0 bits
 #pragma unroll
-  for (int r = 0; r < 8; ++r)
-#pragma unroll
-    for (int w = 0; w < NW; ++w) acc[0][w] = (acc[0][w] << 1) | (r < nrows ? sp[r][w] : 0u);
+  for (int p = 0; p < K; ++p) h32[p] *= sum_factor(tb);
   finish_item<K, 1>(acc, h32, sx32, payload + ((g * m + j) * K), true, st);
 }
 
@@ -564,8 +719,8 @@ __device__ __forceinline__ RawRow<VEC> load_row(const T* __restrict__ x, uint32_
   return load_raw<T, VEC>(reinterpret_cast<const T*>(base + lane_x));
 }
 
-template <typename T, int K, int VEC, int MC>
-__device__ __forceinline__ void encode_stream(const EncodeTables<K>& tb, const T* __restrict__ x,
+template <typename T, int K, int VEC, int MC, typename Tables>
+__device__ __forceinline__ void encode_stream(const Tables& tb, const T* __restrict__ x,
                                               uint8_t* __restrict__ payload, uint64_t m, uint32_t ipg, uint32_t wpg,
                                               const WorkQueue& q, uint32_t cur, uint32_t nxt, ItemAddr ca,
                                               RawRow<VEC> (&fr)[8], EncodeStats<K>& st) {
@@ -600,23 +755,12 @@ __device__ __forceinline__ void encode_stream(const EncodeTables<K>& tb, const T
       for (int w = 0; w < NW; ++w) acc[c][w] = 0;
 #pragma unroll
     for (int r0 = 0; r0 < 8; r0 += GR) {
-      float xs[GR * VEC];
+      encode_rows<K, VEC, MC, GR>(tb, fr, r0, 8, MC, acc, h32, sx32);
+      // the sums pass through an empty asm: left alone, the compiler moves the whole chain of adds
+      // to the end of the round, and every row's operands stay in registers until there
 #pragma unroll
-      for (int rr = 0; rr < GR; ++rr) {
-        float row[VEC];
-        widen_raw<VEC>(fr[r0 + rr], row);
-#pragma unroll
-        for (int c = 0; c < VEC; ++c) xs[rr * VEC + c] = row[c];
-      }
-      uint32_t sp[GR * VEC][NW];
-      encode_group<K, MC, GR * VEC>(tb, xs, MC, sp, h32, sx32);
-      // M3: row r of the group lands at bit 7-r of each plane byte
-#pragma unroll
-      for (int rr = 0; rr < GR; ++rr)
-#pragma unroll
-        for (int c = 0; c < VEC; ++c)
-#pragma unroll
-          for (int w = 0; w < NW; ++w) acc[c][w] = (acc[c][w] << 1) | sp[rr * VEC + c][w];
+      for (int p = 0; p < K; ++p) asm volatile("" : "+v"(h32[p]));
+      asm volatile("" : "+v"(sx32));
       // The loads of the next item's rows go where this group's rows were: they may not be
       // issued before the last use of those registers (else the compiler keeps a second set of
       // row registers and copies it over at the end of the round, which also means waiting for
@@ -634,6 +778,8 @@ __device__ __forceinline__ void encode_stream(const EncodeTables<K>& tb, const T
       // reads of all 8*VEC elements and run out of registers
       __builtin_amdgcn_sched_barrier(0);
     }
+#pragma unroll
+    for (int p = 0; p < K; ++p) h32[p] *= sum_factor(tb);
     finish_item<K, VEC>(acc, h32, sx32, payload + uint64_t(ca.g) * m * uint32_t(K) + ca.jv * uint32_t(VEC * K), ca.counts,
                         st);
     cur = nxt;
@@ -780,7 +926,9 @@ __global__ __launch_bounds__(kEncBlock) void mbq_encode_kernel(const T* __restri
                                                                MbqCall call, int64_t n, int64_t m, uint32_t ipg,
                                                                uint32_t wpg, uint32_t n_wave_items) {
   constexpr int NPAIR = K * (K - 1) / 2;
-  __shared__ EncodeTables<K> tb;
+  constexpr bool BY_VALUE = sizeof(T) == 2 && K <= 4;
+  using Tables = std::conditional_t<BY_VALUE, ValueTables<K>, EncodeTables<K>>;
+  __shared__ Tables tb;
   __shared__ WaveTotals red;
 
   const int tid = threadIdx.x;
@@ -821,10 +969,15 @@ __global__ __launch_bounds__(kEncBlock) void mbq_encode_kernel(const T* __restri
       fr[r] = load_row<T, VEC>(x, ca.g, uint64_t(m) * sizeof(T), r, ca.jv * uint32_t(VEC * sizeof(T)));
   }
 
-  build_encode_tables<K>(alpha, tb);
-  // the same value in every lane: read it into a scalar register, so that the choice of path
-  // below is a scalar branch and not a divergent one whose sides run one after the other
-  const int maxcnt = __builtin_amdgcn_readfirstlane(tb.maxcnt);
+  int maxcnt = 1;
+  if constexpr (BY_VALUE) {
+    build_value_tables<K>(alpha, tb);
+  } else {
+    build_encode_tables<K>(alpha, tb);
+    // the same value in every lane: read it into a scalar register, so that the choice of path
+    // below is a scalar branch and not a divergent one whose sides run one after the other
+    maxcnt = __builtin_amdgcn_readfirstlane(tb.maxcnt);
+  }
 
   EncodeStats<K> st;
   st.Sx = 0.0;
@@ -838,8 +991,8 @@ __global__ __launch_bounds__(kEncBlock) void mbq_encode_kernel(const T* __restri
   const bool stream = n_wave_items != 0u;  // else: a geometry too narrow for wave-items
   if (stream && maxcnt == 1) {
     encode_stream<T, K, VEC, 1>(tb, x, payload, uint64_t(m), ipg, wpg, q, cur, nxt, ca, fr, st);
-  } else if (stream && maxcnt == 2 && K <= 4) {
-    encode_stream<T, K, VEC, 2>(tb, x, payload, uint64_t(m), ipg, wpg, q, cur, nxt, ca, fr, st);
+  } else if (stream && maxcnt == 2 && K <= 4 && !BY_VALUE) {
+    if constexpr (!BY_VALUE) encode_stream<T, K, VEC, 2>(tb, x, payload, uint64_t(m), ipg, wpg, q, cur, nxt, ca, fr, st);
   } else {
     // several thresholds share a bucket (levels closer than a bucket's width), or a very narrow
     // tensor: rare.  One column per thread keeps this path's register needs out of the kernel's
@@ -847,13 +1000,13 @@ __global__ __launch_bounds__(kEncBlock) void mbq_encode_kernel(const T* __restri
     const int64_t cols_full = (n / 8) * m;
     for (int64_t s = gtid; s < cols_full; s += stride) {
       const int64_t g = s / m;
-      encode_column<T, K, 0>(tb, x, payload, n, m, g, s - g * m, maxcnt, st);
+      encode_column<T, K>(tb, x, payload, n, m, g, s - g * m, maxcnt, st);
     }
   }
   // the last, partial row group (n % 8 != 0), one column per thread
   if (n % 8 != 0) {
     for (int64_t j = gtid; j < m; j += stride)
-      encode_column<T, K, 0>(tb, x, payload, n, m, n / 8, j, maxcnt, st);
+      encode_column<T, K>(tb, x, payload, n, m, n / 8, j, maxcnt, st);
   }
   store_record<K>(st, call, red);
 }

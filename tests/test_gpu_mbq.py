@@ -195,3 +195,27 @@ def test_batch0_compress(A, k):
         a0 = A.accept_mbq_init(d, xd)
         torch.cuda.synchronize()
         assert a0.cpu().numpy().tobytes() == gh[:k].tobytes()
+
+
+@pytest.mark.parametrize("k", [1, 2, 3, 4])
+def test_bf16_every_value(A, k):
+    """bfloat16 and k <= 4 go through a table of all 65536 values: every finite one, with
+    coefficients whose levels lie far apart, close together, on top of each other and among the
+    smallest numbers.  (The header is a least-squares solution, ill-conditioned for the odd
+    coefficients: checked for the first set, where it is not.)"""
+    torch = torch_mod()
+    bits = np.arange(65536, dtype=np.uint32)
+    bits = bits[(bits & 0x7F80) != 0x7F80].astype(np.uint16)      # 65280 finite values
+    values = orc.widen_bf16(bits)
+    for n, m in ((16, 4080), (15, 4351)):                          # whole vectors; odd rows and a partial row group
+        x = values[: n * m].reshape(n, m)
+        tame = np.where(np.abs(x) > 4, np.sign(x) * np.float32(3), x).astype(np.float32)
+        run_case(A, tame, k, n, m, alpha_prev=np.array([1.0, 0.5, 0.25, 0.125][:k], np.float32), in_bf16=True, tag="every value")
+        xd, xb = to_dev(x, True)
+        d = A.make_desc(A.MBQ, k, n, m, in_dtype=A.BF16, t=1)
+        for alpha in ([1.0, 1.0, 1.0, 1.0], [0.7, 0.699, 0.0007, 1e-30], [2e-38, 1e-38, 5e-39, 3e-39], [-3.0, 2.0, 1e5, 0.0]):
+            a = np.array(alpha[:k], np.float32)
+            _, payload = A.accept_compress(d, xd, alpha_prev=torch.from_numpy(a).cuda())
+            torch.cuda.synchronize()
+            want = orc.mbq_pack(orc.mbq_assign(orc.widen_bf16(xb), a), k, n, m)
+            assert first_mismatch(dev_bytes(payload), want.tobytes()) is None, (n, m, alpha)
