@@ -276,6 +276,17 @@ __device__ __forceinline__ double wave_sum(double v) {
   return (r0 + r1) + (r2 + r3);
 }
 
+// The same for counts (exact in any order; the sum of 16 lanes has to fit 32 bits).
+__device__ __forceinline__ uint64_t wave_sum(uint32_t v) {
+  v += dpp_u32<kDppQuadSwap1>(v);
+  v += dpp_u32<kDppQuadSwap2>(v);
+  v += dpp_u32<kDppRowHalfMirror>(v);
+  v += dpp_u32<kDppRowMirror>(v);
+  const uint64_t r0 = uint32_t(__builtin_amdgcn_readlane(int(v), 0)), r1 = uint32_t(__builtin_amdgcn_readlane(int(v), 16));
+  const uint64_t r2 = uint32_t(__builtin_amdgcn_readlane(int(v), 32)), r3 = uint32_t(__builtin_amdgcn_readlane(int(v), 48));
+  return (r0 + r1) + (r2 + r3);
+}
+
 // Loads and stores that are coherent across the whole device although every group of compute
 // units has a second-level cache of its own: they go through to memory instead of staying in
 // (or being served from) that cache.  For the few words workgroups hand to each other inside

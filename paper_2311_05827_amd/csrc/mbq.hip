@@ -468,22 +468,70 @@ __device__ __forceinline__ void encode_group(const EncodeTables<K>& tb, const fl
   }
 }
 
+// Bytes of two words: byte i of the result is byte s_i of {hi, lo} (0-3: lo, 4-7: hi).
+template <int S0, int S1, int S2, int S3>
+__device__ __forceinline__ uint32_t bytes_of(uint32_t hi, uint32_t lo) {
+  return __builtin_amdgcn_perm(hi, lo, uint32_t(S0) | uint32_t(S1) << 8 | uint32_t(S2) << 16 | uint32_t(S3) << 24);
+}
+// The k <= 4 plane bytes of four columns (byte p of a[c]): as they lie in the payload (column after
+// column, k bytes each), and plane by plane (byte c of planes[p]).  Written as byte selections: from
+// shifts and masks the compiler makes two to three times as many instructions, and an item has
+// only 32 or 64 elements to share them.
+template <int K>
+__device__ __forceinline__ void columns_to_payload(const uint32_t* a, uint32_t* out) {
+  if constexpr (K == 1) {
+    out[0] = bytes_of<0, 1, 4, 5>(bytes_of<0, 4, 0, 0>(a[3], a[2]), bytes_of<0, 4, 0, 0>(a[1], a[0]));
+  } else if constexpr (K == 2) {
+    out[0] = bytes_of<0, 1, 4, 5>(a[1], a[0]);
+    out[1] = bytes_of<0, 1, 4, 5>(a[3], a[2]);
+  } else if constexpr (K == 3) {
+    out[0] = bytes_of<0, 1, 2, 4>(a[1], a[0]);
+    out[1] = bytes_of<1, 2, 4, 5>(a[2], a[1]);
+    out[2] = bytes_of<2, 4, 5, 6>(a[3], a[2]);
+  } else {
+#pragma unroll
+    for (int c = 0; c < 4; ++c) out[c] = a[c];
+  }
+}
+template <int K>
+__device__ __forceinline__ void columns_to_planes(const uint32_t* a, uint32_t (&planes)[K]) {
+  const uint32_t lo01 = bytes_of<0, 4, 1, 5>(a[1], a[0]), lo23 = bytes_of<0, 4, 1, 5>(a[3], a[2]);
+  planes[0] = bytes_of<0, 1, 4, 5>(lo23, lo01);
+  if constexpr (K > 1) planes[1] = bytes_of<2, 3, 6, 7>(lo23, lo01);
+  if constexpr (K > 2) {
+    const uint32_t hi01 = bytes_of<2, 6, 3, 7>(a[1], a[0]), hi23 = bytes_of<2, 6, 3, 7>(a[3], a[2]);
+    planes[2] = bytes_of<0, 1, 4, 5>(hi23, hi01);
+    if constexpr (K > 3) planes[3] = bytes_of<2, 3, 6, 7>(hi23, hi01);
+  }
+}
+
 // End of an item: bit counts from the finished plane bytes, payload store, float32 partial
 // sums (at most 8*VEC terms) folded into the thread's float64 sums.  A lane whose item lies
 // beyond its row group (the ragged end of the last wave-item of a group) carries a copy of the
 // group's last item: it stores the same bytes to the same place and counts nothing.
 template <int K, int VEC>
-__device__ __forceinline__ void finish_item(const uint32_t (&acc)[VEC][(K + 3) / 4], const float (&h32)[K], float sx32,
+__device__ __forceinline__ void finish_item(const uint32_t (&acc)[VEC][(K + 3) / 4], float (&h32)[K], float sx32,
                                             uint8_t* __restrict__ dst, bool counts, EncodeStats<K>& st) {
   constexpr int NDW = (VEC * K + 3) / 4;
   constexpr int CW = (VEC + 3) / 4;
+  constexpr bool SELECT = VEC > 1 && K <= 4;  // by byte selections, four columns at a time
+  uint32_t pw[K][CW];  // plane bytes of all VEC columns, plane-major
   // payload: byte ((g*m + j)*K + p); the item's VEC*K bytes are contiguous
-  if constexpr (VEC > 1) {
+  if constexpr (SELECT) {
     uint32_t out[NDW];
-    if constexpr (K == 4) {
 #pragma unroll
-      for (int c = 0; c < VEC; ++c) out[c] = acc[c][0];
-    } else {
+    for (int w = 0; w < CW; ++w) {
+      const uint32_t a[4] = {acc[4 * w][0], acc[4 * w + 1][0], acc[4 * w + 2][0], acc[4 * w + 3][0]};
+      columns_to_payload<K>(a, &out[K * w]);
+      uint32_t planes[K];
+      columns_to_planes<K>(a, planes);
+#pragma unroll
+      for (int p = 0; p < K; ++p) pw[p][w] = planes[p];
+    }
+    store_dwords_stream<NDW>(reinterpret_cast<uint32_t*>(dst), out);
+  } else {
+    if constexpr (VEC > 1) {
+      uint32_t out[NDW];
 #pragma unroll
       for (int w = 0; w < NDW; ++w) out[w] = 0;
 #pragma unroll
@@ -493,25 +541,28 @@ __device__ __forceinline__ void finish_item(const uint32_t (&acc)[VEC][(K + 3) /
           const int b = c * K + p;
           out[b / 4] |= ((acc[c][p / 4] >> (8 * (p % 4))) & 0xFFu) << (8 * (b % 4));
         }
+      store_dwords_stream<NDW>(reinterpret_cast<uint32_t*>(dst), out);
+    } else {
+#pragma unroll
+      for (int p = 0; p < K; ++p) dst[p] = uint8_t(acc[0][p / 4] >> (8 * (p % 4)));
     }
-    store_dwords_stream<NDW>(reinterpret_cast<uint32_t*>(dst), out);
-  } else {
 #pragma unroll
-    for (int p = 0; p < K; ++p) dst[p] = uint8_t(acc[0][p / 4] >> (8 * (p % 4)));
+    for (int p = 0; p < K; ++p) {
+#pragma unroll
+      for (int w = 0; w < CW; ++w) pw[p][w] = 0;
+#pragma unroll
+      for (int c = 0; c < VEC; ++c) pw[p][c / 4] |= ((acc[c][p / 4] >> (8 * (p % 4))) & 0xFFu) << (8 * (c % 4));
+    }
   }
-  // (selects, not a branch around the sums: with a branch the compiler moves the whole chain of
-  // per-element adds of the item behind it, to the end of the round, and every row of x then
-  // has to stay in registers until there)
-  const uint32_t keep = counts ? 0xFFFFFFFFu : 0u;
-  uint32_t pw[K][CW];  // plane bytes of all VEC columns, plane-major
+  if (__ballot(!counts) != 0) {  // a scalar branch, taken at the ragged end of a row group only
+    const uint32_t keep = counts ? 0xFFFFFFFFu : 0u;
 #pragma unroll
-  for (int p = 0; p < K; ++p) {
+    for (int p = 0; p < K; ++p) {
+      h32[p] = counts ? h32[p] : 0.0f;
 #pragma unroll
-    for (int w = 0; w < CW; ++w) pw[p][w] = 0;
-#pragma unroll
-    for (int c = 0; c < VEC; ++c) pw[p][c / 4] |= ((acc[c][p / 4] >> (8 * (p % 4))) & 0xFFu) << (8 * (c % 4));
-#pragma unroll
-    for (int w = 0; w < CW; ++w) pw[p][w] &= keep;
+      for (int w = 0; w < CW; ++w) pw[p][w] &= keep;
+    }
+    sx32 = counts ? sx32 : 0.0f;
   }
   {
     int pi = 0;
@@ -527,9 +578,9 @@ __device__ __forceinline__ void finish_item(const uint32_t (&acc)[VEC][(K + 3) /
       }
     }
   }
-  st.Sx += double(counts ? sx32 : 0.0f);
+  st.Sx += double(sx32);
 #pragma unroll
-  for (int p = 0; p < K; ++p) st.H[p] += double(counts ? h32[p] : 0.0f);
+  for (int p = 0; p < K; ++p) st.H[p] += double(h32[p]);
 }
 
 // One row's share of an item as it comes from memory: VEC elements in a 16-byte vector, or a
@@ -870,47 +921,62 @@ struct MbqCall {
 };
 
 // End of an encode kernel (M4): the workgroup adds up its threads' statistics in a fixed order
-// and stores one record.
+// and stores one record.  The counts are added as integers: 8 instructions per statistic and
+// wavefront instead of 30 (a thread's counts stay below 2^28: a thread sees a few parts in 2^17 of
+// the tensor), which at k = 4 are 10 of the 15.
 template <int K>
 __device__ __forceinline__ void store_record(const EncodeStats<K>& st, const MbqCall& call, WaveTotals& buf) {
   constexpr int NPAIR = K * (K - 1) / 2;
   constexpr int NSTAT = nstat_of(K);
-  double sv[NSTAT];
+  const int tid = threadIdx.x, wave = tid / kWave, lane = tid & (kWave - 1);
+  const int nwaves = (blockDim.x + kWave - 1) / kWave;
+  double* mine = buf.v[wave];
 #pragma unroll
-  for (int p = 0; p < K; ++p) sv[p] = st.H[p];
-  sv[K] = st.Sx;
+  for (int p = 0; p < K; ++p) {
+    const double h = wave_sum(st.H[p]);
+    const double c = double(wave_sum(st.cnt[p]));
+    if (lane == 0) { mine[p] = h; mine[K + 1 + p] = c; }
+  }
+  const double sx = wave_sum(st.Sx);
+  if (lane == 0) mine[K] = sx;
 #pragma unroll
-  for (int p = 0; p < K; ++p) sv[K + 1 + p] = double(st.cnt[p]);
-#pragma unroll
-  for (int i = 0; i < NPAIR; ++i) sv[2 * K + 1 + i] = double(st.dis[i]);
-  const double total = block_sum_stats<NSTAT>(sv, buf);
-  if (threadIdx.x < NSTAT) call.records[int64_t(threadIdx.x) * gridDim.x + blockIdx.x] = total;
+  for (int i = 0; i < NPAIR; ++i) {
+    const double d = double(wave_sum(st.dis[i]));
+    if (lane == 0) mine[2 * K + 1 + i] = d;
+  }
+  __syncthreads();
+  if (tid < NSTAT) {
+    double total = buf.v[0][tid];
+    for (int w = 1; w < nwaves; ++w) total += buf.v[w][tid];
+    call.records[int64_t(tid) * gridDim.x + blockIdx.x] = total;
+  }
 }
 
-// M5, one workgroup: thread b takes records b, b + 256, ... of every statistic (all loads of a
-// round issued before their adds), the workgroup adds them up in the same fixed order, one
-// thread solves and writes the header.
+// M5, one workgroup of 16 wavefronts: wavefront w takes the statistics w, w + 16, ... (their records
+// lie together), lane l the records l, l + 64, ..., one wavefront sum per statistic; one thread
+// solves and writes the header.  (With four wavefronts that each added up their share of every
+// statistic the sums alone took 1.9 of the kernel's 3.7 us at k = 4.)
+constexpr int kFinalizeBlock = 1024;
 template <int K>
-__global__ __launch_bounds__(kBlock) void mbq_finalize_kernel(MbqCall call, int nrec) {
+__global__ __launch_bounds__(kFinalizeBlock) void mbq_finalize_kernel(MbqCall call, int nrec) {
   constexpr int NSTAT = nstat_of(K);
-  __shared__ WaveTotals red;
   __shared__ double tot[48];
-  const int tid = threadIdx.x;
+  const int tid = threadIdx.x, wave = tid / kWave, lane = tid & (kWave - 1);
   float alpha_prev[K];  // asked for together with the records: the solve at the end would otherwise wait for them
 #pragma unroll
   for (int p = 0; p < K; ++p) alpha_prev[p] = call.alpha_prev[p];
-  double a[NSTAT];
+  for (int s = wave; s < NSTAT; s += kFinalizeBlock / kWave) {
+    const double* rec = call.records + int64_t(s) * nrec;
+    double a = 0.0;
+    for (int b = lane; b < nrec; b += 4 * kWave) {  // four loads in flight
+      double v[4];
 #pragma unroll
-  for (int s = 0; s < NSTAT; ++s) a[s] = 0.0;
-  for (int b = tid; b < nrec; b += kBlock) {
-    double v[NSTAT];
-#pragma unroll
-    for (int s = 0; s < NSTAT; ++s) v[s] = call.records[int64_t(s) * nrec + b];
-#pragma unroll
-    for (int s = 0; s < NSTAT; ++s) a[s] += v[s];
+      for (int u = 0; u < 4; ++u) v[u] = b + u * kWave < nrec ? rec[b + u * kWave] : 0.0;
+      a += (v[0] + v[1]) + (v[2] + v[3]);
+    }
+    a = wave_sum(a);
+    if (lane == 0) tot[s] = a;
   }
-  const double total = block_sum_stats<NSTAT>(a, red);
-  if (tid < NSTAT) tot[tid] = total;
   if (tid < kMaxGroups) call.counters[tid * kCounterStride] = 0u;  // the encode kernel's work counters, for the next call
   __syncthreads();
   if (tid == 0) solve_and_write_header<K>(tot, alpha_prev, call.n_elems, call.beta, call.header);
@@ -1588,7 +1654,7 @@ hipError_t launch_mbq_compress(const accept_desc& d, const MPlan& p, const void*
   mark(tm, s);
 #define ACCEPT_FIN(KK)                                                                          \
   case KK:                                                                                      \
-    hipLaunchKernelGGL(mbq_finalize_kernel<KK>, dim3(1), dim3(kBlock), 0, s, call, nrec);       \
+    hipLaunchKernelGGL(mbq_finalize_kernel<KK>, dim3(1), dim3(kFinalizeBlock), 0, s, call, nrec); \
     break;
   switch (d.bits) {
     ACCEPT_FIN(1) ACCEPT_FIN(2) ACCEPT_FIN(3) ACCEPT_FIN(4) ACCEPT_FIN(5) ACCEPT_FIN(6) ACCEPT_FIN(7) ACCEPT_FIN(8)
