@@ -93,8 +93,10 @@ hipError_t launch_uniform_decompress(const accept_desc& d, const void* header, c
 struct MPlan {
   int vec;                // columns per work item: 16-byte vectors when rows stay 16-byte aligned, else 1
   int64_t G;              // ceil(n/8) row groups
+  bool ragged;            // rows are not whole 16-byte vectors: vectors at any alignment, then m % vec single columns
   int64_t items;          // G * (m / vec)
-  bool stream;            // complete row groups go through the pipelined wave-item stream
+  bool wide;              // a row group holds at least one full wave-item
+  bool stream;            // wide, and complete row groups exist: they go through the pipelined stream
   uint32_t wpg;           // wave-items (64 items) per row group
   uint32_t n_wave_items;  // of the complete row groups
   int grid;               // workgroups of the encode kernel = number of partial-sum records
@@ -132,6 +134,18 @@ __device__ __forceinline__ uint4 load16_stream(const void* p) {
 __device__ __forceinline__ void store16_stream(void* p, uint4 v) {
   const v4u_t u = {v.x, v.y, v.z, v.w};
   __builtin_nontemporal_store(u, reinterpret_cast<v4u_t*>(p));
+}
+
+// The same for rows that start at any element.  (Vector memory takes any alignment; the 64 lanes'
+// contiguous kilobyte then touches nine cache lines instead of eight.)
+typedef uint32_t v4u_any_t __attribute__((ext_vector_type(4), aligned(2)));
+__device__ __forceinline__ uint4 load16_stream_any(const void* p) {
+  const v4u_any_t v = __builtin_nontemporal_load(reinterpret_cast<const v4u_any_t*>(p));
+  return make_uint4(v.x, v.y, v.z, v.w);
+}
+__device__ __forceinline__ void store16_stream_any(void* p, uint4 v) {
+  const v4u_any_t u = {v.x, v.y, v.z, v.w};
+  __builtin_nontemporal_store(u, reinterpret_cast<v4u_any_t*>(p));
 }
 
 // NDW consecutive dwords of payload (plain stores: streaming stores of the payload gained nothing),
@@ -190,18 +204,20 @@ __device__ __forceinline__ uint32_t bf16_rne(float f) {
   const uint32_t b = f32_as_u32(f);
   return (b + 0x7FFFu + ((b >> 16) & 1u)) >> 16;
 }
-// 16-byte vector store of decompressed values (streaming).
-__device__ __forceinline__ void store_vec(float* p, const float (&f)[4]) {
-  store16_stream(p, make_uint4(f32_as_u32(f[0]), f32_as_u32(f[1]), f32_as_u32(f[2]), f32_as_u32(f[3])));
+__device__ __forceinline__ uint4 narrow(const float (&f)[4]) {
+  return make_uint4(f32_as_u32(f[0]), f32_as_u32(f[1]), f32_as_u32(f[2]), f32_as_u32(f[3]));
 }
-__device__ __forceinline__ void store_vec(bf16_t* p, const float (&f)[8]) {
+__device__ __forceinline__ uint4 narrow(const float (&f)[8]) {
   uint4 v;
   v.x = bf16_rne(f[0]) | (bf16_rne(f[1]) << 16);
   v.y = bf16_rne(f[2]) | (bf16_rne(f[3]) << 16);
   v.z = bf16_rne(f[4]) | (bf16_rne(f[5]) << 16);
   v.w = bf16_rne(f[6]) | (bf16_rne(f[7]) << 16);
-  store16_stream(p, v);
+  return v;
 }
+// 16-byte vector store of decompressed values (streaming).
+__device__ __forceinline__ void store_vec(float* p, const float (&f)[4]) { store16_stream(p, narrow(f)); }
+__device__ __forceinline__ void store_vec(bf16_t* p, const float (&f)[8]) { store16_stream(p, narrow(f)); }
 __device__ __forceinline__ void store_one(float* p, float f) { *p = f; }
 __device__ __forceinline__ void store_one(bf16_t* p, float f) { p->bits = uint16_t(bf16_rne(f)); }
 

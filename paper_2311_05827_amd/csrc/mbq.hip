@@ -509,7 +509,7 @@ __device__ __forceinline__ void columns_to_planes(const uint32_t* a, uint32_t (&
 // sums (at most 8*VEC terms) folded into the thread's float64 sums.  A lane whose item lies
 // beyond its row group (the ragged end of the last wave-item of a group) carries a copy of the
 // group's last item: it stores the same bytes to the same place and counts nothing.
-template <int K, int VEC>
+template <int K, int VEC, bool RAGGED = false>
 __device__ __forceinline__ void finish_item(const uint32_t (&acc)[VEC][(K + 3) / 4], float (&h32)[K], float sx32,
                                             uint8_t* __restrict__ dst, bool counts, EncodeStats<K>& st) {
   constexpr int NDW = (VEC * K + 3) / 4;
@@ -528,7 +528,8 @@ __device__ __forceinline__ void finish_item(const uint32_t (&acc)[VEC][(K + 3) /
 #pragma unroll
       for (int p = 0; p < K; ++p) pw[p][w] = planes[p];
     }
-    store_dwords_stream<NDW>(reinterpret_cast<uint32_t*>(dst), out);
+    if constexpr (RAGGED) __builtin_memcpy(dst, out, sizeof(out));
+    else store_dwords_stream<NDW>(reinterpret_cast<uint32_t*>(dst), out);
   } else {
     if constexpr (VEC > 1) {
       uint32_t out[NDW];
@@ -541,7 +542,8 @@ __device__ __forceinline__ void finish_item(const uint32_t (&acc)[VEC][(K + 3) /
           const int b = c * K + p;
           out[b / 4] |= ((acc[c][p / 4] >> (8 * (p % 4))) & 0xFFu) << (8 * (b % 4));
         }
-      store_dwords_stream<NDW>(reinterpret_cast<uint32_t*>(dst), out);
+      if constexpr (RAGGED) __builtin_memcpy(dst, out, sizeof(out));
+      else store_dwords_stream<NDW>(reinterpret_cast<uint32_t*>(dst), out);
     } else {
 #pragma unroll
       for (int p = 0; p < K; ++p) dst[p] = uint8_t(acc[0][p / 4] >> (8 * (p % 4)));
@@ -594,10 +596,12 @@ template <>
 struct RawRow<1> {
   uint32_t v;
 };
-template <typename T, int VEC>
+template <typename T, int VEC, bool RAGGED = false>
 __device__ __forceinline__ RawRow<VEC> load_raw(const T* p) {
   RawRow<VEC> r;
-  if constexpr (VEC > 1) {
+  if constexpr (VEC > 1 && RAGGED) {
+    r.v = load16_stream_any(p);
+  } else if constexpr (VEC > 1) {
     r.v = load16_stream(p);  // every element of x is read once
   } else if constexpr (sizeof(T) == 4) {
     r.v = f32_as_u32(*reinterpret_cast<const float*>(p));
@@ -763,14 +767,14 @@ __device__ __forceinline__ ItemAddr item_addr(uint32_t w, uint32_t wpg, uint32_t
   return a;
 }
 // Row 8g + r of the item: the base is formed from scalars only; lane_x = jv * VEC * sizeof(T).
-template <typename T, int VEC>
+template <typename T, int VEC, bool RAGGED>
 __device__ __forceinline__ RawRow<VEC> load_row(const T* __restrict__ x, uint32_t g, uint64_t row_bytes, int r,
                                                 uint32_t lane_x) {
   const char* base = reinterpret_cast<const char*>(x) + (uint64_t(g) * 8u + uint64_t(r)) * row_bytes;
-  return load_raw<T, VEC>(reinterpret_cast<const T*>(base + lane_x));
+  return load_raw<T, VEC, RAGGED>(reinterpret_cast<const T*>(base + lane_x));
 }
 
-template <typename T, int K, int VEC, int MC, typename Tables>
+template <typename T, int K, int VEC, bool RAGGED, int MC, typename Tables>
 __device__ __forceinline__ void encode_stream(const Tables& tb, const T* __restrict__ x,
                                               uint8_t* __restrict__ payload, uint64_t m, uint32_t ipg, uint32_t wpg,
                                               const WorkQueue& q, uint32_t cur, uint32_t nxt, ItemAddr ca,
@@ -823,7 +827,7 @@ __device__ __forceinline__ void encode_stream(const Tables& tb, const T* __restr
         uint32_t lane_x = na.jv * uint32_t(VEC * sizeof(T));
         asm volatile("" : "+v"(lane_x));
 #pragma unroll
-        for (int rr = 0; rr < GR; ++rr) fr[r0 + rr] = load_row<T, VEC>(x, na.g, row_bytes, r0 + rr, lane_x);
+        for (int rr = 0; rr < GR; ++rr) fr[r0 + rr] = load_row<T, VEC, RAGGED>(x, na.g, row_bytes, r0 + rr, lane_x);
       }
       // keep the instruction scheduler from mixing groups: it would otherwise hoist the table
       // reads of all 8*VEC elements and run out of registers
@@ -831,11 +835,54 @@ __device__ __forceinline__ void encode_stream(const Tables& tb, const T* __restr
     }
 #pragma unroll
     for (int p = 0; p < K; ++p) h32[p] *= sum_factor(tb);
-    finish_item<K, VEC>(acc, h32, sx32, payload + uint64_t(ca.g) * m * uint32_t(K) + ca.jv * uint32_t(VEC * K), ca.counts,
+    finish_item<K, VEC, RAGGED>(acc, h32, sx32, payload + uint64_t(ca.g) * m * uint32_t(K) + ca.jv * uint32_t(VEC * K), ca.counts,
                         st);
     cur = nxt;
     nxt = q.drawn + uint32_t(__builtin_amdgcn_readfirstlane(int(after_v)));
     ca = na;
+  }
+}
+
+// The last, partial row group (n % 8 != 0) in wave-items, not pipelined: it is at most seven rows
+// of the tensor.  Rows beyond the last are not read; they give 0 bits and add nothing.
+template <typename T, int K, int VEC, bool RAGGED, int MC, typename Tables>
+__device__ __forceinline__ void encode_partial(const Tables& tb, const T* __restrict__ x, uint8_t* __restrict__ payload,
+                                               int64_t n, int64_t m, uint32_t ipg, uint32_t wpg, int maxcnt,
+                                               uint32_t first, uint32_t step, EncodeStats<K>& st) {
+  constexpr int NW = (K + 3) / 4;
+  constexpr int GR = VEC >= 4 ? 1 : 4 / VEC;
+  const int lane = threadIdx.x & (kWave - 1);
+  const int64_t g = n / 8;
+  const int nrows = int(n - g * 8);
+  for (uint32_t w = first; w < wpg; w += step) {
+    const ItemAddr ia = item_addr(w, wpg, ipg, lane);
+    const int64_t j0 = int64_t(ia.jv) * VEC;
+    RawRow<VEC> rows[8];
+#pragma unroll
+    for (int r = 0; r < 8; ++r) {
+      if constexpr (VEC > 1) rows[r].v = make_uint4(0u, 0u, 0u, 0u); else rows[r].v = 0u;
+      if (r < nrows) rows[r] = load_raw<T, VEC, RAGGED>(x + (g * 8 + r) * m + j0);
+    }
+    float h32[K];
+    float sx32 = 0.0f;
+    uint32_t acc[VEC][NW];
+#pragma unroll
+    for (int p = 0; p < K; ++p) h32[p] = 0.0f;
+#pragma unroll
+    for (int c = 0; c < VEC; ++c)
+#pragma unroll
+      for (int v = 0; v < NW; ++v) acc[c][v] = 0;
+#pragma unroll
+    for (int r0 = 0; r0 < 8; r0 += GR) {
+      encode_rows<K, VEC, MC, GR>(tb, rows, r0, nrows, maxcnt, acc, h32, sx32);
+#pragma unroll
+      for (int p = 0; p < K; ++p) asm volatile("" : "+v"(h32[p]));  // as in the stream
+      asm volatile("" : "+v"(sx32));
+      __builtin_amdgcn_sched_barrier(0);
+    }
+#pragma unroll
+    for (int p = 0; p < K; ++p) h32[p] *= sum_factor(tb);
+    finish_item<K, VEC, RAGGED>(acc, h32, sx32, payload + (g * m + j0) * K, ia.counts, st);
   }
 }
 
@@ -985,12 +1032,15 @@ __global__ __launch_bounds__(kFinalizeBlock) void mbq_finalize_kernel(MbqCall ca
 // Fused M1..M4.  Complete row groups go through the pipelined stream: row r of the next
 // wave-item is requested as soon as row r of the current one has been consumed, so a wavefront
 // always has loads in flight while it works; the first wave-item's rows are requested before
-// the tables are built.  The last, partial row group (n % 8 != 0) and the rare case of more
-// than two thresholds per bucket take the plain path, one column per thread.
-template <typename T, int K, int VEC>
+// the tables are built.  The last, partial row group (n % 8 != 0) goes in wave-items too, without
+// the pipeline; the rare case of more than two thresholds per bucket takes the plain path, one
+// column per thread.  RAGGED: m is not a multiple of VEC, so rows start at any alignment; vectors
+// all the same, and the last m % VEC columns one per thread (15 x 390403 float32, k = 3: this kernel
+// 12.0 us and the decoder 7.2, against 14.3 and 9.0 with single columns throughout).
+template <typename T, int K, int VEC, bool RAGGED>
 __global__ __launch_bounds__(kEncBlock) void mbq_encode_kernel(const T* __restrict__ x, uint8_t* __restrict__ payload,
                                                                MbqCall call, int64_t n, int64_t m, uint32_t ipg,
-                                                               uint32_t wpg, uint32_t n_wave_items) {
+                                                               uint32_t wpg, uint32_t n_wave_items, bool wide) {
   constexpr int NPAIR = K * (K - 1) / 2;
   constexpr bool BY_VALUE = sizeof(T) == 2 && K <= 4;
   using Tables = std::conditional_t<BY_VALUE, ValueTables<K>, EncodeTables<K>>;
@@ -1032,7 +1082,7 @@ __global__ __launch_bounds__(kEncBlock) void mbq_encode_kernel(const T* __restri
     ca = item_addr(queue_to_wave_item(cur, q), wpg, ipg, lane);
 #pragma unroll
     for (int r = 0; r < 8; ++r)
-      fr[r] = load_row<T, VEC>(x, ca.g, uint64_t(m) * sizeof(T), r, ca.jv * uint32_t(VEC * sizeof(T)));
+      fr[r] = load_row<T, VEC, RAGGED>(x, ca.g, uint64_t(m) * sizeof(T), r, ca.jv * uint32_t(VEC * sizeof(T)));
   }
 
   int maxcnt = 1;
@@ -1056,9 +1106,10 @@ __global__ __launch_bounds__(kEncBlock) void mbq_encode_kernel(const T* __restri
   const int64_t gtid = int64_t(blockIdx.x) * kEncBlock + tid;
   const bool stream = n_wave_items != 0u;  // else: a geometry too narrow for wave-items
   if (stream && maxcnt == 1) {
-    encode_stream<T, K, VEC, 1>(tb, x, payload, uint64_t(m), ipg, wpg, q, cur, nxt, ca, fr, st);
+    encode_stream<T, K, VEC, RAGGED, 1>(tb, x, payload, uint64_t(m), ipg, wpg, q, cur, nxt, ca, fr, st);
   } else if (stream && maxcnt == 2 && K <= 4 && !BY_VALUE) {
-    if constexpr (!BY_VALUE) encode_stream<T, K, VEC, 2>(tb, x, payload, uint64_t(m), ipg, wpg, q, cur, nxt, ca, fr, st);
+    if constexpr (!BY_VALUE)
+      encode_stream<T, K, VEC, RAGGED, 2>(tb, x, payload, uint64_t(m), ipg, wpg, q, cur, nxt, ca, fr, st);
   } else {
     // several thresholds share a bucket (levels closer than a bucket's width), or a very narrow
     // tensor: rare.  One column per thread keeps this path's register needs out of the kernel's
@@ -1069,10 +1120,26 @@ __global__ __launch_bounds__(kEncBlock) void mbq_encode_kernel(const T* __restri
       encode_column<T, K>(tb, x, payload, n, m, g, s - g * m, maxcnt, st);
     }
   }
-  // the last, partial row group (n % 8 != 0), one column per thread
+  // the last, partial row group: wave-items dealt to the workgroups first and to their wavefronts
+  // second; one column per thread where rows are too narrow for them, or levels too close
+  int64_t col0 = 0;  // columns from here on are left
+  if (n % 8 != 0 && wide && maxcnt == 1) {
+    const uint32_t wave = uint32_t(__builtin_amdgcn_readfirstlane(tid / kWave));
+    encode_partial<T, K, VEC, RAGGED, 1>(tb, x, payload, n, m, ipg, wpg, maxcnt, wave * gridDim.x + blockIdx.x,
+                                         gridDim.x * uint32_t(kEncWaves), st);
+    col0 = int64_t(ipg) * VEC;
+  }
   if (n % 8 != 0) {
-    for (int64_t j = gtid; j < m; j += stride)
+    for (int64_t j = col0 + gtid; j < m; j += stride)
       encode_column<T, K>(tb, x, payload, n, m, n / 8, j, maxcnt, st);
+  }
+  // the up to VEC - 1 columns of the complete row groups that no vector covers
+  if (RAGGED && stream && maxcnt <= (K <= 4 && !BY_VALUE ? 2 : 1)) {
+    const int64_t j0 = int64_t(ipg) * VEC, rem = m - j0;
+    for (int64_t s = gtid; s < (n / 8) * rem; s += stride) {
+      const int64_t g = s / rem;
+      encode_column<T, K>(tb, x, payload, n, m, g, j0 + s - g * rem, maxcnt, st);
+    }
   }
   store_record<K>(st, call, red);
 }
@@ -1216,13 +1283,13 @@ __global__ __launch_bounds__(kBlock) void mbq_decode_plain_kernel(const uint8_t*
 }
 
 // ====================================================================== decode (D1 + D2)
-template <typename TO, int K, int VEC>
+// RAGGED: as in the encoder, vectors at any alignment and the last m % VEC columns one per thread.
+template <typename TO, int K, int VEC, bool RAGGED>
 __global__ __launch_bounds__(kBlock) void mbq_decode_kernel(const uint8_t* __restrict__ payload,
                                                              const float* __restrict__ header,
                                                              TO* __restrict__ xhat, int64_t n, int64_t m,
                                                              int64_t ipg, int64_t items, ItemStep step) {
   constexpr int P = 1 << K;
-  constexpr int NDW = (VEC * K + 3) / 4;
   __shared__ float lut[P];
   const int tid = threadIdx.x;
   if (tid < P) {
@@ -1237,31 +1304,17 @@ __global__ __launch_bounds__(kBlock) void mbq_decode_kernel(const uint8_t* __res
   }
   __syncthreads();
 
-  int64_t it = int64_t(blockIdx.x) * kBlock + tid;
-  ItemPos pos;
-  pos.g = it / ipg;
-  pos.jv = it - pos.g * ipg;
-  for (; it < items; it += int64_t(gridDim.x) * kBlock, item_advance(pos, step, ipg)) {
-    const uint8_t* src = payload + ((pos.g * m + pos.jv * VEC) * K);
-    uint32_t w[NDW];
-    if constexpr (VEC > 1) {
-      const Dwords<NDW> in = *reinterpret_cast<const Dwords<NDW>*>(src);
-#pragma unroll
-      for (int i = 0; i < NDW; ++i) w[i] = in.v[i];
-    } else {
-#pragma unroll
-      for (int i = 0; i < NDW; ++i) w[i] = 0;
-#pragma unroll
-      for (int p = 0; p < K; ++p) w[p / 4] |= uint32_t(src[p]) << (8 * (p % 4));
-    }
-    const int64_t row0 = pos.g * 8;
-    TO* dst = xhat + pos.jv * VEC;
+  // NC columns from column j of row group g, byte b of plane p of column c in byte c*K + p of w
+  auto columns = [&](auto nc, int64_t g, int64_t j, const auto& w) {
+    constexpr int NC = decltype(nc)::value;
+    const int64_t row0 = g * 8;
+    TO* dst = xhat + j;
 #pragma unroll
     for (int r = 0; r < 8; ++r) {
       if (row0 + r < n) {
-        float f[VEC];
+        float f[NC];
 #pragma unroll
-        for (int c = 0; c < VEC; ++c) {
+        for (int c = 0; c < NC; ++c) {
           uint32_t pat = 0;
 #pragma unroll
           for (int p = 0; p < K; ++p) {
@@ -1270,12 +1323,48 @@ __global__ __launch_bounds__(kBlock) void mbq_decode_kernel(const uint8_t* __res
           }
           f[c] = lut[pat];
         }
-        if constexpr (VEC > 1) {
-          store_vec(dst + (row0 + r) * m, f);
-        } else {
-          store_one(dst + (row0 + r) * m, f[0]);
-        }
+        if constexpr (NC > 1 && RAGGED) store16_stream_any(dst + (row0 + r) * m, narrow(f));
+        else if constexpr (NC > 1) store_vec(dst + (row0 + r) * m, f);
+        else store_one(dst + (row0 + r) * m, f[0]);
       }
+    }
+  };
+  auto one_column = [&](int64_t g, int64_t j) {
+    uint32_t w[(K + 3) / 4];
+    const uint8_t* src = payload + (g * m + j) * K;
+#pragma unroll
+    for (int i = 0; i < (K + 3) / 4; ++i) w[i] = 0;
+#pragma unroll
+    for (int p = 0; p < K; ++p) w[p / 4] |= uint32_t(src[p]) << (8 * (p % 4));
+    columns(std::integral_constant<int, 1>{}, g, j, w);
+  };
+
+  int64_t it = int64_t(blockIdx.x) * kBlock + tid;
+  ItemPos pos;
+  pos.g = it / ipg;
+  pos.jv = it - pos.g * ipg;
+  for (; it < items; it += int64_t(gridDim.x) * kBlock, item_advance(pos, step, ipg)) {
+    if constexpr (VEC > 1) {
+      constexpr int NDW = VEC * K / 4;
+      const uint8_t* src = payload + ((pos.g * m + pos.jv * VEC) * K);
+      uint32_t w[NDW];
+      if constexpr (RAGGED) {
+        __builtin_memcpy(w, src, sizeof(w));
+      } else {
+        const Dwords<NDW> in = *reinterpret_cast<const Dwords<NDW>*>(src);
+#pragma unroll
+        for (int i = 0; i < NDW; ++i) w[i] = in.v[i];
+      }
+      columns(std::integral_constant<int, VEC>{}, pos.g, pos.jv * VEC, w);
+    } else {
+      one_column(pos.g, pos.jv);
+    }
+  }
+  if constexpr (RAGGED) {
+    const int64_t j0 = ipg * VEC, rem = m - j0, G = (n + 7) / 8;
+    for (int64_t s = int64_t(blockIdx.x) * kBlock + tid; s < G * rem; s += int64_t(gridDim.x) * kBlock) {
+      const int64_t g = s / rem;
+      one_column(g, j0 + s - g * rem);
     }
   }
 }
@@ -1459,9 +1548,11 @@ __global__ __launch_bounds__(kBlock) void mbq_init_finalize_kernel(const double*
 }
 
 // ============================================================================= host side
-int vec_for(int dtype, int64_t m) {
+// Elements per vector: 16 bytes' worth; for the widths in use (k <= 4) at any alignment, where rows
+// are long enough for wave-items.
+int vec_for(int dtype, int64_t m, int bits) {
   const int v = dtype == ACCEPT_BF16 ? 8 : 4;
-  return (m % v == 0) ? v : 1;
+  return m % v == 0 || (bits <= 4 && m >= v * kWave) ? v : 1;
 }
 
 int grid_for(int64_t items, int grid_max) {
@@ -1490,53 +1581,65 @@ MbqCall make_call(const accept_desc& d, const float* alpha_prev, void* header, v
   return c;
 }
 
-template <typename T, int K, int VEC>
+template <typename T, int K, int VEC, bool RAGGED>
 hipError_t launch_encode(const accept_desc& d, const MPlan& p, const T* x, uint8_t* payload, const MbqCall& call,
                          hipStream_t s) {
-  hipLaunchKernelGGL((mbq_encode_kernel<T, K, VEC>), dim3(p.grid), dim3(kEncBlock), 0, s, x, payload, call, d.n, d.m,
-                     uint32_t(p.stream ? d.m / VEC : 1), p.wpg, p.n_wave_items);
+  hipLaunchKernelGGL((mbq_encode_kernel<T, K, VEC, RAGGED>), dim3(p.grid), dim3(kEncBlock), 0, s, x, payload, call, d.n,
+                     d.m, uint32_t(p.wide ? d.m / VEC : 1), p.wpg, p.n_wave_items, p.wide);
   return hipGetLastError();
 }
 
-template <typename T, int VEC>
+template <typename T, int VEC, bool RAGGED = false>
 hipError_t encode_k(const accept_desc& d, const MPlan& p, const T* x, uint8_t* payload, const MbqCall& call,
                     hipStream_t s) {
   switch (d.bits) {
-    case 1: return launch_encode<T, 1, VEC>(d, p, x, payload, call, s);
-    case 2: return launch_encode<T, 2, VEC>(d, p, x, payload, call, s);
-    case 3: return launch_encode<T, 3, VEC>(d, p, x, payload, call, s);
-    case 4: return launch_encode<T, 4, VEC>(d, p, x, payload, call, s);
-    case 5: return launch_encode<T, 5, VEC>(d, p, x, payload, call, s);
-    case 6: return launch_encode<T, 6, VEC>(d, p, x, payload, call, s);
-    case 7: return launch_encode<T, 7, VEC>(d, p, x, payload, call, s);
-    case 8: return launch_encode<T, 8, VEC>(d, p, x, payload, call, s);
-    default: return hipErrorInvalidValue;
+    case 1: return launch_encode<T, 1, VEC, RAGGED>(d, p, x, payload, call, s);
+    case 2: return launch_encode<T, 2, VEC, RAGGED>(d, p, x, payload, call, s);
+    case 3: return launch_encode<T, 3, VEC, RAGGED>(d, p, x, payload, call, s);
+    case 4: return launch_encode<T, 4, VEC, RAGGED>(d, p, x, payload, call, s);
+    default: break;
   }
+  if constexpr (!RAGGED) {
+    switch (d.bits) {
+      case 5: return launch_encode<T, 5, VEC, false>(d, p, x, payload, call, s);
+      case 6: return launch_encode<T, 6, VEC, false>(d, p, x, payload, call, s);
+      case 7: return launch_encode<T, 7, VEC, false>(d, p, x, payload, call, s);
+      case 8: return launch_encode<T, 8, VEC, false>(d, p, x, payload, call, s);
+      default: break;
+    }
+  }
+  return hipErrorInvalidValue;
 }
 
-template <typename TO, int K, int VEC>
+template <typename TO, int K, int VEC, bool RAGGED>
 hipError_t launch_decode(const accept_desc& d, const uint8_t* payload, const float* header, TO* xhat, hipStream_t s) {
   const int64_t ipg = d.m / VEC;
   const int64_t items = ((d.n + 7) / 8) * ipg;
   const int grid = grid_for(items, kDecodeGridMax);
-  hipLaunchKernelGGL((mbq_decode_kernel<TO, K, VEC>), dim3(grid), dim3(kBlock), 0, s, payload, header, xhat, d.n,
+  hipLaunchKernelGGL((mbq_decode_kernel<TO, K, VEC, RAGGED>), dim3(grid), dim3(kBlock), 0, s, payload, header, xhat, d.n,
                      d.m, ipg, items, step_for(grid, ipg));
   return hipGetLastError();
 }
 
-template <typename TO, int VEC>
+template <typename TO, int VEC, bool RAGGED = false>
 hipError_t decode_k(const accept_desc& d, const uint8_t* payload, const float* header, TO* xhat, hipStream_t s) {
   switch (d.bits) {
-    case 1: return launch_decode<TO, 1, VEC>(d, payload, header, xhat, s);
-    case 2: return launch_decode<TO, 2, VEC>(d, payload, header, xhat, s);
-    case 3: return launch_decode<TO, 3, VEC>(d, payload, header, xhat, s);
-    case 4: return launch_decode<TO, 4, VEC>(d, payload, header, xhat, s);
-    case 5: return launch_decode<TO, 5, VEC>(d, payload, header, xhat, s);
-    case 6: return launch_decode<TO, 6, VEC>(d, payload, header, xhat, s);
-    case 7: return launch_decode<TO, 7, VEC>(d, payload, header, xhat, s);
-    case 8: return launch_decode<TO, 8, VEC>(d, payload, header, xhat, s);
-    default: return hipErrorInvalidValue;
+    case 1: return launch_decode<TO, 1, VEC, RAGGED>(d, payload, header, xhat, s);
+    case 2: return launch_decode<TO, 2, VEC, RAGGED>(d, payload, header, xhat, s);
+    case 3: return launch_decode<TO, 3, VEC, RAGGED>(d, payload, header, xhat, s);
+    case 4: return launch_decode<TO, 4, VEC, RAGGED>(d, payload, header, xhat, s);
+    default: break;
   }
+  if constexpr (!RAGGED) {
+    switch (d.bits) {
+      case 5: return launch_decode<TO, 5, VEC, false>(d, payload, header, xhat, s);
+      case 6: return launch_decode<TO, 6, VEC, false>(d, payload, header, xhat, s);
+      case 7: return launch_decode<TO, 7, VEC, false>(d, payload, header, xhat, s);
+      case 8: return launch_decode<TO, 8, VEC, false>(d, payload, header, xhat, s);
+      default: break;
+    }
+  }
+  return hipErrorInvalidValue;
 }
 
 template <typename T, int K, int VEC>
@@ -1569,24 +1672,26 @@ hipError_t init_encode_k(const accept_desc& d, const T* x, const float* alpha, u
 
 MPlan make_mplan(const accept_desc& d) {
   MPlan p{};
-  p.vec = vec_for(d.in_dtype, d.m);
+  p.vec = vec_for(d.in_dtype, d.m, d.bits);
+  p.ragged = p.vec > 1 && d.m % p.vec != 0;
   p.G = (d.n + 7) / 8;
   p.items = p.G * (d.m / p.vec);
-  // The pipelined stream of the encode kernel works on wave-items (64 items of one row group).
-  // It needs at least one full wave-item per row group to be worth it and 32-bit wave-item
-  // numbers; other geometries (very narrow tensors) go one column per thread.
+  // The encode kernel works on wave-items (64 items of one row group).  A row group needs at least
+  // one full wave-item to be worth it, and numbers and row lengths have to fit 32 bits; other
+  // geometries (very narrow tensors) go one column per thread.
   const int64_t ipg = d.m / p.vec;
   const int64_t wpg = (ipg + kWave - 1) / kWave;
   const int64_t full_groups = d.n / 8;
   const int64_t wave_items = full_groups * wpg;
-  p.stream = full_groups > 0 && ipg >= kWave && wave_items < (int64_t(1) << 31) && d.m * 8 < (int64_t(1) << 32);
-  p.wpg = p.stream ? uint32_t(wpg) : 1u;
+  p.wide = ipg >= kWave && wave_items < (int64_t(1) << 31) && d.m * 8 < (int64_t(1) << 32);
+  p.stream = full_groups > 0 && p.wide;
+  p.wpg = p.wide ? uint32_t(wpg) : 1u;
   p.n_wave_items = p.stream ? uint32_t(wave_items) : 0u;
   {
     // one workgroup of 8 wavefronts per compute unit at most; fewer when there is less work
     int64_t blocks = p.stream ? (wave_items + kEncWaves - 1) / kEncWaves
                               : (full_groups * d.m + kEncBlock - 1) / kEncBlock;
-    const int64_t tail_blocks = (d.n % 8 != 0) ? (d.m + kEncBlock - 1) / kEncBlock : 0;
+    const int64_t tail_blocks = d.n % 8 == 0 ? 0 : p.wide ? wpg : (d.m + kEncBlock - 1) / kEncBlock;
     if (blocks < tail_blocks) blocks = tail_blocks;
     if (blocks < 1) blocks = 1;
     p.grid = int(blocks < kEncodeGridMax ? blocks : kEncodeGridMax);
@@ -1645,10 +1750,14 @@ hipError_t launch_mbq_compress(const accept_desc& d, const MPlan& p, const void*
                                   : encode_plain_k<float>(d, grid, static_cast<const float*>(x), pl, call, s);
   } else if (d.in_dtype == ACCEPT_BF16) {
     const bf16_t* xb = static_cast<const bf16_t*>(x);
-    e = p.vec == 8 ? encode_k<bf16_t, 8>(d, p, xb, pl, call, s) : encode_k<bf16_t, 1>(d, p, xb, pl, call, s);
+    e = p.ragged     ? encode_k<bf16_t, 8, true>(d, p, xb, pl, call, s)
+        : p.vec == 8 ? encode_k<bf16_t, 8>(d, p, xb, pl, call, s)
+                     : encode_k<bf16_t, 1>(d, p, xb, pl, call, s);
   } else {
     const float* xf = static_cast<const float*>(x);
-    e = p.vec == 4 ? encode_k<float, 4>(d, p, xf, pl, call, s) : encode_k<float, 1>(d, p, xf, pl, call, s);
+    e = p.ragged     ? encode_k<float, 4, true>(d, p, xf, pl, call, s)
+        : p.vec == 4 ? encode_k<float, 4>(d, p, xf, pl, call, s)
+                     : encode_k<float, 1>(d, p, xf, pl, call, s);
   }
   if (e != hipSuccess) return e;
   mark(tm, s);
@@ -1671,7 +1780,7 @@ hipError_t launch_mbq_decompress(const accept_desc& d, const void* header, const
                                  hipStream_t s, StageTimer* tm) {
   const uint8_t* pl = static_cast<const uint8_t*>(payload);
   const float* hd = static_cast<const float*>(header);
-  const int vec = vec_for(d.out_dtype, d.m);
+  const int vec = vec_for(d.out_dtype, d.m, d.bits);
   hipError_t e;
   mark(tm, s);
   if (d.layout == ACCEPT_LAYOUT_UNENCODED) {
@@ -1679,10 +1788,14 @@ hipError_t launch_mbq_decompress(const accept_desc& d, const void* header, const
                                    : decode_plain_k<float>(d, pl, hd, static_cast<float*>(xhat), s);
   } else if (d.out_dtype == ACCEPT_BF16) {
     bf16_t* o = static_cast<bf16_t*>(xhat);
-    e = vec == 8 ? decode_k<bf16_t, 8>(d, pl, hd, o, s) : decode_k<bf16_t, 1>(d, pl, hd, o, s);
+    e = vec == 1         ? decode_k<bf16_t, 1>(d, pl, hd, o, s)
+        : d.m % vec != 0 ? decode_k<bf16_t, 8, true>(d, pl, hd, o, s)
+                         : decode_k<bf16_t, 8>(d, pl, hd, o, s);
   } else {
     float* o = static_cast<float*>(xhat);
-    e = vec == 4 ? decode_k<float, 4>(d, pl, hd, o, s) : decode_k<float, 1>(d, pl, hd, o, s);
+    e = vec == 1         ? decode_k<float, 1>(d, pl, hd, o, s)
+        : d.m % vec != 0 ? decode_k<float, 4, true>(d, pl, hd, o, s)
+                         : decode_k<float, 4>(d, pl, hd, o, s);
   }
   if (e != hipSuccess) return e;
   mark(tm, s);
@@ -1704,16 +1817,17 @@ hipError_t launch_mbq_init(const accept_desc& d, const MPlan& p, const void* x, 
     const bool planes = payload != nullptr && j == k - 1;
     int nrec = grid, nstat = 1;
     if (planes) {
-      nrec = grid_for(p.items, kPlainGridMax);
+      const int init_vec = d.m % p.vec == 0 ? p.vec : 1;
+      nrec = grid_for(p.G * (d.m / init_vec), kPlainGridMax);
       nstat = k + 2;
       uint8_t* pl = static_cast<uint8_t*>(payload);
       if (bf) {
         const bf16_t* xb = static_cast<const bf16_t*>(x);
-        e = p.vec == 8 ? init_encode_k<bf16_t, 8>(d, xb, alpha_out, pl, records, nrec, s)
+        e = init_vec == 8 ? init_encode_k<bf16_t, 8>(d, xb, alpha_out, pl, records, nrec, s)
                        : init_encode_k<bf16_t, 1>(d, xb, alpha_out, pl, records, nrec, s);
       } else {
         const float* xf = static_cast<const float*>(x);
-        e = p.vec == 4 ? init_encode_k<float, 4>(d, xf, alpha_out, pl, records, nrec, s)
+        e = init_vec == 4 ? init_encode_k<float, 4>(d, xf, alpha_out, pl, records, nrec, s)
                        : init_encode_k<float, 1>(d, xf, alpha_out, pl, records, nrec, s);
       }
     } else {

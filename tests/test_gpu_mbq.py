@@ -219,3 +219,28 @@ def test_bf16_every_value(A, k):
             torch.cuda.synchronize()
             want = orc.mbq_pack(orc.mbq_assign(orc.widen_bf16(xb), a), k, n, m)
             assert first_mismatch(dev_bytes(payload), want.tobytes()) is None, (n, m, alpha)
+
+
+@pytest.mark.parametrize("bf16", [False, True])
+@pytest.mark.parametrize("n", [1, 7, 8, 9, 23])
+def test_rows_at_any_alignment(A, n, bf16):
+    """Rows that are not whole 16-byte vectors: vectors at any alignment, the last columns one by
+    one, from the narrowest row that goes this way (64 vectors) on, and just below it; complete
+    and partial row groups."""
+    vec = 8 if bf16 else 4
+    for i, m in enumerate([64 * vec - 1, 64 * vec, 64 * vec + 1, 65 * vec - 1, 1024 + 3, 128 * vec + 2, 40 * 64 * vec + vec - 1]):
+        k = 1 + (i + n) % 4
+        x = si.make_shape("student_t3" if i % 2 else "relu_normal", (n, m), 7300 + 10 * n + i)
+        run_case(A, x, k, n, m, t=2, in_bf16=bf16, out_bf16=bf16, tag="ragged")
+    # levels that share a bucket of the search table: two of them, and more
+    for alpha in ([1.0, 0.52, 0.26, 0.1301], [1.0, 0.99, 0.011, 0.01]):
+        m = 40 * 64 * vec + 3
+        x = si.make_shape("student_t3", (n, m), 7400 + n)
+        d = A.make_desc(A.MBQ, 4, n, m, in_dtype=A.BF16 if bf16 else A.F32, t=1)
+        xd, bits = to_dev(x, bf16)
+        a = np.array(alpha, np.float32)
+        torch = torch_mod()
+        _, payload = A.accept_compress(d, xd, alpha_prev=torch.from_numpy(a).cuda())
+        torch.cuda.synchronize()
+        want = orc.mbq_pack(orc.mbq_assign(orc.widen_bf16(bits) if bf16 else x, a), 4, n, m)
+        assert first_mismatch(dev_bytes(payload), want.tobytes()) is None, (n, m, alpha)
