@@ -1004,6 +1004,17 @@ __device__ __forceinline__ void store_record(const EncodeStats<K>& st, const Mbq
 // solves and writes the header.  (With four wavefronts that each added up their share of every
 // statistic the sums alone took 1.9 of the kernel's 3.7 us at k = 4.)
 constexpr int kFinalizeBlock = 1024;
+// Sum of nrec records by one wavefront, four loads in flight; every lane has it.
+__device__ __forceinline__ double sum_records(const double* __restrict__ rec, int nrec, int lane) {
+  double a = 0.0;
+  for (int b = lane; b < nrec; b += 4 * kWave) {
+    double v[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) v[u] = b + u * kWave < nrec ? rec[b + u * kWave] : 0.0;
+    a += (v[0] + v[1]) + (v[2] + v[3]);
+  }
+  return wave_sum(a);
+}
 template <int K>
 __global__ __launch_bounds__(kFinalizeBlock) void mbq_finalize_kernel(MbqCall call, int nrec) {
   constexpr int NSTAT = nstat_of(K);
@@ -1013,15 +1024,7 @@ __global__ __launch_bounds__(kFinalizeBlock) void mbq_finalize_kernel(MbqCall ca
 #pragma unroll
   for (int p = 0; p < K; ++p) alpha_prev[p] = call.alpha_prev[p];
   for (int s = wave; s < NSTAT; s += kFinalizeBlock / kWave) {
-    const double* rec = call.records + int64_t(s) * nrec;
-    double a = 0.0;
-    for (int b = lane; b < nrec; b += 4 * kWave) {  // four loads in flight
-      double v[4];
-#pragma unroll
-      for (int u = 0; u < 4; ++u) v[u] = b + u * kWave < nrec ? rec[b + u * kWave] : 0.0;
-      a += (v[0] + v[1]) + (v[2] + v[3]);
-    }
-    a = wave_sum(a);
+    const double a = sum_records(call.records + int64_t(s) * nrec, nrec, lane);
     if (lane == 0) tot[s] = a;
   }
   if (tid < kMaxGroups) call.counters[tid * kCounterStride] = 0u;  // the encode kernel's work counters, for the next call
@@ -1372,50 +1375,99 @@ __global__ __launch_bounds__(kBlock) void mbq_decode_kernel(const uint8_t* __res
 // ======================================================= residue initialisation (batch 0)
 // rho_0 = x, b_j = sign(rho_j) (sign(0) = +1), alpha_j = mean|rho_j|, rho_(j+1) = rho_j - alpha_j b_j,
 // carried in float64 like the definition.  alpha_j needs the whole tensor's |rho_j|, so the method
-// is k passes over x; pass j reads alpha_0..alpha_(j-1) from device memory.
+// is k passes over x.  Every workgroup of pass j adds up the records of pass j-1 itself, in the same
+// order, and so has alpha_(j-1) without a kernel in between (that kernel took 4 us of each pass);
+// workgroup 0 writes it down.  A batch-0 call on 32 x 401408 float32 at k = 2 / 3 / 4: 33.4 / 50.6 / 67.7
+// -> 28.6 / 39.3 / 51.0 us; 64 x 802816: 85 / 128 / 176 -> 76 / 111 / 145 us.  (More workgroups for
+// the last pass, 1024 to 2048 instead of 768, cost 1 to 3 us; fewer or more for the others as well.)
+//
+// Signs are taken from the sign bit (x + 0 has none for a zero, and no difference of two equal
+// numbers has), so a step is a bit select and an add.
 
-// rho_j of one element.
-__device__ __forceinline__ double residue(float x, const double (&a)[8], int j) {
-  double rho = double(x);
-  for (int q = 0; q < j; ++q) rho -= (rho >= 0.0) ? a[q] : -a[q];
-  return rho;
+// Where pass j leaves its records (one double per workgroup and statistic, statistic-major).
+constexpr int kInitPasses = 8;
+static_assert(kInitPasses + kInitPasses + 2 <= nstat_of(8), "records of all passes, and k + 2 statistics of the last");
+
+// alpha_j from the records of pass j, the same in every thread of every workgroup.
+__device__ __forceinline__ float alpha_of_pass(const double* __restrict__ records, int nrec, double n_elems,
+                                               WaveTotals& buf) {
+  const int tid = threadIdx.x, wave = tid / kWave;
+  double a = 0.0;
+  for (int b = tid; b < nrec; b += kBlock) a += records[b];
+  a = wave_sum(a);
+  if ((tid & (kWave - 1)) == 0) buf.v[wave][0] = a;
+  __syncthreads();
+  a = 0.0;
+#pragma unroll
+  for (int w = 0; w < kBlock / kWave; ++w) a += buf.v[w][0];
+  __syncthreads();  // the buffer is free again
+  return float(a / n_elems);
 }
+// alpha_0 .. alpha_(J-1): the last from the records, which workgroup 0 also writes down, the others
+// from where earlier passes left them.
+template <int J>
+__device__ __forceinline__ void alphas_of_passes(float* __restrict__ alpha_out, const double* __restrict__ records,
+                                                 int nrec, double n_elems, WaveTotals& buf, double (&a)[J > 0 ? J : 1]) {
+  if constexpr (J > 0) {
+#pragma unroll
+    for (int q = 0; q < J - 1; ++q) a[q] = double(alpha_out[q]);
+    const float last = alpha_of_pass(records, nrec, n_elems, buf);
+    if (blockIdx.x == 0 && threadIdx.x == 0) alpha_out[J - 1] = last;
+    a[J - 1] = double(last);
+  }
+}
+// rho <- rho - sign(rho) a
+__device__ __forceinline__ double residue_step(double rho, double a) { return rho - __builtin_copysign(a, rho); }
 
-// Pass j, sums only: sum of |rho_j|, 16-byte streaming loads, four in flight per thread; one
-// record (a single float64) per workgroup.
-template <typename T>
-__global__ __launch_bounds__(kBlock) void mbq_init_pass_kernel(const T* __restrict__ x, int64_t N, int j,
-                                                                const float* __restrict__ alpha,
-                                                                double* __restrict__ records) {
+// Pass J, sums only: sum of |rho_J| over tiles of 8192 elements (all of a thread's 16-byte loads of a
+// tile in flight); one record per workgroup.
+template <typename T, int J>
+__global__ __launch_bounds__(kBlock) void mbq_init_pass_kernel(const T* __restrict__ x, int64_t N,
+                                                                float* __restrict__ alpha_out,
+                                                                const double* __restrict__ prev, int nprev,
+                                                                double n_elems, double* __restrict__ records) {
   constexpr int VEC = Elem<T>::VEC;
-  constexpr int UNROLL = 4;
+  constexpr int LOADS = kTileElems / (kBlock * VEC);
   __shared__ WaveTotals red;
-  double a[8];
-  for (int i = 0; i < 8; ++i) a[i] = i < j ? double(alpha[i]) : 0.0;
-  const int64_t nvec = N / VEC;
-  const int64_t stride = int64_t(gridDim.x) * kBlock;
-  double acc = 0.0;
-  int64_t v = int64_t(blockIdx.x) * kBlock + threadIdx.x;
-  for (; v + (UNROLL - 1) * stride < nvec; v += UNROLL * stride) {
-    float f[UNROLL][VEC];
+  const int tid = threadIdx.x;
+  const int64_t tiles = N / kTileElems;
+  uint4 raw[LOADS];
+  auto ask = [&](int64_t tile) {
 #pragma unroll
-    for (int u = 0; u < UNROLL; ++u) load_vec_stream(x + (v + u * stride) * VEC, f[u]);
+    for (int u = 0; u < LOADS; ++u) raw[u] = load16_stream(x + tile * kTileElems + (u * kBlock + tid) * VEC);
+  };
+  int64_t tile = blockIdx.x;
+  if (tile < tiles) ask(tile);  // under way while alpha is formed
+  double a[J > 0 ? J : 1];
+  alphas_of_passes<J>(alpha_out, prev, nprev, n_elems, red, a);
+  auto magnitude = [&](float v) {
+    double rho = double(v + 0.0f);
 #pragma unroll
-    for (int u = 0; u < UNROLL; ++u)
+    for (int q = 0; q < J; ++q) rho = residue_step(rho, a[q]);
+    return fabs(rho);
+  };
+  double acc[VEC];
 #pragma unroll
-      for (int e = 0; e < VEC; ++e) acc += fabs(residue(f[u][e], a, j));
+  for (int e = 0; e < VEC; ++e) acc[e] = 0.0;
+  while (tile < tiles) {
+#pragma unroll
+    for (int u = 0; u < LOADS; ++u) {
+      float f[VEC];
+      widen(raw[u], f);
+#pragma unroll
+      for (int e = 0; e < VEC; ++e) acc[e] += magnitude(f[e]);
+    }
+    tile += gridDim.x;
+    if (tile < tiles) ask(tile);
   }
-  for (; v < nvec; v += stride) {
-    float f[VEC];
-    load_vec_stream(x + v * VEC, f);
+  // behind the last whole tile
+  for (int64_t i = tiles * kTileElems + int64_t(blockIdx.x) * kBlock + tid; i < N; i += int64_t(gridDim.x) * kBlock)
+    acc[0] += magnitude(load_one(x + i));
 #pragma unroll
-    for (int e = 0; e < VEC; ++e) acc += fabs(residue(f[e], a, j));
-  }
-  if (blockIdx.x == 0 && int64_t(threadIdx.x) < N - nvec * VEC)
-    acc += fabs(residue(load_one(x + nvec * VEC + threadIdx.x), a, j));
-  const double sv[1] = {acc};
+  for (int e = 1; e < VEC; ++e) acc[0] += acc[e];
+  const double sv[1] = {acc[0]};
   const double total = block_sum_stats<1>(sv, red);
-  if (threadIdx.x == 0) records[blockIdx.x] = total;
+  if (tid == 0) records[blockIdx.x] = total;
 }
 
 // Last pass (j = K-1) of a batch-0 compression: the signs b_0..b_(K-1) of every element need
@@ -1425,71 +1477,87 @@ __global__ __launch_bounds__(kBlock) void mbq_init_pass_kernel(const T* __restri
 // sum of x, +1 counts of the K planes.
 template <typename T, int K, int VEC>
 __global__ __launch_bounds__(kBlock) void mbq_init_encode_kernel(const T* __restrict__ x,
-                                                                  const float* __restrict__ alpha,
-                                                                  uint8_t* __restrict__ payload,
+                                                                  float* __restrict__ alpha_out,
+                                                                  const double* __restrict__ prev, int nprev,
+                                                                  double n_elems, uint8_t* __restrict__ payload,
                                                                   double* __restrict__ records, int64_t n, int64_t m,
                                                                   int64_t ipg, int64_t items, ItemStep step) {
   constexpr int NW = (K + 3) / 4;
   constexpr int NDW = (VEC * K + 3) / 4;
-  constexpr int NS = K + 2;
   __shared__ WaveTotals red;
-  double a[8];
-  for (int i = 0; i < 8; ++i) a[i] = i < K - 1 ? double(alpha[i]) : 0.0;
+  const int tid = threadIdx.x;
+  int64_t it = int64_t(blockIdx.x) * kBlock + tid;
+  ItemPos pos;
+  pos.g = it / ipg;
+  pos.jv = it - pos.g * ipg;
+  RawRow<VEC> fr[8];
+  auto ask = [&]() {  // all row loads of an item, so that they overlap
+    const int64_t row0 = pos.g * 8;
+    const T* xc = x + row0 * m + pos.jv * VEC;
+#pragma unroll
+    for (int r = 0; r < 8; ++r)
+      if (row0 + r < n) fr[r] = load_raw<T, VEC>(xc + r * m);
+  };
+  if (it < items) ask();  // under way while alpha is formed
+  double a[K > 1 ? K - 1 : 1];
+  alphas_of_passes<K - 1>(alpha_out, prev, nprev, n_elems, red, a);
   double sum_abs = 0.0, sum_x = 0.0;
   uint32_t cnt[K];
 #pragma unroll
   for (int p = 0; p < K; ++p) cnt[p] = 0;
-  int64_t it = int64_t(blockIdx.x) * kBlock + threadIdx.x;
-  ItemPos pos;
-  pos.g = it / ipg;
-  pos.jv = it - pos.g * ipg;
-  for (; it < items; it += int64_t(gridDim.x) * kBlock, item_advance(pos, step, ipg)) {
+  while (it < items) {
     const int64_t row0 = pos.g * 8;
     const int nrows = (n - row0) < 8 ? int(n - row0) : 8;
-    const T* xc = x + row0 * m + pos.jv * VEC;
-    RawRow<VEC> fr[8];
+    uint32_t neg[VEC][K];  // sign bits, one row after the other entering at the bottom
 #pragma unroll
-    for (int r = 0; r < 8; ++r) {  // all row loads first, so that they overlap
-      if constexpr (VEC > 1) fr[r].v = make_uint4(0u, 0u, 0u, 0u); else fr[r].v = 0u;
-      if (r < nrows) fr[r] = load_raw<T, VEC>(xc + r * m);
+    for (int c = 0; c < VEC; ++c)
+#pragma unroll
+      for (int q = 0; q < K; ++q) neg[c][q] = 0;
+    float sx32 = 0.0f;
+#pragma unroll
+    for (int r = 0; r < 8; ++r) {
+      if (r < nrows) {
+        float row[VEC];
+        widen_raw<VEC>(fr[r], row);
+#pragma unroll
+        for (int c = 0; c < VEC; ++c) {
+          sx32 = __fadd_rn(sx32, row[c]);
+          double rho = double(row[c] + 0.0f);
+#pragma unroll
+          for (int q = 0; q < K; ++q) {
+            neg[c][q] = __builtin_amdgcn_alignbit(neg[c][q], uint32_t(uint64_t(__double_as_longlong(rho)) >> 32), 31);
+            if (q < K - 1) rho = residue_step(rho, a[q]);
+          }
+          sum_abs += fabs(rho);
+        }
+      }
     }
+    // row r at bit 7-r; a missing row contributes 0 bits
     uint32_t acc[VEC][NW];
 #pragma unroll
     for (int c = 0; c < VEC; ++c)
 #pragma unroll
       for (int w = 0; w < NW; ++w) acc[c][w] = 0;
-    float sx32 = 0.0f;
+    const uint32_t valid = 0xFFu & (0xFFu << (8 - nrows));
 #pragma unroll
-    for (int r = 0; r < 8; ++r) {
-      float row[VEC];
-      widen_raw<VEC>(fr[r], row);
+    for (int c = 0; c < VEC; ++c)
 #pragma unroll
-      for (int c = 0; c < VEC; ++c) {
-        // the recurrence of residue(), keeping every sign on the way
-        double rho = double(row[c]);
-        uint32_t sp[NW];
-#pragma unroll
-        for (int w = 0; w < NW; ++w) sp[w] = 0;
-#pragma unroll
-        for (int q = 0; q < K; ++q) {
-          const bool pos_sign = rho >= 0.0;
-          sp[q / 4] |= (pos_sign ? 1u : 0u) << (8 * (q % 4));
-          if (q < K - 1) rho -= pos_sign ? a[q] : -a[q];
-        }
-        const bool have = r < nrows;  // a missing row contributes 0 bits and nothing to the sums
-        sum_abs += have ? fabs(rho) : 0.0;
-        sx32 = __fadd_rn(sx32, have ? row[c] : 0.0f);
-#pragma unroll
-        for (int w = 0; w < NW; ++w) acc[c][w] = (acc[c][w] << 1) | (have ? sp[w] : 0u);
+      for (int q = 0; q < K; ++q) {
+        const uint32_t plus = ~(neg[c][q] << (8 - nrows)) & valid;
+        cnt[q] += __popc(plus);
+        acc[c][q / 4] |= plus << (8 * (q % 4));
       }
-    }
     sum_x += double(sx32);
-#pragma unroll
-    for (int p = 0; p < K; ++p)
-#pragma unroll
-      for (int c = 0; c < VEC; ++c) cnt[p] += __popc((acc[c][p / 4] >> (8 * (p % 4))) & 0xFFu);
     uint8_t* dst = payload + ((pos.g * m + pos.jv * VEC) * K);
-    if constexpr (VEC > 1) {
+    if constexpr (VEC > 1 && K <= 4) {
+      uint32_t out[NDW];
+#pragma unroll
+      for (int w = 0; w < VEC / 4; ++w) {
+        const uint32_t q4[4] = {acc[4 * w][0], acc[4 * w + 1][0], acc[4 * w + 2][0], acc[4 * w + 3][0]};
+        columns_to_payload<K>(q4, &out[K * w]);
+      }
+      store_dwords<NDW>(reinterpret_cast<uint32_t*>(dst), out);
+    } else if constexpr (VEC > 1) {
       uint32_t out[NDW];
 #pragma unroll
       for (int w = 0; w < NDW; ++w) out[w] = 0;
@@ -1505,34 +1573,43 @@ __global__ __launch_bounds__(kBlock) void mbq_init_encode_kernel(const T* __rest
 #pragma unroll
       for (int p = 0; p < K; ++p) dst[p] = uint8_t(acc[0][p / 4] >> (8 * (p % 4)));
     }
+    it += int64_t(gridDim.x) * kBlock;
+    item_advance(pos, step, ipg);
+    if (it < items) ask();
   }
-  double sv[NS];
-  sv[0] = sum_abs;
-  sv[1] = sum_x;
+  const int wave = tid / kWave, lane = tid & (kWave - 1);
+  {
+    const double sa = wave_sum(sum_abs), sx = wave_sum(sum_x);
+    if (lane == 0) { red.v[wave][0] = sa; red.v[wave][1] = sx; }
 #pragma unroll
-  for (int p = 0; p < K; ++p) sv[2 + p] = double(cnt[p]);
-  const double total = block_sum_stats<NS>(sv, red);
-  if (threadIdx.x < NS) records[int64_t(threadIdx.x) * gridDim.x + blockIdx.x] = total;
+    for (int p = 0; p < K; ++p) {
+      const double c = double(wave_sum(cnt[p]));
+      if (lane == 0) red.v[wave][2 + p] = c;
+    }
+  }
+  __syncthreads();
+  if (tid < K + 2) {
+    double total = red.v[0][tid];
+    for (int w = 1; w < kBlock / kWave; ++w) total += red.v[w][tid];
+    records[int64_t(tid) * gridDim.x + blockIdx.x] = total;
+  }
 }
 
-// After pass j: alpha_j = (sum of the workgroups' |rho_j| sums) / N, written to alpha_out[j].
-// After the last pass of a batch-0 compression (nstat = k + 2) also the rest of the header:
+// After the last pass: alpha_j = (sum of the workgroups' |rho_j| sums) / N, written to alpha_out[j]; of
+// a batch-0 compression (nstat = k + 2) also the rest of the header:
 // m_q = mean(B^0 alpha^0 - x) = (sum_p alpha_p (2 cnt_p - N) - sum x) / N  (eq. (biased error)),
-// written behind the k coefficients that the earlier passes left in alpha_out.
-__global__ __launch_bounds__(kBlock) void mbq_init_finalize_kernel(const double* __restrict__ records, int nrec,
-                                                                    int nstat, double n_elems, int j,
-                                                                    float* __restrict__ alpha_out) {
-  __shared__ WaveTotals red;
-  __shared__ double tot[16];
-  const int tid = threadIdx.x;
-  for (int s = 0; s < nstat; ++s) {
-    double a = 0.0;
-    for (int b = tid; b < nrec; b += kBlock) a += records[int64_t(s) * nrec + b];
-    const double sv[1] = {a};
-    const double total = block_sum_stats<1>(sv, red);
-    if (tid == 0) tot[s] = total;
-    __syncthreads();  // the buffer of the workgroup sum is free again
+// written behind the k coefficients that the earlier passes left in alpha_out.  A wavefront per
+// statistic, as in mbq_finalize_kernel.
+__global__ __launch_bounds__(kFinalizeBlock) void mbq_init_finalize_kernel(const double* __restrict__ records, int nrec,
+                                                                            int nstat, double n_elems, int j,
+                                                                            float* __restrict__ alpha_out) {
+  __shared__ double tot[kInitPasses + 2];
+  const int tid = threadIdx.x, wave = tid / kWave, lane = tid & (kWave - 1);
+  for (int s = wave; s < nstat; s += kFinalizeBlock / kWave) {
+    const double t = sum_records(records + int64_t(s) * nrec, nrec, lane);
+    if (lane == 0) tot[s] = t;
   }
+  __syncthreads();
   if (tid != 0) return;
   const float a_j = float(tot[0] / n_elems);
   alpha_out[j] = a_j;
@@ -1642,30 +1719,53 @@ hipError_t decode_k(const accept_desc& d, const uint8_t* payload, const float* h
   return hipErrorInvalidValue;
 }
 
+// What the passes of one initialisation share.
+struct InitCall {
+  float* alpha_out;
+  const double* prev;  // records of the pass before
+  int nprev;
+  double* records;     // of this pass
+  double n_elems;
+};
+
 template <typename T, int K, int VEC>
-hipError_t launch_init_encode(const accept_desc& d, const T* x, const float* alpha, uint8_t* payload, double* records,
-                              int grid, hipStream_t s) {
+hipError_t launch_init_encode(const accept_desc& d, const T* x, const InitCall& c, uint8_t* payload, int grid,
+                              hipStream_t s) {
   const int64_t ipg = d.m / VEC;
   const int64_t items = ((d.n + 7) / 8) * ipg;
-  hipLaunchKernelGGL((mbq_init_encode_kernel<T, K, VEC>), dim3(grid), dim3(kBlock), 0, s, x, alpha, payload, records,
-                     d.n, d.m, ipg, items, step_for(grid, ipg));
+  hipLaunchKernelGGL((mbq_init_encode_kernel<T, K, VEC>), dim3(grid), dim3(kBlock), 0, s, x, c.alpha_out, c.prev,
+                     c.nprev, c.n_elems, payload, c.records, d.n, d.m, ipg, items, step_for(grid, ipg));
   return hipGetLastError();
 }
 
 template <typename T, int VEC>
-hipError_t init_encode_k(const accept_desc& d, const T* x, const float* alpha, uint8_t* payload, double* records,
-                         int grid, hipStream_t s) {
+hipError_t init_encode_k(const accept_desc& d, const T* x, const InitCall& c, uint8_t* payload, int grid, hipStream_t s) {
   switch (d.bits) {
-    case 1: return launch_init_encode<T, 1, VEC>(d, x, alpha, payload, records, grid, s);
-    case 2: return launch_init_encode<T, 2, VEC>(d, x, alpha, payload, records, grid, s);
-    case 3: return launch_init_encode<T, 3, VEC>(d, x, alpha, payload, records, grid, s);
-    case 4: return launch_init_encode<T, 4, VEC>(d, x, alpha, payload, records, grid, s);
-    case 5: return launch_init_encode<T, 5, VEC>(d, x, alpha, payload, records, grid, s);
-    case 6: return launch_init_encode<T, 6, VEC>(d, x, alpha, payload, records, grid, s);
-    case 7: return launch_init_encode<T, 7, VEC>(d, x, alpha, payload, records, grid, s);
-    case 8: return launch_init_encode<T, 8, VEC>(d, x, alpha, payload, records, grid, s);
+    case 1: return launch_init_encode<T, 1, VEC>(d, x, c, payload, grid, s);
+    case 2: return launch_init_encode<T, 2, VEC>(d, x, c, payload, grid, s);
+    case 3: return launch_init_encode<T, 3, VEC>(d, x, c, payload, grid, s);
+    case 4: return launch_init_encode<T, 4, VEC>(d, x, c, payload, grid, s);
+    case 5: return launch_init_encode<T, 5, VEC>(d, x, c, payload, grid, s);
+    case 6: return launch_init_encode<T, 6, VEC>(d, x, c, payload, grid, s);
+    case 7: return launch_init_encode<T, 7, VEC>(d, x, c, payload, grid, s);
+    case 8: return launch_init_encode<T, 8, VEC>(d, x, c, payload, grid, s);
     default: return hipErrorInvalidValue;
   }
+}
+
+template <typename T>
+hipError_t launch_init_pass(int j, const T* x, int64_t N, const InitCall& c, int grid, hipStream_t s) {
+#define ACCEPT_INIT(JJ)                                                                                        \
+  case JJ:                                                                                                     \
+    hipLaunchKernelGGL((mbq_init_pass_kernel<T, JJ>), dim3(grid), dim3(kBlock), 0, s, x, N, c.alpha_out, c.prev, \
+                       c.nprev, c.n_elems, c.records);                                                         \
+    break;
+  switch (j) {
+    ACCEPT_INIT(0) ACCEPT_INIT(1) ACCEPT_INIT(2) ACCEPT_INIT(3) ACCEPT_INIT(4) ACCEPT_INIT(5) ACCEPT_INIT(6) ACCEPT_INIT(7)
+    default: return hipErrorInvalidValue;
+  }
+#undef ACCEPT_INIT
+  return hipGetLastError();
 }
 
 }  // namespace
@@ -1811,41 +1911,34 @@ hipError_t launch_mbq_init(const accept_desc& d, const MPlan& p, const void* x, 
   const int64_t N = d.n * d.m;
   const int k = d.bits;
   const bool bf = d.in_dtype == ACCEPT_BF16;
-  const int grid = grid_for(N / (bf ? 8 : 4) / 4 + 1, kInitGrid);
+  const bf16_t* xb = static_cast<const bf16_t*>(x);
+  const float* xf = static_cast<const float*>(x);
+  const int64_t tiles = (N + kTileElems - 1) / kTileElems;
+  InitCall c{alpha_out, nullptr, 0, nullptr, double(N)};
+  int nrec = 0, nstat = 1;
   hipError_t e;
   for (int j = 0; j < k; ++j) {
-    const bool planes = payload != nullptr && j == k - 1;
-    int nrec = grid, nstat = 1;
-    if (planes) {
-      const int init_vec = d.m % p.vec == 0 ? p.vec : 1;
-      nrec = grid_for(p.G * (d.m / init_vec), kPlainGridMax);
-      nstat = k + 2;
+    c.prev = c.records;
+    c.nprev = nrec;
+    c.records = records + int64_t(j) * kMaxRecords;
+    if (payload != nullptr && j == k - 1) {
       uint8_t* pl = static_cast<uint8_t*>(payload);
-      if (bf) {
-        const bf16_t* xb = static_cast<const bf16_t*>(x);
-        e = init_vec == 8 ? init_encode_k<bf16_t, 8>(d, xb, alpha_out, pl, records, nrec, s)
-                       : init_encode_k<bf16_t, 1>(d, xb, alpha_out, pl, records, nrec, s);
-      } else {
-        const float* xf = static_cast<const float*>(x);
-        e = init_vec == 4 ? init_encode_k<float, 4>(d, xf, alpha_out, pl, records, nrec, s)
-                       : init_encode_k<float, 1>(d, xf, alpha_out, pl, records, nrec, s);
-      }
-    } else {
+      const int vec = d.m % p.vec == 0 ? p.vec : 1;
+      nrec = grid_for(p.G * (d.m / vec), kPlainGridMax);
+      nstat = k + 2;
       if (bf)
-        hipLaunchKernelGGL((mbq_init_pass_kernel<bf16_t>), dim3(grid), dim3(kBlock), 0, s,
-                           static_cast<const bf16_t*>(x), N, j, alpha_out, records);
+        e = vec == 8 ? init_encode_k<bf16_t, 8>(d, xb, c, pl, nrec, s) : init_encode_k<bf16_t, 1>(d, xb, c, pl, nrec, s);
       else
-        hipLaunchKernelGGL((mbq_init_pass_kernel<float>), dim3(grid), dim3(kBlock), 0, s, static_cast<const float*>(x),
-                           N, j, alpha_out, records);
-      e = hipGetLastError();
+        e = vec == 4 ? init_encode_k<float, 4>(d, xf, c, pl, nrec, s) : init_encode_k<float, 1>(d, xf, c, pl, nrec, s);
+    } else {
+      nrec = int(tiles < kInitGrid ? tiles : kInitGrid);
+      e = bf ? launch_init_pass<bf16_t>(j, xb, N, c, nrec, s) : launch_init_pass<float>(j, xf, N, c, nrec, s);
     }
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(mbq_init_finalize_kernel, dim3(1), dim3(kBlock), 0, s, records, nrec, nstat, double(N), j,
-                       alpha_out);
-    e = hipGetLastError();
-    if (e != hipSuccess) return e;
   }
-  return hipSuccess;
+  hipLaunchKernelGGL(mbq_init_finalize_kernel, dim3(1), dim3(kFinalizeBlock), 0, s, c.records, nrec, nstat, c.n_elems,
+                     k - 1, alpha_out);
+  return hipGetLastError();
 }
 
 }  // namespace accept
