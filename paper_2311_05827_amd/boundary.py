@@ -17,6 +17,7 @@ batch and wires it into PyTorch:
 from __future__ import annotations
 
 from . import binding as B
+import torch  # after the binding, which decides the order in which the runtimes are loaded
 
 
 class BitWidthController:
@@ -46,6 +47,7 @@ class ForwardCompressor:
         self.alpha = None       # device tensor of k floats
         self._k = None
         self._bufs = None
+        self._alpha_view = None  # the k coefficients inside the header buffer
 
     def start_epoch(self):
         """Batch 0 of an epoch re-initialises alpha from the data (residue method)."""
@@ -65,6 +67,7 @@ class ForwardCompressor:
         d = self._desc(k)
         if self._bufs is None:
             self._bufs = B.alloc_outputs(d, x.device)
+            self._alpha_view = self._bufs[0][: 4 * k].view(torch.float32)
         header, payload, ws = self._bufs
         if self.alpha is None:
             # batch 0 of an epoch: B^0 and alpha^0 of the residue method are what is sent; the
@@ -72,7 +75,7 @@ class ForwardCompressor:
             B.accept_mbq_compress_first(d, x, header=header, payload=payload, workspace=ws)
         else:
             B.accept_compress(d, x, alpha_prev=self.alpha, header=header, payload=payload, workspace=ws)
-        self.alpha = header[: 4 * k].view(_torch().float32).clone()
+        self.alpha = self._alpha_view.clone()
         self.t += 1
         return d, header, payload
 
@@ -125,9 +128,23 @@ class BackwardCompressor:
         return h + p
 
 
-def _torch():
-    import torch
-    return torch
+class _Boundary(torch.autograd.Function):
+    @staticmethod
+    def forward(ctx, inp, forward, backward):
+        ctx.compressor = backward
+        flat = inp.contiguous().view(-1)
+        d, header, payload = forward.compress(flat)
+        out = forward.decompress(d, header, payload)
+        return out.view(inp.shape)
+
+    @staticmethod
+    def backward(ctx, grad):
+        backward = ctx.compressor
+        if backward is None:
+            return grad, None, None
+        flat = grad.contiguous().view(-1)
+        d, header, payload = backward.compress(flat)
+        return backward.decompress(d, header, payload).view(grad.shape), None, None
 
 
 def boundary(x, forward, backward=None):
@@ -136,22 +153,4 @@ def boundary(x, forward, backward=None):
     Forward: x is compressed and decompressed by `forward` (what the next device receives).
     Backward: straight-through estimator; with `backward` given, the incoming gradient first
     takes that compressor's round trip (what the previous device receives)."""
-    torch = _torch()
-
-    class _Boundary(torch.autograd.Function):
-        @staticmethod
-        def forward(ctx, inp):
-            flat = inp.contiguous().view(-1)
-            d, header, payload = forward.compress(flat)
-            out = forward.decompress(d, header, payload)
-            return out.view(inp.shape)
-
-        @staticmethod
-        def backward(ctx, grad):
-            if backward is None:
-                return grad
-            flat = grad.contiguous().view(-1)
-            d, header, payload = backward.compress(flat)
-            return backward.decompress(d, header, payload).view(grad.shape)
-
-    return _Boundary.apply(x)
+    return _Boundary.apply(x, forward, backward)
