@@ -67,9 +67,10 @@ struct UPlan {
   int col_tx;          // U_GENERIC: column threads per workgroup of the column pass (a power of two)
   int64_t col_grid_x;  // U_GENERIC: workgroups across the columns
   int col_grid_y;      // U_GENERIC: row blocks = maxima kept per column
-  bool fast;           // vector path usable (every 16-byte vector lies inside one range group, or per_element)
+  bool fast;           // vector path usable (every 16-byte vector lies inside one range group, or per_element, or straddling)
   bool local_ranges;   // U_SEGMENTED: the quantize pass finishes the per-channel ranges itself, tile by tile
   bool per_element;    // U_GENERIC: one element per segment and rows of whole vectors (channels-last)
+  bool straddling;     // U_GENERIC: segments longer than a vector but not whole vectors
   bool held;           // U_TENSOR: the range pass keeps the end of the tensor on the chip and quantizes it itself
   int64_t held_units;  // held: whole units (see kUnitElems) of the tensor
   int held_lds;        // held: units per workgroup that stay in local memory (the others in registers)

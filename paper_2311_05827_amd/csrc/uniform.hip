@@ -127,19 +127,33 @@ constexpr int kRangePerVectorLocal = 3;  // as kRangePerVector, quantizer only: 
                                          // its own small table (channel minus the tile's first channel, modulo C)
 constexpr int kOneRangeHeld = 4;  // as kOneRange, quantizer only: after quantize_held_kernel, of whose part only what
                                   // it did not finish is left to do
+constexpr int kRangeStraddling = 5;  // segments longer than a vector but not whole vectors: a vector lies in one segment
+                                     // or across the border of two; positions are counted in elements (ChanGeom.seg_vecs
+                                     // is the segment's elements, ChanPos.rem the element's place in it).  64 x 1024 x 196
+                                     // bfloat16: quantize 22.2 -> 9.5 us, decode 26.5 -> 7.9 us against single elements
+                                     // whose channel is divided out of their index
+// Position units of a vector.
+template <int MODE, int VEC>
+constexpr int kUnitsPerVec = MODE == kRangeStraddling ? VEC : 1;
 constexpr bool one_range(int mode) { return mode == kOneRange || mode == kOneRangeHeld; }
 // The per-group values (reciprocals for the quantizer, scales for the decoder) of a vector's elements.
 template <int MODE, int VEC>
-__device__ __forceinline__ void ranges_of_vector(const float* __restrict__ tab, float one, int32_t ch,
-                                                 float (&out)[VEC]) {
+__device__ __forceinline__ void ranges_of_vector(const float* __restrict__ tab, float one, const ChanPos& pos,
+                                                 const ChanGeom& g, float (&out)[VEC]) {
   if constexpr (MODE == kRangePerElement) {
 #pragma unroll
     for (int h = 0; h < VEC / 4; ++h) {
-      const float4 t = *reinterpret_cast<const float4*>(tab + int64_t(ch) * VEC + 4 * h);  // tab is 16-byte aligned
+      const float4 t = *reinterpret_cast<const float4*>(tab + int64_t(pos.ch) * VEC + 4 * h);  // tab is 16-byte aligned
       out[4 * h] = t.x; out[4 * h + 1] = t.y; out[4 * h + 2] = t.z; out[4 * h + 3] = t.w;
     }
+  } else if constexpr (MODE == kRangeStraddling) {
+    const float v0 = tab[pos.ch], v1 = tab[pos.ch + 1 == g.C ? 0 : pos.ch + 1];
+    const int64_t left = g.seg_vecs - pos.rem;  // elements of the first segment from here on, at least 1
+    const int cut = left < VEC ? int(left) : VEC;
+#pragma unroll
+    for (int e = 0; e < VEC; ++e) out[e] = e < cut ? v0 : v1;
   } else {
-    const float v = one_range(MODE) ? one : tab[ch];
+    const float v = one_range(MODE) ? one : tab[pos.ch];
 #pragma unroll
     for (int e = 0; e < VEC; ++e) out[e] = v;
   }
@@ -210,12 +224,18 @@ __global__ __launch_bounds__(kBlock) void range_tensor_kernel(const T* __restric
 // partial index = (ch*cps + chunk)*rows + r: the maxima of one channel lie together.  Workgroup t takes the chunks that begin inside tile t
 // of the quantize pass (8192 consecutive elements), its wavefronts in turn: the data a die reads
 // here is, up to a chunk's overhang, the data the quantize pass reads through the same die's L2.
-template <typename T>
+// U: 16-byte loads of a lane and chunk that are in flight together; 1, 2 and 4 are for chunks of at
+// most 64 U vectors, of which a wavefront then takes 8/U at a time.  (With eight loads for every
+// chunk, three quarters of them repeats of its last vector, and its place divided out of its number,
+// 64 x 512 x 784 bfloat16, 98 vectors a chunk, took 22.2 us; now 15.5.)
+template <typename T, int U>
 __global__ __launch_bounds__(kBlock) void range_segments_kernel(const T* __restrict__ x, int64_t items, int64_t cps,
                                                                  int64_t seg_vecs, int64_t chunk_vecs, int64_t rows,
                                                                  int64_t C, float* __restrict__ partials) {
   constexpr int VEC = Elem<T>::VEC;
   constexpr int64_t TILE_VECS = kTileElems / VEC;
+  constexpr int NI = 8 / U;  // chunks of a wavefront at a time
+  constexpr int WAVES = kBlock / kWave;
   const int lane = threadIdx.x & (kWave - 1);
   // first chunk that begins at or after vector a: the segment of a, and the chunk of a rounded up
   auto first_item_from = [&](int64_t a) {
@@ -227,49 +247,84 @@ __global__ __launch_bounds__(kBlock) void range_segments_kernel(const T* __restr
   };
   const int64_t it_lo = first_item_from(int64_t(blockIdx.x) * TILE_VECS);
   const int64_t it_hi = blockIdx.x + 1 == gridDim.x ? items : first_item_from((int64_t(blockIdx.x) + 1) * TILE_VECS);
-  for (int64_t it = it_lo + threadIdx.x / kWave; it < it_hi; it += kBlock / kWave) {
-    const int64_t sid = it / cps;
-    const int64_t chunk = it - sid * cps;
-    const int64_t first = chunk * chunk_vecs;
-    int64_t count = seg_vecs - first;
-    if (count > chunk_vecs) count = chunk_vecs;
-    const T* base = x + (sid * seg_vecs + first) * VEC;
-    float c = 0.0f;
-    // eight loads in flight per lane, kept as raw vectors until used; a lane whose turn lies
-    // beyond the chunk's end re-reads the chunk's last vector (a maximum does not mind), so that
-    // the loads stay unconditional and a chunk's last vectors do not cost a trip to memory each
-    // (a chunk that begins in the part of the tensor that is read with streaming loads: see
-    // kRangeKeepBytes; the choice is the same for all lanes of the wavefront)
-    const bool stream = (sid * seg_vecs + first) * int64_t(VEC * sizeof(T)) + kRangeKeepBytes <
-                        items / cps * seg_vecs * int64_t(VEC * sizeof(T));
-    for (int64_t j = lane; j < count; j += 8 * kWave) {
-      uint4 raw[8];
-      if (stream) {
+  // This wavefront's chunk: number, segment, place in the segment, batch row, channel.  All of it is
+  // the same in all lanes and said to be (the arithmetic then runs on the scalar unit), and it is
+  // stepped, not divided out again for every chunk.
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+  int64_t it = it_lo + wave;
+  if (it >= it_hi) return;
+  int64_t sid = it / cps;
+  int64_t chunk = it - sid * cps;
+  int64_t row = sid / C, ch = sid - row * C;
+  const int64_t d_sid = WAVES / cps, d_chunk = WAVES - d_sid * cps;
+  const int64_t stream_vecs = items / cps * seg_vecs - kRangeKeepBytes / int64_t(VEC * sizeof(T));
+  for (bool more = true; more;) {
+    float c[NI];
+    int64_t slot[NI];  // where the chunk's maximum goes
 #pragma unroll
-        for (int u = 0; u < 8; ++u) {
-          int64_t idx = j + u * kWave;
-          if (idx >= count) idx = count - 1;
-          raw[u] = load16_stream(base + idx * VEC);
-        }
-      } else {
+    for (int i = 0; i < NI; ++i) c[i] = 0.0f;
+    uint4 raw[NI][U];
+    auto reduce = [&](int i) {
 #pragma unroll
-        for (int u = 0; u < 8; ++u) {
-          int64_t idx = j + u * kWave;
-          if (idx >= count) idx = count - 1;
-          raw[u] = load16(base + idx * VEC);
-        }
-      }
-#pragma unroll
-      for (int u = 0; u < 8; ++u) {
+      for (int u = 0; u < U; ++u) {
         float f[VEC];
-        widen(raw[u], f);
+        widen(raw[i][u], f);
 #pragma unroll
-        for (int e = 0; e < VEC; ++e) c = fmaxf(c, fabsf(f[e]));
+        for (int e = 0; e < VEC; ++e) c[i] = fmaxf(c[i], fabsf(f[e]));
+      }
+    };
+#pragma unroll
+    for (int i = 0; i < NI; ++i) {
+      const int64_t first = chunk * chunk_vecs;
+      const int count = int(seg_vecs - first < chunk_vecs ? seg_vecs - first : chunk_vecs);  // at most a tile
+      const T* base = x + (sid * seg_vecs + first) * VEC;
+      slot[i] = (ch * cps + chunk) * rows + row;
+      // the loads of a turn are in flight together, kept as raw vectors until used; a lane whose turn
+      // lies beyond the chunk's end re-reads the chunk's last vector (a maximum does not mind), so
+      // that the loads stay unconditional and a chunk's last vectors do not cost a trip to memory each
+      // (a chunk that begins in the part of the tensor that is read with streaming loads: see
+      // kRangeKeepBytes)
+      const bool stream = sid * seg_vecs + first < stream_vecs;
+      for (int j = lane; j < count; j += U * kWave) {
+        if (stream) {
+#pragma unroll
+          for (int u = 0; u < U; ++u) {
+            const int idx = j + u * kWave < count ? j + u * kWave : count - 1;
+            raw[i][u] = load16_stream(base + idx * VEC);
+          }
+        } else {
+#pragma unroll
+          for (int u = 0; u < U; ++u) {
+            const int idx = j + u * kWave < count ? j + u * kWave : count - 1;
+            raw[i][u] = load16(base + idx * VEC);
+          }
+        }
+        if (NI > 1) break;  // one turn covers the chunk
+        reduce(i);
+      }
+      // lanes that had no vector at all (a chunk of fewer than 64)
+      if (NI > 1 && lane >= count) {
+#pragma unroll
+        for (int u = 0; u < U; ++u) raw[i][u] = make_uint4(0u, 0u, 0u, 0u);
+      }
+      // the next chunk; after the last one that one again (its maximum is stored more than once)
+      more = it + WAVES < it_hi;
+      if (more) {
+        it += WAVES;
+        chunk += d_chunk;
+        int64_t step = d_sid;
+        if (chunk >= cps) { chunk -= cps; ++step; }
+        sid += step;
+        ch += step;
+        while (ch >= C) { ch -= C; ++row; }
       }
     }
-    c = wave_max(c);  // every lane of the wavefront reaches this point: the loop bounds are wave-uniform
-    const int64_t row = sid / C;
-    if (lane == 0) partials[((sid - row * C) * cps + chunk) * rows + row] = c;
+#pragma unroll
+    for (int i = 0; i < NI; ++i) {
+      if (NI > 1) reduce(i);
+      c[i] = wave_max(c[i]);  // every lane of the wavefront reaches this point: the loop bounds are wave-uniform
+      if (lane == 0) partials[slot[i]] = c[i];
+    }
   }
 }
 
@@ -503,6 +558,8 @@ __global__ __launch_bounds__(kBlock) void quantize_pack_kernel(
     int64_t seg_len, uint64_t seed, int64_t held_tiles, uint64_t* __restrict__ mail) {
   constexpr int VEC = Elem<T>::VEC;
   constexpr int64_t TILE_VECS = kTileElems / VEC;
+  constexpr int UNITS = kUnitsPerVec<MODE, VEC>;
+  constexpr int64_t TILE_UNITS = TILE_VECS * UNITS;
   constexpr int QPV = VEC / 4;                       // pieces per vector
   constexpr int LOADS = kTileElems / (kBlock * VEC);  // vectors per thread per tile
   constexpr int PIECES = kTileElems / 4;
@@ -577,9 +634,9 @@ __global__ __launch_bounds__(kBlock) void quantize_pack_kernel(
   ChanPos first_pos{0, 0};
   ChanStep mine{0, 0};
   if (!one_range(MODE) && int64_t(blockIdx.x) < full_tiles) {
-    first_pos = chan_init(geom, tile_of(blockIdx.x) * TILE_VECS);
-    mine.dr = int64_t(tid) % geom.seg_vecs;
-    mine.dch = int32_t((int64_t(tid) / geom.seg_vecs) % geom.C);
+    first_pos = chan_init(geom, tile_of(blockIdx.x) * TILE_UNITS);
+    mine.dr = int64_t(tid * UNITS) % geom.seg_vecs;
+    mine.dch = int32_t((int64_t(tid * UNITS) / geom.seg_vecs) % geom.C);
   }
 
   // kRangePerVectorLocal: the reciprocals of the channels a tile touches, entry t for channel
@@ -659,7 +716,7 @@ __global__ __launch_bounds__(kBlock) void quantize_pack_kernel(
     LocalFetch next_lf;
     if (!one_range(MODE) && next_f < tiles) {
       if (next_f < rev_tiles) chan_retreat(geom, next_pos, geom.sgrid);
-      else next_pos = chan_init(geom, tile_of(next_f) * TILE_VECS);
+      else next_pos = chan_init(geom, tile_of(next_f) * TILE_UNITS);
       if (MODE == kRangePerVectorLocal) local_fetch(next_pos, next_lf);
     }
     ChanPos pos = first_pos;
@@ -670,11 +727,12 @@ __global__ __launch_bounds__(kBlock) void quantize_pack_kernel(
     for (int u = 0; u < LOADS; ++u) {
       float r[VEC];
       if (MODE == kRangePerVectorLocal) {
-        int32_t t = pos.ch - ch0;
-        if (t < 0) t += geom.C;
-        ranges_of_vector<MODE, VEC>(local_r[buf], r_tensor, t, r);
+        ChanPos in_table = pos;
+        in_table.ch = pos.ch - ch0;
+        if (in_table.ch < 0) in_table.ch += geom.C;
+        ranges_of_vector<MODE, VEC>(local_r[buf], r_tensor, in_table, geom, r);
       } else {
-        ranges_of_vector<MODE, VEC>(rtab, r_tensor, pos.ch, r);
+        ranges_of_vector<MODE, VEC>(rtab, r_tensor, pos, geom, r);
       }
       if (!one_range(MODE)) chan_advance(geom, pos, geom.s256);
       float f[VEC];
@@ -976,10 +1034,10 @@ __global__ __launch_bounds__(kBlock) void unpack_dequant_kernel(
   int64_t v = int64_t(blockIdx.x) * kBlock + threadIdx.x;
   const float s_tensor = MODE != kOneRange ? 0.0f : header[0];
   ChanPos pos{0, 0};
-  if (MODE != kOneRange && v < fast_vecs) pos = chan_init(geom, v);
+  if (MODE != kOneRange && v < fast_vecs) pos = chan_init(geom, v * kUnitsPerVec<MODE, VEC>);
   for (; v < fast_vecs; v += stride) {
     float s[VEC];
-    ranges_of_vector<MODE, VEC>(header, s_tensor, pos.ch, s);
+    ranges_of_vector<MODE, VEC>(header, s_tensor, pos, geom, s);
     if (MODE != kOneRange) chan_advance(geom, pos, geom.sgrid);
     float f[VEC];
 #pragma unroll
@@ -1013,7 +1071,7 @@ __global__ __launch_bounds__(kBlock) void unpack_dequant_tiled_kernel(
   const float s_tensor = MODE != kOneRange ? 0.0f : header[0];
   ChanPos tile_pos{0, 0};
   if (MODE != kOneRange && full_tiles > 0)
-    tile_pos = chan_init(geom, int64_t(blockIdx.x) * (kTileElems / VEC) + tid);
+    tile_pos = chan_init(geom, (int64_t(blockIdx.x) * (kTileElems / VEC) + tid) * kUnitsPerVec<MODE, VEC>);
   if (tid < 4) { tile[0][TILE_DW + tid] = 0u; tile[1][TILE_DW + tid] = 0u; }
   int buf = 0;
   for (int64_t t = blockIdx.x; t < full_tiles; t += gridDim.x, buf ^= 1) {
@@ -1030,7 +1088,7 @@ __global__ __launch_bounds__(kBlock) void unpack_dequant_tiled_kernel(
 #pragma unroll
     for (int j = 0; j < VPT; ++j) {
       float s[VEC];
-      ranges_of_vector<MODE, VEC>(header, s_tensor, pos.ch, s);
+      ranges_of_vector<MODE, VEC>(header, s_tensor, pos, geom, s);
       if (MODE != kOneRange) chan_advance(geom, pos, geom.s256);
       const int vec_in_tile = j * kBlock + tid;
       float f[VEC];
@@ -1083,10 +1141,11 @@ hipError_t launch_quant(const accept_desc& d, const UPlan& p, const T* x, float*
   g.C = 1;
   if (!one_range(MODE) && p.fast) {
     // per element: the "segments" are single vectors and the "channels" the m / vec vectors of a row
-    g.seg_vecs = MODE == kRangePerElement ? 1 : p.seg_len / p.vec;
+    constexpr int UNITS = kUnitsPerVec<MODE, Elem<T>::VEC>;
+    g.seg_vecs = MODE == kRangePerElement ? 1 : MODE == kRangeStraddling ? p.seg_len : p.seg_len / p.vec;
     g.C = int32_t(MODE == kRangePerElement ? p.m / p.vec : p.C);
-    g.s256 = make_step(kBlock, g.seg_vecs, g.C);
-    g.sgrid = make_step(int64_t(grid) * (kTileElems / p.vec), g.seg_vecs, g.C);
+    g.s256 = make_step(kBlock * UNITS, g.seg_vecs, g.C);
+    g.sgrid = make_step(int64_t(grid) * (kTileElems / p.vec) * UNITS, g.seg_vecs, g.C);
   }
   const int64_t payload_bytes = (N * K + 7) / 8;
   hipLaunchKernelGGL((quantize_pack_kernel<T, K, MODE, STOCH>), dim3(grid), dim3(kBlock), 0, s, x, payload, header,
@@ -1281,6 +1340,10 @@ hipError_t launch_quant_k(const accept_desc& d, const UPlan& p, const T* x, floa
     return stoch ? launch_quant<T, K, kRangePerElement, true>(d, p, x, header, payload, partials, rtab, mail, s)
                  : launch_quant<T, K, kRangePerElement, false>(d, p, x, header, payload, partials, rtab, mail, s);
   }
+  if (p.straddling) {
+    return stoch ? launch_quant<T, K, kRangeStraddling, true>(d, p, x, header, payload, partials, rtab, mail, s)
+                 : launch_quant<T, K, kRangeStraddling, false>(d, p, x, header, payload, partials, rtab, mail, s);
+  }
   if (p.local_ranges) {
     return stoch ? launch_quant<T, K, kRangePerVectorLocal, true>(d, p, x, header, payload, partials, rtab, mail, s)
                  : launch_quant<T, K, kRangePerVectorLocal, false>(d, p, x, header, payload, partials, rtab, mail, s);
@@ -1329,8 +1392,14 @@ hipError_t compress_typed(const accept_desc& d, UPlan p, const T* x, float* head
     hipLaunchKernelGGL((range_tensor_kernel<T>), dim3(p.range_grid), dim3(kBlock), 0, s, x, p.N, partials);
   } else if (p.mode == U_SEGMENTED) {
     const int64_t tiles = (p.N + kTileElems - 1) / kTileElems;  // below 2^31: N is at most 2^40
-    hipLaunchKernelGGL((range_segments_kernel<T>), dim3(unsigned(tiles)), dim3(kBlock), 0, s, x, p.items, p.cps,
-                       p.seg_len / p.vec, p.chunk_vecs, d.n, p.C, partials);
+#define ACCEPT_SEGMENTS(UU)                                                                                   \
+  hipLaunchKernelGGL((range_segments_kernel<T, UU>), dim3(unsigned(tiles)), dim3(kBlock), 0, s, x, p.items, p.cps, \
+                     p.seg_len / p.vec, p.chunk_vecs, d.n, p.C, partials)
+    if (p.chunk_vecs <= kWave) ACCEPT_SEGMENTS(1);
+    else if (p.chunk_vecs <= 2 * kWave) ACCEPT_SEGMENTS(2);
+    else if (p.chunk_vecs <= 4 * kWave) ACCEPT_SEGMENTS(4);
+    else ACCEPT_SEGMENTS(8);
+#undef ACCEPT_SEGMENTS
   } else {
     const dim3 grid(unsigned(p.col_grid_x), unsigned(p.col_grid_y));
     if (p.m % Elem<T>::VEC == 0)
@@ -1395,6 +1464,7 @@ template <typename TO, int K, int MODE>
 hipError_t launch_dequant(const accept_desc& d, const float* header, const uint32_t* payload, TO* xhat,
                           hipStream_t s) {
   constexpr int VEC = Elem<TO>::VEC;
+  constexpr int UNITS = kUnitsPerVec<MODE, VEC>;
   const int64_t N = d.n * d.m;
   const int64_t C = d.channels > 1 ? d.channels : 1;
   const int64_t seg_len = d.m / C;
@@ -1412,9 +1482,9 @@ hipError_t launch_dequant(const accept_desc& d, const float* header, const uint3
   g.seg_vecs = 1;
   g.C = 1;
   if (MODE != kOneRange && fast) {
-    g.seg_vecs = MODE == kRangePerElement ? 1 : seg_len / VEC;
+    g.seg_vecs = MODE == kRangePerElement ? 1 : MODE == kRangeStraddling ? seg_len : seg_len / VEC;
     g.C = int32_t(MODE == kRangePerElement ? d.m / VEC : C);
-    g.sgrid = make_step(int64_t(grid) * kBlock, g.seg_vecs, g.C);
+    g.sgrid = make_step(int64_t(grid) * kBlock * UNITS, g.seg_vecs, g.C);
     g.s256 = g.sgrid;
   }
   const int64_t payload_bytes = (N * K + 7) / 8;
@@ -1424,8 +1494,8 @@ hipError_t launch_dequant(const accept_desc& d, const float* header, const uint3
     int64_t want = full_tiles > (tail + kBlock - 1) / kBlock ? full_tiles : (tail + kBlock - 1) / kBlock;
     const int tgrid = int(want < kDequantGridMax ? want : kDequantGridMax);
     if (MODE != kOneRange) {
-      g.s256 = make_step(kBlock, g.seg_vecs, g.C);
-      g.sgrid = make_step(int64_t(tgrid) * (kTileElems / VEC), g.seg_vecs, g.C);
+      g.s256 = make_step(kBlock * UNITS, g.seg_vecs, g.C);
+      g.sgrid = make_step(int64_t(tgrid) * (kTileElems / VEC) * UNITS, g.seg_vecs, g.C);
     }
     hipLaunchKernelGGL((unpack_dequant_tiled_kernel<TO, K, MODE>), dim3(tgrid), dim3(kBlock), 0, s, payload, header,
                        xhat, N, full_tiles, payload_bytes, g, d.m, seg_len);
@@ -1458,12 +1528,16 @@ hipError_t decompress_typed(const accept_desc& d, const float* header, const uin
   // (the scales are then read as 16-byte vectors: a header that is only 4-byte aligned takes the plain path)
   const bool per_element = d.channels > 1 && d.channels == d.m && d.m % Elem<TO>::VEC == 0 &&
                            (reinterpret_cast<uintptr_t>(header) & 15u) == 0;
-  const int mode = d.channels > 1 ? (per_element ? kRangePerElement : kRangePerVector) : kOneRange;
+  const int64_t seg_len = d.m / (d.channels > 1 ? d.channels : 1);
+  const bool straddling = seg_len > Elem<TO>::VEC && seg_len % Elem<TO>::VEC != 0;
+  const int mode = d.channels > 1 ? (per_element ? kRangePerElement : straddling ? kRangeStraddling : kRangePerVector)
+                                  : kOneRange;
 #define ACCEPT_DQ(KK)                                                                                   \
   case KK:                                                                                              \
-    return mode == kRangePerElement  ? launch_dequant<TO, KK, kRangePerElement>(d, header, payload, xhat, s) \
-           : mode == kRangePerVector ? launch_dequant<TO, KK, kRangePerVector>(d, header, payload, xhat, s)  \
-                                     : launch_dequant<TO, KK, kOneRange>(d, header, payload, xhat, s);
+    return mode == kRangePerElement   ? launch_dequant<TO, KK, kRangePerElement>(d, header, payload, xhat, s) \
+           : mode == kRangePerVector  ? launch_dequant<TO, KK, kRangePerVector>(d, header, payload, xhat, s)  \
+           : mode == kRangeStraddling ? launch_dequant<TO, KK, kRangeStraddling>(d, header, payload, xhat, s) \
+                                      : launch_dequant<TO, KK, kOneRange>(d, header, payload, xhat, s);
   switch (d.bits) {
     ACCEPT_DQ(2) ACCEPT_DQ(3) ACCEPT_DQ(4) ACCEPT_DQ(5) ACCEPT_DQ(6) ACCEPT_DQ(7) ACCEPT_DQ(8)
     default: return hipErrorInvalidValue;
@@ -1521,7 +1595,8 @@ UPlan make_uplan(const accept_desc& d) {
     // channels-last (one element per segment) with rows of whole vectors: the quantizer's fast
     // path with one range per element
     p.per_element = p.seg_len == 1 && d.m % p.vec == 0;
-    p.fast = (p.seg_len % p.vec == 0) || p.per_element;
+    p.straddling = p.seg_len > p.vec && p.seg_len % p.vec != 0;
+    p.fast = (p.seg_len % p.vec == 0) || p.per_element || p.straddling;
     // column pass: threads own vectors of columns when every row keeps them aligned, else columns
     const int64_t ncv = (d.m % p.vec == 0) ? d.m / p.vec : d.m;
     int tx = 1;

@@ -251,6 +251,33 @@ def test_stochastic_rounding_over_many_tiles(A, k, bf16, seed):
     run_case(A, si.make_shape("grad", (1, N), 64), k, 1, N, rounding=1, seed=seed, in_bf16=bf16, tag="stoch-tiles")
 
 
+def per_channel_input(n, C, seg, seed):
+    x = si.make_shape("grad", (n, C, seg), seed)
+    gain = (np.float32(2.0) ** np.random.default_rng(seed).integers(-6, 7, C)).astype(np.float32)
+    return np.ascontiguousarray(x * gain[None, :, None], dtype=np.float32)
+
+
+@pytest.mark.parametrize("seg", [5, 6, 7, 9, 11, 49, 50, 196, 1023])
+def test_segments_that_are_not_whole_vectors(A, seg):
+    """Vectors across the border of two channels, and of the last channel and the next row's first."""
+    for n, C, k, bf16, rounding in ((3, 2, 5, False, 0), (9, 37, 6, True, 0), (40, 5, 8, False, 1), (7, 300, 4, True, 1)):
+        x = per_channel_input(n, C, seg, 300 + seg)
+        run_case(A, x, k, n, C * seg, channels=C, in_bf16=bf16, out_bf16=bf16, rounding=rounding, seed=5, tag="straddling")
+    if seg == 49:  # more tiles than workgroups
+        x = per_channel_input(64, 5376, seg, 350)
+        run_case(A, x, 3, 64, 5376 * seg, channels=5376, tag="straddling, many tiles")
+
+
+@pytest.mark.parametrize("seg", [512, 516, 520, 784, 1024, 1032, 2048, 2056, 4096, 4104, 8200, 20488])
+def test_segment_lengths_of_the_range_pass(A, seg):
+    """One, two, four and eight loads per lane and chunk, chunks that fill them and that do not."""
+    for n, C, k, bf16 in ((3, 5, 4, False), (2, 17, 6, True), (13, 3, 8, seg % 8 == 0)):
+        x = per_channel_input(n, C, seg, 400 + n)
+        x[n - 1, C - 1, seg - 1] = 100.0   # the very last element of the tensor
+        x[0, 0, 0] = -90.0
+        run_case(A, x, k, n, C * seg, channels=C, in_bf16=bf16, out_bf16=bf16, tag="segments")
+
+
 # One range, nearest rounding, 48 to 256 MiB: the end of the tensor is kept on the chip between the
 # range and the quantizer.  256 workgroups, units of 16384 elements; per workgroup 7 (bfloat16: 12)
 # units in registers, 2 (4) in local memory, the rest read twice.
