@@ -318,6 +318,48 @@ def test_held_pass_that_gives_up(A):
             assert first_mismatch(dev_bytes(payload), op.tobytes()) is None, polls
 
 
+def test_held_pass_on_two_streams_and_in_a_graph(A):
+    """Calls that overlap on two streams (each with its own buffers) compete for the compute units
+    the held pass waits on; a captured call is replayed on new inputs between eager ones."""
+    torch = torch_mod()
+    k, N = 6, 3 * HELD_ROUND + 16384 * 20 + 5
+    xs = [torch.from_numpy(si.make_shape("grad", (N,), 240 + i) * np.float32(1 + i)).cuda() for i in range(3)]
+    d = A.make_desc(A.UNIFORM, k, 1, N)
+    want = [orc.uniform_compress(x.cpu().numpy(), k, 1, N) for x in xs]
+    bufs = [A.alloc_outputs(d, "cuda") for _ in range(2)]
+    streams = [torch.cuda.Stream() for _ in range(2)]
+    torch.cuda.synchronize()
+    for turn in range(6):
+        for i, s in enumerate(streams):
+            with torch.cuda.stream(s):
+                header, payload, ws = bufs[i]
+                for rep in range(3):
+                    A.accept_compress(d, xs[(turn + i + rep) % 3], header=header, payload=payload, workspace=ws)
+        torch.cuda.synchronize()
+        for i in range(2):
+            oh, op = want[(turn + i + 2) % 3]
+            assert dev_bytes(bufs[i][0]) == oh, (turn, i)
+            assert first_mismatch(dev_bytes(bufs[i][1]), op.tobytes()) is None, (turn, i)
+    header, payload, ws = bufs[0]
+    x = xs[0].clone()
+    with torch.cuda.stream(streams[0]):
+        A.accept_compress(d, x, header=header, payload=payload, workspace=ws)
+    torch.cuda.synchronize()
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g):
+        A.accept_compress(d, x, header=header, payload=payload, workspace=ws)
+    for i in (1, 2, 0, 1):
+        x.copy_(xs[i])
+        payload.zero_()
+        g.replay()
+        torch.cuda.synchronize()
+        oh, op = want[i]
+        assert dev_bytes(header) == oh and first_mismatch(dev_bytes(payload), op.tobytes()) is None, i
+        A.accept_compress(d, xs[2], header=header, payload=payload, workspace=ws)  # eager, same workspace
+        torch.cuda.synchronize()
+        assert dev_bytes(header) == want[2][0]
+
+
 def test_decoder_on_oracle_stream(A):
     """Feed the oracle's own header and payload to the GPU decoder."""
     torch = torch_mod()
