@@ -1605,7 +1605,13 @@ UPlan make_uplan(const accept_desc& d) {
     const int64_t ty = kBlock / tx;
     const int64_t gx = (ncv + tx - 1) / tx;
     int64_t gy = (d.n + ty - 1) / ty;                      // at most one row per thread row
-    const int64_t want = gx >= 2048 ? 1 : 2048 / gx;       // about 2048 workgroups in all
+    // About 512 workgroups in all.  Each leaves one maximum per column and stage 2 reads them a
+    // column at a time, so more row blocks cost it a cache line per maximum and keep stage 1 in
+    // short columns.  Stages 1 + 2 with 2048 -> 512 workgroups, bfloat16: channels-last
+    // 25088 x 1024 14.5 + 15.9 -> 12.4 + 5.5 us, 4096 x 4096 11.8 + 22.3 -> 9.7 + 7.6; segments
+    // of 49, 64 x 2048 x 49, 9.4 + 6.5 -> 6.6 + 4.1.  Whole call, float32, 200704 x 256: 82.9 ->
+    // 73.9 (1024: 79.0, 768: 74.7, 256: 74.4); 256 loses at 401408 x 64 bfloat16 (30.1 against 26.8).
+    const int64_t want = gx >= 512 ? 1 : 512 / gx;
     if (gy > want) gy = want;
     const int64_t cap = (int64_t(16) << 20) / d.m;         // at most 64 MiB of column maxima
     if (gy > cap) gy = cap;
