@@ -423,6 +423,45 @@ __global__ __launch_bounds__(kBlock) void range_columns_finalize_kernel(const fl
   }
 }
 
+// Stage 2 for channels of one column each (channels-last): a workgroup of 1024 threads folds 16
+// adjacent channels, 64 row blocks at a time, so that a cache line of maxima is read by one
+// workgroup and all 512 row blocks are eight loads per thread in flight together.  Latency bound:
+// against the kernel above, 1024 channels 5.4 -> 3.9 us, 4096 channels 7.5 -> 3.7 us, 300000
+// channels (8 row blocks) 172 -> 40 us; 256 channels 4.8 and 4.8, 64 and 80 channels 2.8 and
+// 2.6, 3.3 and 3.9 us (few workgroups), so the narrow ones stay with the kernel above.
+constexpr int kLastChannels = 16;
+constexpr int64_t kLastMinChannels = 512;
+__global__ __launch_bounds__(1024) void range_last_finalize_kernel(const float* __restrict__ colmax, int64_t m, int nby,
+                                                                   int k, float* __restrict__ header,
+                                                                   float* __restrict__ rtab) {
+  __shared__ float red[1024 / kWave][kLastChannels];
+  const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
+  const int64_t ch = int64_t(blockIdx.x) * kLastChannels + threadIdx.x % kLastChannels;
+  constexpr int kRows = 1024 / kLastChannels;
+  float c = 0.0f;
+  if (ch < m) {
+    for (int by = threadIdx.x / kLastChannels; by < nby; by += 8 * kRows) {
+      float v[8];
+#pragma unroll
+      for (int u = 0; u < 8; ++u) v[u] = by + u * kRows < nby ? colmax[int64_t(by + u * kRows) * m + ch] : 0.0f;
+#pragma unroll
+      for (int u = 0; u < 8; ++u) c = fmaxf(c, v[u]);
+    }
+  }
+#pragma unroll
+  for (int step = kLastChannels; step < kWave; step *= 2) c = fmaxf(c, __shfl_xor(c, step));
+  if (lane < kLastChannels) red[wave][lane] = c;
+  __syncthreads();
+  if (threadIdx.x < kLastChannels && ch < m) {
+#pragma unroll
+    for (int w = 1; w < 1024 / kWave; ++w) c = fmaxf(c, red[w][threadIdx.x]);
+    float s, r;
+    scale_from_range(c, k, s, r);
+    header[ch] = s;
+    rtab[ch] = r;
+  }
+}
+
 // U1b per channel: reduce the channel's `per` partial maxima (they lie together, channel after
 // channel), write s to the header and the reciprocal r to the workspace table.  One wavefront
 // per channel.
@@ -1413,8 +1452,12 @@ hipError_t compress_typed(const accept_desc& d, UPlan p, const T* x, float* head
   mark(tm, s);
   const bool plain = d.layout != ACCEPT_LAYOUT_PACKED;
   if (p.mode == U_GENERIC) {
-    hipLaunchKernelGGL(range_columns_finalize_kernel, dim3(unsigned(p.C)), dim3(kBlock), 0, s, partials, p.m, p.seg_len,
-                       p.col_grid_y, d.bits, header, rtab);
+    if (p.seg_len == 1 && p.C >= kLastMinChannels)
+      hipLaunchKernelGGL(range_last_finalize_kernel, dim3(unsigned((p.C + kLastChannels - 1) / kLastChannels)),
+                         dim3(1024), 0, s, partials, p.m, p.col_grid_y, d.bits, header, rtab);
+    else
+      hipLaunchKernelGGL(range_columns_finalize_kernel, dim3(unsigned(p.C)), dim3(kBlock), 0, s, partials, p.m,
+                         p.seg_len, p.col_grid_y, d.bits, header, rtab);
     e = hipGetLastError();
     if (e != hipSuccess) return e;
     mark(tm, s);
@@ -1607,10 +1650,11 @@ UPlan make_uplan(const accept_desc& d) {
     int64_t gy = (d.n + ty - 1) / ty;                      // at most one row per thread row
     // About 512 workgroups in all.  Each leaves one maximum per column and stage 2 reads them a
     // column at a time, so more row blocks cost it a cache line per maximum and keep stage 1 in
-    // short columns.  Stages 1 + 2 with 2048 -> 512 workgroups, bfloat16: channels-last
-    // 25088 x 1024 14.5 + 15.9 -> 12.4 + 5.5 us, 4096 x 4096 11.8 + 22.3 -> 9.7 + 7.6; segments
-    // of 49, 64 x 2048 x 49, 9.4 + 6.5 -> 6.6 + 4.1.  Whole call, float32, 200704 x 256: 82.9 ->
-    // 73.9 (1024: 79.0, 768: 74.7, 256: 74.4); 256 loses at 401408 x 64 bfloat16 (30.1 against 26.8).
+    // short columns.  Stages 1 + 2 (one workgroup per channel in stage 2) with 2048 -> 512
+    // workgroups, bfloat16: channels-last 25088 x 1024 14.5 + 15.9 -> 12.4 + 5.5 us, 4096 x 4096
+    // 11.8 + 22.3 -> 9.7 + 7.6; segments of 49, 64 x 2048 x 49, 9.4 + 6.5 -> 6.6 + 4.1.  Whole
+    // call, float32, 200704 x 256: 82.9 -> 73.9 (1024: 79.0, 768: 74.7, 256: 74.4); 256 loses at
+    // 401408 x 64 bfloat16 (30.1 against 26.8).
     const int64_t want = gx >= 512 ? 1 : 512 / gx;
     if (gy > want) gy = want;
     const int64_t cap = (int64_t(16) << 20) / d.m;         // at most 64 MiB of column maxima

@@ -278,6 +278,17 @@ def test_segment_lengths_of_the_range_pass(A, seg):
         run_case(A, x, k, n, C * seg, channels=C, in_bf16=bf16, out_bf16=bf16, tag="segments")
 
 
+@pytest.mark.parametrize("n,C", [(1, 512), (65, 511), (65, 513), (520, 1000), (4099, 528), (3, 4097), (200, 300001)])
+def test_channels_last_range(A, n, C):
+    """Wide channels-last tensors: the fold of 16 channels per workgroup, ragged channel counts,
+    one and many row blocks, and the largest value in the last row and channel."""
+    x = per_channel_input(n, C, 1, 450 + n)
+    x[n - 1, C - 1, 0] = 100.0
+    x[0, 0, 0] = -90.0
+    for k, bf16 in ((4, False), (7, True)):
+        run_case(A, x, k, n, C, channels=C, in_bf16=bf16, out_bf16=bf16, tag="channels-last")
+
+
 # One range, nearest rounding, 48 to 256 MiB: the end of the tensor is kept on the chip between the
 # range and the quantizer.  256 workgroups, units of 16384 elements; per workgroup 7 (bfloat16: 12)
 # units in registers, 2 (4) in local memory, the rest read twice.
