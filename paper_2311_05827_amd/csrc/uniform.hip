@@ -1647,7 +1647,17 @@ UPlan make_uplan(const accept_desc& d) {
     p.col_tx = tx;
     const int64_t ty = kBlock / tx;
     const int64_t gx = (ncv + tx - 1) / tx;
-    int64_t gy = (d.n + ty - 1) / ty;                      // at most one row per thread row
+    int64_t gy = (d.n + ty - 1) / ty;  // at most one row per thread row
+    // The space is that of 2048 workgroups: accept_workspace_size, and with it which descriptors
+    // accept_compress_noalloc takes, do not depend on how the pass is split.
+    int64_t rows = gy;
+    const int64_t most = gx >= 2048 ? 1 : 2048 / gx;
+    if (rows > most) rows = most;
+    const int64_t cap = (int64_t(16) << 20) / d.m;         // at most 64 MiB of column maxima
+    if (rows > cap) rows = cap;
+    if (rows < 1) rows = 1;
+    if (rows > 65535) rows = 65535;
+    partial_bytes = size_t(rows) * size_t(d.m) * sizeof(float);
     // About 512 workgroups in all.  Each leaves one maximum per column and stage 2 reads them a
     // column at a time, so more row blocks cost it a cache line per maximum and keep stage 1 in
     // short columns.  Stages 1 + 2 (one workgroup per channel in stage 2) with 2048 -> 512
@@ -1656,14 +1666,9 @@ UPlan make_uplan(const accept_desc& d) {
     // call, float32, 200704 x 256: 82.9 -> 73.9 (1024: 79.0, 768: 74.7, 256: 74.4); 256 loses at
     // 401408 x 64 bfloat16 (30.1 against 26.8).
     const int64_t want = gx >= 512 ? 1 : 512 / gx;
-    if (gy > want) gy = want;
-    const int64_t cap = (int64_t(16) << 20) / d.m;         // at most 64 MiB of column maxima
-    if (gy > cap) gy = cap;
-    if (gy < 1) gy = 1;
-    if (gy > 65535) gy = 65535;
+    gy = rows > want ? want : rows;
     p.col_grid_x = gx;
     p.col_grid_y = int(gy);
-    partial_bytes = size_t(gy) * size_t(d.m) * sizeof(float);
   }
   p.off_rtab = kCtrlBytes + (partial_bytes + 255) / 256 * 256;
   p.bytes = p.off_rtab + (size_t(p.C) * sizeof(float) + 255) / 256 * 256;

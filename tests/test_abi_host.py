@@ -129,3 +129,12 @@ def test_invalid_arguments_are_rejected_before_any_launch(A):
     plain = A.make_desc(0, 4, 4, 4, layout=A.LAYOUT_BATCH)
     assert [A.accept_stage_name(plain, 0, i) for i in range(4)] == ["range", "range_finalize", "quantize_plain", None]
     assert A.accept_stage_name(plain, 1, 0) == "dequant_plain"
+
+
+@pytest.mark.parametrize("n,C,hw,rows", [(200704, 256, 1, 2048), (25088, 1024, 1, 2048), (64, 2048, 49, 41), (3, 5, 7, 1)])
+def test_column_pass_workspace(A, n, C, hw, rows):
+    """The size does not follow the split of the column pass: what accept_compress_noalloc refuses
+    (more than 1 MiB) it goes on refusing."""
+    d = A.make_desc(A.UNIFORM, 4, n, C * hw, channels=C, in_dtype=A.BF16)
+    up = lambda b: (b + 255) // 256 * 256
+    assert A.accept_workspace_size(d) == 16384 + up(rows * C * hw * 4) + up(C * 4)
