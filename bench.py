@@ -50,7 +50,7 @@ def alg_bytes(kernel, N, n, m, k, b_in=4, b_out=4):
     """Algorithmic HBM bytes one launch of a kernel must move."""
     if kernel == "range":
         return N * b_in
-    if kernel == "quantize_pack":
+    if kernel in ("quantize_pack", "quantize_held"):  # held: range and codes from one kernel, priced as one read
         return N * b_in + (N * k + 7) // 8 + 4
     if kernel == "unpack_dequant":
         return (N * k + 7) // 8 + 4 + N * b_out
@@ -299,15 +299,15 @@ def main():
         for nm_, ms in A.accept_decompress_timed(du, b.uh, b.up, b.xhat_u):
             stage_ms.setdefault(nm_, []).append(ms)
     kernels = {}
-    kbits = {"range": K_BWD, "quantize_pack": K_BWD, "unpack_dequant": K_BWD, "mbq_encode": K_FWD,
+    kbits = {"range": K_BWD, "quantize_pack": K_BWD, "quantize_held": K_BWD, "unpack_dequant": K_BWD, "mbq_encode": K_FWD,
              "mbq_decode": K_FWD}
     for nm_, v in stage_ms.items():
         avg = sum(v) / len(v)
         ab = alg_bytes(nm_, N, n, m, kbits.get(nm_, 0))
         kernels[nm_] = {"avg_ms": round(avg, 5), "alg_bytes": ab,
                         "GBps": round(ab / (avg * 1e-3) / 1e9, 1) if ab else None}
-    # the longest kernel of the path in the rocprofv3 trace of this command (profiles/): the MBQ encoder
-    dominant = "mbq_encode"
+    # the longest kernel of the path, as in the rocprofv3 trace of this command (profiles/)
+    dominant = max((k for k in kernels if kernels[k]["alg_bytes"]), key=lambda k: kernels[k]["avg_ms"])
     traffic = read_traffic().get(dominant)
     roofline = {
         "bound": "hbm",

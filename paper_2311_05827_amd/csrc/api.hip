@@ -259,6 +259,10 @@ const char* accept_stage_name(const accept_desc* desc, int is_decompress, int i)
     static const char* const names[] = {"range", "range_finalize", "quantize_pack"};
     return i < 3 ? names[i] : nullptr;
   }
+  if (make_uplan(*desc).held) {  // range and quantizer in one kernel, the second finishes what that one left
+    static const char* const names[] = {"quantize_held", "quantize_rest"};
+    return i < 2 ? names[i] : nullptr;
+  }
   static const char* const names[] = {"range", "quantize_pack"};
   return i < 2 ? names[i] : nullptr;
 }

@@ -125,6 +125,8 @@ def test_invalid_arguments_are_rejected_before_any_launch(A):
     assert lib.accept_compress(ctypes.byref(mbq), V(0x1000), None, V(0x2000), V(0x3000), V(0x4000), None) == INVALID
     assert lib.accept_mbq_init(ctypes.byref(good), V(0x1000), V(0x2000), V(0x4000), None) == INVALID
     assert A.accept_stage_name(good, 0, 0) == "range" and A.accept_stage_name(good, 0, 1) == "quantize_pack"
+    held = A.make_desc(A.UNIFORM, 8, 64, 802816)
+    assert [A.accept_stage_name(held, 0, i) for i in range(3)] == ["quantize_held", "quantize_rest", None]
     assert A.accept_stage_name(good, 0, 2) is None and A.accept_stage_name(mbq, 1, 0) == "mbq_decode"
     plain = A.make_desc(0, 4, 4, 4, layout=A.LAYOUT_BATCH)
     assert [A.accept_stage_name(plain, 0, i) for i in range(4)] == ["range", "range_finalize", "quantize_plain", None]
