@@ -310,17 +310,6 @@ __device__ __forceinline__ uint64_t wave_sum(uint32_t v) {
   return (r0 + r1) + (r2 + r3);
 }
 
-// Loads and stores that are coherent across the whole device although every group of compute
-// units has a second-level cache of its own: they go through to memory instead of staying in
-// (or being served from) that cache.  For the few words workgroups hand to each other inside
-// one kernel.
-__device__ __forceinline__ void store_device_scope(double* p, double v) {
-  __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-__device__ __forceinline__ double load_device_scope(const double* p) {
-  return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-
 // Counter-based uniform numbers: element idx gets u = (top 24 bits of h) * 2^-24, h = splitmix64's
 // output function at the state z = seed + (idx+1) * kRandStep.  States of neighbouring elements
 // differ by a constant, so a kernel forms one state per thread and adds from there.
