@@ -812,10 +812,11 @@ __global__ __launch_bounds__(kBlock) void quantize_pack_kernel(
 // nearest).  The range has to be known before the first element can be quantized, so the plain way
 // reads the tensor twice, and the memory-side cache does not help: it delivers 7.4 TB/s, memory
 // itself 7.2.  The registers and local memories of the chip hold 168 MiB, though.  Here one workgroup per compute unit
-// reads units (16384 elements) b, b + 256, ..., keeps the last of them (151 MB over the chip, two
-// thirds in registers, one in local memory), hands its maximum to the other workgroups through a mailbox, waits for
-// theirs, quantizes what it kept and reads the units before held_first once more.
-// quantize_pack_kernel does the elements behind the last whole unit.
+// reads units (16384 elements) b, b + 256, ..., keeps the last of them (float32: 7 units in registers
+// and 2 in local memory, 151 MB over the chip; bfloat16: 12 and 4, 134 MB), hands its maximum to the
+// other workgroups through a mailbox, waits for theirs, quantizes what it kept and reads the units
+// before held_first once more.  quantize_pack_kernel does the up to 16383 elements behind the last
+// whole unit; for the range every workgroup looks at 64 of them here.
 //
 // The wait is bounded: nothing says that all 256 workgroups run at the same time (another kernel may
 // hold some compute units).  A workgroup that has not seen all mailboxes after `polls` looks gives
@@ -835,8 +836,9 @@ template <typename T, int K>
 __global__ __launch_bounds__(kHeldBlock, 2) void quantize_held_kernel(const T* __restrict__ x,
                                                                       uint32_t* __restrict__ payload32,
                                                                       float2* __restrict__ records,
-                                                                      uint64_t* __restrict__ mail, int64_t units,
-                                                                      int64_t held_first, int lds_units, int polls) {
+                                                                      uint64_t* __restrict__ mail, int64_t N,
+                                                                      int64_t units, int64_t held_first, int lds_units,
+                                                                      int polls) {
   constexpr int VEC = Elem<T>::VEC;
   constexpr int LOADS = kUnitElems / (kHeldBlock * VEC);  // vectors per thread and unit
   constexpr int SLOTS = kHeldUnits<T>;
@@ -870,6 +872,11 @@ __global__ __launch_bounds__(kHeldBlock, 2) void quantize_held_kernel(const T* _
 #pragma unroll
     for (int u = 0; u < LOADS; ++u) raw[u] = load16_stream(xu + (u * kHeldBlock + tid) * VEC);
   };
+  // Elements behind the last whole unit: workgroup b has the 64 from units * 16384 + 64 b on, its
+  // wavefronts all the same ones; where there are none, the tensor's last element stands in for them.
+  static_assert(kUnitElems == kHeldGrid * kWave, "one element per workgroup and lane covers what is behind the last unit");
+  const int64_t behind = units * kUnitElems + int64_t(blockIdx.x) * kWave + lane;
+  const float tail = load_one(x + (behind < N ? behind : N - 1));
   float c = 0.0f;
   auto look = [&](const uint4 (&raw)[LOADS]) {
 #pragma unroll
@@ -892,6 +899,7 @@ __global__ __launch_bounds__(kHeldBlock, 2) void quantize_held_kernel(const T* _
     if (j < extra) ask(j, kept[RING + j]);
 #pragma unroll
   for (int j = 0; j < RING; ++j) ask(extra + j < count ? extra + j : count - 1, kept[j]);
+  c = fabsf(tail);
 #pragma unroll
   for (int j = 0; j < RING - 1; ++j)
     if (j < extra) look(kept[RING + j]);
@@ -1406,7 +1414,7 @@ hipError_t launch_held(const accept_desc& d, const UPlan& p, const T* x, uint32_
 #define ACCEPT_HELD(KK)                                                                                          \
   case KK:                                                                                                       \
     hipLaunchKernelGGL((quantize_held_kernel<T, KK>), dim3(kHeldGrid), dim3(kHeldBlock), 0, s, x, payload, records, \
-                       mail, p.held_units, p.held_first, p.held_lds, polls);                                     \
+                       mail, p.N, p.held_units, p.held_first, p.held_lds, polls);                                    \
     break;
   switch (d.bits) {
     ACCEPT_HELD(2) ACCEPT_HELD(3) ACCEPT_HELD(4) ACCEPT_HELD(5) ACCEPT_HELD(6) ACCEPT_HELD(7) ACCEPT_HELD(8)

@@ -310,6 +310,29 @@ def test_held_pass(A, k, N, bf16):
     run_case(A, x, k, 1, N, in_bf16=bf16, out_bf16=bf16, tag="held")
 
 
+@pytest.mark.parametrize("bf16", [False, True])
+@pytest.mark.parametrize("tail", [0, 1, 63, 64, 65, 8191, 8192, 8193, 16383])
+def test_held_pass_largest_value_at_the_end(A, tail, bf16):
+    """The largest value in the last element, in the first one behind the last whole unit and in the
+    last whole unit, whether the workgroups see each other's maxima or give up."""
+    torch = torch_mod()
+    k, N = 8, (6 if bf16 else 3) * HELD_ROUND + 16384 * 3 + tail
+    print("held, tail", tail, "bf16", bf16, flush=True)
+    base = si.make_shape("grad", (1, N), 230 + tail % 7)
+    d = A.make_desc(A.UNIFORM, k, 1, N, in_dtype=A.BF16 if bf16 else A.F32)
+    header, payload, ws = A.alloc_outputs(d, "cuda")
+    for at in sorted({N - 1, N - max(tail, 1), N - tail - 1, N - tail - 16384}):
+        x = base.copy()
+        x[0, at] = -0.5
+        xd, bits = to_dev(x, bf16)
+        oh, op = orc.uniform_compress(bits if bf16 else x, k, 1, N, 0, bf16)
+        for polls in (64, 0):
+            A.accept_compress_polls(d, xd, header, payload, ws, polls)
+            torch.cuda.synchronize()
+            assert dev_bytes(header) == oh, (N - at, polls)
+            assert first_mismatch(dev_bytes(payload), op.tobytes()) is None, (N - at, polls)
+
+
 def test_held_pass_that_gives_up(A):
     """A workgroup that does not see the others' maxima in time leaves its part to the second
     kernel; whatever share of them does (0, some, none), the bytes are the same, and the
