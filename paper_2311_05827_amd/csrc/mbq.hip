@@ -1382,7 +1382,9 @@ __global__ __launch_bounds__(kBlock) void mbq_decode_kernel(const uint8_t* __res
 // the last pass, 1024 to 2048 instead of 768, cost 1 to 3 us; fewer or more for the others as well.)
 //
 // Signs are taken from the sign bit (x + 0 has none for a zero, and no difference of two equal
-// numbers has), so a step is a bit select and an add.
+// numbers has), so a step is a bit select and an add.  Where a residue is not a number all later ones
+// and their mean are not, whatever sign is taken; only its plane bits need a compare
+// (mbq_init_encode_kernel).
 
 // Where pass j leaves its records (one double per workgroup and statistic, statistic-major).
 constexpr int kInitPasses = 8;
@@ -1499,8 +1501,12 @@ __global__ __launch_bounds__(kBlock) void mbq_init_encode_kernel(const T* __rest
       if (row0 + r < n) fr[r] = load_raw<T, VEC>(xc + r * m);
   };
   if (it < items) ask();  // under way while alpha is formed
-  double a[K > 1 ? K - 1 : 1];
+  double a[K > 1 ? K - 1 : 1] = {};
   alphas_of_passes<K - 1>(alpha_out, prev, nprev, n_elems, red, a);
+  // alpha_0 = mean|x| is finite exactly if every x is, and then every residue is.  Otherwise signs are
+  // compared for: b_j = +1 where rho_j >= 0, which is false for what is not a number, whatever its sign
+  // bit.  (One coefficient: nothing is known of x, and the pass is bound by its read of x either way.)
+  const bool all_finite = __builtin_amdgcn_readfirstlane(fabs(a[0]) < double(__builtin_inff()) ? 1 : 0) != 0;
   double sum_abs = 0.0, sum_x = 0.0;
   uint32_t cnt[K];
 #pragma unroll
@@ -1514,24 +1520,29 @@ __global__ __launch_bounds__(kBlock) void mbq_init_encode_kernel(const T* __rest
 #pragma unroll
       for (int q = 0; q < K; ++q) neg[c][q] = 0;
     float sx32 = 0.0f;
+    auto rows = [&](auto finite) {
 #pragma unroll
-    for (int r = 0; r < 8; ++r) {
-      if (r < nrows) {
-        float row[VEC];
-        widen_raw<VEC>(fr[r], row);
+      for (int r = 0; r < 8; ++r) {
+        if (r < nrows) {
+          float row[VEC];
+          widen_raw<VEC>(fr[r], row);
 #pragma unroll
-        for (int c = 0; c < VEC; ++c) {
-          sx32 = __fadd_rn(sx32, row[c]);
-          double rho = double(row[c] + 0.0f);
+          for (int c = 0; c < VEC; ++c) {
+            sx32 = __fadd_rn(sx32, row[c]);
+            double rho = double(row[c] + 0.0f);
 #pragma unroll
-          for (int q = 0; q < K; ++q) {
-            neg[c][q] = __builtin_amdgcn_alignbit(neg[c][q], uint32_t(uint64_t(__double_as_longlong(rho)) >> 32), 31);
-            if (q < K - 1) rho = residue_step(rho, a[q]);
+            for (int q = 0; q < K; ++q) {
+              const uint32_t sign = decltype(finite)::value ? uint32_t(uint64_t(__double_as_longlong(rho)) >> 32)
+                                                            : (rho >= 0.0 ? 0u : 0x80000000u);
+              neg[c][q] = __builtin_amdgcn_alignbit(neg[c][q], sign, 31);
+              if (q < K - 1) rho = residue_step(rho, a[q]);
+            }
+            sum_abs += fabs(rho);
           }
-          sum_abs += fabs(rho);
         }
       }
-    }
+    };
+    if (K > 1 && all_finite) rows(std::true_type{}); else rows(std::false_type{});
     // row r at bit 7-r; a missing row contributes 0 bits
     uint32_t acc[VEC][NW];
 #pragma unroll

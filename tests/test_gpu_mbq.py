@@ -197,6 +197,29 @@ def test_batch0_compress(A, k):
         assert a0.cpu().numpy().tobytes() == gh[:k].tobytes()
 
 
+@pytest.mark.parametrize("bf16", [False, True])
+@pytest.mark.parametrize("k", [1, 2, 4, 5])
+@pytest.mark.parametrize("bad", ["nan", "negative nan", "inf", "-inf"])
+def test_batch0_planes_with_values_that_are_not_finite(A, k, bf16, bad):
+    """b_j = +1 where rho_j >= 0, which a residue that is not a number is not, whatever its sign bit."""
+    torch = torch_mod()
+    for n, m in ((16, 1000), (7, 333)):
+        x = si.make_shape("student_t3", (n, m), 7700 + k)
+        x.reshape(-1)[::53] = {"nan": np.nan, "negative nan": -np.nan, "inf": np.inf, "-inf": -np.inf}[bad]
+        x.reshape(-1)[::61] = 0.0
+        xd = torch.from_numpy(x.reshape(-1)).cuda()
+        xd = xd.to(torch.bfloat16) if bf16 else xd
+        d = A.make_desc(A.MBQ, k, n, m, in_dtype=A.BF16 if bf16 else A.F32)
+        header, payload = A.accept_mbq_compress_first(d, xd)
+        torch.cuda.synchronize()
+        with np.errstate(invalid="ignore"):
+            oh, op = orc.mbq_compress_first(xd.float().cpu().numpy(), k, n, m)
+        gh, ohf = np.frombuffer(dev_bytes(header), dtype="<f4"), np.frombuffer(oh, dtype="<f4")
+        assert np.array_equal(np.isnan(gh), np.isnan(ohf)) and np.array_equal(np.isinf(gh), np.isinf(ohf)), (gh, ohf)
+        mm = first_mismatch(dev_bytes(payload), op.tobytes())
+        assert mm is None, "B^0 planes differ: " + mm
+
+
 @pytest.mark.parametrize("k", [1, 2, 3, 4])
 def test_bf16_every_value(A, k):
     """bfloat16 and k <= 4 go through a table of all 65536 values: every finite one, with
