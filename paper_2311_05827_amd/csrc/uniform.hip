@@ -8,6 +8,8 @@
 // compressor is one LDS round trip of already-quantized 4-code "pieces" (4k bits each):
 // 8 pieces = 32 codes = exactly k dwords for every k, so one lane can emit whole dwords and
 // no global atomics are needed even when codes straddle dword boundaries.
+#include <atomic>
+
 #include "common.hpp"
 
 namespace accept {
@@ -823,9 +825,10 @@ __global__ __launch_bounds__(kBlock) void quantize_pack_kernel(
 // up, says so in its record and ends; quantize_pack_kernel then takes the held units too.  So every
 // workgroup ends whatever else runs, and the result does not depend on it.
 //
-// A mailbox is one 64-bit word, value and a "full" mark together, written and read with device-scope
+// A mailbox is one 64-bit word, value and the call's mark together, written and read with device-scope
 // accesses (they bypass the dies' second-level caches): no ordering between two words is needed.
-// quantize_pack_kernel empties the mailboxes.
+// quantize_pack_kernel empties the mailboxes, so that a captured call finds none of its own mark when it
+// is replayed; what a call left whose second kernel could not be launched bears another mark.
 //
 // 51.4 M float32 values (205 MB), k = 8: 59.4 us a call against 69.5 with two reads (range 32.8,
 // quantize 38.0); here 32.7 us to the mailboxes, 15 us of quantizing, 4 us of kernel end, 4.5 us for
@@ -838,7 +841,7 @@ __global__ __launch_bounds__(kHeldBlock, 2) void quantize_held_kernel(const T* _
                                                                       float2* __restrict__ records,
                                                                       uint64_t* __restrict__ mail, int64_t N,
                                                                       int64_t units, int64_t held_first, int lds_units,
-                                                                      int polls) {
+                                                                      int polls, uint32_t mark) {
   constexpr int VEC = Elem<T>::VEC;
   constexpr int LOADS = kUnitElems / (kHeldBlock * VEC);  // vectors per thread and unit
   constexpr int SLOTS = kHeldUnits<T>;
@@ -942,14 +945,14 @@ __global__ __launch_bounds__(kHeldBlock, 2) void quantize_held_kernel(const T* _
   for (int w = 1; w < WAVES; ++w) c = fmaxf(c, red[w]);
   const float mine = c;
   if (tid == 0)
-    __hip_atomic_store(mail + blockIdx.x, (uint64_t(1) << 32) | f32_as_u32(mine), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __hip_atomic_store(mail + blockIdx.x, (uint64_t(mark) << 32) | f32_as_u32(mine), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   __syncthreads();  // red is free again
   if (tid < kHeldGrid) {  // wavefront w watches mailboxes 64w .. 64w+63
     uint64_t v = 0;
     bool all = false;
     for (int i = 0; i < polls; ++i) {
       v = __hip_atomic_load(mail + tid, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      all = __ballot((v >> 32) == 0) == 0;
+      all = __ballot(uint32_t(v >> 32) != mark) == 0;
       if (all) break;
       __builtin_amdgcn_s_sleep(4);
     }
@@ -1407,14 +1410,23 @@ int compute_units() {
   return cus;
 }
 
+// Mark of a call's mailboxes: a running number, never 0 (an empty mailbox).
+uint32_t next_mark() {
+  static std::atomic<uint32_t> calls{0};
+  uint32_t mark = 0;
+  while (mark == 0) mark = calls.fetch_add(1, std::memory_order_relaxed) + 1;
+  return mark;
+}
+
 template <typename T>
 hipError_t launch_held(const accept_desc& d, const UPlan& p, const T* x, uint32_t* payload, float* partials,
                        uint64_t* mail, int polls, hipStream_t s) {
   float2* records = reinterpret_cast<float2*>(partials);
+  const uint32_t mark = next_mark();
 #define ACCEPT_HELD(KK)                                                                                          \
   case KK:                                                                                                       \
     hipLaunchKernelGGL((quantize_held_kernel<T, KK>), dim3(kHeldGrid), dim3(kHeldBlock), 0, s, x, payload, records, \
-                       mail, p.N, p.held_units, p.held_first, p.held_lds, polls);                                    \
+                       mail, p.N, p.held_units, p.held_first, p.held_lds, polls, mark);                              \
     break;
   switch (d.bits) {
     ACCEPT_HELD(2) ACCEPT_HELD(3) ACCEPT_HELD(4) ACCEPT_HELD(5) ACCEPT_HELD(6) ACCEPT_HELD(7) ACCEPT_HELD(8)

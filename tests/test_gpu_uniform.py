@@ -352,6 +352,25 @@ def test_held_pass_that_gives_up(A):
             assert first_mismatch(dev_bytes(payload), op.tobytes()) is None, polls
 
 
+def test_held_pass_after_a_call_that_failed(A):
+    """A call whose second launch failed leaves its maxima in the workspace's mailboxes (64-bit words
+    from byte 8192 on, value and mark).  The next call takes none of them for its own."""
+    torch = torch_mod()
+    k, N = 8, 3 * HELD_ROUND
+    x = torch.from_numpy(si.make_shape("grad", (N,), 227)).cuda()
+    oh, op = orc.uniform_compress(x.cpu().numpy(), k, 1, N)
+    d = A.make_desc(A.UNIFORM, k, 1, N)
+    header, payload, ws = A.alloc_outputs(d, "cuda")
+    left = (0x7FFF0000 << 32) | int(np.float32(7.0).view(np.uint32))
+    for boxes in (slice(0, 256), slice(3, 4)):
+        ws[8192:8192 + 2048].view(torch.int64)[boxes] = left
+        for call in range(2):
+            A.accept_compress(d, x, header=header, payload=payload, workspace=ws)
+            torch.cuda.synchronize()
+            assert dev_bytes(header) == oh, (boxes, call)
+            assert first_mismatch(dev_bytes(payload), op.tobytes()) is None, (boxes, call)
+
+
 def test_held_pass_on_two_streams_and_in_a_graph(A):
     """Calls that overlap on two streams (each with its own buffers) compete for the compute units
     the held pass waits on; a captured call is replayed on new inputs between eager ones."""
