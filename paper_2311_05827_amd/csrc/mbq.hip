@@ -34,7 +34,7 @@ constexpr int kInitGrid = 1024;
 constexpr int kMaxRecords = 2048;  // per-workgroup records the workspace has room for
 constexpr int kMaxWaves = 16;      // wavefronts of the largest workgroup
 constexpr int kMaxGroups = kEncodeGridMax / kGroupBlocks;
-static_assert(size_t(kMaxGroups) * kCounterStride * sizeof(uint32_t) <= kCtrlBytes, "the control block holds the counters");
+static_assert(size_t(kMaxGroups) * kCounterStride * sizeof(uint32_t) <= kMailOffset, "the first half of the control block holds the counters");
 static_assert(kEncodeGridMax <= kMaxRecords && kPlainGridMax <= kMaxRecords && kInitGrid <= kMaxRecords, "records");
 
 template <int NDW>
