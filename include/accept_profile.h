@@ -40,7 +40,8 @@ accept_status accept_compress_polls(const accept_desc* desc, const void* x_dev, 
                                     int polls);
 
 /* Name of stage i of the call accept_*_timed would make for this descriptor
- * (is_decompress = 0/1); null when i is out of range.  Host-only. */
+ * (is_decompress = 0/1) on the current device, or, where there is none, on a whole chip of 256
+ * compute units; null when i is out of range.  Host-only. */
 const char* accept_stage_name(const accept_desc* desc, int is_decompress, int i);
 
 #ifdef __cplusplus

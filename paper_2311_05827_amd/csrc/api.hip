@@ -259,7 +259,10 @@ const char* accept_stage_name(const accept_desc* desc, int is_decompress, int i)
     static const char* const names[] = {"range", "range_finalize", "quantize_pack"};
     return i < 3 ? names[i] : nullptr;
   }
-  if (make_uplan(*desc).held) {  // range and quantizer in one kernel, the second finishes what that one left
+  // Range and quantizer in one kernel, the second finishes what that one left; on the current device
+  // (where there is none, on a whole one).
+  const int units = compute_units();
+  if (held_runs(make_uplan(*desc), units != 0 ? units : kHeldGrid)) {
     static const char* const names[] = {"quantize_held", "quantize_rest"};
     return i < 2 ? names[i] : nullptr;
   }

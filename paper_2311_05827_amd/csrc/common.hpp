@@ -80,6 +80,11 @@ struct UPlan {
 };
 
 UPlan make_uplan(const accept_desc& d);
+// Compute units of the current device (0 if there is none), and whether the held pass of a plan that
+// has one runs on a device of that many: its 256 workgroups wait for each other, one per compute unit.
+int compute_units();
+constexpr int kHeldGrid = 256;
+inline bool held_runs(const UPlan& p, int units) { return p.held && units >= kHeldGrid; }
 
 // held_polls: how often a workgroup of the held pass looks for the others' maxima before it gives up
 // (kHeldPolls; fewer only where a test wants the case that it gives up).

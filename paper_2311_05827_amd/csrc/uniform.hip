@@ -35,7 +35,6 @@ constexpr int kRangeGridMax = 512;     // partial maxima of the per-tensor range
 constexpr int kQuantGridMax = 2048;    // workgroups of the quantize+pack kernel
 constexpr int kDequantGridMax = 8192;
 // The held pass (quantize_held_kernel): one workgroup per compute unit, two wavefronts per SIMD.
-constexpr int kHeldGrid = 256;
 constexpr int kHeldBlock = 512;
 constexpr int kUnitElems = 2 * kTileElems;  // elements a workgroup takes at a time
 template <typename T>
@@ -1402,14 +1401,6 @@ hipError_t launch_quant_k(const accept_desc& d, const UPlan& p, const T* x, floa
                : launch_quant<T, K, kRangePerVector, false>(d, p, x, header, payload, partials, rtab, mail, s);
 }
 
-// Compute units of the current device (0 if the question fails).
-int compute_units() {
-  int dev = -1, cus = 0;
-  if (hipGetDevice(&dev) != hipSuccess) return 0;
-  if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) return 0;
-  return cus;
-}
-
 // Mark of a call's mailboxes: a running number, never 0 (an empty mailbox).
 uint32_t next_mark() {
   static std::atomic<uint32_t> calls{0};
@@ -1440,7 +1431,7 @@ template <typename T>
 hipError_t compress_typed(const accept_desc& d, UPlan p, const T* x, float* header, uint32_t* payload,
                           void* ws, hipStream_t s, StageTimer* tm, int held_polls) {
   uint64_t* mail = reinterpret_cast<uint64_t*>(reinterpret_cast<char*>(ws) + kMailOffset);
-  if (p.held && compute_units() < kHeldGrid) p.held = false;  // its workgroups could never run together
+  if (p.held) p.held = held_runs(p, compute_units());
   float* partials = reinterpret_cast<float*>(reinterpret_cast<char*>(ws) + kCtrlBytes);
   float* rtab = reinterpret_cast<float*>(reinterpret_cast<char*>(ws) + p.off_rtab);
   mark(tm, s);
@@ -1609,6 +1600,13 @@ hipError_t decompress_typed(const accept_desc& d, const float* header, const uin
 }
 
 }  // namespace
+
+int compute_units() {
+  int dev = -1, units = 0;
+  if (hipGetDevice(&dev) != hipSuccess) return 0;
+  if (hipDeviceGetAttribute(&units, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) return 0;
+  return units;
+}
 
 UPlan make_uplan(const accept_desc& d) {
   UPlan p{};
