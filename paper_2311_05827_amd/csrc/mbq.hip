@@ -1003,7 +1003,10 @@ __device__ __forceinline__ void store_record(const EncodeStats<K>& st, const Mbq
 // lie together), lane l the records l, l + 64, ..., one wavefront sum per statistic; one thread
 // solves and writes the header.  (With four wavefronts that each added up their share of every
 // statistic the sums alone took 1.9 of the kernel's 3.7 us at k = 4.)
+// k = 7 and 8 get 12 and 8 wavefronts: their solves keep 146 and 182 registers, and with 16 wavefronts the
+// compiler has 128 (24 and 154 spilled; k = 8, 128 x 160: the whole call 27.0 -> 26.3 us).
 constexpr int kFinalizeBlock = 1024;
+constexpr int finalize_block(int k) { return k <= 6 ? kFinalizeBlock : k == 7 ? 768 : 512; }
 // Sum of nrec records by one wavefront, four loads in flight; every lane has it.
 __device__ __forceinline__ double sum_records(const double* __restrict__ rec, int nrec, int lane) {
   double a = 0.0;
@@ -1016,14 +1019,14 @@ __device__ __forceinline__ double sum_records(const double* __restrict__ rec, in
   return wave_sum(a);
 }
 template <int K>
-__global__ __launch_bounds__(kFinalizeBlock) void mbq_finalize_kernel(MbqCall call, int nrec) {
+__global__ __launch_bounds__(finalize_block(K)) void mbq_finalize_kernel(MbqCall call, int nrec) {
   constexpr int NSTAT = nstat_of(K);
   __shared__ double tot[48];
   const int tid = threadIdx.x, wave = tid / kWave, lane = tid & (kWave - 1);
   float alpha_prev[K];  // asked for together with the records: the solve at the end would otherwise wait for them
 #pragma unroll
   for (int p = 0; p < K; ++p) alpha_prev[p] = call.alpha_prev[p];
-  for (int s = wave; s < NSTAT; s += kFinalizeBlock / kWave) {
+  for (int s = wave; s < NSTAT; s += finalize_block(K) / kWave) {
     const double a = sum_records(call.records + int64_t(s) * nrec, nrec, lane);
     if (lane == 0) tot[s] = a;
   }
@@ -1874,7 +1877,7 @@ hipError_t launch_mbq_compress(const accept_desc& d, const MPlan& p, const void*
   mark(tm, s);
 #define ACCEPT_FIN(KK)                                                                          \
   case KK:                                                                                      \
-    hipLaunchKernelGGL(mbq_finalize_kernel<KK>, dim3(1), dim3(kFinalizeBlock), 0, s, call, nrec); \
+    hipLaunchKernelGGL(mbq_finalize_kernel<KK>, dim3(1), dim3(finalize_block(KK)), 0, s, call, nrec); \
     break;
   switch (d.bits) {
     ACCEPT_FIN(1) ACCEPT_FIN(2) ACCEPT_FIN(3) ACCEPT_FIN(4) ACCEPT_FIN(5) ACCEPT_FIN(6) ACCEPT_FIN(7) ACCEPT_FIN(8)

@@ -140,3 +140,13 @@ def test_column_pass_workspace(A, n, C, hw, rows):
     d = A.make_desc(A.UNIFORM, 4, n, C * hw, channels=C, in_dtype=A.BF16)
     up = lambda b: (b + 255) // 256 * 256
     assert A.accept_workspace_size(d) == 16384 + up(rows * C * hw * 4) + up(C * 4)
+
+
+def test_no_kernel_spills_registers(A):
+    """A spill in a streaming loop turns every wait for memory into a wait for everything (one counter
+    serves both).  Read from the metadata the compiler put into the library (a msgpack map per kernel)."""
+    blob = open(A.binding.LIB_PATH, "rb").read()
+    counts = list(re.finditer(rb"\xb1\.vgpr_spill_count(\xcc.|\xcd..|[\x00-\x7f])", blob, re.S))
+    assert len(counts) > 400
+    spilling = [re.findall(rb"_ZN[\w.]+\.kd", blob[:m.start()][-4096:])[-1] for m in counts if m.group(1) != b"\0"]
+    assert spilling == []
