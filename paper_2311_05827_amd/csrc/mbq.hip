@@ -1326,6 +1326,9 @@ __global__ __launch_bounds__(kBlock) void mbq_decode_kernel(const uint8_t* __res
           for (int p = 0; p < K; ++p) {
             const int b = c * K + p;
             pat |= ((w[b / 4] >> (8 * (b % 4) + 7 - r)) & 1u) << p;
+            // (or-ing in one bit after the other is one instruction a bit with its select; the wide
+            // patterns' chains of ors the compiler regroups into one and a half)
+            if constexpr (K >= 7) asm("" : "+v"(pat));
           }
           f[c] = lut[pat];
         }
