@@ -1289,12 +1289,14 @@ __global__ __launch_bounds__(kBlock) void mbq_decode_plain_kernel(const uint8_t*
 }
 
 // ====================================================================== decode (D1 + D2)
-// RAGGED: as in the encoder, vectors at any alignment and the last m % VEC columns one per thread.
+// RAGGED: as in the encoder, vectors at any alignment and the last m % VEC columns one per thread: by the
+// first rem_grid workgroups, beside the others and not behind them (7789 x 1027 float32, k = 2: 8.5 ->
+// 8.2 us; 23 x 173913, k = 3, bfloat16 5.4 -> 4.9).
 template <typename TO, int K, int VEC, bool RAGGED>
 __global__ __launch_bounds__(kBlock) void mbq_decode_kernel(const uint8_t* __restrict__ payload,
                                                              const float* __restrict__ header,
                                                              TO* __restrict__ xhat, int64_t n, int64_t m,
-                                                             int64_t ipg, int64_t items, ItemStep step) {
+                                                             int64_t ipg, int64_t items, ItemStep step, int rem_grid) {
   constexpr int P = 1 << K;
   __shared__ float lut[P];
   const int tid = threadIdx.x;
@@ -1348,11 +1350,24 @@ __global__ __launch_bounds__(kBlock) void mbq_decode_kernel(const uint8_t* __res
     columns(std::integral_constant<int, 1>{}, g, j, w);
   };
 
-  int64_t it = int64_t(blockIdx.x) * kBlock + tid;
+  int block = blockIdx.x, grid = gridDim.x;
+  if constexpr (RAGGED) {
+    if (block < rem_grid) {
+      const int64_t j0 = ipg * VEC, rem = m - j0, G = (n + 7) / 8;
+      for (int64_t s = int64_t(block) * kBlock + tid; s < G * rem; s += int64_t(rem_grid) * kBlock) {
+        const int64_t g = s / rem;
+        one_column(g, j0 + s - g * rem);
+      }
+      return;
+    }
+    block -= rem_grid;
+    grid -= rem_grid;
+  }
+  int64_t it = int64_t(block) * kBlock + tid;
   ItemPos pos;
   pos.g = it / ipg;
   pos.jv = it - pos.g * ipg;
-  for (; it < items; it += int64_t(gridDim.x) * kBlock, item_advance(pos, step, ipg)) {
+  for (; it < items; it += int64_t(grid) * kBlock, item_advance(pos, step, ipg)) {
     if constexpr (VEC > 1) {
       constexpr int NDW = VEC * K / 4;
       const uint8_t* src = payload + ((pos.g * m + pos.jv * VEC) * K);
@@ -1367,13 +1382,6 @@ __global__ __launch_bounds__(kBlock) void mbq_decode_kernel(const uint8_t* __res
       columns(std::integral_constant<int, VEC>{}, pos.g, pos.jv * VEC, w);
     } else {
       one_column(pos.g, pos.jv);
-    }
-  }
-  if constexpr (RAGGED) {
-    const int64_t j0 = ipg * VEC, rem = m - j0, G = (n + 7) / 8;
-    for (int64_t s = int64_t(blockIdx.x) * kBlock + tid; s < G * rem; s += int64_t(gridDim.x) * kBlock) {
-      const int64_t g = s / rem;
-      one_column(g, j0 + s - g * rem);
     }
   }
 }
@@ -1643,10 +1651,22 @@ __global__ __launch_bounds__(kFinalizeBlock) void mbq_init_finalize_kernel(const
 
 // ============================================================================= host side
 // Elements per vector: 16 bytes' worth; for the widths in use (k <= 4) at any alignment, where rows
-// are long enough for wave-items.
-int vec_for(int dtype, int64_t m, int bits) {
+// are long enough for wave-items and the tensor is large enough: the columns that no vector covers, and
+// in the encoder the partial row group, come one after the other behind the vectors, a trip to memory
+// each, where single columns all go at once.  Counted in columns of a row group, measured at 16 K to 9 M
+// values, 4 to 15533 rows, both types (us, single columns / vectors):
+//   decoder: 23 x 86957 4.4 / 4.8, 16 x 187501 5.1 / 5.0, 64 x 62501 6.2 / 5.4, 15 x 390403 9.0 / 7.2;
+//   encoder, complete row groups only: 64 x 7813 9.2 / 9.1, 64 x 15625 9.4 / 9.3, 64 x 23437 12.1 / 10.6;
+//   encoder, complete and partial: 23 x 65217 12.9 / 14.0, 300 x 10001 14.8 / 14.2, 23 x 173913 14.1 / 13.0;
+//   encoder, partial only: 4 x 4001 9.4 / 9.1, 4 x 1000001 18.7 / 12.3.
+constexpr int64_t kRaggedColumns = int64_t(3) << 17;
+constexpr int64_t kRaggedColumnsComplete = int64_t(1) << 17;
+int vec_for(int dtype, int64_t n, int64_t m, int bits, bool encode) {
   const int v = dtype == ACCEPT_BF16 ? 8 : 4;
-  return m % v == 0 || (bits <= 4 && m >= v * kWave) ? v : 1;
+  if (m % v == 0) return v;
+  if (bits > 4 || m < v * kWave) return 1;
+  if (encode && n < 8) return v;
+  return (n + 7) / 8 * m >= (encode && n % 8 == 0 ? kRaggedColumnsComplete : kRaggedColumns) ? v : 1;
 }
 
 int grid_for(int64_t items, int grid_max) {
@@ -1710,8 +1730,9 @@ hipError_t launch_decode(const accept_desc& d, const uint8_t* payload, const flo
   const int64_t ipg = d.m / VEC;
   const int64_t items = ((d.n + 7) / 8) * ipg;
   const int grid = grid_for(items, kDecodeGridMax);
-  hipLaunchKernelGGL((mbq_decode_kernel<TO, K, VEC, RAGGED>), dim3(grid), dim3(kBlock), 0, s, payload, header, xhat, d.n,
-                     d.m, ipg, items, step_for(grid, ipg));
+  const int rem_grid = RAGGED ? grid_for(((d.n + 7) / 8) * (d.m - ipg * VEC), kDecodeGridMax) : 0;
+  hipLaunchKernelGGL((mbq_decode_kernel<TO, K, VEC, RAGGED>), dim3(rem_grid + grid), dim3(kBlock), 0, s, payload, header,
+                     xhat, d.n, d.m, ipg, items, step_for(grid, ipg), rem_grid);
   return hipGetLastError();
 }
 
@@ -1789,7 +1810,7 @@ hipError_t launch_init_pass(int j, const T* x, int64_t N, const InitCall& c, int
 
 MPlan make_mplan(const accept_desc& d) {
   MPlan p{};
-  p.vec = vec_for(d.in_dtype, d.m, d.bits);
+  p.vec = vec_for(d.in_dtype, d.n, d.m, d.bits, true);
   p.ragged = p.vec > 1 && d.m % p.vec != 0;
   p.G = (d.n + 7) / 8;
   p.items = p.G * (d.m / p.vec);
@@ -1897,7 +1918,7 @@ hipError_t launch_mbq_decompress(const accept_desc& d, const void* header, const
                                  hipStream_t s, StageTimer* tm) {
   const uint8_t* pl = static_cast<const uint8_t*>(payload);
   const float* hd = static_cast<const float*>(header);
-  const int vec = vec_for(d.out_dtype, d.m, d.bits);
+  const int vec = vec_for(d.out_dtype, d.n, d.m, d.bits, false);
   hipError_t e;
   mark(tm, s);
   if (d.layout == ACCEPT_LAYOUT_UNENCODED) {

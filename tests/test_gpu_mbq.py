@@ -267,3 +267,22 @@ def test_rows_at_any_alignment(A, n, bf16):
         torch.cuda.synchronize()
         want = orc.mbq_pack(orc.mbq_assign(orc.widen_bf16(bits) if bf16 else x, a), 4, n, m)
         assert first_mismatch(dev_bytes(payload), want.tobytes()) is None, (n, m, alpha)
+
+
+@pytest.mark.parametrize("bf16", [False, True])
+@pytest.mark.parametrize("n,m", [(16, 65535), (16, 65539), (8 * 511, 257 + 256), (9, 196607), (9, 196613), (8 * 768 + 5, 513)])
+def test_rows_at_any_alignment_large(A, n, m, bf16):
+    """Both sides of the sizes from which complete row groups of such rows go in vectors (131072 columns
+    of a row group without a partial group, 393216 with one and in the decoder)."""
+    torch = torch_mod()
+    x = si.make_shape("student_t3", (n, m), 7600 + n % 100)
+    run_case(A, x, 3, n, m, t=2, in_bf16=bf16, out_bf16=bf16, tag="ragged large")
+    d = A.make_desc(A.MBQ, 4, n, m, in_dtype=A.BF16 if bf16 else A.F32, t=1)
+    xd, bits = to_dev(x, bf16)
+    xin = orc.widen_bf16(bits) if bf16 else x
+    for alpha in ([1.0, 0.52, 0.26, 0.1301], [1.0, 0.99, 0.011, 0.01]):   # levels that share a bucket: two, and more
+        a = np.array(alpha, np.float32)
+        _, payload = A.accept_compress(d, xd, alpha_prev=torch.from_numpy(a).cuda())
+        torch.cuda.synchronize()
+        want = orc.mbq_pack(orc.mbq_assign(xin, a), 4, n, m)
+        assert first_mismatch(dev_bytes(payload), want.tobytes()) is None, alpha
