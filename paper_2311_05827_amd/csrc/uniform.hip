@@ -133,6 +133,15 @@ constexpr int kRangeStraddling = 5;  // segments longer than a vector but not wh
                                      // is the segment's elements, ChanPos.rem the element's place in it).  64 x 1024 x 196
                                      // bfloat16: quantize 22.2 -> 9.5 us, decode 26.5 -> 7.9 us against single elements
                                      // whose channel is divided out of their index
+// A small tensor has too few tiles to fill the chip: it is compressed one element at a time, each channel
+// divided out, and decompressed one vector per thread.  Measured at 8 K to 8 M values, segments of 9, 49,
+// 201 and 1063 (us):
+//   compress, single elements / vectors, float32: 0.25 M values 13.1 / 14.4 (segments of 49), 0.5 M
+//   17.6 / 17.0, 0.75 M 22.4 / 17.1; bfloat16: 0.5 M 17.7 / 18.7, 0.75 M 22.3 / 23.1, 1 M 27.2 / 24.4;
+//   decompress, single elements / a vector per thread / tiles, float32: 64 K 2.1 / 2.1 / 3.4, 1 M
+//   3.7 / 2.8 / 3.8, 2 M 5.8 / 4.0 / 4.2, 3 M 7.5 / 5.2 / 4.9; bfloat16: 2 M 5.3 / 3.0 / 3.4, 4 M 8.3 / 4.2 / 4.0.
+constexpr int64_t kStraddleBytes = int64_t(2) << 20;        // of input, from which the compressor takes vectors
+constexpr int64_t kStraddleTiledValues = int64_t(5) << 19;  // from which the decoder takes tiles
 // Position units of a vector.
 template <int MODE, int VEC>
 constexpr int kUnitsPerVec = MODE == kRangeStraddling ? VEC : 1;
@@ -1542,7 +1551,8 @@ hipError_t launch_dequant(const accept_desc& d, const float* header, const uint3
     g.s256 = g.sgrid;
   }
   const int64_t payload_bytes = (N * K + 7) / 8;
-  const int64_t full_tiles = fast ? N / kTileElems : 0;
+  const bool tiled = fast && (MODE != kRangeStraddling || N >= kStraddleTiledValues);
+  const int64_t full_tiles = tiled ? N / kTileElems : 0;
   if (full_tiles > 0) {
     const int64_t tail = N - full_tiles * kTileElems;
     int64_t want = full_tiles > (tail + kBlock - 1) / kBlock ? full_tiles : (tail + kBlock - 1) / kBlock;
@@ -1656,7 +1666,7 @@ UPlan make_uplan(const accept_desc& d) {
     // channels-last (one element per segment) with rows of whole vectors: the quantizer's fast
     // path with one range per element
     p.per_element = p.seg_len == 1 && d.m % p.vec == 0;
-    p.straddling = p.seg_len > p.vec && p.seg_len % p.vec != 0;
+    p.straddling = p.seg_len > p.vec && p.seg_len % p.vec != 0 && p.N * (p.vec == 8 ? 2 : 4) >= kStraddleBytes;
     p.fast = (p.seg_len % p.vec == 0) || p.per_element || p.straddling;
     // column pass: threads own vectors of columns when every row keeps them aligned, else columns
     const int64_t ncv = (d.m % p.vec == 0) ? d.m / p.vec : d.m;

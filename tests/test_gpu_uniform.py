@@ -268,6 +268,20 @@ def test_segments_that_are_not_whole_vectors(A, seg):
         run_case(A, x, 3, 64, 5376 * seg, channels=5376, tag="straddling, many tiles")
 
 
+@pytest.mark.parametrize("values,bf16", [(1 << 19, False), (1 << 20, True), (5 << 19, False), (5 << 19, True)])
+@pytest.mark.parametrize("seg", [9, 201])
+def test_straddling_segments_by_size(A, seg, values, bf16):
+    """Both sides of the sizes from which such a tensor is compressed in vectors (2 MiB) and
+    decompressed in tiles (2621440 values)."""
+    row = 41 * seg
+    for n in (values // row, values // row + 1):
+        assert (n * row >= values) == (n != values // row)
+        x = per_channel_input(n, 41, seg, 360 + seg)
+        x[n - 1, 40, seg - 1] = 100.0
+        for rounding in (0, 1):
+            run_case(A, x, 5, n, row, channels=41, in_bf16=bf16, out_bf16=bf16, rounding=rounding, seed=5, tag="straddling by size")
+
+
 @pytest.mark.parametrize("seg", [512, 516, 520, 784, 1024, 1032, 2048, 2056, 4096, 4104, 8200, 20488])
 def test_segment_lengths_of_the_range_pass(A, seg):
     """One, two, four and eight loads per lane and chunk, chunks that fill them and that do not."""
