@@ -273,6 +273,8 @@ __global__ __launch_bounds__(kBlock) void range_segments_kernel(const T* __restr
     int64_t slot[NI];  // where the chunk's maximum goes
 #pragma unroll
     for (int i = 0; i < NI; ++i) c[i] = 0.0f;
+    int live = 0;  // chunks of this turn; what follows them repeats the last
+    bool next = true;
     uint4 raw[NI][U];
     auto reduce = [&](int i) {
 #pragma unroll
@@ -317,8 +319,9 @@ __global__ __launch_bounds__(kBlock) void range_segments_kernel(const T* __restr
 #pragma unroll
         for (int u = 0; u < U; ++u) raw[i][u] = make_uint4(0u, 0u, 0u, 0u);
       }
-      // the next chunk; after the last one that one again (its maximum is stored more than once)
-      more = it + WAVES < it_hi;
+      // the next chunk; after the last one that one is read again and not looked at
+      live += next ? 1 : 0;
+      next = more = it + WAVES < it_hi;
       if (more) {
         it += WAVES;
         chunk += d_chunk;
@@ -331,6 +334,7 @@ __global__ __launch_bounds__(kBlock) void range_segments_kernel(const T* __restr
     }
 #pragma unroll
     for (int i = 0; i < NI; ++i) {
+      if (i >= live) break;
       if (NI > 1) reduce(i);
       c[i] = wave_max(c[i]);  // every lane of the wavefront reaches this point: the loop bounds are wave-uniform
       if (lane == 0) partials[slot[i]] = c[i];
