@@ -87,7 +87,11 @@ constexpr int kHeldGrid = 256;
 inline bool held_runs(const UPlan& p, int units) { return p.held && units >= kHeldGrid; }
 
 // held_polls: how often a workgroup of the held pass looks for the others' maxima before it gives up
-// (kHeldPolls; fewer only where a test wants the case that it gives up).
+// (kHeldPolls; fewer only where a test wants the case that it gives up).  64 looks take about 50 us.  Alone
+// on the chip, 205 MB, 16 are too few (72.8 us a call) and 32 enough (56.8; 64: 55.8, the spread of the
+// workgroups' ends being that of the memory); next to a kernel that fills the chip, more only keep
+// compute units longer: 100 MB beside copies on another stream 92 us a call at 32, 94 at 64, 108 at 128,
+// 130 at 512.
 constexpr int kHeldPolls = 64;
 hipError_t launch_uniform_compress(const accept_desc& d, const UPlan& p, const void* x, void* header,
                                    void* payload, void* ws, hipStream_t s, StageTimer* tm,

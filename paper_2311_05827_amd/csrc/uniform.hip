@@ -36,7 +36,14 @@ constexpr int kQuantGridMax = 2048;    // workgroups of the quantize+pack kernel
 constexpr int kDequantGridMax = 8192;
 // The held pass (quantize_held_kernel): one workgroup per compute unit, two wavefronts per SIMD.
 constexpr int kHeldBlock = 512;
-constexpr int kUnitElems = 2 * kTileElems;  // elements a workgroup takes at a time
+constexpr int kUnitTiles = 2;
+constexpr int kUnitElems = kUnitTiles * kTileElems;  // elements a workgroup takes at a time
+// Workgroups of the kernel behind it.  Nearly all end at once, unless workgroups of the held pass gave up:
+// then the memory is read as fast as this many allow.  Time with all of them giving up, 205 MB: 256
+// workgroups 80.0 us, 512 74.3, 1024 75.3, 2048 75.3 (two reads 68.8); beside copies on another stream
+// 219, 213, 180, 158; with none giving up 2048 cost 0.7 us more than 512 and 1024.
+constexpr int kHeldRestGrid = 1024;
+static_assert(kHeldRestGrid % (kUnitTiles * kHeldGrid) == 0, "a workgroup's tiles belong to one workgroup of the held pass");
 template <typename T>
 constexpr int kHeldVecs = sizeof(T) == 4 ? 56 : 48;  // 16-byte vectors a thread keeps in registers (bfloat16: 56 would spill)
 constexpr int kHeldLdsVecs = 16;                     // and in local memory
@@ -618,7 +625,6 @@ __global__ __launch_bounds__(kBlock) void quantize_pack_kernel(
   constexpr int PIECES = kTileElems / 4;
   __shared__ __attribute__((aligned(16))) uint32_t pieces[2][PIECES];
   __shared__ float red[kBlock / kWave];
-  __shared__ int red_up[kBlock / kWave];
 
   const int tid = threadIdx.x;
   // Tile order.  The range pass has just read the tensor front to back, so its end is what the
@@ -627,12 +633,12 @@ __global__ __launch_bounds__(kBlock) void quantize_pack_kernel(
   // of the plain order.  A workgroup's tiles then step backwards by one grid stride, and tile and
   // workgroup index stay equal modulo 8: the die that read a tile in the range pass reads it
   // again here.  The up to seven tiles after rev_tiles keep their plain places.
-  // kOneRangeHeld: only the tiles behind the last whole unit, or all if a workgroup of the held
-  // pass gave up; in plain order.
-  int64_t tiles = MODE == kOneRangeHeld ? 0 : full_tiles;  // places to go through
-  int64_t skip = 0;
+  // kOneRangeHeld: plain order.  The grid makes all of a workgroup's tiles belong to units of the same
+  // workgroup of the held pass; if that one finished them, only what lies behind the last whole unit is
+  // left (from place first_f on).
+  int64_t first_f = blockIdx.x;
   auto tile_of = [&](int64_t tile_f) {
-    if (MODE == kOneRangeHeld) return tile_f + skip;
+    if (MODE == kOneRangeHeld) return tile_f;
     return tile_f < rev_tiles ? rev_tiles - 8 - (tile_f & ~int64_t(7)) + (tile_f & 7) : tile_f;
   };
   // A tile's vectors are asked for one tile ahead: those of the first tile here, before anything
@@ -643,24 +649,23 @@ __global__ __launch_bounds__(kBlock) void quantize_pack_kernel(
 #pragma unroll
     for (int u = 0; u < LOADS; ++u) raw[u] = load16_stream(xt + (u * kBlock + tid) * VEC);
   };
-  if (int64_t(blockIdx.x) < tiles) ask_for_tile(tile_of(blockIdx.x));
+  if (MODE == kOneRangeHeld) {
+    // (the records: largest value and whether it finished, per workgroup of the held pass)
+    const float2* rec = reinterpret_cast<const float2*>(partials);
+    if (rec[blockIdx.x / kUnitTiles % kHeldGrid].y != 0.0f && first_f < held_tiles)
+      first_f += (held_tiles - first_f + gridDim.x - 1) / gridDim.x * gridDim.x;
+    // nothing left here, as for nearly all of them in a call in which none gave up
+    if (blockIdx.x != 0 && first_f >= full_tiles && (slow_first_group + int64_t(blockIdx.x) * kBlock) * 8 >= N) return;
+  }
+  if (first_f < full_tiles) ask_for_tile(tile_of(first_f));
 
   float r_tensor = 0.0f;
   if (one_range(MODE)) {
     float c = 0.0f;
-    bool done = true;
-    if (MODE == kOneRangeHeld) {  // one record per workgroup of the held pass
-      for (int i = tid; i < npart; i += kBlock) {
-        const float2 rec = reinterpret_cast<const float2*>(partials)[i];
-        c = fmaxf(c, rec.x);
-        done = done && rec.y != 0.0f;
-      }
-    } else {
-      for (int i = tid; i < npart; i += kBlock) c = fmaxf(c, partials[i]);
-    }
+    for (int i = tid; i < npart; i += kBlock)
+      c = fmaxf(c, MODE == kOneRangeHeld ? reinterpret_cast<const float2*>(partials)[i].x : partials[i]);
     c = wave_max(c);
-    const bool gave_up = __ballot(!done) != 0;
-    if ((tid & (kWave - 1)) == 0) { red[tid / kWave] = c; red_up[tid / kWave] = gave_up ? 1 : 0; }
+    if ((tid & (kWave - 1)) == 0) red[tid / kWave] = c;
     __syncthreads();
     c = red[0];
 #pragma unroll
@@ -668,18 +673,9 @@ __global__ __launch_bounds__(kBlock) void quantize_pack_kernel(
     float s;
     scale_from_range(c, K, s, r_tensor);
     if (blockIdx.x == 0 && tid == 0) header[0] = s;
-    if (MODE == kOneRangeHeld) {
-      // the mailboxes have been read by everyone: empty again for the next call
-      if (blockIdx.x == 0)
-        for (int i = tid; i < kHeldGrid; i += kBlock) mail[i] = 0;
-      int up = 0;
-#pragma unroll
-      for (int w = 0; w < kBlock / kWave; ++w) up |= red_up[w];
-      // rare: one gave up, all tiles once more (the same bytes where they were done)
-      skip = __builtin_amdgcn_readfirstlane(up) != 0 ? 0 : held_tiles;
-      tiles = full_tiles - skip;
-      if (int64_t(blockIdx.x) < tiles) ask_for_tile(tile_of(blockIdx.x));
-    }
+    // the mailboxes have been read by everyone: empty again for the next call
+    if (MODE == kOneRangeHeld && blockIdx.x == 0)
+      for (int i = tid; i < kHeldGrid; i += kBlock) mail[i] = 0;
   }
 
   // Channel position of a tile's first vector (the same in all threads), stepped from tile to
@@ -761,13 +757,13 @@ __global__ __launch_bounds__(kBlock) void quantize_pack_kernel(
   // against a state multiplied out per element and a 64-bit integer converted to float.
   const uint64_t z_thread = STOCH ? rand_state(seed, uint64_t(tid * VEC)) : 0;  // of the thread's first element of tile 0
   int buf = 0;
-  for (int64_t tile_f = blockIdx.x; tile_f < tiles; tile_f += gridDim.x, buf ^= 1) {
+  for (int64_t tile_f = first_f; tile_f < full_tiles; tile_f += gridDim.x, buf ^= 1) {
     const int64_t tile = tile_of(tile_f);
     // the next tile of this workgroup: one grid stride back inside the reversed part
     const int64_t next_f = tile_f + gridDim.x;
     ChanPos next_pos = first_pos;
     LocalFetch next_lf;
-    if (!one_range(MODE) && next_f < tiles) {
+    if (!one_range(MODE) && next_f < full_tiles) {
       if (next_f < rev_tiles) chan_retreat(geom, next_pos, geom.sgrid);
       else next_pos = chan_init(geom, tile_of(next_f) * TILE_UNITS);
       if (MODE == kRangePerVectorLocal) local_fetch(next_pos, next_lf);
@@ -795,8 +791,8 @@ __global__ __launch_bounds__(kBlock) void quantize_pack_kernel(
         pieces[buf][(u * kBlock + tid) * QPV + h] = quantize4<K, STOCH>(&f[4 * h], &r[4 * h], z + uint64_t(4 * h) * kRandStep);
       z += uint64_t(kBlock * VEC) * kRandStep;
     }
-    if (next_f < tiles) ask_for_tile(tile_of(next_f));
-    if (MODE == kRangePerVectorLocal && next_f < tiles)
+    if (next_f < full_tiles) ask_for_tile(tile_of(next_f));
+    if (MODE == kRangePerVectorLocal && next_f < full_tiles)
       local_finish(tile_of(next_f), next_pos, next_lf, local_r[buf ^ 1]);
     first_pos = next_pos;
     __syncthreads();
@@ -834,8 +830,14 @@ __global__ __launch_bounds__(kBlock) void quantize_pack_kernel(
 //
 // The wait is bounded: nothing says that all 256 workgroups run at the same time (another kernel may
 // hold some compute units).  A workgroup that has not seen all mailboxes after `polls` looks gives
-// up, says so in its record and ends; quantize_pack_kernel then takes the held units too.  So every
+// up, says so in its record and ends; quantize_pack_kernel then takes its units too.  So every
 // workgroup ends whatever else runs, and the result does not depend on it.
+//
+// Beside other work: a workgroup needs a whole compute unit (160 KiB of local memory, all registers), so
+// next to a kernel whose workgroups keep filling the chip it starts late, and the early ones give up.
+// Time of a call on one stream while another stream is busy, two reads / held (us): small elementwise
+// kernels, 100 MB float32 43 / 32, 205 MB 85 / 70, 100 MB bfloat16 53 / 39; matrix products 155 / 149,
+// 184 / 179, 160 / 155; copies of 512 MB without a pause 66 / 98, 130 / 161, 72 / 145.
 //
 // A mailbox is one 64-bit word, value and the call's mark together, written and read with device-scope
 // accesses (they bypass the dies' second-level caches): no ordering between two words is needed.
@@ -1190,11 +1192,11 @@ hipError_t launch_quant(const accept_desc& d, const UPlan& p, const T* x, float*
   const int64_t full_tiles = p.fast ? N / kTileElems : 0;
   const int64_t groups = (N + 7) / 8;
   const int64_t slow_first = full_tiles * (kTileElems / 8);
-  const int64_t held_tiles = MODE == kOneRangeHeld ? p.held_units * (kUnitElems / kTileElems) : 0;
+  const int64_t held_tiles = MODE == kOneRangeHeld ? p.held_units * kUnitTiles : 0;
   const int64_t slow_groups = groups - slow_first;
   int64_t want = full_tiles > (slow_groups + kBlock - 1) / kBlock ? full_tiles : (slow_groups + kBlock - 1) / kBlock;
   if (want < 1) want = 1;
-  if (MODE == kOneRangeHeld) want = kHeldGrid;  // nearly nothing to do, but for the case that it is everything
+  if (MODE == kOneRangeHeld) want = kHeldRestGrid;
   const int grid = int(want < kQuantGridMax ? want : kQuantGridMax);
   // the reversed tile order needs tile and workgroup index to agree modulo 8
   const int64_t rev_tiles = (grid % 8 == 0) ? (full_tiles & ~int64_t(7)) : 0;
