@@ -122,7 +122,7 @@ accept_status accept_workspace_size(const accept_desc* desc, size_t* bytes);
  * Compress x_dev (N elements of in_dtype, 16-byte aligned) into header_dev (4-byte
  * aligned) and payload_dev (16-byte aligned), sizes as accept_packed_size reports.
  *
- *   UNIFORM: range pass, then fused quantize + pack (one range and 48 to 256 MiB of input: both in
+ *   UNIFORM: range pass, then fused quantize + pack (one range and 48, bfloat16 72, to 256 MiB of input: both in
  *     one kernel that keeps part of the tensor on the chip).  Code i occupies payload bits
  *     [ik, (i+1)k), most significant bit first, bit b of the stream being bit 7-(b mod 8)
  *     of byte b/8; codes are q + 2^(k-1) for k < 8 and the two's-complement byte for

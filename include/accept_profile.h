@@ -17,8 +17,8 @@ extern "C" {
  * kernel the call launches is bracketed by HIP events on the given stream; the call then
  * WAITS for the last event and writes each stage's duration in milliseconds to the host
  * array stage_ms[0..*n_stages) (capacity ACCEPT_MAX_STAGES).  Stage order:
- *   UNIFORM compress: range, [range finalize], quantize+pack, or for one range and 48 to 256 MiB of
- *   input the held range+quantize and the rest of it;   MBQ compress: encode+sums, finalize;
+ *   UNIFORM compress: range, [range finalize], quantize+pack, or for one range and 48 (bfloat16: 72) to 256 MiB
+ *   of input the held range+quantize and the rest of it;   MBQ compress: encode+sums, finalize;
  *   decompress: the one kernel.
  * For benchmarks only; creates and destroys its events on every call.
  */

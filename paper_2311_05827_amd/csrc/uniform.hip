@@ -51,14 +51,18 @@ template <typename T>
 constexpr int kHeldUnits = kHeldVecs<T> * kHeldBlock * Elem<T>::VEC / kUnitElems;  // 7 (float32), 12 (bfloat16)
 template <typename T>
 constexpr int kHeldLdsUnits = kHeldLdsVecs * kHeldBlock * Elem<T>::VEC / kUnitElems;  // 2, 4
-// Tensors that take the held pass.  Below, its second kernel (4 us that do nearly nothing) costs
-// more than the saved read: 35 MB 18.4 us against 17.8 with two reads, 51 MB 20.9 against 22.1
-// (float32, k = 8), 50 MB 23.9 against 23.7 (bfloat16).  Above, the part that is kept gets small
-// and the workgroups drift apart by more than they wait for each other: 205 MB 59.1 against 69.5,
-// 300 MB 97 against 110, 400 MB 150 against 149.
-constexpr int64_t kHeldMinBytes = int64_t(48) << 20;
+// Tensors that take the held pass.  Below, its second kernel (4 us that do nearly nothing) costs more
+// than the saved read; captured calls, k = 8, two reads / held (us): float32 51 MB 19.2 / 18.9, 55 MB
+// 20.4 / 20.1, 66 MB 23.3 / 21.1; bfloat16, whose values are twice as many, 51 MB 19.6 / 21.9, 60 MB
+// 23.4 / 24.5, 72 MB 27.5 / 27.5, 76 MB 29.4 / 28.4, 95 MB 35.2 / 32.8 (k = 4: 72 MB 23.5 / 23.8, 76 MB
+// 24.8 / 24.8).  Above, the part that is kept gets small and the workgroups drift apart by more than they
+// wait for each other: bfloat16 205 MB 75.9 / 67.7, 262 MB 96.1 / 94.2, 268 MB 98.3 / 95.2.  float32 gains
+// beyond the line too (268 MB 89.6 / 79.5, 300 MB 110 / 97, 400 MB 149 / 150); it lies where both types do.
+template <typename T>
+constexpr int64_t kHeldMinBytes = int64_t(sizeof(T) == 4 ? 48 : 72) << 20;
 constexpr int64_t kHeldMaxBytes = int64_t(256) << 20;
-static_assert(kHeldMinBytes / 4 >= int64_t(kHeldGrid) * kUnitElems, "every workgroup has a unit");
+static_assert(kHeldMinBytes<float> / 4 >= int64_t(kHeldGrid) * kUnitElems, "every workgroup has a unit");
+static_assert(kHeldMinBytes<bf16_t> / 2 >= int64_t(kHeldGrid) * kUnitElems, "every workgroup has a unit");
 static_assert(kMailOffset + kHeldGrid * sizeof(uint64_t) <= kCtrlBytes, "the control block holds the mailboxes");
 static_assert(kQuantGridMax % 8 == 0 && kRangeGridMax % 8 == 0, "grids at their caps keep tile and workgroup index equal modulo 8");
 static_assert(kRangeGridMax <= 4096, "the workspace holds at most 4096 partial maxima");
@@ -1644,8 +1648,8 @@ UPlan make_uplan(const accept_desc& d) {
     p.range_grid = int(blocks < kRangeGridMax ? blocks : kRangeGridMax);
     partial_bytes = size_t(4096) * sizeof(float);
     const int64_t bytes = p.N * (p.vec == 8 ? 2 : 4);
-    p.held = d.layout == ACCEPT_LAYOUT_PACKED && d.rounding == ACCEPT_ROUND_NEAREST_EVEN && bytes >= kHeldMinBytes &&
-             bytes <= kHeldMaxBytes;
+    p.held = d.layout == ACCEPT_LAYOUT_PACKED && d.rounding == ACCEPT_ROUND_NEAREST_EVEN &&
+             bytes >= (p.vec == 8 ? kHeldMinBytes<bf16_t> : kHeldMinBytes<float>) && bytes <= kHeldMaxBytes;
     if (p.held) {
       const int64_t keep = p.vec == 8 ? kHeldUnits<bf16_t> : kHeldUnits<float>;
       const int64_t keep_lds = p.vec == 8 ? kHeldLdsUnits<bf16_t> : kHeldLdsUnits<float>;

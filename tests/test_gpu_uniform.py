@@ -303,7 +303,7 @@ def test_channels_last_range(A, n, C):
         run_case(A, x, k, n, C, channels=C, in_bf16=bf16, out_bf16=bf16, tag="channels-last")
 
 
-# One range, nearest rounding, 48 to 256 MiB: the end of the tensor is kept on the chip between the
+# One range, nearest rounding, 48 (bfloat16: 72) to 256 MiB: the end of the tensor is kept on the chip between the
 # range and the quantizer.  256 workgroups, units of 16384 elements; per workgroup 7 (bfloat16: 12)
 # units in registers, 2 (4) in local memory, the rest read twice.
 HELD_ROUND = 256 * 16384
@@ -314,7 +314,9 @@ HELD_ROUND = 256 * 16384
     (3, 3 * HELD_ROUND + 5 * 16384 + 8193, False),   # a few workgroups with one unit more, a tile and one element behind
     (5, 7 * HELD_ROUND + 16384, False),              # local memory comes into use
     (4, 10 * HELD_ROUND - 16384 * 7 + 33, False),    # one unit per workgroup is read twice, some have none
-    (7, 6 * HELD_ROUND + 31, True),
+    (7, 6 * HELD_ROUND + 31, True),                  # bfloat16 below its own line: two reads
+    (7, 9 * HELD_ROUND + 31, True),                  # the smallest in bfloat16
+    (5, 13 * HELD_ROUND + 16384 * 3 + 9, True),      # local memory comes into use
     (6, 17 * HELD_ROUND + 16384 * 255, True),        # two read twice
     (2, 30 * HELD_ROUND + 8192, True),               # more are read twice than there are slots
 ])
@@ -330,7 +332,7 @@ def test_held_pass_largest_value_at_the_end(A, tail, bf16):
     """The largest value in the last element, in the first one behind the last whole unit and in the
     last whole unit, whether the workgroups see each other's maxima or give up."""
     torch = torch_mod()
-    k, N = 8, (6 if bf16 else 3) * HELD_ROUND + 16384 * 3 + tail
+    k, N = 8, (9 if bf16 else 3) * HELD_ROUND + 16384 * 3 + tail
     print("held, tail", tail, "bf16", bf16, flush=True)
     base = si.make_shape("grad", (1, N), 230 + tail % 7)
     d = A.make_desc(A.UNIFORM, k, 1, N, in_dtype=A.BF16 if bf16 else A.F32)
