@@ -101,16 +101,14 @@ hipError_t launch_uniform_decompress(const accept_desc& d, const void* header, c
 
 // ---- scheme M (multi-bit) ---------------------------------------------------------------
 struct MPlan {
-  int vec;                // columns per work item: 16-byte vectors when rows stay 16-byte aligned, else 1
+  int vec;                // columns per work item: those of a 16-byte vector, or 1 (the rule is at vec_for)
   int64_t G;              // ceil(n/8) row groups
-  bool ragged;            // rows are not whole 16-byte vectors: vectors at any alignment, then m % vec single columns
-  int64_t items;          // G * (m / vec)
+  bool ragged;            // vectors, but rows are not whole ones: at any alignment, then m % vec single columns
   bool wide;              // a row group holds at least one full wave-item
   bool stream;            // wide, and complete row groups exist: they go through the pipelined stream
   uint32_t wpg;           // wave-items (64 items) per row group
   uint32_t n_wave_items;  // of the complete row groups
   int grid;               // workgroups of the encode kernel = number of partial-sum records
-  int nstat;              // doubles per record
   size_t bytes;
 };
 

@@ -99,9 +99,10 @@ template <int K>
 struct EncodeTables {
   static constexpr int P = 1 << K;
   static constexpr int NW = (K + 3) / 4;  // spread words per level
-  float lv_raw[P];
-  float lv_sorted[P];
-  uint32_t pat_sorted[P];
+  static constexpr int SORT = (K <= 4) ? 1 : P;  // k <= 4 sorts in registers
+  float lv_raw[SORT];
+  float lv_sorted[SORT];
+  uint32_t pat_sorted[SORT];
   float tau[3 * P];                        // P-1 thresholds, then +inf padding (the windowed search reads past them)
   uint32_t spread[P * NW];                 // per sorted level: bit p of the sign pattern at bit 8*(p%4) of word p/4
   // k <= 4 only: row lo = {tau[lo] (or +inf), spread[lo]}, so that one 8-byte read at lo*8 and one
@@ -235,11 +236,7 @@ __device__ __forceinline__ void build_encode_tables(const float (&alpha)[K], Enc
 #pragma unroll
       for (int bb = 0; bb < K; ++bb) sp |= ((pat_s >> bb) & 1u) << (8 * bb);
       if (tid < 3 * P) tb.tau[tid] = tau;  // 3P <= 48 lanes: thresholds, then +inf padding
-      if (tid < P) {
-        tb.lv_sorted[tid] = lv_s;
-        tb.pat_sorted[tid] = pat_s;
-        tb.spread[tid] = sp;
-      }
+      if (tid < P) tb.spread[tid] = sp;
       if (tid <= P + 1) {
         tb.pair[2 * tid] = f32_as_u32(tau);  // tau[P-1], tau[P], tau[P+1] are +inf
         tb.pair[2 * tid + 1] = tid < P ? sp : 0u;
@@ -1813,7 +1810,6 @@ MPlan make_mplan(const accept_desc& d) {
   p.vec = vec_for(d.in_dtype, d.n, d.m, d.bits, true);
   p.ragged = p.vec > 1 && d.m % p.vec != 0;
   p.G = (d.n + 7) / 8;
-  p.items = p.G * (d.m / p.vec);
   // The encode kernel works on wave-items (64 items of one row group).  A row group needs at least
   // one full wave-item to be worth it, and numbers and row lengths have to fit 32 bits; other
   // geometries (very narrow tensors) go one column per thread.
@@ -1834,7 +1830,6 @@ MPlan make_mplan(const accept_desc& d) {
     if (blocks < 1) blocks = 1;
     p.grid = int(blocks < kEncodeGridMax ? blocks : kEncodeGridMax);
   }
-  p.nstat = nstat_of(d.bits);
   // control block, then room for kMaxRecords records of the widest kind (k = 8)
   const size_t bytes = kCtrlBytes + size_t(nstat_of(8)) * kMaxRecords * sizeof(double);
   p.bytes = (bytes + 255) / 256 * 256;
