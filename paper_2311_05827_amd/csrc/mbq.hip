@@ -291,11 +291,14 @@ __device__ __forceinline__ void build_encode_tables(const float (&alpha)[K], Enc
 // bfloat16 numbers of one plane (0xBF00 is -0.5), and one dot product of two adds both elements to the
 // plane's sum: two instructions per plane and pair where widening, converting the flag and a
 // multiply-add take four.  (The dot product rounds once, to within an ulp of its largest term,
-// denormals included; the factor -2 is put back at the end of an item.)
+// denormals included; the factor -2 is put back at the end of an item.  Against sums in 64 bits the
+// header is as good as with multiply-adds for ReLU, normal, log-normal and Student-t values; where the
+// terms of a sum differ by many powers of two the dot product's rounding leans to one side: over 40 powers
+// m_q is off by 8e-9 of mean|x| instead of 3e-10, an eighth of the rounding of a level to float32.)
 //
-// What bounded the encoder was the number of vector instructions (18 per element; at two
-// wavefronts per SIMD each costs 4.3 cycles): 51.4 M values at k = 4: 36.9 -> 32.8 us
-// a call, 18 -> 9.4 vector instructions per element; the loop then runs at 7.0 TB/s.
+// What bounded the encoder was the number of vector instructions (at two wavefronts per SIMD each
+// costs 4.3 cycles): 51.4 M values at k = 4: 36.9 -> 32.8 us a call, 18.5 -> 10.2 vector instructions
+// per element (SQ_INSTS_VALU); the loop then runs at 7.0 TB/s.
 constexpr uint32_t kFlagByte = 0xBFu;
 template <int K>
 struct ValueTables {

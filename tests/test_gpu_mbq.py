@@ -245,6 +245,43 @@ def test_bf16_every_value(A, k):
 
 
 @pytest.mark.parametrize("bf16", [False, True])
+@pytest.mark.parametrize("kind", ["outliers", "cancelling", "wide"])
+@pytest.mark.parametrize("k", [2, 3, 4])
+def test_header_of_values_that_differ_much(A, k, kind, bf16):
+    """The header against the sums in 64 bits, with terms of very different size.  An item's sums are
+    float32: at most 64 terms, in 32 steps (two-term dot products) or 64, each good to an ulp of the
+    largest number in it, so to 2^-23 of the item's sum |x|; they add up in float64.  With E = 64 * 2^-23 *
+    sum |x| the plane sums H and S_x are within E, B^T x = 2 H - S_x within 3 E, and the bounds of alpha_t
+    and m_q follow (plus their own rounding to float32)."""
+    torch = torch_mod()
+    rng = np.random.default_rng(7500 + k)
+    for n, m in ((64, 2048), (13, 1003)):
+        x = rng.standard_normal((n, m))
+        if kind == "outliers":
+            x *= np.where(rng.random((n, m)) < 0.01, 1e3, 1.0)
+        elif kind == "cancelling":
+            x = np.where(rng.random((n, m)) < 0.05, np.sign(x) * 1e4, x)
+        else:
+            x *= np.exp2(rng.integers(-20, 20, (n, m)))
+        xd, bits = to_dev(x.astype(np.float32), bf16)
+        x32 = orc.widen_bf16(bits) if bf16 else x.astype(np.float32).reshape(-1)
+        alpha = (np.median(np.abs(x32)) * 0.5 ** np.arange(k)).astype(np.float32)
+        d = A.make_desc(A.MBQ, k, n, m, in_dtype=A.BF16 if bf16 else A.F32, t=0)
+        header, _ = A.accept_compress(d, xd, alpha_prev=torch.from_numpy(alpha).cuda())
+        torch.cuda.synchronize()
+        got = np.frombuffer(dev_bytes(header), dtype="<f4").astype(np.float64)
+        G, h, Sb, Sx = orc.mbq_stats(x32, orc.mbq_assign(x32, alpha), k)
+        beta, N = orc.beta(0), n * m
+        want = beta * alpha.astype(np.float64) + (1 - beta) * np.linalg.solve(G, h)
+        E = 64 * 2.0 ** -23 * np.abs(x32.astype(np.float64)).sum()
+        d_alpha = (1 - beta) * np.abs(np.linalg.inv(G)).sum(axis=1) * 3 * E + 2.0 ** -23 * np.abs(want)
+        mq = (want @ Sb - Sx) / N
+        d_mq = (np.abs(Sb) @ d_alpha + E) / N + 2.0 ** -23 * abs(mq)
+        assert np.all(np.abs(got[:k] - want) <= d_alpha), (got, want, d_alpha)
+        assert abs(got[k] - mq) <= d_mq, (got[k], mq, d_mq)
+
+
+@pytest.mark.parametrize("bf16", [False, True])
 @pytest.mark.parametrize("n", [1, 7, 8, 9, 23])
 def test_rows_at_any_alignment(A, n, bf16):
     """Rows that are not whole 16-byte vectors: vectors at any alignment, the last columns one by
