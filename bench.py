@@ -61,6 +61,13 @@ def alg_bytes(kernel, N, n, m, k, b_in=4, b_out=4):
     return 0
 
 
+def input_reads(A, desc):
+    """How often accept_compress reads its input, by the stages it launches: twice where a range pass
+    comes before the quantizer, once for scheme M and for the held pass (which keeps the end of the
+    tensor on the chip and reads only what does not fit a second time: not counted here)."""
+    return 2 if A.accept_stage_name(desc, 0, 0) == "range" else 1
+
+
 def read_traffic():
     """Measured HBM bytes per launch from committed rocprofv3 --pmc summaries, if present."""
     out = {}
@@ -268,7 +275,7 @@ def main():
         "mbq_compress_k4": (compress_m, decompress_u, alg_bytes("mbq_encode", N, n, m, K_FWD)),
         "mbq_decompress_k4": (decompress_m, compress_u, alg_bytes("mbq_decode", N, n, m, K_FWD)),
         "uniform_compress_k8": (compress_u, decompress_m,
-                                alg_bytes("range", N, n, m, K_BWD) + alg_bytes("quantize_pack", N, n, m, K_BWD)),
+                                (input_reads(A, du) - 1) * N * 4 + alg_bytes("quantize_pack", N, n, m, K_BWD)),
         "uniform_decompress_k8": (decompress_u, compress_m, alg_bytes("unpack_dequant", N, n, m, K_BWD)),
     }
     breakdown = {}
@@ -322,8 +329,8 @@ def main():
         "kernels": kernels,
     }
 
-    # the same for whole calls (every kernel the call launches: range + quantize_pack, encode +
-    # finalize), from the in-mix timings above
+    # the same for whole calls (every kernel the call launches: the held pass and the kernel behind it,
+    # or range + quantize_pack; encode + finalize), from the in-mix timings above
     call_roofline = {name: {"bound": "hbm", "achieved": round(v["alg_bytes"] / (v["ms"] * 1e-3) / 1e9, 1),
                             "peak": HBM_PEAK_GBPS, "unit": "GB/s", "frac": v["alg_hbm_frac"]}
                      for name, v in breakdown.items()}
@@ -568,10 +575,11 @@ class CellTimer:
         else:
             d = A.make_desc(A.MBQ, k, n, m, t=1, in_dtype=tcode, out_dtype=tcode, layout=layout)
             alpha = A.accept_mbq_init(d, x)
-        # algorithmic bytes of the call: the input (twice for scheme U: range pass, quantize pass),
-        # the header and the payload of this layout one way; the same plus the output back
+        # algorithmic bytes of the call: the input as often as its stages read it, the header and the
+        # payload of this layout one way; the same plus the output back
         hb, pb = A.accept_packed_size(d)
-        cb = (2 if scheme[0] == "U" else 1) * N * b + hb + pb
+        reads = input_reads(A, d)
+        cb = reads * N * b + hb + pb
         db = hb + pb + N * b
         h, p, w = A.alloc_outputs(d, dev)
         out = torch.empty(N, dtype=torch.bfloat16 if bf else torch.float32, device=dev)
@@ -581,10 +589,10 @@ class CellTimer:
         td, td_min = self._cold(deco, reps)
         tcw, tdw = self._warm(comp, reps), self._warm(deco, reps)
         frac = lambda nbytes, ms: round(nbytes / ms / 1e6 / HBM_PEAK_GBPS, 4)
-        # scheme U reads its input twice; the tensors here fit the memory-side cache, so the second
-        # read need not reach HBM: the same fraction priced with one read is the lower bound
+        # where the input is read twice: the tensors here fit the memory-side cache, so the second
+        # read need not reach HBM, and the same fraction priced with one read is the lower bound
         extra = {}
-        if scheme[0] == "U":
+        if reads == 2:
             extra = dict(compress_alg_bytes_one_read=cb - N * b, compress_alg_frac_one_read=frac(cb - N * b, tc))
         return dict(config=name, scheme=scheme, k=k, channels=C, dtype="bf16" if bf else "f32",
                     compress_us=round(tc * 1e3, 2), compress_us_min=round(tc_min * 1e3, 2),
@@ -592,7 +600,7 @@ class CellTimer:
                     decompress_us=round(td * 1e3, 2), decompress_us_min=round(td_min * 1e3, 2),
                     decompress_us_warm=round(tdw * 1e3, 2),
                     compress_in_GBps=round(N * b / tc / 1e6, 1), decompress_out_GBps=round(N * b / td / 1e6, 1),
-                    compress_alg_bytes=cb, decompress_alg_bytes=db,
+                    compress_input_reads=reads, compress_alg_bytes=cb, decompress_alg_bytes=db,
                     compress_alg_frac=frac(cb, tc), decompress_alg_frac=frac(db, td),
                     compress_alg_frac_best=frac(cb, tc_min), decompress_alg_frac_best=frac(db, td_min), **extra)
 

@@ -25,6 +25,17 @@ def test_algorithmic_bytes_follow_the_packed_sizes(k):
     assert bench.alg_bytes("mbq_decode", N, n, m, k) == pm + hm + 4 * N
 
 
+def test_input_reads_follow_the_stages():
+    """A compress call is priced with the reads that its stages make."""
+    import paper_2311_05827_amd as A
+    n, m = bench.SHAPE[0], bench.SHAPE[1] * bench.SHAPE[2] * bench.SHAPE[3]
+    assert bench.input_reads(A, A.make_desc(A.UNIFORM, 8, n, m)) == 1            # held pass
+    assert bench.input_reads(A, A.make_desc(A.UNIFORM, 8, 4, 65536)) == 2
+    assert bench.input_reads(A, A.make_desc(A.UNIFORM, 8, n, m, channels=256)) == 2
+    assert bench.input_reads(A, A.make_desc(A.UNIFORM, 8, n, m, rounding=A.ROUND_STOCHASTIC)) == 2
+    assert bench.input_reads(A, A.make_desc(A.MBQ, 4, n, m, t=1)) == 1
+
+
 def test_more_than_one_gpu_is_refused_with_a_message():
     r = subprocess.run([sys.executable, os.path.join(ROOT, "bench.py"), "--gpus", "2"], capture_output=True, text=True,
                        cwd=ROOT, timeout=120)
