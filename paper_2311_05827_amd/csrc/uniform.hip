@@ -147,11 +147,13 @@ constexpr int kRangeStraddling = 5;  // segments longer than a vector but not wh
 // A small tensor has too few tiles to fill the chip: it is compressed one element at a time, each channel
 // divided out, and decompressed one vector per thread.  Measured at 8 K to 8 M values, segments of 9, 49,
 // 201 and 1063 (us):
-//   compress, single elements / vectors, float32: 0.25 M values 13.1 / 14.4 (segments of 49), 0.5 M
-//   17.6 / 17.0, 0.75 M 22.4 / 17.1; bfloat16: 0.5 M 17.7 / 18.7, 0.75 M 22.3 / 23.1, 1 M 27.2 / 24.4;
+//   compress (whole call), single elements / vectors, float32: 1 M values 9.9 / 10.8 (16 rows, segments of
+//   201), 1.5 M 11.1 / 11.1, 2 M 12.1 / 11.3, 4 M 20.6 / 13.7; one row, segments of 1467: 1 M 13.4 / 14.6,
+//   1.5 M 16.7 / 16.4; bfloat16: 1.5 M 10.1 / 10.8, 2 M 11.0 / 11.0, 3 M 12.5 / 11.2;
 //   decompress, single elements / a vector per thread / tiles, float32: 64 K 2.1 / 2.1 / 3.4, 1 M
 //   3.7 / 2.8 / 3.8, 2 M 5.8 / 4.0 / 4.2, 3 M 7.5 / 5.2 / 4.9; bfloat16: 2 M 5.3 / 3.0 / 3.4, 4 M 8.3 / 4.2 / 4.0.
-constexpr int64_t kStraddleBytes = int64_t(2) << 20;        // of input, from which the compressor takes vectors
+template <typename T>
+constexpr int64_t kStraddleValues = sizeof(T) == 4 ? int64_t(3) << 19 : int64_t(1) << 21;  // from which the compressor takes vectors
 constexpr int64_t kStraddleTiledValues = int64_t(5) << 19;  // from which the decoder takes tiles
 // Position units of a vector.
 template <int MODE, int VEC>
@@ -1676,7 +1678,8 @@ UPlan make_uplan(const accept_desc& d) {
     // channels-last (one element per segment) with rows of whole vectors: the quantizer's fast
     // path with one range per element
     p.per_element = p.seg_len == 1 && d.m % p.vec == 0;
-    p.straddling = p.seg_len > p.vec && p.seg_len % p.vec != 0 && p.N * (p.vec == 8 ? 2 : 4) >= kStraddleBytes;
+    p.straddling = p.seg_len > p.vec && p.seg_len % p.vec != 0 &&
+                   p.N >= (p.vec == 8 ? kStraddleValues<bf16_t> : kStraddleValues<float>);
     p.fast = (p.seg_len % p.vec == 0) || p.per_element || p.straddling;
     // column pass: threads own vectors of columns when every row keeps them aligned, else columns
     const int64_t ncv = (d.m % p.vec == 0) ? d.m / p.vec : d.m;

@@ -268,11 +268,11 @@ def test_segments_that_are_not_whole_vectors(A, seg):
         run_case(A, x, 3, 64, 5376 * seg, channels=5376, tag="straddling, many tiles")
 
 
-@pytest.mark.parametrize("values,bf16", [(1 << 19, False), (1 << 20, True), (5 << 19, False), (5 << 19, True)])
+@pytest.mark.parametrize("values,bf16", [(3 << 19, False), (1 << 21, True), (5 << 19, False), (5 << 19, True)])
 @pytest.mark.parametrize("seg", [9, 201])
 def test_straddling_segments_by_size(A, seg, values, bf16):
-    """Both sides of the sizes from which such a tensor is compressed in vectors (2 MiB) and
-    decompressed in tiles (2621440 values)."""
+    """Both sides of the sizes from which such a tensor is compressed in vectors (1572864 and
+    2097152 values) and decompressed in tiles (2621440 values)."""
     row = 41 * seg
     for n in (values // row, values // row + 1):
         assert (n * row >= values) == (n != values // row)
