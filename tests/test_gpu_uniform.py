@@ -303,6 +303,17 @@ def test_channels_last_range(A, n, C):
         run_case(A, x, k, n, C, channels=C, in_bf16=bf16, out_bf16=bf16, tag="channels-last")
 
 
+@pytest.mark.parametrize("rows", [1, 15, 16, 17, 4 * 8192 - 1, 16 * 8192 - 1, 16 * 8192, 16 * 8192 + 1, 21 * 8192 + 5])
+def test_single_columns_by_rows(A, rows):
+    """Rows of 9 channels, which no 16-byte vector divides: a thread's share of the rows below, at and
+    above the 16 and 4 that it takes at a time."""
+    x = per_channel_input(rows, 9, 1, 460)
+    x[rows - 1, 8, 0] = 100.0
+    x[0, 0, 0] = -90.0
+    for k, bf16 in ((4, False), (7, True)):
+        run_case(A, x, k, rows, 9, channels=9, in_bf16=bf16, out_bf16=bf16, tag="single columns")
+
+
 # One range, nearest rounding, 48 (bfloat16: 72) to 256 MiB: the end of the tensor is kept on the chip between the
 # range and the quantizer.  256 workgroups, units of 16384 elements; per workgroup 7 (bfloat16: 12)
 # units in registers, 2 (4) in local memory, the rest read twice.
