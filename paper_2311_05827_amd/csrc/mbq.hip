@@ -1656,7 +1656,8 @@ __global__ __launch_bounds__(kFinalizeBlock) void mbq_init_finalize_kernel(const
 // each, where single columns all go at once.  Counted in columns of a row group, measured at 16 K to 9 M
 // values, 4 to 15533 rows, both types (us, single columns / vectors):
 //   decoder: 23 x 86957 4.4 / 4.8, 16 x 187501 5.1 / 5.0, 64 x 62501 6.2 / 5.4, 15 x 390403 9.0 / 7.2;
-//   encoder, complete row groups only: 64 x 7813 9.2 / 9.1, 64 x 15625 9.4 / 9.3, 64 x 23437 12.1 / 10.6;
+//   encoder, complete row groups only: 64 x 7813 9.2 / 9.1, 64 x 15625 9.4 / 9.3, 64 x 23437 12.1 / 10.6
+//   (k = 1, bfloat16: 64 x 17501 7.6 / 8.5, 64 x 37501 8.8 / 8.8, 64 x 50001 9.5 / 8.7);
 //   encoder, complete and partial: 23 x 65217 12.9 / 14.0, 300 x 10001 14.8 / 14.2, 23 x 173913 14.1 / 13.0;
 //   encoder, partial only: 4 x 4001 9.4 / 9.1, 4 x 1000001 18.7 / 12.3.
 constexpr int64_t kRaggedColumns = int64_t(3) << 17;
@@ -1666,7 +1667,7 @@ int vec_for(int dtype, int64_t n, int64_t m, int bits, bool encode) {
   if (m % v == 0) return v;
   if (bits > 4 || m < v * kWave) return 1;
   if (encode && n < 8) return v;
-  return (n + 7) / 8 * m >= (encode && n % 8 == 0 ? kRaggedColumnsComplete : kRaggedColumns) ? v : 1;
+  return (n + 7) / 8 * m >= (encode && n % 8 == 0 && bits > 1 ? kRaggedColumnsComplete : kRaggedColumns) ? v : 1;
 }
 
 int grid_for(int64_t items, int grid_max) {
