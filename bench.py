@@ -115,7 +115,8 @@ def main():
                          "as many written per copy): the reference for scaling rocprofv3's FETCH_SIZE / WRITE_SIZE")
     ap.add_argument("--calls", default=None, metavar="CFG:S:K:C:DTYPE[,...]",
                     help="only run compress + decompress of the named cells three times each, cold, e.g. "
-                         "cfg3_act:M:3:0:f32,cfg4_grad:U:8:256:f32 (for rocprofv3 counter runs per configuration)")
+                         "cfg3_act:M:3:0:f32,cfg4_grad:U:8:256:f32 (Us: stochastic rounding; for rocprofv3 counter "
+                         "runs per configuration)")
     args = ap.parse_args()
     if args.gpus != 1:
         log("bench.py: this build runs on one GPU only (the codec has no multi-GPU path); use --gpus 1")
@@ -154,8 +155,9 @@ def main():
             x = torch.from_numpy(x_np.reshape(-1)).to(dev)
             x = x.to(torch.bfloat16) if bf else x
             tcode = A.BF16 if bf else A.F32
-            if scheme == "U":
-                d = A.make_desc(A.UNIFORM, k, cn, cm, channels=C, in_dtype=tcode, out_dtype=tcode)
+            if scheme[0] == "U":
+                d = A.make_desc(A.UNIFORM, k, cn, cm, channels=C, in_dtype=tcode, out_dtype=tcode,
+                                rounding=A.ROUND_STOCHASTIC if scheme == "Us" else A.ROUND_NEAREST_EVEN, seed=7)
                 alpha = None
             else:
                 d = A.make_desc(A.MBQ, k, cn, cm, t=1, in_dtype=tcode, out_dtype=tcode)
