@@ -284,9 +284,9 @@ def test_header_of_values_that_differ_much(A, k, kind, bf16):
 @pytest.mark.parametrize("bf16", [False, True])
 @pytest.mark.parametrize("n", [1, 7, 8, 9, 23])
 def test_rows_at_any_alignment(A, n, bf16):
-    """Rows that are not whole 16-byte vectors: vectors at any alignment, the last columns one by
-    one, from the narrowest row that goes this way (64 vectors) on, and just below it; complete
-    and partial row groups."""
+    """Rows that are not whole 16-byte vectors, from the narrowest that can go in vectors (64 of them) on,
+    and just below it; complete and partial row groups.  With fewer than 8 rows the encoder takes
+    vectors at any alignment here; the sizes from which it does with more stand in the next test."""
     vec = 8 if bf16 else 4
     for i, m in enumerate([64 * vec - 1, 64 * vec, 64 * vec + 1, 65 * vec - 1, 1024 + 3, 128 * vec + 2, 40 * 64 * vec + vec - 1]):
         k = 1 + (i + n) % 4
