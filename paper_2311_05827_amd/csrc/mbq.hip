@@ -1334,7 +1334,7 @@ __global__ __launch_bounds__(kBlock) void mbq_decode_kernel(const uint8_t* __res
           }
           f[c] = lut[pat];
         }
-        if constexpr (NC > 1 && RAGGED) store16_stream_any(dst + (row0 + r) * m, narrow(f));
+        if constexpr (NC > 1 && RAGGED) store16_any(dst + (row0 + r) * m, narrow(f));
         else if constexpr (NC > 1) store_vec(dst + (row0 + r) * m, f);
         else store_one(dst + (row0 + r) * m, f[0]);
       }
