@@ -1111,41 +1111,57 @@ __global__ __launch_bounds__(kEncBlock) void mbq_encode_kernel(const T* __restri
   const int64_t stride = int64_t(gridDim.x) * kEncBlock;
   const int64_t gtid = int64_t(blockIdx.x) * kEncBlock + tid;
   const bool stream = n_wave_items != 0u;  // else: a geometry too narrow for wave-items
-  if (stream && maxcnt == 1) {
-    encode_stream<T, K, VEC, RAGGED, 1>(tb, x, payload, uint64_t(m), ipg, wpg, q, cur, nxt, ca, fr, st);
-  } else if (stream && maxcnt == 2 && K <= 4 && !BY_VALUE) {
-    if constexpr (!BY_VALUE)
-      encode_stream<T, K, VEC, RAGGED, 2>(tb, x, payload, uint64_t(m), ipg, wpg, q, cur, nxt, ca, fr, st);
+  auto complete_groups = [&] {
+    if (stream && maxcnt == 1) {
+      encode_stream<T, K, VEC, RAGGED, 1>(tb, x, payload, uint64_t(m), ipg, wpg, q, cur, nxt, ca, fr, st);
+    } else if (stream && maxcnt == 2 && K <= 4 && !BY_VALUE) {
+      if constexpr (!BY_VALUE)
+        encode_stream<T, K, VEC, RAGGED, 2>(tb, x, payload, uint64_t(m), ipg, wpg, q, cur, nxt, ca, fr, st);
+    } else {
+      // several thresholds share a bucket (levels closer than a bucket's width), or a very narrow
+      // tensor: rare.  One column per thread keeps this path's register needs out of the kernel's
+      // budget.
+      const int64_t cols_full = (n / 8) * m;
+      for (int64_t s = gtid; s < cols_full; s += stride) {
+        const int64_t g = s / m;
+        encode_column<T, K>(tb, x, payload, n, m, g, s - g * m, maxcnt, st);
+      }
+    }
+  };
+  auto other_parts = [&] {
+    // the up to VEC - 1 columns of the complete row groups that no vector covers
+    if (RAGGED && stream && maxcnt <= (K <= 4 && !BY_VALUE ? 2 : 1)) {
+      const int64_t j0 = int64_t(ipg) * VEC, rem = m - j0;
+      for (int64_t s = gtid; s < (n / 8) * rem; s += stride) {
+        const int64_t g = s / rem;
+        encode_column<T, K>(tb, x, payload, n, m, g, j0 + s - g * rem, maxcnt, st);
+      }
+    }
+    // the last, partial row group: wave-items dealt to the workgroups first and to their wavefronts
+    // second; one column per thread where rows are too narrow for them, or levels too close
+    int64_t col0 = 0;  // columns from here on are left
+    if (n % 8 != 0 && wide && maxcnt == 1) {
+      const uint32_t wave = uint32_t(__builtin_amdgcn_readfirstlane(tid / kWave));
+      encode_partial<T, K, VEC, RAGGED, 1>(tb, x, payload, n, m, ipg, wpg, maxcnt, wave * gridDim.x + blockIdx.x,
+                                           gridDim.x * uint32_t(kEncWaves), st);
+      col0 = int64_t(ipg) * VEC;
+    }
+    if (n % 8 != 0) {
+      for (int64_t j = col0 + gtid; j < m; j += stride)
+        encode_column<T, K>(tb, x, payload, n, m, n / 8, j, maxcnt, st);
+    }
+  };
+  // What the stream does not cover takes two or three trips to memory one after the other.  Before the
+  // stream (whose first rows are under way by then) they cost a few wavefronts items that others draw from
+  // the queue; behind it, 2 to 4 us at the end of the kernel.  Whole call, float32, k = 2, behind / before:
+  // 13113 x 1309 24.3 / 20.2 us, 3000 x 8193 27.0 / 23.1, 8315 x 1457 22.1 / 19.2.  Not so where values are
+  // looked up in a table of their own (bfloat16, k = 4, 8315 x 1457: 18.6 / 20.6).
+  if constexpr (BY_VALUE) {
+    complete_groups();
+    other_parts();
   } else {
-    // several thresholds share a bucket (levels closer than a bucket's width), or a very narrow
-    // tensor: rare.  One column per thread keeps this path's register needs out of the kernel's
-    // budget.
-    const int64_t cols_full = (n / 8) * m;
-    for (int64_t s = gtid; s < cols_full; s += stride) {
-      const int64_t g = s / m;
-      encode_column<T, K>(tb, x, payload, n, m, g, s - g * m, maxcnt, st);
-    }
-  }
-  // the last, partial row group: wave-items dealt to the workgroups first and to their wavefronts
-  // second; one column per thread where rows are too narrow for them, or levels too close
-  int64_t col0 = 0;  // columns from here on are left
-  if (n % 8 != 0 && wide && maxcnt == 1) {
-    const uint32_t wave = uint32_t(__builtin_amdgcn_readfirstlane(tid / kWave));
-    encode_partial<T, K, VEC, RAGGED, 1>(tb, x, payload, n, m, ipg, wpg, maxcnt, wave * gridDim.x + blockIdx.x,
-                                         gridDim.x * uint32_t(kEncWaves), st);
-    col0 = int64_t(ipg) * VEC;
-  }
-  if (n % 8 != 0) {
-    for (int64_t j = col0 + gtid; j < m; j += stride)
-      encode_column<T, K>(tb, x, payload, n, m, n / 8, j, maxcnt, st);
-  }
-  // the up to VEC - 1 columns of the complete row groups that no vector covers
-  if (RAGGED && stream && maxcnt <= (K <= 4 && !BY_VALUE ? 2 : 1)) {
-    const int64_t j0 = int64_t(ipg) * VEC, rem = m - j0;
-    for (int64_t s = gtid; s < (n / 8) * rem; s += stride) {
-      const int64_t g = s / rem;
-      encode_column<T, K>(tb, x, payload, n, m, g, j0 + s - g * rem, maxcnt, st);
-    }
+    other_parts();
+    complete_groups();
   }
   store_record<K>(st, call, red);
 }
@@ -1651,23 +1667,37 @@ __global__ __launch_bounds__(kFinalizeBlock) void mbq_init_finalize_kernel(const
 
 // ============================================================================= host side
 // Elements per vector: 16 bytes' worth; for the widths in use (k <= 4) at any alignment, where rows
-// are long enough for wave-items and the tensor is large enough: the columns that no vector covers, and
-// in the encoder the partial row group, come one after the other behind the vectors, a trip to memory
-// each, where single columns all go at once.  Counted in columns of a row group, measured at 16 K to 9 M
-// values, 4 to 15533 rows, both types (us, single columns / vectors):
-//   decoder: 23 x 86957 4.4 / 4.8, 16 x 187501 5.1 / 5.0, 64 x 62501 6.2 / 5.4, 15 x 390403 9.0 / 7.2;
+// are long enough for wave-items and the tensor is large enough (ragged_columns).
+//
+// How large, in columns of all row groups: the columns that no vector covers, and in the encoder the partial
+// row group, take trips to memory of their own, where single columns all go at once; narrow rows have
+// more such columns, and the ends of their rows are written in parts.  Measured at 16 K to 54 M values, 4
+// to 101148 rows (us, single columns / vectors):
+//   decoder: 23 x 86957 4.4 / 4.8, 64 x 62501 6.2 / 5.4, 15 x 390403 9.0 / 7.2; float32 rows below 2048:
+//     8315 x 1457 11.7 / 12.7, 10403 x 769 8.5 / 9.0, 16691 x 1519 21.2 / 20.0, 101148 x 535 42 / 40;
 //   encoder, complete row groups only: 64 x 7813 9.2 / 9.1, 64 x 15625 9.4 / 9.3, 64 x 23437 12.1 / 10.6
-//   (k = 1, bfloat16: 64 x 17501 7.6 / 8.5, 64 x 37501 8.8 / 8.8, 64 x 50001 9.5 / 8.7);
+//     (k = 1, bfloat16: 64 x 17501 7.6 / 8.5, 64 x 37501 8.8 / 8.8, 64 x 50001 9.5 / 8.7);
 //   encoder, complete and partial: 23 x 65217 12.9 / 14.0, 300 x 10001 14.8 / 14.2, 23 x 173913 14.1 / 13.0;
-//   encoder, partial only: 4 x 4001 9.4 / 9.1, 4 x 1000001 18.7 / 12.3.
-constexpr int64_t kRaggedColumns = int64_t(3) << 17;
-constexpr int64_t kRaggedColumnsComplete = int64_t(1) << 17;
+//     float32 rows below 4096: 2614 x 1921 13.1 / 14.2, 10403 x 769 16.6 / 16.4, 13113 x 1309 24.5 / 20.2;
+//   encoder, partial only: 4 x 4001 9.4 / 9.1, 4 x 1000001 18.7 / 12.3;
+//   encoder, float32 rows that leave a quarter or more of their wave-items' lanes idle: 55297 x 297
+//     28.5 / 30.9, 19311 x 349 15.3 / 15.9.
+int64_t ragged_columns(int dtype, int64_t n, int64_t m, int bits, bool encode) {
+  const bool f32 = dtype == ACCEPT_F32;
+  if (!encode) return f32 && m < 2048 ? int64_t(1) << 21 : int64_t(3) << 17;
+  if (n < 8) return 0;
+  if (f32) {
+    const int64_t ipg = m / Elem<float>::VEC, lanes = (ipg + kWave - 1) / kWave * kWave;
+    if (4 * ipg < 3 * lanes) return INT64_MAX;
+  }
+  if (n % 8 == 0 && bits > 1) return int64_t(1) << 17;
+  return f32 && m < 4096 ? int64_t(1) << 20 : int64_t(3) << 17;
+}
 int vec_for(int dtype, int64_t n, int64_t m, int bits, bool encode) {
   const int v = dtype == ACCEPT_BF16 ? 8 : 4;
   if (m % v == 0) return v;
   if (bits > 4 || m < v * kWave) return 1;
-  if (encode && n < 8) return v;
-  return (n + 7) / 8 * m >= (encode && n % 8 == 0 && bits > 1 ? kRaggedColumnsComplete : kRaggedColumns) ? v : 1;
+  return (n + 7) / 8 * m >= ragged_columns(dtype, n, m, bits, encode) ? v : 1;
 }
 
 int grid_for(int64_t items, int grid_max) {

@@ -307,10 +307,12 @@ def test_rows_at_any_alignment(A, n, bf16):
 
 
 @pytest.mark.parametrize("bf16", [False, True])
-@pytest.mark.parametrize("n,m", [(16, 65535), (16, 65539), (8 * 511, 257 + 256), (9, 196607), (9, 196613), (8 * 768 + 5, 513)])
+@pytest.mark.parametrize("n,m", [(16, 65535), (16, 65539), (8 * 511, 257 + 256), (9, 196607), (9, 196613), (8 * 768 + 5, 513),
+                                 (8 * 255 + 5, 4103), (8 * 256 + 5, 4103), (8 * 4100 + 3, 513)])
 def test_rows_at_any_alignment_large(A, n, m, bf16):
-    """Both sides of the sizes from which complete row groups of such rows go in vectors (131072 columns
-    of a row group without a partial group, 393216 with one and in the decoder)."""
+    """Both sides of the sizes from which complete row groups of such rows go in vectors: in columns of all
+    row groups 131072 without a partial group, 393216 with one and in the decoder, more for narrow rows of
+    float32."""
     torch = torch_mod()
     x = si.make_shape("student_t3", (n, m), 7600 + n % 100)
     run_case(A, x, 3, n, m, t=2, in_bf16=bf16, out_bf16=bf16, tag="ragged large")
