@@ -1678,7 +1678,8 @@ __global__ __launch_bounds__(kFinalizeBlock) void mbq_init_finalize_kernel(const
 //   encoder, complete row groups only: 64 x 7813 9.2 / 9.1, 64 x 15625 9.4 / 9.3, 64 x 23437 12.1 / 10.6
 //     (k = 1, bfloat16: 64 x 17501 7.6 / 8.5, 64 x 37501 8.8 / 8.8, 64 x 50001 9.5 / 8.7);
 //   encoder, complete and partial: 23 x 65217 12.9 / 14.0, 300 x 10001 14.8 / 14.2, 23 x 173913 14.1 / 13.0;
-//     float32 rows below 4096: 2614 x 1921 13.1 / 14.2, 10403 x 769 16.6 / 16.4, 13113 x 1309 24.5 / 20.2;
+//     float32 rows below 4096, k = 2: 2614 x 1921 13.1 / 14.2, 17950 x 509 16.3 / 17.4, 8315 x 1457
+//     19.6 / 19.2, 13113 x 1309 24.5 / 20.2;
 //   encoder, partial only: 4 x 4001 9.4 / 9.1, 4 x 1000001 18.7 / 12.3;
 //   encoder, float32 rows that leave a quarter or more of their wave-items' lanes idle: 55297 x 297
 //     28.5 / 30.9, 19311 x 349 15.3 / 15.9.
@@ -1691,7 +1692,7 @@ int64_t ragged_columns(int dtype, int64_t n, int64_t m, int bits, bool encode) {
     if (4 * ipg < 3 * lanes) return INT64_MAX;
   }
   if (n % 8 == 0 && bits > 1) return int64_t(1) << 17;
-  return f32 && m < 4096 ? int64_t(1) << 20 : int64_t(3) << 17;
+  return f32 && m < 4096 ? int64_t(3) << 19 : int64_t(3) << 17;
 }
 int vec_for(int dtype, int64_t n, int64_t m, int bits, bool encode) {
   const int v = dtype == ACCEPT_BF16 ? 8 : 4;
