@@ -50,7 +50,7 @@ def alg_bytes(kernel, N, n, m, k, b_in=4, b_out=4):
     """Algorithmic HBM bytes one launch of a kernel must move."""
     if kernel == "range":
         return N * b_in
-    if kernel in ("quantize_pack", "quantize_held"):  # held: range and codes from one kernel, priced as one read
+    if kernel in ("quantize_pack", "quantize_held", "quantize_channels"):  # held: range and codes from one kernel, priced as one read
         return N * b_in + (N * k + 7) // 8 + 4
     if kernel == "unpack_dequant":
         return (N * k + 7) // 8 + 4 + N * b_out
@@ -63,7 +63,7 @@ def alg_bytes(kernel, N, n, m, k, b_in=4, b_out=4):
 
 def input_reads(A, desc):
     """How often accept_compress reads its input, by the stages it launches: twice where a range pass
-    comes before the quantizer, once for scheme M and for the held pass (which keeps the end of the
+    comes before the quantizer, once for scheme M, where channels stay on the chip, and for the held pass (which keeps the end of the
     tensor on the chip and reads only what does not fit a second time: not counted here)."""
     return 2 if A.accept_stage_name(desc, 0, 0) == "range" else 1
 

@@ -123,7 +123,8 @@ accept_status accept_workspace_size(const accept_desc* desc, size_t* bytes);
  * aligned) and payload_dev (16-byte aligned), sizes as accept_packed_size reports.
  *
  *   UNIFORM: range pass, then fused quantize + pack (one range and 48, bfloat16 72, to 256 MiB of input: both in
- *     one kernel that keeps part of the tensor on the chip).  Code i occupies payload bits
+ *     one kernel that keeps part of the tensor on the chip; a range per channel, segments of whole 32s and a tensor
+ *     that fits on the chip: one kernel altogether).  Code i occupies payload bits
  *     [ik, (i+1)k), most significant bit first, bit b of the stream being bit 7-(b mod 8)
  *     of byte b/8; codes are q + 2^(k-1) for k < 8 and the two's-complement byte for
  *     k = 8; unused bits of the last byte are 0.  q = clamp(round(x * fl(L/c)), -2^(k-1), L),
@@ -139,8 +140,8 @@ accept_status accept_workspace_size(const accept_desc* desc, size_t* bytes);
  *
  * workspace_dev: accept_workspace_size bytes, 256-byte aligned.  Zero-fill it once after
  * allocating it (hipMemset); from then on the library keeps it in the state its next call
- * needs (its first 16 KiB hold counters that every call leaves at zero; the rest is
- * scratch whose contents do not matter), so one workspace serves any number of calls and
+ * needs (its first 16 KiB hold counters and mailboxes that the library keeps from call to call;
+ * the rest is scratch whose contents do not matter), so one workspace serves any number of calls and
  * descriptors of both schemes, one call at a time: calls that share a workspace must not
  * overlap.
  * hip_stream: a hipStream_t (null = the default stream).
@@ -170,7 +171,7 @@ accept_status accept_decompress(const accept_desc* desc, const void* header_dev,
  * UNIFORM descriptor fits; per-channel ones fit up to about 250,000 (row, channel) segments).
  * All calls on one GPU share that GPU's array: two calls that overlap in time on one GPU
  * (different streams or threads) race; calls on one stream are safe.  The array starts
- * zero-filled when the library is loaded and every kernel leaves its counters at zero, which
+ * zero-filled when the library is loaded and every kernel leaves it as its next call needs it, which
  * is all the kernels rely on, so no clearing is enqueued.
  */
 enum { ACCEPT_NOALLOC_SCRATCH_BYTES = 1 << 20 };

@@ -48,8 +48,8 @@ inline void mark(StageTimer* t, hipStream_t s) {
 // Every workspace starts with a control block that the library keeps between calls: words that
 // must be zero when a call starts and are put back to zero before it ends (the work counters of
 // the multi-bit encoder in its first half, the mailboxes of the uniform scheme's held pass in its
-// second).  The caller zero-fills the workspace once; no kernel of either scheme writes anything
-// else there.
+// second), and, behind those, mailboxes whose words bear the number of the call they belong to.  The
+// caller zero-fills the workspace once; no kernel of either scheme writes anything else there.
 constexpr size_t kCtrlBytes = 16384;
 constexpr size_t kMailOffset = 8192;
 
@@ -75,6 +75,7 @@ struct UPlan {
   int64_t held_units;  // held: whole units (see kUnitElems) of the tensor
   int held_lds;        // held: units per workgroup that stay in local memory (the others in registers)
   int64_t held_first;  // held: units [held_first, held_units) are kept, the others are read again
+  uint32_t chan_per;   // per channel: groups of 32 elements per workgroup of the pass that keeps the tensor on the chip; 0: not taken
   size_t off_rtab;     // byte offset of the per-channel reciprocal table in the workspace
   size_t bytes;        // workspace bytes
 };
@@ -85,6 +86,7 @@ UPlan make_uplan(const accept_desc& d);
 int compute_units();
 constexpr int kHeldGrid = 256;
 inline bool held_runs(const UPlan& p, int units) { return p.held && units >= kHeldGrid; }
+inline bool channels_run(const UPlan& p, int units) { return p.chan_per != 0 && units >= kHeldGrid; }
 
 // held_polls: how often a workgroup of the held pass looks for the others' maxima before it gives up
 // (kHeldPolls; fewer only where a test wants the case that it gives up).  64 looks take about 50 us.  Alone

@@ -1046,6 +1046,299 @@ __global__ __launch_bounds__(kHeldBlock, 2) void quantize_held_kernel(const T* _
   }
 }
 
+// U1, U1b, U2 and U3 of a tensor with one range per channel, in one kernel and with one read: the
+// tensor stays on the chip between the two steps.  The tensor's groups of 32 elements (k whole dwords
+// of payload each; segments are whole groups) are numbered channel after channel, row after row inside a
+// channel, and workgroup b has the groups b*per .. (b+1)*per - 1 of that order: most of its channels are
+// its own altogether, and at most two, its first and its last, it shares with neighbours.  For these it
+// leaves its maximum in a mailbox and looks for those of the others.  Workgroups are not sure to run at
+// the same time; one that has looked `polls` times in vain reads the whole channel itself.  So every
+// workgroup ends whatever else runs, with the same bits.
+//
+// A mailbox is one 64-bit word, value and the call's mark together, as in quantize_held_kernel.  Every
+// workgroup counts itself off once it has all its ranges; the one that is counted last empties the
+// mailboxes and the count.
+//
+// What bounds it: the read of the tensor (16 of 33 us at 103 MB of bfloat16, with the looking hidden behind
+// it), then the instructions that quantize and pack, two wavefronts on a SIMD, and the payload's stores
+// (38 MB there).  The places of a thread's vectors are stepped, not divided out, and only the loads and
+// stores need them: which channel a unit belongs to is known from scalars (per element, as at first, the
+// kernel took 42 us).  Streaming stores of the payload make a call alone 3 us faster and a decoder that
+// reads it next 8 us slower.  Beside other work on another stream, two or three kernels / this one (us):
+// matrix products 220 / 114 (100 x 8 x 12544 float32), small kernels 29.0 / 20.6 (64 x 100 x 3136 float32); 512 MB
+// copies without a pause 42 / 23 there, but 60 / 80 to 105 for the large one, whose workgroups need a compute
+// unit each.
+constexpr int kChanMaxLocal = 64;   // channels a workgroup may have a part of: at most 14 units of 512 groups, and
+                                    // two parts, of channels of at least 128 groups
+template <typename T>
+constexpr int kChanLdsUnits = sizeof(T) == 4 ? 1 : 3;
+// Place of a group of 32 elements: group inside its segment, batch row, and the group's number in the tensor.
+struct GroupPos {
+  uint32_t pos, row, at;
+};
+struct ChanHeldGeom {
+  uint32_t seg_groups, rows;  // groups of a segment, batch rows
+  uint32_t m_groups;          // groups of a row of the tensor
+  uint32_t total, per;        // groups of the tensor, and of a workgroup
+  GroupPos load_step;         // groups between two loads of a thread
+  GroupPos unit_step;         // groups of a unit
+  uint32_t next_row, next_channel;  // what a step past a segment's, and past a channel's, end adds to `at`
+  uint32_t shared;            // whether any channel lies in two workgroups
+};
+__device__ __forceinline__ GroupPos group_pos(const ChanHeldGeom& g, uint32_t q) {
+  GroupPos p;
+  const uint32_t seg = q / g.seg_groups;
+  p.pos = q - seg * g.seg_groups;
+  const uint32_t ch = seg / g.rows;
+  p.row = seg - ch * g.rows;
+  p.at = p.row * g.m_groups + ch * g.seg_groups + p.pos;
+  return p;
+}
+__device__ __forceinline__ void group_advance(const ChanHeldGeom& g, GroupPos& p, const GroupPos& st) {
+  p.pos += st.pos;
+  p.row += st.row;
+  p.at += st.at;
+  if (p.pos >= g.seg_groups) { p.pos -= g.seg_groups; p.row += 1; p.at += g.next_row; }
+  if (p.row >= g.rows) { p.row -= g.rows; p.at += g.next_channel; }
+}
+
+// What the workgroups of calls with one workspace leave each other, in its control block.  A call's tag is one
+// more than the number of calls before it, of which every workgroup has a word of its own: it reads the
+// word when it starts and raises it when it ends (and those of the workgroups that this call does not have),
+// so all of them agree.  So nothing has to be emptied: a value of an earlier call bears an earlier tag.
+// (Counting the workgroups off on one counter, and the last one emptying everything, cost small tensors
+// 1.5 us.)
+struct ChanMail {
+  uint64_t first[kHeldGrid], last[kHeldGrid];  // tag and the workgroup's maximum of its first, its last channel
+  uint32_t calls[kHeldGrid];
+};
+constexpr size_t kChanMailOffset = kMailOffset + kHeldGrid * sizeof(uint64_t);
+static_assert(kChanMailOffset + sizeof(ChanMail) <= kCtrlBytes, "the control block holds them");
+
+template <typename T, int K, int SLOTS, int LDS_UNITS>
+__global__ __launch_bounds__(kHeldBlock, 2) void quantize_channels_kernel(const T* __restrict__ x,
+                                                                          uint32_t* __restrict__ payload32,
+                                                                          float* __restrict__ header,
+                                                                          ChanMail* __restrict__ mail, ChanHeldGeom g,
+                                                                          int polls) {
+  constexpr int VEC = Elem<T>::VEC;
+  constexpr int GV = 32 / VEC;                            // vectors of a group
+  constexpr int LOADS = kUnitElems / (kHeldBlock * VEC);  // vectors per thread and unit
+  static_assert(LOADS * (kHeldBlock / GV) == kHeldBlock && kUnitElems == 32 * kHeldBlock, "a unit is a group per thread");
+  static_assert(LDS_UNITS <= SLOTS, "units kept in local memory pass through the first slots");
+  constexpr int QPV = VEC / 4;
+  struct Local {
+    uint4 kept[LDS_UNITS > 0 ? LDS_UNITS : 1][LDS_UNITS > 0 ? LOADS : 1][LDS_UNITS > 0 ? kHeldBlock : 1];
+    uint32_t pieces[2][kUnitElems / 4];
+    uint32_t top[kChanMaxLocal];  // largest magnitude of the workgroup's channels, as bits
+    float r[kChanMaxLocal];
+    int up[2];
+  };
+  static_assert(sizeof(Local) <= 160 * 1024, "local memory of a compute unit");
+  __shared__ __attribute__((aligned(16))) Local local;
+  const int tid = threadIdx.x;
+  const int lane = tid & (kWave - 1), wave = __builtin_amdgcn_readfirstlane(tid / kWave);
+
+  const uint32_t q0 = blockIdx.x * g.per;  // below total (host)
+  const uint32_t count = g.total - q0 < g.per ? g.total - q0 : g.per;
+  const uint32_t units = (count + kHeldBlock - 1) / kHeldBlock;
+  const uint32_t tag = mail->calls[blockIdx.x] + 1u;
+  const uint32_t mine = uint32_t(tid) / GV;  // the thread's first vector is in this group of the workgroup's
+  uint4 kept[SLOTS][LOADS];
+  // The loads of the units in ordinal order, one after the other; behind the workgroup's last group its
+  // first vector stands in.  (The place passes through an empty asm at every unit, or the compiler forms
+  // the addresses of all of them first.)
+  auto fresh = [](GroupPos& p) { asm volatile("" : "+v"(p.pos), "+v"(p.row), "+v"(p.at)); };
+  GroupPos from = group_pos(g, q0 + mine);
+  const uint32_t first_at = group_pos(g, q0).at;
+  auto ask = [&](uint32_t ordinal, uint4 (&raw)[LOADS]) {
+    fresh(from);
+#pragma unroll
+    for (int u = 0; u < LOADS; ++u) {
+      const uint32_t at = ordinal * kHeldBlock + uint32_t(u * (kHeldBlock / GV)) + mine < count ? from.at : first_at;
+      raw[u] = load16_stream(reinterpret_cast<const char*>(x) + (at * uint32_t(GV) + uint32_t(tid) % GV) * 16u);
+      group_advance(g, from, g.load_step);
+    }
+  };
+#pragma unroll
+  for (int j = 0; j < SLOTS; ++j) ask(j, kept[j]);
+  const uint32_t per_channel = g.rows * g.seg_groups;
+  const uint32_t ch_lo = q0 / per_channel;
+  const uint32_t ch_hi = (q0 + count - 1) / per_channel;
+  const uint32_t nloc = ch_hi - ch_lo + 1;
+  if (tid < kChanMaxLocal) local.top[tid] = 0u;
+  if (tid < 2) local.up[tid] = 0;
+  __syncthreads();
+  // The workgroup's channels, the first one's index 0; channel i ends before group end_of(i).  Units inside
+  // one channel, which are most, know it from scalars; the others split at the ends inside them.
+  const uint32_t first_end = (ch_lo + 1) * per_channel - q0;
+  float c = 0.0f;             // of the channel at hand
+  uint32_t chan = 0, end = first_end < count ? first_end : count;
+  auto hand_over = [&] {
+    const float t = wave_max(c);
+    if (lane == 0) atomicMax(&local.top[chan], f32_as_u32(t));
+    c = 0.0f;
+  };
+  auto look = [&](uint32_t ordinal, const uint4 (&raw)[LOADS]) {
+    const uint32_t g0 = ordinal * kHeldBlock;
+    auto largest = [&](int u) {
+      float f[VEC];
+      widen(raw[u], f);
+      float v = 0.0f;
+#pragma unroll
+      for (int e = 0; e < VEC; ++e) v = fmaxf(v, fabsf(f[e]));
+      return v;
+    };
+    if (g0 + kHeldBlock <= end) {
+#pragma unroll
+      for (int u = 0; u < LOADS; ++u) c = fmaxf(c, largest(u));
+    } else {
+      uint32_t begin = g0;
+      while (begin < g0 + kHeldBlock && begin < count) {  // the same in all lanes
+#pragma unroll
+        for (int u = 0; u < LOADS; ++u) {
+          const uint32_t grp = g0 + uint32_t(u * (kHeldBlock / GV)) + mine;
+          c = fmaxf(c, grp >= begin && grp < end ? largest(u) : 0.0f);
+        }
+        if (end > g0 + kHeldBlock || end == count) break;
+        hand_over();
+        begin = end;
+        ++chan;
+        end = end + per_channel < count ? end + per_channel : count;
+      }
+    }
+  };
+  if constexpr (LDS_UNITS > 0) {
+#pragma unroll
+    for (int j = 0; j < LDS_UNITS; ++j) {
+      look(j, kept[j]);
+#pragma unroll
+      for (int u = 0; u < LOADS; ++u) local.kept[j][u][tid] = kept[j][u];
+      __builtin_amdgcn_sched_barrier(0);
+      ask(SLOTS + j, kept[j]);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+  }
+#pragma unroll
+  for (int j = 0; j < SLOTS; ++j) look(LDS_UNITS + j, kept[(j + LDS_UNITS) % SLOTS]);
+  hand_over();
+  __syncthreads();
+
+  const bool starts_inside = q0 % per_channel != 0;           // the first channel began before
+  const bool ends_inside = (q0 + count) % per_channel != 0;   // the last one goes on behind
+  if (g.shared != 0) {
+    uint64_t* const mail_first = mail->first;
+    uint64_t* const mail_last = mail->last;
+    const bool one = ch_lo == ch_hi;
+    const bool watch_first = starts_inside || (one && ends_inside), watch_last = !one && ends_inside;
+    auto post = [&](uint64_t* box, uint32_t v) {
+      __hip_atomic_store(box, (uint64_t(tag) << 32) | v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    };
+    if (tid == 0 && watch_first) post(mail_first + blockIdx.x, local.top[0]);
+    if (tid == 0 && watch_last) post(mail_last + blockIdx.x, local.top[nloc - 1]);
+    __syncthreads();
+    // wavefront 0 watches the first channel's other workgroups, wavefront 1 the last one's
+    if ((wave == 0 && watch_first) || (wave == 1 && watch_last)) {
+      const uint32_t ch = wave == 0 ? ch_lo : ch_hi;
+      const uint32_t from_wg = ch * per_channel / g.per, to_wg = (ch * per_channel + per_channel - 1) / g.per;
+      const bool from_first = from_wg * g.per == ch * per_channel;  // it is the first channel of workgroup from_wg
+      uint32_t top = 0;
+      bool all = false;
+      for (int i = 0; i < polls; ++i) {
+        bool seen = true;
+        top = 0;  // (a look may have met values of earlier calls)
+        for (uint32_t w = from_wg + uint32_t(lane); w <= to_wg; w += kWave) {
+          const uint64_t* box = (w != from_wg || from_first ? mail_first : mail_last) + w;
+          const uint64_t v = __hip_atomic_load(box, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+          seen = seen && uint32_t(v >> 32) == tag;
+          top = max(top, uint32_t(v));
+        }
+        all = __ballot(!seen) == 0;
+        if (all) break;
+        __builtin_amdgcn_s_sleep(4);
+      }
+      const float t = wave_max(u32_as_f32(top));
+      if (lane == 0) {
+        if (all) local.top[ch - ch_lo] = f32_as_u32(t);
+        else local.up[wave] = 1;
+      }
+    }
+    __syncthreads();
+    for (int e = 0; e < 2; ++e) {
+      if (local.up[e] == 0) continue;  // the same in all threads
+      const uint32_t ch = e == 0 ? ch_lo : ch_hi;
+      float v = 0.0f;
+      const uint32_t seg_vecs = g.seg_groups * GV, vecs = g.rows * seg_vecs;
+      for (uint32_t i = tid; i < vecs; i += kHeldBlock) {
+        const uint32_t row = i / seg_vecs;
+        float f[VEC];
+        load_vec(x + (size_t(row) * g.m_groups + size_t(ch) * g.seg_groups) * 32 + size_t(i - row * seg_vecs) * VEC, f);
+#pragma unroll
+        for (int q = 0; q < VEC; ++q) v = fmaxf(v, fabsf(f[q]));
+      }
+      v = wave_max(v);
+      if (lane == 0) atomicMax(&local.top[ch - ch_lo], f32_as_u32(v));
+    }
+    __syncthreads();
+    if (tid < kHeldGrid && uint32_t(tid) % gridDim.x == blockIdx.x) mail->calls[tid] = tag;
+  }
+  if (tid < int(nloc)) {
+    float s, r;
+    scale_from_range(u32_as_f32(local.top[tid]), K, s, r);
+    local.r[tid] = r;
+    if (tid > 0 || !starts_inside) header[ch_lo + tid] = s;
+  }
+  __syncthreads();
+
+  GroupPos to = group_pos(g, q0 + uint32_t(tid));  // the group whose codes the thread writes
+  int buf_i = 0;
+  chan = 0;
+  end = first_end < count ? first_end : count;
+  float r_chan = local.r[0];
+  auto quantize_unit = [&](uint32_t ordinal, auto vec_of) {
+    uint32_t* buf = local.pieces[buf_i];
+    buf_i ^= 1;
+    const uint32_t g0 = ordinal * kHeldBlock;
+    auto vector = [&](int u, float r) {
+      uint4 raw = vec_of(u);
+      // (an empty asm: the values widened for the maximum would stay in registers from then to here)
+      asm volatile("" : "+v"(raw.x), "+v"(raw.y), "+v"(raw.z), "+v"(raw.w));
+      float f[VEC];
+      widen(raw, f);
+      const float rv[4] = {r, r, r, r};
+#pragma unroll
+      for (int h = 0; h < QPV; ++h) buf[(u * kHeldBlock + tid) * QPV + h] = quantize4<K, false>(&f[4 * h], rv, 0);
+    };
+    float r[LOADS];
+#pragma unroll
+    for (int u = 0; u < LOADS; ++u) r[u] = r_chan;
+    while (end < g0 + kHeldBlock && end < count) {  // the same in all lanes
+      r_chan = local.r[++chan];
+#pragma unroll
+      for (int u = 0; u < LOADS; ++u) r[u] = g0 + uint32_t(u * (kHeldBlock / GV)) + mine >= end ? r_chan : r[u];
+      end = end + per_channel < count ? end + per_channel : count;
+    }
+#pragma unroll
+    for (int u = 0; u < LOADS; ++u) vector(u, r[u]);
+    __syncthreads();  // double buffered: one barrier per unit
+    const uint4 a = *reinterpret_cast<const uint4*>(&buf[8 * tid]);
+    const uint4 b = *reinterpret_cast<const uint4*>(&buf[8 * tid + 4]);
+    const uint32_t P[8] = {a.x, a.y, a.z, a.w, b.x, b.y, b.z, b.w};
+    uint32_t out[K];
+    pack8<K>(P, out);
+    fresh(to);
+    if (g0 + uint32_t(tid) < count) store_dwords<K>(payload32 + size_t(to.at) * K, out);
+    group_advance(g, to, g.unit_step);
+  };
+  if constexpr (LDS_UNITS > 0) {
+    for (int q = 0; q < LDS_UNITS; ++q)
+      quantize_unit(q, [&](int u) { return local.kept[q][u][tid]; });
+  }
+#pragma unroll
+  for (int j = 0; j < SLOTS; ++j)
+    if (uint32_t(LDS_UNITS + j) < units) quantize_unit(LDS_UNITS + j, [&](int u) { return kept[(j + LDS_UNITS) % SLOTS][u]; });
+}
+
 // ====================================================================== dequantize (U4+U5)
 // Four consecutive codes starting at element index e0 (a multiple of 4): load the one or two
 // payload dwords that hold their 4k bits, view them as a big-endian 64-bit window, extract,
@@ -1459,14 +1752,107 @@ hipError_t launch_held(const accept_desc& d, const UPlan& p, const T* x, uint32_
   return hipGetLastError();
 }
 
+// Registers for the units of a workgroup: three sizes, so that small tensors do not carry the large ones' loads.
+template <typename T>
+struct ChanSlots;
+template <>
+struct ChanSlots<float> {
+  static constexpr int small = 2, middle = 4, large = 6;
+};
+template <>
+struct ChanSlots<bf16_t> {
+  static constexpr int small = 3, middle = 6, large = 11;
+};
+template <typename T>
+constexpr int64_t kChanMaxUnits = ChanSlots<T>::large + kChanLdsUnits<T>;
+
+// Groups of a workgroup of quantize_channels_kernel; 0: the tensor does not take it.  Segments have to be whole
+// groups, and the tensor has to fit on the chip.  Against range and quantize kernels (two, or three with one
+// that finishes the ranges between them; captured calls, us): 64 x 256 x 3136 bfloat16 k = 6 43.3 / 33.2, 32 x 256 x
+// 3136 float32 38.4 / 26.8, 16 x 512 x 1024 15.5 / 10.4, 8 x 32 x 12544 10.7 / 6.5, 130 x 30 x 256 bfloat16 27.6 / 6.2,
+// 64 x 5859 x 64 29.9 / 27.8.  Channels of fewer than 8192 elements are handed over often, which large tensors
+// pay for: 4 x 5859 x 1024 bfloat16 26.2 / 27.9, 4 x 2441 x 1024 15.6 / 13.8; float32 35.7 / 37.3, 19.1 / 18.0.
+constexpr int64_t kChanMinChannel = 4096;
+constexpr int64_t kChanManyValues = int64_t(10) << 20;  // beyond, channels have twice that at least
+// The fewest groups of a workgroup: 32 to 256 take the same time where channels are shared; fewer
+// workgroups then have fewer mailboxes to look through.
+constexpr int64_t kChanMinGroups = 128;
+template <typename T>
+uint32_t channel_groups(int64_t n, int64_t C, int64_t seg_len) {
+  const int64_t groups = n * C * seg_len / 32, most = kChanMaxUnits<T> * kHeldBlock;
+  if (seg_len % 32 != 0 || groups > most * kHeldGrid) return 0;
+  if (n * seg_len < (groups * 32 > kChanManyValues ? 2 : 1) * kChanMinChannel) return 0;
+  int64_t per = (groups + kHeldGrid - 1) / kHeldGrid;
+  if (per < kChanMinGroups) per = kChanMinGroups;
+  // Whole channels, if that is hardly more work for a workgroup: nothing is shared then, and nobody waits
+  // (8 x 61 x 1024 bfloat16: 5.5 -> 4.1 us).
+  const int64_t channel = n * seg_len / 32, whole = (per + channel - 1) / channel * channel;
+  if (whole <= kHeldBlock || whole * 8 <= per * 9) per = whole;
+  return uint32_t(per < most ? per : most);
+}
+
+template <typename T>
+hipError_t launch_channels(const accept_desc& d, const UPlan& p, const T* x, float* header, uint32_t* payload,
+                           ChanMail* mail, int polls, hipStream_t s) {
+  ChanHeldGeom g{};
+  g.seg_groups = uint32_t(p.seg_len / 32);
+  g.rows = uint32_t(d.n);
+  g.m_groups = uint32_t(p.m / 32);
+  g.total = uint32_t(p.N / 32);
+  g.per = p.chan_per;
+  auto step = [&](uint32_t groups) {
+    GroupPos st;
+    const uint32_t segs = groups / g.seg_groups;
+    st.pos = groups % g.seg_groups;
+    const uint32_t chs = segs / g.rows;
+    st.row = segs - chs * g.rows;
+    st.at = st.row * g.m_groups + chs * g.seg_groups + st.pos;
+    return st;
+  };
+  g.next_row = g.m_groups - g.seg_groups;
+  g.next_channel = g.seg_groups - g.rows * g.m_groups;
+  g.load_step = step(uint32_t(kHeldBlock * p.vec / 32));
+  g.unit_step = step(kHeldBlock);
+  const uint32_t per_channel = g.rows * g.seg_groups;
+  static_assert(kChanMaxUnits<T> * kHeldBlock * 32 / kChanMinChannel + 2 <= kChanMaxLocal, "channels of a workgroup");
+  g.shared = g.per % per_channel != 0 ? 1u : 0u;
+  const int grid = int((g.total + g.per - 1) / g.per);
+  const int units = int((g.per + kHeldBlock - 1) / kHeldBlock);
+  using S = ChanSlots<T>;
+#define ACCEPT_CHAN(KK)                                                                                             \
+  case KK:                                                                                                          \
+    if (units <= S::small)                                                                                          \
+      hipLaunchKernelGGL((quantize_channels_kernel<T, KK, S::small, 0>), dim3(grid), dim3(kHeldBlock), 0, s, x, payload, \
+                         header, mail, g, polls);                                                             \
+    else if (units <= S::middle)                                                                                    \
+      hipLaunchKernelGGL((quantize_channels_kernel<T, KK, S::middle, 0>), dim3(grid), dim3(kHeldBlock), 0, s, x, payload, \
+                         header, mail, g, polls);                                                             \
+    else                                                                                                            \
+      hipLaunchKernelGGL((quantize_channels_kernel<T, KK, S::large, kChanLdsUnits<T>>), dim3(grid), dim3(kHeldBlock), 0, s, \
+                         x, payload, header, mail, g, polls);                                                 \
+    break;
+  switch (d.bits) {
+    ACCEPT_CHAN(2) ACCEPT_CHAN(3) ACCEPT_CHAN(4) ACCEPT_CHAN(5) ACCEPT_CHAN(6) ACCEPT_CHAN(7) ACCEPT_CHAN(8)
+    default: return hipErrorInvalidValue;
+  }
+#undef ACCEPT_CHAN
+  return hipGetLastError();
+}
+
 template <typename T>
 hipError_t compress_typed(const accept_desc& d, UPlan p, const T* x, float* header, uint32_t* payload,
                           void* ws, hipStream_t s, StageTimer* tm, int held_polls) {
   uint64_t* mail = reinterpret_cast<uint64_t*>(reinterpret_cast<char*>(ws) + kMailOffset);
   if (p.held) p.held = held_runs(p, compute_units());
+  if (!channels_run(p, compute_units())) p.chan_per = 0;
   float* partials = reinterpret_cast<float*>(reinterpret_cast<char*>(ws) + kCtrlBytes);
   float* rtab = reinterpret_cast<float*>(reinterpret_cast<char*>(ws) + p.off_rtab);
   mark(tm, s);
+  if (p.chan_per != 0) {
+    const hipError_t e = launch_channels<T>(d, p, x, header, payload, reinterpret_cast<ChanMail*>(reinterpret_cast<char*>(ws) + kChanMailOffset), held_polls, s);
+    if (e == hipSuccess) mark(tm, s);
+    return e;
+  }
   if (p.held) {
     const hipError_t e = launch_held<T>(d, p, x, payload, partials, mail, held_polls, s);
     if (e != hipSuccess) return e;
@@ -1722,6 +2108,8 @@ UPlan make_uplan(const accept_desc& d) {
     p.col_grid_x = gx;
     p.col_grid_y = int(gy);
   }
+  if (p.C > 1 && d.layout == ACCEPT_LAYOUT_PACKED && d.rounding == ACCEPT_ROUND_NEAREST_EVEN)
+    p.chan_per = p.vec == 8 ? channel_groups<bf16_t>(d.n, p.C, p.seg_len) : channel_groups<float>(d.n, p.C, p.seg_len);
   p.off_rtab = kCtrlBytes + (partial_bytes + 255) / 256 * 256;
   p.bytes = p.off_rtab + (size_t(p.C) * sizeof(float) + 255) / 256 * 256;
   return p;

@@ -466,3 +466,82 @@ def test_payload_tail_is_not_overwritten(A):
         torch.cuda.synchronize()
         assert buf[pb:].cpu().numpy().tolist() == [0xAB] * 64
         assert buf[:pb].cpu().numpy().tobytes() == orc.uniform_compress(x, k, 1, N)[1].tobytes()
+
+
+# One range per channel, segments of whole 32s, a tensor that fits on the chip: one kernel, in which a workgroup
+# has consecutive groups of 32 elements of the order channel, row, place, and channels may lie in several.
+@pytest.mark.parametrize("n,C,seg,k,bf16", [
+    (4, 5, 1024, 4, False),        # the smallest channels; whole channels per workgroup
+    (3, 7, 1568, 5, True),         # shared channels, a last workgroup with little to do
+    (130, 2, 32, 3, False),        # segments of one group
+    (130, 2, 32, 8, True),
+    (2, 3, 20000, 7, False),       # few channels, many workgroups each
+    (1, 2, 300000, 2, True),
+    (16, 300, 512, 6, False),      # channels of 256 groups, some shared
+    (9, 100, 992, 7, True),        # a segment that no unit divides
+    (33, 260, 1024, 4, False),     # three units per workgroup
+    (33, 260, 1024, 5, True),
+    (64, 100, 3136, 6, False),     # local memory comes into use
+    (60, 256, 3136, 6, True),
+    (7 * 64, 256, 256, 3, False),  # the most that fits, float32
+    (7 * 64 + 1, 256, 256, 3, False),  # and one row more: range and quantizer
+])
+def test_channels_on_the_chip(A, n, C, seg, k, bf16):
+    torch = torch_mod()
+    print("case", n, C, seg, k, bf16, flush=True)
+    x = si.make_shape("relu_lognormal_chgain", (n, C, seg), 300 + k)
+    gain = np.float32(10.0) ** np.linspace(-2, 2, C, dtype=np.float32)
+    x = np.ascontiguousarray(x * gain[None, :, None], dtype=np.float32)
+    xd, bits = to_dev(x, bf16)
+    d = A.make_desc(A.UNIFORM, k, n, C * seg, channels=C, in_dtype=A.BF16 if bf16 else A.F32)
+    fits = n * C * seg <= (14 if bf16 else 7) * HELD_ROUND
+    assert (A.accept_stage_name(d, 0, 0) == "quantize_channels") == fits
+    oh, op = orc.uniform_compress(bits if bf16 else x, k, n, C * seg, C, bf16)
+    header, payload, ws = A.alloc_outputs(d, "cuda")
+    for polls in (64, 0, 64):  # seen by each other; every shared channel read by all that have a part of it
+        payload.zero_()
+        A.accept_compress_polls(d, xd, header, payload, ws, polls)
+        torch.cuda.synchronize()
+        assert dev_bytes(header) == oh, polls
+        assert first_mismatch(dev_bytes(payload), op.tobytes()) is None, polls
+
+
+def test_channels_on_the_chip_on_two_streams_and_in_a_graph(A):
+    """Workgroups of two calls compete for the compute units; one workspace serves descriptors with different
+    numbers of workgroups; a captured call is replayed on new inputs between eager ones."""
+    torch = torch_mod()
+    n, C, seg, k = 40, 96, 3136, 6
+    xs = [torch.from_numpy(si.make_shape("relu_lognormal_chgain", (n, C, seg), 310 + i) * np.float32(1 + i)).cuda() for i in range(3)]
+    d = A.make_desc(A.UNIFORM, k, n, C * seg, channels=C)
+    small = A.make_desc(A.UNIFORM, k, 6, C * seg, channels=C)
+    want = [orc.uniform_compress(x.cpu().numpy(), k, n, C * seg, C) for x in xs]
+    want_small = orc.uniform_compress(xs[0][:6].cpu().numpy(), k, 6, C * seg, C)
+    bufs = [A.alloc_outputs(d, "cuda") for _ in range(2)]
+    streams = [torch.cuda.Stream() for _ in range(2)]
+    torch.cuda.synchronize()
+    for turn in range(4):
+        for i, s in enumerate(streams):
+            with torch.cuda.stream(s):
+                header, payload, ws = bufs[i]
+                for rep in range(3):
+                    A.accept_compress(d, xs[(turn + i + rep) % 3], header=header, payload=payload, workspace=ws)
+        torch.cuda.synchronize()
+        for i in range(2):
+            oh, op = want[(turn + i + 2) % 3]
+            assert dev_bytes(bufs[i][0]) == oh, (turn, i)
+            assert first_mismatch(dev_bytes(bufs[i][1]), op.tobytes()) is None, (turn, i)
+    header, payload, ws = bufs[0]
+    x = xs[0].clone()
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g):
+        A.accept_compress(d, x, header=header, payload=payload, workspace=ws)
+    for i in (1, 2, 0, 1):
+        x.copy_(xs[i])
+        payload.zero_()
+        g.replay()
+        torch.cuda.synchronize()
+        oh, op = want[i]
+        assert dev_bytes(header) == oh and first_mismatch(dev_bytes(payload), op.tobytes()) is None, i
+        h, p = A.accept_compress(small, xs[0][:6].reshape(-1), workspace=ws)  # eager, same workspace
+        torch.cuda.synchronize()
+        assert dev_bytes(h) == want_small[0] and dev_bytes(p) == want_small[1].tobytes()
