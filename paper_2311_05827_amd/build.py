@@ -15,7 +15,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB_PATH = os.path.join(HERE, "libaccept.so")
-SOURCES = ["api.hip", "uniform.hip", "mbq.hip"]
+SOURCES = ["api.hip", "uniform.hip", "uniform_chip_f32.hip", "uniform_chip_bf16.hip", "mbq.hip"]
 
 HIPCC_FLAGS = [
     "-O3",

@@ -1,0 +1,93 @@
+// Scheme U's compressors that keep the tensor, or a part of it, on the chip between the range and the
+// quantizer, and so read it once: which tensors take them (host).  One range per tensor: the held pass; one range
+// per channel: the channels pass.  The kernels are compiled per input type (uniform_chip_f32.hip, uniform_chip_bf16.hip).
+#pragma once
+
+#include "uniform_quant.hpp"
+
+namespace accept {
+
+// The held pass (quantize_held_kernel): one workgroup per compute unit, two wavefronts per SIMD.
+constexpr int kHeldBlock = 512;
+constexpr int kUnitTiles = 2;
+constexpr int kUnitElems = kUnitTiles * kTileElems;  // elements a workgroup takes at a time
+// Workgroups of the kernel behind it.  Nearly all end at once, unless workgroups of the held pass gave up:
+// then the memory is read as fast as this many allow.  Time with all of them giving up, 205 MB: 256
+// workgroups 80.0 us, 512 74.3, 1024 75.3, 2048 75.3 (two reads 68.8); beside copies on another stream
+// 219, 213, 180, 158; with none giving up 2048 cost 0.7 us more than 512 and 1024.
+constexpr int kHeldRestGrid = 1024;
+static_assert(kHeldRestGrid % (kUnitTiles * kHeldGrid) == 0, "a workgroup's tiles belong to one workgroup of the held pass");
+template <typename T>
+constexpr int kHeldVecs = sizeof(T) == 4 ? 56 : 48;  // 16-byte vectors a thread keeps in registers (bfloat16: 56 would spill)
+constexpr int kHeldLdsVecs = 16;                     // and in local memory
+template <typename T>
+constexpr int kHeldUnits = kHeldVecs<T> * kHeldBlock * Elem<T>::VEC / kUnitElems;  // 7 (float32), 12 (bfloat16)
+template <typename T>
+constexpr int kHeldLdsUnits = kHeldLdsVecs * kHeldBlock * Elem<T>::VEC / kUnitElems;  // 2, 4
+// Tensors that take the held pass.  Below, its second kernel (4 us that do nearly nothing) costs more
+// than the saved read; captured calls, k = 8, two reads / held (us): float32 51 MB 19.2 / 18.9, 55 MB
+// 20.4 / 20.1, 66 MB 23.3 / 21.1; bfloat16, whose values are twice as many, 51 MB 19.6 / 21.9, 60 MB
+// 23.4 / 24.5, 72 MB 27.5 / 27.5, 76 MB 29.4 / 28.4, 95 MB 35.2 / 32.8 (k = 4: 72 MB 23.5 / 23.8, 76 MB
+// 24.8 / 24.8).  Above, the part that is kept gets small and the workgroups drift apart by more than they
+// wait for each other: bfloat16 205 MB 75.9 / 67.7, 262 MB 96.1 / 94.2, 268 MB 98.3 / 95.2.  float32 gains
+// beyond the line too (268 MB 89.6 / 79.5, 300 MB 110 / 97, 400 MB 149 / 150); it lies where both types do.
+template <typename T>
+constexpr int64_t kHeldMinBytes = int64_t(sizeof(T) == 4 ? 48 : 72) << 20;
+constexpr int64_t kHeldMaxBytes = int64_t(256) << 20;
+static_assert(kHeldMinBytes<float> / 4 >= int64_t(kHeldGrid) * kUnitElems, "every workgroup has a unit");
+static_assert(kHeldMinBytes<bf16_t> / 2 >= int64_t(kHeldGrid) * kUnitElems, "every workgroup has a unit");
+static_assert(kMailOffset + kHeldGrid * sizeof(uint64_t) <= kCtrlBytes, "the control block holds the mailboxes");
+
+constexpr int kChanMaxLocal = 64;   // channels a workgroup may have a part of: at most 14 units of 512 groups, and
+                                    // two parts, of channels of at least 128 groups
+template <typename T>
+constexpr int kChanLdsUnits = sizeof(T) == 4 ? 1 : 3;
+// Registers for the units of a workgroup: three sizes, so that small tensors do not carry the large ones' loads.
+template <typename T>
+struct ChanSlots;
+template <>
+struct ChanSlots<float> {
+  static constexpr int small = 2, middle = 4, large = 6;
+};
+template <>
+struct ChanSlots<bf16_t> {
+  static constexpr int small = 3, middle = 6, large = 11;
+};
+template <typename T>
+constexpr int64_t kChanMaxUnits = ChanSlots<T>::large + kChanLdsUnits<T>;
+
+// Groups of a workgroup of quantize_channels_kernel; 0: the tensor does not take it.  Segments have to be whole
+// groups, and the tensor has to fit on the chip.  Against range and quantize kernels (two, or three with one
+// that finishes the ranges between them; captured calls, us): 64 x 256 x 3136 bfloat16 k = 6 43.3 / 33.2, 32 x 256 x
+// 3136 float32 38.4 / 26.8, 16 x 512 x 1024 15.5 / 10.4, 8 x 32 x 12544 10.7 / 6.5, 130 x 30 x 256 bfloat16 27.6 / 6.2,
+// 64 x 5859 x 64 29.9 / 27.8.  Channels of fewer than 8192 elements are handed over often, which large tensors
+// pay for: 4 x 5859 x 1024 bfloat16 26.2 / 27.9, 4 x 2441 x 1024 15.6 / 13.8; float32 35.7 / 37.3, 19.1 / 18.0.
+constexpr int64_t kChanMinChannel = 4096;
+constexpr int64_t kChanManyValues = int64_t(10) << 20;  // beyond, channels have twice that at least
+// The fewest groups of a workgroup: 32 to 256 take the same time where channels are shared; fewer
+// workgroups then have fewer mailboxes to look through.
+constexpr int64_t kChanMinGroups = 128;
+template <typename T>
+inline uint32_t channel_groups(int64_t n, int64_t C, int64_t seg_len) {
+  const int64_t groups = n * C * seg_len / 32, most = kChanMaxUnits<T> * kHeldBlock;
+  if (seg_len % 32 != 0 || groups > most * kHeldGrid) return 0;
+  if (n * seg_len < (groups * 32 > kChanManyValues ? 2 : 1) * kChanMinChannel) return 0;
+  int64_t per = (groups + kHeldGrid - 1) / kHeldGrid;
+  if (per < kChanMinGroups) per = kChanMinGroups;
+  // Whole channels, if that is hardly more work for a workgroup: nothing is shared then, and nobody waits
+  // (8 x 61 x 1024 bfloat16: 5.5 -> 4.1 us).
+  const int64_t channel = n * seg_len / 32, whole = (per + channel - 1) / channel * channel;
+  if (whole <= kHeldBlock || whole * 8 <= per * 9) per = whole;
+  return uint32_t(per < most ? per : most);
+}
+
+template <typename T>
+hipError_t launch_held(const accept_desc& d, const UPlan& p, const T* x, uint32_t* payload, float* partials,
+                       uint64_t* mail, int polls, hipStream_t s);
+struct ChanMail;
+template <typename T>
+hipError_t launch_channels(const accept_desc& d, const UPlan& p, const T* x, float* header, uint32_t* payload,
+                           ChanMail* mail, int polls, hipStream_t s);
+constexpr size_t kChanMailOffset = kMailOffset + kHeldGrid * sizeof(uint64_t);
+
+}  // namespace accept
