@@ -255,17 +255,18 @@ const char* accept_stage_name(const accept_desc* desc, int is_decompress, int i)
     static const char* const names[] = {"range", "range_finalize", "quantize_plain"};
     return i < 3 ? names[i] : nullptr;
   }
-  const int units_here = compute_units();  // 0 where there is no device: names are then those of a whole one
-  if (channels_run(make_uplan(*desc), units_here != 0 ? units_here : kHeldGrid)) return i == 0 ? "quantize_channels" : nullptr;
-  if (desc->channels > 1 && !make_uplan(*desc).local_ranges) {
+  const UPlan plan = make_uplan(*desc);
+  int units = compute_units();
+  if (units == 0) units = kHeldGrid;  // no device: the names of a whole one
+  if (channels_run(plan, units)) return i == 0 ? "quantize_channels" : nullptr;
+  if (desc->channels > 1 && !plan.local_ranges) {
     static const char* const names[] = {"range", "range_finalize", "quantize_pack"};
     return i < 3 ? names[i] : nullptr;
   }
-  // Range and quantizer in one kernel, the second finishes what that one left; on the current device
-  // (where there is none, on a whole one).
-  if (held_runs(make_uplan(*desc), units_here != 0 ? units_here : kHeldGrid)) {
+  // range and quantizer in one kernel; of the largest tensors a second one finishes what that one left
+  if (held_runs(plan, units)) {
     static const char* const names[] = {"quantize_held", "quantize_rest"};
-    return i < 2 ? names[i] : nullptr;
+    return i < (plan.held_rest ? 2 : 1) ? names[i] : nullptr;
   }
   static const char* const names[] = {"range", "quantize_pack"};
   return i < 2 ? names[i] : nullptr;

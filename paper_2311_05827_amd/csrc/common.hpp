@@ -73,6 +73,7 @@ struct UPlan {
   bool straddling;     // U_GENERIC: segments longer than a vector but not whole vectors
   bool held;           // U_TENSOR: the range pass keeps the end of the tensor on the chip and quantizes it itself
   int64_t held_units;  // held: whole units (see kUnitElems) of the tensor
+  bool held_rest;      // held: a second kernel does what workgroups that gave up have left
   int held_lds;        // held: units per workgroup that stay in local memory (the others in registers)
   int64_t held_first;  // held: units [held_first, held_units) are kept, the others are read again
   uint32_t chan_per;   // per channel: groups of 32 elements per workgroup of the pass that keeps the tensor on the chip; 0: not taken

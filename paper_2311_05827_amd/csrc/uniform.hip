@@ -92,9 +92,7 @@ constexpr int kRangePerElement = 2;  // one element per segment (channels-last) 
 constexpr int kRangePerVectorLocal = 3;  // as kRangePerVector, quantizer only: no table in memory yet, the workgroup
                                          // finishes the ranges of each tile's channels itself; ChanPos.ch then indexes
                                          // its own small table (channel minus the tile's first channel, modulo C)
-constexpr int kOneRangeHeld = 4;  // as kOneRange, quantizer only: after quantize_held_kernel, of whose part only what
-                                  // it did not finish is left to do
-constexpr int kRangeStraddling = 5;  // segments longer than a vector but not whole vectors: a vector lies in one segment
+constexpr int kRangeStraddling = 4;  // segments longer than a vector but not whole vectors: a vector lies in one segment
                                      // or across the border of two; positions are counted in elements (ChanGeom.seg_vecs
                                      // is the segment's elements, ChanPos.rem the element's place in it).  64 x 1024 x 196
                                      // bfloat16: quantize 22.2 -> 9.5 us, decode 26.5 -> 7.9 us against single elements
@@ -113,7 +111,6 @@ constexpr int64_t kStraddleTiledValues = int64_t(5) << 19;  // from which the de
 // Position units of a vector.
 template <int MODE, int VEC>
 constexpr int kUnitsPerVec = MODE == kRangeStraddling ? VEC : 1;
-constexpr bool one_range(int mode) { return mode == kOneRange || mode == kOneRangeHeld; }
 // The per-group values (reciprocals for the quantizer, scales for the decoder) of a vector's elements.
 template <int MODE, int VEC>
 __device__ __forceinline__ void ranges_of_vector(const float* __restrict__ tab, float one, const ChanPos& pos,
@@ -131,7 +128,7 @@ __device__ __forceinline__ void ranges_of_vector(const float* __restrict__ tab, 
 #pragma unroll
     for (int e = 0; e < VEC; ++e) out[e] = e < cut ? v0 : v1;
   } else {
-    const float v = one_range(MODE) ? one : tab[pos.ch];
+    const float v = MODE == kOneRange ? one : tab[pos.ch];
 #pragma unroll
     for (int e = 0; e < VEC; ++e) out[e] = v;
   }
@@ -478,15 +475,14 @@ __global__ __launch_bounds__(kWave) void range_finalize_kernel(const float* __re
 // barrier per tile is enough.  MODE says where an element's range comes from (kOneRange ..
 // kRangePerVectorLocal above).  kOneRange folds U1b into the prologue: every workgroup reduces
 // the range pass's partial maxima itself and workgroup 0 writes s to the header;
-// kRangePerVectorLocal folds it into the tile loop (see local_r below); kOneRangeHeld is kOneRange
-// after quantize_held_kernel; the other two modes read the table that a U1b kernel has written.  Elements after the last whole tile take the slow
+// kRangePerVectorLocal folds it into the tile loop (see local_r below); the other modes read the table that a U1b kernel has written.  Elements after the last whole tile take the slow
 // path at the end.
 template <typename T, int K, int MODE, bool STOCH>
 __global__ __launch_bounds__(kBlock) void quantize_pack_kernel(
     const T* __restrict__ x, uint32_t* __restrict__ payload32, float* __restrict__ header,
     const float* __restrict__ partials, int npart, const float* __restrict__ rtab, int64_t N, int64_t full_tiles,
     int64_t rev_tiles, int64_t slow_first_group, int64_t payload_bytes, ChanGeom geom, LocalRanges local, int64_t m,
-    int64_t seg_len, uint64_t seed, int64_t held_tiles, uint64_t* __restrict__ mail) {
+    int64_t seg_len, uint64_t seed) {
   constexpr int VEC = Elem<T>::VEC;
   constexpr int64_t TILE_VECS = kTileElems / VEC;
   constexpr int UNITS = kUnitsPerVec<MODE, VEC>;
@@ -504,12 +500,7 @@ __global__ __launch_bounds__(kBlock) void quantize_pack_kernel(
   // of the plain order.  A workgroup's tiles then step backwards by one grid stride, and tile and
   // workgroup index stay equal modulo 8: the die that read a tile in the range pass reads it
   // again here.  The up to seven tiles after rev_tiles keep their plain places.
-  // kOneRangeHeld: plain order.  The grid makes all of a workgroup's tiles belong to units of the same
-  // workgroup of the held pass; if that one finished them, only what lies behind the last whole unit is
-  // left (from place first_f on).
-  int64_t first_f = blockIdx.x;
   auto tile_of = [&](int64_t tile_f) {
-    if (MODE == kOneRangeHeld) return tile_f;
     return tile_f < rev_tiles ? rev_tiles - 8 - (tile_f & ~int64_t(7)) + (tile_f & 7) : tile_f;
   };
   // A tile's vectors are asked for one tile ahead: those of the first tile here, before anything
@@ -520,21 +511,12 @@ __global__ __launch_bounds__(kBlock) void quantize_pack_kernel(
 #pragma unroll
     for (int u = 0; u < LOADS; ++u) raw[u] = load16_stream(xt + (u * kBlock + tid) * VEC);
   };
-  if (MODE == kOneRangeHeld) {
-    // (the records: largest value and whether it finished, per workgroup of the held pass)
-    const float2* rec = reinterpret_cast<const float2*>(partials);
-    if (rec[blockIdx.x / kUnitTiles % kHeldGrid].y != 0.0f && first_f < held_tiles)
-      first_f += (held_tiles - first_f + gridDim.x - 1) / gridDim.x * gridDim.x;
-    // nothing left here, as for nearly all of them in a call in which none gave up
-    if (blockIdx.x != 0 && first_f >= full_tiles && (slow_first_group + int64_t(blockIdx.x) * kBlock) * 8 >= N) return;
-  }
-  if (first_f < full_tiles) ask_for_tile(tile_of(first_f));
+  if (int64_t(blockIdx.x) < full_tiles) ask_for_tile(tile_of(blockIdx.x));
 
   float r_tensor = 0.0f;
-  if (one_range(MODE)) {
+  if (MODE == kOneRange) {
     float c = 0.0f;
-    for (int i = tid; i < npart; i += kBlock)
-      c = fmaxf(c, MODE == kOneRangeHeld ? reinterpret_cast<const float2*>(partials)[i].x : partials[i]);
+    for (int i = tid; i < npart; i += kBlock) c = fmaxf(c, partials[i]);
     c = wave_max(c);
     if ((tid & (kWave - 1)) == 0) red[tid / kWave] = c;
     __syncthreads();
@@ -544,16 +526,13 @@ __global__ __launch_bounds__(kBlock) void quantize_pack_kernel(
     float s;
     scale_from_range(c, K, s, r_tensor);
     if (blockIdx.x == 0 && tid == 0) header[0] = s;
-    // the mailboxes have been read by everyone: empty again for the next call
-    if (MODE == kOneRangeHeld && blockIdx.x == 0)
-      for (int i = tid; i < kHeldGrid; i += kBlock) mail[i] = 0;
   }
 
   // Channel position of a tile's first vector (the same in all threads), stepped from tile to
   // tile; a thread's own position is that plus its index.
   ChanPos first_pos{0, 0};
   ChanStep mine{0, 0};
-  if (!one_range(MODE) && int64_t(blockIdx.x) < full_tiles) {
+  if (MODE != kOneRange && int64_t(blockIdx.x) < full_tiles) {
     first_pos = chan_init(geom, tile_of(blockIdx.x) * TILE_UNITS);
     mine.dr = int64_t(tid * UNITS) % geom.seg_vecs;
     mine.dch = int32_t((int64_t(tid * UNITS) / geom.seg_vecs) % geom.C);
@@ -628,19 +607,19 @@ __global__ __launch_bounds__(kBlock) void quantize_pack_kernel(
   // against a state multiplied out per element and a 64-bit integer converted to float.
   const uint64_t z_thread = STOCH ? rand_state(seed, uint64_t(tid * VEC)) : 0;  // of the thread's first element of tile 0
   int buf = 0;
-  for (int64_t tile_f = first_f; tile_f < full_tiles; tile_f += gridDim.x, buf ^= 1) {
+  for (int64_t tile_f = blockIdx.x; tile_f < full_tiles; tile_f += gridDim.x, buf ^= 1) {
     const int64_t tile = tile_of(tile_f);
     // the next tile of this workgroup: one grid stride back inside the reversed part
     const int64_t next_f = tile_f + gridDim.x;
     ChanPos next_pos = first_pos;
     LocalFetch next_lf;
-    if (!one_range(MODE) && next_f < full_tiles) {
+    if (MODE != kOneRange && next_f < full_tiles) {
       if (next_f < rev_tiles) chan_retreat(geom, next_pos, geom.sgrid);
       else next_pos = chan_init(geom, tile_of(next_f) * TILE_UNITS);
       if (MODE == kRangePerVectorLocal) local_fetch(next_pos, next_lf);
     }
     ChanPos pos = first_pos;
-    if (!one_range(MODE)) chan_advance(geom, pos, mine);
+    if (MODE != kOneRange) chan_advance(geom, pos, mine);
     const int32_t ch0 = first_pos.ch;
     uint64_t z = STOCH ? z_thread + uint64_t(tile) * (uint64_t(kTileElems) * kRandStep) : 0;
 #pragma unroll
@@ -654,7 +633,7 @@ __global__ __launch_bounds__(kBlock) void quantize_pack_kernel(
       } else {
         ranges_of_vector<MODE, VEC>(rtab, r_tensor, pos, geom, r);
       }
-      if (!one_range(MODE)) chan_advance(geom, pos, geom.s256);
+      if (MODE != kOneRange) chan_advance(geom, pos, geom.s256);
       float f[VEC];
       widen(raw[u], f);
 #pragma unroll
@@ -667,12 +646,14 @@ __global__ __launch_bounds__(kBlock) void quantize_pack_kernel(
       local_finish(tile_of(next_f), next_pos, next_lf, local_r[buf ^ 1]);
     first_pos = next_pos;
     __syncthreads();
-    const uint4 a = *reinterpret_cast<const uint4*>(&pieces[buf][8 * tid]);
-    const uint4 b = *reinterpret_cast<const uint4*>(&pieces[buf][8 * tid + 4]);
-    const uint32_t P[8] = {a.x, a.y, a.z, a.w, b.x, b.y, b.z, b.w};
-    uint32_t out[K];
-    pack8<K>(P, out);
-    store_dwords<K>(payload32 + (tile * kBlock + tid) * K, out);
+    const __amdgpu_buffer_rsrc_t codes = payload_buffer(payload32 + tile * (kBlock * K), kBlock * K * 4);
+#pragma unroll
+    for (int i = 0; i < CodeParts<K>::PARTS; ++i) {
+      const int part = i * kBlock + tid;
+      uint32_t out[CodeParts<K>::DWORDS];
+      pack_part<K>(&pieces[buf][part * CodeParts<K>::PIECES], out);
+      store_part<K>(codes, uint32_t(part * CodeParts<K>::DWORDS * 4), out);
+    }
   }
 
   // Everything the tile loop did not cover, 8 elements (k bytes) per thread.
@@ -680,7 +661,7 @@ __global__ __launch_bounds__(kBlock) void quantize_pack_kernel(
   uint8_t* payload8 = reinterpret_cast<uint8_t*>(payload32);
   for (int64_t g = slow_first_group + int64_t(blockIdx.x) * kBlock + tid; g < groups;
        g += int64_t(gridDim.x) * kBlock) {
-    if (!one_range(MODE)) {
+    if (MODE != kOneRange) {
       quantize_group8<T, K, STOCH>(x, payload8, g, N, payload_bytes, seed,
                                    [&](int64_t i) { return rtab[(i % m) / seg_len]; });
     } else {
@@ -847,23 +828,21 @@ ChanStep make_step(int64_t step_vecs, int64_t seg_vecs, int64_t C) {
 
 template <typename T, int K, int MODE, bool STOCH>
 hipError_t launch_quant(const accept_desc& d, const UPlan& p, const T* x, float* header, uint32_t* payload,
-                        const float* partials, const float* rtab, uint64_t* mail, hipStream_t s) {
+                        const float* partials, const float* rtab, hipStream_t s) {
   const int64_t N = p.N;
   const int64_t full_tiles = p.fast ? N / kTileElems : 0;
   const int64_t groups = (N + 7) / 8;
   const int64_t slow_first = full_tiles * (kTileElems / 8);
-  const int64_t held_tiles = MODE == kOneRangeHeld ? p.held_units * kUnitTiles : 0;
   const int64_t slow_groups = groups - slow_first;
   int64_t want = full_tiles > (slow_groups + kBlock - 1) / kBlock ? full_tiles : (slow_groups + kBlock - 1) / kBlock;
   if (want < 1) want = 1;
-  if (MODE == kOneRangeHeld) want = kHeldRestGrid;
   const int grid = int(want < kQuantGridMax ? want : kQuantGridMax);
   // the reversed tile order needs tile and workgroup index to agree modulo 8
   const int64_t rev_tiles = (grid % 8 == 0) ? (full_tiles & ~int64_t(7)) : 0;
   ChanGeom g{};
   g.seg_vecs = 1;
   g.C = 1;
-  if (!one_range(MODE) && p.fast) {
+  if (MODE != kOneRange && p.fast) {
     // per element: the "segments" are single vectors and the "channels" the m / vec vectors of a row
     constexpr int UNITS = kUnitsPerVec<MODE, Elem<T>::VEC>;
     g.seg_vecs = MODE == kRangePerElement ? 1 : MODE == kRangeStraddling ? p.seg_len : p.seg_len / p.vec;
@@ -873,9 +852,8 @@ hipError_t launch_quant(const accept_desc& d, const UPlan& p, const T* x, float*
   }
   const int64_t payload_bytes = (N * K + 7) / 8;
   hipLaunchKernelGGL((quantize_pack_kernel<T, K, MODE, STOCH>), dim3(grid), dim3(kBlock), 0, s, x, payload, header,
-                     partials, MODE == kOneRangeHeld ? kHeldGrid : p.range_grid, rtab, N, full_tiles, rev_tiles,
-                     slow_first, payload_bytes, g, LocalRanges{int32_t(d.n * p.cps)}, p.m, p.seg_len, d.seed, held_tiles,
-                     mail);
+                     partials, p.range_grid, rtab, N, full_tiles, rev_tiles, slow_first, payload_bytes, g,
+                     LocalRanges{int32_t(d.n * p.cps)}, p.m, p.seg_len, d.seed);
   return hipGetLastError();
 }
 
@@ -1053,47 +1031,43 @@ int plain_grid(int64_t units) {
 
 template <typename T, int K>
 hipError_t launch_quant_k(const accept_desc& d, const UPlan& p, const T* x, float* header, uint32_t* payload,
-                          const float* partials, const float* rtab, uint64_t* mail, hipStream_t s) {
+                          const float* partials, const float* rtab, hipStream_t s) {
   const bool stoch = d.rounding == ACCEPT_ROUND_STOCHASTIC;
-  if (p.held) return launch_quant<T, K, kOneRangeHeld, false>(d, p, x, header, payload, partials, rtab, mail, s);
   if (p.mode == U_TENSOR) {
-    return stoch ? launch_quant<T, K, kOneRange, true>(d, p, x, header, payload, partials, rtab, mail, s)
-                 : launch_quant<T, K, kOneRange, false>(d, p, x, header, payload, partials, rtab, mail, s);
+    return stoch ? launch_quant<T, K, kOneRange, true>(d, p, x, header, payload, partials, rtab, s)
+                 : launch_quant<T, K, kOneRange, false>(d, p, x, header, payload, partials, rtab, s);
   }
   if (p.per_element) {
-    return stoch ? launch_quant<T, K, kRangePerElement, true>(d, p, x, header, payload, partials, rtab, mail, s)
-                 : launch_quant<T, K, kRangePerElement, false>(d, p, x, header, payload, partials, rtab, mail, s);
+    return stoch ? launch_quant<T, K, kRangePerElement, true>(d, p, x, header, payload, partials, rtab, s)
+                 : launch_quant<T, K, kRangePerElement, false>(d, p, x, header, payload, partials, rtab, s);
   }
   if (p.straddling) {
-    return stoch ? launch_quant<T, K, kRangeStraddling, true>(d, p, x, header, payload, partials, rtab, mail, s)
-                 : launch_quant<T, K, kRangeStraddling, false>(d, p, x, header, payload, partials, rtab, mail, s);
+    return stoch ? launch_quant<T, K, kRangeStraddling, true>(d, p, x, header, payload, partials, rtab, s)
+                 : launch_quant<T, K, kRangeStraddling, false>(d, p, x, header, payload, partials, rtab, s);
   }
   if (p.local_ranges) {
-    return stoch ? launch_quant<T, K, kRangePerVectorLocal, true>(d, p, x, header, payload, partials, rtab, mail, s)
-                 : launch_quant<T, K, kRangePerVectorLocal, false>(d, p, x, header, payload, partials, rtab, mail, s);
+    return stoch ? launch_quant<T, K, kRangePerVectorLocal, true>(d, p, x, header, payload, partials, rtab, s)
+                 : launch_quant<T, K, kRangePerVectorLocal, false>(d, p, x, header, payload, partials, rtab, s);
   }
-  return stoch ? launch_quant<T, K, kRangePerVector, true>(d, p, x, header, payload, partials, rtab, mail, s)
-               : launch_quant<T, K, kRangePerVector, false>(d, p, x, header, payload, partials, rtab, mail, s);
+  return stoch ? launch_quant<T, K, kRangePerVector, true>(d, p, x, header, payload, partials, rtab, s)
+               : launch_quant<T, K, kRangePerVector, false>(d, p, x, header, payload, partials, rtab, s);
 }
 
 template <typename T>
-hipError_t compress_typed(const accept_desc& d, UPlan p, const T* x, float* header, uint32_t* payload,
+hipError_t compress_typed(const accept_desc& d, const UPlan& p, const T* x, float* header, uint32_t* payload,
                           void* ws, hipStream_t s, StageTimer* tm, int held_polls) {
-  uint64_t* mail = reinterpret_cast<uint64_t*>(reinterpret_cast<char*>(ws) + kMailOffset);
-  if (p.held) p.held = held_runs(p, compute_units());
-  if (!channels_run(p, compute_units())) p.chan_per = 0;
+  const int units = p.held || p.chan_per != 0 ? compute_units() : 0;
+  ChipMail* mail = reinterpret_cast<ChipMail*>(reinterpret_cast<char*>(ws) + kMailOffset);
   float* partials = reinterpret_cast<float*>(reinterpret_cast<char*>(ws) + kCtrlBytes);
   float* rtab = reinterpret_cast<float*>(reinterpret_cast<char*>(ws) + p.off_rtab);
   mark(tm, s);
-  if (p.chan_per != 0) {
-    const hipError_t e = launch_channels<T>(d, p, x, header, payload, reinterpret_cast<ChanMail*>(reinterpret_cast<char*>(ws) + kChanMailOffset), held_polls, s);
+  if (held_runs(p, units) || channels_run(p, units)) {
+    const hipError_t e = p.held ? launch_held<T>(d, p, x, header, payload, mail, held_polls, s, tm)
+                                : launch_channels<T>(d, p, x, header, payload, mail, held_polls, s);
     if (e == hipSuccess) mark(tm, s);
     return e;
   }
-  if (p.held) {
-    const hipError_t e = launch_held<T>(d, p, x, payload, partials, mail, held_polls, s);
-    if (e != hipSuccess) return e;
-  } else if (p.mode == U_TENSOR) {
+  if (p.mode == U_TENSOR) {
     hipLaunchKernelGGL((range_tensor_kernel<T>), dim3(p.range_grid), dim3(kBlock), 0, s, x, p.N, partials);
   } else if (p.mode == U_SEGMENTED) {
     const int64_t tiles = (p.N + kTileElems - 1) / kTileElems;  // below 2^31: N is at most 2^40
@@ -1155,13 +1129,13 @@ hipError_t compress_typed(const accept_desc& d, UPlan p, const T* x, float* head
     return hipSuccess;
   }
   switch (d.bits) {
-    case 2: e = launch_quant_k<T, 2>(d, p, x, header, payload, partials, rtab, mail, s); break;
-    case 3: e = launch_quant_k<T, 3>(d, p, x, header, payload, partials, rtab, mail, s); break;
-    case 4: e = launch_quant_k<T, 4>(d, p, x, header, payload, partials, rtab, mail, s); break;
-    case 5: e = launch_quant_k<T, 5>(d, p, x, header, payload, partials, rtab, mail, s); break;
-    case 6: e = launch_quant_k<T, 6>(d, p, x, header, payload, partials, rtab, mail, s); break;
-    case 7: e = launch_quant_k<T, 7>(d, p, x, header, payload, partials, rtab, mail, s); break;
-    case 8: e = launch_quant_k<T, 8>(d, p, x, header, payload, partials, rtab, mail, s); break;
+    case 2: e = launch_quant_k<T, 2>(d, p, x, header, payload, partials, rtab, s); break;
+    case 3: e = launch_quant_k<T, 3>(d, p, x, header, payload, partials, rtab, s); break;
+    case 4: e = launch_quant_k<T, 4>(d, p, x, header, payload, partials, rtab, s); break;
+    case 5: e = launch_quant_k<T, 5>(d, p, x, header, payload, partials, rtab, s); break;
+    case 6: e = launch_quant_k<T, 6>(d, p, x, header, payload, partials, rtab, s); break;
+    case 7: e = launch_quant_k<T, 7>(d, p, x, header, payload, partials, rtab, s); break;
+    case 8: e = launch_quant_k<T, 8>(d, p, x, header, payload, partials, rtab, s); break;
     default: return hipErrorInvalidValue;
   }
   if (e != hipSuccess) return e;
@@ -1287,10 +1261,12 @@ UPlan make_uplan(const accept_desc& d) {
     p.held = d.layout == ACCEPT_LAYOUT_PACKED && d.rounding == ACCEPT_ROUND_NEAREST_EVEN &&
              bytes >= (p.vec == 8 ? kHeldMinBytes<bf16_t> : kHeldMinBytes<float>) && bytes <= kHeldMaxBytes;
     if (p.held) {
-      const int64_t keep = p.vec == 8 ? kHeldUnits<bf16_t> : kHeldUnits<float>;
+      int64_t keep = p.vec == 8 ? kHeldUnits<bf16_t> : kHeldUnits<float>;
       const int64_t keep_lds = p.vec == 8 ? kHeldLdsUnits<bf16_t> : kHeldLdsUnits<float>;
       p.held_units = p.N / kUnitElems;
       const int64_t rounds = (p.held_units + kHeldGrid - 1) / kHeldGrid;
+      p.held_rest = p.vec == 4 && rounds > keep + keep_lds;
+      if (p.held_rest) keep = kHeldLargeUnits;
       p.held_lds = rounds > keep ? int(keep_lds) : 0;
       p.held_first = rounds > keep + keep_lds ? (rounds - keep - keep_lds) * kHeldGrid : 0;
     }

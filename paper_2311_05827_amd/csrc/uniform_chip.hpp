@@ -11,32 +11,28 @@ namespace accept {
 constexpr int kHeldBlock = 512;
 constexpr int kUnitTiles = 2;
 constexpr int kUnitElems = kUnitTiles * kTileElems;  // elements a workgroup takes at a time
-// Workgroups of the kernel behind it.  Nearly all end at once, unless workgroups of the held pass gave up:
-// then the memory is read as fast as this many allow.  Time with all of them giving up, 205 MB: 256
-// workgroups 80.0 us, 512 74.3, 1024 75.3, 2048 75.3 (two reads 68.8); beside copies on another stream
-// 219, 213, 180, 158; with none giving up 2048 cost 0.7 us more than 512 and 1024.
-constexpr int kHeldRestGrid = 1024;
-static_assert(kHeldRestGrid % (kUnitTiles * kHeldGrid) == 0, "a workgroup's tiles belong to one workgroup of the held pass");
 template <typename T>
-constexpr int kHeldVecs = sizeof(T) == 4 ? 56 : 48;  // 16-byte vectors a thread keeps in registers (bfloat16: 56 would spill)
+constexpr int kHeldVecs = 48;  // 16-byte vectors a thread keeps in registers (more would spill)
 constexpr int kHeldLdsVecs = 16;                     // and in local memory
 template <typename T>
-constexpr int kHeldUnits = kHeldVecs<T> * kHeldBlock * Elem<T>::VEC / kUnitElems;  // 7 (float32), 12 (bfloat16)
+constexpr int kHeldUnits = kHeldVecs<T> * kHeldBlock * Elem<T>::VEC / kUnitElems;  // 6 (float32), 12 (bfloat16)
 template <typename T>
 constexpr int kHeldLdsUnits = kHeldLdsVecs * kHeldBlock * Elem<T>::VEC / kUnitElems;  // 2, 4
-// Tensors that take the held pass.  Below, its second kernel (4 us that do nearly nothing) costs more
-// than the saved read; captured calls, k = 8, two reads / held (us): float32 51 MB 19.2 / 18.9, 55 MB
-// 20.4 / 20.1, 66 MB 23.3 / 21.1; bfloat16, whose values are twice as many, 51 MB 19.6 / 21.9, 60 MB
-// 23.4 / 24.5, 72 MB 27.5 / 27.5, 76 MB 29.4 / 28.4, 95 MB 35.2 / 32.8 (k = 4: 72 MB 23.5 / 23.8, 76 MB
-// 24.8 / 24.8).  Above, the part that is kept gets small and the workgroups drift apart by more than they
-// wait for each other: bfloat16 205 MB 75.9 / 67.7, 262 MB 96.1 / 94.2, 268 MB 98.3 / 95.2.  float32 gains
-// beyond the line too (268 MB 89.6 / 79.5, 300 MB 110 / 97, 400 MB 149 / 150); it lies where both types do.
+// The largest float32 tensors, of which not all is kept: one unit more in registers.  There is then no room left
+// for the code that goes on where a workgroup gives up, and a second kernel (4 us) does that: 205 MB, k = 8 / 4 58.3 /
+// 54.8 us, with six units and no second kernel 59.7 / 56.9; 160 MB 41.5 / 39.7 (before, 45.5 / 42.2).
+constexpr int kHeldLargeUnits = 7;
+// Tensors that take the held pass.  Captured calls, two reads / held (us), when the held pass still had a second
+// kernel (4 us) always: float32 51 MB 19.2 / 18.9 (15.5 now), 66 MB 23.3 / 21.1; bfloat16, whose values are twice as
+// many, 51 MB 19.6 / 21.9, 72 MB 27.5 / 27.5 (22.8 now), 95 MB 35.2 / 32.8.  Above, the part that is kept gets small
+// and the workgroups drift apart by more than they wait for each other: bfloat16 205 MB 75.9 / 67.7, 262 MB 96.1 /
+// 94.2, 268 MB 98.3 / 95.2.  float32 gains beyond the line too (268 MB 89.6 / 79.5, 300 MB 110 / 97, 400 MB 149 /
+// 150); it lies where both types do.
 template <typename T>
 constexpr int64_t kHeldMinBytes = int64_t(sizeof(T) == 4 ? 48 : 72) << 20;
 constexpr int64_t kHeldMaxBytes = int64_t(256) << 20;
 static_assert(kHeldMinBytes<float> / 4 >= int64_t(kHeldGrid) * kUnitElems, "every workgroup has a unit");
 static_assert(kHeldMinBytes<bf16_t> / 2 >= int64_t(kHeldGrid) * kUnitElems, "every workgroup has a unit");
-static_assert(kMailOffset + kHeldGrid * sizeof(uint64_t) <= kCtrlBytes, "the control block holds the mailboxes");
 
 constexpr int kChanMaxLocal = 64;   // channels a workgroup may have a part of: at most 14 units of 512 groups, and
                                     // two parts, of channels of at least 128 groups
@@ -81,13 +77,12 @@ inline uint32_t channel_groups(int64_t n, int64_t C, int64_t seg_len) {
   return uint32_t(per < most ? per : most);
 }
 
+struct ChipMail;
 template <typename T>
-hipError_t launch_held(const accept_desc& d, const UPlan& p, const T* x, uint32_t* payload, float* partials,
-                       uint64_t* mail, int polls, hipStream_t s);
-struct ChanMail;
+hipError_t launch_held(const accept_desc& d, const UPlan& p, const T* x, float* header, uint32_t* payload,
+                       ChipMail* mail, int polls, hipStream_t s, StageTimer* tm);
 template <typename T>
 hipError_t launch_channels(const accept_desc& d, const UPlan& p, const T* x, float* header, uint32_t* payload,
-                           ChanMail* mail, int polls, hipStream_t s);
-constexpr size_t kChanMailOffset = kMailOffset + kHeldGrid * sizeof(uint64_t);
+                           ChipMail* mail, int polls, hipStream_t s);
 
 }  // namespace accept

@@ -3,7 +3,8 @@
 
 namespace accept {
 
-template hipError_t launch_held<bf16_t>(const accept_desc&, const UPlan&, const bf16_t*, uint32_t*, float*, uint64_t*, int, hipStream_t);
-template hipError_t launch_channels<bf16_t>(const accept_desc&, const UPlan&, const bf16_t*, float*, uint32_t*, ChanMail*, int, hipStream_t);
+template hipError_t launch_held<bf16_t>(const accept_desc&, const UPlan&, const bf16_t*, float*, uint32_t*, ChipMail*, int, hipStream_t,
+                                        StageTimer*);
+template hipError_t launch_channels<bf16_t>(const accept_desc&, const UPlan&, const bf16_t*, float*, uint32_t*, ChipMail*, int, hipStream_t);
 
 }  // namespace accept

@@ -1,8 +1,6 @@
 // The kernels of uniform_chip.hpp.
 #pragma once
 
-#include <atomic>
-
 #include "uniform_chip.hpp"
 
 namespace accept {
@@ -13,12 +11,135 @@ namespace accept {
 // so all of them agree.  So nothing has to be emptied: a value of an earlier call bears an earlier tag.
 // (Counting the workgroups off on one counter, and the last one emptying everything, cost small tensors
 // 1.5 us.)
-struct ChanMail {
-  uint64_t first[kHeldGrid], last[kHeldGrid];  // tag and the workgroup's maximum of its first, its last channel
+struct ChipMail {
+  uint64_t first[kHeldGrid], last[kHeldGrid];  // tag and the workgroup's maximum: of its first (or only), its last channel
   uint32_t calls[kHeldGrid];
 };
+static_assert(kMailOffset + sizeof(ChipMail) <= kCtrlBytes, "the control block holds them");
 
 namespace {
+
+// One value of every workgroup of a call, exchanged through the mailboxes: the largest of all.  The wait is
+// bounded: nothing says that all workgroups run at the same time (another kernel may hold some compute
+// units).  Where a workgroup has looked `polls` times in vain, it finds the values that are missing itself, one
+// workgroup's part after the other, and posts them: those that wait share
+// the work of those that have not started, which later post the same values.  So every workgroup ends whatever else
+// runs, and the result does not depend on it.
+struct Exchange {
+  float top[kHeldBlock / kWave];
+  uint64_t missing[kHeldGrid / kWave];
+};
+__device__ __forceinline__ void post(uint64_t* box, uint32_t tag, float v) {
+  __hip_atomic_store(box, (uint64_t(tag) << 32) | f32_as_u32(v), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+// Wavefronts 0 to 3 look for a box per lane, at most `polls` times; on return (in front of a barrier) ex holds
+// what is missing and, where nothing is, the wavefronts' maxima.
+__device__ __forceinline__ void look_for_mail(const ChipMail* mail, uint32_t tag, int polls, Exchange& ex) {
+  const int tid = threadIdx.x;
+  if (tid >= kHeldGrid) return;
+  const bool box = uint32_t(tid) < gridDim.x;
+  uint64_t missing = __ballot(box);
+  uint64_t v = 0;
+  for (int i = 0; i < polls; ++i) {
+    if (box) v = __hip_atomic_load(mail->first + tid, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    missing = __ballot(box && uint32_t(v >> 32) != tag);
+    if (missing == 0) break;
+    __builtin_amdgcn_s_sleep(4);
+  }
+  const float t = wave_max(u32_as_f32(box && missing == 0 ? uint32_t(v) : 0u));
+  if ((tid & (kWave - 1)) == 0) {
+    ex.top[tid / kWave] = t;
+    ex.missing[tid / kWave] = missing;
+  }
+}
+// After look_for_mail and a barrier: how many workgroups are missing, and one of them, another for neighbouring
+// workgroups (both in scalar registers).
+__device__ __forceinline__ int missing_count(const Exchange& ex) {
+  int count = 0;
+#pragma unroll
+  for (int w = 0; w < kHeldGrid / kWave; ++w) count += __popcll((unsigned long long)ex.missing[w]);
+  return __builtin_amdgcn_readfirstlane(count);
+}
+__device__ __forceinline__ int missing_one(const Exchange& ex, int count) {
+  int skip = int(blockIdx.x) % count, found = 0;
+#pragma unroll
+  for (int w = 0; w < kHeldGrid / kWave; ++w) {
+    uint64_t m = ex.missing[w];
+    m = (uint64_t(uint32_t(__builtin_amdgcn_readfirstlane(int(uint32_t(m >> 32))))) << 32) |
+        uint32_t(__builtin_amdgcn_readfirstlane(int(uint32_t(m))));
+    const int here = __popcll((unsigned long long)m);
+    if (skip >= 0 && skip < here) {
+      for (; skip > 0; --skip) m &= m - 1;
+      found = w * kWave + __ffsll((unsigned long long)m) - 1;
+    }
+    skip -= here;
+  }
+  return found;
+}
+__device__ __forceinline__ float largest_mail(const Exchange& ex) {
+  float c = ex.top[0];
+#pragma unroll
+  for (int w = 1; w < kHeldGrid / kWave; ++w) c = fmaxf(c, ex.top[w]);
+  return c;
+}
+// Posts what is missing until nothing is; part(w): a thread's share of the largest value of workgroup w.
+template <typename Part>
+__device__ __forceinline__ void post_missing(ChipMail* mail, uint32_t tag, Exchange& ex, Part part) {
+  const int tid = threadIdx.x;
+  for (int count = missing_count(ex); count != 0; count = missing_count(ex)) {
+    const int w = missing_one(ex, count);
+    const float v = wave_max(part(w));
+    __syncthreads();
+    if ((tid & (kWave - 1)) == 0) ex.top[tid / kWave] = v;
+    __syncthreads();
+    if (tid == 0) {
+      float t = ex.top[0];
+      for (int i = 1; i < kHeldBlock / kWave; ++i) t = fmaxf(t, ex.top[i]);
+      post(mail->first + w, tag, t);
+      __builtin_amdgcn_s_waitcnt(0x0F70);  // it is there before the next look
+    }
+    __syncthreads();
+    look_for_mail(mail, tag, 1, ex);
+    __syncthreads();
+  }
+}
+
+// The codes of unit `unit`: pieces of the thread's vectors through local memory (one barrier; the caller alternates
+// between two buffers), then the parts it packs.
+template <typename T, int K, typename VecOf>
+__device__ __forceinline__ void quantize_unit(uint32_t* buf, float r, uint32_t* __restrict__ payload32, int64_t unit,
+                                              VecOf vec_of) {
+  constexpr int VEC = Elem<T>::VEC;
+  constexpr int LOADS = kUnitElems / (kHeldBlock * VEC), QPV = VEC / 4;
+  const int tid = threadIdx.x;
+  float rv[4];
+#pragma unroll
+  for (int e = 0; e < 4; ++e) rv[e] = r;
+#pragma unroll
+  for (int u = 0; u < LOADS; ++u) {
+    float f[VEC];
+    widen(vec_of(u), f);
+#pragma unroll
+    for (int h = 0; h < QPV; ++h) buf[(u * kHeldBlock + tid) * QPV + h] = quantize4<K, false>(&f[4 * h], rv, 0);
+  }
+  __syncthreads();
+  const __amdgpu_buffer_rsrc_t codes = payload_buffer(payload32 + unit * (kHeldBlock * K), kHeldBlock * K * 4);
+#pragma unroll
+  for (int i = 0; i < CodeParts<K>::PARTS; ++i) {
+    const int part = i * kHeldBlock + tid;
+    uint32_t out[CodeParts<K>::DWORDS];
+    pack_part<K>(&buf[part * CodeParts<K>::PIECES], out);
+    store_part<K>(codes, uint32_t(part * CodeParts<K>::DWORDS * 4), out);
+  }
+}
+// Workgroup b's elements behind the last whole unit, 64 of them: 8 threads take 8 each.
+template <typename T, int K>
+__device__ __forceinline__ void quantize_behind(const T* __restrict__ x, uint32_t* __restrict__ payload32, float r, int64_t N,
+                                                int64_t units, int64_t payload_bytes, int b) {
+  const int64_t g = (units * kUnitElems + int64_t(b) * kWave) / 8 + threadIdx.x;
+  if (threadIdx.x < kWave / 8 && g * 8 < N)
+    quantize_group8<T, K, false>(x, reinterpret_cast<uint8_t*>(payload32), g, N, payload_bytes, 0, [&](int64_t) { return r; });
+}
 
 // U1, and U2 + U3 for the end of the tensor, in one kernel (one range for the tensor, rounding to
 // nearest).  The range has to be known before the first element can be quantized, so the plain way
@@ -27,57 +148,48 @@ namespace {
 // reads units (16384 elements) b, b + 256, ..., keeps the last of them (float32: 7 units in registers
 // and 2 in local memory, 151 MB over the chip; bfloat16: 12 and 4, 134 MB), hands its maximum to the
 // other workgroups through a mailbox, waits for theirs, quantizes what it kept and reads the units
-// before held_first once more.  quantize_pack_kernel does the up to 16383 elements behind the last
-// whole unit; for the range every workgroup looks at 64 of them here.
+// before held_first once more.  The up to 16383 elements behind the last whole unit are shared out, 64 to a
+// workgroup, for the range and for the codes.
 //
-// The wait is bounded: nothing says that all 256 workgroups run at the same time (another kernel may
-// hold some compute units).  A workgroup that has not seen all mailboxes after `polls` looks gives
-// up, says so in its record and ends; quantize_pack_kernel then takes its units too.  So every
-// workgroup ends whatever else runs, and the result does not depend on it.
+// A workgroup that does not see all the others' maxima in time (see Exchange) no longer uses what it kept, so that
+// its registers serve for the others' parts, and reads its own units again; REST: it says so and ends, and
+// quantize_late_kernel does its units.
 //
 // Beside other work: a workgroup needs a whole compute unit (160 KiB of local memory, all registers), so
 // next to a kernel whose workgroups keep filling the chip it starts late, and the early ones give up.
-// Time of a call on one stream while another stream is busy, two reads / held (us): small elementwise
-// kernels, 100 MB float32 43 / 32, 205 MB 85 / 70, 100 MB bfloat16 53 / 39; matrix products 155 / 149,
-// 184 / 179, 160 / 155; copies of 512 MB without a pause 66 / 98, 130 / 161, 72 / 145.
+// Time of a call on one stream while another is busy, k = 8, two reads / held, held with a second kernel always /
+// now (us): small elementwise kernels, 103 MB float32 43 / 32, 28.6 / 22.2, 205 MB 85 / 70, 56 / 49, 103 MB bfloat16 53 /
+// 39, 33.6 / 26.2; matrix products beside 205 MB 184 / 179, 240 / 150, beside 103 MB bfloat16 160 / 155, 228 / 128;
+// copies of 512 MB without a pause 66 / 98, 105 / 115, 130 / 161, 162 / 160, 72 / 145, 142 / 140.
 //
-// A mailbox is one 64-bit word, value and the call's mark together, written and read with device-scope
-// accesses (they bypass the dies' second-level caches): no ordering between two words is needed.
-// quantize_pack_kernel empties the mailboxes, so that a captured call finds none of its own mark when it
-// is replayed; what a call left whose second kernel could not be launched bears another mark.
-//
-// 51.4 M float32 values (205 MB), k = 8: 59.4 us a call against 69.5 with two reads (range 32.8,
-// quantize 38.0); here 32.7 us to the mailboxes, 15 us of quantizing, 4 us of kernel end, 4.5 us for
-// the other kernel.  100 MB: 30.7 against 38.0; bfloat16 103 MB: 35.1 against 44.8.
+// 51.4 M float32 values (205 MB), k = 8: 58.3 us a call (two reads 69.5): 31 us to the mailboxes, 2 to 3 for the
+// exchange.  103 MB: 32 -> 26 us against the held pass with a second kernel and plain stores, bfloat16 103 MB 36 -> 30.
 // Stochastic rounding keeps the two reads: it is bound by its instructions, which the second read
 // hides behind.
-template <typename T, int K>
+template <typename T, int K, int SLOTS, bool REST>
 __global__ __launch_bounds__(kHeldBlock, 2) void quantize_held_kernel(const T* __restrict__ x,
                                                                       uint32_t* __restrict__ payload32,
-                                                                      float2* __restrict__ records,
-                                                                      uint64_t* __restrict__ mail, int64_t N,
+                                                                      float* __restrict__ header,
+                                                                      ChipMail* __restrict__ mail, int64_t N,
                                                                       int64_t units, int64_t held_first, int lds_units,
-                                                                      int polls, uint32_t mark) {
+                                                                      int64_t payload_bytes, int polls) {
   constexpr int VEC = Elem<T>::VEC;
   constexpr int LOADS = kUnitElems / (kHeldBlock * VEC);  // vectors per thread and unit
-  constexpr int SLOTS = kHeldUnits<T>;
   constexpr int RING = 32 / (4 * LOADS) * 2;  // units in flight while nothing is kept yet: 128 KiB per workgroup
   constexpr int WAVES = kHeldBlock / kWave;
   constexpr int LDS_UNITS = kHeldLdsUnits<T>;
-  static_assert(SLOTS * LOADS == kHeldVecs<T> && RING >= 2 && RING < SLOTS, "registers");
+  static_assert(RING >= 2 && RING < SLOTS, "registers");
   static_assert(LDS_UNITS % RING == 0 && LDS_UNITS < SLOTS, "units kept in local memory pass through the ring in whole turns");
-  constexpr int PIECES = kUnitElems / 4;
-  constexpr int QPV = VEC / 4;
-  // local memory, all 160 KiB of it: what is kept, and two buffers of pieces (the first of which the
-  // reductions use before)
+  // local memory, all 160 KiB of it: what is kept, and two buffers of pieces (the second of which the
+  // exchange uses before)
   struct Local {
     uint4 kept[LDS_UNITS][LOADS][kHeldBlock];
-    uint32_t pieces[2][PIECES];
+    uint32_t pieces[2][kUnitElems / 4];
   };
   static_assert(sizeof(Local) <= 160 * 1024, "local memory of a compute unit");
   __shared__ __attribute__((aligned(16))) Local local;
-  float* const red = reinterpret_cast<float*>(local.pieces[0]);
-  int* const red_up = reinterpret_cast<int*>(local.pieces[0]) + WAVES;
+  Exchange& ex = *reinterpret_cast<Exchange*>(local.pieces[1]);
+  const uint32_t tag = uint32_t(__builtin_amdgcn_readfirstlane(int(mail->calls[blockIdx.x]))) + 1u;
   const int tid = threadIdx.x;
   const int lane = tid & (kWave - 1), wave = tid / kWave;
 
@@ -154,81 +266,123 @@ __global__ __launch_bounds__(kHeldBlock, 2) void quantize_held_kernel(const T* _
   __builtin_amdgcn_s_waitcnt(0x0F70);  // nothing is in flight from here on, whichever slots are in use
 
   c = wave_max(c);
-  if (lane == 0) red[wave] = c;
+  if (lane == 0) ex.top[wave] = c;
   __syncthreads();
-  c = red[0];
+  if (tid == 0) {
+    c = ex.top[0];
 #pragma unroll
-  for (int w = 1; w < WAVES; ++w) c = fmaxf(c, red[w]);
-  const float mine = c;
-  if (tid == 0)
-    __hip_atomic_store(mail + blockIdx.x, (uint64_t(mark) << 32) | f32_as_u32(mine), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  __syncthreads();  // red is free again
-  if (tid < kHeldGrid) {  // wavefront w watches mailboxes 64w .. 64w+63
-    uint64_t v = 0;
-    bool all = false;
-    for (int i = 0; i < polls; ++i) {
-      v = __hip_atomic_load(mail + tid, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      all = __ballot(uint32_t(v >> 32) != mark) == 0;
-      if (all) break;
-      __builtin_amdgcn_s_sleep(4);
-    }
-    const float cw = wave_max(u32_as_f32(uint32_t(v)));
-    if (lane == 0) { red[wave] = cw; red_up[wave] = all ? 0 : 1; }
+    for (int w = 1; w < WAVES; ++w) c = fmaxf(c, ex.top[w]);
+    post(mail->first + blockIdx.x, tag, c);
+    mail->calls[blockIdx.x] = tag;
   }
   __syncthreads();
-  int up = 0;
-  c = 0.0f;
-#pragma unroll
-  for (int w = 0; w < kHeldGrid / kWave; ++w) { c = fmaxf(c, red[w]); up |= red_up[w]; }
-  up = __builtin_amdgcn_readfirstlane(up);
-  if (tid == 0) records[blockIdx.x] = make_float2(mine, up ? 0.0f : 1.0f);
-  if (up) return;
+  look_for_mail(mail, tag, polls, ex);
+  __syncthreads();
 
-  float s, r;
-  scale_from_range(c, K, s, r);
-  float rv[VEC];
-#pragma unroll
-  for (int e = 0; e < VEC; ++e) rv[e] = r;
+  float r = 0.0f;
   int buf_i = 0;
-  auto quantize_unit = [&](int ordinal, auto vec_of) {
-    uint32_t* buf = local.pieces[buf_i];
+  auto quantize = [&](int ordinal, auto vec_of) {
+    quantize_unit<T, K>(local.pieces[buf_i], r, payload32, int64_t(ordinal) * kHeldGrid + blockIdx.x, vec_of);
     buf_i ^= 1;
-#pragma unroll
-    for (int u = 0; u < LOADS; ++u) {
-      float f[VEC];
-      widen(vec_of(u), f);
-#pragma unroll
-      for (int h = 0; h < QPV; ++h) buf[(u * kHeldBlock + tid) * QPV + h] = quantize4<K, false>(&f[4 * h], &rv[4 * h], 0);
-    }
-    __syncthreads();  // double buffered: one barrier per unit
-    const uint4 a = *reinterpret_cast<const uint4*>(&buf[8 * tid]);
-    const uint4 b = *reinterpret_cast<const uint4*>(&buf[8 * tid + 4]);
-    const uint32_t P[8] = {a.x, a.y, a.z, a.w, b.x, b.y, b.z, b.w};
-    uint32_t out[K];
-    pack8<K>(P, out);
-    store_dwords<K>(payload32 + ((int64_t(ordinal) * kHeldGrid + blockIdx.x) * kHeldBlock + tid) * K, out);
   };
-  __syncthreads();  // the reductions' words are free: pieces from here on
+  auto ready = [&] {  // the range is known
+    float s;
+    scale_from_range(largest_mail(ex), K, s, r);
+    if (blockIdx.x == 0 && tid == 0) header[0] = s;
+  };
+  // (The hint decides which values the compiler keeps in registers: without it, or with it for the other type, some
+  // are spilled.)
+  const bool late = missing_count(ex) != 0;
+  if (sizeof(T) == 4 ? __builtin_expect(late, 0) : late) {
+    if constexpr (REST) {
+      if (tid == 0) mail->last[blockIdx.x] = (uint64_t(tag) << 32) | 1u;
+      return;
+    }
+    post_missing(mail, tag, ex, [&](int w) {
+      float v = 0.0f;
+      for (int64_t unit = w; unit < units; unit += kHeldGrid) {
+        const T* xu = x + unit * kUnitElems;
+        uint4 raw[LOADS];
+#pragma unroll
+        for (int u = 0; u < LOADS; ++u) raw[u] = load16_stream(xu + (u * kHeldBlock + tid) * VEC);
+#pragma unroll
+        for (int u = 0; u < LOADS; ++u) {
+          float f[VEC];
+          widen(raw[u], f);
+#pragma unroll
+          for (int e = 0; e < VEC; ++e) v = fmaxf(v, fabsf(f[e]));
+        }
+      }
+      const int64_t b = units * kUnitElems + int64_t(w) * kWave + lane;
+      return fmaxf(v, fabsf(load_one(x + (b < N ? b : N - 1))));
+    });
+    ready();
+#pragma nounroll
+    for (int o = 0; o < count; ++o) {
+      uint4 now[LOADS];
+      ask(o, now);
+      quantize(o, [&](int u) { return now[u]; });
+    }
+    quantize_behind<T, K>(x, payload32, r, N, units, payload_bytes, blockIdx.x);
+    return;
+  }
+  ready();
   // A slot that has been quantized takes a unit that was only looked at, the last of them first;
   // those loads are under way while the other kept units are quantized.  (Conditions are the same
   // in all threads.)
 #pragma unroll
   for (int j = 0; j < SLOTS; ++j) {
-    if (base + j < count) quantize_unit(base + j, [&](int u) { return kept[j][u]; });
+    if (base + j < count) quantize(base + j, [&](int u) { return kept[j][u]; });
     if (j < first) ask(first - 1 - j, kept[j]);
   }
   if (lds_units != 0) {
-    for (int q = 0; q < LDS_UNITS; ++q) quantize_unit(first + q, [&](int u) { return local.kept[q][u][tid]; });
+    for (int q = 0; q < LDS_UNITS; ++q) quantize(first + q, [&](int u) { return local.kept[q][u][tid]; });
   }
   for (int o = first - 1; o >= 0; o -= SLOTS) {
 #pragma unroll
     for (int j = 0; j < SLOTS; ++j) {
       if (o - j >= 0) {
-        quantize_unit(o - j, [&](int u) { return kept[j][u]; });
+        quantize(o - j, [&](int u) { return kept[j][u]; });
         if (o - j - SLOTS >= 0) ask(o - j - SLOTS, kept[j]);
       }
     }
   }
+  quantize_behind<T, K>(x, payload32, r, N, units, payload_bytes, blockIdx.x);
+}
+
+// Behind the held pass of the largest float32 tensors: the units of workgroups that gave up, a workgroup to each.
+template <typename T, int K>
+__global__ __launch_bounds__(kHeldBlock) void quantize_late_kernel(const T* __restrict__ x, uint32_t* __restrict__ payload32,
+                                                                   float* __restrict__ header,
+                                                                   const ChipMail* __restrict__ mail, int64_t N,
+                                                                   int64_t units, int64_t payload_bytes) {
+  constexpr int VEC = Elem<T>::VEC;
+  constexpr int LOADS = kUnitElems / (kHeldBlock * VEC);
+  const int b = blockIdx.x;
+  const uint32_t tag = mail->calls[b];  // of the call: the kernel before has raised it
+  if (mail->last[b] != ((uint64_t(tag) << 32) | 1u)) return;
+  __shared__ __attribute__((aligned(16))) uint32_t pieces[2][kUnitElems / 4];
+  __shared__ float red[kHeldGrid / kWave];
+  const int tid = threadIdx.x;
+  if (tid < kHeldGrid) {
+    const float t = wave_max(u32_as_f32(uint32_t(mail->first[tid])));
+    if ((tid & (kWave - 1)) == 0) red[tid / kWave] = t;
+  }
+  __syncthreads();
+  float c = red[0], s, r;
+#pragma unroll
+  for (int w = 1; w < kHeldGrid / kWave; ++w) c = fmaxf(c, red[w]);
+  scale_from_range(c, K, s, r);
+  if (b == 0 && tid == 0) header[0] = s;
+  int buf_i = 0;
+  for (int64_t unit = b; unit < units; unit += kHeldGrid) {
+    uint4 raw[LOADS];
+#pragma unroll
+    for (int u = 0; u < LOADS; ++u) raw[u] = load16_stream(x + unit * kUnitElems + (u * kHeldBlock + tid) * VEC);
+    quantize_unit<T, K>(pieces[buf_i], r, payload32, unit, [&](int u) { return raw[u]; });
+    buf_i ^= 1;
+  }
+  quantize_behind<T, K>(x, payload32, r, N, units, payload_bytes, b);
 }
 
 // U1, U1b, U2 and U3 of a tensor with one range per channel, in one kernel and with one read: the
@@ -262,7 +416,7 @@ struct ChanHeldGeom {
   uint32_t m_groups;          // groups of a row of the tensor
   uint32_t total, per;        // groups of the tensor, and of a workgroup
   GroupPos load_step;         // groups between two loads of a thread
-  GroupPos unit_step;         // groups of a unit
+  GroupPos part_step;         // groups between two parts of a thread
   uint32_t next_row, next_channel;  // what a step past a segment's, and past a channel's, end adds to `at`
   uint32_t shared;            // whether any channel lies in two workgroups
 };
@@ -283,13 +437,12 @@ __device__ __forceinline__ void group_advance(const ChanHeldGeom& g, GroupPos& p
   if (p.row >= g.rows) { p.row -= g.rows; p.at += g.next_channel; }
 }
 
-static_assert(kChanMailOffset + sizeof(ChanMail) <= kCtrlBytes, "the control block holds them");
 
 template <typename T, int K, int SLOTS, int LDS_UNITS>
 __global__ __launch_bounds__(kHeldBlock, 2) void quantize_channels_kernel(const T* __restrict__ x,
                                                                           uint32_t* __restrict__ payload32,
                                                                           float* __restrict__ header,
-                                                                          ChanMail* __restrict__ mail, ChanHeldGeom g,
+                                                                          ChipMail* __restrict__ mail, ChanHeldGeom g,
                                                                           int polls) {
   constexpr int VEC = Elem<T>::VEC;
   constexpr int GV = 32 / VEC;                            // vectors of a group
@@ -401,11 +554,8 @@ __global__ __launch_bounds__(kHeldBlock, 2) void quantize_channels_kernel(const 
     uint64_t* const mail_last = mail->last;
     const bool one = ch_lo == ch_hi;
     const bool watch_first = starts_inside || (one && ends_inside), watch_last = !one && ends_inside;
-    auto post = [&](uint64_t* box, uint32_t v) {
-      __hip_atomic_store(box, (uint64_t(tag) << 32) | v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    };
-    if (tid == 0 && watch_first) post(mail_first + blockIdx.x, local.top[0]);
-    if (tid == 0 && watch_last) post(mail_last + blockIdx.x, local.top[nloc - 1]);
+    if (tid == 0 && watch_first) post(mail_first + blockIdx.x, tag, u32_as_f32(local.top[0]));
+    if (tid == 0 && watch_last) post(mail_last + blockIdx.x, tag, u32_as_f32(local.top[nloc - 1]));
     __syncthreads();
     // wavefront 0 watches the first channel's other workgroups, wavefront 1 the last one's
     if ((wave == 0 && watch_first) || (wave == 1 && watch_last)) {
@@ -460,7 +610,9 @@ __global__ __launch_bounds__(kHeldBlock, 2) void quantize_channels_kernel(const 
   }
   __syncthreads();
 
-  GroupPos to = group_pos(g, q0 + uint32_t(tid));  // the group whose codes the thread writes
+  constexpr int PARTS = CodeParts<K>::PARTS;
+  GroupPos to = group_pos(g, q0 + uint32_t(tid) / PARTS);  // the group a part of whose codes the thread writes next
+  const __amdgpu_buffer_rsrc_t codes = payload_buffer(payload32, g.total * uint32_t(K * 4));
   int buf_i = 0;
   chan = 0;
   end = first_end < count ? first_end : count;
@@ -491,14 +643,16 @@ __global__ __launch_bounds__(kHeldBlock, 2) void quantize_channels_kernel(const 
 #pragma unroll
     for (int u = 0; u < LOADS; ++u) vector(u, r[u]);
     __syncthreads();  // double buffered: one barrier per unit
-    const uint4 a = *reinterpret_cast<const uint4*>(&buf[8 * tid]);
-    const uint4 b = *reinterpret_cast<const uint4*>(&buf[8 * tid + 4]);
-    const uint32_t P[8] = {a.x, a.y, a.z, a.w, b.x, b.y, b.z, b.w};
-    uint32_t out[K];
-    pack8<K>(P, out);
-    fresh(to);
-    if (g0 + uint32_t(tid) < count) store_dwords<K>(payload32 + size_t(to.at) * K, out);
-    group_advance(g, to, g.unit_step);
+#pragma unroll
+    for (int i = 0; i < PARTS; ++i) {
+      const uint32_t part = uint32_t(i * kHeldBlock + tid);
+      uint32_t out[CodeParts<K>::DWORDS];
+      pack_part<K>(&buf[part * CodeParts<K>::PIECES], out);
+      fresh(to);
+      if (g0 + part / PARTS < count)
+        store_part<K>(codes, (to.at * uint32_t(K) + part % PARTS * CodeParts<K>::DWORDS) * 4u, out);
+      group_advance(g, to, g.part_step);
+    }
   };
   if constexpr (LDS_UNITS > 0) {
     for (int q = 0; q < LDS_UNITS; ++q)
@@ -509,25 +663,26 @@ __global__ __launch_bounds__(kHeldBlock, 2) void quantize_channels_kernel(const 
     if (uint32_t(LDS_UNITS + j) < units) quantize_unit(LDS_UNITS + j, [&](int u) { return kept[(j + LDS_UNITS) % SLOTS][u]; });
 }
 
-// Mark of a call's mailboxes: a running number, never 0 (an empty mailbox).
-uint32_t next_mark() {
-  static std::atomic<uint32_t> calls{0};
-  uint32_t mark = 0;
-  while (mark == 0) mark = calls.fetch_add(1, std::memory_order_relaxed) + 1;
-  return mark;
-}
-
 }  // namespace
 
 template <typename T>
-hipError_t launch_held(const accept_desc& d, const UPlan& p, const T* x, uint32_t* payload, float* partials,
-                       uint64_t* mail, int polls, hipStream_t s) {
-  float2* records = reinterpret_cast<float2*>(partials);
-  const uint32_t mark = next_mark();
-#define ACCEPT_HELD(KK)                                                                                          \
-  case KK:                                                                                                       \
-    hipLaunchKernelGGL((quantize_held_kernel<T, KK>), dim3(kHeldGrid), dim3(kHeldBlock), 0, s, x, payload, records, \
-                       mail, p.N, p.held_units, p.held_first, p.held_lds, polls, mark);                              \
+hipError_t launch_held(const accept_desc& d, const UPlan& p, const T* x, float* header, uint32_t* payload,
+                       ChipMail* mail, int polls, hipStream_t s, StageTimer* tm) {
+  const int64_t payload_bytes = (p.N * d.bits + 7) / 8;
+  constexpr bool kTwo = sizeof(T) == 4;  // bfloat16 has one form
+#define ACCEPT_HELD(KK)                                                                                                \
+  case KK:                                                                                                             \
+    if (kTwo && p.held_rest) {                                                                                         \
+      hipLaunchKernelGGL((quantize_held_kernel<T, KK, kTwo ? kHeldLargeUnits : kHeldUnits<T>, kTwo>), dim3(kHeldGrid), \
+                         dim3(kHeldBlock), 0, s, x, payload, header, mail, p.N, p.held_units, p.held_first, p.held_lds, \
+                         payload_bytes, polls);                                                                        \
+      mark(tm, s);                                                                                                     \
+      hipLaunchKernelGGL((quantize_late_kernel<T, KK>), dim3(kHeldGrid), dim3(kHeldBlock), 0, s, x, payload,               \
+                         header, mail, p.N, p.held_units, payload_bytes);                                              \
+    } else {                                                                                                           \
+      hipLaunchKernelGGL((quantize_held_kernel<T, KK, kHeldUnits<T>, false>), dim3(kHeldGrid), dim3(kHeldBlock), 0, s, x, \
+                         payload, header, mail, p.N, p.held_units, p.held_first, p.held_lds, payload_bytes, polls);    \
+    }                                                                                                                  \
     break;
   switch (d.bits) {
     ACCEPT_HELD(2) ACCEPT_HELD(3) ACCEPT_HELD(4) ACCEPT_HELD(5) ACCEPT_HELD(6) ACCEPT_HELD(7) ACCEPT_HELD(8)
@@ -539,7 +694,7 @@ hipError_t launch_held(const accept_desc& d, const UPlan& p, const T* x, uint32_
 
 template <typename T>
 hipError_t launch_channels(const accept_desc& d, const UPlan& p, const T* x, float* header, uint32_t* payload,
-                           ChanMail* mail, int polls, hipStream_t s) {
+                           ChipMail* mail, int polls, hipStream_t s) {
   ChanHeldGeom g{};
   g.seg_groups = uint32_t(p.seg_len / 32);
   g.rows = uint32_t(d.n);
@@ -558,7 +713,7 @@ hipError_t launch_channels(const accept_desc& d, const UPlan& p, const T* x, flo
   g.next_row = g.m_groups - g.seg_groups;
   g.next_channel = g.seg_groups - g.rows * g.m_groups;
   g.load_step = step(uint32_t(kHeldBlock * p.vec / 32));
-  g.unit_step = step(kHeldBlock);
+  g.part_step = step(uint32_t(kHeldBlock / (d.bits == 6 || d.bits == 8 ? 2 : 1)));
   const uint32_t per_channel = g.rows * g.seg_groups;
   static_assert(kChanMaxUnits<T> * kHeldBlock * 32 / kChanMinChannel + 2 <= kChanMaxLocal, "channels of a workgroup");
   g.shared = g.per % per_channel != 0 ? 1u : 0u;

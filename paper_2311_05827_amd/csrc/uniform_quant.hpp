@@ -75,22 +75,65 @@ __device__ __forceinline__ uint32_t quantize4(const float* f, const float* r, ui
   return piece;
 }
 
-// U3 for 32 consecutive codes: eight 4k-bit pieces (in the top bits of a dword each) -> k dwords
-// of the big-endian bit stream, each dword byte-swapped into memory order.
+// U3: a group of 32 consecutive codes, eight 4k-bit pieces (in the top bits of a dword each), is k dwords of the
+// big-endian bit stream, each byte-swapped into memory order.  A thread packs one part of it at a time: the
+// largest of whole dwords that one store instruction takes (k = 8 and 6: half a group, 4 and 3 dwords), so that the
+// 64 lanes' parts lie together in memory, or the whole group (k = 5 and 7 have no such parts).
 template <int K>
-__device__ __forceinline__ void pack8(const uint32_t (&P)[8], uint32_t (&out)[K]) {
-  constexpr int W = 4 * K;
+struct CodeParts {
+  static constexpr int PARTS = K == 6 || K == 8 ? 2 : 1;
+  static constexpr int PIECES = 8 / PARTS, DWORDS = K / PARTS;
+  static constexpr bool ONE_STORE = DWORDS <= 4;
+};
+template <int K>
+__device__ __forceinline__ void pack_part(const uint32_t* pieces, uint32_t (&out)[CodeParts<K>::DWORDS]) {
+  constexpr int W = 4 * K, NP = CodeParts<K>::PIECES;
+  uint32_t P[NP];
 #pragma unroll
-  for (int o = 0; o < K; ++o) {
+  for (int i = 0; i < NP; i += 4) {
+    const uint4 v = *reinterpret_cast<const uint4*>(&pieces[i]);
+    P[i] = v.x; P[i + 1] = v.y; P[i + 2] = v.z; P[i + 3] = v.w;
+  }
+#pragma unroll
+  for (int o = 0; o < CodeParts<K>::DWORDS; ++o) {
     uint32_t w = 0;
 #pragma unroll
-    for (int i = 0; i < 8; ++i) {
+    for (int i = 0; i < NP; ++i) {
       const int at = W * i - 32 * o;  // first bit of the piece, counted from the dword's first bit
       if (at >= 0 && at < 32) w |= P[i] >> at;
       if (at < 0 && at > -W) w |= P[i] << -at;
     }
     out[o] = __builtin_bswap32(w);
   }
+}
+// Stores a part at byte `at` of the buffer.  Where the lanes' parts lie together, the stores write through the
+// second-level cache: the lines stay in it for whoever reads the payload next, and none is left dirty for the end
+// of the kernel, which the next one's start waits for.
+// Plain / streaming / written through (us): held pass, 103 MB float32, k = 4 27.7 / 25.7 / 25.5 and with
+// the decoder behind it 46.4 / 46.2 / 44.6; 64 x 256 x 3136 bfloat16 with a range per channel, k = 6 33.6 / 30.3 / 30.4 and
+// 55.3 / 60.5 / 52.7; stochastic, 205 MB, k = 4 84.9 plain, 81.0.  (With parts that do not lie together, k = 8 as
+// whole groups: 30.6 plain, 32.2 written through.)
+template <int K>
+__device__ __forceinline__ void store_part(__amdgpu_buffer_rsrc_t payload, uint32_t at, const uint32_t (&v)[CodeParts<K>::DWORDS]) {
+  constexpr int ND = CodeParts<K>::DWORDS;
+    constexpr int kWriteThrough = 16;  // the instruction's sc1 bit
+  typedef uint32_t v2u_t __attribute__((ext_vector_type(2)));
+  typedef uint32_t v3u_t __attribute__((ext_vector_type(3)));
+  if constexpr (ND == 2) {
+    __builtin_amdgcn_raw_buffer_store_b64(v2u_t{v[0], v[1]}, payload, at, 0, kWriteThrough);
+  } else if constexpr (ND == 3) {
+    __builtin_amdgcn_raw_buffer_store_b96(v3u_t{v[0], v[1], v[2]}, payload, at, 0, kWriteThrough);
+  } else if constexpr (ND == 4) {
+    __builtin_amdgcn_raw_buffer_store_b128(v4u_t{v[0], v[1], v[2], v[3]}, payload, at, 0, kWriteThrough);
+  } else {
+    __builtin_amdgcn_raw_buffer_store_b128(v4u_t{v[0], v[1], v[2], v[3]}, payload, at, 0, 0);
+    if constexpr (ND == 5) __builtin_amdgcn_raw_buffer_store_b32(v[4], payload, at + 16, 0, 0);
+    if constexpr (ND == 7) __builtin_amdgcn_raw_buffer_store_b96(v3u_t{v[4], v[5], v[6]}, payload, at + 16, 0, 0);
+  }
+}
+// `bytes` of payload from p on, as a buffer (p the same in all lanes).
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t payload_buffer(uint32_t* p, uint32_t bytes) {
+  return __builtin_amdgcn_make_buffer_rsrc(p, 0, int(bytes), 0x00020000);
 }
 
 // k-bit code of a signed value.
