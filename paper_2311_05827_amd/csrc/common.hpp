@@ -197,6 +197,25 @@ __device__ __forceinline__ void store_dwords_stream(uint32_t* p, const uint32_t 
   }
 }
 
+// Payload stores that write through the second-level cache: the lines stay in it for whoever reads the payload next,
+// and none is left dirty for the end of the kernel, which the next one's start waits for.  For wavefronts whose
+// lanes' dwords lie together (lines written in parts cost a trip to memory each).  The instruction takes a buffer
+// (`bytes` from p on, p the same in all lanes) and a byte offset.
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t payload_buffer(void* p, uint32_t bytes) {
+  return __builtin_amdgcn_make_buffer_rsrc(p, 0, int(bytes), 0x00020000);
+}
+template <int ND>
+__device__ __forceinline__ void store_through(__amdgpu_buffer_rsrc_t payload, uint32_t at, const uint32_t (&v)[ND]) {
+  static_assert(ND >= 1 && ND <= 4, "one instruction");
+  constexpr int kWriteThrough = 16;  // the instruction's sc1 bit
+  typedef uint32_t v2u_t __attribute__((ext_vector_type(2)));
+  typedef uint32_t v3u_t __attribute__((ext_vector_type(3)));
+  if constexpr (ND == 1) __builtin_amdgcn_raw_buffer_store_b32(v[0], payload, at, 0, kWriteThrough);
+  if constexpr (ND == 2) __builtin_amdgcn_raw_buffer_store_b64(v2u_t{v[0], v[1]}, payload, at, 0, kWriteThrough);
+  if constexpr (ND == 3) __builtin_amdgcn_raw_buffer_store_b96(v3u_t{v[0], v[1], v[2]}, payload, at, 0, kWriteThrough);
+  if constexpr (ND == 4) __builtin_amdgcn_raw_buffer_store_b128(v4u_t{v[0], v[1], v[2], v[3]}, payload, at, 0, kWriteThrough);
+}
+
 __device__ __forceinline__ void widen(const uint4 v, float (&f)[4]) {
   f[0] = u32_as_f32(v.x); f[1] = u32_as_f32(v.y); f[2] = u32_as_f32(v.z); f[3] = u32_as_f32(v.w);
 }

@@ -505,13 +505,31 @@ __device__ __forceinline__ void columns_to_planes(const uint32_t* a, uint32_t (&
   }
 }
 
+// The planes of a wavefront's items (float32, k <= 4: at most four dwords a lane, one lane's behind the other's), written
+// through the cache.  The first lane's item is the first in memory.  64 x 802816, k = 4, streaming / written through:
+// 46.9 / 46.2 us a call, 87.3 / 81.0 with the decoder behind it.  (bfloat16's eight dwords, two stores that
+// leave gaps: 33.1 / 38.2 us; plain stores 33.6 and with the decoder 59.0 / 54.2: streaming ones are kept.)
+// Smaller tensors lose as much in the call as the reader gains: 64 x 200704, k = 4, 19.8 / 20.0 and 32.0 / 31.5.
+constexpr double kThroughValues = 1 << 25;
+template <int NDW, int N>
+__device__ __forceinline__ void store_planes(uint8_t* dst, const uint32_t (&out)[N]) {
+  const uint64_t at = uint64_t(reinterpret_cast<uintptr_t>(dst));
+  const uint64_t first = (uint64_t(uint32_t(__builtin_amdgcn_readfirstlane(int(uint32_t(at >> 32))))) << 32) |
+                         uint32_t(__builtin_amdgcn_readfirstlane(int(uint32_t(at))));
+  uint32_t v[NDW];
+#pragma unroll
+  for (int i = 0; i < NDW; ++i) v[i] = out[i];
+  store_through<NDW>(payload_buffer(reinterpret_cast<void*>(first), kWave * NDW * 4), uint32_t(at - first), v);
+}
+
 // End of an item: bit counts from the finished plane bytes, payload store, float32 partial
 // sums (at most 8*VEC terms) folded into the thread's float64 sums.  A lane whose item lies
 // beyond its row group (the ragged end of the last wave-item of a group) carries a copy of the
 // group's last item: it stores the same bytes to the same place and counts nothing.
 template <int K, int VEC, bool RAGGED = false>
 __device__ __forceinline__ void finish_item(const uint32_t (&acc)[VEC][(K + 3) / 4], float (&h32)[K], float sx32,
-                                            uint8_t* __restrict__ dst, bool counts, EncodeStats<K>& st) {
+                                            uint8_t* __restrict__ dst, bool counts, EncodeStats<K>& st,
+                                            bool through = false) {
   constexpr int NDW = (VEC * K + 3) / 4;
   constexpr int CW = (VEC + 3) / 4;
   constexpr bool SELECT = VEC > 1 && K <= 4;  // by byte selections, four columns at a time
@@ -529,6 +547,7 @@ __device__ __forceinline__ void finish_item(const uint32_t (&acc)[VEC][(K + 3) /
       for (int p = 0; p < K; ++p) pw[p][w] = planes[p];
     }
     if constexpr (RAGGED) __builtin_memcpy(dst, out, sizeof(out));
+    else if (NDW <= 4 && through) store_planes<(NDW <= 4 ? NDW : 1)>(dst, out);
     else store_dwords_stream<NDW>(reinterpret_cast<uint32_t*>(dst), out);
   } else {
     if constexpr (VEC > 1) {
@@ -742,6 +761,7 @@ struct WorkQueue {
   uint32_t first;     // 64 * group
   uint32_t sweep;     // wave-items all groups take per sweep
   uint32_t count;     // queue positions 0 .. count-1 exist
+  bool through;       // planes are written through the cache (see store_planes)
   uint32_t drawn;     // positions handed out without the counter: two per wavefront of the group
 };
 __device__ __forceinline__ uint32_t queue_to_wave_item(uint32_t c, const WorkQueue& q) {
@@ -836,7 +856,7 @@ __device__ __forceinline__ void encode_stream(const Tables& tb, const T* __restr
 #pragma unroll
     for (int p = 0; p < K; ++p) h32[p] *= sum_factor(tb);
     finish_item<K, VEC, RAGGED>(acc, h32, sx32, payload + uint64_t(ca.g) * m * uint32_t(K) + ca.jv * uint32_t(VEC * K), ca.counts,
-                        st);
+                                st, q.through);
     cur = nxt;
     nxt = q.drawn + uint32_t(__builtin_amdgcn_readfirstlane(int(after_v)));
     ca = na;
@@ -1077,6 +1097,7 @@ __global__ __launch_bounds__(kEncBlock) void mbq_encode_kernel(const T* __restri
         rest > q.first ? (rest - q.first < uint32_t(kGroupSlots) ? rest - q.first : uint32_t(kGroupSlots)) : 0u;
     q.count = full_sweeps * uint32_t(kGroupSlots) + extra;
   }
+  q.through = sizeof(T) == 4 && call.n_elems >= kThroughValues;
   q.drawn = 2u * group_waves;
   const uint32_t cur = uint32_t(__builtin_amdgcn_readfirstlane(
       int((blockIdx.x - group * uint32_t(kGroupBlocks)) * uint32_t(kEncWaves) + uint32_t(tid) / uint32_t(kWave))));

@@ -83,7 +83,6 @@ template <int K>
 struct CodeParts {
   static constexpr int PARTS = K == 6 || K == 8 ? 2 : 1;
   static constexpr int PIECES = 8 / PARTS, DWORDS = K / PARTS;
-  static constexpr bool ONE_STORE = DWORDS <= 4;
 };
 template <int K>
 __device__ __forceinline__ void pack_part(const uint32_t* pieces, uint32_t (&out)[CodeParts<K>::DWORDS]) {
@@ -106,9 +105,7 @@ __device__ __forceinline__ void pack_part(const uint32_t* pieces, uint32_t (&out
     out[o] = __builtin_bswap32(w);
   }
 }
-// Stores a part at byte `at` of the buffer.  Where the lanes' parts lie together, the stores write through the
-// second-level cache: the lines stay in it for whoever reads the payload next, and none is left dirty for the end
-// of the kernel, which the next one's start waits for.
+// Stores a part at byte `at` of the buffer; where the lanes' parts lie together, through the cache.
 // Plain / streaming / written through (us): held pass, 103 MB float32, k = 4 27.7 / 25.7 / 25.5 and with
 // the decoder behind it 46.4 / 46.2 / 44.6; 64 x 256 x 3136 bfloat16 with a range per channel, k = 6 33.6 / 30.3 / 30.4 and
 // 55.3 / 60.5 / 52.7; stochastic, 205 MB, k = 4 84.9 plain, 81.0.  (With parts that do not lie together, k = 8 as
@@ -116,24 +113,14 @@ __device__ __forceinline__ void pack_part(const uint32_t* pieces, uint32_t (&out
 template <int K>
 __device__ __forceinline__ void store_part(__amdgpu_buffer_rsrc_t payload, uint32_t at, const uint32_t (&v)[CodeParts<K>::DWORDS]) {
   constexpr int ND = CodeParts<K>::DWORDS;
-    constexpr int kWriteThrough = 16;  // the instruction's sc1 bit
-  typedef uint32_t v2u_t __attribute__((ext_vector_type(2)));
-  typedef uint32_t v3u_t __attribute__((ext_vector_type(3)));
-  if constexpr (ND == 2) {
-    __builtin_amdgcn_raw_buffer_store_b64(v2u_t{v[0], v[1]}, payload, at, 0, kWriteThrough);
-  } else if constexpr (ND == 3) {
-    __builtin_amdgcn_raw_buffer_store_b96(v3u_t{v[0], v[1], v[2]}, payload, at, 0, kWriteThrough);
-  } else if constexpr (ND == 4) {
-    __builtin_amdgcn_raw_buffer_store_b128(v4u_t{v[0], v[1], v[2], v[3]}, payload, at, 0, kWriteThrough);
+  if constexpr (ND <= 4) {
+    store_through<ND>(payload, at, v);
   } else {
+    typedef uint32_t v3u_t __attribute__((ext_vector_type(3)));
     __builtin_amdgcn_raw_buffer_store_b128(v4u_t{v[0], v[1], v[2], v[3]}, payload, at, 0, 0);
     if constexpr (ND == 5) __builtin_amdgcn_raw_buffer_store_b32(v[4], payload, at + 16, 0, 0);
     if constexpr (ND == 7) __builtin_amdgcn_raw_buffer_store_b96(v3u_t{v[4], v[5], v[6]}, payload, at + 16, 0, 0);
   }
-}
-// `bytes` of payload from p on, as a buffer (p the same in all lanes).
-__device__ __forceinline__ __amdgpu_buffer_rsrc_t payload_buffer(uint32_t* p, uint32_t bytes) {
-  return __builtin_amdgcn_make_buffer_rsrc(p, 0, int(bytes), 0x00020000);
 }
 
 // k-bit code of a signed value.
