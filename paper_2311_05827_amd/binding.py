@@ -1,4 +1,4 @@
-"""ctypes binding of libaccept.so: argument marshalling only.
+"""Binding of libaccept.so (ctypes, and native code for the frequent calls): argument marshalling only.
 
 Every step of the compression path runs in the library's HIP kernels; this module turns
 PyTorch device tensors into pointers, allocates the output buffers with ``torch.empty`` and
@@ -80,6 +80,10 @@ def _load():
 
 
 lib = _load()
+try:
+    from . import _native   # the calls below for plain tensors, without the interpreter
+except ImportError as e:
+    raise ImportError("%s: rebuild with `python -m paper_2311_05827_amd.build`" % e) from e
 
 
 def status_string(status):
@@ -123,8 +127,10 @@ def accept_stage_name(desc, is_decompress, i):
 
 
 # ---------------------------------------------------------------------- device-side calls
-# A small tensor's call is host time: 13-15 us in this module's first form, of which the library's
-# launches are 5.  So sizes are asked for once per geometry, tensors are looked at with a handful of
+# A small tensor's call is host time.  accept_compress, accept_decompress and accept_mbq_compress_first go
+# through csrc/native.cpp, which makes the checks below and the call in one step; whatever it does not
+# take (its answer is negative then, and nothing has been done) comes here.
+# Here sizes are asked for once per geometry, tensors are looked at with a handful of
 # attribute reads, and pointers and the stream travel as plain integers: 6-8 us.
 _DTYPES = (torch.float32, torch.bfloat16)   # by F32 / BF16
 _GEOMETRY_BYTES = Desc.seed.offset          # the fields before seed and t: all that sizes depend on
@@ -249,10 +255,13 @@ def accept_compress(desc, x, alpha_prev=None, header=None, payload=None, workspa
         header = h if header is None else header
         payload = p if payload is None else payload
         workspace = w if workspace is None else workspace
-    _check_compress_args("accept_compress", desc, x, alpha_prev, header, payload, workspace, True)
-    st = lib.accept_compress(ctypes.byref(desc), _ptr(x), _ptr(alpha_prev), _ptr(header), _ptr(payload),
-                             _ptr(workspace), _stream_handle())
-    _check(st, "accept_compress")
+    st = _native.compress(desc, x, alpha_prev, header, payload, workspace, False)
+    if st < 0:
+        _check_compress_args("accept_compress", desc, x, alpha_prev, header, payload, workspace, True)
+        st = lib.accept_compress(ctypes.byref(desc), _ptr(x), _ptr(alpha_prev), _ptr(header), _ptr(payload),
+                                 _ptr(workspace), _stream_handle())
+    if st != 0:
+        _check(st, "accept_compress")
     return header, payload
 
 
@@ -268,12 +277,16 @@ def accept_compress_noalloc(desc, x, alpha_prev, header, payload):
 
 def accept_decompress(desc, header, payload, out=None):
     """Enqueue decompression on the current stream; returns the flat x_hat device tensor."""
-    _check_decompress_args("accept_decompress", desc, header, payload)
     if out is None:
+        _check_decompress_args("accept_decompress", desc, header, payload)
         out = torch.empty(desc.n * desc.m, dtype=_DTYPES[desc.out_dtype], device=payload.device)
-    _check_out("accept_decompress", desc, out)
-    st = lib.accept_decompress(ctypes.byref(desc), _ptr(header), _ptr(payload), _ptr(out), _stream_handle())
-    _check(st, "accept_decompress")
+    st = _native.decompress(desc, header, payload, out)
+    if st < 0:
+        _check_decompress_args("accept_decompress", desc, header, payload)
+        _check_out("accept_decompress", desc, out)
+        st = lib.accept_decompress(ctypes.byref(desc), _ptr(header), _ptr(payload), _ptr(out), _stream_handle())
+    if st != 0:
+        _check(st, "accept_decompress")
     return out
 
 
@@ -298,10 +311,13 @@ def accept_mbq_compress_first(desc, x, header=None, payload=None, workspace=None
         header = h if header is None else header
         payload = p if payload is None else payload
         workspace = w if workspace is None else workspace
-    _check_compress_args("accept_mbq_compress_first", desc, x, None, header, payload, workspace, False)
-    st = lib.accept_mbq_compress_first(ctypes.byref(desc), _ptr(x), _ptr(header), _ptr(payload), _ptr(workspace),
-                                       _stream_handle())
-    _check(st, "accept_mbq_compress_first")
+    st = _native.compress(desc, x, None, header, payload, workspace, True)
+    if st < 0:
+        _check_compress_args("accept_mbq_compress_first", desc, x, None, header, payload, workspace, False)
+        st = lib.accept_mbq_compress_first(ctypes.byref(desc), _ptr(x), _ptr(header), _ptr(payload), _ptr(workspace),
+                                           _stream_handle())
+    if st != 0:
+        _check(st, "accept_mbq_compress_first")
     return header, payload
 
 

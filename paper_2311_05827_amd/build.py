@@ -9,12 +9,14 @@ import os
 import shutil
 import subprocess
 import sys
+import sysconfig
 from concurrent.futures import ThreadPoolExecutor
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB_PATH = os.path.join(HERE, "libaccept.so")
+NATIVE_PATH = os.path.join(HERE, "_native.so")  # csrc/native.cpp: the Python binding's calls
 SOURCES = ["api.hip", "uniform.hip", "uniform_chip_f32.hip", "uniform_chip_bf16.hip", "mbq.hip"]
 
 HIPCC_FLAGS = [
@@ -47,14 +49,32 @@ def _compile(hipcc, src, obj):
     return src, r.returncode, (r.stdout + r.stderr), " ".join(cmd)
 
 
+def torch_lib():
+    import torch
+    return os.path.join(os.path.dirname(torch.__file__), "lib")
+
+
+def _compile_native(obj):
+    """The binding's host code, against the installed PyTorch's headers (no device code: plain g++)."""
+    import torch
+    from torch.utils.cpp_extension import include_paths
+    cmd = ["g++", "-O2", "-std=c++17", "-fPIC", "-Wall",
+           "-D_GLIBCXX_USE_CXX11_ABI=%d" % int(torch._C._GLIBCXX_USE_CXX11_ABI)]
+    for path in include_paths() + [sysconfig.get_paths()["include"]]:
+        cmd += ["-isystem", path]
+    cmd += ["-I", os.path.join(ROOT, "include"), "-c", os.path.join(CSRC, "native.cpp"), "-o", obj]
+    return subprocess.run(cmd, capture_output=True, text=True)
+
+
 def build(verbose=True):
-    """Compile every HIP source and link libaccept.so.  Always recompiles."""
+    """Compile every HIP source and link libaccept.so, then the binding's _native.so.  Always recompiles."""
     hipcc = hipcc_path()
     lib_path = LIB_PATH
     bdir = os.path.join(HERE, "_build")
     os.makedirs(bdir, exist_ok=True)
     objs = [os.path.join(bdir, s.replace(".hip", ".o")) for s in SOURCES]
-    with ThreadPoolExecutor(max_workers=len(SOURCES)) as ex:
+    with ThreadPoolExecutor(max_workers=len(SOURCES) + 1) as ex:
+        compiling_native = ex.submit(_compile_native, os.path.join(bdir, "native.o"))
         results = list(ex.map(lambda so: _compile(hipcc, so[0], so[1]), zip(SOURCES, objs)))
     for src, rc, out, cmd in results:
         noise = "packed-fp32-ops' is not a recognized feature"
@@ -69,8 +89,17 @@ def build(verbose=True):
     if r.returncode != 0:
         raise RuntimeError("link failed\n%s\n%s" % (" ".join(link), r.stdout + r.stderr))
     os.replace(tmp, lib_path)
+    native = compiling_native.result()
+    if native.returncode != 0:
+        raise RuntimeError("g++ failed on native.cpp\n%s\n%s" % (" ".join(native.args), native.stdout + native.stderr))
+    link = ["g++", "-shared", "-o", NATIVE_PATH + ".tmp", os.path.join(bdir, "native.o"), "-L" + HERE, "-l:libaccept.so",
+            "-L" + torch_lib(), "-ltorch_python", "-ltorch_cpu", "-lc10", "-Wl,-rpath,$ORIGIN"]
+    r = subprocess.run(link, capture_output=True, text=True)
+    if r.returncode != 0:
+        raise RuntimeError("link failed\n%s\n%s" % (" ".join(link), r.stdout + r.stderr))
+    os.replace(NATIVE_PATH + ".tmp", NATIVE_PATH)
     if verbose:
-        print("built", lib_path, file=sys.stderr)
+        print("built", lib_path, "and", NATIVE_PATH, file=sys.stderr)
     return lib_path
 
 

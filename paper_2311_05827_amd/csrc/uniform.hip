@@ -8,6 +8,7 @@
 // compressor is one LDS round trip of already-quantized 4-code "pieces" (4k bits each):
 // 8 pieces = 32 codes = exactly k dwords for every k, so one lane can emit whole dwords and
 // no global atomics are needed even when codes straddle dword boundaries.
+#include <atomic>
 #include <type_traits>
 
 #include "uniform_chip.hpp"
@@ -1232,9 +1233,13 @@ hipError_t decompress_typed(const accept_desc& d, const float* header, const uin
 }  // namespace
 
 int compute_units() {
+  constexpr int kDevices = 64;
+  static std::atomic<int> known[kDevices];  // of each device, once it has been asked for; 0 before
   int dev = -1, units = 0;
   if (hipGetDevice(&dev) != hipSuccess) return 0;
+  if (dev >= 0 && dev < kDevices && (units = known[dev].load(std::memory_order_relaxed)) != 0) return units;
   if (hipDeviceGetAttribute(&units, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) return 0;
+  if (dev >= 0 && dev < kDevices) known[dev].store(units, std::memory_order_relaxed);
   return units;
 }
 
