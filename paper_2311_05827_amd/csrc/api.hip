@@ -249,7 +249,7 @@ const char* accept_stage_name(const accept_desc* desc, int is_decompress, int i)
   if (desc->scheme == ACCEPT_MBQ) {
     static const char* const names[] = {"mbq_encode", "mbq_finalize"};
     static const char* const names_plain[] = {"mbq_encode_plain", "mbq_finalize"};
-    return i < 2 ? (plain ? names_plain[i] : names[i]) : nullptr;
+    return i < (make_mplan(*desc).finish ? 1 : 2) ? (plain ? names_plain[i] : names[i]) : nullptr;
   }
   if (plain) {
     static const char* const names[] = {"range", "range_finalize", "quantize_plain"};

@@ -986,12 +986,14 @@ struct MbqCall {
   double n_elems;
   double beta;  // weight of the previous coefficients in the moving average: min(0.9, (1+t)/(10+t))
 };
+constexpr int kDoneCounter = 32;  // word of the counters (between two work counters) that counts off the workgroups
 
 // End of an encode kernel (M4): the workgroup adds up its threads' statistics in a fixed order
 // and stores one record.  The counts are added as integers: 8 instructions per statistic and
 // wavefront instead of 30 (a thread's counts stay below 2^28: a thread sees a few parts in 2^17 of
 // the tensor), which at k = 4 are 10 of the 15.
-template <int K>
+// FINISH: past the second-level cache, for a workgroup of another die that reads it in this kernel.
+template <int K, bool FINISH = false>
 __device__ __forceinline__ void store_record(const EncodeStats<K>& st, const MbqCall& call, WaveTotals& buf) {
   constexpr int NPAIR = K * (K - 1) / 2;
   constexpr int NSTAT = nstat_of(K);
@@ -1015,7 +1017,9 @@ __device__ __forceinline__ void store_record(const EncodeStats<K>& st, const Mbq
   if (tid < NSTAT) {
     double total = buf.v[0][tid];
     for (int w = 1; w < nwaves; ++w) total += buf.v[w][tid];
-    call.records[int64_t(tid) * gridDim.x + blockIdx.x] = total;
+    double* const rec = call.records + int64_t(tid) * gridDim.x + blockIdx.x;
+    if constexpr (FINISH) __hip_atomic_store(rec, total, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    else *rec = total;
   }
 }
 
@@ -1027,13 +1031,18 @@ __device__ __forceinline__ void store_record(const EncodeStats<K>& st, const Mbq
 // compiler has 128 (24 and 154 spilled; k = 8, 128 x 160: the whole call 27.0 -> 26.3 us).
 constexpr int kFinalizeBlock = 1024;
 constexpr int finalize_block(int k) { return k <= 6 ? kFinalizeBlock : k == 7 ? 768 : 512; }
-// Sum of nrec records by one wavefront, four loads in flight; every lane has it.
-__device__ __forceinline__ double sum_records(const double* __restrict__ rec, int nrec, int lane) {
+// Sum of nrec records by one wavefront, four loads in flight; every lane has it.  FRESH: records that
+// other workgroups have written in this kernel.
+template <bool FRESH = false>
+__device__ __forceinline__ double sum_records(const double* rec, int nrec, int lane) {
+  auto one = [&](int b) {
+    return FRESH ? __hip_atomic_load(rec + b, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : rec[b];
+  };
   double a = 0.0;
   for (int b = lane; b < nrec; b += 4 * kWave) {
     double v[4];
 #pragma unroll
-    for (int u = 0; u < 4; ++u) v[u] = b + u * kWave < nrec ? rec[b + u * kWave] : 0.0;
+    for (int u = 0; u < 4; ++u) v[u] = b + u * kWave < nrec ? one(b + u * kWave) : 0.0;
     a += (v[0] + v[1]) + (v[2] + v[3]);
   }
   return wave_sum(a);
@@ -1055,6 +1064,37 @@ __global__ __launch_bounds__(finalize_block(K)) void mbq_finalize_kernel(MbqCall
   if (tid == 0) solve_and_write_header<K>(tot, alpha_prev, call.n_elems, call.beta, call.header);
 }
 
+// The same at the end of an encode kernel of few workgroups: each counts itself off when its record is written, and
+// the last one adds them up, in the finalize kernel's order, and solves.  No one waits for another.
+// A launch less is 3.6 us of host time; on the device, encode and finalize kernels / this (us, replayed graphs, k = 2 and
+// 4): 16 x 2048 float32 7.1 / 6.8, 9.9 / 10.0; 64 x 16384 (64 workgroups) 7.7 / 7.4, 10.3 / 10.5; 64 x 50000 (196: the
+// counter, one address, takes 12 ns each) 8.8 / 9.7, 11.2 / 12.6.
+constexpr int kFinishGridMax = 64;
+template <int K>
+__device__ __forceinline__ void finish_in_last_workgroup(const MbqCall& call, const float (&alpha_prev)[K], WaveTotals& buf) {
+  constexpr int NSTAT = nstat_of(K);
+  const int tid = threadIdx.x, wave = tid / kWave, lane = tid & (kWave - 1);
+  const int nrec = int(gridDim.x);
+  __shared__ int last;
+  __builtin_amdgcn_s_waitcnt(0x0F70);  // this thread's part of the record is written
+  __syncthreads();
+  if (tid == 0) {
+    const uint32_t before = __hip_atomic_fetch_add(call.counters + kDoneCounter, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    last = before + 1u == uint32_t(nrec) ? 1 : 0;
+  }
+  __syncthreads();
+  if (__builtin_amdgcn_readfirstlane(last) == 0) return;
+  double* tot = buf.v[0];
+  for (int s = wave; s < NSTAT; s += kEncWaves) {
+    const double a = sum_records<true>(call.records + int64_t(s) * nrec, nrec, lane);
+    if (lane == 0) tot[s] = a;
+  }
+  if (tid < kMaxGroups) call.counters[tid * kCounterStride] = 0u;
+  if (tid == 0) call.counters[kDoneCounter] = 0u;
+  __syncthreads();
+  if (tid == 0) solve_and_write_header<K>(tot, alpha_prev, call.n_elems, call.beta, call.header);
+}
+
 // Fused M1..M4.  Complete row groups go through the pipelined stream: row r of the next
 // wave-item is requested as soon as row r of the current one has been consumed, so a wavefront
 // always has loads in flight while it works; the first wave-item's rows are requested before
@@ -1063,7 +1103,7 @@ __global__ __launch_bounds__(finalize_block(K)) void mbq_finalize_kernel(MbqCall
 // column per thread.  RAGGED: m is not a multiple of VEC, so rows start at any alignment; vectors
 // all the same, and the last m % VEC columns one per thread (15 x 390403 float32, k = 3: this kernel
 // 12.0 us and the decoder 7.2, against 14.3 and 9.0 with single columns throughout).
-template <typename T, int K, int VEC, bool RAGGED>
+template <typename T, int K, int VEC, bool RAGGED, bool FINISH>
 __global__ __launch_bounds__(kEncBlock) void mbq_encode_kernel(const T* __restrict__ x, uint8_t* __restrict__ payload,
                                                                MbqCall call, int64_t n, int64_t m, uint32_t ipg,
                                                                uint32_t wpg, uint32_t n_wave_items, bool wide) {
@@ -1184,7 +1224,8 @@ __global__ __launch_bounds__(kEncBlock) void mbq_encode_kernel(const T* __restri
     other_parts();
     complete_groups();
   }
-  store_record<K>(st, call, red);
+  store_record<K, FINISH>(st, call, red);
+  if constexpr (FINISH) finish_in_last_workgroup<K>(call, alpha, red);
 }
 
 // ================================================ comparison layout: one byte per binary base
@@ -1751,8 +1792,17 @@ MbqCall make_call(const accept_desc& d, const float* alpha_prev, void* header, v
 template <typename T, int K, int VEC, bool RAGGED>
 hipError_t launch_encode(const accept_desc& d, const MPlan& p, const T* x, uint8_t* payload, const MbqCall& call,
                          hipStream_t s) {
-  hipLaunchKernelGGL((mbq_encode_kernel<T, K, VEC, RAGGED>), dim3(p.grid), dim3(kEncBlock), 0, s, x, payload, call, d.n,
-                     d.m, uint32_t(p.wide ? d.m / VEC : 1), p.wpg, p.n_wave_items, p.wide);
+  auto launch = [&](auto finish) {
+    hipLaunchKernelGGL((mbq_encode_kernel<T, K, VEC, RAGGED, decltype(finish)::value>), dim3(p.grid), dim3(kEncBlock), 0, s, x,
+                       payload, call, d.n, d.m, uint32_t(p.wide ? d.m / VEC : 1), p.wpg, p.n_wave_items, p.wide);
+  };
+  if constexpr (K <= 4) {
+    if (p.finish) {
+      launch(std::true_type{});
+      return hipGetLastError();
+    }
+  }
+  launch(std::false_type{});
   return hipGetLastError();
 }
 
@@ -1881,11 +1931,15 @@ MPlan make_mplan(const accept_desc& d) {
     // one workgroup of 8 wavefronts per compute unit at most; fewer when there is less work
     int64_t blocks = p.stream ? (wave_items + kEncWaves - 1) / kEncWaves
                               : (full_groups * d.m + kEncBlock - 1) / kEncBlock;
-    const int64_t tail_blocks = d.n % 8 == 0 ? 0 : p.wide ? wpg : (d.m + kEncBlock - 1) / kEncBlock;
+    // The partial row group's wave-items are dealt to workgroups; where there is nothing else and few of them, four to
+    // a workgroup, which then are few enough to finish (4 x 65536 float32, k = 2: 7.3 -> 7.2 us, and a launch less).
+    const bool few = full_groups == 0 && wpg <= 4 * kFinishGridMax;
+    const int64_t tail_blocks = d.n % 8 == 0 ? 0 : !p.wide ? (d.m + kEncBlock - 1) / kEncBlock : few ? (wpg + 3) / 4 : wpg;
     if (blocks < tail_blocks) blocks = tail_blocks;
     if (blocks < 1) blocks = 1;
     p.grid = int(blocks < kEncodeGridMax ? blocks : kEncodeGridMax);
   }
+  p.finish = d.layout == ACCEPT_LAYOUT_PACKED && d.bits <= 4 && p.grid <= kFinishGridMax;
   // control block, then room for kMaxRecords records of the widest kind (k = 8)
   const size_t bytes = kCtrlBytes + size_t(nstat_of(8)) * kMaxRecords * sizeof(double);
   p.bytes = (bytes + 255) / 256 * 256;
@@ -1950,6 +2004,7 @@ hipError_t launch_mbq_compress(const accept_desc& d, const MPlan& p, const void*
   }
   if (e != hipSuccess) return e;
   mark(tm, s);
+  if (p.finish) return hipSuccess;
 #define ACCEPT_FIN(KK)                                                                          \
   case KK:                                                                                      \
     hipLaunchKernelGGL(mbq_finalize_kernel<KK>, dim3(1), dim3(finalize_block(KK)), 0, s, call, nrec); \

@@ -325,3 +325,43 @@ def test_rows_at_any_alignment_large(A, n, m, bf16):
         torch.cuda.synchronize()
         want = orc.mbq_pack(orc.mbq_assign(xin, a), 4, n, m)
         assert first_mismatch(dev_bytes(payload), want.tobytes()) is None, alpha
+
+
+# Encode kernels of at most 64 workgroups solve for the coefficients themselves, in the workgroup that ends last.
+@pytest.mark.parametrize("n,m,bf16,one", [
+    (8, 40, False, True),                    # one workgroup, too narrow for wave-items
+    (64, 8 * 64 * 4 * 8, False, True),       # 64 workgroups
+    (64, 8 * 64 * 4 * 8 + 4, False, False),  # one wave-item more per row group: 65
+    (64, 8 * 64 * 8 * 8, True, True),
+    (5, 256 * 64 * 4, False, True),          # a partial row group only, four wave-items to a workgroup
+    (5, 256 * 64 * 4 + 4, False, False),     # one wave-item more: one to a workgroup
+    (13, 4096, True, True),                  # complete and partial
+    (13, 4100, True, False),                 # the same in single columns: 65 for the partial one
+])
+def test_encoder_that_solves_itself(A, n, m, bf16, one):
+    torch = torch_mod()
+    k = 4 if n != 13 else 3
+    d = A.make_desc(A.MBQ, k, n, m, in_dtype=A.BF16 if bf16 else A.F32, t=7)
+    assert (A.accept_stage_name(d, 0, 1) is None) == one
+    x = si.make_shape("relu_lognormal", (n, m), 900 + n)
+    run_case(A, x, k, n, m, t=7, in_bf16=bf16, out_bf16=bf16, tag="solves itself")
+    # one workspace, other numbers of workgroups in between, and replays of a captured call: the counters are back at 0
+    xd, bits = to_dev(x, bf16)
+    alpha, _ = orc.mbq_residue_init(orc.widen_bf16(bits) if bf16 else x.reshape(-1), k)
+    ad = torch.from_numpy(np.asarray(alpha, np.float32)).cuda()
+    header, payload, ws = A.alloc_outputs(d, "cuda")
+    big = A.make_desc(A.MBQ, 2, 64, 40000, t=3)
+    xb = torch.randn(64 * 40000, device="cuda")
+    A.accept_compress(d, xd, alpha_prev=ad, header=header, payload=payload, workspace=ws)
+    torch.cuda.synchronize()
+    want = dev_bytes(header), dev_bytes(payload)
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g):
+        A.accept_compress(d, xd, alpha_prev=ad, header=header, payload=payload, workspace=ws)
+    for _ in range(3):
+        A.accept_compress(big, xb, alpha_prev=ad[:2].clone(), workspace=ws)
+        payload.zero_()
+        header.zero_()
+        g.replay()
+        torch.cuda.synchronize()
+        assert (dev_bytes(header), dev_bytes(payload)) == want
