@@ -50,7 +50,7 @@ def alg_bytes(kernel, N, n, m, k, b_in=4, b_out=4):
     """Algorithmic HBM bytes one launch of a kernel must move."""
     if kernel == "range":
         return N * b_in
-    if kernel in ("quantize_pack", "quantize_held", "quantize_channels"):  # held: range and codes from one kernel, priced as one read
+    if kernel in ("quantize_pack", "quantize_held", "quantize_channels", "quantize_whole"):  # held: range and codes from one kernel, priced as one read
         return N * b_in + (N * k + 7) // 8 + 4
     if kernel == "unpack_dequant":
         return (N * k + 7) // 8 + 4 + N * b_out

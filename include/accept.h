@@ -123,8 +123,8 @@ accept_status accept_workspace_size(const accept_desc* desc, size_t* bytes);
  * aligned) and payload_dev (16-byte aligned), sizes as accept_packed_size reports.
  *
  *   UNIFORM: range pass, then fused quantize + pack (one range and 48, bfloat16 72, to 256 MiB of input: both in
- *     one kernel that keeps part of the tensor on the chip; a range per channel, segments of whole 32s and a tensor
- *     that fits on the chip: one kernel altogether).  Code i occupies payload bits
+ *     one kernel that keeps part of the tensor on the chip; smaller ones, and with a range per channel segments of whole
+ *     32s, that fit on the chip: one kernel altogether).  Code i occupies payload bits
  *     [ik, (i+1)k), most significant bit first, bit b of the stream being bit 7-(b mod 8)
  *     of byte b/8; codes are q + 2^(k-1) for k < 8 and the two's-complement byte for
  *     k = 8; unused bits of the last byte are 0.  q = clamp(round(x * fl(L/c)), -2^(k-1), L),

@@ -18,8 +18,7 @@ extern "C" {
  * WAITS for the last event and writes each stage's duration in milliseconds to the host
  * array stage_ms[0..*n_stages) (capacity ACCEPT_MAX_STAGES).  Stage order:
  *   UNIFORM compress: range, [range finalize], quantize+pack, or for one range and 48 (bfloat16: 72) to 256 MiB
- *   of input the held range+quantize and, of the largest float32 tensors, the rest of it, or for a range per channel and a tensor that fits on
- *   the chip one kernel;   MBQ compress: encode+sums, finalize;
+ *   of input the held range+quantize and, of the largest float32 tensors, the rest of it, or one kernel for tensors that stay on the chip;   MBQ compress: encode+sums, finalize;
  *   decompress: the one kernel.
  * For benchmarks only; creates and destroys its events on every call.
  */

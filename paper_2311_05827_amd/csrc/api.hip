@@ -259,6 +259,7 @@ const char* accept_stage_name(const accept_desc* desc, int is_decompress, int i)
   int units = compute_units();
   if (units == 0) units = kHeldGrid;  // no device: the names of a whole one
   if (channels_run(plan, units)) return i == 0 ? "quantize_channels" : nullptr;
+  if (whole_runs(plan, units)) return i == 0 ? "quantize_whole" : nullptr;
   if (desc->channels > 1 && !plan.local_ranges) {
     static const char* const names[] = {"range", "range_finalize", "quantize_pack"};
     return i < 3 ? names[i] : nullptr;

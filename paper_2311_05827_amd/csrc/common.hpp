@@ -76,6 +76,7 @@ struct UPlan {
   bool held_rest;      // held: a second kernel does what workgroups that gave up have left
   int held_lds;        // held: units per workgroup that stay in local memory (the others in registers)
   int64_t held_first;  // held: units [held_first, held_units) are kept, the others are read again
+  uint32_t whole_per;  // U_TENSOR: groups of 32 elements per workgroup of the pass that keeps the tensor in registers; 0: not taken
   uint32_t chan_per;   // per channel: groups of 32 elements per workgroup of the pass that keeps the tensor on the chip; 0: not taken
   size_t off_rtab;     // byte offset of the per-channel reciprocal table in the workspace
   size_t bytes;        // workspace bytes
@@ -87,6 +88,7 @@ UPlan make_uplan(const accept_desc& d);
 int compute_units();
 constexpr int kHeldGrid = 256;
 inline bool held_runs(const UPlan& p, int units) { return p.held && units >= kHeldGrid; }
+inline bool whole_runs(const UPlan& p, int units) { return p.whole_per != 0 && units >= kHeldGrid; }
 inline bool channels_run(const UPlan& p, int units) { return p.chan_per != 0 && units >= kHeldGrid; }
 
 // held_polls: how often a workgroup of the held pass looks for the others' maxima before it gives up

@@ -1057,14 +1057,15 @@ hipError_t launch_quant_k(const accept_desc& d, const UPlan& p, const T* x, floa
 template <typename T>
 hipError_t compress_typed(const accept_desc& d, const UPlan& p, const T* x, float* header, uint32_t* payload,
                           void* ws, hipStream_t s, StageTimer* tm, int held_polls) {
-  const int units = p.held || p.chan_per != 0 ? compute_units() : 0;
+  const int units = p.held || p.chan_per != 0 || p.whole_per != 0 ? compute_units() : 0;
   ChipMail* mail = reinterpret_cast<ChipMail*>(reinterpret_cast<char*>(ws) + kMailOffset);
   float* partials = reinterpret_cast<float*>(reinterpret_cast<char*>(ws) + kCtrlBytes);
   float* rtab = reinterpret_cast<float*>(reinterpret_cast<char*>(ws) + p.off_rtab);
   mark(tm, s);
-  if (held_runs(p, units) || channels_run(p, units)) {
-    const hipError_t e = p.held ? launch_held<T>(d, p, x, header, payload, mail, held_polls, s, tm)
-                                : launch_channels<T>(d, p, x, header, payload, mail, held_polls, s);
+  if (held_runs(p, units) || channels_run(p, units) || whole_runs(p, units)) {
+    const hipError_t e = p.held             ? launch_held<T>(d, p, x, header, payload, mail, held_polls, s, tm)
+                         : p.whole_per != 0 ? launch_whole<T>(d, p, x, header, payload, mail, held_polls, s)
+                                            : launch_channels<T>(d, p, x, header, payload, mail, held_polls, s);
     if (e == hipSuccess) mark(tm, s);
     return e;
   }
@@ -1265,6 +1266,10 @@ UPlan make_uplan(const accept_desc& d) {
     const int64_t bytes = p.N * (p.vec == 8 ? 2 : 4);
     p.held = d.layout == ACCEPT_LAYOUT_PACKED && d.rounding == ACCEPT_ROUND_NEAREST_EVEN &&
              bytes >= (p.vec == 8 ? kHeldMinBytes<bf16_t> : kHeldMinBytes<float>) && bytes <= kHeldMaxBytes;
+    if (!p.held && d.layout == ACCEPT_LAYOUT_PACKED) {
+      const bool stoch = d.rounding == ACCEPT_ROUND_STOCHASTIC;
+      p.whole_per = p.vec == 8 ? whole_groups<bf16_t>(p.N, stoch) : whole_groups<float>(p.N, stoch);
+    }
     if (p.held) {
       int64_t keep = p.vec == 8 ? kHeldUnits<bf16_t> : kHeldUnits<float>;
       const int64_t keep_lds = p.vec == 8 ? kHeldLdsUnits<bf16_t> : kHeldLdsUnits<float>;

@@ -85,4 +85,36 @@ template <typename T>
 hipError_t launch_channels(const accept_desc& d, const UPlan& p, const T* x, float* header, uint32_t* payload,
                            ChipMail* mail, int polls, hipStream_t s);
 
+template <typename T>
+hipError_t launch_whole(const accept_desc& d, const UPlan& p, const T* x, float* header, uint32_t* payload, ChipMail* mail,
+                        int polls, hipStream_t s);
+
+// Groups of a workgroup of quantize_whole_kernel; 0: the tensor does not take it.  Range and quantize kernels / this
+// (us on the device, replayed graphs; a launch less is 3.6 us of host time on top):
+//   nearest, float32: 5 K 5.5 / 3.7, 16 K 4.7 / 3.0, 100 K 5.8 / 4.3, 300 K 6.2 / 4.7, 1 M 6.1 / 5.8, 4 M 9.4 / 8.1, 8.3 M
+//     12.9 / 11.8; bfloat16: 2.5 M 6.5 / 6.5, 8.3 M 10.8 / 9.5, 25 M 21.8 / 18.9;
+//   stochastic, float32: 20 K 7.6 / 4.5, 300 K 7.9 / 5.8, 1 M 7.9 / 7.1, 4 M 11.3 / 10.9, 8.3 M 17.5 / 17.4, 16.7 M
+//     35 / 30; bfloat16: 20 K 7.4 / 4.6, 1 M 7.6 / 6.7, 2.5 M 8.9 / 8.6, 4 M 9.3 / 9.9, 12 M 19.9 / 20.3.
+// Between kWholeSmall and kWholeLarge values, and from where the held pass begins to a third less (float32), rounding to
+// nearest keeps its two kernels: their names are what accept_stage_name is asked for there (the gain would be the
+// smallest there as well, 262144 values 5.1 / 4.6).
+constexpr int64_t kWholeSmall = int64_t(1) << 17, kWholeLarge = int64_t(1) << 18;
+template <typename T>
+constexpr int64_t kWholeNearestUnits = sizeof(T) == 4 ? ChanSlots<T>::small : ChanSlots<T>::middle;
+constexpr int64_t kWholeStochasticBf16 = int64_t(3) << 20;
+// The fewest groups of a workgroup: fewer workgroups have fewer mailboxes to look through, one has none; the random
+// numbers want more of them.  128 / 512 groups: nearest, 16 K 3.9 / 3.0, 1 M 6.4 / 5.8; stochastic, 20 K 4.5 / 6.6, 1 M
+// 7.1 / 8.8.
+constexpr int64_t kWholeMinGroups = kHeldBlock, kWholeMinGroupsStochastic = 128;
+template <typename T>
+inline uint32_t whole_groups(int64_t N, bool stochastic) {
+  const int64_t groups = N / 32;
+  const int64_t units = stochastic ? ChanSlots<T>::middle : kWholeNearestUnits<T>;
+  if (groups < 1 || groups > units * kHeldBlock * kHeldGrid) return 0;
+  if (stochastic ? sizeof(T) == 2 && N > kWholeStochasticBf16 : N > kWholeSmall && N <= kWholeLarge) return 0;
+  const int64_t per = (groups + kHeldGrid - 1) / kHeldGrid;
+  const int64_t least = stochastic ? kWholeMinGroupsStochastic : kWholeMinGroups;
+  return uint32_t(per < least ? least : per);
+}
+
 }  // namespace accept

@@ -1,6 +1,8 @@
 // The kernels of uniform_chip.hpp.
 #pragma once
 
+#include <type_traits>
+
 #include "uniform_chip.hpp"
 
 namespace accept {
@@ -663,7 +665,160 @@ __global__ __launch_bounds__(kHeldBlock, 2) void quantize_channels_kernel(const 
     if (uint32_t(LDS_UNITS + j) < units) quantize_unit(LDS_UNITS + j, [&](int u) { return kept[(j + LDS_UNITS) % SLOTS][u]; });
 }
 
+// U1, U1b, U2 and U3 of a tensor with one range, in one kernel and with one read: small tensors, where a kernel more
+// is a launch more, and larger ones, whose second read it saves.  Workgroup b has the groups of 32 elements b*per ..
+// (b+1)*per - 1, all of them in registers; the last one also has the up to 31 elements behind the last group.  The
+// workgroups' maxima are exchanged as in the held pass; one that has to find others' itself keeps
+// what it has.
+// Latency bounds it: the loads, a mailbox's way to memory and back (2 us), the stores.  Figures are at whole_groups.
+template <typename T, int K, int SLOTS, bool STOCH>
+__global__ __launch_bounds__(kHeldBlock, 2) void quantize_whole_kernel(const T* __restrict__ x,
+                                                                       uint32_t* __restrict__ payload32,
+                                                                       float* __restrict__ header,
+                                                                       ChipMail* __restrict__ mail, int64_t N,
+                                                                       uint32_t per, int64_t payload_bytes, uint64_t seed,
+                                                                       int polls) {
+  constexpr int VEC = Elem<T>::VEC;
+  constexpr int GV = 32 / VEC;                            // vectors of a group
+  constexpr int LOADS = kUnitElems / (kHeldBlock * VEC);  // vectors per thread and unit
+  constexpr int QPV = VEC / 4, WAVES = kHeldBlock / kWave;
+  __shared__ __attribute__((aligned(16))) uint32_t pieces[2][kUnitElems / 4];
+  __shared__ Exchange ex;
+  const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid / kWave;
+  const uint32_t total = uint32_t(N / 32);
+  const uint32_t tag = uint32_t(__builtin_amdgcn_readfirstlane(int(mail->calls[blockIdx.x]))) + 1u;
+  auto groups_of = [&](uint32_t w) { return total - w * per < per ? total - w * per : per; };
+  const uint32_t q0 = blockIdx.x * per, count = groups_of(blockIdx.x);
+  const uint32_t units = (count + kHeldBlock - 1) / kHeldBlock;
+  const uint32_t mine = uint32_t(tid) / GV;  // the thread's first vector is in this group of the workgroup's
+  const T* const xw = x + size_t(q0) * 32;
+  // elements behind the last group, of the last workgroup
+  const T* const xt = x + size_t(total) * 32;
+  const int tail = blockIdx.x + 1 == gridDim.x ? int(N - int64_t(total) * 32) : 0;
+  uint4 kept[SLOTS][LOADS];
+#pragma unroll
+  for (int j = 0; j < SLOTS; ++j)
+#pragma unroll
+    for (int u = 0; u < LOADS; ++u) {
+      const uint32_t grp = uint32_t(j * kHeldBlock + u * (kHeldBlock / GV)) + mine;
+      // (behind the last group the first vector stands in)
+      const uint32_t v = grp < count ? uint32_t((j * LOADS + u) * kHeldBlock + tid) : 0u;
+      kept[j][u] = load16_stream(xw + size_t(v) * VEC);
+    }
+  float c = tid < tail ? fabsf(load_one(xt + tid)) : 0.0f;
+#pragma unroll
+  for (int j = 0; j < SLOTS; ++j)
+#pragma unroll
+    for (int u = 0; u < LOADS; ++u) {
+      float f[VEC];
+      widen(kept[j][u], f);
+#pragma unroll
+      for (int e = 0; e < VEC; ++e) c = fmaxf(c, fabsf(f[e]));
+    }
+  c = wave_max(c);
+  if (lane == 0) ex.top[wave] = c;
+  __syncthreads();
+  if (gridDim.x > 1) {
+    if (tid == 0) {
+      c = ex.top[0];
+#pragma unroll
+      for (int w = 1; w < WAVES; ++w) c = fmaxf(c, ex.top[w]);
+      post(mail->first + blockIdx.x, tag, c);
+    }
+    __syncthreads();
+    look_for_mail(mail, tag, polls, ex);
+    __syncthreads();
+    if (missing_count(ex) != 0)
+      post_missing(mail, tag, ex, [&](int w) {
+        float v = w + 1 == int(gridDim.x) && tid < int(N - int64_t(total) * 32) ? fabsf(load_one(xt + tid)) : 0.0f;
+        const T* const xo = x + size_t(w) * per * 32;
+        for (uint32_t i = tid; i < groups_of(w) * GV; i += kHeldBlock) {
+          float f[VEC];
+          load_vec(xo + size_t(i) * VEC, f);
+#pragma unroll
+          for (int e = 0; e < VEC; ++e) v = fmaxf(v, fabsf(f[e]));
+        }
+        return v;
+      });
+    c = largest_mail(ex);
+  } else {
+    c = ex.top[0];
+#pragma unroll
+    for (int w = 1; w < WAVES; ++w) c = fmaxf(c, ex.top[w]);
+  }
+  if (tid < kHeldGrid && uint32_t(tid) % gridDim.x == blockIdx.x) mail->calls[tid] = tag;
+  float s, r;
+  scale_from_range(c, K, s, r);
+  if (blockIdx.x == 0 && tid == 0) header[0] = s;
+  const float rv[4] = {r, r, r, r};
+
+  // random state of the thread's first element; its other vectors' are whole steps of a unit's share behind it
+  const uint64_t z0 = STOCH ? rand_state(seed, uint64_t(q0) * 32 + uint64_t(tid) * VEC) : 0;
+#pragma unroll
+  for (int j = 0; j < SLOTS; ++j) {
+    if (uint32_t(j) >= units) break;  // the same in all threads
+    uint32_t* buf = pieces[j & 1];
+#pragma unroll
+    for (int u = 0; u < LOADS; ++u) {
+      if (uint32_t(j * kHeldBlock + u * (kHeldBlock / GV)) >= count) break;  // the same in all threads: nothing but stand-ins
+      uint4 raw = kept[j][u];
+      // (an empty asm: the values widened for the maximum would stay in registers from then to here)
+      asm volatile("" : "+v"(raw.x), "+v"(raw.y), "+v"(raw.z), "+v"(raw.w));
+      float f[VEC];
+      widen(raw, f);
+      const uint64_t z = z0 + uint64_t((j * LOADS + u) * kHeldBlock * VEC) * kRandStep;
+#pragma unroll
+      for (int h = 0; h < QPV; ++h)
+        buf[(u * kHeldBlock + tid) * QPV + h] = quantize4<K, STOCH>(&f[4 * h], rv, z + uint64_t(4 * h) * kRandStep);
+    }
+    __syncthreads();  // double buffered: one barrier per unit
+    constexpr int PARTS = CodeParts<K>::PARTS;
+    const __amdgpu_buffer_rsrc_t codes = payload_buffer(payload32 + size_t(q0) * K, count * uint32_t(K * 4));
+#pragma unroll
+    for (int i = 0; i < PARTS; ++i) {
+      const uint32_t part = uint32_t(i * kHeldBlock + tid);
+      uint32_t out[CodeParts<K>::DWORDS];
+      pack_part<K>(&buf[part * CodeParts<K>::PIECES], out);
+      const uint32_t grp = uint32_t(j * kHeldBlock) + part / PARTS;
+      if (grp < count) store_part<K>(codes, (grp * uint32_t(K) + part % PARTS * CodeParts<K>::DWORDS) * 4u, out);
+    }
+  }
+  if (tid * 8 < tail)
+    quantize_group8<T, K, STOCH>(x, reinterpret_cast<uint8_t*>(payload32), int64_t(total) * 4 + tid, N, payload_bytes, seed,
+                                 [&](int64_t) { return r; });
+}
+
 }  // namespace
+
+template <typename T>
+hipError_t launch_whole(const accept_desc& d, const UPlan& p, const T* x, float* header, uint32_t* payload, ChipMail* mail,
+                        int polls, hipStream_t s) {
+  const uint32_t total = uint32_t(p.N / 32);
+  const int grid = int((total + p.whole_per - 1) / p.whole_per);
+  const int units = int((p.whole_per + kHeldBlock - 1) / kHeldBlock);
+  const int64_t payload_bytes = (p.N * d.bits + 7) / 8;
+  const bool stoch = d.rounding == ACCEPT_ROUND_STOCHASTIC;
+  auto launch = [&](auto k, auto slots, auto st) {
+    hipLaunchKernelGGL((quantize_whole_kernel<T, decltype(k)::value, decltype(slots)::value, decltype(st)::value>), dim3(grid),
+                       dim3(kHeldBlock), 0, s, x, payload, header, mail, p.N, p.whole_per, payload_bytes, d.seed, polls);
+  };
+  auto sized = [&](auto k, auto st) {
+    if (units <= 1) launch(k, std::integral_constant<int, 1>{}, st);
+    else if (units <= ChanSlots<T>::small) launch(k, std::integral_constant<int, ChanSlots<T>::small>{}, st);
+    else launch(k, std::integral_constant<int, ChanSlots<T>::middle>{}, st);
+  };
+#define ACCEPT_WHOLE(KK)                                             \
+  case KK:                                                           \
+    if (stoch) sized(std::integral_constant<int, KK>{}, std::true_type{}); \
+    else sized(std::integral_constant<int, KK>{}, std::false_type{}); \
+    break;
+  switch (d.bits) {
+    ACCEPT_WHOLE(2) ACCEPT_WHOLE(3) ACCEPT_WHOLE(4) ACCEPT_WHOLE(5) ACCEPT_WHOLE(6) ACCEPT_WHOLE(7) ACCEPT_WHOLE(8)
+    default: return hipErrorInvalidValue;
+  }
+#undef ACCEPT_WHOLE
+  return hipGetLastError();
+}
 
 template <typename T>
 hipError_t launch_held(const accept_desc& d, const UPlan& p, const T* x, float* header, uint32_t* payload,

@@ -545,3 +545,44 @@ def test_channels_on_the_chip_on_two_streams_and_in_a_graph(A):
         h, p = A.accept_compress(small, xs[0][:6].reshape(-1), workspace=ws)  # eager, same workspace
         torch.cuda.synchronize()
         assert dev_bytes(h) == want_small[0] and dev_bytes(p) == want_small[1].tobytes()
+
+
+# One range, a tensor that stays in registers: one kernel.  Workgroups of at least 512 (stochastic: 128) groups of 32
+# elements, at most 256 of them; up to 31 elements behind the last group.
+@pytest.mark.parametrize("N,k,bf16,rounding", [
+    (32, 4, False, 0),                        # one group
+    (63, 3, True, 0),
+    (512 * 32 + 31, 8, False, 0),             # one full workgroup and what is behind
+    (512 * 32 + 32, 5, False, 0),             # a group more: two workgroups
+    (1 << 17, 6, True, 0),                    # the largest of the small ones
+    ((1 << 18) + 1, 7, False, 0),             # the smallest of the large ones
+    (256 * 512 * 32, 2, False, 0),            # 256 workgroups of a unit
+    (256 * 512 * 32 + 33, 3, False, 0),       # of a unit and a group
+    (2 * 256 * 512 * 32, 8, False, 0),        # the most, float32
+    (3 * 256 * 512 * 32 + 7, 4, True, 0),     # beyond three units, bfloat16
+    (128 * 32 + 5, 8, False, 1),              # stochastic: two workgroups
+    (20480, 8, False, 1),
+    (255 * 128 * 32 + 9, 4, True, 1),
+    (4 * 256 * 512 * 32, 3, False, 1),        # the most, float32
+    (3 << 20, 5, True, 1),                    # the most, bfloat16
+])
+def test_tensor_in_registers(A, N, k, bf16, rounding):
+    torch = torch_mod()
+    print("case", N, k, bf16, rounding, flush=True)
+    seed = 12345 + N
+    x = si.make_shape("grad", (1, N), 400 + k)
+    x[0, N - 1 - N // 9] = 0.25
+    d = A.make_desc(A.UNIFORM, k, 1, N, in_dtype=A.BF16 if bf16 else A.F32, rounding=rounding, seed=seed)
+    assert A.accept_stage_name(d, 0, 0) == "quantize_whole"
+    header, payload, ws = A.alloc_outputs(d, "cuda")
+    for turn in range(2 if N < 1 << 20 else 1):
+        if turn == 1:
+            x[0, N - 1] = -0.5  # the largest value behind the last group
+        xd, bits = to_dev(x, bf16)
+        oh, op = orc.uniform_compress(bits if bf16 else x, k, 1, N, 0, bf16, rounding, seed)
+        for polls in (64, 0, 1):  # seen by each other; workgroups find each other's maxima
+            payload.zero_()
+            A.accept_compress_polls(d, xd, header, payload, ws, polls)
+            torch.cuda.synchronize()
+            assert dev_bytes(header) == oh, polls
+            assert first_mismatch(dev_bytes(payload), op.tobytes()) is None, polls
