@@ -118,6 +118,20 @@ accept_status do_decompress(const accept_desc* d, const void* header, const void
   return *launch_err == hipSuccess ? ACCEPT_OK : ACCEPT_ERR_HIP;
 }
 
+accept_status do_first(const accept_desc* desc, const void* x_dev, void* header_dev, void* payload_dev,
+                       void* workspace_dev, void* hip_stream, int polls) {
+  const accept_status st = check_desc(desc);
+  if (st != ACCEPT_OK) return st;
+  if (desc->scheme != ACCEPT_MBQ || desc->layout != ACCEPT_LAYOUT_PACKED) return ACCEPT_ERR_INVALID_ARG;
+  if (!x_dev || !header_dev || !payload_dev || !workspace_dev) return ACCEPT_ERR_INVALID_ARG;
+  if (!aligned(x_dev, 16) || !aligned(payload_dev, 16) || !aligned(header_dev, 4) || !aligned(workspace_dev, 256))
+    return ACCEPT_ERR_INVALID_ARG;
+  const MPlan p = make_mplan(*desc);
+  const hipError_t e = launch_mbq_init(*desc, p, x_dev, static_cast<float*>(header_dev), payload_dev, workspace_dev,
+                                       static_cast<hipStream_t>(hip_stream), polls);
+  return e == hipSuccess ? ACCEPT_OK : ACCEPT_ERR_HIP;
+}
+
 }  // namespace
 
 extern "C" {
@@ -193,16 +207,7 @@ accept_status accept_mbq_init(const accept_desc* desc, const void* x_dev, float*
 
 accept_status accept_mbq_compress_first(const accept_desc* desc, const void* x_dev, void* header_dev,
                                         void* payload_dev, void* workspace_dev, void* hip_stream) {
-  const accept_status st = check_desc(desc);
-  if (st != ACCEPT_OK) return st;
-  if (desc->scheme != ACCEPT_MBQ || desc->layout != ACCEPT_LAYOUT_PACKED) return ACCEPT_ERR_INVALID_ARG;
-  if (!x_dev || !header_dev || !payload_dev || !workspace_dev) return ACCEPT_ERR_INVALID_ARG;
-  if (!aligned(x_dev, 16) || !aligned(payload_dev, 16) || !aligned(header_dev, 4) || !aligned(workspace_dev, 256))
-    return ACCEPT_ERR_INVALID_ARG;
-  const MPlan p = make_mplan(*desc);
-  const hipError_t e = launch_mbq_init(*desc, p, x_dev, static_cast<float*>(header_dev), payload_dev, workspace_dev,
-                                       static_cast<hipStream_t>(hip_stream));
-  return e == hipSuccess ? ACCEPT_OK : ACCEPT_ERR_HIP;
+  return do_first(desc, x_dev, header_dev, payload_dev, workspace_dev, hip_stream, kHeldPolls);
 }
 
 accept_status accept_compress_timed(const accept_desc* desc, const void* x_dev, const float* alpha_prev_dev,
@@ -222,6 +227,8 @@ accept_status accept_compress_polls(const accept_desc* desc, const void* x_dev, 
                                     void* header_dev, void* payload_dev, void* workspace_dev, void* hip_stream,
                                     int polls) {
   if (polls < 0 || polls > kHeldPolls) return ACCEPT_ERR_INVALID_ARG;
+  if (desc && desc->scheme == ACCEPT_MBQ && !alpha_prev_dev)
+    return do_first(desc, x_dev, header_dev, payload_dev, workspace_dev, hip_stream, polls);
   hipError_t e;
   return do_compress(desc, x_dev, alpha_prev_dev, header_dev, payload_dev, workspace_dev, hip_stream, nullptr, &e,
                      polls);

@@ -91,6 +91,20 @@ inline bool held_runs(const UPlan& p, int units) { return p.held && units >= kHe
 inline bool whole_runs(const UPlan& p, int units) { return p.whole_per != 0 && units >= kHeldGrid; }
 inline bool channels_run(const UPlan& p, int units) { return p.chan_per != 0 && units >= kHeldGrid; }
 
+// What the workgroups of calls with one workspace leave each other, in its control block.  A call's tag is one
+// more than the number of calls before it, of which every workgroup has a word of its own: it reads the
+// word when it starts and raises it when it ends (and those of the workgroups that this call does not have),
+// so all of them agree.  So nothing has to be emptied: a value of an earlier call bears an earlier tag.
+// (Counting the workgroups off on one counter, and the last one emptying everything, cost small tensors
+// 1.5 us.)
+struct ChipMail {
+  uint64_t first[kHeldGrid], last[kHeldGrid];  // tag and the workgroup's maximum: of its first (or only), its last
+                                               // channel; or tag and half of its sum (see mbq_first_kernel)
+  uint64_t more[kHeldGrid];
+  uint32_t calls[kHeldGrid];
+};
+static_assert(kMailOffset + sizeof(ChipMail) <= kCtrlBytes, "the control block holds them");
+
 // held_polls: how often a workgroup of the held pass looks for the others' maxima before it gives up
 // (kHeldPolls; fewer only where a test wants the case that it gives up).  64 looks take about 50 us.  Alone
 // on the chip, 205 MB, 16 are too few (72.8 us a call) and 32 enough (56.8; 64: 55.8, the spread of the
@@ -125,7 +139,7 @@ hipError_t launch_mbq_compress(const accept_desc& d, const MPlan& p, const void*
 hipError_t launch_mbq_decompress(const accept_desc& d, const void* header, const void* payload, void* xhat,
                                  hipStream_t s, StageTimer* tm);
 hipError_t launch_mbq_init(const accept_desc& d, const MPlan& p, const void* x, float* alpha_out, void* payload,
-                           void* ws, hipStream_t s);
+                           void* ws, hipStream_t s, int polls = kHeldPolls);
 
 // ---- device helpers ---------------------------------------------------------------------
 #if defined(__HIPCC__)

@@ -986,7 +986,7 @@ struct MbqCall {
   double n_elems;
   double beta;  // weight of the previous coefficients in the moving average: min(0.9, (1+t)/(10+t))
 };
-constexpr int kDoneCounter = 32;  // word of the counters (between two work counters) that counts off the workgroups
+constexpr int kDoneCounter = 2;  // word of the counters (between two work counters) that counts off the workgroups
 
 // End of an encode kernel (M4): the workgroup adds up its threads' statistics in a fixed order
 // and stores one record.  The counts are added as integers: 8 instructions per statistic and
@@ -1070,20 +1070,23 @@ __global__ __launch_bounds__(finalize_block(K)) void mbq_finalize_kernel(MbqCall
 // 4): 16 x 2048 float32 7.1 / 6.8, 9.9 / 10.0; 64 x 16384 (64 workgroups) 7.7 / 7.4, 10.3 / 10.5; 64 x 50000 (196: the
 // counter, one address, takes 12 ns each) 8.8 / 9.7, 11.2 / 12.6.
 constexpr int kFinishGridMax = 64;
+__device__ __forceinline__ bool last_workgroup(uint32_t* counters) {
+  __shared__ int last;
+  __builtin_amdgcn_s_waitcnt(0x0F70);  // this thread's part of the record is written
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    const uint32_t before = __hip_atomic_fetch_add(counters + kDoneCounter, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    last = before + 1u == gridDim.x ? 1 : 0;
+  }
+  __syncthreads();
+  return __builtin_amdgcn_readfirstlane(last) != 0;
+}
 template <int K>
 __device__ __forceinline__ void finish_in_last_workgroup(const MbqCall& call, const float (&alpha_prev)[K], WaveTotals& buf) {
   constexpr int NSTAT = nstat_of(K);
   const int tid = threadIdx.x, wave = tid / kWave, lane = tid & (kWave - 1);
   const int nrec = int(gridDim.x);
-  __shared__ int last;
-  __builtin_amdgcn_s_waitcnt(0x0F70);  // this thread's part of the record is written
-  __syncthreads();
-  if (tid == 0) {
-    const uint32_t before = __hip_atomic_fetch_add(call.counters + kDoneCounter, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    last = before + 1u == uint32_t(nrec) ? 1 : 0;
-  }
-  __syncthreads();
-  if (__builtin_amdgcn_readfirstlane(last) == 0) return;
+  if (!last_workgroup(call.counters)) return;
   double* tot = buf.v[0];
   for (int s = wave; s < NSTAT; s += kEncWaves) {
     const double a = sum_records<true>(call.records + int64_t(s) * nrec, nrec, lane);
@@ -1698,6 +1701,294 @@ __global__ __launch_bounds__(kBlock) void mbq_init_encode_kernel(const T* __rest
   }
 }
 
+// Batch 0 of a small tensor in one kernel instead of k + 1: an item of the encoder's kind per thread, its rows in registers for
+// all k passes; between the passes the workgroups exchange their sums of |rho_j| through mailboxes, and the last one to
+// end writes the rest of the header.
+//
+// The wait for the others is bounded as in scheme U's held pass: a workgroup that has looked `polls` times in
+// vain adds up the missing parts itself, in the same order as their owners, so to the same bits, and posts them.
+//
+// A mailbox is two words, each with half of the float64 and the number of the exchange.  Every exchange of a call (k - 1,
+// at most three) has a set of its own: a workgroup may be late for one that all others have left.
+//
+// What it saves is host time, 3.6 us a launch; on the device it takes, k + 1 kernels / this (us, float32): 128 x 160, k = 2
+// 8.4 / 6.8; 64 x 4000 8.6 / 7.5, k = 4 15.8 / 14.9; 64 x 16000, k = 2 9.6 / 9.8 (bfloat16 9.8 / 10.5).  (With up to four items per thread it
+// ran on tensors of 51 MB as well, which it reads once instead of k times, and gained nothing: 32 x 401408, k = 3 39.9 /
+// 42.7: two wavefronts on a SIMD take longer for the float64 sums than more of them with a second read.)
+constexpr int kFirstBlock = 512, kFirstWaves = kFirstBlock / kWave;
+struct SumExchange {
+  double part[kHeldGrid / kWave];
+  uint64_t missing[kHeldGrid / kWave];
+};
+struct SumBox {
+  uint64_t *lo, *hi;
+};
+// (Between two work counters of the control block there is room for 31 words; what the second half of the block does
+// not hold lies there: eight workgroups' words of a kind in a row.)
+__device__ __forceinline__ SumBox sum_box(uint32_t* ctrl, int set, int b) {
+  ChipMail* mail = reinterpret_cast<ChipMail*>(reinterpret_cast<char*>(ctrl) + kMailOffset);
+  uint64_t* between = reinterpret_cast<uint64_t*>(ctrl + (b / 8) * kCounterStride) + b % 8;
+  if (set == 0) return {mail->first + b, mail->last + b};
+  if (set == 1) return {mail->more + b, between + 8};
+  return {between + 16, between + 24};
+}
+static_assert(kCounterStride * sizeof(uint32_t) == 32 * sizeof(uint64_t) && kMaxGroups * 8 == kHeldGrid && kDoneCounter < 16,
+              "three times eight words behind the first eight, which hold the counters");
+__device__ __forceinline__ void post_sum(const SumBox& box, uint32_t tag, double v) {
+  const uint64_t bits = uint64_t(__double_as_longlong(v)), t = uint64_t(tag) << 32;
+  __hip_atomic_store(box.lo, t | uint32_t(bits), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  __hip_atomic_store(box.hi, t | uint32_t(bits >> 32), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ void look_for_sums(uint32_t* ctrl, int set, uint32_t tag, int polls, SumExchange& ex) {
+  const int tid = threadIdx.x;
+  if (tid >= kHeldGrid) return;
+  const bool box = uint32_t(tid) < gridDim.x;
+  const SumBox at = sum_box(ctrl, set, tid);
+  uint64_t missing = __ballot(box), lo = 0, hi = 0;
+  for (int i = 0; i < polls; ++i) {
+    if (box) {
+      lo = __hip_atomic_load(at.lo, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      hi = __hip_atomic_load(at.hi, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    missing = __ballot(box && (uint32_t(lo >> 32) != tag || uint32_t(hi >> 32) != tag));
+    if (missing == 0) break;
+    __builtin_amdgcn_s_sleep(2);
+  }
+  const uint64_t bits = (hi << 32) | uint32_t(lo);
+  const double t = wave_sum(box && missing == 0 ? __longlong_as_double((long long)bits) : 0.0);
+  if ((tid & (kWave - 1)) == 0) {
+    ex.part[tid / kWave] = t;
+    ex.missing[tid / kWave] = missing;
+  }
+}
+
+template <typename T, int K, int VEC>
+__global__ __launch_bounds__(kFirstBlock, 2) void mbq_first_kernel(const T* __restrict__ x, float* __restrict__ header,
+                                                                   uint8_t* __restrict__ payload, uint32_t* ctrl,
+                                                                   double* records, int64_t n, int64_t m, uint32_t ipg,
+                                                                   uint32_t items, double n_elems, int polls) {
+  constexpr int NDW = (VEC * K + 3) / 4;
+  static_assert(K >= 1 && K <= 4, "plane bytes of a column in one word");
+  __shared__ WaveTotals red;
+  __shared__ SumExchange ex;
+  const int tid = threadIdx.x, wave = tid / kWave, lane = tid & (kWave - 1);
+  ChipMail* mail = reinterpret_cast<ChipMail*>(reinterpret_cast<char*>(ctrl) + kMailOffset);
+  const uint32_t calls = uint32_t(__builtin_amdgcn_readfirstlane(int(mail->calls[blockIdx.x])));
+  // the thread's item in workgroup b: its first row and column, and how many rows it has (0: none)
+  struct Place {
+    int64_t row0, col;
+    int rows;
+  };
+  auto place = [&](int b) {
+    const uint32_t it = uint32_t(b) * kFirstBlock + uint32_t(tid);
+    const uint32_t g = it / ipg;
+    Place p;
+    p.row0 = int64_t(g) * 8;
+    p.col = int64_t(it - g * ipg) * VEC;
+    p.rows = it < items ? (n - p.row0 < 8 ? int(n - p.row0) : 8) : 0;
+    return p;
+  };
+  auto load = [&](const Place& p, RawRow<VEC> (&rows)[8]) {
+    const T* xc = x + p.row0 * m + p.col;
+#pragma unroll
+    for (int r = 0; r < 8; ++r) {
+      if constexpr (VEC > 1) rows[r].v = make_uint4(0u, 0u, 0u, 0u); else rows[r].v = 0u;
+      if (r < p.rows) rows[r] = load_raw<T, VEC>(xc + r * m);
+    }
+  };
+  const Place mine = place(blockIdx.x);
+  RawRow<VEC> kept[8];
+  load(mine, kept);
+
+  double a[K > 1 ? K - 1 : 1] = {};
+  // the sum of |rho_J| over the workgroup's items, whoever's items `rows` are; thread 0 has it
+  auto add_item = [&](auto J, const RawRow<VEC> (&rows)[8], int nrows, double (&acc)[VEC]) {
+    constexpr int j = decltype(J)::value;
+#pragma unroll
+    for (int r = 0; r < 8; ++r) {
+      if (r < nrows) {
+        float f[VEC];
+        widen_raw<VEC>(rows[r], f);
+#pragma unroll
+        for (int c = 0; c < VEC; ++c) {
+          double rho = double(f[c] + 0.0f);
+#pragma unroll
+          for (int q = 0; q < j; ++q) rho = residue_step(rho, a[q]);
+          acc[c] += fabs(rho);
+        }
+      }
+    }
+  };
+  auto block_total = [&](double (&acc)[VEC]) {
+#pragma unroll
+    for (int c = 1; c < VEC; ++c) acc[0] += acc[c];
+    const double t = wave_sum(acc[0]);
+    if (lane == 0) red.v[wave][0] = t;
+    __syncthreads();
+    double total = red.v[0][0];
+#pragma unroll
+    for (int w = 1; w < kFirstWaves; ++w) total += red.v[w][0];
+    __syncthreads();  // the buffer is free again
+    return total;
+  };
+  auto pass = [&](auto J) {
+    constexpr int j = decltype(J)::value;
+    double acc[VEC];
+#pragma unroll
+    for (int c = 0; c < VEC; ++c) acc[c] = 0.0;
+    add_item(J, kept, mine.rows, acc);
+    double total = block_total(acc);
+    if (gridDim.x > 1) {
+      const uint32_t tag = calls + 1u + uint32_t(j);
+      if (tid == 0) post_sum(sum_box(ctrl, j, blockIdx.x), tag, total);
+      look_for_sums(ctrl, j, tag, polls, ex);
+      __syncthreads();
+      for (;;) {
+        int count = 0;
+#pragma unroll
+        for (int w = 0; w < kHeldGrid / kWave; ++w) count += __popcll((unsigned long long)ex.missing[w]);
+        count = __builtin_amdgcn_readfirstlane(count);
+        if (count == 0) break;
+        // one of the missing workgroups, another for neighbouring ones
+        int skip = int(blockIdx.x) % count, found = 0;
+#pragma unroll
+        for (int w = 0; w < kHeldGrid / kWave; ++w) {
+          uint64_t mw = ex.missing[w];
+          const int here = __popcll((unsigned long long)mw);
+          if (skip >= 0 && skip < here) {
+            for (; skip > 0; --skip) mw &= mw - 1;
+            found = w * kWave + __ffsll((unsigned long long)mw) - 1;
+          }
+          skip -= here;
+        }
+        const int b = __builtin_amdgcn_readfirstlane(found);
+        double other[VEC];
+#pragma unroll
+        for (int c = 0; c < VEC; ++c) other[c] = 0.0;
+        RawRow<VEC> rows[8];
+        const Place p = place(b);
+        load(p, rows);
+        add_item(J, rows, p.rows, other);
+        const double t = block_total(other);  // (its barriers: ex has been read by all)
+        if (tid == 0) {
+          post_sum(sum_box(ctrl, j, b), tag, t);
+          __builtin_amdgcn_s_waitcnt(0x0F70);  // it is there before the next look
+        }
+        __syncthreads();
+        look_for_sums(ctrl, j, tag, 1, ex);
+        __syncthreads();
+      }
+      total = (ex.part[0] + ex.part[1]) + (ex.part[2] + ex.part[3]);
+      __syncthreads();  // ex is free again
+    }
+    const float alpha = float(total / n_elems);
+    if (blockIdx.x == 0 && tid == 0) header[j] = alpha;
+    a[j] = double(alpha);
+  };
+  if constexpr (K > 1) pass(std::integral_constant<int, 0>{});
+  if constexpr (K > 2) pass(std::integral_constant<int, 1>{});
+  if constexpr (K > 3) pass(std::integral_constant<int, 2>{});
+  if (K > 1 && gridDim.x > 1 && tid < kHeldGrid && uint32_t(tid) % gridDim.x == blockIdx.x) mail->calls[tid] = calls + uint32_t(K - 1);
+
+  // last pass: signs, planes and sums, as in mbq_init_encode_kernel
+  const bool all_finite = __builtin_amdgcn_readfirstlane(fabs(a[0]) < double(__builtin_inff()) ? 1 : 0) != 0;
+  double sum_abs = 0.0, sum_x = 0.0;
+  uint32_t cnt[K];
+#pragma unroll
+  for (int p = 0; p < K; ++p) cnt[p] = 0;
+  {
+    uint32_t neg[VEC][K];
+#pragma unroll
+    for (int c = 0; c < VEC; ++c)
+#pragma unroll
+      for (int q = 0; q < K; ++q) neg[c][q] = 0;
+    float sx32 = 0.0f;
+    auto rows = [&](auto finite) {
+#pragma unroll
+      for (int r = 0; r < 8; ++r) {
+        if (r < mine.rows) {
+          float row[VEC];
+          widen_raw<VEC>(kept[r], row);
+#pragma unroll
+          for (int c = 0; c < VEC; ++c) {
+            sx32 = __fadd_rn(sx32, row[c]);
+            double rho = double(row[c] + 0.0f);
+#pragma unroll
+            for (int q = 0; q < K; ++q) {
+              const uint32_t sign = decltype(finite)::value ? uint32_t(uint64_t(__double_as_longlong(rho)) >> 32)
+                                                            : (rho >= 0.0 ? 0u : 0x80000000u);
+              neg[c][q] = __builtin_amdgcn_alignbit(neg[c][q], sign, 31);
+              if (q < K - 1) rho = residue_step(rho, a[q]);
+            }
+            sum_abs += fabs(rho);
+          }
+        }
+      }
+    };
+    if (K > 1 && all_finite) rows(std::true_type{}); else rows(std::false_type{});
+    uint32_t acc[VEC];
+    const uint32_t valid = 0xFFu & (0xFFu << (8 - mine.rows));
+#pragma unroll
+    for (int c = 0; c < VEC; ++c) {
+      acc[c] = 0;
+#pragma unroll
+      for (int q = 0; q < K; ++q) {
+        const uint32_t plus = ~(neg[c][q] << (8 - mine.rows)) & valid;
+        cnt[q] += __popc(plus);
+        acc[c] |= plus << (8 * q);
+      }
+    }
+    sum_x += double(sx32);
+    if (mine.rows > 0) {
+      uint8_t* dst = payload + ((mine.row0 / 8 * m + mine.col) * K);
+      if constexpr (VEC > 1) {
+        uint32_t out[NDW];
+#pragma unroll
+        for (int w = 0; w < VEC / 4; ++w) {
+          const uint32_t q4[4] = {acc[4 * w], acc[4 * w + 1], acc[4 * w + 2], acc[4 * w + 3]};
+          columns_to_payload<K>(q4, &out[K * w]);
+        }
+        store_dwords<NDW>(reinterpret_cast<uint32_t*>(dst), out);
+      } else {
+#pragma unroll
+        for (int p = 0; p < K; ++p) dst[p] = uint8_t(acc[0] >> (8 * p));
+      }
+    }
+  }
+  {
+    const double sa = wave_sum(sum_abs), sx = wave_sum(sum_x);
+    if (lane == 0) { red.v[wave][0] = sa; red.v[wave][1] = sx; }
+#pragma unroll
+    for (int p = 0; p < K; ++p) {
+      const double c = double(wave_sum(cnt[p]));
+      if (lane == 0) red.v[wave][2 + p] = c;
+    }
+  }
+  __syncthreads();
+  if (tid < K + 2) {
+    double total = red.v[0][tid];
+    for (int w = 1; w < kFirstWaves; ++w) total += red.v[w][tid];
+    double* const rec = records + int64_t(tid) * gridDim.x + blockIdx.x;
+    __hip_atomic_store(rec, total, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  }
+  if (!last_workgroup(ctrl)) return;
+  double* tot = red.v[0];
+  const int nrec = int(gridDim.x);
+  for (int s = wave; s < K + 2; s += kFirstWaves) {
+    const double t = sum_records<true>(records + int64_t(s) * nrec, nrec, lane);
+    if (lane == 0) tot[s] = t;
+  }
+  if (tid == 0) ctrl[kDoneCounter] = 0u;
+  __syncthreads();
+  if (tid != 0) return;
+  const float last_alpha = float(tot[0] / n_elems);
+  header[K - 1] = last_alpha;
+  double dot = 0.0;
+#pragma unroll
+  for (int p = 0; p < K; ++p) dot += (p == K - 1 ? double(last_alpha) : a[p < K - 1 ? p : 0]) * (2.0 * tot[2 + p] - n_elems);
+  header[K] = float((dot - tot[1]) / n_elems);
+}
+
 // After the last pass: alpha_j = (sum of the workgroups' |rho_j| sums) / N, written to alpha_out[j]; of
 // a batch-0 compression (nstat = k + 2) also the rest of the header:
 // m_q = mean(B^0 alpha^0 - x) = (sum_p alpha_p (2 cnt_p - N) - sum x) / N  (eq. (biased error)),
@@ -1894,6 +2185,41 @@ hipError_t init_encode_k(const accept_desc& d, const T* x, const InitCall& c, ui
   }
 }
 
+// Batch 0 in one kernel: tensors of at most kFinishGridMax workgroups of an item per thread, the widths in use.
+struct FirstPlan {
+  int vec, grid;  // grid 0: not taken
+  uint32_t ipg, items;
+};
+FirstPlan first_plan(const accept_desc& d, int vec) {
+  FirstPlan f{};
+  f.vec = d.m % vec == 0 ? vec : 1;
+  const int64_t ipg = d.m / f.vec, items = (d.n + 7) / 8 * ipg;
+  if (d.bits > 4 || items > int64_t(kFinishGridMax) * kFirstBlock) return f;
+  f.ipg = uint32_t(ipg);
+  f.items = uint32_t(items);
+  f.grid = int((items + kFirstBlock - 1) / kFirstBlock);
+  return f;
+}
+template <typename T, int K, int VEC>
+hipError_t launch_first(const accept_desc& d, const FirstPlan& f, const T* x, float* header, uint8_t* payload, void* ws,
+                        int polls, hipStream_t s) {
+  double* records = reinterpret_cast<double*>(static_cast<char*>(ws) + kCtrlBytes);
+  hipLaunchKernelGGL((mbq_first_kernel<T, K, VEC>), dim3(f.grid), dim3(kFirstBlock), 0, s, x, header, payload,
+                     static_cast<uint32_t*>(ws), records, d.n, d.m, f.ipg, f.items, double(d.n) * double(d.m), polls);
+  return hipGetLastError();
+}
+template <typename T, int VEC>
+hipError_t first_k(const accept_desc& d, const FirstPlan& f, const T* x, float* header, uint8_t* payload, void* ws, int polls,
+                   hipStream_t s) {
+  switch (d.bits) {
+    case 1: return launch_first<T, 1, VEC>(d, f, x, header, payload, ws, polls, s);
+    case 2: return launch_first<T, 2, VEC>(d, f, x, header, payload, ws, polls, s);
+    case 3: return launch_first<T, 3, VEC>(d, f, x, header, payload, ws, polls, s);
+    case 4: return launch_first<T, 4, VEC>(d, f, x, header, payload, ws, polls, s);
+    default: return hipErrorInvalidValue;
+  }
+}
+
 template <typename T>
 hipError_t launch_init_pass(int j, const T* x, int64_t N, const InitCall& c, int grid, hipStream_t s) {
 #define ACCEPT_INIT(JJ)                                                                                        \
@@ -2050,13 +2376,21 @@ hipError_t launch_mbq_decompress(const accept_desc& d, const void* header, const
 // Otherwise a batch-0 compression: k - 1 sum passes and one pass that also writes the bit planes
 // of B^0 to payload; alpha_out is then the header, [alpha^0, m_q].
 hipError_t launch_mbq_init(const accept_desc& d, const MPlan& p, const void* x, float* alpha_out, void* payload,
-                           void* ws, hipStream_t s) {
+                           void* ws, hipStream_t s, int polls) {
   double* records = reinterpret_cast<double*>(static_cast<char*>(ws) + kCtrlBytes);
   const int64_t N = d.n * d.m;
   const int k = d.bits;
   const bool bf = d.in_dtype == ACCEPT_BF16;
   const bf16_t* xb = static_cast<const bf16_t*>(x);
   const float* xf = static_cast<const float*>(x);
+  if (payload != nullptr) {
+    const FirstPlan f = first_plan(d, p.vec);
+    if (f.grid != 0) {
+      uint8_t* pl = static_cast<uint8_t*>(payload);
+      if (bf) return f.vec == 8 ? first_k<bf16_t, 8>(d, f, xb, alpha_out, pl, ws, polls, s) : first_k<bf16_t, 1>(d, f, xb, alpha_out, pl, ws, polls, s);
+      return f.vec == 4 ? first_k<float, 4>(d, f, xf, alpha_out, pl, ws, polls, s) : first_k<float, 1>(d, f, xf, alpha_out, pl, ws, polls, s);
+    }
+  }
   const int64_t tiles = (N + kTileElems - 1) / kTileElems;
   InitCall c{alpha_out, nullptr, 0, nullptr, double(N)};
   int nrec = 0, nstat = 1;

@@ -7,18 +7,6 @@
 
 namespace accept {
 
-// What the workgroups of calls with one workspace leave each other, in its control block.  A call's tag is one
-// more than the number of calls before it, of which every workgroup has a word of its own: it reads the
-// word when it starts and raises it when it ends (and those of the workgroups that this call does not have),
-// so all of them agree.  So nothing has to be emptied: a value of an earlier call bears an earlier tag.
-// (Counting the workgroups off on one counter, and the last one emptying everything, cost small tensors
-// 1.5 us.)
-struct ChipMail {
-  uint64_t first[kHeldGrid], last[kHeldGrid];  // tag and the workgroup's maximum: of its first (or only), its last channel
-  uint32_t calls[kHeldGrid];
-};
-static_assert(kMailOffset + sizeof(ChipMail) <= kCtrlBytes, "the control block holds them");
-
 namespace {
 
 // One value of every workgroup of a call, exchanged through the mailboxes: the largest of all.  The wait is

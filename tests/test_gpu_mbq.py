@@ -365,3 +365,45 @@ def test_encoder_that_solves_itself(A, n, m, bf16, one):
         g.replay()
         torch.cuda.synchronize()
         assert (dev_bytes(header), dev_bytes(payload)) == want
+
+
+# Batch 0 of at most 64 workgroups of 512 items (8 rows, a 16-byte vector or a column): one kernel, the passes in registers.
+@pytest.mark.parametrize("n,m,k,bf16", [
+    (8, 64, 2, False),              # one workgroup
+    (128, 160, 4, False),           # two, the second not full
+    (5, 333, 3, True),              # single columns, a partial row group
+    (64, 64 * 64 * 4, 3, False),    # 64 workgroups
+    (64, 64 * 64 * 4 + 4, 4, False),  # one item more: a kernel for every pass
+    (31, 16384, 4, True),
+    (40, 6553, 2, False),           # 64 of single columns
+])
+def test_batch0_in_one_kernel(A, n, m, k, bf16):
+    torch = torch_mod()
+    x = si.make_shape("relu_lognormal", (n, m), 950 + k)
+    xd, bits = to_dev(x, bf16)
+    xf = orc.widen_bf16(bits).reshape(n, m) if bf16 else x
+    d = A.make_desc(A.MBQ, k, n, m, in_dtype=A.BF16 if bf16 else A.F32)
+    header, payload, ws = A.alloc_outputs(d, "cuda")
+    oh = np.frombuffer(orc.mbq_compress_first(xf, k, n, m)[0], dtype="<f4")
+    seen = set()
+    for polls in (64, 0, 1, 64):  # seen by each other; workgroups add up each other's parts
+        print("case", n, m, k, bf16, polls, flush=True)
+        header.zero_()
+        payload.zero_()
+        A.accept_compress_polls(d, xd, header, payload, ws, polls)
+        torch.cuda.synchronize()
+        gh = np.frombuffer(dev_bytes(header), dtype="<f4")
+        assert np.all(np.abs(gh.astype(np.float64) - oh) <= 1e-6 * np.abs(oh[:k]).sum()), (gh, oh, polls)
+        op = orc.mbq_pack(orc.mbq_residue_signs(xf, gh[:k]), k, n, m)
+        assert first_mismatch(dev_bytes(payload), op.tobytes()) is None, polls
+        seen.add(gh.tobytes())
+    assert len(seen) == 1  # the same bits, whoever added up
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g):
+        A.accept_mbq_compress_first(d, xd, header=header, payload=payload, workspace=ws)
+    for _ in range(3):
+        A.accept_compress(d, xd, alpha_prev=header.view(torch.float32)[:k].clone(), workspace=ws)  # eager, same workspace
+        header.zero_()
+        g.replay()
+        torch.cuda.synchronize()
+        assert dev_bytes(header) in seen
