@@ -407,3 +407,10 @@ def test_batch0_in_one_kernel(A, n, m, k, bf16):
         g.replay()
         torch.cuda.synchronize()
         assert dev_bytes(header) in seen
+
+
+@pytest.mark.parametrize("n,m,k,bf16", [(5, 64 * 4 * 2048 + 516, 4, False), (1, 64 * 4 * 2050, 3, False), (3, 64 * 8 * 2048 + 1032, 2, True)])
+def test_few_rows_and_more_wave_items_than_wavefronts(A, n, m, k, bf16):
+    """A tensor of fewer than eight rows: some wavefronts have a second wave-item, asked for while the first is used."""
+    x = si.make_shape("student_t3", (n, m), 970 + n)
+    run_case(A, x, k, n, m, t=5, in_bf16=bf16, out_bf16=bf16, tag="few rows")
