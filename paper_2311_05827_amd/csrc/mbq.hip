@@ -888,11 +888,11 @@ __device__ __forceinline__ void skip_rows(const EncodeTables<K>&, uint32_t (&acc
 }
 template <int K, int VEC, int GR>
 __device__ __forceinline__ void skip_rows(const ValueTables<K>&, uint32_t (&)[VEC][1]) {}
-// rows: the first wave-item's (`loaded`), else any registers.
-template <typename T, int K, int VEC, bool RAGGED, int MC, typename Tables>
+// AHEAD: the tensor has nothing else; rows: those of the first wave-item.
+template <typename T, int K, int VEC, bool RAGGED, int MC, bool AHEAD, typename Tables>
 __device__ __forceinline__ void encode_partial(const Tables& tb, const T* __restrict__ x, uint8_t* __restrict__ payload,
                                                int64_t n, int64_t m, uint32_t ipg, uint32_t wpg, int maxcnt,
-                                               uint32_t first, uint32_t step, RawRow<VEC> (&rows)[8], bool loaded,
+                                               uint32_t first, uint32_t step, RawRow<VEC> (&rows)[8],
                                                EncodeStats<K>& st) {
   constexpr int NW = (K + 3) / 4;
   constexpr int GR = VEC >= 4 ? 1 : 4 / VEC;
@@ -901,7 +901,6 @@ __device__ __forceinline__ void encode_partial(const Tables& tb, const T* __rest
   const int nrows = int(n - g * 8);
   if (first >= wpg) return;
   ItemAddr ia = item_addr(first, wpg, ipg, lane);
-  if (!loaded) load_partial<T, VEC, RAGGED>(x, n, m, ia, rows);
   auto work = [&] {
     float h32[K];
     float sx32 = 0.0f;
@@ -933,6 +932,14 @@ __device__ __forceinline__ void encode_partial(const Tables& tb, const T* __rest
     for (int p = 0; p < K; ++p) h32[p] *= sum_factor(tb);
     finish_item<K, VEC, RAGGED>(acc, h32, sx32, payload + (g * m + int64_t(ia.jv) * VEC) * K, ia.counts, st);
   };
+  if constexpr (!AHEAD) {
+    for (uint32_t w = first; w < wpg; w += step) {
+      ia = item_addr(w, wpg, ipg, lane);
+      load_partial<T, VEC, RAGGED>(x, n, m, ia, rows);
+      work();
+    }
+    return;
+  }
   if (first + step >= wpg) {  // one wave-item: nothing to ask for
     work();
     return;
@@ -1148,7 +1155,8 @@ __device__ __forceinline__ void finish_in_last_workgroup(const MbqCall& call, co
 // column per thread.  RAGGED: m is not a multiple of VEC, so rows start at any alignment; vectors
 // all the same, and the last m % VEC columns one per thread (15 x 390403 float32, k = 3: this kernel
 // 12.0 us and the decoder 7.2, against 14.3 and 9.0 with single columns throughout).
-template <typename T, int K, int VEC, bool RAGGED, bool FINISH>
+// FEW: fewer than eight rows (a kernel of its own: what they need cost the others 0.3 us).
+template <typename T, int K, int VEC, bool RAGGED, bool FINISH, bool FEW>
 __global__ __launch_bounds__(kEncBlock) void mbq_encode_kernel(const T* __restrict__ x, uint8_t* __restrict__ payload,
                                                                MbqCall call, int64_t n, int64_t m, uint32_t ipg,
                                                                uint32_t wpg, uint32_t n_wave_items, bool wide) {
@@ -1199,8 +1207,8 @@ __global__ __launch_bounds__(kEncBlock) void mbq_encode_kernel(const T* __restri
 
   const uint32_t wave_id = uint32_t(__builtin_amdgcn_readfirstlane(tid / kWave));
   const uint32_t partial_first = wave_id * gridDim.x + blockIdx.x;
-  const bool partial_loaded = n < 8 && wide && partial_first < wpg;  // there is no stream: its registers are free
-  if (partial_loaded) load_partial<T, VEC, RAGGED>(x, n, m, item_addr(partial_first, wpg, ipg, lane), fr);
+  if (FEW && wide && partial_first < wpg)  // there is no stream: its registers are free
+    load_partial<T, VEC, RAGGED>(x, n, m, item_addr(partial_first, wpg, ipg, lane), fr);
 
   int maxcnt = 1;
   if constexpr (BY_VALUE) {
@@ -1223,6 +1231,7 @@ __global__ __launch_bounds__(kEncBlock) void mbq_encode_kernel(const T* __restri
   const int64_t gtid = int64_t(blockIdx.x) * kEncBlock + tid;
   const bool stream = n_wave_items != 0u;  // else: a geometry too narrow for wave-items
   auto complete_groups = [&] {
+    if constexpr (FEW) return;
     if (stream && maxcnt == 1) {
       encode_stream<T, K, VEC, RAGGED, 1>(tb, x, payload, uint64_t(m), ipg, wpg, q, cur, nxt, ca, fr, st);
     } else if (stream && maxcnt == 2 && K <= 4 && !BY_VALUE) {
@@ -1253,10 +1262,12 @@ __global__ __launch_bounds__(kEncBlock) void mbq_encode_kernel(const T* __restri
     int64_t col0 = 0;  // columns from here on are left
     if (n % 8 != 0 && wide && maxcnt == 1) {
       RawRow<VEC> own[8];
+      if constexpr (FEW) {
 #pragma unroll
-      for (int r = 0; r < 8; ++r) own[r] = fr[r];
-      encode_partial<T, K, VEC, RAGGED, 1>(tb, x, payload, n, m, ipg, wpg, maxcnt, partial_first,
-                                           gridDim.x * uint32_t(kEncWaves), own, partial_loaded, st);
+        for (int r = 0; r < 8; ++r) own[r] = fr[r];
+      }
+      encode_partial<T, K, VEC, RAGGED, 1, FEW>(tb, x, payload, n, m, ipg, wpg, maxcnt, partial_first,
+                                           gridDim.x * uint32_t(kEncWaves), own, st);
       col0 = int64_t(ipg) * VEC;
     }
     if (n % 8 != 0) {
@@ -2132,9 +2143,13 @@ MbqCall make_call(const accept_desc& d, const float* alpha_prev, void* header, v
 template <typename T, int K, int VEC, bool RAGGED>
 hipError_t launch_encode(const accept_desc& d, const MPlan& p, const T* x, uint8_t* payload, const MbqCall& call,
                          hipStream_t s) {
-  auto launch = [&](auto finish) {
-    hipLaunchKernelGGL((mbq_encode_kernel<T, K, VEC, RAGGED, decltype(finish)::value>), dim3(p.grid), dim3(kEncBlock), 0, s, x,
+  auto launch_rows = [&](auto finish, auto few) {
+    hipLaunchKernelGGL((mbq_encode_kernel<T, K, VEC, RAGGED, decltype(finish)::value, decltype(few)::value>), dim3(p.grid), dim3(kEncBlock), 0, s, x,
                        payload, call, d.n, d.m, uint32_t(p.wide ? d.m / VEC : 1), p.wpg, p.n_wave_items, p.wide);
+  };
+  auto launch = [&](auto finish) {
+    if (d.n < 8) launch_rows(finish, std::true_type{});
+    else launch_rows(finish, std::false_type{});
   };
   if constexpr (K <= 4) {
     if (p.finish) {
