@@ -1799,26 +1799,16 @@ __device__ __forceinline__ void post_sum(const SumBox& box, uint32_t tag, double
   __hip_atomic_store(box.lo, t | uint32_t(bits), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   __hip_atomic_store(box.hi, t | uint32_t(bits >> 32), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
-__device__ __forceinline__ void look_for_sums(uint32_t* ctrl, int set, uint32_t tag, int polls, SumExchange& ex) {
-  const int tid = threadIdx.x;
-  if (tid >= kHeldGrid) return;
-  const bool box = uint32_t(tid) < gridDim.x;
-  const SumBox at = sum_box(ctrl, set, tid);
-  uint64_t missing = __ballot(box), lo = 0, hi = 0;
-  for (int i = 0; i < polls; ++i) {
-    if (box) {
-      lo = __hip_atomic_load(at.lo, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      hi = __hip_atomic_load(at.hi, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    }
-    missing = __ballot(box && (uint32_t(lo >> 32) != tag || uint32_t(hi >> 32) != tag));
-    if (missing == 0) break;
-    __builtin_amdgcn_s_sleep(2);
-  }
-  const uint64_t bits = (hi << 32) | uint32_t(lo);
-  const double t = wave_sum(box && missing == 0 ? __longlong_as_double((long long)bits) : 0.0);
-  if ((tid & (kWave - 1)) == 0) {
-    ex.part[tid / kWave] = t;
-    ex.missing[tid / kWave] = missing;
+// Wavefronts 0 to 3 look for a lane's box each, at most `polls` times; `mine` is the lane's, `here` whether it is there.
+__device__ __forceinline__ void look_for_sums(uint32_t* ctrl, int set, uint32_t tag, int polls, double& mine, bool& here) {
+  const SumBox at = sum_box(ctrl, set, threadIdx.x);
+  for (int i = 0; i < polls && __ballot(!here) != 0; ++i) {
+    if (i > 0) __builtin_amdgcn_s_sleep(2);
+    if (here) continue;
+    const uint64_t lo = __hip_atomic_load(at.lo, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    const uint64_t hi = __hip_atomic_load(at.hi, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    here = uint32_t(lo >> 32) == tag && uint32_t(hi >> 32) == tag;
+    if (here) mine = __longlong_as_double((long long)((hi << 32) | uint32_t(lo)));
   }
 }
 
@@ -1901,9 +1891,16 @@ __global__ __launch_bounds__(kFirstBlock, 2) void mbq_first_kernel(const T* __re
     if (gridDim.x > 1) {
       const uint32_t tag = calls + 1u + uint32_t(j);
       if (tid == 0) post_sum(sum_box(ctrl, j, blockIdx.x), tag, total);
-      look_for_sums(ctrl, j, tag, polls, ex);
-      __syncthreads();
-      for (;;) {
+      // threads 0 to 255 hold a workgroup's sum each, once it is there
+      double one = 0.0;
+      bool here = uint32_t(tid) >= gridDim.x;
+      if (wave < kHeldGrid / kWave) look_for_sums(ctrl, j, tag, polls, one, here);
+      for (;;) {  // a workgroup less is missing after every turn, whatever becomes of its mailbox
+        if (wave < kHeldGrid / kWave) {
+          const uint64_t missing = __ballot(!here);
+          if (lane == 0) ex.missing[wave] = missing;
+        }
+        __syncthreads();
         int count = 0;
 #pragma unroll
         for (int w = 0; w < kHeldGrid / kWave; ++w) count += __popcll((unsigned long long)ex.missing[w]);
@@ -1914,12 +1911,12 @@ __global__ __launch_bounds__(kFirstBlock, 2) void mbq_first_kernel(const T* __re
 #pragma unroll
         for (int w = 0; w < kHeldGrid / kWave; ++w) {
           uint64_t mw = ex.missing[w];
-          const int here = __popcll((unsigned long long)mw);
-          if (skip >= 0 && skip < here) {
+          const int number = __popcll((unsigned long long)mw);
+          if (skip >= 0 && skip < number) {
             for (; skip > 0; --skip) mw &= mw - 1;
             found = w * kWave + __ffsll((unsigned long long)mw) - 1;
           }
-          skip -= here;
+          skip -= number;
         }
         const int b = __builtin_amdgcn_readfirstlane(found);
         double other[VEC];
@@ -1930,14 +1927,15 @@ __global__ __launch_bounds__(kFirstBlock, 2) void mbq_first_kernel(const T* __re
         load(p, rows);
         add_item(J, rows, p.rows, other);
         const double t = block_total(other);  // (its barriers: ex has been read by all)
-        if (tid == 0) {
-          post_sum(sum_box(ctrl, j, b), tag, t);
-          __builtin_amdgcn_s_waitcnt(0x0F70);  // it is there before the next look
-        }
-        __syncthreads();
-        look_for_sums(ctrl, j, tag, 1, ex);
-        __syncthreads();
+        if (tid == 0) post_sum(sum_box(ctrl, j, b), tag, t);
+        if (tid == b) { one = t; here = true; }
+        if (wave < kHeldGrid / kWave) look_for_sums(ctrl, j, tag, 1, one, here);
       }
+      if (wave < kHeldGrid / kWave) {
+        const double t = wave_sum(one);
+        if (lane == 0) ex.part[wave] = t;
+      }
+      __syncthreads();
       total = (ex.part[0] + ex.part[1]) + (ex.part[2] + ex.part[3]);
       __syncthreads();  // ex is free again
     }

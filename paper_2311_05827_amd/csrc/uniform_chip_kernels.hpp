@@ -16,14 +16,15 @@ namespace {
 // the work of those that have not started, which later post the same values.  So every workgroup ends whatever else
 // runs, and the result does not depend on it.
 struct Exchange {
-  float top[kHeldBlock / kWave];
+  float top[kHeldBlock / kWave];  // of the values seen so far, by wavefront
+  float part[kHeldBlock / kWave];
   uint64_t missing[kHeldGrid / kWave];
 };
 __device__ __forceinline__ void post(uint64_t* box, uint32_t tag, float v) {
   __hip_atomic_store(box, (uint64_t(tag) << 32) | f32_as_u32(v), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 // Wavefronts 0 to 3 look for a box per lane, at most `polls` times; on return (in front of a barrier) ex holds
-// what is missing and, where nothing is, the wavefronts' maxima.
+// what is missing and the wavefronts' maxima of what is there.
 __device__ __forceinline__ void look_for_mail(const ChipMail* mail, uint32_t tag, int polls, Exchange& ex) {
   const int tid = threadIdx.x;
   if (tid >= kHeldGrid) return;
@@ -36,7 +37,7 @@ __device__ __forceinline__ void look_for_mail(const ChipMail* mail, uint32_t tag
     if (missing == 0) break;
     __builtin_amdgcn_s_sleep(4);
   }
-  const float t = wave_max(u32_as_f32(box && missing == 0 ? uint32_t(v) : 0u));
+  const float t = wave_max(u32_as_f32(box && uint32_t(v >> 32) == tag ? uint32_t(v) : 0u));
   if ((tid & (kWave - 1)) == 0) {
     ex.top[tid / kWave] = t;
     ex.missing[tid / kWave] = missing;
@@ -72,24 +73,31 @@ __device__ __forceinline__ float largest_mail(const Exchange& ex) {
   for (int w = 1; w < kHeldGrid / kWave; ++w) c = fmaxf(c, ex.top[w]);
   return c;
 }
-// Posts what is missing until nothing is; part(w): a thread's share of the largest value of workgroup w.
+// Finds and posts what is missing until nothing is; part(w): a thread's share of the largest value of workgroup w.  Every
+// turn takes at least one workgroup off the list, whatever becomes of its mailbox.
 template <typename Part>
 __device__ __forceinline__ void post_missing(ChipMail* mail, uint32_t tag, Exchange& ex, Part part) {
-  const int tid = threadIdx.x;
+  const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid / kWave;
   for (int count = missing_count(ex); count != 0; count = missing_count(ex)) {
     const int w = missing_one(ex, count);
     const float v = wave_max(part(w));
+    if (lane == 0) ex.part[wave] = v;
     __syncthreads();
-    if ((tid & (kWave - 1)) == 0) ex.top[tid / kWave] = v;
-    __syncthreads();
-    if (tid == 0) {
-      float t = ex.top[0];
-      for (int i = 1; i < kHeldBlock / kWave; ++i) t = fmaxf(t, ex.top[i]);
-      post(mail->first + w, tag, t);
-      __builtin_amdgcn_s_waitcnt(0x0F70);  // it is there before the next look
+    if (wave < kHeldGrid / kWave) {
+      float t = ex.part[0];
+      for (int i = 1; i < kHeldBlock / kWave; ++i) t = fmaxf(t, ex.part[i]);
+      if (tid == 0) post(mail->first + w, tag, t);
+      const uint64_t missing = ex.missing[wave];
+      const bool look = (missing >> lane) & 1u;
+      const uint64_t box = look ? __hip_atomic_load(mail->first + tid, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0;
+      const bool there = look && uint32_t(box >> 32) == tag;
+      const float seen = wave_max(tid == w ? t : there ? u32_as_f32(uint32_t(box)) : 0.0f);
+      const uint64_t left = missing & ~__ballot(there || tid == w);
+      if (lane == 0) {
+        ex.top[wave] = fmaxf(ex.top[wave], seen);
+        ex.missing[wave] = left;
+      }
     }
-    __syncthreads();
-    look_for_mail(mail, tag, 1, ex);
     __syncthreads();
   }
 }
@@ -292,15 +300,18 @@ __global__ __launch_bounds__(kHeldBlock, 2) void quantize_held_kernel(const T* _
       float v = 0.0f;
       for (int64_t unit = w; unit < units; unit += kHeldGrid) {
         const T* xu = x + unit * kUnitElems;
-        uint4 raw[LOADS];
+#pragma nounroll
+        for (int half = 0; half < LOADS; half += 4) {  // four loads at a time: registers
+          uint4 raw[4];
 #pragma unroll
-        for (int u = 0; u < LOADS; ++u) raw[u] = load16_stream(xu + (u * kHeldBlock + tid) * VEC);
+          for (int u = 0; u < 4; ++u) raw[u] = load16_stream(xu + ((half + u) * kHeldBlock + tid) * VEC);
 #pragma unroll
-        for (int u = 0; u < LOADS; ++u) {
-          float f[VEC];
-          widen(raw[u], f);
+          for (int u = 0; u < 4; ++u) {
+            float f[VEC];
+            widen(raw[u], f);
 #pragma unroll
-          for (int e = 0; e < VEC; ++e) v = fmaxf(v, fabsf(f[e]));
+            for (int e = 0; e < VEC; ++e) v = fmaxf(v, fabsf(f[e]));
+          }
         }
       }
       const int64_t b = units * kUnitElems + int64_t(w) * kWave + lane;
