@@ -158,7 +158,7 @@ __device__ __forceinline__ void quantize_behind(const T* __restrict__ x, uint32_
 // Time of a call on one stream while another is busy, k = 8, two reads / held, held with a second kernel always /
 // now (us): small elementwise kernels, 103 MB float32 43 / 32, 28.6 / 22.2, 205 MB 85 / 70, 56 / 49, 103 MB bfloat16 53 /
 // 39, 33.6 / 26.2; matrix products beside 205 MB 184 / 179, 240 / 150, beside 103 MB bfloat16 160 / 155, 228 / 128;
-// copies of 512 MB without a pause 66 / 98, 105 / 115, 130 / 161, 162 / 160, 72 / 145, 142 / 140.
+// copies of 512 MB without a pause 66 / 98, 105 / 86, 130 / 161, 162 / 160, 72 / 145, 142 / 140.
 //
 // 51.4 M float32 values (205 MB), k = 8: 58.3 us a call (two reads 69.5): 31 us to the mailboxes, 2 to 3 for the
 // exchange.  103 MB: 32 -> 26 us against the held pass with a second kernel and plain stores, bfloat16 103 MB 36 -> 30.
