@@ -94,6 +94,10 @@ hipError_t launch_whole(const accept_desc& d, const UPlan& p, const T* x, float*
 //     12.9 / 11.8; bfloat16: 2.5 M 6.5 / 6.5, 8.3 M 10.8 / 9.5, 25 M 21.8 / 18.9;
 //   stochastic, float32: 20 K 7.6 / 4.5, 300 K 7.9 / 5.8, 1 M 7.9 / 7.1, 4 M 11.3 / 10.9, 8.3 M 17.5 / 17.4, 16.7 M
 //     35 / 30; bfloat16: 20 K 7.4 / 4.6, 1 M 7.6 / 6.7, 2.5 M 8.9 / 8.6, 4 M 9.3 / 9.9, 12 M 19.9 / 20.3.
+// Nearest, from 0.5 M (if not whole tiles of 8192 values, 1.5 M) to 3.2 M values (bfloat16 5 M), the device alone is faster with
+// two kernels, k = 4: float32 0.5 M 5.0 / 5.6, 2.1 M 5.4 / 6.3 to 7.1, 2.5 M 6.7 / 7.2, 3.2 M 7.4 / 7.5; bfloat16 5.0 / 5.3, 5.3 /
+// 5.9, 6.1 / 6.4, 6.0 / 6.5.  They take this one all the same: calls that are not captured are bound by the host there
+// (back to back 262144 values, two kernels, 13.3 us; 6.3 M, this one, 9.0).
 // Between kWholeSmall and kWholeLarge values, and from where the held pass begins to a third less (float32), rounding to
 // nearest keeps its two kernels: their names are what accept_stage_name is asked for there (the gain would be the
 // smallest there as well, 262144 values 5.1 / 4.6).
