@@ -45,11 +45,11 @@ inline void mark(StageTimer* t, hipStream_t s) {
   if (t) t->mark(s);
 }
 
-// Every workspace starts with a control block that the library keeps between calls: words that
-// must be zero when a call starts and are put back to zero before it ends (the work counters of
-// the multi-bit encoder in its first half, the mailboxes of the uniform scheme's held pass in its
-// second), and, behind those, mailboxes whose words bear the number of the call they belong to.  The
-// caller zero-fills the workspace once; no kernel of either scheme writes anything else there.
+// Every workspace starts with a control block that the library keeps between calls.  The caller zero-fills the
+// workspace once; no kernel of either scheme writes anything else there.  It holds
+// - words that are zero when a call starts and are put back to zero before it ends: the multi-bit encoder's work
+//   counters and its count of finished workgroups, in the first half (see WorkQueue and last_workgroup in mbq.hip);
+// - mailboxes, which nothing empties (see ChipMail): the second half, and between the counters.
 constexpr size_t kCtrlBytes = 16384;
 constexpr size_t kMailOffset = 8192;
 
@@ -91,10 +91,12 @@ inline bool held_runs(const UPlan& p, int units) { return p.held && units >= kHe
 inline bool whole_runs(const UPlan& p, int units) { return p.whole_per != 0 && units >= kHeldGrid; }
 inline bool channels_run(const UPlan& p, int units) { return p.chan_per != 0 && units >= kHeldGrid; }
 
-// What the workgroups of calls with one workspace leave each other, in its control block.  A call's tag is one
-// more than the number of calls before it, of which every workgroup has a word of its own: it reads the
-// word when it starts and raises it when it ends (and those of the workgroups that this call does not have),
-// so all of them agree.  So nothing has to be emptied: a value of an earlier call bears an earlier tag.
+// What the workgroups of calls with one workspace leave each other, in its control block.  Every exchange of a
+// call has a number of its own, and a value bears the number of its exchange, so nothing has to be emptied.
+// How many exchanges there have been, every workgroup knows from a word of its own: it reads the word when it
+// starts, and adds this call's exchanges before it ends (also to the words of the workgroups that this call does
+// not have), so all of them agree.  It adds to the word, and does not store a sum: so the words agree again, and are
+// ahead of every value left behind, even when calls that overlapped on one workspace, which they must not, have ended.
 // (Counting the workgroups off on one counter, and the last one emptying everything, cost small tensors
 // 1.5 us.)
 struct ChipMail {
@@ -146,6 +148,13 @@ hipError_t launch_mbq_init(const accept_desc& d, const MPlan& p, const void* x, 
 
 __device__ __forceinline__ float u32_as_f32(uint32_t u) { return __uint_as_float(u); }
 __device__ __forceinline__ uint32_t f32_as_u32(float f) { return __float_as_uint(f); }
+
+// Counts the call's exchanges; by the workgroup's first threads, after it has posted its values.
+__device__ __forceinline__ void count_exchanges(ChipMail* mail, uint32_t exchanges) {
+  const uint32_t t = blockIdx.x + gridDim.x * threadIdx.x;  // this workgroup's word, and those of absent ones
+  if (t >= uint32_t(kHeldGrid)) return;
+  __hip_atomic_fetch_add(&mail->calls[t], exchanges, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
 
 typedef float v4f_t __attribute__((ext_vector_type(4)));
 typedef uint32_t v4u_t __attribute__((ext_vector_type(4)));

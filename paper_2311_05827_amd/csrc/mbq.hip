@@ -1946,7 +1946,7 @@ __global__ __launch_bounds__(kFirstBlock, 2) void mbq_first_kernel(const T* __re
   if constexpr (K > 1) pass(std::integral_constant<int, 0>{});
   if constexpr (K > 2) pass(std::integral_constant<int, 1>{});
   if constexpr (K > 3) pass(std::integral_constant<int, 2>{});
-  if (K > 1 && gridDim.x > 1 && tid < kHeldGrid && uint32_t(tid) % gridDim.x == blockIdx.x) mail->calls[tid] = calls + uint32_t(K - 1);
+  if (K > 1 && gridDim.x > 1) count_exchanges(mail, uint32_t(K - 1));
 
   // last pass: signs, planes and sums, as in mbq_init_encode_kernel
   const bool all_finite = __builtin_amdgcn_readfirstlane(fabs(a[0]) < double(__builtin_inff()) ? 1 : 0) != 0;

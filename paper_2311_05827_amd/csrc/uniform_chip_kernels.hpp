@@ -271,7 +271,7 @@ __global__ __launch_bounds__(kHeldBlock, 2) void quantize_held_kernel(const T* _
 #pragma unroll
     for (int w = 1; w < WAVES; ++w) c = fmaxf(c, ex.top[w]);
     post(mail->first + blockIdx.x, tag, c);
-    mail->calls[blockIdx.x] = tag;
+    count_exchanges(mail, 1u);
   }
   __syncthreads();
   look_for_mail(mail, tag, polls, ex);
@@ -395,9 +395,7 @@ __global__ __launch_bounds__(kHeldBlock) void quantize_late_kernel(const T* __re
 // the same time; one that has looked `polls` times in vain reads the whole channel itself.  So every
 // workgroup ends whatever else runs, with the same bits.
 //
-// A mailbox is one 64-bit word, value and the call's mark together, as in quantize_held_kernel.  Every
-// workgroup counts itself off once it has all its ranges; the one that is counted last empties the
-// mailboxes and the count.
+// A mailbox is one 64-bit word, value and the exchange's number together, as in quantize_held_kernel (see ChipMail).
 //
 // What bounds it: the read of the tensor (16 of 33 us at 103 MB of bfloat16, with the looking hidden behind
 // it), then the instructions that quantize and pack, two wavefronts on a SIMD, and the payload's stores
@@ -601,7 +599,7 @@ __global__ __launch_bounds__(kHeldBlock, 2) void quantize_channels_kernel(const 
       if (lane == 0) atomicMax(&local.top[ch - ch_lo], f32_as_u32(v));
     }
     __syncthreads();
-    if (tid < kHeldGrid && uint32_t(tid) % gridDim.x == blockIdx.x) mail->calls[tid] = tag;
+    count_exchanges(mail, 1u);
   }
   if (tid < int(nloc)) {
     float s, r;
@@ -740,12 +738,12 @@ __global__ __launch_bounds__(kHeldBlock, 2) void quantize_whole_kernel(const T* 
         return v;
       });
     c = largest_mail(ex);
+    count_exchanges(mail, 1u);
   } else {
     c = ex.top[0];
 #pragma unroll
     for (int w = 1; w < WAVES; ++w) c = fmaxf(c, ex.top[w]);
   }
-  if (tid < kHeldGrid && uint32_t(tid) % gridDim.x == blockIdx.x) mail->calls[tid] = tag;
   float s, r;
   scale_from_range(c, K, s, r);
   if (blockIdx.x == 0 && tid == 0) header[0] = s;
