@@ -106,6 +106,10 @@ struct ChipMail {
   uint32_t calls[kHeldGrid];
 };
 static_assert(kMailOffset + sizeof(ChipMail) <= kCtrlBytes, "the control block holds them");
+// Three more boxes for a workgroup lie between the multi-bit encoder's counters, in the first half of the block: the
+// counters take the first 8 of 32 words of 64 bits, eight workgroups' boxes of a kind (0 .. 2) the next 8 each.
+constexpr int kBetweenStride = 32;
+static_assert(kHeldGrid / 8 * kBetweenStride * sizeof(uint64_t) <= kMailOffset, "in front of the mailboxes");
 
 // held_polls: how often a workgroup of the held pass looks for the others' maxima before it gives up
 // (kHeldPolls; fewer only where a test wants the case that it gives up).  64 looks take about 50 us.  Alone
@@ -149,11 +153,29 @@ hipError_t launch_mbq_init(const accept_desc& d, const MPlan& p, const void* x, 
 __device__ __forceinline__ float u32_as_f32(uint32_t u) { return __uint_as_float(u); }
 __device__ __forceinline__ uint32_t f32_as_u32(float f) { return __float_as_uint(f); }
 
-// Counts the call's exchanges; by the workgroup's first threads, after it has posted its values.
-__device__ __forceinline__ void count_exchanges(ChipMail* mail, uint32_t exchanges) {
+// Box of workgroup t between the counters.
+__device__ __forceinline__ uint64_t* between_box(ChipMail* mail, int kind, uint32_t t) {
+  uint64_t* const ctrl = reinterpret_cast<uint64_t*>(reinterpret_cast<char*>(mail) - kMailOffset);
+  return ctrl + t / 8 * kBetweenStride + 8 * (1 + kind) + t % 8;
+}
+// Counts the call's exchanges, `before` of which there were before; by the workgroup's first threads, after it has
+// posted its values.
+// The number wraps after 2^32 exchanges.  A box may not have been written for as long (a call with many workgroups,
+// then none for half a day), and would then bear the number of the exchange at hand.  So a call that goes past a
+// multiple of 2^30 gives every box that none of its own exchanges has written the number of the one before.
+constexpr int kRenumberShift = 30;
+__device__ __forceinline__ void count_exchanges(ChipMail* mail, uint32_t before, uint32_t exchanges) {
   const uint32_t t = blockIdx.x + gridDim.x * threadIdx.x;  // this workgroup's word, and those of absent ones
   if (t >= uint32_t(kHeldGrid)) return;
   __hip_atomic_fetch_add(&mail->calls[t], exchanges, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  if (((before ^ (before + exchanges)) >> kRenumberShift) == 0) return;
+  uint64_t* const boxes[6] = {mail->first + t,           mail->last + t,            mail->more + t,
+                              between_box(mail, 0, t), between_box(mail, 1, t), between_box(mail, 2, t)};
+  for (uint64_t* box : boxes) {
+    const uint64_t v = __hip_atomic_load(box, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (before + exchanges - uint32_t(v >> 32) >= exchanges)
+      __hip_atomic_store(box, uint64_t(before) << 32, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  }
 }
 
 typedef float v4f_t __attribute__((ext_vector_type(4)));

@@ -1783,25 +1783,21 @@ struct SumExchange {
 struct SumBox {
   uint64_t *lo, *hi;
 };
-// (Between two work counters of the control block there is room for 31 words; what the second half of the block does
-// not hold lies there: eight workgroups' words of a kind in a row.)
-__device__ __forceinline__ SumBox sum_box(uint32_t* ctrl, int set, int b) {
-  ChipMail* mail = reinterpret_cast<ChipMail*>(reinterpret_cast<char*>(ctrl) + kMailOffset);
-  uint64_t* between = reinterpret_cast<uint64_t*>(ctrl + (b / 8) * kCounterStride) + b % 8;
+__device__ __forceinline__ SumBox sum_box(ChipMail* mail, int set, int b) {
   if (set == 0) return {mail->first + b, mail->last + b};
-  if (set == 1) return {mail->more + b, between + 8};
-  return {between + 16, between + 24};
+  if (set == 1) return {mail->more + b, between_box(mail, 0, b)};
+  return {between_box(mail, 1, b), between_box(mail, 2, b)};
 }
-static_assert(kCounterStride * sizeof(uint32_t) == 32 * sizeof(uint64_t) && kMaxGroups * 8 == kHeldGrid && kDoneCounter < 16,
-              "three times eight words behind the first eight, which hold the counters");
+static_assert(kCounterStride * sizeof(uint32_t) == kBetweenStride * sizeof(uint64_t) && kMaxGroups * 8 == kHeldGrid && kDoneCounter < 16,
+              "the boxes between the counters are behind the first eight of 32 words, which hold the counters");
 __device__ __forceinline__ void post_sum(const SumBox& box, uint32_t tag, double v) {
   const uint64_t bits = uint64_t(__double_as_longlong(v)), t = uint64_t(tag) << 32;
   __hip_atomic_store(box.lo, t | uint32_t(bits), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   __hip_atomic_store(box.hi, t | uint32_t(bits >> 32), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 // Wavefronts 0 to 3 look for a lane's box each, at most `polls` times; `mine` is the lane's, `here` whether it is there.
-__device__ __forceinline__ void look_for_sums(uint32_t* ctrl, int set, uint32_t tag, int polls, double& mine, bool& here) {
-  const SumBox at = sum_box(ctrl, set, threadIdx.x);
+__device__ __forceinline__ void look_for_sums(ChipMail* mail, int set, uint32_t tag, int polls, double& mine, bool& here) {
+  const SumBox at = sum_box(mail, set, threadIdx.x);
   for (int i = 0; i < polls && __ballot(!here) != 0; ++i) {
     if (i > 0) __builtin_amdgcn_s_sleep(2);
     if (here) continue;
@@ -1890,11 +1886,11 @@ __global__ __launch_bounds__(kFirstBlock, 2) void mbq_first_kernel(const T* __re
     double total = block_total(acc);
     if (gridDim.x > 1) {
       const uint32_t tag = calls + 1u + uint32_t(j);
-      if (tid == 0) post_sum(sum_box(ctrl, j, blockIdx.x), tag, total);
+      if (tid == 0) post_sum(sum_box(mail, j, blockIdx.x), tag, total);
       // threads 0 to 255 hold a workgroup's sum each, once it is there
       double one = 0.0;
       bool here = uint32_t(tid) >= gridDim.x;
-      if (wave < kHeldGrid / kWave) look_for_sums(ctrl, j, tag, polls, one, here);
+      if (wave < kHeldGrid / kWave) look_for_sums(mail, j, tag, polls, one, here);
       for (;;) {  // a workgroup less is missing after every turn, whatever becomes of its mailbox
         if (wave < kHeldGrid / kWave) {
           const uint64_t missing = __ballot(!here);
@@ -1927,9 +1923,9 @@ __global__ __launch_bounds__(kFirstBlock, 2) void mbq_first_kernel(const T* __re
         load(p, rows);
         add_item(J, rows, p.rows, other);
         const double t = block_total(other);  // (its barriers: ex has been read by all)
-        if (tid == 0) post_sum(sum_box(ctrl, j, b), tag, t);
+        if (tid == 0) post_sum(sum_box(mail, j, b), tag, t);
         if (tid == b) { one = t; here = true; }
-        if (wave < kHeldGrid / kWave) look_for_sums(ctrl, j, tag, 1, one, here);
+        if (wave < kHeldGrid / kWave) look_for_sums(mail, j, tag, 1, one, here);
       }
       if (wave < kHeldGrid / kWave) {
         const double t = wave_sum(one);
@@ -1946,7 +1942,7 @@ __global__ __launch_bounds__(kFirstBlock, 2) void mbq_first_kernel(const T* __re
   if constexpr (K > 1) pass(std::integral_constant<int, 0>{});
   if constexpr (K > 2) pass(std::integral_constant<int, 1>{});
   if constexpr (K > 3) pass(std::integral_constant<int, 2>{});
-  if (K > 1 && gridDim.x > 1) count_exchanges(mail, uint32_t(K - 1));
+  if (K > 1 && gridDim.x > 1) count_exchanges(mail, calls, uint32_t(K - 1));
 
   // last pass: signs, planes and sums, as in mbq_init_encode_kernel
   const bool all_finite = __builtin_amdgcn_readfirstlane(fabs(a[0]) < double(__builtin_inff()) ? 1 : 0) != 0;

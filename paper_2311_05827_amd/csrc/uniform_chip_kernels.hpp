@@ -271,7 +271,7 @@ __global__ __launch_bounds__(kHeldBlock, 2) void quantize_held_kernel(const T* _
 #pragma unroll
     for (int w = 1; w < WAVES; ++w) c = fmaxf(c, ex.top[w]);
     post(mail->first + blockIdx.x, tag, c);
-    count_exchanges(mail, 1u);
+    count_exchanges(mail, tag - 1u, 1u);
   }
   __syncthreads();
   look_for_mail(mail, tag, polls, ex);
@@ -599,7 +599,7 @@ __global__ __launch_bounds__(kHeldBlock, 2) void quantize_channels_kernel(const 
       if (lane == 0) atomicMax(&local.top[ch - ch_lo], f32_as_u32(v));
     }
     __syncthreads();
-    count_exchanges(mail, 1u);
+    count_exchanges(mail, tag - 1u, 1u);
   }
   if (tid < int(nloc)) {
     float s, r;
@@ -738,7 +738,7 @@ __global__ __launch_bounds__(kHeldBlock, 2) void quantize_whole_kernel(const T* 
         return v;
       });
     c = largest_mail(ex);
-    count_exchanges(mail, 1u);
+    count_exchanges(mail, tag - 1u, 1u);
   } else {
     c = ex.top[0];
 #pragma unroll

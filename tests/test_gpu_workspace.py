@@ -90,3 +90,30 @@ def test_calls_that_overlapped_spoil_no_later_call(A):
         c.call(ws)
         torch.cuda.synchronize()
         c.check()
+
+
+def test_numbers_of_exchanges_wrap(A):
+    """The number has 32 bits.  Boxes of workgroups that only a call before the wrap had, or none at all (0), are not
+    taken for the wrapped call's; on the way there, at multiples of 2^30, every box is renumbered."""
+    torch = torch_mod()
+    small, large = Uniform(A, 2 * 512 * 32, 8, 11), Uniform(A, ROUND, 8, 12)     # 2 and 256 workgroups
+    channels, first = Uniform(A, 64 * 6 * 3136, 6, 13, channels=6, n=64), First(A, 64, 4096, 4, 14)
+    ws = A.alloc_outputs(first.d, "cuda")[2]
+    boxes = [ws[FIRST:WORDS].view(torch.int64)]
+    boxes += [ws[64:FIRST].view(torch.int64).as_strided((32, 24), (32, 1))]       # between the counters
+
+    def number(t):
+        return (t >> 32) & 0xFFFFFFFF
+
+    for quarter in range(1, 5):  # the first call of a turn goes past the multiple; the one that has number 0 is a large one
+        words(ws).fill_((quarter << 30) - 1 - ((1 << 32) if quarter > 2 else 0))
+        for c in (large, channels, first, small) if quarter == 4 else (small, first) if quarter == 2 else (small,):
+            c.header.zero_()
+            c.payload.zero_()
+            c.call(ws)
+            torch.cuda.synchronize()
+            c.check(quarter)
+        now = int(words(ws)[0]) & 0xFFFFFFFF
+        assert now < 8 if quarter == 4 else now >= quarter << 30
+        for b in boxes:
+            assert int(((now - number(b)) & 0xFFFFFFFF).max()) <= 8, quarter
