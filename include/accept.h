@@ -143,7 +143,8 @@ accept_status accept_workspace_size(const accept_desc* desc, size_t* bytes);
  * needs (its first 16 KiB hold counters and mailboxes that the library keeps from call to call;
  * the rest is scratch whose contents do not matter), so one workspace serves any number of calls and
  * descriptors of both schemes, one call at a time: calls that share a workspace must not
- * overlap.
+ * overlap.  (Headers and payloads of calls that do are unspecified; calls after all of them have ended
+ * are not affected.)
  * hip_stream: a hipStream_t (null = the default stream).
  */
 accept_status accept_compress(const accept_desc* desc, const void* x_dev, const float* alpha_prev_dev,

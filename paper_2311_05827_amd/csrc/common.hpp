@@ -47,8 +47,8 @@ inline void mark(StageTimer* t, hipStream_t s) {
 
 // Every workspace starts with a control block that the library keeps between calls.  The caller zero-fills the
 // workspace once; no kernel of either scheme writes anything else there.  It holds
-// - words that are zero when a call starts and are put back to zero before it ends: the multi-bit encoder's work
-//   counters and its count of finished workgroups, in the first half (see WorkQueue and last_workgroup in mbq.hip);
+// - the multi-bit encoder's work counters, which are zero when a call starts and are put back to zero before it ends,
+//   and its count of finished workgroups, in the first half (see WorkQueue and last_workgroup in mbq.hip);
 // - mailboxes, which nothing empties (see ChipMail): the second half, and between the counters.
 constexpr size_t kCtrlBytes = 16384;
 constexpr size_t kMailOffset = 8192;

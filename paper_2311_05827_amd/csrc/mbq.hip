@@ -757,7 +757,7 @@ __device__ __forceinline__ void encode_column(const Tables& tb, const T* __restr
 // groups: at any time the grid reads one contiguous stretch of each of eight rows (the pattern
 // memory likes best), the groups advancing through the tensor side by side.
 struct WorkQueue {
-  uint32_t* counter;  // the group's counter: zero when the kernel starts, put back by the finalize kernel
+  uint32_t* counter;  // the group's counter: zero when the kernel starts, put back by the finalize kernel or the last workgroup
   uint32_t first;     // 64 * group
   uint32_t sweep;     // wave-items all groups take per sweep
   uint32_t count;     // queue positions 0 .. count-1 exist
@@ -1118,17 +1118,23 @@ __global__ __launch_bounds__(finalize_block(K)) void mbq_finalize_kernel(MbqCall
 // A launch less is 3.6 us of host time; on the device, encode and finalize kernels / this (us, replayed graphs, k = 2 and
 // 4): 16 x 2048 float32 7.1 / 6.8, 9.9 / 10.0; 64 x 16384 (64 workgroups) 7.7 / 7.4, 10.3 / 10.5; 64 x 50000 (196: the
 // counter, one address, takes 12 ns each) 8.8 / 9.7, 11.2 / 12.6.
+// The workgroups of a call add 64 to the count together, whatever their number is, and nothing puts it back: so it is
+// a multiple of 64 whenever no call is under way, also after calls that overlapped on one workspace, which they must not
+// (the last of all to end then finds it so, and clears the work counters behind all of them, whichever call it is of).
 constexpr int kFinishGridMax = 64;
 __device__ __forceinline__ bool last_workgroup(uint32_t* counters) {
   __shared__ int last;
   __builtin_amdgcn_s_waitcnt(0x0F70);  // this thread's part of the record is written
   __syncthreads();
   if (threadIdx.x == 0) {
-    const uint32_t before = __hip_atomic_fetch_add(counters + kDoneCounter, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    last = before + 1u == gridDim.x ? 1 : 0;
+    const uint32_t share = (uint32_t(kFinishGridMax) - 1u - blockIdx.x) / gridDim.x + 1u;  // of the numbers 0 .. 63, those that are blockIdx.x modulo gridDim.x
+    const uint32_t before = __hip_atomic_fetch_add(counters + kDoneCounter, share, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    last = (before + share) % uint32_t(kFinishGridMax) == 0u ? 1 : 0;
   }
   __syncthreads();
-  return __builtin_amdgcn_readfirstlane(last) != 0;
+  if (__builtin_amdgcn_readfirstlane(last) == 0) return false;
+  if (threadIdx.x < uint32_t(kMaxGroups)) counters[threadIdx.x * kCounterStride] = 0u;  // the work counters, for the next call
+  return true;
 }
 template <int K>
 __device__ __forceinline__ void finish_in_last_workgroup(const MbqCall& call, const float (&alpha_prev)[K], WaveTotals& buf) {
@@ -1141,8 +1147,6 @@ __device__ __forceinline__ void finish_in_last_workgroup(const MbqCall& call, co
     const double a = sum_records<true>(call.records + int64_t(s) * nrec, nrec, lane);
     if (lane == 0) tot[s] = a;
   }
-  if (tid < kMaxGroups) call.counters[tid * kCounterStride] = 0u;
-  if (tid == 0) call.counters[kDoneCounter] = 0u;
   __syncthreads();
   if (tid == 0) solve_and_write_header<K>(tot, alpha_prev, call.n_elems, call.beta, call.header);
 }
@@ -2032,7 +2036,6 @@ __global__ __launch_bounds__(kFirstBlock, 2) void mbq_first_kernel(const T* __re
     const double t = sum_records<true>(records + int64_t(s) * nrec, nrec, lane);
     if (lane == 0) tot[s] = t;
   }
-  if (tid == 0) ctrl[kDoneCounter] = 0u;
   __syncthreads();
   if (tid != 0) return;
   const float last_alpha = float(tot[0] / n_elems);

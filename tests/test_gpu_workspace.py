@@ -92,6 +92,38 @@ def test_calls_that_overlapped_spoil_no_later_call(A):
         c.check()
 
 
+def test_solving_calls_that_overlapped_spoil_no_later_call(A):
+    """The same for encoders and first batches whose last workgroup solves, of 1 to 64 workgroups."""
+    torch = torch_mod()
+    on = [[First(A, n, m, 3, 20 + n) for n, m in ((8, 2000), (64, 16384), (40, 4096))] for _ in range(2)]
+    alpha = torch.tensor([1.0, 0.5, 0.25], device="cuda")
+    ws = A.alloc_outputs(on[0][0].d, "cuda")[2]
+    later = []
+    for c in on[0]:
+        header, payload = A.accept_compress(c.d, c.x, alpha_prev=alpha)
+        torch.cuda.synchronize()
+        later.append((dev_bytes(header), dev_bytes(payload)))
+    streams = [torch.cuda.Stream() for _ in on]
+    for _ in range(30):
+        for s, calls in zip(streams, on):
+            with torch.cuda.stream(s):
+                for c in calls:
+                    c.call(ws)
+                    A.accept_compress(c.d, c.x, alpha_prev=alpha, header=c.header, payload=c.payload, workspace=ws)
+    torch.cuda.synchronize()
+    assert ws[:FIRST].view(torch.int32).view(32, 64)[:, 0].tolist() == [0] * 32   # work counters
+    assert int(ws[8:12].view(torch.int32)[0]) % 64 == 0
+    for c, want in zip(on[0], later):
+        c.header.zero_()
+        c.payload.zero_()
+        c.call(ws)
+        torch.cuda.synchronize()
+        c.check()
+        header, payload = A.accept_compress(c.d, c.x, alpha_prev=alpha, workspace=ws)
+        torch.cuda.synchronize()
+        assert (dev_bytes(header), dev_bytes(payload)) == want
+
+
 def test_numbers_of_exchanges_wrap(A):
     """The number has 32 bits.  Boxes of workgroups that only a call before the wrap had, or none at all (0), are not
     taken for the wrapped call's; on the way there, at multiples of 2^30, every box is renumbered."""
