@@ -9,12 +9,13 @@ namespace accept {
 
 namespace {
 
-// One value of every workgroup of a call, exchanged through the mailboxes: the largest of all.  The wait is
-// bounded: nothing says that all workgroups run at the same time (another kernel may hold some compute
-// units).  Where a workgroup has looked `polls` times in vain, it finds the values that are missing itself, one
-// workgroup's part after the other, and posts them: those that wait share
+// One value of every workgroup of a list (all of a call's, or those that share a channel), exchanged through
+// mailboxes: the largest of all.  The wait is bounded: nothing says that all workgroups run at the same time (another
+// kernel may hold some compute units).  Where a workgroup has looked `polls` times in vain, it finds the values that
+// are missing itself, one workgroup's part after the other, and posts them: those that wait share
 // the work of those that have not started, which later post the same values.  So every workgroup ends whatever else
 // runs, and the result does not depend on it.
+// The list has at most 256 members, 0 .. n-1; box(i) is the mailbox of member i.
 struct Exchange {
   float top[kHeldBlock / kWave];  // of the values seen so far, by wavefront
   float part[kHeldBlock / kWave];
@@ -23,27 +24,30 @@ struct Exchange {
 __device__ __forceinline__ void post(uint64_t* box, uint32_t tag, float v) {
   __hip_atomic_store(box, (uint64_t(tag) << 32) | f32_as_u32(v), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
-// Wavefronts 0 to 3 look for a box per lane, at most `polls` times; on return (in front of a barrier) ex holds
-// what is missing and the wavefronts' maxima of what is there.
-__device__ __forceinline__ void look_for_mail(const ChipMail* mail, uint32_t tag, int polls, Exchange& ex) {
-  const int tid = threadIdx.x;
-  if (tid >= kHeldGrid) return;
-  const bool box = uint32_t(tid) < gridDim.x;
-  uint64_t missing = __ballot(box);
+__device__ __forceinline__ uint64_t look(const uint64_t* box) {
+  return __hip_atomic_load(box, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+// Four wavefronts look for member `i` each lane (0 .. 255), at most `polls` times; on return (in front of a barrier) ex
+// holds what is missing and the wavefronts' maxima of what is there.  Returns what this wavefront misses.
+template <typename Box>
+__device__ __forceinline__ uint64_t look_for_mail(int i, int n, uint32_t tag, int polls, Exchange& ex, Box box) {
+  const bool member = i < n;
+  uint64_t missing = __ballot(member);
   uint64_t v = 0;
-  for (int i = 0; i < polls; ++i) {
-    if (box) v = __hip_atomic_load(mail->first + tid, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    missing = __ballot(box && uint32_t(v >> 32) != tag);
+  for (int p = 0; p < polls; ++p) {
+    if (member) v = look(box(i));
+    missing = __ballot(member && uint32_t(v >> 32) != tag);
     if (missing == 0) break;
     __builtin_amdgcn_s_sleep(4);
   }
-  const float t = wave_max(u32_as_f32(box && uint32_t(v >> 32) == tag ? uint32_t(v) : 0u));
-  if ((tid & (kWave - 1)) == 0) {
-    ex.top[tid / kWave] = t;
-    ex.missing[tid / kWave] = missing;
+  const float t = wave_max(u32_as_f32(member && uint32_t(v >> 32) == tag ? uint32_t(v) : 0u));
+  if ((i & (kWave - 1)) == 0) {
+    ex.top[i / kWave] = t;
+    ex.missing[i / kWave] = missing;
   }
+  return missing;
 }
-// After look_for_mail and a barrier: how many workgroups are missing, and one of them, another for neighbouring
+// After look_for_mail and a barrier: how many members are missing, and one of them, another for neighbouring
 // workgroups (both in scalar registers).
 __device__ __forceinline__ int missing_count(const Exchange& ex) {
   int count = 0;
@@ -73,10 +77,10 @@ __device__ __forceinline__ float largest_mail(const Exchange& ex) {
   for (int w = 1; w < kHeldGrid / kWave; ++w) c = fmaxf(c, ex.top[w]);
   return c;
 }
-// Finds and posts what is missing until nothing is; part(w): a thread's share of the largest value of workgroup w.  Every
-// turn takes at least one workgroup off the list, whatever becomes of its mailbox.
-template <typename Part>
-__device__ __forceinline__ void post_missing(ChipMail* mail, uint32_t tag, Exchange& ex, Part part) {
+// Finds and posts what is missing until nothing is; part(i): a thread's share of member i's largest value.  Every
+// turn takes at least one member off the list, whatever becomes of its mailbox.
+template <typename Box, typename Part>
+__device__ __forceinline__ void post_missing(uint32_t tag, Exchange& ex, Box box, Part part) {
   const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid / kWave;
   for (int count = missing_count(ex); count != 0; count = missing_count(ex)) {
     const int w = missing_one(ex, count);
@@ -86,12 +90,12 @@ __device__ __forceinline__ void post_missing(ChipMail* mail, uint32_t tag, Excha
     if (wave < kHeldGrid / kWave) {
       float t = ex.part[0];
       for (int i = 1; i < kHeldBlock / kWave; ++i) t = fmaxf(t, ex.part[i]);
-      if (tid == 0) post(mail->first + w, tag, t);
+      if (tid == 0) post(box(w), tag, t);
       const uint64_t missing = ex.missing[wave];
-      const bool look = (missing >> lane) & 1u;
-      const uint64_t box = look ? __hip_atomic_load(mail->first + tid, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0;
-      const bool there = look && uint32_t(box >> 32) == tag;
-      const float seen = wave_max(tid == w ? t : there ? u32_as_f32(uint32_t(box)) : 0.0f);
+      const bool wanted = (missing >> lane) & 1u;
+      const uint64_t found = wanted ? look(box(tid)) : 0;
+      const bool there = wanted && uint32_t(found >> 32) == tag;
+      const float seen = wave_max(tid == w ? t : there ? u32_as_f32(uint32_t(found)) : 0.0f);
       const uint64_t left = missing & ~__ballot(there || tid == w);
       if (lane == 0) {
         ex.top[wave] = fmaxf(ex.top[wave], seen);
@@ -274,7 +278,8 @@ __global__ __launch_bounds__(kHeldBlock, 2) void quantize_held_kernel(const T* _
     count_exchanges(mail, tag - 1u, 1u);
   }
   __syncthreads();
-  look_for_mail(mail, tag, polls, ex);
+  auto box = [&](int w) { return mail->first + w; };
+  if (wave < kHeldGrid / kWave) look_for_mail(tid, kHeldGrid, tag, polls, ex, box);
   __syncthreads();
 
   float r = 0.0f;
@@ -296,7 +301,7 @@ __global__ __launch_bounds__(kHeldBlock, 2) void quantize_held_kernel(const T* _
       if (tid == 0) mail->last[blockIdx.x] = (uint64_t(tag) << 32) | 1u;
       return;
     }
-    post_missing(mail, tag, ex, [&](int w) {
+    post_missing(tag, ex, box, [&](int w) {
       float v = 0.0f;
       for (int64_t unit = w; unit < units; unit += kHeldGrid) {
         const T* xu = x + unit * kUnitElems;
@@ -391,9 +396,8 @@ __global__ __launch_bounds__(kHeldBlock) void quantize_late_kernel(const T* __re
 // of payload each; segments are whole groups) are numbered channel after channel, row after row inside a
 // channel, and workgroup b has the groups b*per .. (b+1)*per - 1 of that order: most of its channels are
 // its own altogether, and at most two, its first and its last, it shares with neighbours.  For these it
-// leaves its maximum in a mailbox and looks for those of the others.  Workgroups are not sure to run at
-// the same time; one that has looked `polls` times in vain reads the whole channel itself.  So every
-// workgroup ends whatever else runs, with the same bits.
+// leaves its maximum in a mailbox and looks for those of the others, as far as they have a part of the channel (see
+// Exchange).
 //
 // A mailbox is one 64-bit word, value and the exchange's number together, as in quantize_held_kernel (see ChipMail).
 //
@@ -402,10 +406,14 @@ __global__ __launch_bounds__(kHeldBlock) void quantize_late_kernel(const T* __re
 // (38 MB there).  The places of a thread's vectors are stepped, not divided out, and only the loads and
 // stores need them: which channel a unit belongs to is known from scalars (per element, as at first, the
 // kernel took 42 us).  Streaming stores of the payload make a call alone 3 us faster and a decoder that
-// reads it next 8 us slower.  Beside other work on another stream, two or three kernels / this one (us):
-// matrix products 220 / 114 (100 x 8 x 12544 float32), small kernels 29.0 / 20.6 (64 x 100 x 3136 float32); 512 MB
-// copies without a pause 42 / 23 there, but 60 / 80 to 105 for the large one, whose workgroups need a compute
-// unit each.
+// reads it next 8 us slower.
+//
+// Beside other work on another stream, two or three kernels / this one (us): matrix products 224 / 121 (4 x 4 x 1605632
+// float32), small kernels 40.5 / 21.9, 35.5 / 21.5 (64 x 128 x 3136); 512 MB copies without a pause 85 / 74 to 89, 71 / 72 to 80,
+// and 45 to 92 / 61 to 68 (1 x 2 x 12845056).  There workgroups start late, and how others make up for them counts: as
+// long as each that had waited in vain read the whole channel itself, 370 to 410 and 230 to 650; and where all look in
+// vain, 25.7 M values in two channels took 2756 us, now 43 (24 if they see each other).
+//
 // Place of a group of 32 elements: group inside its segment, batch row, and the group's number in the tensor.
 struct GroupPos {
   uint32_t pos, row, at;
@@ -449,12 +457,19 @@ __global__ __launch_bounds__(kHeldBlock, 2) void quantize_channels_kernel(const 
   static_assert(LOADS * (kHeldBlock / GV) == kHeldBlock && kUnitElems == 32 * kHeldBlock, "a unit is a group per thread");
   static_assert(LDS_UNITS <= SLOTS, "units kept in local memory pass through the first slots");
   constexpr int QPV = VEC / 4;
+  // What finds others' missing parts needs registers, of which the largest forms have none left: vectors that are kept
+  // make room then.
+  constexpr int ASIDE = SLOTS * LOADS < 44 ? 0 : sizeof(T) == 4 ? 7 : 3;
+  constexpr int ASK = ASIDE > 0 ? 2 : 4;  // loads in flight there
+  static_assert(ASIDE <= LOADS, "they are of one slot");
   struct Local {
     uint4 kept[LDS_UNITS > 0 ? LDS_UNITS : 1][LDS_UNITS > 0 ? LOADS : 1][LDS_UNITS > 0 ? kHeldBlock : 1];
     uint32_t pieces[2][kUnitElems / 4];
     uint32_t top[kChanMaxLocal];  // largest magnitude of the workgroup's channels, as bits
     float r[kChanMaxLocal];
-    int up[2];
+    Exchange ex[2];  // of the first channel and of the last
+    int late;        // something was not seen in time
+    uint4 aside[ASIDE > 0 ? ASIDE : 1][ASIDE > 0 ? kHeldBlock : 1];
   };
   static_assert(sizeof(Local) <= 160 * 1024, "local memory of a compute unit");
   __shared__ __attribute__((aligned(16))) Local local;
@@ -464,7 +479,6 @@ __global__ __launch_bounds__(kHeldBlock, 2) void quantize_channels_kernel(const 
   const uint32_t q0 = blockIdx.x * g.per;  // below total (host)
   const uint32_t count = g.total - q0 < g.per ? g.total - q0 : g.per;
   const uint32_t units = (count + kHeldBlock - 1) / kHeldBlock;
-  const uint32_t tag = mail->calls[blockIdx.x] + 1u;
   const uint32_t mine = uint32_t(tid) / GV;  // the thread's first vector is in this group of the workgroup's
   uint4 kept[SLOTS][LOADS];
   // The loads of the units in ordinal order, one after the other; behind the workgroup's last group its
@@ -484,12 +498,13 @@ __global__ __launch_bounds__(kHeldBlock, 2) void quantize_channels_kernel(const 
   };
 #pragma unroll
   for (int j = 0; j < SLOTS; ++j) ask(j, kept[j]);
+  const uint32_t tag = mail->calls[blockIdx.x] + 1u;
   const uint32_t per_channel = g.rows * g.seg_groups;
   const uint32_t ch_lo = q0 / per_channel;
   const uint32_t ch_hi = (q0 + count - 1) / per_channel;
   const uint32_t nloc = ch_hi - ch_lo + 1;
   if (tid < kChanMaxLocal) local.top[tid] = 0u;
-  if (tid < 2) local.up[tid] = 0;
+  if (tid == 0) local.late = 0;
   __syncthreads();
   // The workgroup's channels, the first one's index 0; channel i ends before group end_of(i).  Units inside
   // one channel, which are most, know it from scalars; the others split at the ends inside them.
@@ -549,56 +564,76 @@ __global__ __launch_bounds__(kHeldBlock, 2) void quantize_channels_kernel(const 
   const bool starts_inside = q0 % per_channel != 0;           // the first channel began before
   const bool ends_inside = (q0 + count) % per_channel != 0;   // the last one goes on behind
   if (g.shared != 0) {
-    uint64_t* const mail_first = mail->first;
-    uint64_t* const mail_last = mail->last;
+    uint32_t thread = threadIdx.x;
+    asm volatile("" : "+v"(thread));
     const bool one = ch_lo == ch_hi;
-    const bool watch_first = starts_inside || (one && ends_inside), watch_last = !one && ends_inside;
-    if (tid == 0 && watch_first) post(mail_first + blockIdx.x, tag, u32_as_f32(local.top[0]));
-    if (tid == 0 && watch_last) post(mail_last + blockIdx.x, tag, u32_as_f32(local.top[nloc - 1]));
+    // what the workgroup shares: e = 0 its first channel, 1 its last one
+    auto watched = [&](int e) { return e == 0 ? starts_inside || (one && ends_inside) : !one && ends_inside; };
+    // the workgroups that have a part of channel ch, the list's members; it is the first channel of all but the first
+    auto first_of = [&](uint32_t ch) { return ch * per_channel / g.per; };
+    auto members = [&](uint32_t ch) { return int((ch * per_channel + per_channel - 1) / g.per - first_of(ch) + 1); };
+    auto boxes = [&](uint32_t ch) {
+      const uint32_t from = first_of(ch);
+      const bool its_first = from * g.per == ch * per_channel;
+      return [=](int i) { return (i > 0 || its_first ? mail->first : mail->last) + from + i; };
+    };
+    if (thread == 0 && watched(0)) post(mail->first + blockIdx.x, tag, u32_as_f32(local.top[0]));
+    if (thread == 0 && watched(1)) post(mail->last + blockIdx.x, tag, u32_as_f32(local.top[nloc - 1]));
     __syncthreads();
-    // wavefront 0 watches the first channel's other workgroups, wavefront 1 the last one's
-    if ((wave == 0 && watch_first) || (wave == 1 && watch_last)) {
-      const uint32_t ch = wave == 0 ? ch_lo : ch_hi;
-      const uint32_t from_wg = ch * per_channel / g.per, to_wg = (ch * per_channel + per_channel - 1) / g.per;
-      const bool from_first = from_wg * g.per == ch * per_channel;  // it is the first channel of workgroup from_wg
-      uint32_t top = 0;
-      bool all = false;
-      for (int i = 0; i < polls; ++i) {
-        bool seen = true;
-        top = 0;  // (a look may have met values of earlier calls)
-        for (uint32_t w = from_wg + uint32_t(lane); w <= to_wg; w += kWave) {
-          const uint64_t* box = (w != from_wg || from_first ? mail_first : mail_last) + w;
-          const uint64_t v = __hip_atomic_load(box, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-          seen = seen && uint32_t(v >> 32) == tag;
-          top = max(top, uint32_t(v));
-        }
-        all = __ballot(!seen) == 0;
-        if (all) break;
-        __builtin_amdgcn_s_sleep(4);
-      }
-      const float t = wave_max(u32_as_f32(top));
-      if (lane == 0) {
-        if (all) local.top[ch - ch_lo] = f32_as_u32(t);
-        else local.up[wave] = 1;
+    // four wavefronts look for the first channel's other workgroups, four for the last one's
+    const int half = wave / (kHeldGrid / kWave);
+    if (watched(half)) {
+      const uint32_t ch = half == 0 ? ch_lo : ch_hi;
+      const int i = int(thread % uint32_t(kHeldGrid));
+      const uint64_t missing = look_for_mail(i, members(ch), tag, polls, local.ex[half], boxes(ch));
+      if (i % kWave == 0) {
+        atomicMax(&local.top[ch - ch_lo], f32_as_u32(local.ex[half].top[i / kWave]));
+        if (missing != 0) local.late = 1;
       }
     }
     __syncthreads();
-    for (int e = 0; e < 2; ++e) {
-      if (local.up[e] == 0) continue;  // the same in all threads
-      const uint32_t ch = e == 0 ? ch_lo : ch_hi;
-      float v = 0.0f;
-      const uint32_t seg_vecs = g.seg_groups * GV, vecs = g.rows * seg_vecs;
-      for (uint32_t i = tid; i < vecs; i += kHeldBlock) {
-        const uint32_t row = i / seg_vecs;
-        float f[VEC];
-        load_vec(x + (size_t(row) * g.m_groups + size_t(ch) * g.seg_groups) * 32 + size_t(i - row * seg_vecs) * VEC, f);
+    const bool late = __builtin_amdgcn_readfirstlane(local.late) != 0;
+    if (ASIDE > 0 && late) {
 #pragma unroll
-        for (int q = 0; q < VEC; ++q) v = fmaxf(v, fabsf(f[q]));
-      }
-      v = wave_max(v);
-      if (lane == 0) atomicMax(&local.top[ch - ch_lo], f32_as_u32(v));
+      for (int u = 0; u < ASIDE; ++u) local.aside[u][thread] = kept[SLOTS - 1][u];
     }
-    __syncthreads();
+#pragma nounroll
+    for (int e = 0; e < 2 && late; ++e) {
+      if (!watched(e)) continue;  // the same in all threads
+      const uint32_t ch = e == 0 ? ch_lo : ch_hi;
+      const uint32_t from = first_of(ch);
+      post_missing(tag, local.ex[e], boxes(ch), [&](int i) {  // the channel's groups that workgroup from + i has
+        const uint32_t begin = max(ch * per_channel, (from + uint32_t(i)) * g.per);
+        const uint32_t behind = min((ch + 1) * per_channel, (from + uint32_t(i) + 1) * g.per);
+        const uint32_t at0 = group_pos(g, begin).at;
+        GroupPos p = group_pos(g, begin + thread / uint32_t(GV));
+        float v = 0.0f;
+#pragma nounroll
+        for (uint32_t q = begin; q < behind; q += ASK * (kHeldBlock / GV)) {
+          uint4 raw[ASK];
+#pragma unroll
+          for (int u = 0; u < ASK; ++u) {
+            const uint32_t at = q + uint32_t(u * (kHeldBlock / GV)) + thread / uint32_t(GV) < behind ? p.at : at0;
+            raw[u] = load16_stream(reinterpret_cast<const char*>(x) + (at * uint32_t(GV) + thread % uint32_t(GV)) * 16u);
+            group_advance(g, p, g.load_step);
+          }
+#pragma unroll
+          for (int u = 0; u < ASK; ++u) {
+            float f[VEC];
+            widen(raw[u], f);
+#pragma unroll
+            for (int k = 0; k < VEC; ++k) v = fmaxf(v, fabsf(f[k]));
+          }
+        }
+        return v;
+      });
+      if (thread == 0) local.top[ch - ch_lo] = f32_as_u32(largest_mail(local.ex[e]));
+    }
+    if (ASIDE > 0 && late) {
+#pragma unroll
+      for (int u = 0; u < ASIDE; ++u) kept[SLOTS - 1][u] = local.aside[u][thread];
+    }
+    if (late) __syncthreads();
     count_exchanges(mail, tag - 1u, 1u);
   }
   if (tid < int(nloc)) {
@@ -723,10 +758,11 @@ __global__ __launch_bounds__(kHeldBlock, 2) void quantize_whole_kernel(const T* 
       post(mail->first + blockIdx.x, tag, c);
     }
     __syncthreads();
-    look_for_mail(mail, tag, polls, ex);
+    auto box = [&](int w) { return mail->first + w; };
+    if (wave < kHeldGrid / kWave) look_for_mail(tid, int(gridDim.x), tag, polls, ex, box);
     __syncthreads();
     if (missing_count(ex) != 0)
-      post_missing(mail, tag, ex, [&](int w) {
+      post_missing(tag, ex, box, [&](int w) {
         float v = w + 1 == int(gridDim.x) && tid < int(N - int64_t(total) * 32) ? fabsf(load_one(xt + tid)) : 0.0f;
         const T* const xo = x + size_t(w) * per * 32;
         for (uint32_t i = tid; i < groups_of(w) * GV; i += kHeldBlock) {

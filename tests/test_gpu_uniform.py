@@ -506,6 +506,42 @@ def test_channels_on_the_chip(A, n, C, seg, k, bf16):
         assert first_mismatch(dev_bytes(payload), op.tobytes()) is None, polls
 
 
+@pytest.mark.parametrize("n,C,seg,k,bf16", [
+    (1, 2, 12845056, 8, False),    # the largest form, both channels in 128 workgroups
+    (2, 3, 4300032, 5, True),      # a workgroup in two channels
+    (16, 4, 100352, 4, False),
+    (64, 16, 25088, 6, False),
+])
+def test_few_large_channels_that_are_not_seen_in_time(A, n, C, seg, k, bf16):
+    """Where workgroups look in vain, they share out what is missing of a channel: the bytes are the same, and it
+    costs a few exchanges, not the whole channel once per workgroup (115 times as long, two channels of 51 MB)."""
+    torch = torch_mod()
+    print("case", n, C, seg, k, bf16, flush=True)
+    x = si.make_shape("grad", (n, C, seg), 320 + k)
+    x[n - 1, C - 1, seg - 1] = 0.5
+    xd, bits = to_dev(x, bf16)
+    d = A.make_desc(A.UNIFORM, k, n, C * seg, channels=C, in_dtype=A.BF16 if bf16 else A.F32)
+    assert A.accept_stage_name(d, 0, 0) == "quantize_channels"
+    oh, op = orc.uniform_compress(bits if bf16 else x, k, n, C * seg, C, bf16)
+    header, payload, ws = A.alloc_outputs(d, "cuda")
+    took = {}
+    for polls in (64, 0, 1, 2, 64, 0):
+        times = []
+        for _ in range(5):
+            payload.zero_()
+            begin, end = (torch.cuda.Event(enable_timing=True) for _ in range(2))
+            begin.record()
+            A.accept_compress_polls(d, xd, header, payload, ws, polls)
+            end.record()
+            torch.cuda.synchronize()
+            times.append(begin.elapsed_time(end))
+        took[polls] = sorted(times)[2]
+        assert dev_bytes(header) == oh, polls
+        assert first_mismatch(dev_bytes(payload), op.tobytes()) is None, polls
+    print(took, flush=True)
+    assert took[0] < 8 * took[64], took
+
+
 def test_channels_on_the_chip_on_two_streams_and_in_a_graph(A):
     """Workgroups of two calls compete for the compute units; one workspace serves descriptors with different
     numbers of workgroups; a captured call is replayed on new inputs between eager ones."""
