@@ -1828,7 +1828,6 @@ __global__ __launch_bounds__(kFirstBlock, 2) void mbq_first_kernel(const T* __re
   __shared__ SumExchange ex;
   const int tid = threadIdx.x, wave = tid / kWave, lane = tid & (kWave - 1);
   ChipMail* mail = reinterpret_cast<ChipMail*>(reinterpret_cast<char*>(ctrl) + kMailOffset);
-  const uint32_t calls = uint32_t(__builtin_amdgcn_readfirstlane(int(mail->calls[blockIdx.x])));
   // the thread's item in workgroup b: its first row and column, and how many rows it has (0: none)
   struct Place {
     int64_t row0, col;
@@ -1854,6 +1853,7 @@ __global__ __launch_bounds__(kFirstBlock, 2) void mbq_first_kernel(const T* __re
   const Place mine = place(blockIdx.x);
   RawRow<VEC> kept[8];
   load(mine, kept);
+  const uint32_t calls = mail->calls[blockIdx.x];  // (behind the tensor's loads, which do not wait for it)
 
   double a[K > 1 ? K - 1 : 1] = {};
   // the sum of |rho_J| over the workgroup's items, whoever's items `rows` are; thread 0 has it
