@@ -77,10 +77,10 @@ __device__ __forceinline__ float largest_mail(const Exchange& ex) {
   for (int w = 1; w < kHeldGrid / kWave; ++w) c = fmaxf(c, ex.top[w]);
   return c;
 }
-// Finds and posts what is missing until nothing is; part(i): a thread's share of member i's largest value.  Every
-// turn takes at least one member off the list, whatever becomes of its mailbox.
-template <typename Box, typename Part>
-__device__ __forceinline__ void post_missing(uint32_t tag, Exchange& ex, Box box, Part part) {
+// Finds and posts what is missing until nothing is; part(i): a thread's share of member i's largest value; put(i, v), by
+// some threads from 0 on, posts it.  Every turn takes at least one member off the list, whatever becomes of its mailbox.
+template <typename Box, typename Part, typename Put>
+__device__ __forceinline__ void post_missing(uint32_t tag, Exchange& ex, Box box, Part part, Put put) {
   const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid / kWave;
   for (int count = missing_count(ex); count != 0; count = missing_count(ex)) {
     const int w = missing_one(ex, count);
@@ -90,7 +90,7 @@ __device__ __forceinline__ void post_missing(uint32_t tag, Exchange& ex, Box box
     if (wave < kHeldGrid / kWave) {
       float t = ex.part[0];
       for (int i = 1; i < kHeldBlock / kWave; ++i) t = fmaxf(t, ex.part[i]);
-      if (tid == 0) post(box(w), tag, t);
+      put(w, t);
       const uint64_t missing = ex.missing[wave];
       const bool wanted = (missing >> lane) & 1u;
       const uint64_t found = wanted ? look(box(tid)) : 0;
@@ -322,7 +322,7 @@ __global__ __launch_bounds__(kHeldBlock, 2) void quantize_held_kernel(const T* _
       }
       const int64_t b = units * kUnitElems + int64_t(w) * kWave + lane;
       return fmaxf(v, fabsf(load_one(x + (b < N ? b : N - 1))));
-    });
+    }, [&](int w, float v) { if (tid == 0) post(box(w), tag, v); });
     ready();
 #pragma nounroll
     for (int o = 0; o < count; ++o) {
@@ -627,7 +627,7 @@ __global__ __launch_bounds__(kHeldBlock, 2) void quantize_channels_kernel(const 
           }
         }
         return v;
-      });
+      }, [&](int i, float v) { if (thread == 0) post(boxes(ch)(i), tag, v); });
       if (thread == 0) local.top[ch - ch_lo] = f32_as_u32(largest_mail(local.ex[e]));
     }
     if (ASIDE > 0 && late) {
@@ -753,14 +753,23 @@ __global__ __launch_bounds__(kHeldBlock, 2) void quantize_whole_kernel(const T* 
   if (lane == 0) ex.top[wave] = c;
   __syncthreads();
   if (gridDim.x > 1) {
-    if (tid == 0) {
+    // Many workgroups that look at the same boxes wait for each other there: every value is posted six times then, and
+    // each workgroup looks at one set of boxes.  One set / six (us, k = 4): 1.05 M float32 5.12 / 4.89, 2.1 M 6.80 / 5.68, 8.3 M
+    // 10.9 / 10.2, 4.2 M bfloat16 6.3 / 5.5; 65536 (4 workgroups) 3.95 / 4.1, so only from 32 workgroups on.
+    constexpr int SETS = 6;
+    const bool many = gridDim.x >= 32;
+    auto box_of = [&](int set, int w) { return set < 3 ? mail->first + set * kHeldGrid + w : between_box(mail, set - 3, w); };
+    static_assert(offsetof(ChipMail, more) == 2 * sizeof(mail->first) && offsetof(ChipMail, last) == sizeof(mail->first), "sets 0 to 2 in a row");
+    auto put = [&](int w, float v) { if (tid < (many ? SETS : 1)) post(box_of(tid, w), tag, v); };
+    if (tid < SETS) {
       c = ex.top[0];
 #pragma unroll
       for (int w = 1; w < WAVES; ++w) c = fmaxf(c, ex.top[w]);
-      post(mail->first + blockIdx.x, tag, c);
+      put(int(blockIdx.x), c);
     }
     __syncthreads();
-    auto box = [&](int w) { return mail->first + w; };
+    const int mine_set = many ? int(blockIdx.x % uint32_t(SETS)) : 0;
+    auto box = [&](int w) { return box_of(mine_set, w); };
     if (wave < kHeldGrid / kWave) look_for_mail(tid, int(gridDim.x), tag, polls, ex, box);
     __syncthreads();
     if (missing_count(ex) != 0)
@@ -774,7 +783,7 @@ __global__ __launch_bounds__(kHeldBlock, 2) void quantize_whole_kernel(const T* 
           for (int e = 0; e < VEC; ++e) v = fmaxf(v, fabsf(f[e]));
         }
         return v;
-      });
+      }, put);
     c = largest_mail(ex);
     count_exchanges(mail, tag - 1u, 1u);
   } else {
