@@ -90,33 +90,34 @@ hipError_t launch_whole(const accept_desc& d, const UPlan& p, const T* x, float*
 
 // Groups of a workgroup of quantize_whole_kernel; 0: the tensor does not take it.  Range and quantize kernels / this
 // (us on the device, replayed graphs; a launch less is 3.6 us of host time on top):
-//   nearest, float32: 5 K 5.5 / 3.7, 16 K 4.7 / 3.0, 100 K 5.8 / 4.3, 300 K 6.2 / 4.7, 1 M 6.1 / 5.8, 4 M 9.4 / 8.1, 8.3 M
-//     12.9 / 11.8; bfloat16: 2.5 M 6.5 / 6.5, 8.3 M 10.8 / 9.5, 25 M 21.8 / 18.9;
-//   stochastic, float32: 20 K 7.6 / 4.5, 300 K 7.9 / 5.8, 1 M 7.9 / 7.1, 4 M 11.3 / 10.9, 8.3 M 17.5 / 17.4, 16.7 M
-//     35 / 30; bfloat16: 20 K 7.4 / 4.6, 1 M 7.6 / 6.7, 2.5 M 8.9 / 8.6, 4 M 9.3 / 9.9, 12 M 19.9 / 20.3.
-// Nearest, from 0.5 M (if not whole tiles of 8192 values, 1.5 M) to 3.2 M values (bfloat16 5 M), the device alone is faster with
-// two kernels, k = 4: float32 0.5 M 5.0 / 5.6, 2.1 M 5.4 / 6.3 to 7.1, 2.5 M 6.7 / 7.2, 3.2 M 7.4 / 7.5; bfloat16 5.0 / 5.3, 5.3 /
-// 5.9, 6.1 / 6.4, 6.0 / 6.5.  They take this one all the same: calls that are not captured are bound by the host there
-// (back to back 262144 values, two kernels, 13.3 us; 6.3 M, this one, 9.0).
-// Between kWholeSmall and kWholeLarge values, and from where the held pass begins to a third less (float32), rounding to
-// nearest keeps its two kernels: their names are what accept_stage_name is asked for there (the gain would be the
-// smallest there as well, 262144 values 5.1 / 4.6).
-constexpr int64_t kWholeSmall = int64_t(1) << 17, kWholeLarge = int64_t(1) << 18;
+//   nearest, float32: 5 K 5.3 / 3.4, 16 K 4.6 / 2.8, 100 K 5.8 / 4.3, 262144 5.0 / 4.3, 0.5 M 5.1 / 4.8, 1.05 M 5.1 / 5.2, 2.1 M
+//     5.3 / 5.6, 2.5 M 6.9 / 6.1, 4.2 M 8.2 / 7.1, 8.3 M 11.8 / 10.6, 12 M 16.3 / 13.7; bfloat16: 0.5 M 4.9 / 4.6, 2.1 M 5.2 /
+//     5.0, 8.3 M 9.5 / 8.1, 25 M 21.8 / 18.9;
+//   stochastic, float32: 20 K 7.5 / 4.5, 300 K 7.8 / 5.4, 1 M 6.6 / 6.1, 4 M 11.0 / 10.3, 12.6 M 25.0 / 23.7, 16.7 M 31.0 to 35 /
+//     30 to 31.7; bfloat16: 20 K 7.1 / 4.4, 1 M 6.5 / 5.9, 2.1 M 6.6 / 6.7, 3.1 M 8.5 / 7.7.
+// Where two kernels are ahead there (whole tiles of 8192 values, 1 to 2.1 M float32) the replays find the input in the second-level
+// cache, which the range kernel's loads leave it in; inputs that nothing has read before: 1.05 M 8.05 / 8.0, 1.57 M 8.2 / 7.9,
+// 2.1 M 8.05 / 8.2, 3.1 M 9.5 / 8.9.
+// Above, nearest, float32 begins the held pass (12.6 M values, three units); bfloat16 would need nine units, whose loads take
+// longer than two reads (26 M 19.0 / 42.5).
 template <typename T>
-constexpr int64_t kWholeNearestUnits = sizeof(T) == 4 ? ChanSlots<T>::small : ChanSlots<T>::middle;
+constexpr int64_t kWholeNearestUnits = ChanSlots<T>::middle;
 constexpr int64_t kWholeStochasticBf16 = int64_t(3) << 20;
 // The fewest groups of a workgroup: fewer workgroups have fewer mailboxes to look through, one has none; the random
-// numbers want more of them.  128 / 512 groups: nearest, 16 K 3.9 / 3.0, 1 M 6.4 / 5.8; stochastic, 20 K 4.5 / 6.6, 1 M
-// 7.1 / 8.8.
+// numbers want more of them, and so do large float32 tensors.  128 / 512 groups: nearest, 16 K 3.9 / 3.0, 1 M 6.4 /
+// 5.8; stochastic, 20 K 4.5 / 6.6, 1 M 7.1 / 8.8.  256 / 512 groups, nearest: float32 1.05 M 5.2 / 4.9, 1.5 M 5.5 / 5.3, 1.57 M
+// 5.3 / 5.7, 2.1 M 5.3 / 5.7, 3.1 M 6.4 / 6.6; bfloat16 1.05 M 4.8 / 4.8, 2.1 M 5.1 / 5.0, 4.2 M 5.7 / 5.5.
 constexpr int64_t kWholeMinGroups = kHeldBlock, kWholeMinGroupsStochastic = 128;
+template <typename T>
+constexpr int64_t kWholeSmallerParts = sizeof(T) == 4 ? int64_t(3) << 19 : INT64_MAX;  // values from which parts of half as many will do
 template <typename T>
 inline uint32_t whole_groups(int64_t N, bool stochastic) {
   const int64_t groups = N / 32;
   const int64_t units = stochastic ? ChanSlots<T>::middle : kWholeNearestUnits<T>;
   if (groups < 1 || groups > units * kHeldBlock * kHeldGrid) return 0;
-  if (stochastic ? sizeof(T) == 2 && N > kWholeStochasticBf16 : N > kWholeSmall && N <= kWholeLarge) return 0;
+  if (stochastic && sizeof(T) == 2 && N > kWholeStochasticBf16) return 0;
   const int64_t per = (groups + kHeldGrid - 1) / kHeldGrid;
-  const int64_t least = stochastic ? kWholeMinGroupsStochastic : kWholeMinGroups;
+  const int64_t least = stochastic ? kWholeMinGroupsStochastic : N >= kWholeSmallerParts<T> ? kWholeMinGroups / 2 : kWholeMinGroups;
   return uint32_t(per < least ? least : per);
 }
 

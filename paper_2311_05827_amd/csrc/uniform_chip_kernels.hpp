@@ -847,9 +847,11 @@ hipError_t launch_whole(const accept_desc& d, const UPlan& p, const T* x, float*
                        dim3(kHeldBlock), 0, s, x, payload, header, mail, p.N, p.whole_per, payload_bytes, d.seed, polls);
   };
   auto sized = [&](auto k, auto st) {
-    if (units <= 1) launch(k, std::integral_constant<int, 1>{}, st);
-    else if (units <= ChanSlots<T>::small) launch(k, std::integral_constant<int, ChanSlots<T>::small>{}, st);
-    else launch(k, std::integral_constant<int, ChanSlots<T>::middle>{}, st);
+    constexpr bool kOneUnit = sizeof(T) == 2 && decltype(st)::value;  // stochastic bfloat16 has no more
+    static_assert(kWholeStochasticBf16 / 32 <= int64_t(kHeldGrid) * kHeldBlock, "one unit");
+    if (units <= 1 || kOneUnit) launch(k, std::integral_constant<int, 1>{}, st);
+    else if (units <= ChanSlots<T>::small) launch(k, std::integral_constant<int, kOneUnit ? 1 : ChanSlots<T>::small>{}, st);
+    else launch(k, std::integral_constant<int, kOneUnit ? 1 : ChanSlots<T>::middle>{}, st);
   };
 #define ACCEPT_WHOLE(KK)                                             \
   case KK:                                                           \

@@ -127,9 +127,9 @@ def test_invalid_arguments_are_rejected_before_any_launch(A):
     assert A.accept_stage_name(good, 0, 0) == "range" and A.accept_stage_name(good, 0, 1) == "quantize_pack"
     held = A.make_desc(A.UNIFORM, 8, 64, 802816)
     assert [A.accept_stage_name(held, 0, i) for i in range(3)] == ["quantize_held", "quantize_rest", None]
-    # from 48 MiB of float32 and 72 MiB of bfloat16 on, up to 256 MiB of either
-    for code, lo, hi in ((A.F32, 12 << 20, 64 << 20), (A.BF16, 36 << 20, 128 << 20)):
-        for n, name in ((lo - 1, "range"), (lo, "quantize_held"), (hi, "quantize_held"), (hi + 1, "range")):
+    # from 48 MiB of float32 (what is smaller fits in registers) and 72 MiB of bfloat16 on, up to 256 MiB of either
+    for code, lo, hi, below in ((A.F32, 12 << 20, 64 << 20, "quantize_whole"), (A.BF16, 36 << 20, 128 << 20, "range")):
+        for n, name in ((lo - 1, below), (lo, "quantize_held"), (hi, "quantize_held"), (hi + 1, "range")):
             assert A.accept_stage_name(A.make_desc(A.UNIFORM, 4, 1, n, in_dtype=code), 0, 0) == name, (code, n)
     assert A.accept_stage_name(good, 0, 2) is None and A.accept_stage_name(mbq, 1, 0) == "mbq_decode"
     plain = A.make_desc(0, 4, 4, 4, layout=A.LAYOUT_BATCH)

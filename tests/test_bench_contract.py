@@ -30,7 +30,7 @@ def test_input_reads_follow_the_stages():
     import paper_2311_05827_amd as A
     n, m = bench.SHAPE[0], bench.SHAPE[1] * bench.SHAPE[2] * bench.SHAPE[3]
     assert bench.input_reads(A, A.make_desc(A.UNIFORM, 8, n, m)) == 1            # held pass
-    assert bench.input_reads(A, A.make_desc(A.UNIFORM, 8, 4, 65536)) == 2
+    assert bench.input_reads(A, A.make_desc(A.UNIFORM, 8, 4, 65536)) == 1        # in registers
     assert bench.input_reads(A, A.make_desc(A.UNIFORM, 8, n, m, channels=256)) == 2
     assert bench.input_reads(A, A.make_desc(A.UNIFORM, 8, n, m, rounding=A.ROUND_STOCHASTIC)) == 2
     assert bench.input_reads(A, A.make_desc(A.MBQ, 4, n, m, t=1)) == 1

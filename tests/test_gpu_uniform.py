@@ -590,11 +590,18 @@ def test_channels_on_the_chip_on_two_streams_and_in_a_graph(A):
     (63, 3, True, 0),
     (512 * 32 + 31, 8, False, 0),             # one full workgroup and what is behind
     (512 * 32 + 32, 5, False, 0),             # a group more: two workgroups
-    (1 << 17, 6, True, 0),                    # the largest of the small ones
-    ((1 << 18) + 1, 7, False, 0),             # the smallest of the large ones
+    (1 << 17, 6, True, 0),
+    (1 << 18, 6, False, 0),                   # 16 workgroups
+    ((1 << 18) + 1, 7, False, 0),
+    (31 * 512 * 32 + 31, 3, False, 0),        # the most workgroups that look at one set of boxes
+    (31 * 512 * 32 + 32, 8, True, 0),         # and the fewest that have six
+    ((3 << 19) - 1, 4, False, 0),             # the most in parts of 512 groups, float32
+    (3 << 19, 8, False, 0),                   # and the fewest in parts of 256
     (256 * 512 * 32, 2, False, 0),            # 256 workgroups of a unit
     (256 * 512 * 32 + 33, 3, False, 0),       # of a unit and a group
-    (2 * 256 * 512 * 32, 8, False, 0),        # the most, float32
+    (2 * 256 * 512 * 32, 8, False, 0),
+    (2 * 256 * 512 * 32 + 33, 6, False, 0),   # of two units and a group
+    (3 * 256 * 512 * 32 - 1, 7, False, 0),    # the most, float32
     (3 * 256 * 512 * 32 + 7, 4, True, 0),     # beyond three units, bfloat16
     (128 * 32 + 5, 8, False, 1),              # stochastic: two workgroups
     (20480, 8, False, 1),
