@@ -499,7 +499,7 @@ __global__ __launch_bounds__(kHeldBlock, 2) void quantize_channels_kernel(const 
   };
 #pragma unroll
   for (int j = 0; j < SLOTS; ++j) ask(j, kept[j]);
-  const uint32_t tag = mail->calls[blockIdx.x] + 1u;
+  const uint32_t tag = g.shared != 0 ? mail->calls[blockIdx.x] + 1u : 0u;
   const uint32_t per_channel = g.rows * g.seg_groups;
   const uint32_t ch_lo = q0 / per_channel;
   const uint32_t ch_hi = (q0 + count - 1) / per_channel;
