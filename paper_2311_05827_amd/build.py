@@ -54,16 +54,23 @@ def torch_lib():
     return os.path.join(os.path.dirname(torch.__file__), "lib")
 
 
+def _run(cmd):
+    try:
+        r = subprocess.run(cmd, capture_output=True, text=True)
+    except OSError as e:
+        return "%s\n%s" % (" ".join(cmd), e)
+    return "" if r.returncode == 0 else "%s\n%s" % (" ".join(cmd), r.stdout + r.stderr)
+
+
 def _compile_native(obj):
-    """The binding's host code, against the installed PyTorch's headers (no device code: plain g++)."""
+    """The binding's host code, against the installed PyTorch's headers (no device code: plain g++).  Returns what failed."""
     import torch
     from torch.utils.cpp_extension import include_paths
     cmd = ["g++", "-O2", "-std=c++17", "-fPIC", "-Wall",
            "-D_GLIBCXX_USE_CXX11_ABI=%d" % int(torch._C._GLIBCXX_USE_CXX11_ABI)]
     for path in include_paths() + [sysconfig.get_paths()["include"]]:
         cmd += ["-isystem", path]
-    cmd += ["-I", os.path.join(ROOT, "include"), "-c", os.path.join(CSRC, "native.cpp"), "-o", obj]
-    return subprocess.run(cmd, capture_output=True, text=True)
+    return _run(cmd + ["-I", os.path.join(ROOT, "include"), "-c", os.path.join(CSRC, "native.cpp"), "-o", obj])
 
 
 def build(verbose=True):
@@ -89,17 +96,19 @@ def build(verbose=True):
     if r.returncode != 0:
         raise RuntimeError("link failed\n%s\n%s" % (" ".join(link), r.stdout + r.stderr))
     os.replace(tmp, lib_path)
-    native = compiling_native.result()
-    if native.returncode != 0:
-        raise RuntimeError("g++ failed on native.cpp\n%s\n%s" % (" ".join(native.args), native.stdout + native.stderr))
-    link = ["g++", "-shared", "-o", NATIVE_PATH + ".tmp", os.path.join(bdir, "native.o"), "-L" + HERE, "-l:libaccept.so",
-            "-L" + torch_lib(), "-ltorch_python", "-ltorch_cpu", "-lc10", "-Wl,-rpath,$ORIGIN"]
-    r = subprocess.run(link, capture_output=True, text=True)
-    if r.returncode != 0:
-        raise RuntimeError("link failed\n%s\n%s" % (" ".join(link), r.stdout + r.stderr))
-    os.replace(NATIVE_PATH + ".tmp", NATIVE_PATH)
+    # The library serves every call without _native.so (the binding then goes through ctypes, in more host time), so
+    # a machine without g++ or Python's headers still builds it.
+    failed = compiling_native.result() or _run(
+        ["g++", "-shared", "-o", NATIVE_PATH + ".tmp", os.path.join(bdir, "native.o"), "-L" + HERE, "-l:libaccept.so",
+         "-L" + torch_lib(), "-ltorch_python", "-ltorch_cpu", "-lc10", "-Wl,-rpath,$ORIGIN"])
+    if failed:
+        if os.path.exists(NATIVE_PATH):
+            os.remove(NATIVE_PATH)  # an older one would be loaded
+        print("not built: %s\n%s" % (NATIVE_PATH, failed), file=sys.stderr)
+    else:
+        os.replace(NATIVE_PATH + ".tmp", NATIVE_PATH)
     if verbose:
-        print("built", lib_path, "and", NATIVE_PATH, file=sys.stderr)
+        print("built", lib_path, "" if failed else "and " + NATIVE_PATH, file=sys.stderr)
     return lib_path
 
 

@@ -126,3 +126,36 @@ def test_decompress_rejects_small_or_mistyped_buffers(no_library_calls):
     bad = A.make_desc(A.UNIFORM, 9, n, m)
     with pytest.raises(A.AcceptError):
         A.accept_decompress(bad, h, p, out=FakeTensor(torch.float32, n * m))
+
+
+# -------------------------------------------------------------------- with and without the native calls
+def _import_copy(tmp_path, native):
+    """Imports a copy of the package whose _native.so is missing (None) or holds the given bytes; what a child says."""
+    import os
+    import subprocess
+    import sys
+    pkg = tmp_path / "paper_2311_05827_amd"
+    pkg.mkdir()
+    for name in os.listdir(B.HERE):
+        if name.endswith(".py") or name == "libaccept.so":
+            (pkg / name).symlink_to(os.path.join(B.HERE, name))
+    if native is not None:
+        (pkg / "_native.so").write_bytes(native)
+    code = ("import paper_2311_05827_amd as A\n"
+            "d = A.make_desc(A.UNIFORM, 4, 8, 64)\n"
+            "assert A.__file__.startswith(%r)\n"
+            "print(A.accept_packed_size(d), A.binding._native.compress(d, None, None, None, None, None, False))\n" % str(tmp_path))
+    return subprocess.run([sys.executable, "-W", "always", "-c", code], capture_output=True, text=True, cwd=str(tmp_path), timeout=300)
+
+
+@pytest.mark.parametrize("native", [None, b"built against another PyTorch"])
+def test_the_package_works_without_the_native_calls(tmp_path, native):
+    """They save host time; without them (not built, or for another PyTorch) ctypes serves every call, and a warning says so."""
+    r = _import_copy(tmp_path, native)
+    assert r.returncode == 0, r.stderr
+    assert r.stdout.strip() == "(4, 256) -1"
+    assert "calls go through ctypes" in r.stderr
+
+
+def test_the_native_calls_are_built():
+    assert B._native.__file__.endswith("_native.so")
