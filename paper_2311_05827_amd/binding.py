@@ -133,7 +133,8 @@ def accept_stage_name(desc, is_decompress, i):
 # ---------------------------------------------------------------------- device-side calls
 # A small tensor's call is host time.  accept_compress, accept_decompress and accept_mbq_compress_first go
 # through csrc/native.cpp, which makes the checks below and the call in one step; whatever it does not
-# take (its answer is negative then, and nothing has been done) comes here.
+# take (its answer is negative then, and nothing has been done) comes here.  It reads a descriptor's bytes, so it
+# is given none but Desc: other objects of 64 bytes go the way on which they are refused.
 # Here sizes are asked for once per geometry, tensors are looked at with a handful of
 # attribute reads, and pointers and the stream travel as plain integers: 6-8 us.
 _DTYPES = (torch.float32, torch.bfloat16)   # by F32 / BF16
@@ -259,7 +260,7 @@ def accept_compress(desc, x, alpha_prev=None, header=None, payload=None, workspa
         header = h if header is None else header
         payload = p if payload is None else payload
         workspace = w if workspace is None else workspace
-    st = _native.compress(desc, x, alpha_prev, header, payload, workspace, False)
+    st = _native.compress(desc, x, alpha_prev, header, payload, workspace, False) if type(desc) is Desc else -1
     if st < 0:
         _check_compress_args("accept_compress", desc, x, alpha_prev, header, payload, workspace, True)
         st = lib.accept_compress(ctypes.byref(desc), _ptr(x), _ptr(alpha_prev), _ptr(header), _ptr(payload),
@@ -284,7 +285,7 @@ def accept_decompress(desc, header, payload, out=None):
     if out is None:
         _check_decompress_args("accept_decompress", desc, header, payload)
         out = torch.empty(desc.n * desc.m, dtype=_DTYPES[desc.out_dtype], device=payload.device)
-    st = _native.decompress(desc, header, payload, out)
+    st = _native.decompress(desc, header, payload, out) if type(desc) is Desc else -1
     if st < 0:
         _check_decompress_args("accept_decompress", desc, header, payload)
         _check_out("accept_decompress", desc, out)
@@ -315,7 +316,7 @@ def accept_mbq_compress_first(desc, x, header=None, payload=None, workspace=None
         header = h if header is None else header
         payload = p if payload is None else payload
         workspace = w if workspace is None else workspace
-    st = _native.compress(desc, x, None, header, payload, workspace, True)
+    st = _native.compress(desc, x, None, header, payload, workspace, True) if type(desc) is Desc else -1
     if st < 0:
         _check_compress_args("accept_mbq_compress_first", desc, x, None, header, payload, workspace, False)
         st = lib.accept_mbq_compress_first(ctypes.byref(desc), _ptr(x), _ptr(header), _ptr(payload), _ptr(workspace),

@@ -75,3 +75,39 @@ def test_every_tensor_the_binding_refuses(A, scheme):
             A.accept_decompress(d, h, p, out=o)
     A.accept_decompress(d, header, payload, out=out)
     torch.cuda.synchronize()
+
+
+def test_other_objects_than_a_descriptor_are_refused(A):
+    """64 bytes that happen to describe the call are not a descriptor; a subclass of it is."""
+    import ctypes
+    torch = torch_mod()
+
+    class Words(ctypes.Structure):
+        _fields_ = [("words", ctypes.c_int64 * 8)]
+
+    class Mine(A.Desc):
+        pass
+
+    x = torch.from_numpy(si.make_shape("grad", (N, M), 6).reshape(-1)).cuda()
+    out = torch.empty(N * M, device="cuda")
+    for scheme in (A.UNIFORM, A.MBQ):
+        d = A.make_desc(scheme, 4, N, M)
+        alpha = torch.ones(4, device="cuda")
+        header, payload, ws = A.alloc_outputs(d, "cuda")
+        want = [dev_bytes(t) for t in A.accept_compress(d, x, alpha_prev=alpha, header=header, payload=payload, workspace=ws)]
+        values = dev_bytes(A.accept_decompress(d, header, payload, out=out))
+        header.zero_()
+        payload.zero_()
+        for other in (bytes(d), bytearray(bytes(d)), memoryview(bytes(d)), Words.from_buffer_copy(bytes(d))):
+            with pytest.raises((AttributeError, TypeError, ctypes.ArgumentError)):
+                A.accept_compress(other, x, alpha_prev=alpha, header=header, payload=payload, workspace=ws)
+            with pytest.raises((AttributeError, TypeError, ctypes.ArgumentError)):
+                A.accept_decompress(other, header, payload, out=out)
+            if scheme == A.MBQ:
+                with pytest.raises((AttributeError, TypeError, ctypes.ArgumentError)):
+                    A.accept_mbq_compress_first(other, x, header=header, payload=payload, workspace=ws)
+        torch.cuda.synchronize()
+        assert not header.any() and not payload.any()
+        mine = Mine.from_buffer_copy(bytes(d))
+        got = [dev_bytes(t) for t in A.accept_compress(mine, x, alpha_prev=alpha, header=header, payload=payload, workspace=ws)]
+        assert got == want and dev_bytes(A.accept_decompress(mine, header, payload, out=out)) == values
