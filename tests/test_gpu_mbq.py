@@ -169,8 +169,10 @@ def test_batch0_compress(A, k):
     bit planes of B^0 bit-exact for the GPU's own alpha^0 bits, and the decoder reads the pair
     like any other batch."""
     torch = torch_mod()
+    # in one kernel (k <= 4), then, from 32769 items of eight rows on, in a kernel for every pass: vectors and single columns
     for shape, bf in [((16, 1000), False), ((7, 333), False), ((21, 4100), False), ((24, 2056), True), ((10, 1004), True),
-                      ((64, 8192 + 4), False)]:
+                      ((64, 8192 + 4), False),
+                      ((21, 43700), False), ((13, 16387), False), ((10, 131080), True), ((9, 16389), True), ((16, 65540), False)]:
         n, m = shape
         print("batch0 k", k, "shape", shape, "bf16", bf, flush=True)
         x = si.make_shape("relu_lognormal", shape, 6500 + k)
@@ -201,9 +203,10 @@ def test_batch0_compress(A, k):
 @pytest.mark.parametrize("k", [1, 2, 4, 5])
 @pytest.mark.parametrize("bad", ["nan", "negative nan", "inf", "-inf"])
 def test_batch0_planes_with_values_that_are_not_finite(A, k, bf16, bad):
-    """b_j = +1 where rho_j >= 0, which a residue that is not a number is not, whatever its sign bit."""
+    """b_j = +1 where rho_j >= 0, which a residue that is not a number is not, whatever its sign bit.  The last two
+    shapes take a kernel for every pass."""
     torch = torch_mod()
-    for n, m in ((16, 1000), (7, 333)):
+    for n, m in ((16, 1000), (7, 333), (9, 16389), (13, 131200)):
         x = si.make_shape("student_t3", (n, m), 7700 + k)
         x.reshape(-1)[::53] = {"nan": np.nan, "negative nan": -np.nan, "inf": np.inf, "-inf": -np.inf}[bad]
         x.reshape(-1)[::61] = 0.0

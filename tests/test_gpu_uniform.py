@@ -315,8 +315,9 @@ def test_single_columns_by_rows(A, rows):
 
 
 # One range, nearest rounding, 48 (bfloat16: 72) to 256 MiB: the end of the tensor is kept on the chip between the
-# range and the quantizer.  256 workgroups, units of 16384 elements; per workgroup 7 (bfloat16: 12)
-# units in registers, 2 (4) in local memory, the rest read twice.
+# range and the quantizer.  256 workgroups, units of 16384 elements; per workgroup 6 (bfloat16: 12)
+# units in registers, 2 (4) in local memory; of float32 tensors that this does not hold 7 and 2, the rest read twice, and a
+# second kernel does the units of workgroups that gave up.
 HELD_ROUND = 256 * 16384
 
 
@@ -325,13 +326,15 @@ HELD_ROUND = 256 * 16384
     (3, 3 * HELD_ROUND + 5 * 16384 + 8193, False),   # a few workgroups with one unit more, a tile and one element behind
     (5, 7 * HELD_ROUND + 16384, False),              # local memory comes into use
     (4, 10 * HELD_ROUND - 16384 * 7 + 33, False),    # one unit per workgroup is read twice, some have none
-    (7, 6 * HELD_ROUND + 31, True),                  # bfloat16 below its own line: two reads
+    (7, 7 * HELD_ROUND + 31, True),                  # bfloat16 below its own line: two reads
     (7, 9 * HELD_ROUND + 31, True),                  # the smallest in bfloat16
     (5, 13 * HELD_ROUND + 16384 * 3 + 9, True),      # local memory comes into use
     (6, 17 * HELD_ROUND + 16384 * 255, True),        # two read twice
     (2, 30 * HELD_ROUND + 8192, True),               # more are read twice than there are slots
 ])
 def test_held_pass(A, k, N, bf16):
+    d = A.make_desc(A.UNIFORM, k, 1, N, in_dtype=A.BF16 if bf16 else A.F32)
+    assert A.accept_stage_name(d, 0, 0) == ("range" if N == 7 * HELD_ROUND + 31 else "quantize_held")
     x = si.make_shape("grad", (1, N), 200 + k)
     x[0, N - 1 - N // 7] = 0.5  # the largest value, far from either end
     run_case(A, x, k, 1, N, in_bf16=bf16, out_bf16=bf16, tag="held")
@@ -361,13 +364,13 @@ def test_held_pass_largest_value_at_the_end(A, tail, bf16):
 
 
 def test_held_pass_that_gives_up(A):
-    """A workgroup that does not see the others' maxima in time leaves its part to the second
-    kernel; whatever share of them does (0, some, none), the bytes are the same, and the
-    workspace is ready for the next call."""
+    """A workgroup that does not see the others' maxima in time finds them itself; whatever share of them does
+    (0, some, none), the bytes are the same, and the workspace is ready for the next call."""
     torch = torch_mod()
     k, N = 5, 3 * HELD_ROUND + 16384 * 9 + 100
     xs = [torch.from_numpy(si.make_shape("grad", (N,), 220 + i) * np.float32(1 + i)).cuda() for i in range(2)]
     d = A.make_desc(A.UNIFORM, k, 1, N)
+    assert [A.accept_stage_name(d, 0, i) for i in range(2)] == ["quantize_held", None]
     want = [orc.uniform_compress(x.cpu().numpy(), k, 1, N) for x in xs]
     header, payload, ws = A.alloc_outputs(d, "cuda")
     for polls in (0, 1, 2, 64, 0, 3, 64):
@@ -379,23 +382,56 @@ def test_held_pass_that_gives_up(A):
             assert first_mismatch(dev_bytes(payload), op.tobytes()) is None, polls
 
 
-def test_held_pass_after_a_call_that_failed(A):
-    """A call whose second launch failed leaves its maxima in the workspace's mailboxes (64-bit words
-    from byte 8192 on, value and mark).  The next call takes none of them for its own."""
+@pytest.mark.parametrize("k,N,bf16,largest_behind", [
+    (5, 9 * HELD_ROUND + 33, False, True),             # a round is read twice; float32: the second kernel has work
+    (8, 8 * HELD_ROUND + 16384, False, False),         # one workgroup has a ninth unit
+    (6, 17 * HELD_ROUND + 16384 * 5 + 77, True, True),   # bfloat16, of which more than fits: one kernel all the same
+])
+def test_held_pass_of_more_than_fits_that_gives_up(A, k, N, bf16, largest_behind):
+    """As above, for tensors of which only a part is kept: what a workgroup that gives up has not quantized is all
+    read again, of float32 by the second kernel."""
+    torch = torch_mod()
+    print("case", k, N, bf16, flush=True)
+    d = A.make_desc(A.UNIFORM, k, 1, N, in_dtype=A.BF16 if bf16 else A.F32)
+    assert [A.accept_stage_name(d, 0, i) for i in range(2)] == ["quantize_held", None if bf16 else "quantize_rest"]
+    header, payload, ws = A.alloc_outputs(d, "cuda")
+    for turn in range(2):
+        x = si.make_shape("grad", (1, N), 225 + turn)
+        x[0, N - 1 if largest_behind and turn == 1 else N // 3] = -0.5
+        xd, bits = to_dev(x, bf16)
+        oh, op = orc.uniform_compress(bits if bf16 else x, k, 1, N, 0, bf16)
+        for polls in (0, 1, 2, 64):
+            header.zero_()
+            payload.zero_()
+            A.accept_compress_polls(d, xd, header, payload, ws, polls)
+            torch.cuda.synchronize()
+            assert dev_bytes(header) == oh, (turn, polls)
+            assert first_mismatch(dev_bytes(payload), op.tobytes()) is None, (turn, polls)
+
+
+def test_held_pass_and_what_earlier_calls_left(A):
+    """The mailboxes (64-bit words from byte 8192 on, value and number of the exchange) keep what the last call
+    posted, or an earlier one where later calls had fewer workgroups.  The next call takes none of it for its own."""
     torch = torch_mod()
     k, N = 8, 3 * HELD_ROUND
     x = torch.from_numpy(si.make_shape("grad", (N,), 227)).cuda()
     oh, op = orc.uniform_compress(x.cpu().numpy(), k, 1, N)
     d = A.make_desc(A.UNIFORM, k, 1, N)
     header, payload, ws = A.alloc_outputs(d, "cuda")
-    left = (0x7FFF0000 << 32) | int(np.float32(7.0).view(np.uint32))
-    for boxes in (slice(0, 256), slice(3, 4)):
-        ws[8192:8192 + 2048].view(torch.int64)[boxes] = left
-        for call in range(2):
-            A.accept_compress(d, x, header=header, payload=payload, workspace=ws)
+    number = ws[8192 + 3 * 2048:8192 + 3 * 2048 + 1024].view(torch.int32)  # of exchanges so far, by workgroup
+    A.accept_compress(d, x, header=header, payload=payload, workspace=ws)
+    for back in (0, 1, 5):
+        for boxes in (slice(0, 256), slice(3, 4)):
             torch.cuda.synchronize()
-            assert dev_bytes(header) == oh, (boxes, call)
-            assert first_mismatch(dev_bytes(payload), op.tobytes()) is None, (boxes, call)
+            now = int(number[0])
+            assert number.tolist() == [now] * 256 and now > 0
+            left = (max(now - back, 0) << 32) | int(np.float32(7.0).view(np.uint32))
+            ws[8192:8192 + 2048].view(torch.int64)[boxes] = left
+            for call in range(2):
+                A.accept_compress(d, x, header=header, payload=payload, workspace=ws)
+                torch.cuda.synchronize()
+                assert dev_bytes(header) == oh, (back, boxes, call)
+                assert first_mismatch(dev_bytes(payload), op.tobytes()) is None, (back, boxes, call)
 
 
 def test_held_pass_on_two_streams_and_in_a_graph(A):

@@ -37,8 +37,8 @@ class Uniform:
         self.want = orc.uniform_compress(x, k, n, N // n, channels)
         self.header, self.payload, _ = A.alloc_outputs(self.d, "cuda")
 
-    def call(self, ws):
-        self.A.accept_compress(self.d, self.x, header=self.header, payload=self.payload, workspace=ws)
+    def call(self, ws, polls=64):
+        self.A.accept_compress_polls(self.d, self.x, self.header, self.payload, ws, polls)
 
     def check(self, what=None):
         assert dev_bytes(self.header) == self.want[0], what
@@ -62,11 +62,94 @@ class First:
         op = orc.mbq_pack(orc.mbq_residue_signs(x, gh[:k]), k, n, m)
         self.want = dev_bytes(self.header), op.tobytes()
 
-    def call(self, ws):
-        self.A.accept_mbq_compress_first(self.d, self.x, header=self.header, payload=self.payload, workspace=ws)
+    def call(self, ws, polls=64):
+        self.A.accept_compress_polls(self.d, self.x, self.header, self.payload, ws, polls)
 
     def check(self, what=None):
         assert (dev_bytes(self.header), dev_bytes(self.payload)) == self.want, what
+
+
+class Encode:
+    """A batch that is not the first; encoders of few workgroups count these, all draw from work counters."""
+
+    def __init__(self, A, n, m, k, seed):
+        torch = torch_mod()
+        self.A, self.d = A, A.make_desc(A.MBQ, k, n, m, t=5)
+        x = si.make_shape("relu_lognormal", (n, m), seed)
+        self.x = torch.from_numpy(x.reshape(-1)).cuda()
+        self.alpha = torch.tensor([1.0, 0.5, 0.25, 0.125][:k], device="cuda")
+        self.header, self.payload, ws = A.alloc_outputs(self.d, "cuda")
+        self.call(ws)
+        torch.cuda.synchronize()
+        self.planes = orc.mbq_pack(orc.mbq_assign(x, self.alpha.cpu().numpy()), k, n, m).tobytes()
+        self.coefficients = np.frombuffer(dev_bytes(self.header), dtype="<f4").astype(np.float64)
+
+    def call(self, ws, polls=64):
+        self.A.accept_compress(self.d, self.x, alpha_prev=self.alpha, header=self.header, payload=self.payload, workspace=ws)
+
+    def check(self, what=None):
+        got = np.frombuffer(dev_bytes(self.header), dtype="<f4").astype(np.float64)
+        # which wavefront takes which part decides how the float64 sums are grouped
+        assert np.all(np.abs(got - self.coefficients) <= 1e-6 * np.abs(self.coefficients[:-1]).sum()), what
+        assert first_mismatch(dev_bytes(self.payload), self.planes) is None, what
+
+
+def test_all_kinds_of_calls_on_one_workspace(A):
+    """Every kernel that exchanges or counts something, with many and few workgroups, one after the other in any order;
+    some look in vain and make up for the others."""
+    torch = torch_mod()
+    rng = np.random.default_rng(31)
+    calls = [Uniform(A, 2 * 512 * 32 + 5, 3, 30), Uniform(A, ROUND, 8, 31), Uniform(A, 40 * 512 * 32, 4, 32),
+             Uniform(A, 3 * ROUND + 16384 + 3, 8, 33), Uniform(A, 9 * ROUND + 9, 4, 34),
+             Uniform(A, 64 * 6 * 3136, 6, 35, channels=6, n=64), Uniform(A, 3 * 7 * 1568, 5, 36, channels=7, n=3),
+             Uniform(A, 2 * 2 * 2000000, 8, 37, channels=2, n=2),
+             First(A, 64, 16384, 4, 38), First(A, 128, 160, 2, 39), First(A, 40, 6000, 3, 40),
+             Encode(A, 4, 65536, 2, 41), Encode(A, 64, 100000, 4, 42)]
+    ws = torch.zeros(max(A.accept_workspace_size(c.d) for c in calls), dtype=torch.uint8, device="cuda")
+    order = np.concatenate([rng.permutation(len(calls)) for _ in range(6)])
+    for step, i in enumerate(order):
+        c, polls = calls[i], int(rng.choice([64, 64, 0, 1, 3]))
+        c.header.zero_()
+        c.payload.zero_()
+        c.call(ws, polls)
+        torch.cuda.synchronize()
+        c.check((step, int(i), polls))
+        assert len(set(words(ws).tolist())) == 1, (step, int(i))
+
+
+@pytest.mark.parametrize("kind", ["whole", "whole, many", "first", "encode"])
+def test_small_calls_on_two_streams_and_in_a_graph(A, kind):
+    """Calls of two streams, each with its own workspace, run side by side; a captured call is replayed between eager ones."""
+    torch = torch_mod()
+    make = {"whole": lambda i: Uniform(A, (3 + i) * 512 * 32 + 7, 5, 50 + i), "whole, many": lambda i: Uniform(A, ROUND - i * 9999, 8, 52 + i),
+            "first": lambda i: First(A, 64, 16384 - 4 * i, 4, 54 + i), "encode": lambda i: Encode(A, 8, 60000 + 8 * i, 3, 56 + i)}[kind]
+    on = [make(0), make(1)]
+    spaces = [A.alloc_outputs(c.d, "cuda")[2] for c in on]
+    streams = [torch.cuda.Stream() for _ in on]
+    torch.cuda.synchronize()
+    for turn in range(8):
+        for _ in range(12):
+            for c, ws, s in zip(on, spaces, streams):
+                with torch.cuda.stream(s):
+                    c.call(ws, 64 if turn % 2 == 0 else 2)
+        torch.cuda.synchronize()
+        for c in on:
+            c.check((kind, turn))
+            c.header.zero_()
+            c.payload.zero_()
+        torch.cuda.synchronize()
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g):
+        on[0].call(spaces[0])
+    for turn in range(4):
+        on[0].header.zero_()
+        on[0].payload.zero_()
+        g.replay()
+        torch.cuda.synchronize()
+        on[0].check((kind, "replay", turn))
+        on[1].call(spaces[0])  # another call on the same workspace
+        torch.cuda.synchronize()
+        on[1].check((kind, "between", turn))
 
 
 def test_calls_that_overlapped_spoil_no_later_call(A):
