@@ -122,9 +122,9 @@ accept_status accept_workspace_size(const accept_desc* desc, size_t* bytes);
  * Compress x_dev (N elements of in_dtype, 16-byte aligned) into header_dev (4-byte
  * aligned) and payload_dev (16-byte aligned), sizes as accept_packed_size reports.
  *
- *   UNIFORM: range pass, then fused quantize + pack (one range and 48, bfloat16 72, to 256 MiB of input: both in
- *     one kernel that keeps part of the tensor on the chip; smaller ones, and with a range per channel segments of whole
- *     32s, that fit on the chip: one kernel altogether).  Code i occupies payload bits
+ *   UNIFORM: range pass, then fused quantize + pack; tensors that fit on the chip between the two, altogether or
+ *     for the most part, in one kernel (one range: up to 256 MiB of input but for the largest stochastic and some
+ *     bfloat16 ones; a range per channel: segments of whole 32s).  Code i occupies payload bits
  *     [ik, (i+1)k), most significant bit first, bit b of the stream being bit 7-(b mod 8)
  *     of byte b/8; codes are q + 2^(k-1) for k < 8 and the two's-complement byte for
  *     k = 8; unused bits of the last byte are 0.  q = clamp(round(x * fl(L/c)), -2^(k-1), L),
@@ -134,7 +134,8 @@ accept_status accept_workspace_size(const accept_desc* desc, size_t* bytes);
  *     residue initialisation).  One pass assigns every element to its nearest level,
  *     writes the bit planes (byte ((g*m + j)*k + p), g = row/8, holds bit p of rows
  *     8g..8g+7 of column j, first row in the most significant bit, rows >= n as 0) and
- *     accumulates the least-squares sums; a second, small kernel solves for alpha_t
+ *     accumulates the least-squares sums; a second, small kernel, or for small tensors the
+ *     workgroup of the first that ends last, solves for alpha_t
  *     (eqs. (alpha solution), (alpha update)) and writes header = [alpha_t, m_q].  Feed
  *     header[0..k) back as alpha_prev of the next batch.
  *
@@ -195,7 +196,8 @@ accept_status accept_mbq_init(const accept_desc* desc, const void* x_dev, float*
  * sign(rho_j), layout as accept_compress) and header = [alpha^0, m_q] with m_q =
  * mean(B^0 alpha^0 - x) (eq. (biased error)); accept_decompress reads them like any other
  * batch, and header[0..k) is alpha_prev of batch 1.  k passes over x (alpha_j needs the whole
- * tensor's |rho_j|); the last one also writes the planes.  MBQ descriptors with
+ * tensor's |rho_j|); the last one also writes the planes.  Small tensors: one kernel, which reads x once and passes
+ * over it in registers.  MBQ descriptors with
  * ACCEPT_LAYOUT_PACKED only; desc->t is ignored; buffers and workspace as for accept_compress.
  */
 accept_status accept_mbq_compress_first(const accept_desc* desc, const void* x_dev, void* header_dev,

@@ -509,7 +509,10 @@ __device__ __forceinline__ void columns_to_planes(const uint32_t* a, uint32_t (&
 // through the cache.  The first lane's item is the first in memory.  64 x 802816, k = 4, streaming / written through:
 // 46.9 / 46.2 us a call, 87.3 / 81.0 with the decoder behind it.  (bfloat16's eight dwords, two stores that
 // leave gaps: 33.1 / 38.2 us; plain stores 33.6 and with the decoder 59.0 / 54.2: streaming ones are kept.)
-// Smaller tensors lose as much in the call as the reader gains: 64 x 200704, k = 4, 19.8 / 20.0 and 32.0 / 31.5.
+// Of smaller tensors the reader gains as well, but the call itself loses up to 1 % (k = 2, streaming / written through, us):
+// 64 x 200704 16.9 / 17.1 and with the decoder behind it 28.6 / 27.6, 300032 21.1 / 21.3, 38.3 / 36.3, 400384 25.4 / 25.6, 46.2 /
+// 44.5, 458752 27.1 / 27.5, 49.7 / 47.7; from the line on it loses nothing: 524288 29.9 / 29.7, 55.5 / 52.6, 600064 33.8 / 33.6, 62.9 /
+// 60.0 (k = 4 33.4 / 33.4, 60.8 / 56.8).
 constexpr double kThroughValues = 1 << 25;
 template <int NDW, int N>
 __device__ __forceinline__ void store_planes(uint8_t* dst, const uint32_t (&out)[N]) {
@@ -1115,9 +1118,10 @@ __global__ __launch_bounds__(finalize_block(K)) void mbq_finalize_kernel(MbqCall
 
 // The same at the end of an encode kernel of few workgroups: each counts itself off when its record is written, and
 // the last one adds them up, in the finalize kernel's order, and solves.  No one waits for another.
-// A launch less is 3.6 us of host time; on the device, encode and finalize kernels / this (us, replayed graphs, k = 2 and
-// 4): 16 x 2048 float32 7.1 / 6.8, 9.9 / 10.0; 64 x 16384 (64 workgroups) 7.7 / 7.4, 10.3 / 10.5; 64 x 50000 (196: the
-// counter, one address, takes 12 ns each) 8.8 / 9.7, 11.2 / 12.6.
+// A launch less is 3.6 us of host time; on the device, encode and finalize kernels / this (us, replayed graphs, float32,
+// k = 2; 4): 16 x 2048 7.1 / 6.8; 9.9 / 10.0; 64 x 8448 (33 workgroups) 7.3 / 7.1; 10.2 / 10.4; 64 x 16384 (64) 7.5 / 7.4;
+// 10.3 / 10.6; beyond the line, where the counter, one address, takes 12 ns each: 64 x 16640 (65) 7.6 / 7.5; 10.3 / 10.7, 64 x
+// 20480 (80) 7.6 / 7.7; 10.3 / 10.9, 64 x 32768 (128) 7.9 / 8.3; 10.6 / 11.4, 64 x 50000 (196) 8.8 / 9.7; 11.2 / 12.6.
 // The workgroups of a call add 64 to the count together, whatever their number is, and nothing puts it back: so it is
 // a multiple of 64 whenever no call is under way, also after calls that overlapped on one workspace, which they must not
 // (the last of all to end then finds it so, and clears the work counters behind all of them, whichever call it is of).
@@ -1781,9 +1785,11 @@ __global__ __launch_bounds__(kBlock) void mbq_init_encode_kernel(const T* __rest
 // at most three) has a set of its own: a workgroup may be late for one that all others have left.
 //
 // What it saves is host time, 3.6 us a launch; on the device it takes, k + 1 kernels / this (us, float32): 128 x 160, k = 2
-// 8.4 / 6.8; 64 x 4000 8.6 / 7.5, k = 4 15.8 / 14.9; 64 x 16000, k = 2 9.6 / 9.8 (bfloat16 9.8 / 10.5).  (With up to four items per thread it
-// ran on tensors of 51 MB as well, which it reads once instead of k times, and gained nothing: 32 x 401408, k = 3 39.9 /
-// 42.7: two wavefronts on a SIMD take longer for the float64 sums than more of them with a second read.)
+// 8.4 / 6.8; 64 x 6144 9.0 / 8.1, k = 4 15.9 / 15.2; 64 x 8448 9.2 / 8.6, 15.9 / 15.9; 64 x 16384 (64 workgroups) 9.4 / 9.3,
+// 16.6 / 17.0; beyond the line 64 x 20480 9.4 / 10.0, 16.9 / 18.5; 64 x 32768 10.1 / 10.8, 18.0 / 19.8.  (With up to
+// four items per thread it ran on tensors of 51 MB as well, which it reads once instead of k times, and gained nothing:
+// 32 x 401408, k = 3 39.9 / 42.7.  What took the time was not measured: by its instructions, its read and its exchanges it
+// should take about 22.)
 constexpr int kFirstBlock = 512, kFirstWaves = kFirstBlock / kWave;
 struct SumExchange {
   double part[kHeldGrid / kWave];
@@ -2325,7 +2331,9 @@ MPlan make_mplan(const accept_desc& d) {
     int64_t blocks = p.stream ? (wave_items + kEncWaves - 1) / kEncWaves
                               : (full_groups * d.m + kEncBlock - 1) / kEncBlock;
     // The partial row group's wave-items are dealt to workgroups; where there is nothing else and few of them, four to
-    // a workgroup, which then are few enough to finish (4 x 65536 float32, k = 2: 7.3 -> 7.2 us, and a launch less).
+    // a workgroup, which then are few enough to finish.  One to a workgroup and a finalize kernel / four (us, float32, n = 4,
+    // k = 2; 4): 132 wave-items 6.9 / 6.5; 9.3 / 9.2, 256 6.9 / 6.7; 9.4 / 9.5, and with a line beyond, 260 6.9 / 6.8; 9.5 / 9.5,
+    // 320 6.9 / 6.9; 9.4 / 9.7, 400 7.0 / 7.2; 9.4 / 9.9, 512 7.0 / 7.5; 9.4 / 10.2.
     const bool few = full_groups == 0 && wpg <= 4 * kFinishGridMax;
     const int64_t tail_blocks = d.n % 8 == 0 ? 0 : !p.wide ? (d.m + kEncBlock - 1) / kEncBlock : few ? (wpg + 3) / 4 : wpg;
     if (blocks < tail_blocks) blocks = tail_blocks;
