@@ -1141,9 +1141,12 @@ __device__ __forceinline__ bool last_workgroup(uint32_t* counters) {
     last = (before + share) % uint32_t(kFinishGridMax) == 0u ? 1 : 0;
   }
   __syncthreads();
-  if (__builtin_amdgcn_readfirstlane(last) == 0) return false;
-  if (threadIdx.x < uint32_t(kMaxGroups)) counters[threadIdx.x * kCounterStride] = 0u;  // the work counters, for the next call
-  return true;
+  return __builtin_amdgcn_readfirstlane(last) != 0;
+}
+// The work counters, for the next call; by the last workgroup, behind its loads of the records (which in front of them
+// wait for these stores: 0.1 us).
+__device__ __forceinline__ void clear_work_counters(uint32_t* counters) {
+  if (threadIdx.x < uint32_t(kMaxGroups)) counters[threadIdx.x * kCounterStride] = 0u;
 }
 template <int K>
 __device__ __forceinline__ void finish_in_last_workgroup(const MbqCall& call, const float (&alpha_prev)[K], WaveTotals& buf) {
@@ -1156,6 +1159,7 @@ __device__ __forceinline__ void finish_in_last_workgroup(const MbqCall& call, co
     const double a = sum_records<true>(call.records + int64_t(s) * nrec, nrec, lane);
     if (lane == 0) tot[s] = a;
   }
+  clear_work_counters(call.counters);
   __syncthreads();
   if (tid == 0) solve_and_write_header<K>(tot, alpha_prev, call.n_elems, call.beta, call.header);
 }
@@ -2048,6 +2052,7 @@ __global__ __launch_bounds__(kFirstBlock, 2) void mbq_first_kernel(const T* __re
     const double t = sum_records<true>(records + int64_t(s) * nrec, nrec, lane);
     if (lane == 0) tot[s] = t;
   }
+  clear_work_counters(ctrl);
   __syncthreads();
   if (tid != 0) return;
   const float last_alpha = float(tot[0] / n_elems);
