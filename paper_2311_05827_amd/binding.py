@@ -338,7 +338,7 @@ def accept_compress_timed(desc, x, alpha_prev, header, payload, workspace):
 
 
 def accept_compress_polls(desc, x, header, payload, workspace, polls):
-    """accept_compress with a bounded number of looks inside the uniform compressor (see accept_profile.h)."""
+    """accept_compress (scheme M: accept_mbq_compress_first) with fewer looks at other workgroups (see accept_profile.h)."""
     _check_compress_args("accept_compress_polls", desc, x, None, header, payload, workspace, False)
     st = lib.accept_compress_polls(ctypes.byref(desc), _ptr(x), _ptr(None), _ptr(header), _ptr(payload),
                                    _ptr(workspace), _stream_handle(), int(polls))
