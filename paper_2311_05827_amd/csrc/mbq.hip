@@ -25,7 +25,8 @@ constexpr int kEncWaves = kEncBlock / kWave;
 // Wavefronts draw their work from counters in device memory; the workgroups with block indices
 // 8i .. 8i+7 (under round-robin dispatch one on each of the chip's eight dies) share counter i.
 constexpr int kGroupBlocks = 8;
-constexpr int kGroupSlots = 64;     // wave-items a group takes out of every sweep over the tensor
+// Wave-items a group takes out of every sweep over the tensor (as a shift; the rule is at WorkQueue).
+constexpr uint32_t kGroupSlotsShift = 2, kOneSweepSlotsShift = 6;
 constexpr int kCounterStride = 64;  // uint32 words between two counters (256 bytes: their own cache lines)
 constexpr int kEncodeGridMax = 256;
 constexpr int kPlainGridMax = 768;
@@ -756,19 +757,26 @@ __device__ __forceinline__ void encode_column(const Tables& tb, const T* __restr
 // Which wavefront ran which wave-item decides only the grouping of the float64 partial sums,
 // never a payload bit.
 //
-// Queue position c of group i is wave-item (c / 64) * sweep + 64 * i + c % 64, sweep = 64 *
+// Queue position c of group i is wave-item (c / slots) * sweep + slots * i + c % slots, sweep = slots *
 // groups: at any time the grid reads one contiguous stretch of each of eight rows (the pattern
-// memory likes best), the groups advancing through the tensor side by side.
+// memory likes best), the groups advancing through the tensor side by side.  slots = 4: the groups' shares then differ by
+// four wave-items at most.  (With 64, as many as a group has wavefronts, they differed by 64, a wave-item a
+// wavefront, for which half of the chip waited at the end.  Whole call, 64 / 16 / 4 / 1 slots, us: 64 x 802816 float32, k = 4 43.5 /
+// 42.7 / 42.7 / 43.2, bfloat16 30.8 / 29.4 / 29.3 / 29.3; 32 x 401408 float32, k = 3 16.5 / 15.5 / 15.4 / 15.4.)  A grid smaller
+// than the chip has a wavefront for every wave-item, and its last group may be smaller than the others: there a
+// sweep is all there is, and a group's share is its number of wavefronts (128 x 12544 float32, 98 workgroups, 64 / 4 slots
+// 8.3 / 11.9).
 struct WorkQueue {
   uint32_t* counter;  // the group's counter: zero when the kernel starts, put back by the finalize kernel or the last workgroup
-  uint32_t first;     // 64 * group
+  uint32_t shift;     // slots = 1 << shift
+  uint32_t first;     // slots * group
   uint32_t sweep;     // wave-items all groups take per sweep
   uint32_t count;     // queue positions 0 .. count-1 exist
   bool through;       // planes are written through the cache (see store_planes)
   uint32_t drawn;     // positions handed out without the counter: two per wavefront of the group
 };
 __device__ __forceinline__ uint32_t queue_to_wave_item(uint32_t c, const WorkQueue& q) {
-  return (c / uint32_t(kGroupSlots)) * q.sweep + q.first + (c % uint32_t(kGroupSlots));
+  return (c >> q.shift) * q.sweep + q.first + (c & ((1u << q.shift) - 1u));
 }
 
 // Where a lane's item of a wave-item lives: the row group (the same in all lanes and kept in
@@ -1198,14 +1206,15 @@ __global__ __launch_bounds__(kEncBlock) void mbq_encode_kernel(const T* __restri
                                                                         : uint32_t(kGroupBlocks);
   const uint32_t group_waves = group_blocks * uint32_t(kEncWaves);
   q.counter = call.counters + group * uint32_t(kCounterStride);
-  q.first = group * uint32_t(kGroupSlots);
-  q.sweep = groups * uint32_t(kGroupSlots);
+  q.shift = gridDim.x == uint32_t(kEncodeGridMax) ? kGroupSlotsShift : kOneSweepSlotsShift;
+  const uint32_t slots = 1u << q.shift;
+  q.first = group << q.shift;
+  q.sweep = groups << q.shift;
   {
     const uint32_t full_sweeps = n_wave_items / q.sweep;
     const uint32_t rest = n_wave_items - full_sweeps * q.sweep;
-    const uint32_t extra =
-        rest > q.first ? (rest - q.first < uint32_t(kGroupSlots) ? rest - q.first : uint32_t(kGroupSlots)) : 0u;
-    q.count = full_sweeps * uint32_t(kGroupSlots) + extra;
+    const uint32_t extra = rest > q.first ? (rest - q.first < slots ? rest - q.first : slots) : 0u;
+    q.count = (full_sweeps << q.shift) + extra;
   }
   q.through = sizeof(T) == 4 && call.n_elems >= kThroughValues;
   q.drawn = 2u * group_waves;
