@@ -130,9 +130,10 @@ struct MPlan {
   int64_t G;              // ceil(n/8) row groups
   bool ragged;            // vectors, but rows are not whole ones: at any alignment, then m % vec single columns
   bool wide;              // a row group holds at least one full wave-item
-  bool stream;            // wide, and complete row groups exist: they go through the pipelined stream
+  bool stream;            // wide, and complete row groups exist: row groups go through the pipelined stream
+  bool mixed;             // the stream's last row group is a partial one
   uint32_t wpg;           // wave-items (64 items) per row group
-  uint32_t n_wave_items;  // of the complete row groups
+  uint32_t n_wave_items;  // of the stream
   int grid;               // workgroups of the encode kernel = number of partial-sum records
   bool finish;            // the encode kernel also does the finalize kernel's work
   size_t bytes;

@@ -805,90 +805,12 @@ __device__ __forceinline__ RawRow<VEC> load_row(const T* __restrict__ x, uint32_
   return load_raw<T, VEC, RAGGED>(reinterpret_cast<const T*>(base + lane_x));
 }
 
-template <typename T, int K, int VEC, bool RAGGED, int MC, typename Tables>
-__device__ __forceinline__ void encode_stream(const Tables& tb, const T* __restrict__ x,
-                                              uint8_t* __restrict__ payload, uint64_t m, uint32_t ipg, uint32_t wpg,
-                                              const WorkQueue& q, uint32_t cur, uint32_t nxt, ItemAddr ca,
-                                              RawRow<VEC> (&fr)[8], EncodeStats<K>& st) {
-  constexpr int NW = (K + 3) / 4;
-  constexpr int GR = VEC >= 4 ? 1 : 4 / VEC;  // rows whose table lookups are issued together (at least 4 elements)
-  const int lane = threadIdx.x & (kWave - 1);
-  const uint64_t row_bytes = m * sizeof(T);
-  // The first item's rows have had the whole table build to arrive.  Waiting for them here
-  // (vmcnt 0, the other counters untouched) gives the loop an empty set of outstanding loads
-  // on entry whatever code precedes it, so that the waits the compiler places inside the loop
-  // are the ones its own steady state needs and no more.
-  __builtin_amdgcn_s_waitcnt(0x0F70);
-  while (cur < q.count) {
-    // the wave-item after the next: asked for now, looked at when this item is done (the answer
-    // comes back in line with the row loads issued below, well before it is needed)
-    uint32_t after_v = 0;
-    if (lane == 0) after_v = __hip_atomic_fetch_add(q.counter, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    // When there is no next wave-item every lane re-reads the first item of the tensor (valid,
-    // one cache line per row for the whole wavefront), so that the loads stay unconditional and
-    // the compiler can reuse the row registers in place.
-    ItemAddr na;
-    na.g = 0; na.jv = 0; na.counts = false;
-    if (nxt < q.count) na = item_addr(queue_to_wave_item(nxt, q), wpg, ipg, lane);
-    uint32_t acc[VEC][NW];
-    float h32[K];
-    float sx32 = 0.0f;
-#pragma unroll
-    for (int p = 0; p < K; ++p) h32[p] = 0.0f;
-#pragma unroll
-    for (int c = 0; c < VEC; ++c)
-#pragma unroll
-      for (int w = 0; w < NW; ++w) acc[c][w] = 0;
-#pragma unroll
-    for (int r0 = 0; r0 < 8; r0 += GR) {
-      encode_rows<K, VEC, MC, GR>(tb, fr, r0, 8, MC, acc, h32, sx32);
-      // the sums pass through an empty asm: left alone, the compiler moves the whole chain of adds
-      // to the end of the round, and every row's operands stay in registers until there
-#pragma unroll
-      for (int p = 0; p < K; ++p) asm volatile("" : "+v"(h32[p]));
-      asm volatile("" : "+v"(sx32));
-      // The loads of the next item's rows go where this group's rows were: they may not be
-      // issued before the last use of those registers (else the compiler keeps a second set of
-      // row registers and copies it over at the end of the round, which also means waiting for
-      // all eight loads there).
-      __builtin_amdgcn_sched_barrier(0);
-      {
-        // the lane offset passes through an empty asm, so that the addresses of this group's loads
-        // are formed here and not, all eight of them, at the top of the round
-        uint32_t lane_x = na.jv * uint32_t(VEC * sizeof(T));
-        asm volatile("" : "+v"(lane_x));
-#pragma unroll
-        for (int rr = 0; rr < GR; ++rr) fr[r0 + rr] = load_row<T, VEC, RAGGED>(x, na.g, row_bytes, r0 + rr, lane_x);
-      }
-      // keep the instruction scheduler from mixing groups: it would otherwise hoist the table
-      // reads of all 8*VEC elements and run out of registers
-      __builtin_amdgcn_sched_barrier(0);
-    }
-#pragma unroll
-    for (int p = 0; p < K; ++p) h32[p] *= sum_factor(tb);
-    finish_item<K, VEC, RAGGED>(acc, h32, sx32, payload + uint64_t(ca.g) * m * uint32_t(K) + ca.jv * uint32_t(VEC * K), ca.counts,
-                                st, q.through);
-    cur = nxt;
-    nxt = q.drawn + uint32_t(__builtin_amdgcn_readfirstlane(int(after_v)));
-    ca = na;
-  }
-}
-
-// The last, partial row group (n % 8 != 0) in wave-items.  Rows beyond the last give 0 bits and add nothing: they are
-// not worked through, and the last row is read in their place, so that the loads are unconditional.  The next
-// wave-item's rows are asked for before the current one's are used: a tensor of fewer than eight rows is all partial
-// group, and its wavefronts otherwise wait for memory and work in turns (us a call,
-// before / now: 1 x 12000000, k = 3, float32 56.7 / 39.7, bfloat16 42.8 / 29.7; 4 x 5416312, k = 4 38.3 / 33.3, 30.5 /
-// 25.7; 3 x 2208816, k = 2 16.8 / 13.6).
-template <typename T, int VEC, bool RAGGED>
-__device__ __forceinline__ void load_partial(const T* __restrict__ x, int64_t n, int64_t m, const ItemAddr& ia,
-                                             RawRow<VEC> (&rows)[8]) {
-  const int64_t row0 = n / 8 * 8;
-  const int last = int(n - row0) - 1;
-  const T* xc = x + row0 * m + int64_t(ia.jv) * VEC;
-#pragma unroll
-  for (int r = 0; r < 8; ++r) rows[r] = load_raw<T, VEC, RAGGED>(xc + (r < last ? r : last) * m);
-}
+// The partial row group (n % 8 != 0), behind the complete ones in the queue.
+struct PartialGroup {
+  uint32_t g;  // its number: that of the complete groups
+  int rows;    // how many it has
+  __device__ __forceinline__ int last_row(uint32_t group) const { return group == g ? rows - 1 : 7; }
+};
 // GR rows that are not there: their bits are 0.
 template <int K, int VEC, int GR>
 __device__ __forceinline__ void skip_rows(const EncodeTables<K>&, uint32_t (&acc)[VEC][(K + 3) / 4]) {
@@ -899,17 +821,127 @@ __device__ __forceinline__ void skip_rows(const EncodeTables<K>&, uint32_t (&acc
 }
 template <int K, int VEC, int GR>
 __device__ __forceinline__ void skip_rows(const ValueTables<K>&, uint32_t (&)[VEC][1]) {}
-// AHEAD: the tensor has nothing else; rows: those of the first wave-item.
-template <typename T, int K, int VEC, bool RAGGED, int MC, bool AHEAD, typename Tables>
-__device__ __forceinline__ void encode_partial(const Tables& tb, const T* __restrict__ x, uint8_t* __restrict__ payload,
-                                               int64_t n, int64_t m, uint32_t ipg, uint32_t wpg, int maxcnt,
-                                               uint32_t first, uint32_t step, RawRow<VEC> (&rows)[8],
-                                               EncodeStats<K>& st) {
+// Rows r0 .. r0+GR-1 of an item of the partial group, of which the first `nrows` are there.
+template <int K, int VEC, int MC, int GR, typename Tables>
+__device__ __forceinline__ void encode_partial_rows(const Tables& tb, RawRow<VEC> (&rows)[8], int r0, int nrows, int maxcnt,
+                                                    uint32_t (&acc)[VEC][(K + 3) / 4], float (&h32)[K], float& sx32) {
+  if (r0 < nrows) {  // the same in all lanes
+    if constexpr (GR > 1) {
+#pragma unroll
+      for (int r = r0; r < r0 + GR; ++r)
+        if (r >= nrows) rows[r].v = 0u;
+    }
+    encode_rows<K, VEC, MC, GR>(tb, rows, r0, nrows, maxcnt, acc, h32, sx32);
+  } else {
+    skip_rows<K, VEC, GR>(tb, acc);
+  }
+}
+
+// MIXED: behind the complete row groups there is a partial one; its wave-items are the last of the queue.  Rows beyond the
+// last give 0 bits and add nothing: they are not worked through, and the last row is read in their place, so that
+// the loads are unconditional.  (The partial group used to go in front of the stream or behind it, a wave-item at a time and with
+// nothing in flight meanwhile, on workgroups that had their share of the others as well.  Whole call, beside / in the queue, us:
+// 15 x 390403, k = 3, float32 15.1 / 13.1, bfloat16 15.0 / 12.0; 23 x 173913 13.9 / 10.8, k = 4 15.8 / 12.8; 15 x 20000, k = 2
+// 9.1 / 7.7; 125 x 400000, k = 4 43.6 / 42.3, 29.4 / 29.2.)
+template <typename T, int K, int VEC, bool RAGGED, int MC, bool MIXED, typename Tables>
+__device__ __forceinline__ void encode_stream(const Tables& tb, const T* __restrict__ x,
+                                              uint8_t* __restrict__ payload, uint64_t m, uint32_t ipg, uint32_t wpg,
+                                              const WorkQueue& q, const PartialGroup& part, uint32_t cur, uint32_t nxt,
+                                              ItemAddr ca, RawRow<VEC> (&fr)[8], EncodeStats<K>& st) {
+  constexpr int NW = (K + 3) / 4;
+  constexpr int GR = VEC >= 4 ? 1 : 4 / VEC;  // rows whose table lookups are issued together (at least 4 elements)
+  const int lane = threadIdx.x & (kWave - 1);
+  const uint64_t row_bytes = m * sizeof(T);
+  // The first item's rows have had the whole table build to arrive.  Waiting for them here
+  // (vmcnt 0, the other counters untouched) gives the loop an empty set of outstanding loads
+  // on entry whatever code precedes it, so that the waits the compiler places inside the loop
+  // are the ones its own steady state needs and no more.
+  __builtin_amdgcn_s_waitcnt(0x0F70);
+  auto items = [&](auto partial) {
+    while (cur < q.count && (!MIXED || decltype(partial)::value || ca.g != part.g)) {
+      // the wave-item after the next: asked for now, looked at when this item is done (the answer
+      // comes back in line with the row loads issued below, well before it is needed)
+      uint32_t after_v = 0;
+      if (lane == 0) after_v = __hip_atomic_fetch_add(q.counter, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      // When there is no next wave-item every lane re-reads the first item of the tensor (valid,
+      // one cache line per row for the whole wavefront), so that the loads stay unconditional and
+      // the compiler can reuse the row registers in place.
+      ItemAddr na;
+      na.g = 0; na.jv = 0; na.counts = false;
+      if (nxt < q.count) na = item_addr(queue_to_wave_item(nxt, q), wpg, ipg, lane);
+      const char* na_row = reinterpret_cast<const char*>(x) + uint64_t(na.g) * 8u * row_bytes;
+      const int na_last = MIXED ? part.last_row(na.g) : 7;
+      uint32_t acc[VEC][NW];
+      float h32[K];
+      float sx32 = 0.0f;
+#pragma unroll
+      for (int p = 0; p < K; ++p) h32[p] = 0.0f;
+#pragma unroll
+      for (int c = 0; c < VEC; ++c)
+#pragma unroll
+        for (int w = 0; w < NW; ++w) acc[c][w] = 0;
+#pragma unroll
+      for (int r0 = 0; r0 < 8; r0 += GR) {
+        if constexpr (decltype(partial)::value) encode_partial_rows<K, VEC, MC, GR>(tb, fr, r0, part.rows, MC, acc, h32, sx32);
+        else encode_rows<K, VEC, MC, GR>(tb, fr, r0, 8, MC, acc, h32, sx32);
+        // the sums pass through an empty asm: left alone, the compiler moves the whole chain of adds
+        // to the end of the round, and every row's operands stay in registers until there
+#pragma unroll
+        for (int p = 0; p < K; ++p) asm volatile("" : "+v"(h32[p]));
+        asm volatile("" : "+v"(sx32));
+        // The loads of the next item's rows go where this group's rows were: they may not be
+        // issued before the last use of those registers (else the compiler keeps a second set of
+        // row registers and copies it over at the end of the round, which also means waiting for
+        // all eight loads there).
+        __builtin_amdgcn_sched_barrier(0);
+        {
+          // the lane offset passes through an empty asm, so that the addresses of this group's loads
+          // are formed here and not, all eight of them, at the top of the round (and so that a last row
+          // read in another's place stays a load: a branch round it cost a third of the rate)
+          uint32_t lane_x = na.jv * uint32_t(VEC * sizeof(T));
+#pragma unroll
+          for (int r = r0; r < r0 + GR; ++r) {
+            asm volatile("" : "+v"(lane_x));
+            fr[r] = load_raw<T, VEC, RAGGED>(reinterpret_cast<const T*>(na_row + lane_x));
+            if (!MIXED || r < na_last) na_row += row_bytes;
+          }
+        }
+        // keep the instruction scheduler from mixing groups: it would otherwise hoist the table
+        // reads of all 8*VEC elements and run out of registers
+        __builtin_amdgcn_sched_barrier(0);
+      }
+#pragma unroll
+      for (int p = 0; p < K; ++p) h32[p] *= sum_factor(tb);
+      finish_item<K, VEC, RAGGED>(acc, h32, sx32, payload + uint64_t(ca.g) * m * uint32_t(K) + ca.jv * uint32_t(VEC * K), ca.counts,
+                                  st, q.through);
+      cur = nxt;
+      nxt = q.drawn + uint32_t(__builtin_amdgcn_readfirstlane(int(after_v)));
+      ca = na;
+    }
+  };
+  items(std::false_type{});
+  if constexpr (MIXED) items(std::true_type{});
+}
+
+// A partial row group by itself: all there is of a tensor of fewer than eight rows (x and payload are the group's).  The next wave-item's rows are asked for before the
+// current one's are used; its wavefronts otherwise wait for memory and work in turns (us a call,
+// before / now: 1 x 12000000, k = 3, float32 56.7 / 39.7, bfloat16 42.8 / 29.7; 4 x 5416312, k = 4 38.3 / 33.3, 30.5 /
+// 25.7; 3 x 2208816, k = 2 16.8 / 13.6).
+template <typename T, int VEC, bool RAGGED>
+__device__ __forceinline__ void load_few(const T* __restrict__ x, int n, int64_t m, const ItemAddr& ia,
+                                         RawRow<VEC> (&rows)[8]) {
+  const T* xc = x + int64_t(ia.jv) * VEC;
+#pragma unroll
+  for (int r = 0; r < 8; ++r) rows[r] = load_raw<T, VEC, RAGGED>(xc + (r < n ? r : n - 1) * m);
+}
+// rows: those of the first wave-item.
+template <typename T, int K, int VEC, bool RAGGED, int MC, typename Tables>
+__device__ __forceinline__ void encode_few(const Tables& tb, const T* __restrict__ x, uint8_t* __restrict__ payload,
+                                           int n, int64_t m, uint32_t ipg, uint32_t wpg, int maxcnt,
+                                           uint32_t first, uint32_t step, RawRow<VEC> (&rows)[8], EncodeStats<K>& st) {
   constexpr int NW = (K + 3) / 4;
   constexpr int GR = VEC >= 4 ? 1 : 4 / VEC;
   const int lane = threadIdx.x & (kWave - 1);
-  const int64_t g = n / 8;
-  const int nrows = int(n - g * 8);
   if (first >= wpg) return;
   ItemAddr ia = item_addr(first, wpg, ipg, lane);
   auto work = [&] {
@@ -924,16 +956,7 @@ __device__ __forceinline__ void encode_partial(const Tables& tb, const T* __rest
       for (int v = 0; v < NW; ++v) acc[c][v] = 0;
 #pragma unroll
     for (int r0 = 0; r0 < 8; r0 += GR) {
-      if (r0 < nrows) {  // the same in all lanes
-        if constexpr (GR > 1) {
-#pragma unroll
-          for (int r = r0; r < r0 + GR; ++r)
-            if (r >= nrows) rows[r].v = 0u;
-        }
-        encode_rows<K, VEC, MC, GR>(tb, rows, r0, nrows, maxcnt, acc, h32, sx32);
-      } else {
-        skip_rows<K, VEC, GR>(tb, acc);
-      }
+      encode_partial_rows<K, VEC, MC, GR>(tb, rows, r0, n, maxcnt, acc, h32, sx32);
 #pragma unroll
       for (int p = 0; p < K; ++p) asm volatile("" : "+v"(h32[p]));  // as in the stream
       asm volatile("" : "+v"(sx32));
@@ -941,16 +964,8 @@ __device__ __forceinline__ void encode_partial(const Tables& tb, const T* __rest
     }
 #pragma unroll
     for (int p = 0; p < K; ++p) h32[p] *= sum_factor(tb);
-    finish_item<K, VEC, RAGGED>(acc, h32, sx32, payload + (g * m + int64_t(ia.jv) * VEC) * K, ia.counts, st);
+    finish_item<K, VEC, RAGGED>(acc, h32, sx32, payload + int64_t(ia.jv) * VEC * K, ia.counts, st);
   };
-  if constexpr (!AHEAD) {
-    for (uint32_t w = first; w < wpg; w += step) {
-      ia = item_addr(w, wpg, ipg, lane);
-      load_partial<T, VEC, RAGGED>(x, n, m, ia, rows);
-      work();
-    }
-    return;
-  }
   if (first + step >= wpg) {  // one wave-item: nothing to ask for
     work();
     return;
@@ -958,7 +973,7 @@ __device__ __forceinline__ void encode_partial(const Tables& tb, const T* __rest
   for (uint32_t w = first; w < wpg; w += step) {
     const ItemAddr na = item_addr(w + step < wpg ? w + step : w, wpg, ipg, lane);
     RawRow<VEC> next[8];
-    load_partial<T, VEC, RAGGED>(x, n, m, na, next);
+    load_few<T, VEC, RAGGED>(x, n, m, na, next);
     work();
     ia = na;
 #pragma unroll
@@ -1172,21 +1187,25 @@ __device__ __forceinline__ void finish_in_last_workgroup(const MbqCall& call, co
   if (tid == 0) solve_and_write_header<K>(tot, alpha_prev, call.n_elems, call.beta, call.header);
 }
 
-// Fused M1..M4.  Complete row groups go through the pipelined stream: row r of the next
+// Which rows a tensor has (a kernel for each kind: what the others need costs 0.3 us): complete row groups only, complete ones
+// and a partial one, fewer than eight rows.
+enum Rows { kRowsComplete, kRowsMixed, kRowsFew };
+
+// Fused M1..M4.  Row groups go through the pipelined stream: row r of the next
 // wave-item is requested as soon as row r of the current one has been consumed, so a wavefront
 // always has loads in flight while it works; the first wave-item's rows are requested before
-// the tables are built.  The last, partial row group (n % 8 != 0) goes in wave-items too, without
-// the pipeline; the rare case of more than two thresholds per bucket takes the plain path, one
+// the tables are built.  The partial row group (n % 8 != 0) is the end of the same queue; the rare case of more
+// than two thresholds per bucket takes the plain path, one
 // column per thread.  RAGGED: m is not a multiple of VEC, so rows start at any alignment; vectors
 // all the same, and the last m % VEC columns one per thread (15 x 390403 float32, k = 3: this kernel
 // 12.0 us and the decoder 7.2, against 14.3 and 9.0 with single columns throughout).
-// FEW: fewer than eight rows (a kernel of its own: what they need cost the others 0.3 us).
-template <typename T, int K, int VEC, bool RAGGED, bool FINISH, bool FEW>
+template <typename T, int K, int VEC, bool RAGGED, bool FINISH, int ROWS>
 __global__ __launch_bounds__(kEncBlock) void mbq_encode_kernel(const T* __restrict__ x, uint8_t* __restrict__ payload,
                                                                MbqCall call, int64_t n, int64_t m, uint32_t ipg,
                                                                uint32_t wpg, uint32_t n_wave_items, bool wide) {
   constexpr int NPAIR = K * (K - 1) / 2;
   constexpr bool BY_VALUE = sizeof(T) == 2 && K <= 4;
+  constexpr bool FEW = ROWS == kRowsFew, MIXED = ROWS == kRowsMixed;
   using Tables = std::conditional_t<BY_VALUE, ValueTables<K>, EncodeTables<K>>;
   __shared__ Tables tb;
   __shared__ WaveTotals red;
@@ -1218,6 +1237,7 @@ __global__ __launch_bounds__(kEncBlock) void mbq_encode_kernel(const T* __restri
   }
   q.through = sizeof(T) == 4 && call.n_elems >= kThroughValues;
   q.drawn = 2u * group_waves;
+  const PartialGroup part{MIXED ? uint32_t(n / 8) : 0xFFFFFFFFu, int(n % 8)};
   const uint32_t cur = uint32_t(__builtin_amdgcn_readfirstlane(
       int((blockIdx.x - group * uint32_t(kGroupBlocks)) * uint32_t(kEncWaves) + uint32_t(tid) / uint32_t(kWave))));
   const uint32_t nxt = cur + group_waves;
@@ -1226,15 +1246,16 @@ __global__ __launch_bounds__(kEncBlock) void mbq_encode_kernel(const T* __restri
   ca.g = 0; ca.jv = 0; ca.counts = false;
   if (cur < q.count) {
     ca = item_addr(queue_to_wave_item(cur, q), wpg, ipg, lane);
+    const int last = MIXED ? part.last_row(ca.g) : 7;
 #pragma unroll
     for (int r = 0; r < 8; ++r)
-      fr[r] = load_row<T, VEC, RAGGED>(x, ca.g, uint64_t(m) * sizeof(T), r, ca.jv * uint32_t(VEC * sizeof(T)));
+      fr[r] = load_row<T, VEC, RAGGED>(x, ca.g, uint64_t(m) * sizeof(T), MIXED && r > last ? last : r, ca.jv * uint32_t(VEC * sizeof(T)));
   }
 
   const uint32_t wave_id = uint32_t(__builtin_amdgcn_readfirstlane(tid / kWave));
-  const uint32_t partial_first = wave_id * gridDim.x + blockIdx.x;
-  if (FEW && wide && partial_first < wpg)  // there is no stream: its registers are free
-    load_partial<T, VEC, RAGGED>(x, n, m, item_addr(partial_first, wpg, ipg, lane), fr);
+  const uint32_t few_first = wave_id * gridDim.x + blockIdx.x;  // wave-items are dealt to the workgroups first and to their wavefronts second
+  if (FEW && wide && few_first < wpg)
+    load_few<T, VEC, RAGGED>(x, int(n), m, item_addr(few_first, wpg, ipg, lane), fr);
 
   int maxcnt = 1;
   if constexpr (BY_VALUE) {
@@ -1255,63 +1276,66 @@ __global__ __launch_bounds__(kEncBlock) void mbq_encode_kernel(const T* __restri
 
   const int64_t stride = int64_t(gridDim.x) * kEncBlock;
   const int64_t gtid = int64_t(blockIdx.x) * kEncBlock + tid;
-  const bool stream = n_wave_items != 0u;  // else: a geometry too narrow for wave-items
-  auto complete_groups = [&] {
-    if constexpr (FEW) return;
-    if (stream && maxcnt == 1) {
-      encode_stream<T, K, VEC, RAGGED, 1>(tb, x, payload, uint64_t(m), ipg, wpg, q, cur, nxt, ca, fr, st);
-    } else if (stream && maxcnt == 2 && K <= 4 && !BY_VALUE) {
-      if constexpr (!BY_VALUE)
-        encode_stream<T, K, VEC, RAGGED, 2>(tb, x, payload, uint64_t(m), ipg, wpg, q, cur, nxt, ca, fr, st);
-    } else {
-      // several thresholds share a bucket (levels closer than a bucket's width), or a very narrow
-      // tensor: rare.  One column per thread keeps this path's register needs out of the kernel's
-      // budget.
-      const int64_t cols_full = (n / 8) * m;
-      for (int64_t s = gtid; s < cols_full; s += stride) {
-        const int64_t g = s / m;
-        encode_column<T, K>(tb, x, payload, n, m, g, s - g * m, maxcnt, st);
-      }
+  // columns j0 .. j0 + rem - 1 of row groups 0 .. G - 1, one per thread
+  auto single_columns = [&](int64_t G, int64_t j0, int64_t rem) {
+    for (int64_t s = gtid; s < G * rem; s += stride) {
+      const int64_t g = s / rem;
+      encode_column<T, K>(tb, x, payload, n, m, g, j0 + s - g * rem, maxcnt, st);
     }
   };
-  auto other_parts = [&] {
-    // the up to VEC - 1 columns of the complete row groups that no vector covers
-    if (RAGGED && stream && maxcnt <= (K <= 4 && !BY_VALUE ? 2 : 1)) {
-      const int64_t j0 = int64_t(ipg) * VEC, rem = m - j0;
-      for (int64_t s = gtid; s < (n / 8) * rem; s += stride) {
-        const int64_t g = s / rem;
-        encode_column<T, K>(tb, x, payload, n, m, g, j0 + s - g * rem, maxcnt, st);
-      }
-    }
-    // the last, partial row group: wave-items dealt to the workgroups first and to their wavefronts
-    // second; one column per thread where rows are too narrow for them, or levels too close
-    int64_t col0 = 0;  // columns from here on are left
-    if (n % 8 != 0 && wide && maxcnt == 1) {
-      RawRow<VEC> own[8];
-      if constexpr (FEW) {
-#pragma unroll
-        for (int r = 0; r < 8; ++r) own[r] = fr[r];
-      }
-      encode_partial<T, K, VEC, RAGGED, 1, FEW>(tb, x, payload, n, m, ipg, wpg, maxcnt, partial_first,
-                                           gridDim.x * uint32_t(kEncWaves), own, st);
+  if constexpr (FEW) {
+    int64_t col0 = 0;  // columns from here on go one per thread: all, where rows are too narrow or levels too close
+    if (wide && maxcnt == 1) {
+      encode_few<T, K, VEC, RAGGED, 1>(tb, x, payload, int(n), m, ipg, wpg, maxcnt, few_first,
+                                       gridDim.x * uint32_t(kEncWaves), fr, st);
       col0 = int64_t(ipg) * VEC;
     }
-    if (n % 8 != 0) {
-      for (int64_t j = col0 + gtid; j < m; j += stride)
-        encode_column<T, K>(tb, x, payload, n, m, n / 8, j, maxcnt, st);
-    }
-  };
-  // What the stream does not cover takes two or three trips to memory one after the other.  Before the
-  // stream (whose first rows are under way by then) they cost a few wavefronts items that others draw from
-  // the queue; behind it, 2 to 4 us at the end of the kernel.  Whole call, float32, k = 2, behind / before:
-  // 13113 x 1309 24.3 / 20.2 us, 3000 x 8193 27.0 / 23.1, 8315 x 1457 22.1 / 19.2.  Not so where values are
-  // looked up in a table of their own (bfloat16, k = 4, 8315 x 1457: 18.6 / 20.6).
-  if constexpr (BY_VALUE) {
-    complete_groups();
-    other_parts();
+    single_columns(1, col0, m - col0);
   } else {
-    other_parts();
-    complete_groups();
+    const bool stream = n_wave_items != 0u;  // else: a geometry too narrow for wave-items
+    auto row_groups = [&] {
+      if (stream && maxcnt == 1) {
+        encode_stream<T, K, VEC, RAGGED, 1, MIXED>(tb, x, payload, uint64_t(m), ipg, wpg, q, part, cur, nxt, ca, fr, st);
+      } else if (stream && maxcnt == 2 && K <= 4 && !BY_VALUE) {
+        if constexpr (!BY_VALUE)
+          encode_stream<T, K, VEC, RAGGED, 2, MIXED>(tb, x, payload, uint64_t(m), ipg, wpg, q, part, cur, nxt, ca, fr, st);
+      } else {
+        // several thresholds share a bucket (levels closer than a bucket's width), or a very narrow
+        // tensor: rare.  One column per thread keeps this path's register needs out of the kernel's
+        // budget.
+        single_columns((n + 7) / 8, 0, m);
+      }
+    };
+    auto other_parts = [&] {
+      // the up to VEC - 1 columns that no vector covers
+      if (RAGGED && stream && maxcnt <= (K <= 4 && !BY_VALUE ? 2 : 1))
+        single_columns((n + 7) / 8, int64_t(ipg) * VEC, m - int64_t(ipg) * VEC);
+      if constexpr (VEC == 1 && !MIXED) {  // a partial row group that is not in the queue (kMixedColumnGroups)
+        if (stream && n % 8 != 0) {
+          const int64_t g = n / 8;
+          if (maxcnt == 1) {
+            RawRow<VEC> own[8];
+            if (few_first < wpg) load_few<T, VEC, RAGGED>(x + g * 8 * m, int(n % 8), m, item_addr(few_first, wpg, ipg, lane), own);
+            encode_few<T, K, VEC, RAGGED, 1>(tb, x + g * 8 * m, payload + g * m * K, int(n % 8), m, ipg, wpg, maxcnt, few_first,
+                                             gridDim.x * uint32_t(kEncWaves), own, st);
+          } else if (maxcnt == 2 && K <= 4) {
+            for (int64_t j = gtid; j < m; j += stride) encode_column<T, K>(tb, x, payload, n, m, g, j, maxcnt, st);
+          }
+        }
+      }
+    };
+    // What the stream does not cover takes two or three trips to memory one after the other.  Before the
+    // stream (whose first rows are under way by then) they cost a few wavefronts items that others draw from
+    // the queue; behind it, 2 to 4 us at the end of the kernel.  Whole call, float32, k = 2, behind / before:
+    // 13113 x 1309 24.3 / 20.2 us, 3000 x 8193 27.0 / 23.1, 8315 x 1457 22.1 / 19.2.  Not so where values are
+    // looked up in a table of their own (bfloat16, k = 4, 8315 x 1457: 18.6 / 20.6).
+    if constexpr (BY_VALUE) {
+      row_groups();
+      other_parts();
+    } else {
+      other_parts();
+      row_groups();
+    }
   }
   store_record<K, FINISH>(st, call, red);
   if constexpr (FINISH) finish_in_last_workgroup<K>(call, alpha, red);
@@ -2166,13 +2190,14 @@ MbqCall make_call(const accept_desc& d, const float* alpha_prev, void* header, v
 template <typename T, int K, int VEC, bool RAGGED>
 hipError_t launch_encode(const accept_desc& d, const MPlan& p, const T* x, uint8_t* payload, const MbqCall& call,
                          hipStream_t s) {
-  auto launch_rows = [&](auto finish, auto few) {
-    hipLaunchKernelGGL((mbq_encode_kernel<T, K, VEC, RAGGED, decltype(finish)::value, decltype(few)::value>), dim3(p.grid), dim3(kEncBlock), 0, s, x,
+  auto launch_rows = [&](auto finish, auto rows) {
+    hipLaunchKernelGGL((mbq_encode_kernel<T, K, VEC, RAGGED, decltype(finish)::value, decltype(rows)::value>), dim3(p.grid), dim3(kEncBlock), 0, s, x,
                        payload, call, d.n, d.m, uint32_t(p.wide ? d.m / VEC : 1), p.wpg, p.n_wave_items, p.wide);
   };
   auto launch = [&](auto finish) {
-    if (d.n < 8) launch_rows(finish, std::true_type{});
-    else launch_rows(finish, std::false_type{});
+    if (d.n < 8) launch_rows(finish, std::integral_constant<int, kRowsFew>{});
+    else if (p.mixed) launch_rows(finish, std::integral_constant<int, kRowsMixed>{});
+    else launch_rows(finish, std::integral_constant<int, kRowsComplete>{});
   };
   if constexpr (K <= 4) {
     if (p.finish) {
@@ -2335,21 +2360,28 @@ MPlan make_mplan(const accept_desc& d) {
   const int64_t ipg = d.m / p.vec;
   const int64_t wpg = (ipg + kWave - 1) / kWave;
   const int64_t full_groups = d.n / 8;
-  const int64_t wave_items = full_groups * wpg;
+  // A partial row group behind complete ones is in the queue as well, except where items are single columns and complete
+  // groups many: which rows a wave-item has costs scalar instructions for every one of them, a few percent of
+  // that short work.  In the queue / beside it, float32, us: 15 x 20001, k = 2 7.2 / 7.6, 300 x 10001, k = 3 10.8 / 10.6, 8315 x
+  // 1457, k = 2 20.2 / 19.6; vectors: 15 x 390403, k = 3 13.5 / 15.2, 23 x 173913 10.9 / 14.1, 101 x 500000, k = 4 42.6 / 43.9.
+  constexpr int64_t kMixedColumnGroups = 16;
+  p.mixed = d.n % 8 != 0 && full_groups > 0 && (p.vec > 1 || full_groups <= kMixedColumnGroups);
+  const int64_t wave_items = (p.mixed ? p.G : full_groups) * wpg;
   p.wide = ipg >= kWave && wave_items < (int64_t(1) << 31) && d.m * 8 < (int64_t(1) << 32);
   p.stream = full_groups > 0 && p.wide;
+  p.mixed = p.mixed && p.wide;
   p.wpg = p.wide ? uint32_t(wpg) : 1u;
   p.n_wave_items = p.stream ? uint32_t(wave_items) : 0u;
   {
     // one workgroup of 8 wavefronts per compute unit at most; fewer when there is less work
     int64_t blocks = p.stream ? (wave_items + kEncWaves - 1) / kEncWaves
                               : (full_groups * d.m + kEncBlock - 1) / kEncBlock;
-    // The partial row group's wave-items are dealt to workgroups; where there is nothing else and few of them, four to
+    // The wave-items of fewer than eight rows are dealt to workgroups; where there are few of them, four to
     // a workgroup, which then are few enough to finish.  One to a workgroup and a finalize kernel / four (us, float32, n = 4,
     // k = 2; 4): 132 wave-items 6.9 / 6.5; 9.3 / 9.2, 256 6.9 / 6.7; 9.4 / 9.5, and with a line beyond, 260 6.9 / 6.8; 9.5 / 9.5,
     // 320 6.9 / 6.9; 9.4 / 9.7, 400 7.0 / 7.2; 9.4 / 9.9, 512 7.0 / 7.5; 9.4 / 10.2.
     const bool few = full_groups == 0 && wpg <= 4 * kFinishGridMax;
-    const int64_t tail_blocks = d.n % 8 == 0 ? 0 : !p.wide ? (d.m + kEncBlock - 1) / kEncBlock : few ? (wpg + 3) / 4 : wpg;
+    const int64_t tail_blocks = d.n % 8 == 0 || (p.mixed && p.vec > 1) ? 0 : !p.wide ? (d.m + kEncBlock - 1) / kEncBlock : few ? (wpg + 3) / 4 : wpg;
     if (blocks < tail_blocks) blocks = tail_blocks;
     if (blocks < 1) blocks = 1;
     p.grid = int(blocks < kEncodeGridMax ? blocks : kEncodeGridMax);
