@@ -1822,11 +1822,8 @@ __global__ __launch_bounds__(kBlock) void mbq_init_encode_kernel(const T* __rest
 // at most three) has a set of its own: a workgroup may be late for one that all others have left.
 //
 // What it saves is host time, 3.6 us a launch; on the device it takes, k + 1 kernels / this (us, float32): 128 x 160, k = 2
-// 8.4 / 6.8; 64 x 6144 9.0 / 8.1, k = 4 15.9 / 15.2; 64 x 8448 9.2 / 8.6, 15.9 / 15.9; 64 x 16384 (64 workgroups) 9.4 / 9.3,
-// 16.6 / 17.0; beyond the line 64 x 20480 9.4 / 10.0, 16.9 / 18.5; 64 x 32768 10.1 / 10.8, 18.0 / 19.8.  (With up to
-// four items per thread it ran on tensors of 51 MB as well, which it reads once instead of k times, and gained nothing:
-// 32 x 401408, k = 3 39.9 / 42.7.  What took the time was not measured: by its instructions, its read and its exchanges it
-// should take about 22.)
+// 8.4 / 6.6; 64 x 6144 k = 4 15.9 / 14.2; 64 x 16384 (64 workgroups) 9.4 / 9.2,
+// 16.6 / 15.1; beyond the line mbq_first_held_kernel follows.
 constexpr int kFirstBlock = 512, kFirstWaves = kFirstBlock / kWave;
 struct SumExchange {
   double part[kHeldGrid / kWave];
@@ -1848,16 +1845,69 @@ __device__ __forceinline__ void post_sum(const SumBox& box, uint32_t tag, double
   __hip_atomic_store(box.hi, t | uint32_t(bits >> 32), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 // Wavefronts 0 to 3 look for a lane's box each, at most `polls` times; `mine` is the lane's, `here` whether it is there.
+// (Looking in vain holds up the others' posts, which go to the same lines: so the first look comes when most are there.  A
+// first look at once / after 24 units of 64 cycles, 256 workgroups, k = 4, us: 64 x 20480 float32 19.3 / 13.2, 32 x 401408
+// 37.4 / 31.8; after 12 34.2, after 48 33.3.  64 workgroups at once / after 16: 64 x 16384 17.0 / 15.5, 24: 15.5 / 14.2, two
+// workgroups, k = 2 6.9 / 7.2.)
 __device__ __forceinline__ void look_for_sums(ChipMail* mail, int set, uint32_t tag, int polls, double& mine, bool& here) {
   const SumBox at = sum_box(mail, set, threadIdx.x);
+  if (gridDim.x > 64) __builtin_amdgcn_s_sleep(24);
+  else if (gridDim.x >= 16) __builtin_amdgcn_s_sleep(16);
   for (int i = 0; i < polls && __ballot(!here) != 0; ++i) {
-    if (i > 0) __builtin_amdgcn_s_sleep(2);
+    if (i > 0) __builtin_amdgcn_s_sleep(4);
     if (here) continue;
     const uint64_t lo = __hip_atomic_load(at.lo, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     const uint64_t hi = __hip_atomic_load(at.hi, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     here = uint32_t(lo >> 32) == tag && uint32_t(hi >> 32) == tag;
     if (here) mine = __longlong_as_double((long long)((hi << 32) | uint32_t(lo)));
   }
+}
+
+// The sum of all workgroups' `total` (the same in all threads), in their order; part(b): workgroup b's, by all threads.
+template <typename Part>
+__device__ __forceinline__ double exchange_sums(ChipMail* mail, int set, uint32_t tag, int polls, double total, SumExchange& ex,
+                                                Part part) {
+  const int tid = threadIdx.x, wave = tid / kWave, lane = tid & (kWave - 1);
+  if (tid == 0) post_sum(sum_box(mail, set, blockIdx.x), tag, total);
+  // threads 0 to 255 hold a workgroup's sum each, once it is there
+  double one = 0.0;
+  bool here = uint32_t(tid) >= gridDim.x;
+  auto share = [&] {  // with the other wavefronts
+    if (wave < kHeldGrid / kWave) {
+      const uint64_t missing = __ballot(!here);
+      const double t = wave_sum(one);
+      if (lane == 0) {
+        ex.missing[wave] = missing;
+        ex.part[wave] = t;
+      }
+    }
+    __syncthreads();
+    int count = 0;
+#pragma unroll
+    for (int w = 0; w < kHeldGrid / kWave; ++w) count += __popcll((unsigned long long)ex.missing[w]);
+    return __builtin_amdgcn_readfirstlane(count);
+  };
+  if (wave < kHeldGrid / kWave) look_for_sums(mail, set, tag, polls, one, here);
+  for (int count = share(); count != 0; count = share()) {  // a workgroup less is missing after every turn, whatever becomes of its mailbox
+    // one of the missing workgroups, another for neighbouring ones
+    int skip = int(blockIdx.x) % count, found = 0;
+#pragma unroll
+    for (int w = 0; w < kHeldGrid / kWave; ++w) {
+      uint64_t mw = ex.missing[w];
+      const int number = __popcll((unsigned long long)mw);
+      if (skip >= 0 && skip < number) {
+        for (; skip > 0; --skip) mw &= mw - 1;
+        found = w * kWave + __ffsll((unsigned long long)mw) - 1;
+      }
+      skip -= number;
+    }
+    const int b = __builtin_amdgcn_readfirstlane(found);
+    const double t = part(b);  // (its barrier: ex has been read by all)
+    if (tid == 0) post_sum(sum_box(mail, set, b), tag, t);
+    if (tid == b) { one = t; here = true; }
+    if (wave < kHeldGrid / kWave) look_for_sums(mail, set, tag, 1, one, here);
+  }
+  return (ex.part[0] + ex.part[1]) + (ex.part[2] + ex.part[3]);  // ex is free again behind the next barrier
 }
 
 template <typename T, int K, int VEC>
@@ -1926,8 +1976,7 @@ __global__ __launch_bounds__(kFirstBlock, 2) void mbq_first_kernel(const T* __re
     double total = red.v[0][0];
 #pragma unroll
     for (int w = 1; w < kFirstWaves; ++w) total += red.v[w][0];
-    __syncthreads();  // the buffer is free again
-    return total;
+    return total;  // the buffer is free again behind the next barrier: one of exchange_sums
   };
   auto pass = [&](auto J) {
     constexpr int j = decltype(J)::value;
@@ -1936,37 +1985,8 @@ __global__ __launch_bounds__(kFirstBlock, 2) void mbq_first_kernel(const T* __re
     for (int c = 0; c < VEC; ++c) acc[c] = 0.0;
     add_item(J, kept, mine.rows, acc);
     double total = block_total(acc);
-    if (gridDim.x > 1) {
-      const uint32_t tag = calls + 1u + uint32_t(j);
-      if (tid == 0) post_sum(sum_box(mail, j, blockIdx.x), tag, total);
-      // threads 0 to 255 hold a workgroup's sum each, once it is there
-      double one = 0.0;
-      bool here = uint32_t(tid) >= gridDim.x;
-      if (wave < kHeldGrid / kWave) look_for_sums(mail, j, tag, polls, one, here);
-      for (;;) {  // a workgroup less is missing after every turn, whatever becomes of its mailbox
-        if (wave < kHeldGrid / kWave) {
-          const uint64_t missing = __ballot(!here);
-          if (lane == 0) ex.missing[wave] = missing;
-        }
-        __syncthreads();
-        int count = 0;
-#pragma unroll
-        for (int w = 0; w < kHeldGrid / kWave; ++w) count += __popcll((unsigned long long)ex.missing[w]);
-        count = __builtin_amdgcn_readfirstlane(count);
-        if (count == 0) break;
-        // one of the missing workgroups, another for neighbouring ones
-        int skip = int(blockIdx.x) % count, found = 0;
-#pragma unroll
-        for (int w = 0; w < kHeldGrid / kWave; ++w) {
-          uint64_t mw = ex.missing[w];
-          const int number = __popcll((unsigned long long)mw);
-          if (skip >= 0 && skip < number) {
-            for (; skip > 0; --skip) mw &= mw - 1;
-            found = w * kWave + __ffsll((unsigned long long)mw) - 1;
-          }
-          skip -= number;
-        }
-        const int b = __builtin_amdgcn_readfirstlane(found);
+    if (gridDim.x > 1)
+      total = exchange_sums(mail, j, calls + 1u + uint32_t(j), polls, total, ex, [&](int b) {
         double other[VEC];
 #pragma unroll
         for (int c = 0; c < VEC; ++c) other[c] = 0.0;
@@ -1974,19 +1994,10 @@ __global__ __launch_bounds__(kFirstBlock, 2) void mbq_first_kernel(const T* __re
         const Place p = place(b);
         load(p, rows);
         add_item(J, rows, p.rows, other);
-        const double t = block_total(other);  // (its barriers: ex has been read by all)
-        if (tid == 0) post_sum(sum_box(mail, j, b), tag, t);
-        if (tid == b) { one = t; here = true; }
-        if (wave < kHeldGrid / kWave) look_for_sums(mail, j, tag, 1, one, here);
-      }
-      if (wave < kHeldGrid / kWave) {
-        const double t = wave_sum(one);
-        if (lane == 0) ex.part[wave] = t;
-      }
+        return block_total(other);
+      });
+    else
       __syncthreads();
-      total = (ex.part[0] + ex.part[1]) + (ex.part[2] + ex.part[3]);
-      __syncthreads();  // ex is free again
-    }
     const float alpha = float(total / n_elems);
     if (blockIdx.x == 0 && tid == 0) header[j] = alpha;
     a[j] = double(alpha);
@@ -2094,6 +2105,217 @@ __global__ __launch_bounds__(kFirstBlock, 2) void mbq_first_kernel(const T* __re
 #pragma unroll
   for (int p = 0; p < K; ++p) dot += (p == K - 1 ? double(last_alpha) : a[p < K - 1 ? p : 0]) * (2.0 * tot[2 + p] - n_elems);
   header[K] = float((dot - tot[1]) / n_elems);
+}
+
+// The same for larger tensors, up to SLOTS items per thread on 256 workgroups: the tensor is read once and stays in registers for
+// all passes; the header's rest is left to mbq_init_finalize_kernel.  Items go by chunks of 64, one per wavefront: chunk
+// (slot * 8 + wavefront) * 256 + workgroup, so that a last slot that is not full is spread over all workgroups.
+// k kernels and their reads / this (whole call, us): 32 x 401408, k = 2, 3, 4 27.7 / 19.0, 39.2 / 25.0, 50.6 / 31.6, bfloat16 21.3 / 17.8,
+// 30.8 / 25.7, 40.8 / 34.0; 64 x 40000, k = 3 17.6 / 12.1; 64 x 20480, k = 2 10.1 / 7.9; 3 x 800008 bfloat16 and the like as well.
+// Of the 25 us at k = 3 the read takes 10 with the launch, an exchange about 2, a pass of float64 instructions 2 to 4.5 at two
+// wavefronts per SIMD, the header's kernel 4.
+template <typename T, int K, int SLOTS>
+__global__ __launch_bounds__(kFirstBlock, 2) void mbq_first_held_kernel(const T* __restrict__ x, float* __restrict__ header,
+                                                                        uint8_t* __restrict__ payload, uint32_t* ctrl,
+                                                                        double* __restrict__ records, int64_t n, int64_t m,
+                                                                        uint32_t ipg, uint32_t items, double n_elems,
+                                                                        int polls) {
+  constexpr int VEC = Elem<T>::VEC;
+  constexpr int NDW = (VEC * K + 3) / 4;
+  static_assert(K >= 2 && K <= 4, "plane bytes of a column in one word");
+  __shared__ WaveTotals red;
+  __shared__ SumExchange ex;
+  const int tid = threadIdx.x, lane = tid & (kWave - 1);
+  const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);
+  ChipMail* mail = reinterpret_cast<ChipMail*>(reinterpret_cast<char*>(ctrl) + kMailOffset);
+  const uint32_t chunks = (items + kWave - 1) / kWave;
+  auto chunk_of = [&](int b, int slot) { return uint32_t((slot * kFirstWaves + wave) * kHeldGrid + b); };
+  // the lane's item of a chunk: row group, place in it and rows (0: a copy of the last item, which counts nothing)
+  struct Place {
+    uint32_t g, jv;
+    int rows;
+  };
+  auto place = [&](uint32_t chunk) {
+    const uint32_t it = chunk * kWave + uint32_t(lane), at = it < items ? it : items - 1u;
+    Place p;
+    p.g = at / ipg;
+    p.jv = at - p.g * ipg;
+    const int64_t left = n - int64_t(p.g) * 8;
+    p.rows = it < items ? (left < 8 ? int(left) : 8) : 0;
+    return p;
+  };
+  // (the last row in the place of those that are not there: the loads are unconditional)
+  auto load = [&](const Place& p, RawRow<VEC> (&rows)[8]) {
+    const T* at = x + int64_t(p.g) * 8 * m + int64_t(p.jv) * VEC;
+    const int64_t left = n - int64_t(p.g) * 8;
+#pragma unroll
+    for (int r = 0; r < 8; ++r) {
+      rows[r] = load_raw<T, VEC>(at);
+      if (r + 1 < left) at += m;
+    }
+  };
+  // A row's values for one pass.  (An empty asm: widened, to 64 bits in the end, they would otherwise stay in registers from
+  // one pass to the next, and be spilled.)
+  auto widen_row = [](RawRow<VEC> row, float (&f)[VEC]) {
+    asm volatile("" : "+v"(row.v.x), "+v"(row.v.y), "+v"(row.v.z), "+v"(row.v.w));
+    widen_raw<VEC>(row, f);
+  };
+  RawRow<VEC> kept[SLOTS][8];
+#pragma unroll
+  for (int j = 0; j < SLOTS; ++j) {
+    const uint32_t c = chunk_of(blockIdx.x, j);
+    if (c < chunks) load(place(c), kept[j]);  // the same in all lanes
+  }
+  const uint32_t calls = mail->calls[blockIdx.x];
+
+  double a[K - 1] = {};
+  auto add_item = [&](auto J, const RawRow<VEC> (&rows)[8], int nrows, double (&acc)[VEC]) {
+    constexpr int j = decltype(J)::value;
+    auto add = [&](auto whole) {
+#pragma unroll
+      for (int r = 0; r < 8; ++r) {
+        if (!decltype(whole)::value && __ballot(r < nrows) == 0) break;
+        float f[VEC];
+        widen_row(rows[r], f);
+#pragma unroll
+        for (int c = 0; c < VEC; ++c) {
+          double rho = double(j > 0 ? f[c] + 0.0f : f[c]);
+#pragma unroll
+          for (int q = 0; q < j; ++q) rho = residue_step(rho, a[q]);
+          acc[c] += decltype(whole)::value || r < nrows ? fabs(rho) : 0.0;
+        }
+      }
+    };
+    if (__ballot(nrows != 8) == 0) add(std::true_type{}); else add(std::false_type{});
+  };
+  auto block_total = [&](double (&acc)[VEC]) {
+#pragma unroll
+    for (int c = 1; c < VEC; ++c) acc[0] += acc[c];
+    const double t = wave_sum(acc[0]);
+    if (lane == 0) red.v[wave][0] = t;
+    __syncthreads();
+    double total = red.v[0][0];
+#pragma unroll
+    for (int w = 1; w < kFirstWaves; ++w) total += red.v[w][0];
+    return total;  // the buffer is free again behind the next barrier: one of exchange_sums
+  };
+  auto pass = [&](auto J) {
+    constexpr int j = decltype(J)::value;
+    double acc[VEC];
+#pragma unroll
+    for (int c = 0; c < VEC; ++c) acc[c] = 0.0;
+#pragma unroll
+    for (int i = 0; i < SLOTS; ++i) {
+      const uint32_t c = chunk_of(blockIdx.x, i);
+      if (c < chunks) add_item(J, kept[i], place(c).rows, acc);
+    }
+    const double total = exchange_sums(mail, j, calls + 1u + uint32_t(j), polls, block_total(acc), ex, [&](int b) {
+      double other[VEC];
+#pragma unroll
+      for (int c = 0; c < VEC; ++c) other[c] = 0.0;
+#pragma nounroll
+      for (int i = 0; i < SLOTS; ++i) {
+        const uint32_t c = chunk_of(b, i);
+        if (c >= chunks) break;
+        const Place p = place(c);
+        RawRow<VEC> rows[8];
+        load(p, rows);
+        add_item(J, rows, p.rows, other);
+      }
+      return block_total(other);
+    });
+    const float alpha = float(total / n_elems);
+    if (blockIdx.x == 0 && tid == 0) header[j] = alpha;
+    a[j] = double(alpha);
+  };
+  pass(std::integral_constant<int, 0>{});
+  if constexpr (K > 2) pass(std::integral_constant<int, 1>{});
+  if constexpr (K > 3) pass(std::integral_constant<int, 2>{});
+
+  // last pass: signs, planes and sums, as in mbq_init_encode_kernel; by compares where a residue may not be finite
+  const bool all_finite = __builtin_amdgcn_readfirstlane(fabs(a[0]) < double(__builtin_inff()) ? 1 : 0) != 0;
+  double sum_abs = 0.0, sum_x = 0.0;
+  uint32_t cnt[K];
+#pragma unroll
+  for (int p = 0; p < K; ++p) cnt[p] = 0;
+#pragma unroll
+  for (int i = 0; i < SLOTS; ++i) {
+    const uint32_t chunk = chunk_of(blockIdx.x, i);
+    if (chunk >= chunks) break;
+    const Place p = place(chunk);
+    uint32_t neg[VEC][K];
+#pragma unroll
+    for (int c = 0; c < VEC; ++c)
+#pragma unroll
+      for (int q = 0; q < K; ++q) neg[c][q] = 0;
+    float sx32 = 0.0f;
+    auto rows = [&](auto plain) {  // all rows there, all values finite
+      constexpr bool PLAIN = decltype(plain)::value;
+#pragma unroll
+      for (int r = 0; r < 8; ++r) {
+        if (!PLAIN && __ballot(r < p.rows) == 0) {  // their bits are masked out
+#pragma unroll
+          for (int c = 0; c < VEC; ++c)
+#pragma unroll
+            for (int q = 0; q < K; ++q) neg[c][q] <<= 1;
+          continue;
+        }
+        float row[VEC];
+        widen_row(kept[i][r], row);
+#pragma unroll
+        for (int c = 0; c < VEC; ++c) {
+          sx32 = __fadd_rn(sx32, PLAIN || r < p.rows ? row[c] : 0.0f);
+          double rho = double(row[c] + 0.0f);
+#pragma unroll
+          for (int q = 0; q < K; ++q) {
+            const uint32_t sign = PLAIN ? uint32_t(uint64_t(__double_as_longlong(rho)) >> 32) : (rho >= 0.0 ? 0u : 0x80000000u);
+            neg[c][q] = __builtin_amdgcn_alignbit(neg[c][q], sign, 31);
+            if (q < K - 1) rho = residue_step(rho, a[q]);
+          }
+          sum_abs += PLAIN || r < p.rows ? fabs(rho) : 0.0;
+        }
+      }
+    };
+    if (all_finite && __ballot(p.rows != 8) == 0) rows(std::true_type{}); else rows(std::false_type{});
+    uint32_t acc[VEC];
+    const uint32_t valid = 0xFFu & (0xFFu << (8 - p.rows));
+#pragma unroll
+    for (int c = 0; c < VEC; ++c) {
+      acc[c] = 0;
+#pragma unroll
+      for (int q = 0; q < K; ++q) {
+        const uint32_t plus = ~neg[c][q] & valid;  // row r at bit 7 - r; rows that are not there give 0 bits
+        cnt[q] += __popc(plus);
+        acc[c] |= plus << (8 * q);
+      }
+    }
+    sum_x += double(sx32);
+    if (p.rows > 0) {
+      uint32_t out[NDW];
+#pragma unroll
+      for (int w = 0; w < VEC / 4; ++w) {
+        const uint32_t q4[4] = {acc[4 * w], acc[4 * w + 1], acc[4 * w + 2], acc[4 * w + 3]};
+        columns_to_payload<K>(q4, &out[K * w]);
+      }
+      store_dwords<NDW>(reinterpret_cast<uint32_t*>(payload + (int64_t(p.g) * m + int64_t(p.jv) * VEC) * K), out);
+    }
+  }
+  {
+    const double sa = wave_sum(sum_abs), sx = wave_sum(sum_x);
+    if (lane == 0) { red.v[wave][0] = sa; red.v[wave][1] = sx; }
+#pragma unroll
+    for (int p = 0; p < K; ++p) {
+      const double c = double(wave_sum(cnt[p]));
+      if (lane == 0) red.v[wave][2 + p] = c;
+    }
+  }
+  __syncthreads();
+  if (tid < K + 2) {
+    double total = red.v[0][tid];
+    for (int w = 1; w < kFirstWaves; ++w) total += red.v[w][tid];
+    records[int64_t(tid) * gridDim.x + blockIdx.x] = total;
+  }
+  count_exchanges(mail, calls, uint32_t(K - 1));
 }
 
 // After the last pass: alpha_j = (sum of the workgroups' |rho_j| sums) / N, written to alpha_out[j]; of
@@ -2332,6 +2554,37 @@ hipError_t first_k(const accept_desc& d, const FirstPlan& f, const T* x, float* 
   }
 }
 
+// Batch 0 with the tensor kept in registers: items per thread of 256 workgroups; 0: not taken.
+constexpr int kFirstSlots = 4;
+int first_slots(const accept_desc& d, int vec) {
+  const int64_t items = d.m % vec == 0 ? (d.n + 7) / 8 * (d.m / vec) : INT64_MAX;
+  if (d.bits < 2 || d.bits > 4 || vec == 1 || items > int64_t(kFirstSlots) * kHeldGrid * kFirstBlock) return 0;
+  return int((items + kHeldGrid * kFirstBlock - 1) / (kHeldGrid * kFirstBlock));
+}
+template <typename T, int K, int SLOTS>
+hipError_t launch_first_held(const accept_desc& d, const T* x, float* header, uint8_t* payload, void* ws, double* records,
+                             int polls, hipStream_t s) {
+  const int64_t ipg = d.m / Elem<T>::VEC;
+  hipLaunchKernelGGL((mbq_first_held_kernel<T, K, SLOTS>), dim3(kHeldGrid), dim3(kFirstBlock), 0, s, x, header, payload,
+                     static_cast<uint32_t*>(ws), records, d.n, d.m, uint32_t(ipg), uint32_t((d.n + 7) / 8 * ipg),
+                     double(d.n) * double(d.m), polls);
+  return hipGetLastError();
+}
+template <typename T>
+hipError_t first_held_k(const accept_desc& d, int slots, const T* x, float* header, uint8_t* payload, void* ws, double* records,
+                        int polls, hipStream_t s) {
+#define ACCEPT_FIRST(KK)                                                                                        \
+  case KK:                                                                                                      \
+    return slots == 1   ? launch_first_held<T, KK, 1>(d, x, header, payload, ws, records, polls, s)             \
+           : slots == 2 ? launch_first_held<T, KK, 2>(d, x, header, payload, ws, records, polls, s)             \
+                        : launch_first_held<T, KK, kFirstSlots>(d, x, header, payload, ws, records, polls, s);
+  switch (d.bits) {
+    ACCEPT_FIRST(2) ACCEPT_FIRST(3) ACCEPT_FIRST(4)
+    default: return hipErrorInvalidValue;
+  }
+#undef ACCEPT_FIRST
+}
+
 template <typename T>
 hipError_t launch_init_pass(int j, const T* x, int64_t N, const InitCall& c, int grid, hipStream_t s) {
 #define ACCEPT_INIT(JJ)                                                                                        \
@@ -2512,10 +2765,20 @@ hipError_t launch_mbq_init(const accept_desc& d, const MPlan& p, const void* x, 
       return f.vec == 4 ? first_k<float, 4>(d, f, xf, alpha_out, pl, ws, polls, s) : first_k<float, 1>(d, f, xf, alpha_out, pl, ws, polls, s);
     }
   }
+  hipError_t e;
+  const int slots = payload != nullptr ? first_slots(d, bf ? Elem<bf16_t>::VEC : Elem<float>::VEC) : 0;
+  if (slots != 0 && compute_units() >= kHeldGrid) {
+    uint8_t* pl = static_cast<uint8_t*>(payload);
+    e = bf ? first_held_k<bf16_t>(d, slots, xb, alpha_out, pl, ws, records, polls, s)
+           : first_held_k<float>(d, slots, xf, alpha_out, pl, ws, records, polls, s);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(mbq_init_finalize_kernel, dim3(1), dim3(kFinalizeBlock), 0, s, records, kHeldGrid, k + 2, double(N),
+                       k - 1, alpha_out);
+    return hipGetLastError();
+  }
   const int64_t tiles = (N + kTileElems - 1) / kTileElems;
   InitCall c{alpha_out, nullptr, 0, nullptr, double(N)};
   int nrec = 0, nstat = 1;
-  hipError_t e;
   for (int j = 0; j < k; ++j) {
     c.prev = c.records;
     c.nprev = nrec;

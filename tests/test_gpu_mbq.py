@@ -442,3 +442,69 @@ def test_partial_row_group_in_the_queue(A, n, m, k, bf16):
     if k in (3, 4) and not bf16:
         run_case(A, x, k, n, m, alpha_prev=np.array([1.0, 0.5, 0.03, 0.02], np.float32) if k == 4 else
                  np.array([1.0, 0.03, 0.02], np.float32), tag="partial, two thresholds")
+
+
+# Batch 0 with the tensor in the registers of 256 workgroups: up to one, two, four items per thread.
+@pytest.mark.parametrize("n,m,k,bf16", [
+    (8, 4 * 131072, 2, False),       # one item per thread, all of them
+    (8, 4 * 131073, 3, False),       # one item more: a chunk of one
+    (13, 4 * 50001, 4, False),       # a chunk with lanes of both row groups, a partial row group
+    (3, 8 * 100001, 4, True),        # nothing but a partial row group
+    (21, 8 * 50000, 2, True),
+    (9, 8 * 196608, 3, True),        # four items in some wavefronts
+    (8, 4 * 524288, 3, False),       # the largest
+    (8, 4 * 524289, 2, False),       # one item more: a kernel for every pass
+])
+def test_batch0_held(A, n, m, k, bf16):
+    torch = torch_mod()
+    x = si.make_shape("relu_lognormal", (n, m), 960 + k)
+    xd, bits = to_dev(x, bf16)
+    xf = orc.widen_bf16(bits).reshape(n, m) if bf16 else x
+    d = A.make_desc(A.MBQ, k, n, m, in_dtype=A.BF16 if bf16 else A.F32)
+    header, payload, ws = A.alloc_outputs(d, "cuda")
+    oh = np.frombuffer(orc.mbq_compress_first(xf, k, n, m)[0], dtype="<f4")
+    want = None
+    for polls in (64, 0, 1, 64):  # seen by each other; workgroups add up each other's parts
+        print("case", n, m, k, bf16, polls, flush=True)
+        header.zero_()
+        payload.zero_()
+        A.accept_compress_polls(d, xd, header, payload, ws, polls)
+        torch.cuda.synchronize()
+        gh = np.frombuffer(dev_bytes(header), dtype="<f4")
+        assert np.all(np.abs(gh.astype(np.float64) - oh) <= 1e-6 * np.abs(oh[:k]).sum()), (gh, oh, polls)
+        got = (gh.tobytes(), dev_bytes(payload))
+        if want is None:
+            op = orc.mbq_pack(orc.mbq_residue_signs(xf, gh[:k]), k, n, m)
+            assert first_mismatch(got[1], op.tobytes()) is None
+            want = got
+        assert got == want, polls  # the same bits, whoever added up
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g):
+        A.accept_mbq_compress_first(d, xd, header=header, payload=payload, workspace=ws)
+    for _ in range(3):
+        A.accept_compress(d, xd, alpha_prev=header.view(torch.float32)[:k].clone(), workspace=ws)  # eager, same workspace
+        header.zero_()
+        payload.zero_()
+        g.replay()
+        torch.cuda.synchronize()
+        assert (dev_bytes(header), dev_bytes(payload)) == want
+
+
+@pytest.mark.parametrize("bf16", [False, True])
+@pytest.mark.parametrize("bad", [np.nan, -np.nan, np.inf, -np.inf])
+def test_batch0_held_values_that_are_not_finite(A, bad, bf16):
+    torch = torch_mod()
+    n, m, k = 13, 8 * 20001, 3
+    x = si.make_shape("student_t3", (n, m), 970)
+    x.reshape(-1)[::53001] = bad
+    x.reshape(-1)[::61] = 0.0
+    xd = torch.from_numpy(x.reshape(-1)).cuda()
+    xd = xd.to(torch.bfloat16) if bf16 else xd
+    d = A.make_desc(A.MBQ, k, n, m, in_dtype=A.BF16 if bf16 else A.F32)
+    header, payload = A.accept_mbq_compress_first(d, xd)
+    torch.cuda.synchronize()
+    with np.errstate(invalid="ignore"):
+        oh, op = orc.mbq_compress_first(xd.float().cpu().numpy(), k, n, m)
+    gh, ohf = np.frombuffer(dev_bytes(header), dtype="<f4"), np.frombuffer(oh, dtype="<f4")
+    assert np.array_equal(np.isnan(gh), np.isnan(ohf)) and np.array_equal(np.isinf(gh), np.isinf(ohf)), (gh, ohf)
+    assert first_mismatch(dev_bytes(payload), op.tobytes()) is None
