@@ -29,6 +29,12 @@ __device__ __forceinline__ uint64_t look(const uint64_t* box) {
 }
 // Four wavefronts look for member `i` each lane (0 .. 255), at most `polls` times; on return (in front of a barrier) ex
 // holds what is missing and the wavefronts' maxima of what is there.  Returns what this wavefront misses.
+// Looking in vain holds up the others' posts, which go to the same lines: where many look, the first look comes when
+// most posts are there (sleep units of 64 cycles).  Whole call, at once / after 8 / 16 / 24 units, us, tensors in registers,
+// float32, k = 8: 1.05 M 5.8 / 5.5 / 5.15 / 5.3, 2.1 M 6.4 / 5.7 / 5.3 / 5.5, 8.3 M 10.6 / 10.1 / 9.9 / 9.9; stochastic, 0.5 M 6.0 / 5.6 /
+// 5.1 / 5.3; held pass, after 0 / 12 / 24 / 36: 103 MB 23.9 / 23.4 / 23.3 / 23.3, 205 MB 55.7 / 55.5 / 55.3 / 55.35; two channels of 51 MB
+// 23.7 / 23.6 (8) / 23.3 (16) / 23.2 (24), while channels of few workgroups lose by any (8 x 32 x 12288 bfloat16 5.7 / 5.9 (24)).
+constexpr int kManyLook = 32;  // workgroups
 template <typename Box>
 __device__ __forceinline__ uint64_t look_for_mail(int i, int n, uint32_t tag, int polls, Exchange& ex, Box box) {
   const bool member = i < n;
@@ -280,7 +286,10 @@ __global__ __launch_bounds__(kHeldBlock, 2) void quantize_held_kernel(const T* _
   }
   __syncthreads();
   auto box = [&](int w) { return mail->first + w; };
-  if (wave < kHeldGrid / kWave) look_for_mail(tid, kHeldGrid, tag, polls, ex, box);
+  if (wave < kHeldGrid / kWave) {
+    __builtin_amdgcn_s_sleep(24);
+    look_for_mail(tid, kHeldGrid, tag, polls, ex, box);
+  }
   __syncthreads();
 
   float r = 0.0f;
@@ -586,6 +595,7 @@ __global__ __launch_bounds__(kHeldBlock, 2) void quantize_channels_kernel(const 
     if (watched(half)) {
       const uint32_t ch = half == 0 ? ch_lo : ch_hi;
       const int i = int(thread % uint32_t(kHeldGrid));
+      if (members(ch) >= kManyLook) __builtin_amdgcn_s_sleep(24);
       const uint64_t missing = look_for_mail(i, members(ch), tag, polls, local.ex[half], boxes(ch));
       if (i % kWave == 0) {
         atomicMax(&local.top[ch - ch_lo], f32_as_u32(local.ex[half].top[i / kWave]));
@@ -757,7 +767,7 @@ __global__ __launch_bounds__(kHeldBlock, 2) void quantize_whole_kernel(const T* 
     // each workgroup looks at one set of boxes.  One set / six (us, k = 4): 1.05 M float32 5.12 / 4.89, 2.1 M 6.80 / 5.68, 8.3 M
     // 10.9 / 10.2, 4.2 M bfloat16 6.3 / 5.5; 65536 (4 workgroups) 3.95 / 4.1, so only from 32 workgroups on.
     constexpr int SETS = 6;
-    const bool many = gridDim.x >= 32;
+    const bool many = gridDim.x >= uint32_t(kManyLook);
     auto box_of = [&](int set, int w) { return set < 3 ? mail->first + set * kHeldGrid + w : between_box(mail, set - 3, w); };
     static_assert(offsetof(ChipMail, more) == 2 * sizeof(mail->first) && offsetof(ChipMail, last) == sizeof(mail->first), "sets 0 to 2 in a row");
     auto put = [&](int w, float v) { if (tid < (many ? SETS : 1)) post(box_of(tid, w), tag, v); };
@@ -770,7 +780,10 @@ __global__ __launch_bounds__(kHeldBlock, 2) void quantize_whole_kernel(const T* 
     __syncthreads();
     const int mine_set = many ? int(blockIdx.x % uint32_t(SETS)) : 0;
     auto box = [&](int w) { return box_of(mine_set, w); };
-    if (wave < kHeldGrid / kWave) look_for_mail(tid, int(gridDim.x), tag, polls, ex, box);
+    if (wave < kHeldGrid / kWave) {
+      if (many) __builtin_amdgcn_s_sleep(16);
+      look_for_mail(tid, int(gridDim.x), tag, polls, ex, box);
+    }
     __syncthreads();
     if (missing_count(ex) != 0)
       post_missing(tag, ex, box, [&](int w) {
