@@ -33,8 +33,7 @@ accept_status accept_decompress_timed(const accept_desc* desc, const void* heade
 /*
  * accept_compress (MBQ without alpha_prev_dev: accept_mbq_compress_first) with a smaller bound on the wait
  * inside some of its kernels: workgroups that exchange results look at most `polls` times (0 .. 64, 64 being what
- * the call does) for each other's before they find what is missing themselves, or leave the rest to a kernel that
- * follows.  The outputs are the same for every value; tests use it to take the second way on purpose.
+ * the call does) for each other's before they find what is missing themselves.  The outputs are the same for every value; tests use it to take the second way on purpose.
  */
 accept_status accept_compress_polls(const accept_desc* desc, const void* x_dev, const float* alpha_prev_dev,
                                     void* header_dev, void* payload_dev, void* workspace_dev, void* hip_stream,

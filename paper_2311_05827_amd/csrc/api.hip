@@ -271,10 +271,10 @@ const char* accept_stage_name(const accept_desc* desc, int is_decompress, int i)
     static const char* const names[] = {"range", "range_finalize", "quantize_pack"};
     return i < 3 ? names[i] : nullptr;
   }
-  // range and quantizer in one kernel; of the largest tensors a second one finishes what that one left
+  // range and quantizer in one kernel (and see held_two_stages)
   if (held_runs(plan, units)) {
     static const char* const names[] = {"quantize_held", "quantize_rest"};
-    return i < (plan.held_rest ? 2 : 1) ? names[i] : nullptr;
+    return i < (plan.held_two_stages ? 2 : 1) ? names[i] : nullptr;
   }
   static const char* const names[] = {"range", "quantize_pack"};
   return i < 2 ? names[i] : nullptr;

@@ -1271,12 +1271,11 @@ UPlan make_uplan(const accept_desc& d) {
       p.whole_per = p.vec == 8 ? whole_groups<bf16_t>(p.N, stoch) : whole_groups<float>(p.N, stoch);
     }
     if (p.held) {
-      int64_t keep = p.vec == 8 ? kHeldUnits<bf16_t> : kHeldUnits<float>;
+      const int64_t keep = p.vec == 8 ? kHeldUnits<bf16_t> : kHeldUnits<float>;
       const int64_t keep_lds = p.vec == 8 ? kHeldLdsUnits<bf16_t> : kHeldLdsUnits<float>;
       p.held_units = p.N / kUnitElems;
       const int64_t rounds = (p.held_units + kHeldGrid - 1) / kHeldGrid;
-      p.held_rest = p.vec == 4 && rounds > keep + keep_lds;
-      if (p.held_rest) keep = kHeldLargeUnits;
+      p.held_two_stages = p.vec == 4 && rounds > 8;
       p.held_lds = rounds > keep ? int(keep_lds) : 0;
       p.held_first = rounds > keep + keep_lds ? (rounds - keep - keep_lds) * kHeldGrid : 0;
     }

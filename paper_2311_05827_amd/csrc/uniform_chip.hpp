@@ -12,16 +12,13 @@ constexpr int kHeldBlock = 512;
 constexpr int kUnitTiles = 2;
 constexpr int kUnitElems = kUnitTiles * kTileElems;  // elements a workgroup takes at a time
 template <typename T>
-constexpr int kHeldVecs = 48;  // 16-byte vectors a thread keeps in registers (more would spill)
+constexpr int kHeldVecs = 56;  // 16-byte vectors a thread keeps in registers (more would spill); 48: bfloat16 141 MB 38.6 / 37.1 us, 205 MB
+                               // 64.4 / 60.8, 103 MB equal
 constexpr int kHeldLdsVecs = 16;                     // and in local memory
 template <typename T>
-constexpr int kHeldUnits = kHeldVecs<T> * kHeldBlock * Elem<T>::VEC / kUnitElems;  // 6 (float32), 12 (bfloat16)
+constexpr int kHeldUnits = kHeldVecs<T> * kHeldBlock * Elem<T>::VEC / kUnitElems;  // 7 (float32), 14 (bfloat16)
 template <typename T>
 constexpr int kHeldLdsUnits = kHeldLdsVecs * kHeldBlock * Elem<T>::VEC / kUnitElems;  // 2, 4
-// The largest float32 tensors, of which not all is kept: one unit more in registers.  There is then no room left
-// for the code that goes on where a workgroup gives up, and a second kernel (4 us) does that: 205 MB, k = 8 / 4 58.3 /
-// 54.8 us, with six units and no second kernel 59.7 / 56.9; 160 MB 41.5 / 39.7 (before, 45.5 / 42.2).
-constexpr int kHeldLargeUnits = 7;
 // Tensors that take the held pass.  Captured calls, two reads / held (us), when the held pass still had a second
 // kernel (4 us) always: float32 51 MB 19.2 / 18.9 (15.5 now), 66 MB 23.3 / 21.1; bfloat16, whose values are twice as
 // many, 51 MB 19.6 / 21.9, 72 MB 27.5 / 27.5 (22.8 now), 95 MB 35.2 / 32.8.  Above, the part that is kept gets small

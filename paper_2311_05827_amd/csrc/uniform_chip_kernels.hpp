@@ -154,14 +154,15 @@ __device__ __forceinline__ void quantize_behind(const T* __restrict__ x, uint32_
 // reads the tensor twice, and the memory-side cache does not help: it delivers 7.4 TB/s, memory
 // itself 7.2.  The registers and local memories of the chip hold 168 MiB, though.  Here one workgroup per compute unit
 // reads units (16384 elements) b, b + 256, ..., keeps the last of them (float32: 7 units in registers
-// and 2 in local memory, 151 MB over the chip; bfloat16: 12 and 4, 134 MB), hands its maximum to the
+// and 2 in local memory, 151 MB over the chip; bfloat16: 14 and 4, the same), hands its maximum to the
 // other workgroups through a mailbox, waits for theirs, quantizes what it kept and reads the units
 // before held_first once more.  The up to 16383 elements behind the last whole unit are shared out, 64 to a
 // workgroup, for the range and for the codes.
 //
 // A workgroup that does not see all the others' maxima in time (see Exchange) no longer uses what it kept, so that
-// its registers serve for the others' parts, and reads its own units again; REST: it says so and ends, and
-// quantize_late_kernel does its units.
+// its registers serve for the others' parts, and reads its own units again, the way it reads those that it did not keep.
+// (With code of its own for that, seven slots were spilled; a second kernel for such workgroups' units took 3 us of every
+// call: 205 MB, k = 8 / 4 55.3 / 52.5 -> HELDNEW8 / HELDNEW4 us.)
 //
 // Beside other work: a workgroup needs a whole compute unit (160 KiB of local memory, all registers), so
 // next to a kernel whose workgroups keep filling the chip it starts late, and the early ones give up.
@@ -170,11 +171,11 @@ __device__ __forceinline__ void quantize_behind(const T* __restrict__ x, uint32_
 // 39, 33.6 / 26.2; matrix products beside 205 MB 184 / 179, 240 / 150, beside 103 MB bfloat16 160 / 155, 228 / 128;
 // copies of 512 MB without a pause 66 / 98, 105 / 86, 130 / 161, 162 / 160, 72 / 145, 142 / 140.
 //
-// 51.4 M float32 values (205 MB), k = 8: 58.3 us a call (two reads 69.5): 31 us to the mailboxes, 2 to 3 for the
+// 51.4 M float32 values (205 MB), k = 8: 54.1 us a call (two reads 69.5): 31 us to the mailboxes, 2 to 3 for the
 // exchange.  103 MB: 32 -> 26 us against the held pass with a second kernel and plain stores, bfloat16 103 MB 36 -> 30.
 // Stochastic rounding keeps the two reads: it is bound by its instructions, which the second read
 // hides behind.
-template <typename T, int K, int SLOTS, bool REST>
+template <typename T, int K, int SLOTS>
 __global__ __launch_bounds__(kHeldBlock, 2) void quantize_held_kernel(const T* __restrict__ x,
                                                                       uint32_t* __restrict__ payload32,
                                                                       float* __restrict__ header,
@@ -298,19 +299,9 @@ __global__ __launch_bounds__(kHeldBlock, 2) void quantize_held_kernel(const T* _
     quantize_unit<T, K>(local.pieces[buf_i], r, payload32, int64_t(ordinal) * kHeldGrid + blockIdx.x, vec_of);
     buf_i ^= 1;
   };
-  auto ready = [&] {  // the range is known
-    float s;
-    scale_from_range(largest_mail(ex), K, s, r);
-    if (blockIdx.x == 0 && tid == 0) header[0] = s;
-  };
-  // (The hint decides which values the compiler keeps in registers: without it, or with it for the other type, some
-  // are spilled.)
   const bool late = missing_count(ex) != 0;
-  if (sizeof(T) == 4 ? __builtin_expect(late, 0) : late) {
-    if constexpr (REST) {
-      if (tid == 0) mail->last[blockIdx.x] = (uint64_t(tag) << 32) | 1u;
-      return;
-    }
+  int from = first, held_from = base, in_lds = lds_units;  // ordinals before `from` are to be read again
+  if (late) {
     post_missing(tag, ex, box, [&](int w) {
       float v = 0.0f;
       for (int64_t unit = w; unit < units; unit += kHeldGrid) {
@@ -332,29 +323,32 @@ __global__ __launch_bounds__(kHeldBlock, 2) void quantize_held_kernel(const T* _
       const int64_t b = units * kUnitElems + int64_t(w) * kWave + lane;
       return fmaxf(v, fabsf(load_one(x + (b < N ? b : N - 1))));
     }, [&](int w, float v) { if (tid == 0) post(box(w), tag, v); });
-    ready();
-#pragma nounroll
-    for (int o = 0; o < count; ++o) {
-      uint4 now[LOADS];
-      ask(o, now);
-      quantize(o, [&](int u) { return now[u]; });
-    }
-    quantize_behind<T, K>(x, payload32, r, N, units, payload_bytes, blockIdx.x);
-    return;
+    from = held_from = count;
+    in_lds = 0;
+    // (an empty asm: what was kept need not live through the above)
+#pragma unroll
+    for (int j = 0; j < SLOTS; ++j)
+#pragma unroll
+      for (int u = 0; u < LOADS; ++u)
+        asm volatile("" : "=v"(kept[j][u].x), "=v"(kept[j][u].y), "=v"(kept[j][u].z), "=v"(kept[j][u].w));
   }
-  ready();
+  {
+    float s;
+    scale_from_range(largest_mail(ex), K, s, r);
+    if (blockIdx.x == 0 && tid == 0) header[0] = s;
+  }
   // A slot that has been quantized takes a unit that was only looked at, the last of them first;
   // those loads are under way while the other kept units are quantized.  (Conditions are the same
   // in all threads.)
 #pragma unroll
   for (int j = 0; j < SLOTS; ++j) {
-    if (base + j < count) quantize(base + j, [&](int u) { return kept[j][u]; });
-    if (j < first) ask(first - 1 - j, kept[j]);
+    if (held_from + j < count) quantize(held_from + j, [&](int u) { return kept[j][u]; });
+    if (j < from) ask(from - 1 - j, kept[j]);
   }
-  if (lds_units != 0) {
+  if (in_lds != 0) {
     for (int q = 0; q < LDS_UNITS; ++q) quantize(first + q, [&](int u) { return local.kept[q][u][tid]; });
   }
-  for (int o = first - 1; o >= 0; o -= SLOTS) {
+  for (int o = from - 1; o >= 0; o -= SLOTS) {
 #pragma unroll
     for (int j = 0; j < SLOTS; ++j) {
       if (o - j >= 0) {
@@ -364,41 +358,6 @@ __global__ __launch_bounds__(kHeldBlock, 2) void quantize_held_kernel(const T* _
     }
   }
   quantize_behind<T, K>(x, payload32, r, N, units, payload_bytes, blockIdx.x);
-}
-
-// Behind the held pass of the largest float32 tensors: the units of workgroups that gave up, a workgroup to each.
-template <typename T, int K>
-__global__ __launch_bounds__(kHeldBlock) void quantize_late_kernel(const T* __restrict__ x, uint32_t* __restrict__ payload32,
-                                                                   float* __restrict__ header,
-                                                                   const ChipMail* __restrict__ mail, int64_t N,
-                                                                   int64_t units, int64_t payload_bytes) {
-  constexpr int VEC = Elem<T>::VEC;
-  constexpr int LOADS = kUnitElems / (kHeldBlock * VEC);
-  const int b = blockIdx.x;
-  const uint32_t tag = mail->calls[b];  // of the call: the kernel before has raised it
-  if (mail->last[b] != ((uint64_t(tag) << 32) | 1u)) return;
-  __shared__ __attribute__((aligned(16))) uint32_t pieces[2][kUnitElems / 4];
-  __shared__ float red[kHeldGrid / kWave];
-  const int tid = threadIdx.x;
-  if (tid < kHeldGrid) {
-    const float t = wave_max(u32_as_f32(uint32_t(mail->first[tid])));
-    if ((tid & (kWave - 1)) == 0) red[tid / kWave] = t;
-  }
-  __syncthreads();
-  float c = red[0], s, r;
-#pragma unroll
-  for (int w = 1; w < kHeldGrid / kWave; ++w) c = fmaxf(c, red[w]);
-  scale_from_range(c, K, s, r);
-  if (b == 0 && tid == 0) header[0] = s;
-  int buf_i = 0;
-  for (int64_t unit = b; unit < units; unit += kHeldGrid) {
-    uint4 raw[LOADS];
-#pragma unroll
-    for (int u = 0; u < LOADS; ++u) raw[u] = load16_stream(x + unit * kUnitElems + (u * kHeldBlock + tid) * VEC);
-    quantize_unit<T, K>(pieces[buf_i], r, payload32, unit, [&](int u) { return raw[u]; });
-    buf_i ^= 1;
-  }
-  quantize_behind<T, K>(x, payload32, r, N, units, payload_bytes, b);
 }
 
 // U1, U1b, U2 and U3 of a tensor with one range per channel, in one kernel and with one read: the
@@ -883,26 +842,17 @@ template <typename T>
 hipError_t launch_held(const accept_desc& d, const UPlan& p, const T* x, float* header, uint32_t* payload,
                        ChipMail* mail, int polls, hipStream_t s, StageTimer* tm) {
   const int64_t payload_bytes = (p.N * d.bits + 7) / 8;
-  constexpr bool kTwo = sizeof(T) == 4;  // bfloat16 has one form
-#define ACCEPT_HELD(KK)                                                                                                \
-  case KK:                                                                                                             \
-    if (kTwo && p.held_rest) {                                                                                         \
-      hipLaunchKernelGGL((quantize_held_kernel<T, KK, kTwo ? kHeldLargeUnits : kHeldUnits<T>, kTwo>), dim3(kHeldGrid), \
-                         dim3(kHeldBlock), 0, s, x, payload, header, mail, p.N, p.held_units, p.held_first, p.held_lds, \
-                         payload_bytes, polls);                                                                        \
-      mark(tm, s);                                                                                                     \
-      hipLaunchKernelGGL((quantize_late_kernel<T, KK>), dim3(kHeldGrid), dim3(kHeldBlock), 0, s, x, payload,               \
-                         header, mail, p.N, p.held_units, payload_bytes);                                              \
-    } else {                                                                                                           \
-      hipLaunchKernelGGL((quantize_held_kernel<T, KK, kHeldUnits<T>, false>), dim3(kHeldGrid), dim3(kHeldBlock), 0, s, x, \
-                         payload, header, mail, p.N, p.held_units, p.held_first, p.held_lds, payload_bytes, polls);    \
-    }                                                                                                                  \
+#define ACCEPT_HELD(KK)                                                                                                 \
+  case KK:                                                                                                              \
+    hipLaunchKernelGGL((quantize_held_kernel<T, KK, kHeldUnits<T>>), dim3(kHeldGrid), dim3(kHeldBlock), 0, s, x, payload, \
+                       header, mail, p.N, p.held_units, p.held_first, p.held_lds, payload_bytes, polls);                \
     break;
   switch (d.bits) {
     ACCEPT_HELD(2) ACCEPT_HELD(3) ACCEPT_HELD(4) ACCEPT_HELD(5) ACCEPT_HELD(6) ACCEPT_HELD(7) ACCEPT_HELD(8)
     default: return hipErrorInvalidValue;
   }
 #undef ACCEPT_HELD
+  if (p.held_two_stages) mark(tm, s);
   return hipGetLastError();
 }
 
