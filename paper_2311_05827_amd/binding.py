@@ -282,11 +282,13 @@ def accept_compress_noalloc(desc, x, alpha_prev, header, payload):
 
 def accept_decompress(desc, header, payload, out=None):
     """Enqueue decompression on the current stream; returns the flat x_hat device tensor."""
-    if out is None:
-        _check_decompress_args("accept_decompress", desc, header, payload)
-        out = torch.empty(desc.n * desc.m, dtype=_DTYPES[desc.out_dtype], device=payload.device)
     st = _native.decompress(desc, header, payload, out) if type(desc) is Desc else -1
+    if type(st) is torch.Tensor:  # made there, in place of the `out` that was not given
+        return st
     if st < 0:
+        if out is None:
+            _check_decompress_args("accept_decompress", desc, header, payload)
+            out = torch.empty(desc.n * desc.m, dtype=_DTYPES[desc.out_dtype], device=payload.device)
         _check_decompress_args("accept_decompress", desc, header, payload)
         _check_out("accept_decompress", desc, out)
         st = lib.accept_decompress(ctypes.byref(desc), _ptr(header), _ptr(payload), _ptr(out), _stream_handle())

@@ -3,8 +3,8 @@
 // type or size, a tensor without storage) returns kNotHere before anything was done: binding.py then takes it,
 // and says what is wrong.
 //
-// A small tensor's call is host time, of which a launch is 3.6 us.  Through ctypes / here, with the program's own
-// lines: decompressing 9.1 / 7.1 us, compressing (two launches) 13.8 / 10.7, both 23 / 17.7.
+// A small tensor's call is host time, nearly all of it the launch: compressing 3.2 us, decompressing 3.1, of which 0.1 are the
+// wrapper's in binding.py.
 #define PY_SSIZE_T_CLEAN
 #include <Python.h>
 
@@ -87,7 +87,7 @@ PyObject* compress(PyObject*, PyObject* const* args, Py_ssize_t nargs) {
   }
 }
 
-// decompress(desc, header, payload, out) -> status or kNotHere
+// decompress(desc, header, payload, out or None) -> status, or where there was no `out` the tensor made for it, or kNotHere
 PyObject* decompress(PyObject*, PyObject* const* args, Py_ssize_t nargs) {
   if (nargs != 4) return PyLong_FromLong(kNotHere);
   try {
@@ -95,17 +95,24 @@ PyObject* decompress(PyObject*, PyObject* const* args, Py_ssize_t nargs) {
     const accept_desc* d = dv.get(args[0]);
     size_t hb = 0, pb = 0;
     if (!d || accept_packed_size(d, &hb, &pb) != ACCEPT_OK) return PyLong_FromLong(kNotHere);
-    const at::Tensor *header = plain_tensor(args[1]), *payload = plain_tensor(args[2]), *out = plain_tensor(args[3]);
+    const at::Tensor *header = plain_tensor(args[1]), *payload = plain_tensor(args[2]);
+    const bool make = args[3] == Py_None;
+    const at::Tensor* out = make ? nullptr : plain_tensor(args[3]);
     void* stream = nullptr;
-    if (!fits(header, hb) || !fits(payload, pb) || !fits(out, d->out_dtype, d->n * d->m) || !current_stream(&stream))
+    if (!fits(header, hb) || !fits(payload, pb) || (!make && !fits(out, d->out_dtype, d->n * d->m)) || !current_stream(&stream))
       return PyLong_FromLong(kNotHere);
+    at::Tensor made;
+    if (make) {
+      made = at::empty({d->n * d->m}, payload->options().dtype(d->out_dtype == ACCEPT_BF16 ? at::kBFloat16 : at::kFloat));
+      out = &made;
+    }
     const void *hp = header->data_ptr(), *pp = payload->data_ptr();
     void* op = out->data_ptr();
     accept_status st;
     Py_BEGIN_ALLOW_THREADS
     st = accept_decompress(d, hp, pp, op, stream);
     Py_END_ALLOW_THREADS
-    return PyLong_FromLong(st);
+    return make && st == ACCEPT_OK ? THPVariable_Wrap(made) : PyLong_FromLong(st);
   } catch (const std::exception&) {
     return PyLong_FromLong(kNotHere);
   }

@@ -111,3 +111,21 @@ def test_other_objects_than_a_descriptor_are_refused(A):
         mine = Mine.from_buffer_copy(bytes(d))
         got = [dev_bytes(t) for t in A.accept_compress(mine, x, alpha_prev=alpha, header=header, payload=payload, workspace=ws)]
         assert got == want and dev_bytes(A.accept_decompress(mine, header, payload, out=out)) == values
+
+
+def test_decompress_makes_its_output(A):
+    """Without `out`, the tensor comes from the native call, on the payload's device and of the descriptor's type; what is wrong is
+    refused as with one."""
+    torch = torch_mod()
+    for code, dtype in ((A.F32, torch.float32), (A.BF16, torch.bfloat16)):
+        x = torch.randn(24 * 333, device="cuda").to(dtype)
+        d = A.make_desc(A.UNIFORM, 6, 24, 333, in_dtype=code, out_dtype=code)
+        header, payload = A.accept_compress(d, x)
+        want = A.accept_decompress(d, header, payload, out=torch.empty_like(x))
+        got = A.accept_decompress(d, header, payload)
+        assert got.dtype is dtype and got.device == payload.device and not got.requires_grad
+        assert torch.equal(got.view(torch.uint8), want.view(torch.uint8))
+        with pytest.raises(A.AcceptError):
+            A.accept_decompress(d, header, payload[:-1].clone())
+        with pytest.raises(A.AcceptError):
+            A.accept_decompress(A.make_desc(A.UNIFORM, 1, 24, 333), header, payload)
