@@ -136,6 +136,7 @@ struct MPlan {
   uint32_t wpg;           // wave-items (64 items) per row group
   uint32_t n_wave_items;  // of the stream
   int grid;               // workgroups of the encode kernel = number of partial-sum records
+  bool direct;            // levels are found by comparisons, not through tables
   bool finish;            // the encode kernel also does the finalize kernel's work
   size_t bytes;
 };

@@ -361,6 +361,29 @@ __device__ __forceinline__ void build_value_tables(const float (&alpha)[K], Valu
   __syncthreads();
 }
 
+// M2 by comparing with every threshold, in registers: for few levels, and no table to build before the first value can be looked up.
+// Every wavefront sorts the levels itself.
+template <int K>
+struct DirectTables {
+  static constexpr int P = 1 << K;
+  float tau[P - 1];
+  uint32_t spread[P];
+};
+template <int K>
+__device__ __forceinline__ void build_direct_tables(const float (&alpha)[K], DirectTables<K>& tb) {
+  constexpr int P = 1 << K;
+  float lv_s, tau;
+  uint32_t pat_s, sp = 0;
+  sort_levels<K>(alpha, lv_s, pat_s, tau);
+#pragma unroll
+  for (int bb = 0; bb < K; ++bb) sp |= ((pat_s >> bb) & 1u) << (8 * bb);
+#pragma unroll
+  for (int i = 0; i < P; ++i) {
+    if (i < P - 1) tb.tau[i] = u32_as_f32(uint32_t(__builtin_amdgcn_readlane(int(f32_as_u32(tau)), i)));
+    tb.spread[i] = uint32_t(__builtin_amdgcn_readlane(int(sp), i));
+  }
+}
+
 // Sum of NS per-thread float64 values over the threads of a workgroup, in a fixed order (so the
 // result does not depend on timing): every wavefront adds its 64 lanes with register-to-register
 // lane exchanges, lane 0 parks the NS wave totals in local memory, and thread s < NS adds the
@@ -712,9 +735,29 @@ __device__ __forceinline__ void encode_rows(const ValueTables<K>& tb, const RawR
       acc[c][0] |= (r0 + rr < nrows ? f : 0u) & (0x01010101u << bit);
     }
 }
+// The same by comparisons.
+template <int K, int VEC, int MC, int GR>
+__device__ __forceinline__ void encode_rows(const DirectTables<K>& tb, const RawRow<VEC> (&rows)[8], int r0, int nrows, int,
+                                            uint32_t (&acc)[VEC][1], float (&a32)[K], float& sx32) {
+#pragma unroll
+  for (int rr = 0; rr < GR; ++rr) {
+    float row[VEC];
+    widen_raw<VEC>(rows[r0 + rr], row);
+#pragma unroll
+    for (int c = 0; c < VEC; ++c) {
+      uint32_t sp[1] = {tb.spread[0]};
+#pragma unroll
+      for (int i = 0; i < DirectTables<K>::P - 1; ++i) sp[0] = row[c] > tb.tau[i] ? tb.spread[i + 1] : sp[0];
+      accumulate_elem<K>(row[c], sp, a32, sx32);
+      acc[c][0] = (acc[c][0] << 1) | (r0 + rr < nrows ? sp[0] : 0u);
+    }
+  }
+}
 // What the float32 sums of encode_rows have to be multiplied by.
 template <int K>
 __device__ __forceinline__ constexpr float sum_factor(const EncodeTables<K>&) { return 1.0f; }
+template <int K>
+__device__ __forceinline__ constexpr float sum_factor(const DirectTables<K>&) { return 1.0f; }
 template <int K>
 __device__ __forceinline__ constexpr float sum_factor(const ValueTables<K>&) { return -2.0f; }
 
@@ -818,6 +861,11 @@ __device__ __forceinline__ void skip_rows(const EncodeTables<K>&, uint32_t (&acc
   for (int c = 0; c < VEC; ++c)
 #pragma unroll
     for (int w = 0; w < (K + 3) / 4; ++w) acc[c][w] <<= GR;
+}
+template <int K, int VEC, int GR>
+__device__ __forceinline__ void skip_rows(const DirectTables<K>&, uint32_t (&acc)[VEC][1]) {
+#pragma unroll
+  for (int c = 0; c < VEC; ++c) acc[c][0] <<= GR;
 }
 template <int K, int VEC, int GR>
 __device__ __forceinline__ void skip_rows(const ValueTables<K>&, uint32_t (&)[VEC][1]) {}
@@ -1187,6 +1235,13 @@ __device__ __forceinline__ void finish_in_last_workgroup(const MbqCall& call, co
   if (tid == 0) solve_and_write_header<K>(tot, alpha_prev, call.n_elems, call.beta, call.header);
 }
 
+// DIRECT: levels are found by comparisons (direct_levels below).
+template <int K, bool DIRECT, typename S>
+__device__ __forceinline__ decltype(auto) tables_of(S& shared) {
+  if constexpr (DIRECT) return DirectTables<K>{};
+  else return (shared);
+}
+
 // Which rows a tensor has (a kernel for each kind: what the others need costs 0.3 us): complete row groups only, complete ones
 // and a partial one, fewer than eight rows.
 enum Rows { kRowsComplete, kRowsMixed, kRowsFew };
@@ -1199,16 +1254,17 @@ enum Rows { kRowsComplete, kRowsMixed, kRowsFew };
 // column per thread.  RAGGED: m is not a multiple of VEC, so rows start at any alignment; vectors
 // all the same, and the last m % VEC columns one per thread (15 x 390403 float32, k = 3: this kernel
 // 12.0 us and the decoder 7.2, against 14.3 and 9.0 with single columns throughout).
-template <typename T, int K, int VEC, bool RAGGED, bool FINISH, int ROWS>
+template <typename T, int K, int VEC, bool RAGGED, bool FINISH, int ROWS, bool DIRECT>
 __global__ __launch_bounds__(kEncBlock) void mbq_encode_kernel(const T* __restrict__ x, uint8_t* __restrict__ payload,
                                                                MbqCall call, int64_t n, int64_t m, uint32_t ipg,
                                                                uint32_t wpg, uint32_t n_wave_items, bool wide) {
   constexpr int NPAIR = K * (K - 1) / 2;
-  constexpr bool BY_VALUE = sizeof(T) == 2 && K <= 4;
+  constexpr bool BY_VALUE = sizeof(T) == 2 && K <= 4 && !DIRECT;
   constexpr bool FEW = ROWS == kRowsFew, MIXED = ROWS == kRowsMixed;
-  using Tables = std::conditional_t<BY_VALUE, ValueTables<K>, EncodeTables<K>>;
-  __shared__ Tables tb;
+  using SharedTables = std::conditional_t<DIRECT, char, std::conditional_t<BY_VALUE, ValueTables<K>, EncodeTables<K>>>;
+  __shared__ SharedTables shared_tb;
   __shared__ WaveTotals red;
+  std::conditional_t<DIRECT, DirectTables<K>, SharedTables&> tb = tables_of<K, DIRECT>(shared_tb);
 
   const int tid = threadIdx.x;
   const int lane = tid & (kWave - 1);
@@ -1258,7 +1314,9 @@ __global__ __launch_bounds__(kEncBlock) void mbq_encode_kernel(const T* __restri
     load_few<T, VEC, RAGGED>(x, int(n), m, item_addr(few_first, wpg, ipg, lane), fr);
 
   int maxcnt = 1;
-  if constexpr (BY_VALUE) {
+  if constexpr (DIRECT) {
+    build_direct_tables<K>(alpha, tb);
+  } else if constexpr (BY_VALUE) {
     build_value_tables<K>(alpha, tb);
   } else {
     build_encode_tables<K>(alpha, tb);
@@ -1296,8 +1354,8 @@ __global__ __launch_bounds__(kEncBlock) void mbq_encode_kernel(const T* __restri
     auto row_groups = [&] {
       if (stream && maxcnt == 1) {
         encode_stream<T, K, VEC, RAGGED, 1, MIXED>(tb, x, payload, uint64_t(m), ipg, wpg, q, part, cur, nxt, ca, fr, st);
-      } else if (stream && maxcnt == 2 && K <= 4 && !BY_VALUE) {
-        if constexpr (!BY_VALUE)
+      } else if (stream && maxcnt == 2 && K <= 4 && !BY_VALUE && !DIRECT) {
+        if constexpr (!BY_VALUE && !DIRECT)
           encode_stream<T, K, VEC, RAGGED, 2, MIXED>(tb, x, payload, uint64_t(m), ipg, wpg, q, part, cur, nxt, ca, fr, st);
       } else {
         // several thresholds share a bucket (levels closer than a bucket's width), or a very narrow
@@ -2412,9 +2470,17 @@ MbqCall make_call(const accept_desc& d, const float* alpha_prev, void* header, v
 template <typename T, int K, int VEC, bool RAGGED>
 hipError_t launch_encode(const accept_desc& d, const MPlan& p, const T* x, uint8_t* payload, const MbqCall& call,
                          hipStream_t s) {
-  auto launch_rows = [&](auto finish, auto rows) {
-    hipLaunchKernelGGL((mbq_encode_kernel<T, K, VEC, RAGGED, decltype(finish)::value, decltype(rows)::value>), dim3(p.grid), dim3(kEncBlock), 0, s, x,
-                       payload, call, d.n, d.m, uint32_t(p.wide ? d.m / VEC : 1), p.wpg, p.n_wave_items, p.wide);
+  auto launch_one = [&](auto finish, auto rows, auto direct) {
+    hipLaunchKernelGGL((mbq_encode_kernel<T, K, VEC, RAGGED, decltype(finish)::value, decltype(rows)::value, decltype(direct)::value>),
+                       dim3(p.grid), dim3(kEncBlock), 0, s, x, payload, call, d.n, d.m, uint32_t(p.wide ? d.m / VEC : 1), p.wpg,
+                       p.n_wave_items, p.wide);
+  };
+  auto launch_rows = [&](auto finish, auto rows) {  // (only what direct_levels can ask for is compiled)
+    constexpr bool kNarrow = decltype(finish)::value && decltype(rows)::value != kRowsMixed && !RAGGED;
+    if constexpr (K == 1) launch_one(finish, rows, std::true_type{});
+    else if constexpr (K == 2) p.direct ? launch_one(finish, rows, std::true_type{}) : launch_one(finish, rows, std::false_type{});
+    else if constexpr (K <= 4 && kNarrow) p.direct ? launch_one(finish, rows, std::true_type{}) : launch_one(finish, rows, std::false_type{});
+    else launch_one(finish, rows, std::false_type{});
   };
   auto launch = [&](auto finish) {
     if (d.n < 8) launch_rows(finish, std::integral_constant<int, kRowsFew>{});
@@ -2602,6 +2668,19 @@ hipError_t launch_init_pass(int j, const T* x, int64_t N, const InitCall& c, int
 
 }  // namespace
 
+// Whether levels are found by comparing with every threshold, 2^k - 1 of them, instead of through tables that have to be built first
+// (1.1 us; bfloat16's more).  Tables / comparisons (whole call, us): k = 1: 64 x 802816 float32 36.8 / 36.3, bfloat16 22.4 / 22.3, 15 x 20001
+// 6.2 / 5.8; k = 2, float32: 4 x 65536 6.6 / 5.8, 64 x 32768 8.45 / 7.9, 15 x 390403 11.7 / 11.2, 64 x 400000 22.45 / 22.45, 64 x 802816
+// 38.6 / 39.0; bfloat16: 4 x 65536 6.3 / 6.0, 64 x 16384 7.9 / 8.3, 64 x 400000 14.9 / 16.7; k = 3, float32: 64 x 8192 8.9 / 9.2, and
+// bfloat16 9.5 / 11.7; but too narrow for wave-items, a column or less for a thread: 128 x 160, k = 2 6.8 / 5.7, k = 3
+// 8.4 / 7.4, k = 4 9.8 / 9.05.
+bool direct_levels(const accept_desc& d, const MPlan& p) {
+  if (d.bits == 1) return true;
+  if (d.bits <= 4 && p.finish && !p.wide) return true;
+  if (d.bits != 2) return false;
+  return d.in_dtype == ACCEPT_BF16 ? d.n < 8 && p.finish : double(d.n) * double(d.m) < kThroughValues;
+}
+
 MPlan make_mplan(const accept_desc& d) {
   MPlan p{};
   p.vec = vec_for(d.in_dtype, d.n, d.m, d.bits, true);
@@ -2640,6 +2719,7 @@ MPlan make_mplan(const accept_desc& d) {
     p.grid = int(blocks < kEncodeGridMax ? blocks : kEncodeGridMax);
   }
   p.finish = d.layout == ACCEPT_LAYOUT_PACKED && d.bits <= 4 && p.grid <= kFinishGridMax;
+  p.direct = direct_levels(d, p);
   // control block, then room for kMaxRecords records of the widest kind (k = 8)
   const size_t bytes = kCtrlBytes + size_t(nstat_of(8)) * kMaxRecords * sizeof(double);
   p.bytes = (bytes + 255) / 256 * 256;

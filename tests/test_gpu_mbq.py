@@ -508,3 +508,21 @@ def test_batch0_held_values_that_are_not_finite(A, bad, bf16):
     gh, ohf = np.frombuffer(dev_bytes(header), dtype="<f4"), np.frombuffer(oh, dtype="<f4")
     assert np.array_equal(np.isnan(gh), np.isnan(ohf)) and np.array_equal(np.isinf(gh), np.isinf(ohf)), (gh, ohf)
     assert first_mismatch(dev_bytes(payload), op.tobytes()) is None
+
+
+@pytest.mark.parametrize("n,m,k,bf16", [
+    (64, 2048, 1, False), (64, 2048, 1, True), (64, 2048, 2, False),   # by comparisons
+    (7, 4096, 2, True), (8, 4096, 2, True),                            # by comparisons; through a table
+    (24, 255, 3, False), (24, 256, 3, False), (24, 511, 4, True),      # too narrow for wave-items; wide; too narrow
+    (3, 100, 4, False), (520, 63, 4, False), (524281, 3, 3, False),    # few rows; 64 workgroups of single columns; more than 64
+])
+def test_levels_by_comparison_and_through_tables(A, n, m, k, bf16):
+    """Values on the thresholds, next to them, zeros of both signs and denormals; coefficients apart, equal, and one that is zero."""
+    for alpha in ([1.0, 0.5, 0.25, 0.125], [0.5, 0.5, 0.5, 0.5], [0.75, 0.0, 0.25, 0.125]):
+        alpha = np.array(alpha[:k], np.float32)
+        _, _, tau = orc.mbq_levels(alpha)
+        near = np.concatenate([tau, np.nextafter(tau, np.float32(9)), np.nextafter(tau, np.float32(-9)),
+                               np.array([0.0, -0.0, 1e-45, -1e-45], np.float32)]).astype(np.float32)
+        x = si.make_shape("relu_normal", (n, m), 9700 + k)
+        x.reshape(-1)[: 4 * near.size] = np.tile(near, 4)[: x.size]  # (short tensors: as many as there is room for)
+        run_case(A, x, k, n, m, alpha_prev=alpha, in_bf16=bf16, out_bf16=bf16, tag="levels")
