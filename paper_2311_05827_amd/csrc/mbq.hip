@@ -1060,9 +1060,9 @@ __device__ __forceinline__ void solve_and_write_header(const double* tot, const 
 #pragma unroll
   for (int col = 0; col < K; ++col) {
     // bring the largest |entry| of the column to the diagonal (compare-and-swap keeps the
-    // indices static, so the system stays in registers)
+    // indices static, so the system stays in registers); in the first column it is there, n_elems
 #pragma unroll
-    for (int r = col + 1; r < K; ++r) {
+    for (int r = col + 1; r < K && col > 0; ++r) {
       if (fabs(G[r][col]) > fabs(G[col][col])) {
 #pragma unroll
         for (int c = 0; c < K; ++c) { const double tmp = G[col][c]; G[col][c] = G[r][c]; G[r][c] = tmp; }
@@ -1111,10 +1111,39 @@ struct MbqCall {
 };
 constexpr int kDoneCounter = 2;  // word of the counters (between two work counters) that counts off the workgroups
 
+// The sums of N values (a power of two) over the 16 lanes of a row, in a fixed order: in every step a lane gives its partner one half of
+// what it has left and takes the other half of the partner's, so that N - 1 additions and exchanges do, instead of 4 N.
+// On return a lane has the sum number row_sum_index(lane).
+template <int N, int CTRL>
+__device__ __forceinline__ void row_sum_step(double* v, bool upper) {
+  if constexpr (N > 1) {
+#pragma unroll
+    for (int i = 0; i < N / 2; ++i) {
+      const double keep = upper ? v[N / 2 + i] : v[i], give = upper ? v[i] : v[N / 2 + i];
+      v[i] = keep + dpp_f64<CTRL>(give);
+    }
+  } else {
+    v[0] += dpp_f64<CTRL>(v[0]);
+  }
+}
+constexpr int kDppQuadReverse = 0x1B;  // quad_perm [3,2,1,0]
+template <int N>
+__device__ __forceinline__ double row_sums(double (&v)[N], int lane) {
+  row_sum_step<N, kDppRowMirror>(v, (lane & 8) != 0);
+  row_sum_step<(N > 1 ? N / 2 : 1), kDppRowHalfMirror>(v, (lane & 4) != 0);
+  row_sum_step<(N > 2 ? N / 4 : 1), kDppQuadReverse>(v, (lane & 2) != 0);
+  row_sum_step<(N > 4 ? N / 8 : 1), kDppQuadSwap1>(v, (lane & 1) != 0);
+  return v[0];
+}
+template <int N>
+__device__ __forceinline__ int row_sum_index(int lane) {
+  return (lane & 15) * N / 16;
+}
+
 // End of an encode kernel (M4): the workgroup adds up its threads' statistics in a fixed order
-// and stores one record.  The counts are added as integers: 8 instructions per statistic and
-// wavefront instead of 30 (a thread's counts stay below 2^28: a thread sees a few parts in 2^17 of
-// the tensor), which at k = 4 are 10 of the 15.
+// and stores one record.  (Up to 16 statistics, k <= 4; the wavefronts' sums one statistic after the other took
+// 30 instructions each.  Whole call before / now, us: k = 4, 64 x 802816 float32 42.5 / 41.5, bfloat16 29.2 / 28.4, 32 x 401408 16.7 / 15.9,
+// 64 x 8192 9.85 / 8.85, 128 x 160 8.6 / 7.4; k = 2, 4 x 65536 5.7 / 5.5.)
 // FINISH: past the second-level cache, for a workgroup of another die that reads it in this kernel.
 template <int K, bool FINISH = false>
 __device__ __forceinline__ void store_record(const EncodeStats<K>& st, const MbqCall& call, WaveTotals& buf) {
@@ -1122,24 +1151,54 @@ __device__ __forceinline__ void store_record(const EncodeStats<K>& st, const Mbq
   constexpr int NSTAT = nstat_of(K);
   const int tid = threadIdx.x, wave = tid / kWave, lane = tid & (kWave - 1);
   const int nwaves = (blockDim.x + kWave - 1) / kWave;
-  double* mine = buf.v[wave];
+  double total = 0.0;
+  if constexpr (NSTAT <= 16) {
+    constexpr int N = NSTAT <= 4 ? 4 : NSTAT <= 8 ? 8 : 16;
+    static_assert(sizeof(buf) >= kMaxWaves * (kWave / 16) / 2 * 16 * sizeof(double), "rows of half of the most wavefronts");
+    static_assert(kEncWaves <= kMaxWaves / 2 && kBlock / kWave <= kMaxWaves / 2, "wavefronts of the kernels that store records");
+    double v[N];
 #pragma unroll
-  for (int p = 0; p < K; ++p) {
-    const double h = wave_sum(st.H[p]);
-    const double c = double(wave_sum(st.cnt[p]));
-    if (lane == 0) { mine[p] = h; mine[K + 1 + p] = c; }
-  }
-  const double sx = wave_sum(st.Sx);
-  if (lane == 0) mine[K] = sx;
+    for (int i = 0; i < N; ++i) v[i] = 0.0;
 #pragma unroll
-  for (int i = 0; i < NPAIR; ++i) {
-    const double d = double(wave_sum(st.dis[i]));
-    if (lane == 0) mine[2 * K + 1 + i] = d;
+    for (int p = 0; p < K; ++p) {
+      v[p] = st.H[p];
+      v[K + 1 + p] = double(st.cnt[p]);
+    }
+    v[K] = st.Sx;
+#pragma unroll
+    for (int i = 0; i < NPAIR; ++i) v[2 * K + 1 + i] = double(st.dis[i]);
+    double* const rows = &buf.v[0][0];
+    rows[(tid / 16) * N + row_sum_index<N>(lane)] = row_sums<N>(v, lane);  // (N < 16: several lanes store the same)
+    __syncthreads();
+    if (tid < NSTAT) {
+      double part[4] = {0.0, 0.0, 0.0, 0.0};
+      for (int j = 0; j < nwaves * (kWave / 16); j += 4)
+#pragma unroll
+        for (int u = 0; u < 4; ++u) part[u] += rows[(j + u) * N + tid];
+      total = (part[0] + part[1]) + (part[2] + part[3]);
+    }
+  } else {
+    double* mine = buf.v[wave];
+#pragma unroll
+    for (int p = 0; p < K; ++p) {
+      const double h = wave_sum(st.H[p]);
+      const double c = double(wave_sum(st.cnt[p]));
+      if (lane == 0) { mine[p] = h; mine[K + 1 + p] = c; }
+    }
+    const double sx = wave_sum(st.Sx);
+    if (lane == 0) mine[K] = sx;
+#pragma unroll
+    for (int i = 0; i < NPAIR; ++i) {
+      const double d = double(wave_sum(st.dis[i]));
+      if (lane == 0) mine[2 * K + 1 + i] = d;
+    }
+    __syncthreads();
+    if (tid < NSTAT) {
+      total = buf.v[0][tid];
+      for (int w = 1; w < nwaves; ++w) total += buf.v[w][tid];
+    }
   }
-  __syncthreads();
   if (tid < NSTAT) {
-    double total = buf.v[0][tid];
-    for (int w = 1; w < nwaves; ++w) total += buf.v[w][tid];
     double* const rec = call.records + int64_t(tid) * gridDim.x + blockIdx.x;
     if constexpr (FINISH) __hip_atomic_store(rec, total, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     else *rec = total;
@@ -1226,9 +1285,20 @@ __device__ __forceinline__ void finish_in_last_workgroup(const MbqCall& call, co
   const int nrec = int(gridDim.x);
   if (!last_workgroup(call.counters)) return;
   double* tot = buf.v[0];
-  for (int s = wave; s < NSTAT; s += kEncWaves) {
-    const double a = sum_records<true>(call.records + int64_t(s) * nrec, nrec, lane);
-    if (lane == 0) tot[s] = a;
+  static_assert(kFinishGridMax <= kWave, "a record per lane");
+  constexpr int EACH = (NSTAT + kEncWaves - 1) / kEncWaves;  // statistics of a wavefront, asked for together
+  double v[EACH];
+#pragma unroll
+  for (int i = 0; i < EACH; ++i) {
+    const int s = wave + i * kEncWaves;
+    v[i] = s < NSTAT && lane < nrec
+               ? __hip_atomic_load(call.records + int64_t(s) * nrec + lane, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0.0;
+  }
+#pragma unroll
+  for (int i = 0; i < EACH; ++i) {
+    const int s = wave + i * kEncWaves;
+    const double a = wave_sum(v[i]);
+    if (s < NSTAT && lane == 0) tot[s] = a;
   }
   clear_work_counters(call.counters);
   __syncthreads();
