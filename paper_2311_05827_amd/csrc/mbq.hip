@@ -1140,6 +1140,16 @@ __device__ __forceinline__ int row_sum_index(int lane) {
   return (lane & 15) * N / 16;
 }
 
+// Sum number i over the rows of nwaves wavefronts, which lie behind each other.
+template <int N>
+__device__ __forceinline__ double sum_of_rows(const double* rows, int i, int nwaves) {
+  double part[4] = {0.0, 0.0, 0.0, 0.0};
+  for (int j = 0; j < nwaves * (kWave / 16); j += 4)
+#pragma unroll
+    for (int u = 0; u < 4; ++u) part[u] += rows[(j + u) * N + i];
+  return (part[0] + part[1]) + (part[2] + part[3]);
+}
+
 // End of an encode kernel (M4): the workgroup adds up its threads' statistics in a fixed order
 // and stores one record.  (Up to 16 statistics, k <= 4; the wavefronts' sums one statistic after the other took
 // 30 instructions each.  Whole call before / now, us: k = 4, 64 x 802816 float32 42.5 / 41.5, bfloat16 29.2 / 28.4, 32 x 401408 16.7 / 15.9,
@@ -1170,13 +1180,7 @@ __device__ __forceinline__ void store_record(const EncodeStats<K>& st, const Mbq
     double* const rows = &buf.v[0][0];
     rows[(tid / 16) * N + row_sum_index<N>(lane)] = row_sums<N>(v, lane);  // (N < 16: several lanes store the same)
     __syncthreads();
-    if (tid < NSTAT) {
-      double part[4] = {0.0, 0.0, 0.0, 0.0};
-      for (int j = 0; j < nwaves * (kWave / 16); j += 4)
-#pragma unroll
-        for (int u = 0; u < 4; ++u) part[u] += rows[(j + u) * N + tid];
-      total = (part[0] + part[1]) + (part[2] + part[3]);
-    }
+    if (tid < NSTAT) total = sum_of_rows<N>(rows, tid, nwaves);
   } else {
     double* mine = buf.v[wave];
 #pragma unroll
@@ -2199,19 +2203,14 @@ __global__ __launch_bounds__(kFirstBlock, 2) void mbq_first_kernel(const T* __re
       }
     }
   }
-  {
-    const double sa = wave_sum(sum_abs), sx = wave_sum(sum_x);
-    if (lane == 0) { red.v[wave][0] = sa; red.v[wave][1] = sx; }
+  double v[8] = {sum_abs, sum_x};
 #pragma unroll
-    for (int p = 0; p < K; ++p) {
-      const double c = double(wave_sum(cnt[p]));
-      if (lane == 0) red.v[wave][2 + p] = c;
-    }
-  }
+  for (int p = 0; p < K; ++p) v[2 + p] = double(cnt[p]);
+  double* const rows = &red.v[0][0];
+  rows[(tid / 16) * 8 + row_sum_index<8>(lane)] = row_sums<8>(v, lane);
   __syncthreads();
   if (tid < K + 2) {
-    double total = red.v[0][tid];
-    for (int w = 1; w < kFirstWaves; ++w) total += red.v[w][tid];
+    const double total = sum_of_rows<8>(rows, tid, kFirstWaves);
     double* const rec = records + int64_t(tid) * gridDim.x + blockIdx.x;
     __hip_atomic_store(rec, total, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   }
@@ -2241,7 +2240,8 @@ __global__ __launch_bounds__(kFirstBlock, 2) void mbq_first_kernel(const T* __re
 // k kernels and their reads / this (whole call, us): 32 x 401408, k = 2, 3, 4 27.7 / 19.0, 39.2 / 25.0, 50.6 / 31.6, bfloat16 21.3 / 17.8,
 // 30.8 / 25.7, 40.8 / 34.0; 64 x 40000, k = 3 17.6 / 12.1; 64 x 20480, k = 2 10.1 / 7.9; 3 x 800008 bfloat16 and the like as well.
 // Of the 25 us at k = 3 the read takes 10 with the launch, an exchange about 2, a pass of float64 instructions 2 to 4.5 at two
-// wavefronts per SIMD, the header's kernel 4.
+// wavefronts per SIMD, the header's kernel 4.  Beside other work on another stream, kernels / this (us a call, 32 x 401408, k = 3):
+// matrix products 294 / 135, small kernels 35 / 23, 512 MB copies without a pause 36 / 42.
 template <typename T, int K, int SLOTS>
 __global__ __launch_bounds__(kFirstBlock, 2) void mbq_first_held_kernel(const T* __restrict__ x, float* __restrict__ header,
                                                                         uint8_t* __restrict__ payload, uint32_t* ctrl,
@@ -2428,19 +2428,14 @@ __global__ __launch_bounds__(kFirstBlock, 2) void mbq_first_held_kernel(const T*
       store_dwords<NDW>(reinterpret_cast<uint32_t*>(payload + (int64_t(p.g) * m + int64_t(p.jv) * VEC) * K), out);
     }
   }
-  {
-    const double sa = wave_sum(sum_abs), sx = wave_sum(sum_x);
-    if (lane == 0) { red.v[wave][0] = sa; red.v[wave][1] = sx; }
+  double v[8] = {sum_abs, sum_x};
 #pragma unroll
-    for (int p = 0; p < K; ++p) {
-      const double c = double(wave_sum(cnt[p]));
-      if (lane == 0) red.v[wave][2 + p] = c;
-    }
-  }
+  for (int p = 0; p < K; ++p) v[2 + p] = double(cnt[p]);
+  double* const rows = &red.v[0][0];
+  rows[(tid / 16) * 8 + row_sum_index<8>(lane)] = row_sums<8>(v, lane);
   __syncthreads();
   if (tid < K + 2) {
-    double total = red.v[0][tid];
-    for (int w = 1; w < kFirstWaves; ++w) total += red.v[w][tid];
+    const double total = sum_of_rows<8>(rows, tid, kFirstWaves);
     records[int64_t(tid) * gridDim.x + blockIdx.x] = total;
   }
   count_exchanges(mail, calls, uint32_t(K - 1));
