@@ -400,6 +400,19 @@ __device__ __forceinline__ uint64_t wave_sum(uint32_t v) {
 constexpr uint64_t kRandStep = 0x9E3779B97F4A7C15ull;
 __device__ __forceinline__ uint64_t rand_state(uint64_t seed, uint64_t idx) { return seed + (idx + 1ull) * kRandStep; }
 
+// The low word of a * b + c in one instruction, v_mad_u64_u32, whose addend is a register pair: what its high word holds does
+// not matter.  (The compiler makes a multiplication and an addition of it, as the high word would be 0 to it.  Stochastic
+// rounding, whole call, two instructions / one, us: 64 x 802816 k = 4 float32 72.3 / 71.6, k = 8 bfloat16 61.9 / 60.4, 64 x 262144 29.7 /
+// 29.1, 128 x 160 4.61 / 4.56.)
+__device__ __forceinline__ uint32_t mad_low(uint32_t a, uint32_t b, uint32_t c) {
+  typedef uint32_t v2u_t __attribute__((ext_vector_type(2)));
+  uint32_t any;
+  asm("" : "=v"(any) : "v"(c));
+  uint64_t sum, carry;
+  asm("v_mad_u64_u32 %0, %1, %2, %3, %4" : "=v"(sum), "=s"(carry) : "v"(a), "s"(b), "v"(__builtin_bit_cast(uint64_t, v2u_t{c, any})));
+  return uint32_t(sum);
+}
+
 // u * 2^32 as a float32 (exact: 24 significant bits).  Written on 32-bit halves: the output
 // function's last step z ^ (z >> 31) leaves the top 31 bits as they are, so only the high word of
 // the second product is formed, and a 64-bit source would be converted to float by a sequence of
@@ -409,7 +422,7 @@ __device__ __forceinline__ float rand_u32(uint64_t z) {
   z ^= z >> 27;
   constexpr uint64_t C2 = 0x94D049BB133111EBull;
   const uint32_t lo = uint32_t(z), hi = uint32_t(z >> 32);
-  uint32_t h = __umulhi(lo, uint32_t(C2)) + lo * uint32_t(C2 >> 32) + hi * uint32_t(C2);
+  uint32_t h = mad_low(hi, uint32_t(C2), mad_low(lo, uint32_t(C2 >> 32), __umulhi(lo, uint32_t(C2))));
   h &= 0xFFFFFF00u;
   return float(h);
 }

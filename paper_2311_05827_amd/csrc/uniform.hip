@@ -601,7 +601,7 @@ __global__ __launch_bounds__(kBlock) void quantize_pack_kernel(
     __syncthreads();
   }
 
-  // Stochastic rounding is bound by its vector instructions (26 per element, 17 of them the random
+  // Stochastic rounding is bound by its vector instructions (25 per element, 16 of them the random
   // number; every 64-bit or multiply instruction costs about 4.3 cycles like any other on this
   // chip, so the count is what matters): states step by constants from one per thread, and the
   // number is formed on 32-bit halves.  51.4 M float32 values at k = 4: call 80.5 -> 73.2 us
@@ -641,6 +641,7 @@ __global__ __launch_bounds__(kBlock) void quantize_pack_kernel(
       for (int h = 0; h < QPV; ++h)
         pieces[buf][(u * kBlock + tid) * QPV + h] = quantize4<K, STOCH>(&f[4 * h], &r[4 * h], z + uint64_t(4 * h) * kRandStep);
       z += uint64_t(kBlock * VEC) * kRandStep;
+      if constexpr (STOCH) __builtin_amdgcn_sched_barrier(0);  // (interleaved, the vectors' chains take 119 registers, one after the other 73)
     }
     if (next_f < full_tiles) ask_for_tile(tile_of(next_f));
     if (MODE == kRangePerVectorLocal && next_f < full_tiles)
