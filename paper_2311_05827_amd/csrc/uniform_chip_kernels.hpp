@@ -161,8 +161,8 @@ __device__ __forceinline__ void quantize_behind(const T* __restrict__ x, uint32_
 //
 // A workgroup that does not see all the others' maxima in time (see Exchange) no longer uses what it kept, so that
 // its registers serve for the others' parts, and reads its own units again, the way it reads those that it did not keep.
-// (With code of its own for that, seven slots were spilled; a second kernel for such workgroups' units took 3 us of every
-// call: 205 MB, k = 8 / 4 55.3 / 52.5 -> HELDNEW8 / HELDNEW4 us.)
+// (With code of its own for that, seven slots were spilled; a second kernel for such workgroups' units took 2 us of every
+// call above 134 MB: 205 MB, k = 8 / 4 55.7 / 52.8 -> 54.1 / 51.2 us, 154 MB 37.0 -> 35.5.)
 //
 // Beside other work: a workgroup needs a whole compute unit (160 KiB of local memory, all registers), so
 // next to a kernel whose workgroups keep filling the chip it starts late, and the early ones give up.
