@@ -331,8 +331,8 @@ def main():
         "kernels": kernels,
     }
 
-    # the same for whole calls (every kernel the call launches: the held pass and the kernel behind it,
-    # or range + quantize_pack; encode + finalize), from the in-mix timings above
+    # the same for whole calls (every kernel the call launches: the held pass, or range + quantize_pack;
+    # encode + finalize), from the in-mix timings above
     call_roofline = {name: {"bound": "hbm", "achieved": round(v["alg_bytes"] / (v["ms"] * 1e-3) / 1e9, 1),
                             "peak": HBM_PEAK_GBPS, "unit": "GB/s", "frac": v["alg_hbm_frac"]}
                      for name, v in breakdown.items()}

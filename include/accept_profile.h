@@ -17,8 +17,8 @@ extern "C" {
  * kernel the call launches is bracketed by HIP events on the given stream; the call then
  * WAITS for the last event and writes each stage's duration in milliseconds to the host
  * array stage_ms[0..*n_stages) (capacity ACCEPT_MAX_STAGES).  Stage order:
- *   UNIFORM compress: range, [range finalize], quantize+pack; or the one kernel of tensors that stay on the chip, and
- *     behind it, for the largest float32 tensors with one range, the one that does the rest;
+ *   UNIFORM compress: range, [range finalize], quantize+pack; or the one kernel of tensors that stay on the chip, whole or in
+ *     part;
  *   MBQ compress: encode+sums, finalize; small tensors: the encoder alone, which solves itself;
  *   decompress: the one kernel.
  * For benchmarks only; creates and destroys its events on every call.

@@ -271,11 +271,7 @@ const char* accept_stage_name(const accept_desc* desc, int is_decompress, int i)
     static const char* const names[] = {"range", "range_finalize", "quantize_pack"};
     return i < 3 ? names[i] : nullptr;
   }
-  // range and quantizer in one kernel (and see held_two_stages)
-  if (held_runs(plan, units)) {
-    static const char* const names[] = {"quantize_held", "quantize_rest"};
-    return i < (plan.held_two_stages ? 2 : 1) ? names[i] : nullptr;
-  }
+  if (held_runs(plan, units)) return i == 0 ? "quantize_held" : nullptr;
   static const char* const names[] = {"range", "quantize_pack"};
   return i < 2 ? names[i] : nullptr;
 }

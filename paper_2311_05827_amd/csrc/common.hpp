@@ -73,8 +73,6 @@ struct UPlan {
   bool straddling;     // U_GENERIC: segments longer than a vector but not whole vectors
   bool held;           // U_TENSOR: the range pass keeps the end of the tensor on the chip and quantizes it itself
   int64_t held_units;  // held: whole units (see kUnitElems) of the tensor
-  bool held_two_stages;  // held: a second stage is named and timed, which is empty (it was a kernel for what workgroups
-                         // that gave up had left; programs that read the list of stages find the same one)
   int held_lds;        // held: units per workgroup that stay in local memory (the others in registers)
   int64_t held_first;  // held: units [held_first, held_units) are kept, the others are read again
   uint32_t whole_per;  // U_TENSOR: groups of 32 elements per workgroup of the pass that keeps the tensor in registers; 0: not taken

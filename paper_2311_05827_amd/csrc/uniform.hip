@@ -1064,7 +1064,7 @@ hipError_t compress_typed(const accept_desc& d, const UPlan& p, const T* x, floa
   float* rtab = reinterpret_cast<float*>(reinterpret_cast<char*>(ws) + p.off_rtab);
   mark(tm, s);
   if (held_runs(p, units) || channels_run(p, units) || whole_runs(p, units)) {
-    const hipError_t e = p.held             ? launch_held<T>(d, p, x, header, payload, mail, held_polls, s, tm)
+    const hipError_t e = p.held             ? launch_held<T>(d, p, x, header, payload, mail, held_polls, s)
                          : p.whole_per != 0 ? launch_whole<T>(d, p, x, header, payload, mail, held_polls, s)
                                             : launch_channels<T>(d, p, x, header, payload, mail, held_polls, s);
     if (e == hipSuccess) mark(tm, s);
@@ -1276,7 +1276,6 @@ UPlan make_uplan(const accept_desc& d) {
       const int64_t keep_lds = p.vec == 8 ? kHeldLdsUnits<bf16_t> : kHeldLdsUnits<float>;
       p.held_units = p.N / kUnitElems;
       const int64_t rounds = (p.held_units + kHeldGrid - 1) / kHeldGrid;
-      p.held_two_stages = p.vec == 4 && rounds > 8;
       p.held_lds = rounds > keep ? int(keep_lds) : 0;
       p.held_first = rounds > keep + keep_lds ? (rounds - keep - keep_lds) * kHeldGrid : 0;
     }

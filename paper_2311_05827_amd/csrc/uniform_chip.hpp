@@ -76,7 +76,7 @@ inline uint32_t channel_groups(int64_t n, int64_t C, int64_t seg_len) {
 
 template <typename T>
 hipError_t launch_held(const accept_desc& d, const UPlan& p, const T* x, float* header, uint32_t* payload,
-                       ChipMail* mail, int polls, hipStream_t s, StageTimer* tm);
+                       ChipMail* mail, int polls, hipStream_t s);
 template <typename T>
 hipError_t launch_channels(const accept_desc& d, const UPlan& p, const T* x, float* header, uint32_t* payload,
                            ChipMail* mail, int polls, hipStream_t s);

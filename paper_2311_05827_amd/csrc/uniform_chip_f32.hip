@@ -3,8 +3,7 @@
 
 namespace accept {
 
-template hipError_t launch_held<float>(const accept_desc&, const UPlan&, const float*, float*, uint32_t*, ChipMail*, int, hipStream_t,
-                                        StageTimer*);
+template hipError_t launch_held<float>(const accept_desc&, const UPlan&, const float*, float*, uint32_t*, ChipMail*, int, hipStream_t);
 template hipError_t launch_channels<float>(const accept_desc&, const UPlan&, const float*, float*, uint32_t*, ChipMail*, int, hipStream_t);
 template hipError_t launch_whole<float>(const accept_desc&, const UPlan&, const float*, float*, uint32_t*, ChipMail*, int, hipStream_t);
 

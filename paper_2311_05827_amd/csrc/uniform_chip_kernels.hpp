@@ -840,7 +840,7 @@ hipError_t launch_whole(const accept_desc& d, const UPlan& p, const T* x, float*
 
 template <typename T>
 hipError_t launch_held(const accept_desc& d, const UPlan& p, const T* x, float* header, uint32_t* payload,
-                       ChipMail* mail, int polls, hipStream_t s, StageTimer* tm) {
+                       ChipMail* mail, int polls, hipStream_t s) {
   const int64_t payload_bytes = (p.N * d.bits + 7) / 8;
 #define ACCEPT_HELD(KK)                                                                                                 \
   case KK:                                                                                                              \
@@ -852,7 +852,6 @@ hipError_t launch_held(const accept_desc& d, const UPlan& p, const T* x, float* 
     default: return hipErrorInvalidValue;
   }
 #undef ACCEPT_HELD
-  if (p.held_two_stages) mark(tm, s);
   return hipGetLastError();
 }
 

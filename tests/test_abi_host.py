@@ -126,7 +126,7 @@ def test_invalid_arguments_are_rejected_before_any_launch(A):
     assert lib.accept_mbq_init(ctypes.byref(good), V(0x1000), V(0x2000), V(0x4000), None) == INVALID
     assert A.accept_stage_name(good, 0, 0) == "range" and A.accept_stage_name(good, 0, 1) == "quantize_pack"
     held = A.make_desc(A.UNIFORM, 8, 64, 802816)
-    assert [A.accept_stage_name(held, 0, i) for i in range(3)] == ["quantize_held", "quantize_rest", None]
+    assert [A.accept_stage_name(held, 0, i) for i in range(2)] == ["quantize_held", None]  # one kernel, so one stage
     # from 48 MiB of float32 (what is smaller fits in registers) and 72 MiB of bfloat16 on, up to 256 MiB of either
     for code, lo, hi, below in ((A.F32, 12 << 20, 64 << 20, "quantize_whole"), (A.BF16, 36 << 20, 128 << 20, "range")):
         for n, name in ((lo - 1, below), (lo, "quantize_held"), (hi, "quantize_held"), (hi + 1, "range")):

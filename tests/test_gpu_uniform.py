@@ -393,7 +393,7 @@ def test_held_pass_of_more_than_fits_that_gives_up(A, k, N, bf16, largest_behind
     torch = torch_mod()
     print("case", k, N, bf16, flush=True)
     d = A.make_desc(A.UNIFORM, k, 1, N, in_dtype=A.BF16 if bf16 else A.F32)
-    assert [A.accept_stage_name(d, 0, i) for i in range(2)] == ["quantize_held", None if bf16 else "quantize_rest"]
+    assert [A.accept_stage_name(d, 0, i) for i in range(2)] == ["quantize_held", None]
     header, payload, ws = A.alloc_outputs(d, "cuda")
     for turn in range(2):
         x = si.make_shape("grad", (1, N), 225 + turn)
