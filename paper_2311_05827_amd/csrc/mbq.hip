@@ -2551,8 +2551,9 @@ hipError_t launch_encode(const accept_desc& d, const MPlan& p, const T* x, uint8
   };
   auto launch = [&](auto finish) {
     if (d.n < 8) launch_rows(finish, std::integral_constant<int, kRowsFew>{});
-    else if (p.mixed) launch_rows(finish, std::integral_constant<int, kRowsMixed>{});
-    else launch_rows(finish, std::integral_constant<int, kRowsComplete>{});
+    else if (p.mixed) {
+      if constexpr (VEC > 1 || K <= 4) launch_rows(finish, std::integral_constant<int, kRowsMixed>{});
+    } else launch_rows(finish, std::integral_constant<int, kRowsComplete>{});
   };
   if constexpr (K <= 4) {
     if (p.finish) {
@@ -2763,8 +2764,9 @@ MPlan make_mplan(const accept_desc& d) {
   // groups many: which rows a wave-item has costs scalar instructions for every one of them, a few percent of
   // that short work.  In the queue / beside it, float32, us: 15 x 20001, k = 2 7.2 / 7.6, 300 x 10001, k = 3 10.8 / 10.6, 8315 x
   // 1457, k = 2 20.2 / 19.6; vectors: 15 x 390403, k = 3 13.5 / 15.2, 23 x 173913 10.9 / 14.1, 101 x 500000, k = 4 42.6 / 43.9.
+  // (More than four bits, single columns: 84 x 117318 bfloat16, k = 6 45.9 / 44.3.)
   constexpr int64_t kMixedColumnGroups = 16;
-  p.mixed = d.n % 8 != 0 && full_groups > 0 && (p.vec > 1 || full_groups <= kMixedColumnGroups);
+  p.mixed = d.n % 8 != 0 && full_groups > 0 && (p.vec > 1 || (d.bits <= 4 && full_groups <= kMixedColumnGroups));
   const int64_t wave_items = (p.mixed ? p.G : full_groups) * wpg;
   p.wide = ipg >= kWave && wave_items < (int64_t(1) << 31) && d.m * 8 < (int64_t(1) << 32);
   p.stream = full_groups > 0 && p.wide;
@@ -2780,7 +2782,11 @@ MPlan make_mplan(const accept_desc& d) {
     // k = 2; 4): 132 wave-items 6.9 / 6.5; 9.3 / 9.2, 256 6.9 / 6.7; 9.4 / 9.5, and with a line beyond, 260 6.9 / 6.8; 9.5 / 9.5,
     // 320 6.9 / 6.9; 9.4 / 9.7, 400 7.0 / 7.2; 9.4 / 9.9, 512 7.0 / 7.5; 9.4 / 10.2.
     const bool few = full_groups == 0 && wpg <= 4 * kFinishGridMax;
-    const int64_t tail_blocks = d.n % 8 == 0 || (p.mixed && p.vec > 1) ? 0 : !p.wide ? (d.m + kEncBlock - 1) / kEncBlock : few ? (wpg + 3) / 4 : wpg;
+    // Where the partial row group is in the queue it has been counted; but of more than four bits several thresholds mostly
+    // share a bucket, columns then go one per thread, and the grid is at least a row group's wave-items.  As many workgroups as the
+    // queue needs / as this, k = 6, us: 9 x 100000 float32 20.5 / 17.1, bfloat16 30.3 / 17.8; 31 x 40000 20.7 / 17.1, 32.6 / 23.0.
+    const bool counted = p.mixed && p.vec > 1 && d.bits <= 4;
+    const int64_t tail_blocks = d.n % 8 == 0 || counted ? 0 : !p.wide ? (d.m + kEncBlock - 1) / kEncBlock : few ? (wpg + 3) / 4 : wpg;
     if (blocks < tail_blocks) blocks = tail_blocks;
     if (blocks < 1) blocks = 1;
     p.grid = int(blocks < kEncodeGridMax ? blocks : kEncodeGridMax);

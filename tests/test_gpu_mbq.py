@@ -432,10 +432,11 @@ def test_shares_of_the_work_queue(A, wave_items, bf16):
 @pytest.mark.parametrize("bf16", [False, True])
 @pytest.mark.parametrize("n,m,k", [(9, 512, 2), (15, 4096, 3), (12, 20000, 4), (14, 1000, 5), (12, 520192, 2), (15, 526336, 3),
                                    (15, 200003, 3), (23, 173913, 4), (9, 393217, 1),
-                                   (9, 1001, 2), (135, 1001, 3), (143, 1001, 3)])
+                                   (9, 1001, 2), (135, 1001, 3), (143, 1001, 3),
+                                   (9, 20008, 6), (9, 1001, 5), (15, 20001, 8)])
 def test_partial_row_group_in_the_queue(A, n, m, k, bf16):
     """The partial row group's wave-items are the last of the work queue: one of them, fewer than wavefronts, more; rows at any
-    alignment; single columns, in the queue up to 16 complete groups and beside it above.  Levels that lie close (two thresholds
+    alignment; single columns, in the queue up to 16 complete groups (k <= 4) and beside it above.  Levels that lie close (two thresholds
     in a bucket) as well."""
     x = si.make_shape("relu_lognormal", (n, m), 9900 + n + m)
     run_case(A, x, k, n, m, in_bf16=bf16, out_bf16=bf16, tag="partial")
