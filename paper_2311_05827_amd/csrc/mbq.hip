@@ -2544,8 +2544,8 @@ hipError_t launch_encode(const accept_desc& d, const MPlan& p, const T* x, uint8
   };
   auto launch_rows = [&](auto finish, auto rows) {  // (only what direct_levels can ask for is compiled)
     constexpr bool kNarrow = decltype(finish)::value && decltype(rows)::value != kRowsMixed && !RAGGED;
-    if constexpr (K == 1) launch_one(finish, rows, std::true_type{});
-    else if constexpr (K == 2) p.direct ? launch_one(finish, rows, std::true_type{}) : launch_one(finish, rows, std::false_type{});
+    if constexpr (K == 1 && (sizeof(T) == 4 || decltype(rows)::value != kRowsComplete || RAGGED)) launch_one(finish, rows, std::true_type{});
+    else if constexpr (K <= 2) p.direct ? launch_one(finish, rows, std::true_type{}) : launch_one(finish, rows, std::false_type{});
     else if constexpr (K <= 4 && kNarrow) p.direct ? launch_one(finish, rows, std::true_type{}) : launch_one(finish, rows, std::false_type{});
     else launch_one(finish, rows, std::false_type{});
   };
@@ -2741,9 +2741,11 @@ hipError_t launch_init_pass(int j, const T* x, int64_t N, const InitCall& c, int
 // 6.2 / 5.8; k = 2, float32: 4 x 65536 6.6 / 5.8, 64 x 32768 8.45 / 7.9, 15 x 390403 11.7 / 11.2, 64 x 400000 22.45 / 22.45, 64 x 802816
 // 38.6 / 39.0; bfloat16: 4 x 65536 6.3 / 6.0, 64 x 16384 7.9 / 8.3, 64 x 400000 14.9 / 16.7; k = 3, float32: 64 x 8192 8.9 / 9.2, and
 // bfloat16 9.5 / 11.7; but too narrow for wave-items, a column or less for a thread: 128 x 160, k = 2 6.8 / 5.7, k = 3
-// 8.4 / 7.4, k = 4 9.8 / 9.05.
+// 8.4 / 7.4, k = 4 9.8 / 9.05.  k = 1, bfloat16, too narrow for wave-items: 3000 x 256 6.45 / 5.95, 6000 x 256 7.4 / 7.2, 12000 x 256
+// 8.3 / 8.6, 25000 x 128 9.1 / 9.75, 100000 x 256 48.7 / 72.4, 100000 x 504 90 / 136: tables beyond two columns for a thread.
 bool direct_levels(const accept_desc& d, const MPlan& p) {
-  if (d.bits == 1) return true;
+  constexpr int64_t kDirectColumns = 2 * int64_t(kEncodeGridMax) * kEncBlock;
+  if (d.bits == 1) return d.in_dtype == ACCEPT_F32 || p.wide || p.G * d.m <= kDirectColumns;
   if (d.bits <= 4 && p.finish && !p.wide) return true;
   if (d.bits != 2) return false;
   return d.in_dtype == ACCEPT_BF16 ? d.n < 8 && p.finish : double(d.n) * double(d.m) < kThroughValues;

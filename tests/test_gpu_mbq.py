@@ -516,6 +516,7 @@ def test_batch0_held_values_that_are_not_finite(A, bad, bf16):
     (7, 4096, 2, True), (8, 4096, 2, True),                            # by comparisons; through a table
     (24, 255, 3, False), (24, 256, 3, False), (24, 511, 4, True),      # too narrow for wave-items; wide; too narrow
     (3, 100, 4, False), (520, 63, 4, False), (524281, 3, 3, False),    # few rows; 64 workgroups of single columns; more than 64
+    (4096, 511, 1, True), (4104, 511, 1, True), (4099, 511, 1, True),  # narrow: two columns for a thread; more, through a table
 ])
 def test_levels_by_comparison_and_through_tables(A, n, m, k, bf16):
     """Values on the thresholds, next to them, zeros of both signs and denormals; coefficients apart, equal, and one that is zero."""
