@@ -401,7 +401,8 @@ __device__ __forceinline__ uint64_t rand_state(uint64_t seed, uint64_t idx) { re
 // The low word of a * b + c in one instruction, v_mad_u64_u32, whose addend is a register pair: what its high word holds does
 // not matter.  (The compiler makes a multiplication and an addition of it, as the high word would be 0 to it.  Stochastic
 // rounding, whole call, two instructions / one, us: 64 x 802816 k = 4 float32 72.3 / 71.6, k = 8 bfloat16 61.9 / 60.4, 64 x 262144 29.7 /
-// 29.1, 128 x 160 4.61 / 4.56.)
+// 29.1, 128 x 160 4.61 / 4.56; element by element, in the code for odd channel geometries, which 64-bit divisions hold up, the compiler's two are
+// better: 192367 x 251 channels-last bfloat16, k = 2 157.6 / 163.4, 131427 x 19 x 7 k = 4 53.9 / 55.3.)
 __device__ __forceinline__ uint32_t mad_low(uint32_t a, uint32_t b, uint32_t c) {
   typedef uint32_t v2u_t __attribute__((ext_vector_type(2)));
   uint32_t any;
@@ -415,12 +416,15 @@ __device__ __forceinline__ uint32_t mad_low(uint32_t a, uint32_t b, uint32_t c) 
 // function's last step z ^ (z >> 31) leaves the top 31 bits as they are, so only the high word of
 // the second product is formed, and a 64-bit source would be converted to float by a sequence of
 // seven instructions where one does.
+template <bool MAD>
 __device__ __forceinline__ float rand_u32(uint64_t z) {
   z = (z ^ (z >> 30)) * 0xBF58476D1CE4E5B9ull;
   z ^= z >> 27;
   constexpr uint64_t C2 = 0x94D049BB133111EBull;
   const uint32_t lo = uint32_t(z), hi = uint32_t(z >> 32);
-  uint32_t h = mad_low(hi, uint32_t(C2), mad_low(lo, uint32_t(C2 >> 32), __umulhi(lo, uint32_t(C2))));
+  uint32_t h;
+  if constexpr (MAD) h = mad_low(hi, uint32_t(C2), mad_low(lo, uint32_t(C2 >> 32), __umulhi(lo, uint32_t(C2))));
+  else h = __umulhi(lo, uint32_t(C2)) + lo * uint32_t(C2 >> 32) + hi * uint32_t(C2);
   h &= 0xFFFFFF00u;
   return float(h);
 }

@@ -876,7 +876,7 @@ __device__ __forceinline__ uint32_t quantize_any(float f, float r, int k, bool s
     const float t = __fadd_rn(v, kRoundMagic + float(k == 8 ? 0 : half));
     return f32_as_u32(t) & mask;
   }
-  return code_of_q(quantize_stochastic(f, r, half, rand_state(seed, uint64_t(idx))), k);
+  return code_of_q(quantize_stochastic<false>(f, r, half, rand_state(seed, uint64_t(idx))), k);
 }
 // Signed value of a code.
 __device__ __forceinline__ int code_to_q(uint32_t code, int k) {

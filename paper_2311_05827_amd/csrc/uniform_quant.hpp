@@ -42,12 +42,13 @@ __device__ __forceinline__ uint32_t quantize_rne(float f, float r) {
 }
 
 // One element, stochastic: floor(v) + (u < v - floor(v)), clamped; the signed value.  z is the
-// element's random state.
+// element's random state.  TILES: an element of a whole tile (see mad_low).
+template <bool TILES>
 __device__ __forceinline__ int quantize_stochastic(float f, float r, int half, uint64_t z) {
   const float v = __fmul_rn(f, r);
   const float fl = floorf(v);
   const float pr = __fsub_rn(v, fl);
-  const int q = int(fl) + (rand_u32(z) < pr * 0x1p32f ? 1 : 0);
+  const int q = int(fl) + (rand_u32<TILES>(z) < pr * 0x1p32f ? 1 : 0);
   return min(max(q, -half), half - 1);
 }
 
@@ -63,7 +64,7 @@ __device__ __forceinline__ uint32_t quantize4(const float* f, const float* r, ui
   for (int e = 3; e >= 0; --e) {
     uint32_t code;
     if constexpr (STOCH)
-      code = uint32_t(quantize_stochastic(f[e], r[e], HALF, z0 + uint64_t(e) * kRandStep));
+      code = uint32_t(quantize_stochastic<true>(f[e], r[e], HALF, z0 + uint64_t(e) * kRandStep));
     else
       code = quantize_rne_raw<K>(f[e], r[e]);
     piece = __builtin_amdgcn_alignbit(code, piece, K);
@@ -141,7 +142,7 @@ __device__ __forceinline__ void quantize_group8(const T* __restrict__ x, uint8_t
     uint64_t code = 0;
     if (i < N) {
       const float f = load_one(x + i), r = r_of(i);
-      code = STOCH ? code_of_q(quantize_stochastic(f, r, 1 << (K - 1), rand_state(seed, uint64_t(i))), K)
+      code = STOCH ? code_of_q(quantize_stochastic<false>(f, r, 1 << (K - 1), rand_state(seed, uint64_t(i))), K)
                    : quantize_rne<K>(f, r);
     }
     acc = (acc << K) | code;
