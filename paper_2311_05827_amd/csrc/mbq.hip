@@ -2689,10 +2689,25 @@ hipError_t first_k(const accept_desc& d, const FirstPlan& f, const T* x, float* 
 }
 
 // Batch 0 with the tensor kept in registers: items per thread of 256 workgroups; 0: not taken.
+//
+// Of fewer than eight rows an item has room for eight all the same, and its last pass goes by compares; kernels for every pass read and
+// work through the rows that there are.  A kernel per pass / this, us, k = 2; 3; 4, float32: one row, 262144 items 10.1 / 9.65; 13.7 / 12.7;
+// 17.8 / 15.8, 393000 10.8 / 11.45; 14.7 / 15.2; 19.3 / 19.2, 520000 11.6 / 13.2; 15.5 / 18.2; 20.4 / 22.2; two rows, 520000 13.6 / 14.4;
+// 18.9 / 20.3; 24.1 / 24.8; from three on this is ahead everywhere (520000 15.9 / 15.4; 21.9 / 22.1; 28.0 / 27.8; seven 28.4 / 25.2; 39.1 /
+// 33.1; 50.3 / 42.0).  bfloat16: one row, 180000 items 10.2 / 9.6; 14.3 / 12.6; 18.5 / 16.1, 524000 13.3 / 16.0; 18.9 / 22.6; 25.0 / 28.7;
+// three, 180000 11.8 / 10.9; 16.9 / 15.1; 22.9 / 19.8, 205000 12.6 / 13.55; 18.0 / 20.0; 23.9 / 26.7; seven, 205000 17.8 / 18.7; 25.7 / 28.5;
+// 34.4 / 38.5.  And just beyond half an item a thread, where one wavefront of five shares its SIMD: five rows, 76000 items 10.8 / 10.6;
+// 15.0 / 14.9; 19.8 / 20.7, seven 11.7 / 11.7; 16.8 / 18.3; 22.5 / 24.9, but 84000 11.9 / 11.4; 17.0 / 16.1; 22.8 / 21.5.
 constexpr int kFirstSlots = 4;
 int first_slots(const accept_desc& d, int vec) {
   const int64_t items = d.m % vec == 0 ? (d.n + 7) / 8 * (d.m / vec) : INT64_MAX;
-  if (d.bits < 2 || d.bits > 4 || vec == 1 || items > int64_t(kFirstSlots) * kHeldGrid * kFirstBlock) return 0;
+  constexpr int64_t kSlot = int64_t(kHeldGrid) * kFirstBlock;
+  int64_t most = kFirstSlots * kSlot;
+  if (d.n < 8) {
+    most = vec == 8 ? kSlot / 2 * 3 : d.n <= 2 ? 2 * kSlot : most;
+    if (vec == 8 && d.n >= 5 && items > kSlot / 2 && items <= kSlot / 8 * 5) return 0;
+  }
+  if (d.bits < 2 || d.bits > 4 || vec == 1 || items > most) return 0;
   return int((items + kHeldGrid * kFirstBlock - 1) / (kHeldGrid * kFirstBlock));
 }
 template <typename T, int K, int SLOTS>

@@ -455,6 +455,9 @@ def test_partial_row_group_in_the_queue(A, n, m, k, bf16):
     (9, 8 * 196608, 3, True),        # four items in some wavefronts
     (8, 4 * 524288, 3, False),       # the largest
     (8, 4 * 524289, 2, False),       # one item more: a kernel for every pass
+    (2, 4 * 262144, 3, False), (2, 4 * 262145, 3, False), (3, 4 * 524288, 2, False),                      # few rows: both sides
+    (1, 8 * 196608, 2, True), (7, 8 * 196609, 3, True),                                                   # of the lines
+    (5, 8 * 65536, 4, True), (5, 8 * 65537, 4, True), (6, 8 * 81920, 2, True), (7, 8 * 81921, 3, True),
 ])
 def test_batch0_held(A, n, m, k, bf16):
     torch = torch_mod()
