@@ -26,7 +26,7 @@ constexpr int kEncWaves = kEncBlock / kWave;
 // 8i .. 8i+7 (under round-robin dispatch one on each of the chip's eight dies) share counter i.
 constexpr int kGroupBlocks = 8;
 // Wave-items a group takes out of every sweep over the tensor (as a shift; the rule is at WorkQueue).
-constexpr uint32_t kGroupSlotsShift = 2, kOneSweepSlotsShift = 6;
+constexpr uint32_t kGroupSlotsShift = 2, kWaveSlotsShift = 6;
 constexpr int kCounterStride = 64;  // uint32 words between two counters (256 bytes: their own cache lines)
 constexpr int kEncodeGridMax = 256;
 constexpr int kPlainGridMax = 768;
@@ -808,7 +808,10 @@ __device__ __forceinline__ void encode_column(const Tables& tb, const T* __restr
 // 42.7 / 42.7 / 43.2, bfloat16 30.8 / 29.4 / 29.3 / 29.3; 32 x 401408 float32, k = 3 16.5 / 15.5 / 15.4 / 15.4.)  A grid smaller
 // than the chip has a wavefront for every wave-item, and its last group may be smaller than the others: there a
 // sweep is all there is, and a group's share is its number of wavefronts (128 x 12544 float32, 98 workgroups, 64 / 4 slots
-// 8.3 / 11.9).
+// 8.3 / 11.9).  So too for wave-items of one and an eighth to one and seven eighths times the wavefronts: nobody has more than two
+// then, however they are shared out, and rows of any alignment pay for neighbours on other compute units (64 / 4 slots, six
+// placements of the buffers each: 8000 x 1457 bfloat16, k = 2 12.5 / 13.6, k = 4 15.1 / 18.2, 3464 x 1457 float32, k = 4 14.4 / 16.8, 600 x
+// 20001 bfloat16, k = 3 12.7 / 13.1, 15 x 390403 float32 11.2 / 11.7; aligned rows 40 x 400000 bfloat16, k = 4 13.7 / 13.8).
 struct WorkQueue {
   uint32_t* counter;  // the group's counter: zero when the kernel starts, put back by the finalize kernel or the last workgroup
   uint32_t shift;     // slots = 1 << shift
@@ -1355,7 +1358,9 @@ __global__ __launch_bounds__(kEncBlock) void mbq_encode_kernel(const T* __restri
                                                                         : uint32_t(kGroupBlocks);
   const uint32_t group_waves = group_blocks * uint32_t(kEncWaves);
   q.counter = call.counters + group * uint32_t(kCounterStride);
-  q.shift = gridDim.x == uint32_t(kEncodeGridMax) ? kGroupSlotsShift : kOneSweepSlotsShift;
+  constexpr uint32_t kWavefronts = uint32_t(kEncodeGridMax) * uint32_t(kEncWaves);
+  const bool two_sweeps = n_wave_items > kWavefronts / 8u * 9u && n_wave_items <= kWavefronts / 8u * 15u;
+  q.shift = gridDim.x == uint32_t(kEncodeGridMax) && !two_sweeps ? kGroupSlotsShift : kWaveSlotsShift;
   const uint32_t slots = 1u << q.shift;
   q.first = group << q.shift;
   q.sweep = groups << q.shift;

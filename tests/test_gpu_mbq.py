@@ -420,10 +420,10 @@ def test_few_rows_and_more_wave_items_than_wavefronts(A, n, m, k, bf16):
 
 
 @pytest.mark.parametrize("bf16", [False, True])
-@pytest.mark.parametrize("wave_items", [2041, 2048, 2049, 2180, 4097])
+@pytest.mark.parametrize("wave_items", [2041, 2048, 2049, 2180, 2304, 2305, 2399, 3840, 3841, 4097])
 def test_shares_of_the_work_queue(A, wave_items, bf16):
-    """256 workgroups, in 32 groups that take four wave-items each out of a sweep of 128: fewer wave-items than wavefronts, as
-    many, and last sweeps that not all groups, or not all of a group, have a part of."""
+    """256 workgroups, in 32 groups that take four wave-items each out of a sweep of 128 (2305 to 3840 wave-items: 64 out of 2048): fewer
+    wave-items than wavefronts, as many, and last sweeps that not all groups, or not all of a group, have a part of."""
     m = wave_items * 64 * (8 if bf16 else 4)
     x = si.make_shape("relu_normal", (8, m), 9800 + wave_items)
     run_case(A, x, 2, 8, m, in_bf16=bf16, out_bf16=bf16, tag="shares")
