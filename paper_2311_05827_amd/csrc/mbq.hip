@@ -1331,7 +1331,8 @@ enum Rows { kRowsComplete, kRowsMixed, kRowsFew };
 // column per thread.  RAGGED: m is not a multiple of VEC, so rows start at any alignment; vectors
 // all the same, and the last m % VEC columns one per thread (15 x 390403 float32, k = 3: this kernel
 // 12.0 us and the decoder 7.2, against 14.3 and 9.0 with single columns throughout).
-template <typename T, int K, int VEC, bool RAGGED, bool FINISH, int ROWS, bool DIRECT>
+// NARROW: too narrow for wave-items, so all columns one per thread, whatever the rows (VEC = 1, kRowsComplete).
+template <typename T, int K, int VEC, bool RAGGED, bool FINISH, int ROWS, bool DIRECT, bool NARROW>
 __global__ __launch_bounds__(kEncBlock) void mbq_encode_kernel(const T* __restrict__ x, uint8_t* __restrict__ payload,
                                                                MbqCall call, int64_t n, int64_t m, uint32_t ipg,
                                                                uint32_t wpg, uint32_t n_wave_items, bool wide) {
@@ -1343,6 +1344,10 @@ __global__ __launch_bounds__(kEncBlock) void mbq_encode_kernel(const T* __restri
   __shared__ WaveTotals red;
   std::conditional_t<DIRECT, DirectTables<K>, SharedTables&> tb = tables_of<K, DIRECT>(shared_tb);
 
+  if constexpr (NARROW) {
+    n_wave_items = 0;
+    wide = false;
+  }
   const int tid = threadIdx.x;
   const int lane = tid & (kWave - 1);
   float alpha[K];  // asked for first: nothing below needs them before the tables are built
@@ -2542,17 +2547,29 @@ MbqCall make_call(const accept_desc& d, const float* alpha_prev, void* header, v
 template <typename T, int K, int VEC, bool RAGGED>
 hipError_t launch_encode(const accept_desc& d, const MPlan& p, const T* x, uint8_t* payload, const MbqCall& call,
                          hipStream_t s) {
+  // (only what direct_levels can ask for is compiled)
+  constexpr bool F32 = sizeof(T) == 4;
+  auto launch_narrow = [&](auto finish, auto direct) {
+    hipLaunchKernelGGL((mbq_encode_kernel<T, K, 1, false, decltype(finish)::value, kRowsComplete, decltype(direct)::value, true>), dim3(p.grid),
+                       dim3(kEncBlock), 0, s, x, payload, call, d.n, d.m, 1u, 1u, 0u, false);
+    return hipGetLastError();
+  };
+  if constexpr (K == 1 && !F32) {
+    if (!p.direct) return launch_narrow(std::false_type{}, std::false_type{});
+  } else if constexpr (K == 3 || K == 4 || (K == 2 && !F32)) {
+    if (p.direct && !p.wide) return launch_narrow(std::true_type{}, std::true_type{});
+  }
   auto launch_one = [&](auto finish, auto rows, auto direct) {
-    hipLaunchKernelGGL((mbq_encode_kernel<T, K, VEC, RAGGED, decltype(finish)::value, decltype(rows)::value, decltype(direct)::value>),
+    hipLaunchKernelGGL((mbq_encode_kernel<T, K, VEC, RAGGED, decltype(finish)::value, decltype(rows)::value, decltype(direct)::value, false>),
                        dim3(p.grid), dim3(kEncBlock), 0, s, x, payload, call, d.n, d.m, uint32_t(p.wide ? d.m / VEC : 1), p.wpg,
                        p.n_wave_items, p.wide);
   };
-  auto launch_rows = [&](auto finish, auto rows) {  // (only what direct_levels can ask for is compiled)
-    constexpr bool kNarrow = decltype(finish)::value && decltype(rows)::value != kRowsMixed && !RAGGED;
-    if constexpr (K == 1 && (sizeof(T) == 4 || decltype(rows)::value != kRowsComplete || RAGGED)) launch_one(finish, rows, std::true_type{});
-    else if constexpr (K <= 2) p.direct ? launch_one(finish, rows, std::true_type{}) : launch_one(finish, rows, std::false_type{});
-    else if constexpr (K <= 4 && kNarrow) p.direct ? launch_one(finish, rows, std::true_type{}) : launch_one(finish, rows, std::false_type{});
-    else launch_one(finish, rows, std::false_type{});
+  auto launch_rows = [&](auto finish, auto rows) {
+    constexpr bool kFinish = decltype(finish)::value, kFew = decltype(rows)::value == kRowsFew;
+    if constexpr (K == 2 && F32 && !kFinish)
+      p.direct ? launch_one(finish, rows, std::true_type{}) : launch_one(finish, rows, std::false_type{});
+    else
+      launch_one(finish, rows, std::bool_constant<K == 1 || (K == 2 && kFinish && (F32 || kFew))>{});
   };
   auto launch = [&](auto finish) {
     if (d.n < 8) launch_rows(finish, std::integral_constant<int, kRowsFew>{});

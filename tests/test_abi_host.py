@@ -1,6 +1,7 @@
 """C ABI checks that need no GPU: the library loads, exports every symbol the header
 declares, and its host-only entry points agree with the oracle and reject bad arguments."""
 import ctypes
+import itertools
 import os
 import re
 import subprocess
@@ -144,6 +145,31 @@ def test_column_pass_workspace(A, n, C, hw, rows):
     d = A.make_desc(A.UNIFORM, 4, n, C * hw, channels=C, in_dtype=A.BF16)
     up = lambda b: (b + 255) // 256 * 256
     assert A.accept_workspace_size(d) == 16384 + up(rows * C * hw * 4) + up(C * 4)
+
+
+def test_encoder_forms(A):
+    """One kernel for every way an MBQ encoder call can go, and none that no call takes.  Levels by comparison (D): k = 1; k = 2 float32,
+    and where that kernel may have 2^25 values or more through tables too, bfloat16 in few rows that finish by themselves; tensors too
+    narrow for wave-items (N) that finish by themselves up to k = 4.  Those of k = 1 bfloat16 that do not finish have tables as well.
+    A partial row group in the queue of single columns: up to k = 4."""
+    blob = open(A.binding.LIB_PATH, "rb").read()
+    name = rb"mbq_encode_kernelI(f|NS_6bf16_tE)Li(\d)ELi(\d)ELb(\d)ELb(\d)ELi(\d)ELb(\d)ELb(\d)EEE\w*\.kd"
+    got = {(t == b"f",) + tuple(int(v) for v in rest) for t, *rest in re.findall(name, blob)}
+    want = set()
+    for f32, k in itertools.product((True, False), range(1, 9)):
+        if f32 and k in (3, 4) or not f32 and k in (2, 3, 4):
+            want.add((f32, k, 1, 0, 1, 0, 1, 1))
+        if not f32 and k == 1:
+            want.add((f32, k, 1, 0, 0, 0, 0, 1))
+        for (vec, ragged), finish, rows in itertools.product(((1, 0), (4 if f32 else 8, 0), (4 if f32 else 8, 1)), (0, 1), (0, 1, 2)):
+            if k > 4 and (ragged or finish or (vec == 1 and rows == 1)):
+                continue
+            if k == 2 and f32 and not finish:
+                forms = (0, 1)
+            else:
+                forms = (int(k == 1 or k == 2 and finish == 1 and (f32 or rows == 2)),)
+            want |= {(f32, k, vec, ragged, finish, rows, direct, 0) for direct in forms}
+    assert got == want, (sorted(got - want), sorted(want - got))
 
 
 def test_no_kernel_spills_registers(A):
