@@ -1433,8 +1433,8 @@ __global__ __launch_bounds__(kEncBlock) void mbq_encode_kernel(const T* __restri
       col0 = int64_t(ipg) * VEC;
     }
     // (without the division by which single_columns finds the row group: 1 x 12000000, k = 8, with / without, us: float32 300 /
-    // 285, bfloat16 312 / 291)
-    for (int64_t j = col0 + gtid; j < m; j += stride) encode_column<T, K>(tb, x, payload, n, m, 0, j, maxcnt, st);
+    // 285, bfloat16 312 / 291; and n / 8 for 0: knowing it, the compiler puts a wait between the rows' loads)
+    for (int64_t j = col0 + gtid; j < m; j += stride) encode_column<T, K>(tb, x, payload, n, m, n / 8, j, maxcnt, st);
   } else {
     const bool stream = n_wave_items != 0u;  // else: a geometry too narrow for wave-items
     auto row_groups = [&] {
@@ -2573,9 +2573,8 @@ hipError_t launch_encode(const accept_desc& d, const MPlan& p, const T* x, uint8
   };
   auto launch = [&](auto finish) {
     if (d.n < 8) launch_rows(finish, std::integral_constant<int, kRowsFew>{});
-    else if (p.mixed) {
-      if constexpr (VEC > 1 || K <= 4) launch_rows(finish, std::integral_constant<int, kRowsMixed>{});
-    } else launch_rows(finish, std::integral_constant<int, kRowsComplete>{});
+    else if (p.mixed) launch_rows(finish, std::integral_constant<int, kRowsMixed>{});
+    else launch_rows(finish, std::integral_constant<int, kRowsComplete>{});
   };
   if constexpr (K <= 4) {
     if (p.finish) {
@@ -2803,9 +2802,8 @@ MPlan make_mplan(const accept_desc& d) {
   // groups many: which rows a wave-item has costs scalar instructions for every one of them, a few percent of
   // that short work.  In the queue / beside it, float32, us: 15 x 20001, k = 2 7.2 / 7.6, 300 x 10001, k = 3 10.8 / 10.6, 8315 x
   // 1457, k = 2 20.2 / 19.6; vectors: 15 x 390403, k = 3 13.5 / 15.2, 23 x 173913 10.9 / 14.1, 101 x 500000, k = 4 42.6 / 43.9.
-  // (More than four bits, single columns: 84 x 117318 bfloat16, k = 6 45.9 / 44.3.)
   constexpr int64_t kMixedColumnGroups = 16;
-  p.mixed = d.n % 8 != 0 && full_groups > 0 && (p.vec > 1 || (d.bits <= 4 && full_groups <= kMixedColumnGroups));
+  p.mixed = d.n % 8 != 0 && full_groups > 0 && (p.vec > 1 || full_groups <= kMixedColumnGroups);
   const int64_t wave_items = (p.mixed ? p.G : full_groups) * wpg;
   p.wide = ipg >= kWave && wave_items < (int64_t(1) << 31) && d.m * 8 < (int64_t(1) << 32);
   p.stream = full_groups > 0 && p.wide;

@@ -150,8 +150,7 @@ def test_column_pass_workspace(A, n, C, hw, rows):
 def test_encoder_forms(A):
     """One kernel for every way an MBQ encoder call can go, and none that no call takes.  Levels by comparison (D): k = 1; k = 2 float32,
     and where that kernel may have 2^25 values or more through tables too, bfloat16 in few rows that finish by themselves; tensors too
-    narrow for wave-items (N) that finish by themselves up to k = 4.  Those of k = 1 bfloat16 that do not finish have tables as well.
-    A partial row group in the queue of single columns: up to k = 4."""
+    narrow for wave-items (N) that finish by themselves up to k = 4.  Those of k = 1 bfloat16 that do not finish have tables as well."""
     blob = open(A.binding.LIB_PATH, "rb").read()
     name = rb"mbq_encode_kernelI(f|NS_6bf16_tE)Li(\d)ELi(\d)ELb(\d)ELb(\d)ELi(\d)ELb(\d)ELb(\d)EEE\w*\.kd"
     got = {(t == b"f",) + tuple(int(v) for v in rest) for t, *rest in re.findall(name, blob)}
@@ -162,7 +161,7 @@ def test_encoder_forms(A):
         if not f32 and k == 1:
             want.add((f32, k, 1, 0, 0, 0, 0, 1))
         for (vec, ragged), finish, rows in itertools.product(((1, 0), (4 if f32 else 8, 0), (4 if f32 else 8, 1)), (0, 1), (0, 1, 2)):
-            if k > 4 and (ragged or finish or (vec == 1 and rows == 1)):
+            if k > 4 and (ragged or finish):
                 continue
             if k == 2 and f32 and not finish:
                 forms = (0, 1)

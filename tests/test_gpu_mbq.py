@@ -436,7 +436,7 @@ def test_shares_of_the_work_queue(A, wave_items, bf16):
                                    (9, 20008, 6), (9, 1001, 5), (15, 20001, 8)])
 def test_partial_row_group_in_the_queue(A, n, m, k, bf16):
     """The partial row group's wave-items are the last of the work queue: one of them, fewer than wavefronts, more; rows at any
-    alignment; single columns, in the queue up to 16 complete groups (k <= 4) and beside it above.  Levels that lie close (two thresholds
+    alignment; single columns, in the queue up to 16 complete groups and beside it above.  Levels that lie close (two thresholds
     in a bucket) as well."""
     x = si.make_shape("relu_lognormal", (n, m), 9900 + n + m)
     run_case(A, x, k, n, m, in_bf16=bf16, out_bf16=bf16, tag="partial")
