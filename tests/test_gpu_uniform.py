@@ -315,9 +315,9 @@ def test_single_columns_by_rows(A, rows):
 
 
 # One range, nearest rounding, 48 (bfloat16: 72) to 256 MiB: the end of the tensor is kept on the chip between the
-# range and the quantizer.  256 workgroups, units of 16384 elements; per workgroup 6 (bfloat16: 12)
-# units in registers, 2 (4) in local memory; of float32 tensors that this does not hold 7 and 2, the rest read twice, and a
-# second kernel does the units of workgroups that gave up.
+# range and the quantizer.  256 workgroups, units of 16384 elements; per workgroup 7 (bfloat16: 14)
+# units in registers, 2 (4) in local memory; what this does not hold, from the tenth (19th) round of units on, is read twice, 2 (4) units
+# at a time and what is left over by a division in front of them.
 HELD_ROUND = 256 * 16384
 
 
@@ -328,9 +328,15 @@ HELD_ROUND = 256 * 16384
     (4, 10 * HELD_ROUND - 16384 * 7 + 33, False),    # one unit per workgroup is read twice, some have none
     (7, 7 * HELD_ROUND + 31, True),                  # bfloat16 below its own line: two reads
     (7, 9 * HELD_ROUND + 31, True),                  # the smallest in bfloat16
-    (5, 13 * HELD_ROUND + 16384 * 3 + 9, True),      # local memory comes into use
-    (6, 17 * HELD_ROUND + 16384 * 255, True),        # two read twice
-    (2, 30 * HELD_ROUND + 8192, True),               # more are read twice than there are slots
+    (7, 12 * HELD_ROUND + 16384 * 64, False),        # four are read twice
+    (5, 13 * HELD_ROUND + 16384 * 3 + 9, True),      # as many as there are slots
+    (5, 14 * HELD_ROUND + 16384 * 3 + 9, True),      # local memory comes into use
+    (6, 17 * HELD_ROUND + 16384 * 255, True),        # the largest that fits, but for a unit
+    (6, 18 * HELD_ROUND + 16384 * 255, True),        # one, two, three per workgroup are read twice
+    (3, 19 * HELD_ROUND + 16384 * 7 + 1, True),
+    (8, 20 * HELD_ROUND + 16384, True),
+    (2, 30 * HELD_ROUND + 8192, True),               # twelve
+    (4, 30 * HELD_ROUND + 16384 * 9 + 77, True),     # thirteen
 ])
 def test_held_pass(A, k, N, bf16):
     d = A.make_desc(A.UNIFORM, k, 1, N, in_dtype=A.BF16 if bf16 else A.F32)
@@ -383,13 +389,17 @@ def test_held_pass_that_gives_up(A):
 
 
 @pytest.mark.parametrize("k,N,bf16,largest_behind", [
-    (5, 9 * HELD_ROUND + 33, False, True),             # a round is read twice; float32: the second kernel has work
+    (5, 9 * HELD_ROUND + 33, False, True),             # the largest that fits
     (8, 8 * HELD_ROUND + 16384, False, False),         # one workgroup has a ninth unit
-    (6, 17 * HELD_ROUND + 16384 * 5 + 77, True, True),   # bfloat16, of which more than fits: one kernel all the same
+    (6, 17 * HELD_ROUND + 16384 * 5 + 77, True, True),   # bfloat16: some have an 18th, which fits
+    (5, 9 * HELD_ROUND + 16384 * 5 + 33, False, True),   # some have a tenth: one unit of everyone's is read twice
+    (8, 12 * HELD_ROUND + 16384 * 64 + 8193, False, False),  # four
+    (6, 18 * HELD_ROUND + 16384 * 5 + 77, True, True),   # bfloat16: one
+    (3, 20 * HELD_ROUND + 16384 * 250 + 1, True, False),  # three
 ])
 def test_held_pass_of_more_than_fits_that_gives_up(A, k, N, bf16, largest_behind):
-    """As above, for tensors of which only a part is kept: what a workgroup that gives up has not quantized is all
-    read again, of float32 by the second kernel."""
+    """As above, for tensors that fill what can be kept, or of which only a part is: a workgroup that gives up reads all of its units
+    again, those that it kept as well, by the loop that reads what was not kept."""
     torch = torch_mod()
     print("case", k, N, bf16, flush=True)
     d = A.make_desc(A.UNIFORM, k, 1, N, in_dtype=A.BF16 if bf16 else A.F32)
