@@ -169,7 +169,8 @@ def test_batch0_compress(A, k):
     bit planes of B^0 bit-exact for the GPU's own alpha^0 bits, and the decoder reads the pair
     like any other batch."""
     torch = torch_mod()
-    # in one kernel (k <= 4), then, from 32769 items of eight rows on, in a kernel for every pass: vectors and single columns
+    # in one kernel (k <= 4), then, from 32769 items of eight rows on, in a kernel for every pass: single columns, and vectors for k = 1
+    # and 6 (k = 2 to 4 of vectors: test_batch0_held)
     for shape, bf in [((16, 1000), False), ((7, 333), False), ((21, 4100), False), ((24, 2056), True), ((10, 1004), True),
                       ((64, 8192 + 4), False),
                       ((21, 43700), False), ((13, 16387), False), ((10, 131080), True), ((9, 16389), True), ((16, 65540), False)]:
@@ -204,7 +205,7 @@ def test_batch0_compress(A, k):
 @pytest.mark.parametrize("bad", ["nan", "negative nan", "inf", "-inf"])
 def test_batch0_planes_with_values_that_are_not_finite(A, k, bf16, bad):
     """b_j = +1 where rho_j >= 0, which a residue that is not a number is not, whatever its sign bit.  The last two
-    shapes take a kernel for every pass."""
+    shapes take a kernel for every pass (the last one for k = 2 and 4 is kept in registers: test_batch0_held_values_that_are_not_finite goes beyond)."""
     torch = torch_mod()
     for n, m in ((16, 1000), (7, 333), (9, 16389), (13, 131200)):
         x = si.make_shape("student_t3", (n, m), 7700 + k)
@@ -445,7 +446,7 @@ def test_partial_row_group_in_the_queue(A, n, m, k, bf16):
                  np.array([1.0, 0.03, 0.02], np.float32), tag="partial, two thresholds")
 
 
-# Batch 0 with the tensor in the registers of 256 workgroups: up to one, two, four items per thread.
+# Batch 0 with the tensor in the registers of 256 workgroups: up to one, two, four items per thread; beyond, a kernel for every pass.
 @pytest.mark.parametrize("n,m,k,bf16", [
     (8, 4 * 131072, 2, False),       # one item per thread, all of them
     (8, 4 * 131073, 3, False),       # one item more: a chunk of one
@@ -455,6 +456,9 @@ def test_partial_row_group_in_the_queue(A, n, m, k, bf16):
     (9, 8 * 196608, 3, True),        # four items in some wavefronts
     (8, 4 * 524288, 3, False),       # the largest
     (8, 4 * 524289, 2, False),       # one item more: a kernel for every pass
+    (9, 4 * 262147, 3, False), (15, 4 * 262145, 4, False),         # the same, with a partial row group
+    (9, 8 * 262147, 2, True), (15, 8 * 262145, 3, True), (12, 8 * 262145, 4, True),
+    (300005, 4, 2, False), (300003, 8, 3, True), (70001, 12, 4, False), (52003, 40, 4, True),  # a wavefront's items in many row groups
     (2, 4 * 262144, 3, False), (2, 4 * 262145, 3, False), (3, 4 * 524288, 2, False),                      # few rows: both sides
     (1, 8 * 196608, 2, True), (7, 8 * 196609, 3, True),                                                   # of the lines
     (5, 8 * 65536, 4, True), (5, 8 * 65537, 4, True), (6, 8 * 81920, 2, True), (7, 8 * 81921, 3, True),
@@ -496,9 +500,11 @@ def test_batch0_held(A, n, m, k, bf16):
 
 @pytest.mark.parametrize("bf16", [False, True])
 @pytest.mark.parametrize("bad", [np.nan, -np.nan, np.inf, -np.inf])
-def test_batch0_held_values_that_are_not_finite(A, bad, bf16):
+@pytest.mark.parametrize("n,m", [(13, 8 * 20001), (9, 8 * 262147)])
+def test_batch0_held_values_that_are_not_finite(A, n, m, bad, bf16):
+    """Kept in registers; in a kernel for every pass.  A partial row group both times."""
     torch = torch_mod()
-    n, m, k = 13, 8 * 20001, 3
+    k = 3
     x = si.make_shape("student_t3", (n, m), 970)
     x.reshape(-1)[::53001] = bad
     x.reshape(-1)[::61] = 0.0
