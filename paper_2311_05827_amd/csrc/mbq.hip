@@ -2486,30 +2486,35 @@ __global__ __launch_bounds__(kFinalizeBlock) void mbq_init_finalize_kernel(const
 // Elements per vector: 16 bytes' worth; for the widths in use (k <= 4) at any alignment, where rows
 // are long enough for wave-items and the tensor is large enough (ragged_columns).
 //
-// How large, in columns of all row groups: the columns that no vector covers, and in the encoder the partial
-// row group, take trips to memory of their own, where single columns all go at once; narrow rows have
-// more such columns, and the ends of their rows are written in parts.  Measured at 16 K to 54 M values, 4
-// to 101148 rows (us, single columns / vectors):
+// How large, in columns of all row groups: the columns that no vector covers take trips to memory of their own, where
+// single columns all go at once; narrow rows have more such columns, and the ends of their rows are written in parts.
+// Measured at 16 K to 54 M values, 4 to 101148 rows (us, single columns / vectors; encoder: k = 2; 3; 4):
 //   decoder: 23 x 86957 4.4 / 4.8, 64 x 62501 6.2 / 5.4, 15 x 390403 9.0 / 7.2; float32 rows below 2048:
 //     8315 x 1457 11.7 / 12.7, 10403 x 769 8.5 / 9.0, 16691 x 1519 21.2 / 20.0, 101148 x 535 42 / 40;
-//   encoder, complete row groups only: 64 x 7813 9.2 / 9.1, 64 x 15625 9.4 / 9.3, 64 x 23437 12.1 / 10.6
-//     (k = 1, bfloat16: 64 x 17501 7.6 / 8.5, 64 x 37501 8.8 / 8.8, 64 x 50001 9.5 / 8.7);
-//   encoder, complete and partial: 23 x 65217 12.9 / 14.0, 300 x 10001 14.8 / 14.2, 23 x 173913 14.1 / 13.0;
-//     float32 rows below 4096, k = 2: 2614 x 1921 13.1 / 14.2, 17950 x 509 16.3 / 17.4, 8315 x 1457
-//     19.6 / 19.2, 13113 x 1309 24.5 / 20.2;
-//   encoder, partial only: 4 x 4001 9.4 / 9.1, 4 x 1000001 18.7 / 12.3;
-//   encoder, float32 rows that leave a quarter or more of their wave-items' lanes idle: 55297 x 297
-//     28.5 / 30.9, 19311 x 349 15.3 / 15.9.
+//   encoder, float32: 64 x 23437 6.8 / 6.9; 8.4 / 8.7; 9.6 / 10.1, 15 x 130003 7.4 / 7.15; 9.2 / 9.5; 10.0 / 10.35, 504 x 5003 7.3 / 7.3; 8.9 /
+//     9.6; 10.1 / 10.6, 15 x 196613 8.5 / 7.8; 10.3 / 9.4; 11.1 / 10.5, 64 x 50001 8.0 / 7.9; 9.5 / 9.1; 10.8 / 10.2, 101 x 60001 11.3 / 9.8;
+//     12.9 / 11.3; 13.9 / 12.2; rows below 4096 and a partial row group: 2614 x 1921 10.0 / 11.6; 11.5 / 13.6; 12.7 / 14.6, 8315 x 1457
+//     18.2 / 19.4; 19.8 / 21.9; 21.1 / 23.1, 13113 x 1309 22.9 / 21.5; 24.5 / 23.5; 25.4 / 24.3, without one: 2000 x 3001 10.7 / 10.4;
+//     12.3 / 12.2; 13.5 / 13.5; rows that leave a quarter or more of their wave-items' lanes idle: 55297 x 297 22.8 / 26.1; 24.4 / 29.5;
+//     25.6 / 31.3, 19311 x 349 12.0 / 13.7; 13.5 / 16.6; 14.8 / 18.2;
+//   encoder, bfloat16: 64 x 15625 7.25 / 7.95; 7.95 / 8.8; 8.9 / 9.8, 64 x 23437 8.1 / 8.0; 9.0 / 8.9; 9.75 / 10.0, 504 x 5003 8.8 / 8.4; 9.6 / 9.4; 10.2 /
+//     10.5; with a partial row group 23 x 86957 8.4 / 8.4; 9.4 / 9.2; 10.05 / 10.4, 23 x 131073 9.7 / 8.9; 10.5 / 9.8; 10.9 / 11.1, 101 x
+//     60001 12.6 / 9.3; 13.6 / 10.4; 13.8 / 11.5, 6001 x 1921 19.6 / 13.1; 20.5 / 14.3; 18.2 / 15.6; k = 1: 64 x 23437 6.9 / 6.9, 23 x 131073
+//     7.9 / 7.9, 64 x 50001 8.1 / 7.85;
+//   encoder, fewer than eight rows: float32 4 x 4001 4.65 / 5.4; 6.1 / 7.6; 6.9 / 8.5, 4 x 16383 5.0 / 5.4; 6.45 / 7.4; 7.3 / 8.5, and where
+//     single columns are too many to finish by themselves 4 x 16387 5.3 / 5.2; 6.8 / 7.6; 7.9 / 8.5, 2 x 30001 5.4 / 4.95; 6.8 / 7.1; 7.9 /
+//     8.2, 4 x 400001 7.3 / 6.5; 8.5 / 8.2; 9.6 / 9.2; bfloat16 4 x 4001 4.75 / 6.1; 6.2 / 6.9; 7.1 / 8.0, 4 x 16383 5.1 / 6.0; 6.6 / 7.0; 7.3 /
+//     8.0, 2 x 30001 6.1 / 5.5; 6.8 / 6.65; 7.9 / 7.6, 4 x 400001 7.8 / 7.2; 8.6 / 7.7; 9.6 / 9.0.
 int64_t ragged_columns(int dtype, int64_t n, int64_t m, int bits, bool encode) {
   const bool f32 = dtype == ACCEPT_F32;
   if (!encode) return f32 && m < 2048 ? int64_t(1) << 21 : int64_t(3) << 17;
-  if (n < 8) return 0;
+  if (n < 8) return int64_t(kFinishGridMax) * 4 * kWave;  // (see tail_blocks in make_mplan)
   if (f32) {
     const int64_t ipg = m / Elem<float>::VEC, lanes = (ipg + kWave - 1) / kWave * kWave;
     if (4 * ipg < 3 * lanes) return INT64_MAX;
+    return m < 4096 && n % 8 != 0 ? int64_t(3) << 19 : int64_t(3) << 17;
   }
-  if (n % 8 == 0 && bits > 1) return int64_t(1) << 17;
-  return f32 && m < 4096 ? int64_t(3) << 19 : int64_t(3) << 17;
+  return n % 8 == 0 && bits > 1 ? int64_t(1) << 17 : int64_t(3) << 17;
 }
 int vec_for(int dtype, int64_t n, int64_t m, int bits, bool encode) {
   const int v = dtype == ACCEPT_BF16 ? 8 : 4;

@@ -289,8 +289,8 @@ def test_header_of_values_that_differ_much(A, k, kind, bf16):
 @pytest.mark.parametrize("n", [1, 7, 8, 9, 23])
 def test_rows_at_any_alignment(A, n, bf16):
     """Rows that are not whole 16-byte vectors, from the narrowest that can go in vectors (64 of them) on,
-    and just below it; complete and partial row groups.  With fewer than 8 rows the encoder takes
-    vectors at any alignment here; the sizes from which it does with more stand in the next test."""
+    and just below it; complete and partial row groups.  The sizes from which the encoder takes vectors at any
+    alignment stand in the next test."""
     vec = 8 if bf16 else 4
     for i, m in enumerate([64 * vec - 1, 64 * vec, 64 * vec + 1, 65 * vec - 1, 1024 + 3, 128 * vec + 2, 40 * 64 * vec + vec - 1]):
         k = 1 + (i + n) % 4
@@ -312,11 +312,11 @@ def test_rows_at_any_alignment(A, n, bf16):
 
 @pytest.mark.parametrize("bf16", [False, True])
 @pytest.mark.parametrize("n,m", [(16, 65535), (16, 65539), (8 * 511, 257 + 256), (9, 196607), (9, 196613), (8 * 768 + 5, 513),
-                                 (8 * 255 + 5, 4103), (8 * 256 + 5, 4103), (8 * 4100 + 3, 513)])
+                                 (8 * 255 + 5, 4103), (8 * 256 + 5, 4103), (8 * 4100 + 3, 513),
+                                 (16, 196607), (16, 196613), (4, 16383), (4, 16387), (7, 16391), (1, 131075)])
 def test_rows_at_any_alignment_large(A, n, m, bf16):
-    """Both sides of the sizes from which complete row groups of such rows go in vectors: in columns of all
-    row groups 131072 without a partial group, 393216 with one and in the decoder, more for narrow rows of
-    float32."""
+    """Both sides of the sizes from which such rows go in vectors: in columns of all row groups 393216 (bfloat16 without a
+    partial group 131072, fewer than eight rows 16384 in the encoder), more for narrow rows of float32."""
     torch = torch_mod()
     x = si.make_shape("student_t3", (n, m), 7600 + n % 100)
     run_case(A, x, 3, n, m, t=2, in_bf16=bf16, out_bf16=bf16, tag="ragged large")
