@@ -811,7 +811,8 @@ __device__ __forceinline__ void encode_column(const Tables& tb, const T* __restr
 // 8.3 / 11.9).  So too for wave-items of one and an eighth to one and seven eighths times the wavefronts: nobody has more than two
 // then, however they are shared out, and rows of any alignment pay for neighbours on other compute units (64 / 4 slots, six
 // placements of the buffers each: 8000 x 1457 bfloat16, k = 2 12.5 / 13.6, k = 4 15.1 / 18.2, 3464 x 1457 float32, k = 4 14.4 / 16.8, 600 x
-// 20001 bfloat16, k = 3 12.7 / 13.1, 15 x 390403 float32 11.2 / 11.7; aligned rows 40 x 400000 bfloat16, k = 4 13.7 / 13.8).
+// 20001 bfloat16, k = 3 12.7 / 13.1, 15 x 390403 float32 11.2 / 11.7; aligned rows 40 x 400000 bfloat16, k = 4 13.7 / 13.8; but single columns,
+// whose wave-items are short, 16 x 100003 float32, k = 1 6.3 / 6.0, 800 x 2051 6.4 / 6.1).
 struct WorkQueue {
   uint32_t* counter;  // the group's counter: zero when the kernel starts, put back by the finalize kernel or the last workgroup
   uint32_t shift;     // slots = 1 << shift
@@ -1365,7 +1366,7 @@ __global__ __launch_bounds__(kEncBlock) void mbq_encode_kernel(const T* __restri
   q.counter = call.counters + group * uint32_t(kCounterStride);
   constexpr uint32_t kWavefronts = uint32_t(kEncodeGridMax) * uint32_t(kEncWaves);
   const bool two_sweeps = n_wave_items > kWavefronts / 8u * 9u && n_wave_items <= kWavefronts / 8u * 15u;
-  q.shift = gridDim.x == uint32_t(kEncodeGridMax) && !two_sweeps ? kGroupSlotsShift : kWaveSlotsShift;
+  q.shift = gridDim.x == uint32_t(kEncodeGridMax) && !(VEC > 1 && two_sweeps) ? kGroupSlotsShift : kWaveSlotsShift;
   const uint32_t slots = 1u << q.shift;
   q.first = group << q.shift;
   q.sweep = groups << q.shift;
