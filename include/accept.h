@@ -196,8 +196,9 @@ accept_status accept_mbq_init(const accept_desc* desc, const void* x_dev, float*
  * sign(rho_j), layout as accept_compress) and header = [alpha^0, m_q] with m_q =
  * mean(B^0 alpha^0 - x) (eq. (biased error)); accept_decompress reads them like any other
  * batch, and header[0..k) is alpha_prev of batch 1.  k passes over x (alpha_j needs the whole
- * tensor's |rho_j|); the last one also writes the planes.  Small tensors: one kernel, which reads x once and passes
- * over it in registers.  MBQ descriptors with
+ * tensor's |rho_j|); the last one also writes the planes.  Tensors that fit in registers are read once and passed
+ * over there: up to 4 bits and 32768 items (8 rows of a 16-byte vector, or of one column) in one kernel; of 2 to 4 bits and rows of whole
+ * vectors up to 524288 items (16.8 M float32, 33.5 M bfloat16 values; fewer where n < 8) in two.  MBQ descriptors with
  * ACCEPT_LAYOUT_PACKED only; desc->t is ignored; buffers and workspace as for accept_compress.
  */
 accept_status accept_mbq_compress_first(const accept_desc* desc, const void* x_dev, void* header_dev,
