@@ -133,6 +133,7 @@ struct MPlan {
   bool mixed;             // the stream's last row group is a partial one
   uint32_t wpg;           // wave-items (64 items) per row group
   uint32_t n_wave_items;  // of the stream
+  uint8_t queue_shift;    // a group of workgroups takes 1 << queue_shift of them out of a sweep
   int grid;               // workgroups of the encode kernel = number of partial-sum records
   bool direct;            // levels are found by comparisons, not through tables
   bool finish;            // the encode kernel also does the finalize kernel's work

@@ -26,7 +26,7 @@ constexpr int kEncWaves = kEncBlock / kWave;
 // 8i .. 8i+7 (under round-robin dispatch one on each of the chip's eight dies) share counter i.
 constexpr int kGroupBlocks = 8;
 // Wave-items a group takes out of every sweep over the tensor (as a shift; the rule is at WorkQueue).
-constexpr uint32_t kGroupSlotsShift = 2, kWaveSlotsShift = 6;
+constexpr uint8_t kGroupSlotsShift = 2, kWaveSlotsShift = 6;
 constexpr int kCounterStride = 64;  // uint32 words between two counters (256 bytes: their own cache lines)
 constexpr int kEncodeGridMax = 256;
 constexpr int kPlainGridMax = 768;
@@ -1336,7 +1336,8 @@ enum Rows { kRowsComplete, kRowsMixed, kRowsFew };
 template <typename T, int K, int VEC, bool RAGGED, bool FINISH, int ROWS, bool DIRECT, bool NARROW>
 __global__ __launch_bounds__(kEncBlock) void mbq_encode_kernel(const T* __restrict__ x, uint8_t* __restrict__ payload,
                                                                MbqCall call, int64_t n, int64_t m, uint32_t ipg,
-                                                               uint32_t wpg, uint32_t n_wave_items, bool wide) {
+                                                               uint32_t wpg, uint32_t n_wave_items, bool wide,
+                                                               uint8_t queue_shift) {
   constexpr int NPAIR = K * (K - 1) / 2;
   constexpr bool BY_VALUE = sizeof(T) == 2 && K <= 4 && !DIRECT;
   constexpr bool FEW = ROWS == kRowsFew, MIXED = ROWS == kRowsMixed;
@@ -1364,9 +1365,7 @@ __global__ __launch_bounds__(kEncBlock) void mbq_encode_kernel(const T* __restri
                                                                         : uint32_t(kGroupBlocks);
   const uint32_t group_waves = group_blocks * uint32_t(kEncWaves);
   q.counter = call.counters + group * uint32_t(kCounterStride);
-  constexpr uint32_t kWavefronts = uint32_t(kEncodeGridMax) * uint32_t(kEncWaves);
-  const bool two_sweeps = n_wave_items > kWavefronts / 8u * 9u && n_wave_items <= kWavefronts / 8u * 15u;
-  q.shift = gridDim.x == uint32_t(kEncodeGridMax) && !(VEC > 1 && two_sweeps) ? kGroupSlotsShift : kWaveSlotsShift;
+  q.shift = queue_shift;
   const uint32_t slots = 1u << q.shift;
   q.first = group << q.shift;
   q.sweep = groups << q.shift;
@@ -2561,7 +2560,7 @@ hipError_t launch_encode(const accept_desc& d, const MPlan& p, const T* x, uint8
   constexpr bool F32 = sizeof(T) == 4;
   auto launch_narrow = [&](auto finish, auto direct) {
     hipLaunchKernelGGL((mbq_encode_kernel<T, K, 1, false, decltype(finish)::value, kRowsComplete, decltype(direct)::value, true>), dim3(p.grid),
-                       dim3(kEncBlock), 0, s, x, payload, call, d.n, d.m, 1u, 1u, 0u, false);
+                       dim3(kEncBlock), 0, s, x, payload, call, d.n, d.m, 1u, 1u, 0u, false, uint8_t(0));
     return hipGetLastError();
   };
   if constexpr (K == 1 && !F32) {
@@ -2572,7 +2571,7 @@ hipError_t launch_encode(const accept_desc& d, const MPlan& p, const T* x, uint8
   auto launch_one = [&](auto finish, auto rows, auto direct) {
     hipLaunchKernelGGL((mbq_encode_kernel<T, K, VEC, RAGGED, decltype(finish)::value, decltype(rows)::value, decltype(direct)::value, false>),
                        dim3(p.grid), dim3(kEncBlock), 0, s, x, payload, call, d.n, d.m, uint32_t(p.wide ? d.m / VEC : 1), p.wpg,
-                       p.n_wave_items, p.wide);
+                       p.n_wave_items, p.wide, p.queue_shift);
   };
   auto launch_rows = [&](auto finish, auto rows) {
     constexpr bool kFinish = decltype(finish)::value, kFew = decltype(rows)::value == kRowsFew;
@@ -2838,6 +2837,11 @@ MPlan make_mplan(const accept_desc& d) {
     if (blocks < 1) blocks = 1;
     p.grid = int(blocks < kEncodeGridMax ? blocks : kEncodeGridMax);
   }
+  // (see WorkQueue; in the kernel, which has this call's numbers later than its address, the coefficients' load waited for them:
+  // 8 x 13488 bfloat16, k = 3 8.3 us, so 8.1)
+  constexpr uint32_t kWavefronts = uint32_t(kEncodeGridMax) * uint32_t(kEncWaves);
+  const bool two_sweeps = p.vec > 1 && p.n_wave_items > kWavefronts / 8u * 9u && p.n_wave_items <= kWavefronts / 8u * 15u;
+  p.queue_shift = p.grid == kEncodeGridMax && !two_sweeps ? kGroupSlotsShift : kWaveSlotsShift;
   p.finish = d.layout == ACCEPT_LAYOUT_PACKED && d.bits <= 4 && p.grid <= kFinishGridMax;
   p.direct = direct_levels(d, p);
   // control block, then room for kMaxRecords records of the widest kind (k = 8)
