@@ -1434,7 +1434,7 @@ __global__ __launch_bounds__(kEncBlock) void mbq_encode_kernel(const T* __restri
     }
     if constexpr (DIRECT || BY_VALUE) {  // a few columns, or a narrow tensor
       single_columns(1, col0, m - col0);
-    } else {
+    } else if (col0 < m) {  // (in front of what the loop needs: 4 x 2000 float32, k = 4 7.83 / 7.74 us)
       // (Perhaps all, so without the division by which single_columns finds the row group: 1 x 12000000, k = 8, with / without, us:
       // float32 300 / 285, bfloat16 312 / 291; and n / 8 for 0: knowing it, the compiler puts a wait between the rows' loads.)
       for (int64_t j = col0 + gtid; j < m; j += stride) encode_column<T, K>(tb, x, payload, n, m, n / 8, j, maxcnt, st);
