@@ -3,8 +3,8 @@
 // type or size, a tensor without storage) returns kNotHere before anything was done: binding.py then takes it,
 // and says what is wrong.
 //
-// A small tensor's call is host time, nearly all of it the launch: compressing 3.2 us, decompressing 3.1, of which 0.1 are the
-// wrapper's in binding.py.
+// A small tensor's call is host time, nearly all of it the launches, about 3 us each: compressing in one kernel 3.2 us where the host
+// is fast, of which 0.1 are the wrapper's in binding.py, and 5.1 where it is slow, in two there 7.7.
 #define PY_SSIZE_T_CLEAN
 #include <Python.h>
 

@@ -86,7 +86,7 @@ hipError_t launch_whole(const accept_desc& d, const UPlan& p, const T* x, float*
                         int polls, hipStream_t s);
 
 // Groups of a workgroup of quantize_whole_kernel; 0: the tensor does not take it.  Range and quantize kernels / this
-// (us on the device, replayed graphs; a launch less is 3.6 us of host time on top):
+// (us on the device, replayed graphs; a launch less is about 3 us of host time on top):
 //   nearest, float32: 5 K 5.3 / 3.4, 16 K 4.6 / 2.8, 100 K 5.8 / 4.3, 262144 5.0 / 4.3, 0.5 M 5.1 / 4.8, 1.05 M 5.1 / 5.2, 2.1 M
 //     5.3 / 5.6, 2.5 M 6.9 / 6.1, 4.2 M 8.2 / 7.1, 8.3 M 11.8 / 10.6, 12 M 16.3 / 13.7; bfloat16: 0.5 M 4.9 / 4.6, 2.1 M 5.2 /
 //     5.0, 8.3 M 9.5 / 8.1, 25 M 21.8 / 18.9;

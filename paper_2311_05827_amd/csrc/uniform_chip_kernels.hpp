@@ -166,10 +166,11 @@ __device__ __forceinline__ void quantize_behind(const T* __restrict__ x, uint32_
 //
 // Beside other work: a workgroup needs a whole compute unit (160 KiB of local memory, all registers), so
 // next to a kernel whose workgroups keep filling the chip it starts late, and the early ones give up.
-// Time of a call on one stream while another is busy, k = 8, two reads / held, held with a second kernel always /
-// now (us): small elementwise kernels, 103 MB float32 43 / 32, 28.6 / 22.2, 205 MB 85 / 70, 56 / 49, 103 MB bfloat16 53 /
-// 39, 33.6 / 26.2; matrix products beside 205 MB 184 / 179, 240 / 150, beside 103 MB bfloat16 160 / 155, 228 / 128;
-// copies of 512 MB without a pause 66 / 98, 105 / 86, 130 / 161, 162 / 160, 72 / 145, 142 / 140.
+// Time of a call on one stream while another is busy, k = 8, two reads / this (us; calls one behind the other, all measured in
+// turn): float32 103, 154, 205 MB, bfloat16 103, 205 MB beside small elementwise kernels 41 / 26, 59 / 39, 78 / 55, 45 / 31,
+// 87 / 61; beside matrix products 219 / 123, 228 / 134, - / 150, 233 / 127, 250 / 156; beside copies of 512 MB without a pause
+// 73 / 97, 103 / 136, 133 / 192, 78 / 120, 148 / 221, which is lost.  The second kernel for late workgroups, which float32 had
+// above 134 MB, was better beside copies and worse beside matrix products: 154 MB 106 and 239, 205 MB 130 and 270.
 //
 // 51.4 M float32 values (205 MB), k = 8: 54.1 us a call (two reads 69.5): 31 us to the mailboxes, 2 to 3 for the
 // exchange.  103 MB: 32 -> 26 us against the held pass with a second kernel and plain stores, bfloat16 103 MB 36 -> 30.
