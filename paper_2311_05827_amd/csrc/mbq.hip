@@ -894,7 +894,8 @@ __device__ __forceinline__ void encode_partial_rows(const Tables& tb, RawRow<VEC
 // the loads are unconditional.  (The partial group used to go in front of the stream or behind it, a wave-item at a time and with
 // nothing in flight meanwhile, on workgroups that had their share of the others as well.  Whole call, beside / in the queue, us:
 // 15 x 390403, k = 3, float32 15.1 / 13.1, bfloat16 15.0 / 12.0; 23 x 173913 13.9 / 10.8, k = 4 15.8 / 12.8; 15 x 20000, k = 2
-// 9.1 / 7.7; 125 x 400000, k = 4 43.6 / 42.3, 29.4 / 29.2.)
+// 9.1 / 7.7; 125 x 400000, k = 4 43.6 / 42.3, 29.4 / 29.2; 101 x 500000 bfloat16, k = 4 was 1 % slower by it, which shares of
+// four wave-items (see WorkQueue) took back: 30.1 before both, 29.6 with both.)
 template <typename T, int K, int VEC, bool RAGGED, int MC, bool MIXED, typename Tables>
 __device__ __forceinline__ void encode_stream(const Tables& tb, const T* __restrict__ x,
                                               uint8_t* __restrict__ payload, uint64_t m, uint32_t ipg, uint32_t wpg,
@@ -1256,7 +1257,7 @@ __global__ __launch_bounds__(finalize_block(K)) void mbq_finalize_kernel(MbqCall
 
 // The same at the end of an encode kernel of few workgroups: each counts itself off when its record is written, and
 // the last one adds them up, in the finalize kernel's order, and solves.  No one waits for another.
-// A launch less is 3.6 us of host time; on the device, encode and finalize kernels / this (us, replayed graphs, float32,
+// A launch less is about 3 us of host time; on the device, encode and finalize kernels / this (us, replayed graphs, float32,
 // k = 2; 4): 16 x 2048 7.1 / 6.8; 9.9 / 10.0; 64 x 8448 (33 workgroups) 7.3 / 7.1; 10.2 / 10.4; 64 x 16384 (64) 7.5 / 7.4;
 // 10.3 / 10.6; beyond the line, where the counter, one address, takes 12 ns each: 64 x 16640 (65) 7.6 / 7.5; 10.3 / 10.7, 64 x
 // 20480 (80) 7.6 / 7.7; 10.3 / 10.9, 64 x 32768 (128) 7.9 / 8.3; 10.6 / 11.4, 64 x 50000 (196) 8.8 / 9.7; 11.2 / 12.6.
@@ -1969,7 +1970,7 @@ __global__ __launch_bounds__(kBlock) void mbq_init_encode_kernel(const T* __rest
 // A mailbox is two words, each with half of the float64 and the number of the exchange.  Every exchange of a call (k - 1,
 // at most three) has a set of its own: a workgroup may be late for one that all others have left.
 //
-// What it saves is host time, 3.6 us a launch; on the device it takes, k + 1 kernels / this (us, float32): 128 x 160, k = 2
+// What it saves is host time, about 3 us a launch; on the device it takes, k + 1 kernels / this (us, float32): 128 x 160, k = 2
 // 8.4 / 6.6; 64 x 6144 k = 4 15.9 / 14.2; 64 x 16384 (64 workgroups) 9.4 / 9.2,
 // 16.6 / 15.1; beyond the line mbq_first_held_kernel follows.
 constexpr int kFirstBlock = 512, kFirstWaves = kFirstBlock / kWave;
@@ -2256,8 +2257,8 @@ __global__ __launch_bounds__(kFirstBlock, 2) void mbq_first_kernel(const T* __re
 // k kernels and their reads / this (whole call, us): 32 x 401408, k = 2, 3, 4 27.7 / 19.0, 39.2 / 25.0, 50.6 / 31.6, bfloat16 21.3 / 17.8,
 // 30.8 / 25.7, 40.8 / 34.0; 64 x 40000, k = 3 17.6 / 12.1; 64 x 20480, k = 2 10.1 / 7.9; 3 x 800008 bfloat16 and the like as well.
 // Of the 25 us at k = 3 the read takes 10 with the launch, an exchange about 2, a pass of float64 instructions 2 to 4.5 at two
-// wavefronts per SIMD, the header's kernel 4.  Beside other work on another stream, kernels / this (us a call, 32 x 401408, k = 3):
-// matrix products 294 / 135, small kernels 35 / 23, 512 MB copies without a pause 36 / 42.
+// wavefronts per SIMD, the header's kernel 4.  Beside other work on another stream, kernels / this (us, 32 x 401408, k = 3, calls
+// one behind the other): matrix products 326 / 160, small kernels 47 / 30, 512 MB copies without a pause 80 / 47.
 template <typename T, int K, int SLOTS>
 __global__ __launch_bounds__(kFirstBlock, 2) void mbq_first_held_kernel(const T* __restrict__ x, float* __restrict__ header,
                                                                         uint8_t* __restrict__ payload, uint32_t* ctrl,
