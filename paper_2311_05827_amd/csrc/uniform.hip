@@ -641,10 +641,11 @@ __global__ __launch_bounds__(kBlock) void quantize_pack_kernel(
       for (int h = 0; h < QPV; ++h)
         pieces[buf][(u * kBlock + tid) * QPV + h] = quantize4<K, STOCH>(&f[4 * h], &r[4 * h], z + uint64_t(4 * h) * kRandStep);
       z += uint64_t(kBlock * VEC) * kRandStep;
-      // Interleaved, the vectors' chains take 119 registers, one after the other 73.  Not so with ranges of channels, whose reads the
+      // Interleaved, the vectors' chains take 119 registers, one after the other 73.  Not so with ranges of segments, whose reads the
       // scheduler then cannot move: free / barrier, us: 9463 x 4 x 1024 float32, k = 8 96.8 / 103, 2 x 2 x 4000000 k = 4
-      // 37.2 / 38.8, 15959 x 176 x 7 44.0 / 45.6.
-      if constexpr (STOCH && MODE == kOneRange) __builtin_amdgcn_sched_barrier(0);
+      // 37.2 / 38.8, 15959 x 176 x 7 44.0 / 45.6; channels-last, whose ranges are vectors, is even: 16667 x 56 float32, k = 3 13.0 / 12.9, 25088 x 256
+      // k = 4 19.5 / 19.3, 100000 x 128 k = 5 31.2 / 31.5.
+      if constexpr (STOCH && (MODE == kOneRange || MODE == kRangePerElement)) __builtin_amdgcn_sched_barrier(0);
     }
     if (next_f < full_tiles) ask_for_tile(tile_of(next_f));
     if (MODE == kRangePerVectorLocal && next_f < full_tiles)
