@@ -601,7 +601,7 @@ __global__ __launch_bounds__(kBlock) void quantize_pack_kernel(
     __syncthreads();
   }
 
-  // Stochastic rounding is bound by its vector instructions (25 per element, 16 of them the random
+  // Stochastic rounding is bound by its vector instructions (26 per element, 16 of them the random
   // number; every 64-bit or multiply instruction costs about 4.3 cycles like any other on this
   // chip, so the count is what matters): states step by constants from one per thread, and the
   // number is formed on 32-bit halves.  51.4 M float32 values at k = 4: call 80.5 -> 73.2 us
