@@ -87,6 +87,12 @@ PyObject* compress(PyObject*, PyObject* const* args, Py_ssize_t nargs) {
   }
 }
 
+// Other Python threads run on while this lives.
+struct Unlocked {
+  PyThreadState* state = PyEval_SaveThread();
+  ~Unlocked() { PyEval_RestoreThread(state); }
+};
+
 // decompress(desc, header, payload, out or None) -> status, or where there was no `out` the tensor made for it, or kNotHere
 PyObject* decompress(PyObject*, PyObject* const* args, Py_ssize_t nargs) {
   if (nargs != 4) return PyLong_FromLong(kNotHere);
@@ -103,6 +109,7 @@ PyObject* decompress(PyObject*, PyObject* const* args, Py_ssize_t nargs) {
       return PyLong_FromLong(kNotHere);
     at::Tensor made;
     if (make) {
+      const Unlocked unlocked;  // as in torch.empty: memory that has to be made or freed first waits for the device, and with it for what other threads do for it
       made = at::empty({d->n * d->m}, payload->options().dtype(d->out_dtype == ACCEPT_BF16 ? at::kBFloat16 : at::kFloat));
       out = &made;
     }
